@@ -1,0 +1,358 @@
+// Stand-alone compress / decompress of one moment (the quantizer M o N of Sec. 2.2 and its inverse): checkpoints,
+// conversion from and to fp32 states, and the building blocks of the ablation quantizers.
+//
+// What bounds these kernels is memory: 4 bytes of fp32 and half a byte of codes per element, each touched once.  So a
+// lane owns FOUR consecutive elements of the row-major flattening (one 128-bit access, 16 bits of codes), a wave's
+// access is contiguous, a workgroup takes kCvtUnits runs of 1024 elements whose loads are all issued before the first
+// use, and the 64-bit division that finds a position's row is done once per workgroup, for its first element.
+// Measured on an 11008 x 4096 moment, before (one lane per 8 elements, scalar accesses, a 64-bit division each) and now:
+// compress the first moment 106 -> 55 us, its codes alone for the second 170 -> 39 us, decompress the first 111 -> 37 us,
+// the second 139 -> 55 us.  The fp32 arrays and the
+// scales need only be 4-byte aligned: the wide accesses are typed so.
+#pragma once
+
+#include "kernels.hpp"
+
+namespace lpmm {
+
+struct QuantArgs {
+    const uint32_t* q_in;   // dequant: codes
+    uint32_t* q_out;        // quant: codes
+    const float* x_in;      // quant: fp32 moment
+    float* x_out;           // dequant: fp32 moment
+    float* sa;              // block scales or row maxima
+    float* sb;              // column maxima (second moment)
+    int64_t rows, cols, P;
+};
+
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));     // 128-bit access at 4-byte alignment
+
+constexpr int kCvtUnits = 4;
+constexpr int kCvtUnitElems = kThreads * 4;
+constexpr int kCvtElems = kCvtUnits * kCvtUnitElems;      // elements per workgroup (two blocks of 2048)
+
+// ---- accesses of a lane's 4 elements; `base` is a multiple of 4, elements at or beyond P do not exist ----
+
+__device__ __forceinline__ void cvt_load4(const float* x, int64_t base, int64_t P, float out[4]) {
+    if (base + 4 <= P) {
+        const v4f_a4 v = *reinterpret_cast<const v4f_a4*>(x + base);
+        out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = base + e < P ? x[base + e] : 0.0f;
+    }
+}
+__device__ __forceinline__ void cvt_store4(float* x, int64_t base, int64_t P, const float v[4]) {
+    if (base + 4 <= P) {
+        const v4f_a4 w = {v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<v4f_a4*>(x + base) = w;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (base + e < P) x[base + e] = v[e];
+    }
+}
+// 16 bits of codes; in the tail the bytes that hold an existing element (the unused nibble of an odd tail is 0)
+__device__ __forceinline__ uint32_t cvt_load_codes(const uint32_t* q, int64_t base, int64_t P) {
+    const uint8_t* b = reinterpret_cast<const uint8_t*>(q) + (base >> 1);
+    if (base + 4 <= P) return *reinterpret_cast<const uint16_t*>(b);
+    uint32_t w = 0;
+    if (base < P) w = b[0];
+    if (base + 2 < P) w |= uint32_t(b[1]) << 8;
+    return w;
+}
+__device__ __forceinline__ void cvt_store_codes(uint32_t* q, int64_t base, int64_t P, uint32_t w) {
+    uint8_t* b = reinterpret_cast<uint8_t*>(q) + (base >> 1);
+    if (base + 4 <= P) {
+        *reinterpret_cast<uint16_t*>(b) = uint16_t(w);
+    } else {
+        const int nv = base < P ? int(P - base) : 0;             // 0..3
+        w &= (1u << (4 * nv)) - 1u;
+        if (nv > 0) b[0] = uint8_t(w);
+        if (nv > 2) b[1] = uint8_t(w >> 8);
+    }
+}
+
+// Row and column of a workgroup's first element; rows and columns of its other elements follow by 32-bit arithmetic
+// (cols <= 2^31, and a workgroup spans kCvtElems elements).
+struct CvtOrigin {
+    int64_t i;
+    uint32_t j, cols;
+};
+__device__ __forceinline__ CvtOrigin cvt_origin(int64_t first, int64_t cols) {
+    CvtOrigin o;
+    o.i = first / cols;
+    o.j = uint32_t(first - o.i * cols);
+    o.cols = uint32_t(cols);
+    return o;
+}
+// The rank-1 scales min(r_i, c_j) of the 4 elements that lie `off` behind the workgroup's first one.  Elements beyond
+// the tensor get scale 0.
+__device__ __forceinline__ void rank1_scales4(const CvtOrigin& o, uint32_t off, int64_t rows, const float* r, const float* c,
+                                              float s[4]) {
+    uint32_t j = o.j + off;                                       // < 2^31 + kCvtElems
+    int64_t i = o.i;
+    if (j >= o.cols) {
+        const uint32_t q = j / o.cols;
+        i += q;
+        j -= q * o.cols;
+    }
+    if (i < rows && j + 4u <= o.cols) {
+        const float rv = r[i];
+        const v4f_a4 cv = *reinterpret_cast<const v4f_a4*>(c + j);
+        s[0] = fminf(rv, cv.x); s[1] = fminf(rv, cv.y); s[2] = fminf(rv, cv.z); s[3] = fminf(rv, cv.w);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s[e] = i < rows ? fminf(r[i], c[j]) : 0.0f;
+            if (++j == o.cols) { j = 0; ++i; }
+        }
+    }
+}
+
+// ---- first moment ----------------------------------------------------------------------------------------------------
+
+__global__ __launch_bounds__(kThreads) void dequant_m_kernel(const QuantArgs q) {
+    __shared__ float2 s_deq[256];
+    const float2* gd = reinterpret_cast<const float2*>(d_byte_decode);
+    s_deq[threadIdx.x] = gd[threadIdx.x];
+    const int64_t first = int64_t(blockIdx.x) * kCvtElems + threadIdx.x * 4;
+    uint32_t w[kCvtUnits];
+    float s[kCvtUnits];
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        const int64_t base = first + u * kCvtUnitElems;
+        w[u] = cvt_load_codes(q.q_in, base, q.P);
+        s[u] = base < q.P ? q.sa[base >> 7] : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        const float2 a = s_deq[w[u] & 255u], b = s_deq[w[u] >> 8];
+        const float v[4] = {a.x * s[u], a.y * s[u], b.x * s[u], b.y * s[u]};
+        cvt_store4(q.x_out, first + u * kCvtUnitElems, q.P, v);
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void quant_m_kernel(const QuantArgs q) {
+    __shared__ SearchEntry s_search[kBucketsPadded];
+    const int64_t first = int64_t(blockIdx.x) * kCvtElems + threadIdx.x * 4;
+    float x[kCvtUnits][4];
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) cvt_load4(q.x_in, first + u * kCvtUnitElems, q.P, x[u]);
+    const uint2* gs = reinterpret_cast<const uint2*>(d_search);
+    uint2* ss = reinterpret_cast<uint2*>(s_search);
+    for (int i = threadIdx.x; i < kBucketsPadded; i += kThreads) ss[i] = gs[i];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        const int64_t base = first + u * kCvtUnitElems;
+        const float sc = group32_allmax(fmaxf(fmaxf(fabsf(x[u][0]), fabsf(x[u][1])), fmaxf(fabsf(x[u][2]), fabsf(x[u][3]))));
+        // reciprocal and guard, exact division where some lane comes close to a threshold (as in the step kernels)
+        const float inv = approx_inv(sc);
+        uint32_t w = 0, dist = scale_is_tame(sc) ? 0xFFFFFFFFu : 0u, d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            w |= quant_m_code_fast(s_search, x[u][e], inv, d) << (4 * e);
+            dist = min(dist, d);
+        }
+        if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
+            w = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w |= quant_m_code(s_search, x[u][e], sc) << (4 * e);
+        }
+        cvt_store_codes(q.q_out, base, q.P, w);
+        if ((threadIdx.x & 31) == 0 && base < q.P) q.sa[base >> 7] = sc;
+    }
+}
+
+// ---- second moment ---------------------------------------------------------------------------------------------------
+
+// codes of 4 elements under the Linear map: reciprocal and guard, IEEE division for a wave that needs it.  The inputs
+// of lanes beyond the tensor are 0 with scale 0.
+__device__ __forceinline__ uint32_t linear_codes4(const float x[4], const float s[4]) {
+    uint32_t lo = 0, hi = 0;
+    float closest = 0.5f, fa, fb;
+    bool tame = true;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tame = bool(int(tame) & int(scale_is_tame(s[e])));
+    lo = quant_v_code_fast<0>(x[0], approx_inv(s[0]), lo, fa);
+    hi = quant_v_code_fast<0>(x[1], approx_inv(s[1]), hi, fb);
+    closest = fminf(fminf(closest, fabsf(fa)), fabsf(fb));
+    lo = quant_v_code_fast<1>(x[2], approx_inv(s[2]), lo, fa);
+    hi = quant_v_code_fast<1>(x[3], approx_inv(s[3]), hi, fb);
+    closest = fminf(fminf(closest, fabsf(fa)), fabsf(fb));
+    uint32_t w = lo | (hi << 4);
+    if (__builtin_expect(__ballot(closest < kMarginV || !tame) != 0, 0)) {
+        w = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w |= quant_v_code(x[e], s[e]) << (4 * e);
+    }
+    return w;
+}
+
+__global__ __launch_bounds__(kThreads) void dequant_v_kernel(const QuantArgs q) {
+    const int64_t wg_first = int64_t(blockIdx.x) * kCvtElems;
+    const CvtOrigin o = cvt_origin(wg_first, q.cols);
+    uint32_t w[kCvtUnits];
+    float s[kCvtUnits][4];
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        const uint32_t off = u * kCvtUnitElems + threadIdx.x * 4;
+        w[u] = cvt_load_codes(q.q_in, wg_first + off, q.P);
+        rank1_scales4(o, off, q.rows, q.sa, q.sb, s[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = dequant_v((w[u] >> (4 * e)) & 15u, s[u][e]);
+        cvt_store4(q.x_out, wg_first + u * kCvtUnitElems + threadIdx.x * 4, q.P, v);
+    }
+}
+
+// second moment with block scales (1-dimensional / flattened tensors)
+__global__ __launch_bounds__(kThreads) void dequant_vb_kernel(const QuantArgs q) {
+    const int64_t first = int64_t(blockIdx.x) * kCvtElems + threadIdx.x * 4;
+    uint32_t w[kCvtUnits];
+    float s[kCvtUnits];
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        const int64_t base = first + u * kCvtUnitElems;
+        w[u] = cvt_load_codes(q.q_in, base, q.P);
+        s[u] = base < q.P ? q.sa[base >> 7] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = dequant_v((w[u] >> (4 * e)) & 15u, s[u]);
+        cvt_store4(q.x_out, first + u * kCvtUnitElems, q.P, v);
+    }
+}
+
+// block-wise second moment (values >= 0): block maximum, Linear map
+__global__ __launch_bounds__(kThreads) void quant_vb_kernel(const QuantArgs q) {
+    const int64_t first = int64_t(blockIdx.x) * kCvtElems + threadIdx.x * 4;
+    float x[kCvtUnits][4];
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) cvt_load4(q.x_in, first + u * kCvtUnitElems, q.P, x[u]);
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        const int64_t base = first + u * kCvtUnitElems;
+        const float sc = group32_allmax(fmaxf(fmaxf(fabsf(x[u][0]), fabsf(x[u][1])), fmaxf(fabsf(x[u][2]), fabsf(x[u][3]))));
+        const float s[4] = {sc, sc, sc, sc};
+        cvt_store_codes(q.q_out, base, q.P, linear_codes4(x[u], s));
+        if ((threadIdx.x & 31) == 0 && base < q.P) q.sa[base >> 7] = sc;
+    }
+}
+
+// Row and column maxima of a rows x cols matrix into sa / sb (zero on entry), for rank-1 normalization.
+//
+// A workgroup takes `rows_per_wg` rows x a strip of 4 * tx columns, tx = 2^tx_log2 lanes of 4 columns side by side and
+// 256 / tx rows at a time: a lane keeps its columns' maxima in registers, a row's maximum is reduced over its lanes and
+// combined in LDS, and one global atomic per row and per column of the tile follows at the end.  An atomic per element
+// -- read first and skipped where it cannot raise the value -- made the atomics' queues the bound: 2.96 ms for
+// 11008 x 4096, 54 us this way.
+constexpr int kMaxTileRows = 512;
+constexpr int kMaxMinTxLog2 = 4;          // 16 lanes: a DPP row
+
+struct MaxTiling {
+    int tx_log2;          // 4..8
+    int rows_per_wg;      // <= kMaxTileRows, a multiple of 256 >> tx_log2
+    int strips;           // ceil(cols / (4 << tx_log2))
+};
+
+__global__ __launch_bounds__(kThreads) void quant_v_max_kernel(const QuantArgs q, const MaxTiling t) {
+    __shared__ unsigned int s_row[kMaxTileRows];
+    __shared__ unsigned int s_col[kThreads * 4];
+    const int strip = blockIdx.x % t.strips;
+    const int64_t row0 = int64_t(blockIdx.x / t.strips) * t.rows_per_wg;
+    const int64_t left = q.rows - row0;
+    const int n = left < t.rows_per_wg ? int(left) : t.rows_per_wg;
+    const int tx = 1 << t.tx_log2, ty = kThreads >> t.tx_log2;
+    const int x = threadIdx.x & (tx - 1), y = threadIdx.x >> t.tx_log2;
+    for (int k = threadIdx.x; k < n; k += kThreads) s_row[k] = 0u;
+    for (int k = threadIdx.x; k < 4 * tx; k += kThreads) s_col[k] = 0u;
+    __syncthreads();
+    const int64_t col0 = int64_t(strip) * (4 << t.tx_log2) + 4 * x;
+    const int nc = q.cols - col0 >= 4 ? 4 : (q.cols > col0 ? int(q.cols - col0) : 0);      // the lane's columns
+    const float* p = q.x_in + row0 * q.cols + col0;
+    float cm[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int kDepth = 4;
+    // n and ty are uniform: every lane of a wave runs the same rounds, so the cross-lane steps see whole waves
+    for (int base = 0; base < n; base += ty * kDepth) {
+        float v[kDepth][4];
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            const int il = base + u * ty + y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = 0.0f;
+            if (il < n) {
+                const float* pr = p + int64_t(il) * q.cols;
+                if (nc == 4) {
+                    const v4f_a4 w = *reinterpret_cast<const v4f_a4*>(pr);
+                    v[u][0] = w.x; v[u][1] = w.y; v[u][2] = w.z; v[u][3] = w.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (e < nc) v[u][e] = pr[e];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            const int il = base + u * ty + y;
+            float rm = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float z = v[u][e] > 0.0f ? v[u][e] : 0.0f;
+                cm[e] = max_nonneg(cm[e], z);
+                rm = max_nonneg(rm, z);
+            }
+            if (t.tx_log2 == 4) {
+                rm = row16_allmax(rm);
+            } else {
+                rm = group32_allmax(rm);
+                if (t.tx_log2 > 5) rm = max_nonneg(rm, __shfl_xor(rm, 32));
+            }
+            if ((threadIdx.x & ((tx < 64 ? tx : 64) - 1)) == 0 && il < n && rm > 0.0f)
+                (void)__hip_atomic_fetch_max(&s_row[il], __float_as_uint(rm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        (void)__hip_atomic_fetch_max(&s_col[4 * x + e], __float_as_uint(cm[e]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += kThreads)
+        if (s_row[k]) atomicMax(reinterpret_cast<unsigned int*>(q.sa) + row0 + k, s_row[k]);
+    for (int k = threadIdx.x; k < 4 * tx; k += kThreads)
+        if (s_col[k]) atomicMax(reinterpret_cast<unsigned int*>(q.sb) + int64_t(strip) * (4 << t.tx_log2) + k, s_col[k]);
+}
+
+// second moment, after the maxima: codes against min(r_i, c_j)
+__global__ __launch_bounds__(kThreads) void quant_v_code_kernel(const QuantArgs q) {
+    const int64_t wg_first = int64_t(blockIdx.x) * kCvtElems;
+    const CvtOrigin o = cvt_origin(wg_first, q.cols);
+    float x[kCvtUnits][4], s[kCvtUnits][4];
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u) {
+        const uint32_t off = u * kCvtUnitElems + threadIdx.x * 4;
+        cvt_load4(q.x_in, wg_first + off, q.P, x[u]);
+        rank1_scales4(o, off, q.rows, q.sa, q.sb, s[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kCvtUnits; ++u)
+        cvt_store_codes(q.q_out, wg_first + u * kCvtUnitElems + threadIdx.x * 4, q.P, linear_codes4(x[u], s[u]));
+}
+
+// zero two float arrays in one launch (row and column maxima before they are raised)
+__global__ __launch_bounds__(kThreads) void clear_two_kernel(float* a, int64_t na, float* b, int64_t nb) {
+    const int64_t stride = int64_t(gridDim.x) * kThreads;
+    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < na + nb; i += stride) {
+        if (i < na) a[i] = 0.0f;
+        else b[i - na] = 0.0f;
+    }
+}
+
+}  // namespace lpmm

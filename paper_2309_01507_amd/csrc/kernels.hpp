@@ -2394,118 +2394,8 @@ __global__ __launch_bounds__(kThreads) void sgdm_phase_kernel(const Phase ph, co
 }
 
 // =====================================================================================================
-// Stand-alone decompress / compress of one moment, and the zero state.
+// The zero state.
 // =====================================================================================================
-
-struct QuantArgs {
-    const uint32_t* q_in;   // dequant: codes
-    uint32_t* q_out;        // quant: codes
-    const float* x_in;      // quant: fp32 moment
-    float* x_out;           // dequant: fp32 moment
-    float* sa;              // block scales or row maxima
-    float* sb;              // column maxima (second moment)
-    int64_t rows, cols, P;
-};
-
-__global__ __launch_bounds__(kThreads) void dequant_m_kernel(const QuantArgs q) {
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    const LaneIo io = lane_io(q.P, q.cols, t);
-    if (!io.nv) return;
-    const uint32_t w = load_codes(q.q_in, io);
-    const float s = q.sa[t >> 4];
-    for (int e = 0; e < io.nv; ++e)
-        q.x_out[io.base + e] = d_byte_decode[2 * ((w >> (4 * e)) & 15u)] * s;   // entry b<16: {T[b], T[0]}
-}
-
-__global__ __launch_bounds__(kThreads) void dequant_v_kernel(const QuantArgs q) {
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    const LaneIo io = lane_io(q.P, q.cols, t);
-    if (!io.nv) return;
-    const uint32_t w = load_codes(q.q_in, io);
-    int64_t i = io.i, j = io.j;
-    for (int e = 0; e < io.nv; ++e) {
-        q.x_out[io.base + e] = dequant_v((w >> (4 * e)) & 15u, fminf(q.sa[i], q.sb[j]));
-        if (++j == q.cols) { j = 0; ++i; }
-    }
-}
-
-// second moment with block scales (1-dimensional / flattened tensors)
-__global__ __launch_bounds__(kThreads) void dequant_vb_kernel(const QuantArgs q) {
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    const LaneIo io = lane_io(q.P, q.cols, t);
-    if (!io.nv) return;
-    const uint32_t w = load_codes(q.q_in, io);
-    const float s = q.sa[t >> 4];
-    for (int e = 0; e < io.nv; ++e) q.x_out[io.base + e] = dequant_v((w >> (4 * e)) & 15u, s);
-}
-
-__global__ __launch_bounds__(kThreads) void quant_m_kernel(const QuantArgs q) {
-    __shared__ Lds s;
-    load_tables(s);
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if ((t >> 4) * 128 >= q.P) return;
-    const LaneIo io = lane_io(q.P, q.cols, t);
-    float x[8], amax = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        x[e] = e < io.nv ? q.x_in[io.base + e] : 0.0f;
-        amax = fmaxf(amax, fabsf(x[e]));
-    }
-    const float sc = row16_allmax(amax);
-    uint32_t w = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        if (e < io.nv) w |= quant_m_code(s.search, x[e], sc) << (4 * e);
-    if (io.nv) store_codes(q.q_out, io, w);
-    if ((threadIdx.x & 15) == 0) q.sa[t >> 4] = sc;
-}
-
-// block-wise second moment (values >= 0): block maximum, Linear map
-__global__ __launch_bounds__(kThreads) void quant_vb_kernel(const QuantArgs q) {
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if ((t >> 4) * 128 >= q.P) return;
-    const LaneIo io = lane_io(q.P, q.cols, t);
-    float x[8], vmax = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        x[e] = e < io.nv ? q.x_in[io.base + e] : 0.0f;
-        vmax = fmaxf(vmax, fabsf(x[e]));
-    }
-    const float sc = row16_allmax(vmax);
-    uint32_t w = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        if (e < io.nv) w |= quant_v_code(x[e], sc) << (4 * e);
-    if (io.nv) store_codes(q.q_out, io, w);
-    if ((threadIdx.x & 15) == 0) q.sa[t >> 4] = sc;
-}
-
-// second moment, stage 1: row / column maxima into sa / sb (which must be zero on entry)
-__global__ __launch_bounds__(kThreads) void quant_v_max_kernel(const QuantArgs q) {
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    const LaneIo io = lane_io(q.P, q.cols, t);
-    int64_t i = io.i, j = io.j;
-    for (int e = 0; e < io.nv; ++e) {
-        const float x = q.x_in[io.base + e];
-        raise_max(q.sa + i, x);
-        raise_max(q.sb + j, x);
-        if (++j == q.cols) { j = 0; ++i; }
-    }
-}
-
-// second moment, stage 2: codes against min(r_i, c_j)
-__global__ __launch_bounds__(kThreads) void quant_v_code_kernel(const QuantArgs q) {
-    const int64_t t = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    const LaneIo io = lane_io(q.P, q.cols, t);
-    if (!io.nv) return;
-    uint32_t w = 0;
-    int64_t i = io.i, j = io.j;
-    for (int e = 0; e < io.nv; ++e) {
-        w |= quant_v_code(q.x_in[io.base + e], fminf(q.sa[i], q.sb[j])) << (4 * e);
-        if (++j == q.cols) { j = 0; ++i; }
-    }
-    store_codes(q.q_out, io, w);
-}
 
 // fill `n` bytes at dst with `value`, and force the byte at index `last_index` (if >= 0) to `last`
 __global__ __launch_bounds__(kThreads) void fill_bytes_kernel(uint8_t* dst, int64_t n, uint8_t value,

@@ -14,6 +14,7 @@
 
 #include "../../include/lpmm4.h"
 #include "kernels.hpp"
+#include "convert.hpp"
 #include "ablation.hpp"
 
 namespace {
@@ -725,6 +726,27 @@ int fill(void* dst, int64_t n, uint8_t value, int64_t last_index, uint8_t last, 
     return LPMM_OK;
 }
 
+// Row and column maxima of q.x_in into q.sa / q.sb.  As many lanes side by side as the columns need, rounded up to a
+// power of two between 16 and 256; 32 rows per group of lanes, halved down to 4 (one batch of loads) while the tensor
+// would give the chip fewer than four workgroups per CU.
+int launch_maxima(const QuantArgs& q, int n_cu, hipStream_t s) {
+    hipLaunchKernelGGL(clear_two_kernel, dim3(grid_for(q.rows + q.cols, 4, 1024)), dim3(kThreads), 0, s, q.sa, q.rows, q.sb,
+                       q.cols);
+    LPMM_HIP(hipGetLastError());
+    MaxTiling t;
+    t.tx_log2 = kMaxMinTxLog2;
+    while (t.tx_log2 < 8 && (int64_t(4) << t.tx_log2) < q.cols) ++t.tx_log2;
+    const int ty = kThreads >> t.tx_log2;
+    const int64_t strips = (q.cols + (4 << t.tx_log2) - 1) / (4 << t.tx_log2);
+    int64_t per = std::min<int64_t>(32 * ty, kMaxTileRows);
+    while (per > 4 * ty && strips * ((q.rows + per - 1) / per) < 4 * int64_t(n_cu)) per /= 2;
+    t.strips = int(strips);
+    t.rows_per_wg = int(per);
+    hipLaunchKernelGGL(quant_v_max_kernel, dim3(unsigned(strips * ((q.rows + per - 1) / per))), dim3(kThreads), 0, s, q, t);
+    LPMM_HIP(hipGetLastError());
+    return LPMM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1081,7 +1103,7 @@ int lpmm_dequant_state(int which, const uint8_t* codes, const float* scale_a, co
     q.sb = const_cast<float*>(scale_b);
     q.rows = rows; q.cols = cols; q.P = rows * cols;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int grid = grid_for(q.P, 8);
+    const int grid = grid_for(q.P, kCvtElems / kThreads);
     if (which == 0) hipLaunchKernelGGL(dequant_m_kernel, dim3(grid), dim3(kThreads), 0, s, q);
     else if (which == 1) hipLaunchKernelGGL(dequant_v_kernel, dim3(grid), dim3(kThreads), 0, s, q);
     else hipLaunchKernelGGL(dequant_vb_kernel, dim3(grid), dim3(kThreads), 0, s, q);
@@ -1107,7 +1129,7 @@ int lpmm_quant_state(int which, const float* in, const int64_t shape[2], uint8_t
     q.sb = scale_b;
     q.rows = rows; q.cols = cols; q.P = rows * cols;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int grid = grid_for(q.P, 8);
+    const int grid = grid_for(q.P, kCvtElems / kThreads);
     if (which == 0) {
         hipLaunchKernelGGL(quant_m_kernel, dim3(grid), dim3(kThreads), 0, s, q);
         LPMM_HIP(hipGetLastError());
@@ -1115,11 +1137,8 @@ int lpmm_quant_state(int which, const float* in, const int64_t shape[2], uint8_t
         hipLaunchKernelGGL(quant_vb_kernel, dim3(grid), dim3(kThreads), 0, s, q);
         LPMM_HIP(hipGetLastError());
     } else {
-        int r = fill(scale_a, rows * int64_t(sizeof(float)), 0, -1, 0, s);
-        if (!r) r = fill(scale_b, cols * int64_t(sizeof(float)), 0, -1, 0, s);
+        const int r = launch_maxima(q, ctx->n_cu, s);
         if (r) return r;
-        hipLaunchKernelGGL(quant_v_max_kernel, dim3(grid), dim3(kThreads), 0, s, q);
-        LPMM_HIP(hipGetLastError());
         hipLaunchKernelGGL(quant_v_code_kernel, dim3(grid), dim3(kThreads), 0, s, q);
         LPMM_HIP(hipGetLastError());
     }
@@ -1187,22 +1206,20 @@ int lpmm_quant_ablation(int norm, int map, int is_signed, int rounding, uint64_t
     a.stochastic = rounding == LPMM_ROUND_STOCHASTIC;
     a.seed = seed;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int grid = grid_for(a.P, 8);
+    const int grid = grid_for(a.P, kCvtElems / kThreads);
     if (norm == LPMM_NORM_RANK1) {
-        int r = fill(scale_a, rows * int64_t(sizeof(float)), 0, -1, 0, s);
-        if (!r) r = fill(scale_b, cols * int64_t(sizeof(float)), 0, -1, 0, s);
-        if (r) return r;
         QuantArgs q{};
         q.x_in = in; q.sa = scale_a; q.sb = scale_b;
         q.rows = rows; q.cols = cols; q.P = a.P;
-        hipLaunchKernelGGL(quant_v_max_kernel, dim3(grid), dim3(kThreads), 0, s, q);
-        LPMM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(abl_quant_rank1_kernel, dim3(grid), dim3(kThreads), 0, s, a, m);
-    } else if (norm == LPMM_NORM_B128) {
-        hipLaunchKernelGGL(abl_quant_block_kernel<128>, dim3(grid), dim3(kThreads), 0, s, a, m);
-    } else {
-        hipLaunchKernelGGL(abl_quant_block_kernel<2048>, dim3(grid), dim3(kThreads), 0, s, a, m);
+        const int r = launch_maxima(q, 256, s);       // this call needs no init, hence no device context
+        if (r) return r;
     }
+#define LPMM_ABL_LAUNCH(SR)                                                                                            \
+    if (norm == LPMM_NORM_RANK1) hipLaunchKernelGGL(abl_quant_rank1_kernel<SR>, dim3(grid), dim3(kThreads), 0, s, a, m); \
+    else if (norm == LPMM_NORM_B128) hipLaunchKernelGGL((abl_quant_block_kernel<128, SR>), dim3(grid), dim3(kThreads), 0, s, a, m); \
+    else hipLaunchKernelGGL((abl_quant_block_kernel<2048, SR>), dim3(grid), dim3(kThreads), 0, s, a, m);
+    if (a.stochastic) { LPMM_ABL_LAUNCH(true) } else { LPMM_ABL_LAUNCH(false) }
+#undef LPMM_ABL_LAUNCH
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
 }
@@ -1223,7 +1240,7 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
     a.sb = const_cast<float*>(scale_b);
     a.rows = rows; a.cols = cols; a.P = rows * cols;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(abl_dequant_kernel, dim3(grid_for(a.P, 8)), dim3(kThreads), 0, s, a, m, norm);
+    hipLaunchKernelGGL(abl_dequant_kernel, dim3(grid_for(a.P, kCvtElems / kThreads)), dim3(kThreads), 0, s, a, m, norm);
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
 }

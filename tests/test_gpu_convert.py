@@ -1,0 +1,74 @@
+"""Stand-alone compress / decompress at the edges of their tiles: 4 elements per lane, 4096 per workgroup, strips of 64 to
+1024 columns and up to 512 rows for the maxima; arrays at 4-byte alignment; nothing written behind a buffer's end."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2309_01507_amd as lpmm
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 3), (5, 4), (2, 63), (1100, 65), (513, 128), (31, 129), (33, 255), (67, 257), (9, 1023), (40, 1025),
+          (6, 4097), (3, 8190), (4500, 7), (12, 1365)]
+
+
+def _at_offset(a, dtype, words):
+    """A device copy of the array that starts `words` fp32 words behind a 16-byte boundary."""
+    a = np.ascontiguousarray(a).reshape(-1)
+    item = a.itemsize
+    buf = torch.zeros(a.size + 64, dtype=dtype, device=DEV)
+    lo = words * 4 // item
+    buf[lo:lo + a.size] = torch.from_numpy(a).to(DEV)
+    return buf[lo:lo + a.size]
+
+
+def _guarded(n, dtype, fill, words=0):
+    lo = words * 4 // torch.empty(0, dtype=dtype).element_size()
+    buf = torch.full((n + 64,), fill, dtype=dtype, device=DEV)
+    return buf, buf[lo:lo + n], lo
+
+
+def _clean(buf, lo, n, fill):
+    rest = torch.cat([buf[:lo], buf[lo + n:]])
+    return bool((rest == fill).all())
+
+
+@pytest.mark.parametrize("rows,cols", SHAPES)
+def test_compress_and_decompress_match_the_oracle(rows, cols):
+    print(f"[gpu-test] convert {rows}x{cols}", flush=True)
+    lpmm.ensure_init(4096)
+    rng = np.random.default_rng(rows * 31 + cols)
+    P, nb, half = rows * cols, (rows * cols + 127) // 128, (rows * cols + 1) // 2
+    m = (rng.standard_normal((rows, cols)) * 1e-3).astype(np.float32)
+    v = (rng.standard_normal((rows, cols)) ** 2 * np.exp(rng.standard_normal(cols))[None, :] * 1e-8).astype(np.float32)
+    m.reshape(-1)[: min(P, 128)] = 0.0
+    v[rows // 2, :] = 0.0
+    v[:, cols // 2] = 0.0
+    if P > 200:
+        v.reshape(-1)[200:] *= np.float32(1e-35)            # scales outside the reciprocal's range
+    want = {0: oracle.quant_m(m), 1: oracle.quant_v(v), 2: oracle.quant_v_block(v)}
+    sizes = {0: (nb, 0), 1: (rows, cols), 2: (nb, 0)}
+    for which, x in ((0, m), (1, v), (2, v)):
+        for words in (0, 1, 3):
+            xin = _at_offset(x, torch.float32, words)
+            cb, codes, clo = _guarded(half, torch.uint8, 0xEE, words)
+            na, nb_ = sizes[which]
+            ab, sa, alo = _guarded(na, torch.float32, -1.0, words)
+            bb, sb, blo = _guarded(nb_, torch.float32, -1.0, words) if nb_ else (None, None, 0)
+            lpmm.lpmm_quant_state(which, xin, rows, cols, codes, sa, sb)
+            ob, out, olo = _guarded(P, torch.float32, -7.0, words)
+            lpmm.lpmm_dequant_state(which, codes, sa, sb, rows, cols, out)
+            torch.cuda.synchronize()
+            w = want[which]
+            np.testing.assert_array_equal(sa.cpu().numpy(), w[1])
+            np.testing.assert_array_equal(codes.cpu().numpy(), w[0])
+            assert _clean(cb, clo, half, 0xEE) and _clean(ab, alo, na, -1.0) and _clean(ob, olo, P, -7.0)
+            if which == 1:
+                np.testing.assert_array_equal(sb.cpu().numpy(), w[2])
+                assert _clean(bb, blo, nb_, -1.0)
+                dec = oracle.dequant_v(w[0], w[1], w[2]).reshape(-1)
+            else:
+                dec = (oracle.dequant_m if which == 0 else oracle.dequant_v_block)(w[0], w[1], P)
+            np.testing.assert_array_equal(out.cpu().numpy(), dec)

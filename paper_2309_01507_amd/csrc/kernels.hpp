@@ -34,7 +34,7 @@ __device__ float d_byte_decode[512];          // entry b: {T_DE[b & 15], T_DE[b 
 __device__ SearchEntry d_search[kBucketsPadded];    // nearest-entry search for the DE map
 
 enum TensorKind : int { kQuantFast = 0, kQuantGeneral = 1, kFp32State = 2, kQuantBlockV = 3, kFactorFast = 4, kFactorGeneral = 5,
-                        kSgdmBlock = 6, kSgdmFp32 = 7 };
+                        kSgdmBlock = 6, kSgdmFp32 = 7, kQuantRagged = 8 };
 
 struct Tensor4 {
     float* p;               // parameters, fp32 [P]
@@ -52,7 +52,8 @@ struct Tensor4 {
     int nb;                 // column blocks per row = cols / 128    (kQuantBlockV: whole blocks of the tensor)
     int gx, gy;             // a workgroup's 8 groups: gx column blocks x gy row phases
     int rw;                 // rows per workgroup tile; rw * cols < 2^29   (kQuantBlockV, kSgdmBlock: blocks a group takes in
-                            // a row; general path: chunks of 2048 elements a workgroup of the first pass takes)
+                            // a row; general path: chunks of 2048 elements a workgroup of the first pass takes;
+                            // kQuantRagged: blocks of a tile if strips == 1, else rows of a tile, both passes)
     int strips;             // nb / gx
     int n_wg;               // workgroups of pass 1 (kQuantBlockV, kSgdmBlock: of the step;
                             // kFactor*: of the statistics pass, which is tiled like pass 2)
@@ -74,6 +75,7 @@ struct Tensor4 {
     int det;                // kFactorFast in a plan: the sums of g^2 are reduced in a fixed order (no float atomics);
                             // vq then points at the partial sums: float[strips2][round_up(rows, 64)] per strip and row,
                             // then float[tiles][round_up(cols, 64)] per row tile and column
+    int sw;                 // kQuantRagged: columns of a strip
 };
 
 // The tensor table of a plan lives in device memory.  A pointer read from memory is a generic
@@ -95,7 +97,7 @@ struct Tensor4Table {
     float LPMM_AS_GLOBAL* c_new;
     unsigned int LPMM_AS_GLOBAL* counter;
     int64_t rows, cols, P;
-    int nb, gx, gy, rw, strips, n_wg, kind, strips2, rw2, n_wg2, rs, rs2, tot_slots, flat, no_decay, c_extra, nd_index, det;
+    int nb, gx, gy, rw, strips, n_wg, kind, strips2, rw2, n_wg2, rs, rs2, tot_slots, flat, no_decay, c_extra, nd_index, det, sw;
 };
 static_assert(sizeof(Tensor4Table) == sizeof(Tensor4), "the table twin must mirror Tensor4");
 __device__ __forceinline__ Tensor4 from_table(const Tensor4Table& t) {
@@ -113,7 +115,7 @@ __device__ __forceinline__ Tensor4 from_table(const Tensor4Table& t) {
     a.rows = t.rows; a.cols = t.cols; a.P = t.P;
     a.nb = t.nb; a.gx = t.gx; a.gy = t.gy; a.rw = t.rw; a.strips = t.strips; a.n_wg = t.n_wg; a.kind = t.kind;
     a.strips2 = t.strips2; a.rw2 = t.rw2; a.n_wg2 = t.n_wg2; a.rs = t.rs; a.rs2 = t.rs2;
-    a.tot_slots = t.tot_slots; a.flat = t.flat; a.no_decay = t.no_decay; a.c_extra = t.c_extra; a.nd_index = t.nd_index; a.det = t.det;
+    a.tot_slots = t.tot_slots; a.flat = t.flat; a.no_decay = t.no_decay; a.c_extra = t.c_extra; a.nd_index = t.nd_index; a.det = t.det; a.sw = t.sw;
     return a;
 }
 #else
@@ -135,11 +137,13 @@ __device__ __forceinline__ int logical_wg() {
 constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0) only: expcnt and lgkmcnt fields at their maxima
 constexpr int kMaxRowSlots = 512;    // rows of a pass-1 tile x column blocks of its strip (rw * gx)
 
+constexpr int kColSlots = 9 * 128;   // columns of a strip; a ragged strip's last block may reach 127 columns beyond it
+
 struct Lds {
     float2 deq[256];
     SearchEntry search[kBucketsPadded];
-    float col[8 * 128];
-    float cold[8 * 128];        // flat tiling of pass 1: the strip's old column maxima / 16
+    float col[kColSlots];
+    float cold[kColSlots];      // flat tiling of pass 1: the strip's old column maxima / 16
     // per row and column block of the tile: new block scale of m and the block's maximum of v_t.
     // They leave for global memory at the end of the tile, so that the row loop issues the same
     // memory instructions on every path (loads, the parameter store, the code store) and nothing
@@ -837,44 +841,65 @@ struct RowScalars {
     float r_old, r_new, r16, inv;
     uint64_t wild;
 };
+// The same of the rows that follow the wave's rows, and which of the lane's 4 elements lie in the following row (ragged
+// tensors only, see pass2_tile).
+struct NextRow {
+    RowScalars sc;
+    bool beyond[4];
+};
 
 // New codes of the lane's 4 elements of row k of the wave.  The usual route multiplies by approximate reciprocals and
 // keeps track of how close it came to a decision boundary; if the row is marked wild, or some lane came too close, the
 // whole wave computes the row again from its inputs with exact arithmetic (same bits where both apply).  The second
 // route shares no value with the first, so that nothing has to be kept in registers for it.
-template <bool BF16>
-__device__ __forceinline__ uint32_t pass2_row(const Tensor4& a, const Hyper& h, uint32_t col0, const Row2<BF16>& row,
-                                              const RowScalars& rs, int k, const float cold16[4],
+template <bool BF16, bool RAGGED>
+__device__ __forceinline__ uint32_t pass2_row(const Tensor4& a, const Hyper& h, const uint32_t col[4], const Row2<BF16>& row,
+                                              const RowScalars& rs, const NextRow& nx, int k, const float cold16[4],
                                               const float inv_cnew[4]) {
     float g[4];
     unpack_grad4<BF16>(row.g, g);
     // wave-uniform: the whole wave takes one route
     if (__builtin_expect(((rs.wild >> k) & 1u) == 0u, 1)) {
-        float qf[4], vt[4];
+        float qf[4], vt[4], r16[4], inv_r[4];
         codes_to_float4(row.vq, qf);
-        const float r16 = lane_value(rs.r16, k), inv_r = lane_value(rs.inv, k);
+        r16[0] = lane_value(rs.r16, k);
+        inv_r[0] = lane_value(rs.inv, k);
+        if constexpr (RAGGED) {
+            const float r16n = lane_value(nx.sc.r16, k), invn = lane_value(nx.sc.inv, k);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) vt[e] = moment_v(h, dequant_v16(qf[e], min_nonneg(r16, cold16[e])), g[e]);
+            for (int e = 3; e >= 0; --e) {                       // an element beyond the row's end has one before it
+                r16[e] = nx.beyond[e] ? r16n : r16[0];
+                inv_r[e] = nx.beyond[e] ? invn : inv_r[0];
+            }
+        } else {
+#pragma unroll
+            for (int e = 1; e < 4; ++e) { r16[e] = r16[0]; inv_r[e] = inv_r[0]; }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vt[e] = moment_v(h, dequant_v16(qf[e], min_nonneg(r16[e], cold16[e])), g[e]);
         // even elements collect in the bytes of `lo`, odd ones in `hi`; word = lo | hi << 4
         uint32_t lo = 0, hi = 0;
         float closest = 0.5f, fa, fb;
 #define LPMM_V2(K)                                                                                        \
-        lo = quant_v_code_fast<K>(vt[2 * K], max_nonneg(inv_r, inv_cnew[2 * K]), lo, fa);                 \
-        hi = quant_v_code_fast<K>(vt[2 * K + 1], max_nonneg(inv_r, inv_cnew[2 * K + 1]), hi, fb);         \
+        lo = quant_v_code_fast<K>(vt[2 * K], max_nonneg(inv_r[2 * K], inv_cnew[2 * K]), lo, fa);          \
+        hi = quant_v_code_fast<K>(vt[2 * K + 1], max_nonneg(inv_r[2 * K + 1], inv_cnew[2 * K + 1]), hi, fb); \
         closest = fminf(fminf(closest, fabsf(fa)), fabsf(fb));
         LPMM_V2(0) LPMM_V2(1)
 #undef LPMM_V2
         if (__builtin_expect(__ballot(closest < kMarginV) == 0, 1)) return lo | (hi << 4);
     }
-    const float r_old = lane_value(rs.r_old, k), r_new = lane_value(rs.r_new, k);
-    float cold[4], cnew[4];
-    load4(a.c + col0, cold);
-    load4(a.c_new + col0, cnew);
     uint32_t out = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const float vt = moment_v(h, dequant_v((uint32_t(row.vq) >> (4 * e)) & 15u, fminf(r_old, cold[e])), g[e]);
-        out |= quant_v_code(vt, fminf(r_new, cnew[e])) << (4 * e);
+        float r_old = lane_value(rs.r_old, k), r_new = lane_value(rs.r_new, k);
+        if constexpr (RAGGED) {
+            const float ron = lane_value(nx.sc.r_old, k), rnn = lane_value(nx.sc.r_new, k);
+            r_old = nx.beyond[e] ? ron : r_old;
+            r_new = nx.beyond[e] ? rnn : r_new;
+        }
+        const float cold = a.c[col[e]], cnew = a.c_new[col[e]];
+        const float vt = moment_v(h, dequant_v((uint32_t(row.vq) >> (4 * e)) & 15u, fminf(r_old, cold)), g[e]);
+        out |= quant_v_code(vt, fminf(r_new, cnew)) << (4 * e);
     }
     return out;
 }
@@ -882,41 +907,80 @@ __device__ __forceinline__ uint32_t pass2_row(const Tensor4& a, const Hyper& h, 
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxRw2 = 64 * kWaves;      // rows of a pass-2 tile: a wave keeps its rows' scalars one per lane
 
-template <bool BF16>
-__device__ __forceinline__ void pass2_fast_tile(const Tensor4& a, const Hyper& h, int wg) {
+// RAGGED: rows that are no multiple of 128 elements long, so that a row's first element need not be the first of its
+// code byte.  Nothing in pass 2 knows about blocks; all that has to be aligned is a lane's 4 elements in the flattening.
+// The lanes of row i therefore start at the first multiple of 4 at or behind i * cols, `shift` = -i * cols mod 4 columns
+// into the row, and that shift is the same for all rows a wave takes (they are a multiple of 4 apart): a lane's columns
+// are fixed down the tile here, too.  The last lane of a row may reach up to 3 elements into the next row; its columns
+// are those of the next row's beginning, and only the row's scalars have to be chosen per element.  Where that would
+// reach beyond the tensor (its size is no multiple of 4) the last row is left to pass2_last_row.  Measured on 4096 x 4000
+// with bf16 gradients: 19 us, 15 for 4096 x 4096 on the plain form.  (Blocks of 128 with the column vectors in LDS, as
+// pass 1 has to take them: 28 us; the general kernel: more than 100.)
+__host__ __device__ __forceinline__ int64_t pass2_rows(const Tensor4& a, bool ragged) {
+    return ragged && (a.P & 3) ? a.rows - 1 : a.rows;
+}
+
+template <bool BF16, bool RAGGED = false>
+__device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int wg) {
     const int strip = wg % a.strips2, tile = wg / a.strips2;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
-    // With an odd number of column blocks the upper half-wave of the last strip has no columns.  Those lanes stay
-    // in the loop all the same, because every lane of the wave holds the scalars of one of its rows (below): they
-    // work on the lower half's columns a second time and only their stores are left out.
-    const uint32_t col_own = uint32_t(strip) * 256u + uint32_t(lane) * 4u;
-    const bool live = col_own < uint32_t(a.cols);
-    const uint32_t col0 = live ? col_own : col_own - 128u;
-    const int64_t row0 = int64_t(tile) * a.rw2;
-    const int64_t left = a.rows - row0;
+    const int64_t row0 = int64_t(tile) * a.rw2;                   // ragged: a multiple of 4
+    const int64_t left = pass2_rows(a, RAGGED) - row0;
     const int n = left < a.rw2 ? int(left) : a.rw2;
-    const TileBase tb = tile_base<BF16>(a, row0, n);
+    const uint32_t cols = uint32_t(a.cols);
     // rows of this wave in the order it takes them, as in pass 1: the four waves are 2^rs2 rows apart
-    const int rs = a.rs2;
+    const int rs = RAGGED ? 0 : a.rs2;
     const int row_w = wave << rs, hop = kWaves << rs, low = (1 << rs) - 1;
     auto row = [&](int k) { return row_w + (k & low) + (k >> rs) * hop; };
+    int last = n - 1;
+    uint32_t shift = 0;
+    if constexpr (RAGGED) {
+        if (row_w >= n) return;                                   // no barrier in this function
+        last -= (last - row_w) % kWaves;                          // the wave's own last row
+        shift = (0u - uint32_t(wave) * cols) & 3u;
+    }
+    // With an odd number of column blocks the upper half-wave of the last strip has no columns (ragged: any number of
+    // its lanes).  Those lanes stay in the loop all the same, because every lane of the wave holds the scalars of one
+    // of its rows (below): they work on other columns a second time and only their stores are left out.
+    const uint32_t col_own = uint32_t(strip) * 256u + uint32_t(lane) * 4u + shift;
+    const bool live = col_own < cols;
+    const uint32_t col0 = live ? col_own : (RAGGED ? shift : col_own - 128u);
+    uint32_t col[4];
+    NextRow nx;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        nx.beyond[e] = RAGGED && col0 + e >= cols;
+        col[e] = nx.beyond[e] ? col0 + e - cols : col0 + e;
+    }
+    const int n_stat = RAGGED && row0 + n < a.rows ? n + 1 : n;   // ragged: the statistics of one row more
+    const TileBase tb = tile_base<BF16>(a, row0, n_stat);
     // The scalars of the wave's rows (at most 64 per tile), one row per lane; the row loop fetches what it needs
     // with v_readlane instead of two loads, a reciprocal, a select and two range checks per row.  Rows past the
     // tile read as zeros through the bounds-checked resources.
-    RowScalars sc;
-    {
-        const uint32_t il_l = uint32_t(row(lane));
-        sc.r_old = buf_ld_f(tb.rr, il_l * 4u);
-        sc.r_new = buf_ld_f(tb.rr_new, il_l * 4u);
+    auto scalars = [&](uint32_t il) {
+        RowScalars sc;
+        sc.r_old = buf_ld_f(tb.rr, il * 4u);
+        sc.r_new = buf_ld_f(tb.rr_new, il * 4u);
         sc.r16 = sc.r_old * 0.0625f;
         sc.inv = approx_inv(sc.r_new);
         const bool row_tame = bool(int(scale_is_tame(sc.r_old)) & int(scale_is_tame(sc.r_new)));
         sc.wild = __ballot(!row_tame);
+        return sc;
+    };
+    RowScalars sc = scalars(uint32_t(row(lane)));
+    if constexpr (RAGGED) {
+        nx.sc = scalars(uint32_t(row(lane)) + 1u);
+        sc.wild |= nx.sc.wild;
     }
     float cold16[4], inv_cnew[4];
-    load4(a.c + col0, cold16);
-    load4(a.c_new + col0, inv_cnew);
+    if constexpr (RAGGED) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { cold16[e] = a.c[col[e]]; inv_cnew[e] = a.c_new[col[e]]; }
+    } else {
+        load4(a.c + col0, cold16);
+        load4(a.c_new + col0, inv_cnew);
+    }
     bool lane_tame = true;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -926,15 +990,16 @@ __device__ __forceinline__ void pass2_fast_tile(const Tensor4& a, const Hyper& h
     }
     if (__ballot(!lane_tame) != 0) sc.wild = ~uint64_t(0);        // a wild column scale: every row takes the exact route
     // the loads of two rows are in flight while a third is computed (three register sets take turns, the loop is
-    // unrolled by three); a prefetch past the tile takes the tile's last row again and is never used
-    const uint32_t cols = uint32_t(a.cols);
-    const uint32_t lane_g = col0 * (BF16 ? 2u : 4u), lane_q = col0 >> 1;
-    const int last = n - 1;
-    auto fetch = [&](int il) { return load_row2<BF16>(tb, uint32_t(il < last ? il : last) * cols, lane_g, lane_q); };   // il * cols < 2^29
+    // unrolled by three); a prefetch past the tile takes the tile's last row again and is never used.  Ragged: the
+    // scalar offset counts from the wave's first row and the lane's from the tile's, both multiples of 4 elements.
+    const uint32_t lane_e = RAGGED ? col0 + uint32_t(wave) * cols : col0;
+    const uint32_t lane_g = lane_e * (BF16 ? 2u : 4u), lane_q = lane_e >> 1;
+    const int row_b = RAGGED ? wave : 0;
+    auto fetch = [&](int il) { return load_row2<BF16>(tb, uint32_t((il < last ? il : last) - row_b) * cols, lane_g, lane_q); };   // il * cols < 2^29
     auto put = [&](int il, uint32_t codes) {
-        if (live) __builtin_amdgcn_raw_buffer_store_b16(short(codes), tb.rvq, int(lane_q), int((uint32_t(il) * cols) >> 1), 0);
+        if (live) __builtin_amdgcn_raw_buffer_store_b16(short(codes), tb.rvq, int(lane_q), int((uint32_t(il - row_b) * cols) >> 1), 0);
     };
-    auto codes_of = [&](const Row2<BF16>& r, int k) { return pass2_row<BF16>(a, h, col0, r, sc, k, cold16, inv_cnew); };
+    auto codes_of = [&](const Row2<BF16>& r, int k) { return pass2_row<BF16, RAGGED>(a, h, col, r, sc, nx, k, cold16, inv_cnew); };
     int k = 0;
     Row2<BF16> r0 = fetch(row(0));
     Row2<BF16> r1 = fetch(row(1));
@@ -961,6 +1026,30 @@ __device__ __forceinline__ void pass2_fast_tile(const Tensor4& a, const Hyper& h
     if (row(k) < n) {
         put(row(k), codes_of(r0, k));
         if (row(k + 1) < n) put(row(k + 1), codes_of(r1, k + 1));
+    }
+}
+
+// The last row of a ragged tensor whose size is no multiple of 4, from the first multiple of 4 elements in it on: a
+// thread per byte of codes, exact arithmetic.  `part` counts workgroups of kLastRowElems elements.
+constexpr int kLastRowElems = kThreads * 8;
+__host__ __device__ __forceinline__ int64_t pass2_last_row_begin(const Tensor4& a) { return ((a.rows - 1) * a.cols + 3) / 4 * 4; }
+
+template <bool BF16>
+__device__ __forceinline__ void pass2_last_row(const Tensor4& a, const Hyper& h, int part) {
+    const int64_t first = pass2_last_row_begin(a) + int64_t(part) * kLastRowElems;
+    const float r_old = a.r[a.rows - 1], r_new = a.r_new[a.rows - 1];
+    for (int u = 0; u < kLastRowElems / (2 * kThreads); ++u) {
+        const int64_t e0 = first + 2 * (int64_t(u) * kThreads + threadIdx.x);
+        if (e0 >= a.P) return;
+        uint8_t* byte = reinterpret_cast<uint8_t*>(a.vq) + (e0 >> 1);
+        const uint32_t q = *byte;
+        uint32_t out = 0;
+        for (int k = 0; k < 2 && e0 + k < a.P; ++k) {
+            const int64_t j = e0 + k - (a.rows - 1) * a.cols;
+            const float vt = moment_v(h, dequant_v((q >> (4 * k)) & 15u, fminf(r_old, a.c[j])), load_grad1<BF16>(a.g, e0 + k));
+            out |= quant_v_code(vt, fminf(r_new, a.c_new[j])) << (4 * k);
+        }
+        *byte = uint8_t(out);
     }
 }
 
@@ -1294,15 +1383,15 @@ constexpr int kGenMaxChunks = 16;
 constexpr int kGenColsLds = 2048;                        // s.col and s.cold together
 constexpr int kGenRowsLds = 2 * kMaxRowSlots;            // s.blk_scale and s.blk_vmax together
 
+// elements [e_first, e_end) of the tensor; e_first is a multiple of 128, e_end the tensor's end or a multiple of 2048 behind
+// e_first
 template <bool BF16>
-__device__ __forceinline__ void pass1_general_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
-    static_assert(offsetof(Lds, cold) == offsetof(Lds, col) + sizeof(float) * 1024, "col and cold are one array here");
+__device__ __forceinline__ void pass1_general_range(const Tensor4& a, const Hyper& h, int64_t e_first, int64_t e_end, Lds& s) {
+    static_assert(offsetof(Lds, cold) == offsetof(Lds, col) + sizeof(float) * kColSlots, "col and cold are one array here");
     static_assert(offsetof(Lds, blk_vmax) == offsetof(Lds, blk_scale) + sizeof(float) * kMaxRowSlots, "row slots");
     unsigned int* col_l = reinterpret_cast<unsigned int*>(s.col);          // [kGenColsLds]
     unsigned int* row_l = reinterpret_cast<unsigned int*>(s.blk_scale);    // [kGenRowsLds]
-    const int n_chunks = a.rw;
-    const int64_t e_first = int64_t(wg) * n_chunks * kGenChunkElems;
-    const int64_t e_end = e_first + int64_t(n_chunks) * kGenChunkElems < a.P ? e_first + int64_t(n_chunks) * kGenChunkElems : a.P;
+    const int n_chunks = int((e_end - e_first + kGenChunkElems - 1) / kGenChunkElems);
     const int64_t i0 = e_first / a.cols;                                   // first row this workgroup touches
     const int64_t n_rows_wg = (e_end - 1) / a.cols - i0 + 1;
     const bool cols_in_lds = a.cols <= kGenColsLds;
@@ -1321,7 +1410,7 @@ __device__ __forceinline__ void pass1_general_tile(const Tensor4& a, const Hyper
         else raise_max(a.r_new + i, v);
     };
     for (int c = 0; c < n_chunks; ++c) {
-        const int64_t t = (int64_t(wg) * n_chunks + c) * kThreads + threadIdx.x;
+        const int64_t t = e_first / 8 + int64_t(c) * kThreads + threadIdx.x;
         const int64_t block = t >> 4;                       // uniform over the 16 lanes of a block
         const bool alive = block * 128 < a.P;               // dead lanes are the highest of the last chunk
         const LaneIo io = lane_io(a.P, a.cols, t);
@@ -1409,9 +1498,16 @@ __device__ __forceinline__ void pass1_general_tile(const Tensor4& a, const Hyper
 }
 
 template <bool BF16>
-__device__ __forceinline__ void pass2_general_tile(const Tensor4& a, const Hyper& h, int wg) {
-    const int64_t t = int64_t(wg) * kThreads + threadIdx.x;
-    const LaneIo io = lane_io(a.P, a.cols, t);
+__device__ __forceinline__ void pass1_general_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    const int64_t e_first = int64_t(wg) * a.rw * kGenChunkElems;
+    const int64_t e_end = e_first + int64_t(a.rw) * kGenChunkElems;
+    pass1_general_range<BF16>(a, h, e_first, e_end < a.P ? e_end : a.P, s);
+}
+
+// the 2048 elements from e_first (a multiple of 8) on
+template <bool BF16>
+__device__ __forceinline__ void pass2_general_chunk(const Tensor4& a, const Hyper& h, int64_t e_first) {
+    const LaneIo io = lane_io(a.P, a.cols, e_first / 8 + threadIdx.x);
     if (!io.nv) return;
     float g[8];
     if (io.nv == 8) {
@@ -2001,408 +2097,6 @@ __device__ __forceinline__ void sgdm32_tile(float* p, const void* g, float* m, i
             p[idx] = param_sgdm(h, p[idx], mt);
         }
     }
-}
-
-// =====================================================================================================
-// Kernels for one tensor: two launches per step.
-// =====================================================================================================
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass1_fast(const Tensor4 a, const Hyper h) {
-    __shared__ Lds s;
-    const int wg = logical_wg();
-    if (wg >= a.n_wg) return;
-    if (a.flat) pass1_flat_tile<BF16>(a, h, wg, s);
-    else pass1_fast_tile<BF16, false>(a, h, wg, s);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass2_fast(const Tensor4 a, const Hyper h) {
-    __shared__ int s_last;
-    const int wg = logical_wg();
-    if (wg < a.n_wg2) pass2_fast_tile<BF16>(a, h, wg);
-    publish_if_last(a, blockIdx.x, gridDim.x, s_last);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void b128_kernel(const Tensor4 a, const Hyper h) {
-    __shared__ Lds s;
-    const int wg = logical_wg();
-    if (wg < a.n_wg) b128_work<BF16>(a, h, wg, s);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void factor_stats_fast(const Tensor4 a) {
-    __shared__ Lds s;
-    const int wg = logical_wg();
-    if (wg < a.n_wg) factor_stats_tile<BF16>(a, wg, s);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void factor_update_fast(const Tensor4 a, const Hyper h) {
-    __shared__ Lds s;
-    __shared__ int s_last;
-    const int wg = logical_wg();
-    if (wg < a.n_wg2) factor_update_tile<BF16>(a, h, wg, s);
-    factor_publish_if_last(a, h, blockIdx.x, gridDim.x, s_last);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void factor_stats_general(const Tensor4 a) {
-    __shared__ Lds s;
-    factor_stats_general_tile<BF16>(a, blockIdx.x, gridDim.x, s);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void factor_update_general(const Tensor4 a, const Hyper h) {
-    __shared__ Lds s;
-    __shared__ int s_last;
-    load_tables(s);
-    factor_update_general_tile<BF16>(a, h, blockIdx.x, s);
-    factor_publish_if_last(a, h, blockIdx.x, gridDim.x, s_last);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void sgdm4_kernel(const Tensor4 a, const Hyper h) {
-    __shared__ Lds s;
-    const int wg = logical_wg();
-    if (wg < a.n_wg) b128_work<BF16, true>(a, h, wg, s);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void sgdm32_kernel(float* p, const void* g, float* m, int64_t n, const Hyper h) {
-    sgdm32_tile<BF16>(p, g, m, n, h, blockIdx.x);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass1_general(const Tensor4 a, const Hyper h) {
-    __shared__ Lds s;
-    pass1_general_tile<BF16>(a, h, blockIdx.x, s);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass2_general(const Tensor4 a, const Hyper h) {
-    __shared__ int s_last;
-    pass2_general_tile<BF16>(a, h, blockIdx.x);
-    publish_if_last(a, blockIdx.x, gridDim.x, s_last);
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void adamw32_kernel(float* p, const void* g, float* m, float* v,
-                                                           int64_t n, const Hyper h) {
-    adamw32_tile<BF16>(p, g, m, v, n, h, blockIdx.x);
-}
-
-// =====================================================================================================
-// Phase kernel of the multi-tensor step.  A phase runs the "A" work of one set of tensors (pass 1
-// of quantized tensors, the whole update of fp32-state tensors) together with the "B" work of the
-// previous set (pass 2).  The two kinds are interleaved in proportion, so that at any time each CU
-// holds memory-bound pass-1 workgroups next to arithmetic-bound pass-2 workgroups.
-// =====================================================================================================
-
-// Hyper-parameters of a plan's launches: by value, or -- for a step that is captured into a graph and replayed
-// while the learning rate and the step number change -- read from device memory, where a one-thread kernel
-// enqueued in front of the step has put them.
-struct HyperArg {
-    Hyper h;
-    const Hyper* dev;       // non-null: use *dev
-};
-__device__ __forceinline__ Hyper resolve(const HyperArg& a) { return a.dev ? *a.dev : a.h; }
-
-// the host's make_hyper on the device: lr and the step number come from device memory
-__global__ void hyper_prepare_kernel(const float* lr_dev, const int64_t* step_dev, float beta1, float beta2, float eps,
-                                     float wd, Hyper* out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const double lr = double(*lr_dev);
-    int64_t t = *step_dev;
-    if (t < 1) t = 1;
-    Hyper h;
-    h.beta1 = beta1;
-    h.beta2 = beta2;
-    h.omb1 = 1.0f - beta1;
-    h.omb2 = 1.0f - beta2;
-    h.eps = eps;
-    const double bc1 = 1.0 - pow(double(beta1), double(t));
-    const double bc2 = 1.0 - pow(double(beta2), double(t));
-    h.step_size = float(lr / bc1);
-    h.inv_sqrt_bc2 = float(1.0 / sqrt(bc2));
-    h.lr_wd = float(lr * double(wd));
-    *out = h;
-}
-__global__ void sgdm_hyper_prepare_kernel(const float* lr_dev, float momentum, Hyper* out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    Hyper h{};
-    h.beta1 = momentum;
-    h.step_size = *lr_dev;
-    *out = h;
-}
-
-struct Segment {        // a run of workgroups that work on one tensor
-    int wg_begin;       // first workgroup of the run, in its kind's numbering
-    int tensor;         // index into the tensor table
-};
-
-// Tensors per kind in one phase; the tables travel as kernel arguments (3 KiB of the 4 KiB a launch may carry).
-// As many as fit: sets of a few hundred small tensors run fastest as a single group (the 108 M-parameter set of 197
-// tensors: 0.361 ms per step as one group against 0.397 as two with their passes overlapped).
-constexpr int kMaxSeg = 192;
-
-struct Phase {
-    const Tensor4Table* tensors;
-    int n_seg_a, n_seg_b;
-    int n_a, n_b;           // workgroups of each kind
-    Segment seg_a[kMaxSeg];
-    Segment seg_b[kMaxSeg];
-};
-
-static_assert(sizeof(Phase) + sizeof(HyperArg) <= 4000, "kernel arguments of a phase launch");
-
-// the hyper-parameters as they apply to one tensor of a plan
-__device__ __forceinline__ Hyper for_tensor(const Hyper& h, const Tensor4& a) {
-    Hyper t = h;
-    if (a.no_decay) t.lr_wd = 0.0f;
-    return t;
-}
-
-// last segment whose first workgroup is <= wg (segments are sorted by wg_begin, seg[0].wg_begin = 0;
-// a uniform binary search on scalar registers)
-__device__ __forceinline__ Segment find_segment(const Segment* seg, int n_seg, int wg) {
-    int lo = 0, hi = n_seg;                 // answer in [lo, hi)
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (seg[mid].wg_begin <= wg) lo = mid; else hi = mid;
-    }
-    return seg[lo];
-}
-
-// ROLES: 0 = A and B work interleaved in one launch; 1 = A work only; 2 = B work only; 3 = A work
-// only of a group without rank-1 tensors (block-wise and fp32-state tensors: no pass-1 code).  The
-// single-role kernels exist because a kernel's register and LDS footprint is that of its heaviest
-// path: launched on their own (on a second stream), the light pass-2 workgroups fit into the
-// register space that the resident pass-1 workgroups leave free.
-template <bool BF16, int ROLES>
-__global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const HyperArg ha) {
-    const Hyper h = resolve(ha);
-    const int x = logical_wg();
-    constexpr bool kOnlyA = ROLES == 1 || ROLES == 3;
-    const int n = (ROLES == 2 ? 0 : ph.n_a) + (kOnlyA ? 0 : ph.n_b);
-    if (x >= n) return;
-    // B workgroups sit at the positions where floor(x * n_b / n) steps up
-    const int b_before = kOnlyA ? 0 : (ROLES == 2 ? x : int((int64_t(x) * ph.n_b) / n));
-    const int b_after = kOnlyA ? 0 : (ROLES == 2 ? x + 1 : int((int64_t(x + 1) * ph.n_b) / n));
-    if (!kOnlyA && b_after > b_before) {
-        __shared__ int s_last;
-        const Segment sg = find_segment(ph.seg_b, ph.n_seg_b, b_before);
-        const Tensor4 a = from_table(ph.tensors[sg.tensor]);
-        const int wg = b_before - sg.wg_begin;
-        if (a.kind == kQuantFast) pass2_fast_tile<BF16>(a, h, wg);
-        else pass2_general_tile<BF16>(a, h, wg);
-        publish_if_last(a, wg, a.n_wg2, s_last);
-    } else if (ROLES != 2) {
-        __shared__ Lds s;
-        const int xa = x - b_before;
-        const Segment sg = find_segment(ph.seg_a, ph.n_seg_a, xa);
-        const Tensor4 a = from_table(ph.tensors[sg.tensor]);
-        const Hyper ht = for_tensor(h, a);
-        const int wg = xa - sg.wg_begin;
-        if (a.kind == kFp32State) {
-            adamw32_tile<BF16>(a.p, a.g, reinterpret_cast<float*>(a.mq), reinterpret_cast<float*>(a.vq), a.P, ht, wg);
-        } else if (a.kind == kQuantBlockV) {
-            b128_work<BF16>(a, ht, wg, s);
-        } else if (ROLES == 3) {
-            // not reached: the host launches this variant only for groups without rank-1 tensors
-        } else if (a.kind == kQuantFast) {
-            if (a.flat) pass1_flat_tile<BF16>(a, ht, wg, s);
-            else pass1_fast_tile<BF16, false>(a, ht, wg, s);
-        } else {
-            pass1_general_tile<BF16>(a, ht, wg, s);
-        }
-    }
-}
-
-// =====================================================================================================
-// Rank-1 normalization of a tensor with more than two dimensions (App. F Alg. 4): one statistic per
-// index of every dimension, an element's scale is the minimum of its statistics.  Seen as a matrix of
-// d_1 rows and d_2 * ... * d_p columns, the scale is min(mu_1[i], colscale[col]) with colscale[col] =
-// min over the other dimensions of their statistic at the column's index: the two passes of the
-// matrix step run unchanged on (mu_1, colscale), and two small kernels between them turn the column
-// maxima of v_t into the new statistics (reduce) and those into the new colscale (expand).
-// =====================================================================================================
-
-constexpr int kMaxInnerDims = 7;
-
-struct InnerDims {                  // dimensions 2..p
-    int n;
-    int64_t d[kMaxInnerDims];       // sizes
-    int64_t first[kMaxInnerDims];   // where each dimension's statistics start in the statistics array
-};
-
-// One workgroup per statistic: mu_new[first[r] + j] = max of colmax over the columns whose index in inner
-// dimension r is j (cols / d_r of them: col = a * d_r * inner + j * inner + b).  No atomics: with a small
-// dimension (a 3 x 3 kernel) thousands of columns share a statistic, and atomics on one address queue up.
-// `stat` = which statistic this workgroup computes (0 .. d_2 + ... + d_p - 1).
-__device__ __forceinline__ void nd_reduce_one(const float* colmax, float* mu_new, int64_t cols, const InnerDims& dm,
-                                              int64_t stat, float* s_part) {
-    int r = 0;
-    int64_t j = stat;
-    while (r < dm.n - 1 && j >= dm.d[r]) { j -= dm.d[r]; ++r; }
-    int64_t inner = 1;
-    for (int q = r + 1; q < dm.n; ++q) inner *= dm.d[q];
-    const int64_t count = cols / dm.d[r];
-    float m = 0.0f;
-    for (int64_t k = threadIdx.x; k < count; k += kThreads) {
-        const int64_t a = k / inner, b = k - a * inner;
-        m = fmaxf(m, colmax[(a * dm.d[r] + j) * inner + b]);
-    }
-    m = row16_allmax(m);                    // values are >= +0
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
-    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) mu_new[dm.first[r] + j] = fmaxf(fmaxf(s_part[0], s_part[1]), fmaxf(s_part[2], s_part[3]));
-}
-
-// colscale[col] = min over the inner dimensions of mu[first[r] + idx_r(col)]
-__device__ __forceinline__ void nd_expand_one(const float* mu, float* colscale, int64_t cols, const InnerDims& dm,
-                                              int64_t col) {
-    if (col >= cols) return;
-    int64_t rest = col;
-    float m = 0.0f;
-    for (int r = dm.n - 1; r >= 0; --r) {
-        const int64_t idx = rest % dm.d[r];
-        rest /= dm.d[r];
-        const float v = mu[dm.first[r] + idx];
-        m = (r == dm.n - 1) ? v : fminf(m, v);
-    }
-    colscale[col] = m;
-}
-
-__global__ __launch_bounds__(kThreads) void nd_reduce_kernel(const float* colmax, float* mu_new, int64_t cols,
-                                                             const InnerDims dm) {
-    __shared__ float s_part[kThreads / 64];
-    nd_reduce_one(colmax, mu_new, cols, dm, blockIdx.x, s_part);
-}
-
-__global__ __launch_bounds__(kThreads) void nd_expand_kernel(const float* mu, float* colscale, int64_t cols,
-                                                             const InnerDims dm) {
-    nd_expand_one(mu, colscale, cols, dm, int64_t(blockIdx.x) * kThreads + threadIdx.x);
-}
-
-// The two small kernels between the passes for all tensors with more than two dimensions of one group of a plan.
-struct NdPhase {
-    const Tensor4Table* tensors;
-    const InnerDims* dims;          // device table, indexed by Tensor4::nd_index
-    int n_seg, n_r, n_e;            // tensors; workgroups of the reduce and of the expand kernel
-    Segment seg_r[kMaxSeg];         // per tensor: first workgroup of the reduce kernel (one per statistic)
-    Segment seg_e[kMaxSeg];         // per tensor: first workgroup of the expand kernel (one per 256 columns)
-};
-
-static_assert(sizeof(NdPhase) <= 4000, "kernel arguments of the reduce / expand launches");
-
-__global__ __launch_bounds__(kThreads) void nd_plan_reduce(const NdPhase ph) {
-    __shared__ float s_part[kThreads / 64];
-    const int x = blockIdx.x;
-    if (x >= ph.n_r) return;
-    const Segment sg = find_segment(ph.seg_r, ph.n_seg, x);
-    const Tensor4 a = from_table(ph.tensors[sg.tensor]);
-    const InnerDims dm = ph.dims[a.nd_index];
-    nd_reduce_one(a.c_new, a.c_new + a.cols, a.cols, dm, x - sg.wg_begin, s_part);
-}
-
-__global__ __launch_bounds__(kThreads) void nd_plan_expand(const NdPhase ph) {
-    const int x = blockIdx.x;
-    if (x >= ph.n_e) return;
-    const Segment sg = find_segment(ph.seg_e, ph.n_seg, x);
-    const Tensor4 a = from_table(ph.tensors[sg.tensor]);
-    const InnerDims dm = ph.dims[a.nd_index];
-    nd_expand_one(a.c_new + a.cols, a.c_new, a.cols, dm, int64_t(x - sg.wg_begin) * kThreads + threadIdx.x);
-}
-
-// The reduce and totals steps for all tensors with deterministic sums of one group of a plan.
-struct DetPhase {
-    const Tensor4Table* tensors;
-    int n_seg, n_r;                 // tensors; workgroups of the reduce kernel
-    Segment seg_r[kMaxSeg];         // per tensor: first workgroup of the reduce kernel
-};
-
-__global__ __launch_bounds__(kThreads) void factor_plan_reduce(const DetPhase ph) {
-    __shared__ float s_part[kThreads / 64];
-    const int x = blockIdx.x;
-    if (x >= ph.n_r) return;
-    const Segment sg = find_segment(ph.seg_r, ph.n_seg, x);
-    factor_reduce_one(from_table(ph.tensors[sg.tensor]), x - sg.wg_begin, s_part);
-}
-
-__global__ __launch_bounds__(kThreads) void factor_plan_totals(const DetPhase ph) {
-    __shared__ float s_part[kThreads / 64];
-    if (int(blockIdx.x) >= ph.n_seg) return;
-    factor_totals_one(from_table(ph.tensors[ph.seg_r[blockIdx.x].tensor]), s_part);
-}
-
-// The same for a plan whose 2-dimensional tensors keep a factorized second moment: "A" work is the
-// statistics pass (next to block-wise and fp32-state tensors, which are complete after it), "B" work
-// the update pass.  ROLES: 0 = both interleaved, 1 = A only, 2 = B only.  Separate kernels, so that the
-// rank-1 kernels above keep their register footprint.
-template <bool BF16, int ROLES>
-__global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, const HyperArg ha) {
-    const Hyper h = resolve(ha);
-    __shared__ Lds s;
-    const int x = logical_wg();
-    const int n = (ROLES == 2 ? 0 : ph.n_a) + (ROLES == 1 ? 0 : ph.n_b);
-    if (x >= n) return;
-    const int b_before = ROLES == 1 ? 0 : (ROLES == 2 ? x : int((int64_t(x) * ph.n_b) / n));
-    const int b_after = ROLES == 1 ? 0 : (ROLES == 2 ? x + 1 : int((int64_t(x + 1) * ph.n_b) / n));
-    if (ROLES != 1 && b_after > b_before) {
-        __shared__ int s_last;
-        const Segment sg = find_segment(ph.seg_b, ph.n_seg_b, b_before);
-        const Tensor4 a = from_table(ph.tensors[sg.tensor]);
-        const Hyper ht = for_tensor(h, a);
-        const int wg = b_before - sg.wg_begin;
-        if (a.kind == kFactorFast) {
-            factor_update_tile<BF16>(a, ht, wg, s);
-        } else {
-            load_tables(s);
-            factor_update_general_tile<BF16>(a, ht, wg, s);
-        }
-        factor_publish_if_last(a, h, wg, a.n_wg2, s_last);
-    } else if (ROLES != 2) {
-        const int xa = x - b_before;
-        const Segment sg = find_segment(ph.seg_a, ph.n_seg_a, xa);
-        const Tensor4 a = from_table(ph.tensors[sg.tensor]);
-        const int wg = xa - sg.wg_begin;
-        const Hyper ht = for_tensor(h, a);
-        if (a.kind == kFp32State)
-            adamw32_tile<BF16>(a.p, a.g, reinterpret_cast<float*>(a.mq), reinterpret_cast<float*>(a.vq), a.P, ht, wg);
-        else if (a.kind == kQuantBlockV) b128_work<BF16>(a, ht, wg, s);
-        else if (a.kind == kFactorFast) factor_stats_tile<BF16>(a, wg, s);
-        else factor_stats_general_tile<BF16>(a, wg, a.n_wg, s);
-    }
-}
-
-// A plan of SGD-with-momentum tensors (App. E Alg. 2): everything is one pass, so only "A" work exists.
-template <bool BF16>
-__global__ __launch_bounds__(kThreads) void sgdm_phase_kernel(const Phase ph, const HyperArg ha) {
-    const Hyper h = resolve(ha);
-    __shared__ Lds s;
-    const int x = logical_wg();
-    if (x >= ph.n_a) return;
-    const Segment sg = find_segment(ph.seg_a, ph.n_seg_a, x);
-    const Tensor4 a = from_table(ph.tensors[sg.tensor]);
-    const int wg = x - sg.wg_begin;
-    if (a.kind == kSgdmFp32) sgdm32_tile<BF16>(a.p, a.g, reinterpret_cast<float*>(a.mq), a.P, h, wg);
-    else b128_work<BF16, true>(a, h, wg, s);
-}
-
-// =====================================================================================================
-// The zero state.
-// =====================================================================================================
-
-// fill `n` bytes at dst with `value`, and force the byte at index `last_index` (if >= 0) to `last`
-__global__ __launch_bounds__(kThreads) void fill_bytes_kernel(uint8_t* dst, int64_t n, uint8_t value,
-                                                              int64_t last_index, uint8_t last) {
-    const int64_t stride = int64_t(gridDim.x) * kThreads;
-    for (int64_t i = int64_t(blockIdx.x) * kThreads + threadIdx.x; i < n; i += stride)
-        dst[i] = (i == last_index) ? last : value;
 }
 
 }  // namespace lpmm

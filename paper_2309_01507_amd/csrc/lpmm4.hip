@@ -13,7 +13,7 @@
 #include <vector>
 
 #include "../../include/lpmm4.h"
-#include "kernels.hpp"
+#include "launch.hpp"
 #include "convert.hpp"
 #include "ablation.hpp"
 
@@ -119,6 +119,7 @@ int current_ctx(DeviceCtx** out) {
     return LPMM_OK;
 }
 
+bool is_rank1(int kind) { return kind == kQuantFast || kind == kQuantRagged || kind == kQuantGeneral; }
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 int pad8(int64_t n) { return int(round_up(n, kXcds)); }
 
@@ -245,18 +246,104 @@ void general_geometry(Tensor4* a, int n_cu) {
     a->n_wg2 = int(chunks);
 }
 
+// Matrices that miss the fast path but have at least one block per row take the ragged tiles (general / ragged, us per
+// step: 4096 x 4000 bf16 419 / 60, 30000 x 1000 fp32 291 / 153, 2304 x 576 fp32 31 / 24, 300 x 200 fp32 14.4 / 13.5).
+// Narrower ones stay on the general path: there a block touches several rows, and combining an element's row maximum
+// is most of the work.
+bool ragged_eligible(int64_t rows, int64_t cols) {
+    return cols >= LPMM_BLOCK && cols < (int64_t(1) << 24) && rows * cols <= (int64_t(1) << 37) &&
+           !env_int("LPMM_FORCE_GENERAL", 0);
+}
+
+// Tiling of the ragged path (see ragged.hpp).
+// Pass 1, one strip: a tile touches every column, so every tile ends with an atomic per column, and atomics on one
+// address follow each other at about 18 ns (measured: 648 tiles of a 2304 x 576 tensor took 31 us, whatever they held).
+// With T tiles that is 18 ns x T against blocks / (8 T) units of about half a microsecond one after the other in a
+// group: T = sqrt(3.5 x blocks) balances the two, in tiles of 8 to 128 blocks (a power of two).
+// Wider: strips of equal width, at most 1024 columns, by 32 rows; the rows are halved down to one per group and then
+// the strips down to 256 columns while the tensor would give the chip fewer than two workgroups per CU (n_cu = 0: `shrink` halvings
+// of the rows instead, for plans).
+// Pass 2: strips of 256 columns by 64 rows (plans: 128), halved down to 4 in the same way; a multiple of 4.
+void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
+    a->kind = kQuantRagged;
+    a->nb = int(a->P / LPMM_BLOCK);
+    const int tail = (a->P % LPMM_BLOCK) ? 1 : 0;
+    constexpr int64_t kWide = kFlatBlocks * LPMM_BLOCK;
+    if (a->cols <= kWide) {
+        a->strips = 1;
+        a->sw = int(a->cols);
+        const double tiles = std::sqrt(3.5 * double(a->nb));
+        int64_t rw = 128;
+        while (rw > kGroups && double(rw) * tiles > double(a->nb) * 1.4) rw /= 2;
+        a->rw = int(rw);
+        a->n_wg = int((a->nb + rw - 1) / rw) + tail;
+    } else {
+        int64_t rw = 32, sw = kWide, tiles;
+        while (rw > kGroups && rw * a->cols > (int64_t(1) << 28)) rw /= 2;        // byte offsets inside a tile stay below 2^30
+        for (int k = 0; k < shrink && rw > kGroups; ++k) rw /= 2;
+        for (;;) {
+            const int64_t want = (a->cols + sw - 1) / sw;
+            a->sw = int(round_up((a->cols + want - 1) / want, LPMM_BLOCK));
+            a->strips = int((a->cols + a->sw - 1) / a->sw);
+            tiles = a->strips * ((a->rows + rw - 1) / rw);
+            if (tiles >= 2 * int64_t(n_cu)) break;
+            if (rw > kGroups) rw /= 2;
+            else if (sw > 256) sw /= 2;
+            else break;
+        }
+        a->rw = int(rw);
+        a->n_wg = int(tiles) + tail;
+    }
+    a->strips2 = int((a->cols + 255) / 256);
+    const int64_t rows2 = pass2_rows(*a, true);
+    int64_t rw2 = n_cu ? 64 : std::max<int64_t>(128 >> shrink, kWaves);
+    while (rw2 > kWaves && rw2 * a->cols >= (int64_t(1) << 29)) rw2 /= 2;
+    while (n_cu && rw2 > kWaves && a->strips2 * ((rows2 + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 /= 2;
+    a->rw2 = int(rw2);
+    a->rs2 = 0;
+    a->n_wg2 = int(a->strips2 * ((rows2 + rw2 - 1) / rw2));
+    if (rows2 != a->rows) a->n_wg2 += int((a->P - pass2_last_row_begin(*a) + kLastRowElems - 1) / kLastRowElems);
+}
+
+// pass 1 or 2 of the rank-1 step on one tensor
 template <bool BF16>
-int launch_step(const Tensor4& t, const Hyper& h, bool fast, hipStream_t s) {
+void launch_pass(int pass, const Tensor4& t, const Hyper& h, hipStream_t s) {
+    const int n = pass == 1 ? t.n_wg : t.n_wg2;
+    const dim3 grid(t.kind == kQuantGeneral ? n : pad8(n)), block(kThreads);
+    if (t.kind == kQuantFast) {
+        if (pass == 1) hipLaunchKernelGGL(pass1_fast<BF16>, grid, block, 0, s, t, h);
+        else hipLaunchKernelGGL(pass2_fast<BF16>, grid, block, 0, s, t, h);
+    } else if (t.kind == kQuantRagged) {
+        if (pass == 1) hipLaunchKernelGGL(pass1_ragged_kernel<BF16>, grid, block, 0, s, t, h);
+        else hipLaunchKernelGGL(pass2_ragged_kernel<BF16>, grid, block, 0, s, t, h);
+    } else {
+        if (pass == 1) hipLaunchKernelGGL(pass1_general<BF16>, grid, block, 0, s, t, h);
+        else hipLaunchKernelGGL(pass2_general<BF16>, grid, block, 0, s, t, h);
+    }
+}
+
+// tiling of one rank-1 tensor stepped on its own
+void rank1_geometry(Tensor4* t, int n_cu, int grad_bytes) {
+    if (fast_eligible(t->cols, t->c)) {
+        t->kind = kQuantFast;
+        fast_geometry(t, n_cu, 0, 0, grad_bytes);
+    } else if (ragged_eligible(t->rows, t->cols)) {
+        ragged_geometry(t, n_cu, 0);
+    } else {
+        t->kind = kQuantGeneral;
+        general_geometry(t, n_cu);
+    }
+}
+
+template <bool BF16>
+int launch_step(const Tensor4& t, const Hyper& h, hipStream_t s) {
     const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls;
     const int64_t call = g_prof.calls;
     if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), s));
-    const int grid = fast ? pad8(t.n_wg) : t.n_wg;
-    if (fast) hipLaunchKernelGGL(pass1_fast<BF16>, dim3(grid), dim3(kThreads), 0, s, t, h);
-    else hipLaunchKernelGGL(pass1_general<BF16>, dim3(grid), dim3(kThreads), 0, s, t, h);
+    launch_pass<BF16>(1, t, h, s);
     LPMM_HIP(hipGetLastError());
     if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 1), s));
-    if (fast) hipLaunchKernelGGL(pass2_fast<BF16>, dim3(pad8(t.n_wg2)), dim3(kThreads), 0, s, t, h);
-    else hipLaunchKernelGGL(pass2_general<BF16>, dim3(t.n_wg2), dim3(kThreads), 0, s, t, h);
+    launch_pass<BF16>(2, t, h, s);
     LPMM_HIP(hipGetLastError());
     if (rec) {
         LPMM_HIP(hipEventRecord(prof_event(call, 2), s));
@@ -333,11 +420,8 @@ int step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, float*
     t.rows = rows;
     t.cols = cols;
     t.P = rows * cols;
-    const bool fast = fast_eligible(cols, v_colmax);
-    t.kind = fast ? kQuantFast : kQuantGeneral;
-    if (fast) fast_geometry(&t, ctx->n_cu, 0, 0, bf16 ? 2 : 4);
-    else general_geometry(&t, ctx->n_cu);
-    return bf16 ? launch_step<true>(t, h, fast, s) : launch_step<false>(t, h, fast, s);
+    rank1_geometry(&t, ctx->n_cu, bf16 ? 2 : 4);
+    return bf16 ? launch_step<true>(t, h, s) : launch_step<false>(t, h, s);
 }
 
 int b128_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, float* m_blockscale,
@@ -492,27 +576,20 @@ int nd_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, flo
     t.rows = rows;
     t.cols = cols;
     t.P = rows * cols;
-    const bool fast = fast_eligible(cols, v_col);
-    t.kind = fast ? kQuantFast : kQuantGeneral;
-    if (fast) fast_geometry(&t, ctx->n_cu, 0, 0, bf16 ? 2 : 4);
-    else general_geometry(&t, ctx->n_cu);
+    rank1_geometry(&t, ctx->n_cu, bf16 ? 2 : 4);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int grid = fast ? pad8(t.n_wg) : t.n_wg;
-    const int grid_cols = grid_for(cols, 1);
-#define LPMM_ND_LAUNCH(B)                                                                                         \
-    if (fast) hipLaunchKernelGGL(pass1_fast<B>, dim3(grid), dim3(kThreads), 0, s, t, h);                          \
-    else hipLaunchKernelGGL(pass1_general<B>, dim3(grid), dim3(kThreads), 0, s, t, h);                            \
-    LPMM_HIP(hipGetLastError());                                                                                  \
-    hipLaunchKernelGGL(nd_reduce_kernel, dim3(int(ext)), dim3(kThreads), 0, s, t.c_new, t.c_new + cols, cols, dm);  \
-    LPMM_HIP(hipGetLastError());                                                                                  \
-    hipLaunchKernelGGL(nd_expand_kernel, dim3(grid_cols), dim3(kThreads), 0, s, t.c_new + cols, t.c_new, cols, dm); \
-    LPMM_HIP(hipGetLastError());                                                                                  \
-    if (fast) hipLaunchKernelGGL(pass2_fast<B>, dim3(pad8(t.n_wg2)), dim3(kThreads), 0, s, t, h);                 \
-    else hipLaunchKernelGGL(pass2_general<B>, dim3(t.n_wg2), dim3(kThreads), 0, s, t, h);                         \
+    auto pass = [&](int p) -> int {
+        if (bf16) launch_pass<true>(p, t, h, s); else launch_pass<false>(p, t, h, s);
+        LPMM_HIP(hipGetLastError());
+        return LPMM_OK;
+    };
+    rc = pass(1);
+    if (rc) return rc;
+    hipLaunchKernelGGL(nd_reduce_kernel, dim3(int(ext)), dim3(kThreads), 0, s, t.c_new, t.c_new + cols, cols, dm);
     LPMM_HIP(hipGetLastError());
-    if (bf16) { LPMM_ND_LAUNCH(true) } else { LPMM_ND_LAUNCH(false) }
-#undef LPMM_ND_LAUNCH
-    return LPMM_OK;
+    hipLaunchKernelGGL(nd_expand_kernel, dim3(grid_for(cols, 1)), dim3(kThreads), 0, s, t.c_new + cols, t.c_new, cols, dm);
+    LPMM_HIP(hipGetLastError());
+    return pass(2);
 }
 
 // Tiling of a tensor with a factorized second moment: the statistics pass is tiled like pass 2 and is the
@@ -1343,6 +1420,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             factor_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1);
         } else if (t.kind == kQuantFast) {
             fast_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, plan_flat && t.P >= kFlatMinElems);
+        } else if (t.kind == kQuantRagged) {
+            ragged_geometry(&t, 0, shrink);
         }
     };
     int64_t fofs = 0;
@@ -1439,6 +1518,9 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
                 t.kind = kQuantFast;
                 set_geometry(t, d, 0);
                 if (t.flat) host->flat = true;
+            } else if (ragged_eligible(d.rows, d.cols)) {
+                t.kind = kQuantRagged;
+                set_geometry(t, d, 0);
             } else {
                 t.kind = kQuantGeneral;
                 general_geometry(&t, ctx->n_cu);
@@ -1465,7 +1547,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             bool two_pass = false;
             for (int64_t i = gr.first; i < gr.second; ++i) {
                 n_a += tens[i].n_wg;
-                const bool has_b = tens[i].kind == kQuantFast || tens[i].kind == kQuantGeneral ||
+                const bool has_b = is_rank1(tens[i].kind) ||
                                    tens[i].kind == kFactorFast || tens[i].kind == kFactorGeneral;
                 if (has_b) { n_b += tens[i].n_wg2; two_pass = true; }
             }
@@ -1479,7 +1561,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         if (j < groups.size())
             for (int64_t i = groups[j].first; i < groups[j].second; ++i) {
                 pl.ph.seg_a[pl.ph.n_seg_a++] = Segment{pl.ph.n_a, int(i)};
-                if (tens[i].kind == kQuantFast || tens[i].kind == kQuantGeneral) pl.a_has_rank1 = true;
+                if (is_rank1(tens[i].kind)) pl.a_has_rank1 = true;
                 pl.ph.n_a += tens[i].n_wg;
             }
         if (j >= 1)
@@ -1494,7 +1576,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
                     pl.det.seg_r[pl.det.n_seg++] = Segment{pl.det.n_r, int(i)};
                     pl.det.n_r += int((tens[i].rows + kThreads - 1) / kThreads + (tens[i].cols + 63) / 64);
                 }
-                if (tens[i].nd_index >= 0 && (tens[i].kind == kQuantFast || tens[i].kind == kQuantGeneral)) {
+                if (tens[i].nd_index >= 0 && is_rank1(tens[i].kind)) {
                     pl.has_nd = true;
                     pl.nd.seg_r[pl.nd.n_seg] = Segment{pl.nd.n_r, int(i)};
                     pl.nd.seg_e[pl.nd.n_seg] = Segment{pl.nd.n_e, int(i)};

@@ -1,0 +1,320 @@
+// Pass 1 of the rank-1 step for matrices whose rows are no multiple of 128 elements long (or whose column maxima
+// are not 16-byte aligned).  First-moment blocks are 128 elements of the row-major FLATTENING, so here they start
+// anywhere in a row and may straddle the end of one.
+//
+// What bounds the step is memory, as on the fast path, so the work unit is the fast path's: 32 lanes own one block, 4
+// consecutive elements per lane, and every access is aligned because blocks start at multiples of 128 elements.  A
+// block belongs to the row and to the strip of columns in which it STARTS.  Positions inside a tile are counted from
+// the strip's first column, p = 0 .. width + 127: a block that starts in the strip may reach up to 127 columns beyond
+// it, and beyond the end of the row position p continues with the next row's first columns.  The strip's old column
+// maxima and the running new ones sit in LDS indexed by p, so only the row of an element needs a compare per element.
+// (Before, a lane owned 8 elements, tracked row and column of each with 64-bit arithmetic, divided exactly, and for
+// more than 2048 columns sent every maximum to a global atomic: 554 + 225 us for 1024 x 50257 with bf16 gradients, now
+// 120 + 55 us, 4.9 TB/s in this pass.)
+//
+// Two ways to cut a matrix (chosen by the host):
+//   cols <= 1024:  one strip; a tile is a run of a.rw consecutive blocks, each of the 8 groups of a workgroup takes an
+//                  eighth of the run.  Every unit is a whole block, whatever the row length.
+//   wider:         strips of a.sw columns (a multiple of 128, at most 1024) x a.rw rows; a group walks along the blocks
+//                  of its row that start in the strip.  In the last strip their number varies by one from row to row;
+//                  a unit that does not exist gets an offset beyond the tile, where loads return zeros and stores are
+//                  dropped.
+// The partial last block of a tensor whose size is no multiple of 128 is left to one workgroup of the general path.
+// (Pass 2 needs none of this: nothing in it is reduced over a block, see pass2_tile.)
+#pragma once
+
+#include "kernels.hpp"
+
+namespace lpmm {
+
+constexpr int kRagRowSlots = kMaxRowSlots / 2;            // s.blk_vmax: old row maxima, then the new ones
+constexpr uint32_t kRagNowhere = 0x7FFFFF00u;             // a byte offset beyond every tile (also after >> 1 and >> 3)
+
+struct RagTile {
+    int64_t e0;          // first element of the tile's first block (a multiple of 128)
+    int64_t row0;        // row of position 0 of the tile's first row
+    int f0;              // first row's position 0, relative to e0
+    int n_blocks;        // contiguous tiling: blocks of the tile
+    int n_rows;          // rows whose statistics the tile touches (one more than it owns where blocks straddle)
+    int own_rows;        // strip tiling: rows of the tile
+    int c0, width;       // the strip's first column and its width
+    int lim;             // positions at or beyond this belong to the next row
+    int per_row;         // strip tiling: units per row
+    int end;             // strip tiling: blocks of the tensor behind e0
+    uint32_t inv_cols;   // contiguous tiling: x / cols == umulhi(x, inv_cols) for the positions of a tile
+    uint32_t bytes4;     // bytes of the tile in an fp32 array (its whole blocks)
+};
+
+struct RagUnit {         // one block
+    uint32_t off4;       // byte offset of the block in the tile's fp32 array, kRagNowhere if it does not exist
+    int il;              // its row in the tile
+    int p;               // position of its first element in that row
+    int slot;            // its slot among the staged block scales
+};
+
+template <bool ONE_STRIP>
+__device__ __forceinline__ RagTile rag_tile(const Tensor4& a, int wg) {
+    RagTile t;
+    const int64_t nb = a.nb;                                             // whole blocks of the tensor
+    if constexpr (ONE_STRIP) {
+        const int64_t b0 = int64_t(wg) * a.rw;
+        t.n_blocks = nb - b0 < a.rw ? int(nb - b0) : a.rw;
+        t.e0 = b0 * 128;
+        t.row0 = t.e0 / a.cols;
+        t.f0 = int(t.row0 * a.cols - t.e0);                              // <= 0
+        t.c0 = 0;
+        t.width = t.lim = int(a.cols);
+        t.inv_cols = uint32_t((uint64_t(1) << 32) / uint32_t(a.cols)) + 1u;
+        t.n_rows = int((uint32_t(t.n_blocks) * 128u - uint32_t(t.f0) - 1u) / uint32_t(a.cols)) + 1;
+        t.own_rows = t.per_row = t.end = 0;
+        t.bytes4 = uint32_t(t.n_blocks) * 512u;
+    } else {
+        const int strip = wg % a.strips;
+        t.row0 = int64_t(wg / a.strips) * a.rw;
+        t.own_rows = a.rows - t.row0 < a.rw ? int(a.rows - t.row0) : a.rw;
+        t.n_rows = t.own_rows + 1;
+        t.c0 = strip * a.sw;
+        t.lim = int(a.cols) - t.c0;
+        t.width = t.lim < a.sw ? t.lim : a.sw;
+        const int64_t f = t.row0 * a.cols + t.c0;
+        t.e0 = (f + 127) / 128 * 128;
+        t.f0 = int(f - t.e0);                                            // -127 .. 0
+        t.per_row = (t.width + 127) / 128;
+        const int64_t left = nb - t.e0 / 128;                            // may be negative: no whole block starts here
+        t.end = int(left < (1 << 24) ? (left > 0 ? left : 0) : (1 << 24));
+        t.inv_cols = 0;
+        t.n_blocks = 0;
+        // the blocks that start before the end of the tile's last row of the strip
+        const int64_t last = (int64_t(t.own_rows - 1) * a.cols + t.f0 + t.width + 127) >> 7;
+        t.bytes4 = uint32_t(last < t.end ? last : t.end) * 512u;
+    }
+    return t;
+}
+
+// unit q of group grp, in the order the group takes them
+template <bool ONE_STRIP>
+__device__ __forceinline__ RagUnit rag_unit(const RagTile& t, const Tensor4& a, int grp, int q) {
+    RagUnit u;
+    if constexpr (ONE_STRIP) {
+        const int run = a.rw / kGroups;
+        const int b = grp * run + q;
+        const bool ok = q < run && b < t.n_blocks;
+        const uint32_t x = ok ? uint32_t(b) * 128u - uint32_t(t.f0) : 0u;
+        u.il = int(__umulhi(x, t.inv_cols));
+        u.p = int(x) - u.il * t.width;
+        u.off4 = ok ? uint32_t(b) * 512u : kRagNowhere;
+        u.slot = b;
+    } else {
+        const int k = int((uint32_t(q) * ((65536u + uint32_t(t.per_row) - 1u) / uint32_t(t.per_row))) >> 16);   // q / per_row
+        const int j = q - k * t.per_row;
+        u.il = k * kGroups + grp;
+        const int f = t.f0 + int(row_offset(u.il, a.cols, 0u));          // < 2^29 for rows of the tile
+        const int b = ((f + 127) >> 7) + j;
+        u.p = b * 128 - f;
+        const bool ok = u.il < t.own_rows && u.p < t.width && b < t.end;
+        u.off4 = ok ? uint32_t(b) * 512u : kRagNowhere;
+        u.slot = u.il * kFlatBlocks + j;
+    }
+    return u;
+}
+// units a group runs through (the same for all groups of the workgroup)
+template <bool ONE_STRIP>
+__device__ __forceinline__ int rag_units(const RagTile& t, const Tensor4& a) {
+    if constexpr (ONE_STRIP) return a.rw / kGroups;
+    else return (t.own_rows + kGroups - 1) / kGroups * t.per_row;
+}
+
+// the four column-vector entries of a lane: position p of the strip, 4-byte aligned
+__device__ __forceinline__ void lds_load4(const float* s, float out[4]) {
+    typedef float v4f_l __attribute__((ext_vector_type(4), aligned(4)));
+    const v4f_l v = *reinterpret_cast<const v4f_l*>(s);
+    out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
+}
+__device__ __forceinline__ int rag_col(const RagTile& t, int64_t cols, int p) { return p < t.lim ? t.c0 + p : p - t.lim; }
+
+// codes of 4 first moments against their block's scale (see pass1_row)
+__device__ __forceinline__ uint32_t compress_m4(const SearchEntry* s_search, const float mt[4], float s_new) {
+    uint32_t q = 0, dist = scale_is_tame(s_new) ? 0xFFFFFFFFu : 0u;
+    const float inv_s = approx_inv(s_new);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint32_t d;
+        q |= quant_m_code_fast(s_search, mt[e], inv_s, d) << (4 * e);
+        dist = min(dist, d);
+    }
+    if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
+        q = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q |= quant_m_code(s_search, mt[e], s_new) << (4 * e);
+    }
+    return q;
+}
+
+template <bool BF16>
+__device__ __forceinline__ Row1<BF16> rag_load1(const TileBase& b, uint32_t off4) {       // off4: the lane's
+    Row1<BF16> r;
+    r.p = buf_ld_f4_stream(b.rp, off4);
+    r.g = load_grad_regs4<BF16>(b.rg, off4);
+    r.mq = buf_ld_u16(b.rmq, off4 >> 3);
+    r.vq = buf_ld_u16(b.rvq, off4 >> 3);
+    return r;
+}
+
+template <bool BF16>
+__device__ __forceinline__ TileBase rag_base(const Tensor4& a, const RagTile& t) {
+    TileBase b;
+    const int64_t e = t.e0;
+    b.ms = a.ms + e / 128;
+    b.rp = tile_rsrc(a.p + e, t.bytes4);
+    b.rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + e * (BF16 ? 2 : 4), BF16 ? t.bytes4 / 2 : t.bytes4);
+    b.rmq = tile_rsrc(reinterpret_cast<const uint8_t*>(a.mq) + (e >> 1), t.bytes4 / 8);
+    b.rvq = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (e >> 1), t.bytes4 / 8);
+    return b;
+}
+
+// One block of pass 1.  l = lane of the group.
+template <bool BF16, class Mid>
+__device__ __forceinline__ void rag_unit1(const Tensor4& a, const Hyper& h, const TileBase& tb, const RagTile& t, Lds& s,
+                                          const Row1<BF16>& cur, const RagUnit& u, int l, bool cols_tame, Mid mid) {
+    float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
+    float g[4];
+    unpack_grad4<BF16>(cur.g, g);
+    const bool ok = u.off4 != kRagNowhere;
+    // a unit that does not exist has zero gradients, and with zero scales all its moments are zero
+    const float s_old = ok ? s.blk_scale[u.slot] : 0.0f;
+    const float r_a = ok ? s.blk_vmax[u.il] : 0.0f, r_b = ok ? s.blk_vmax[u.il + 1] : 0.0f;
+    const int p4 = ok ? u.p + 4 * l : 0;
+    float mt[4], vt[4], amax = 0.0f, rmax_a = 0.0f, rmax_b = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const float2 d = s.deq[(uint32_t(cur.mq) >> (8 * k)) & 255u];
+        mt[2 * k] = d.x * s_old;
+        mt[2 * k + 1] = d.y * s_old;
+    }
+    const bool tame = bool(int(cols_tame) & int(scale_is_tame(r_a)) & int(scale_is_tame(r_b)));
+    if (__builtin_expect(__ballot(!tame) == 0, 1)) {
+        float qf[4], c16[4];
+        codes_to_float4(cur.vq, qf);
+        lds_load4(&s.cold[p4], c16);
+        const float ra16 = r_a * 0.0625f, rb16 = r_b * 0.0625f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(p4 + e < t.lim ? ra16 : rb16, c16[e]));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            vt[e] = dequant_v((uint32_t(cur.vq) >> (4 * e)) & 15u, fminf(p4 + e < t.lim ? r_a : r_b, a.c[rag_col(t, a.cols, p4 + e)]));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        mt[e] = moment_m(h, mt[e], g[e]);
+        vt[e] = moment_v(h, vt[e], g[e]);
+        w[e] = param_update(h, w[e], mt[e], vt[e]);
+        amax = fmaxf(amax, fabsf(mt[e]));
+        const bool here = p4 + e < t.lim;
+        rmax_a = max_nonneg(rmax_a, here ? vt[e] : 0.0f);
+        rmax_b = max_nonneg(rmax_b, here ? 0.0f : vt[e]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    mid();
+    __builtin_amdgcn_sched_barrier(0);
+    unsigned int* cbits = reinterpret_cast<unsigned int*>(&s.col[p4]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        (void)__hip_atomic_fetch_max(cbits + e, __float_as_uint(vt[e]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const float s_new = group32_allmax(amax);
+    rmax_a = group32_allmax(rmax_a);
+    if (__ballot(u.p + 128 > t.lim) != 0) rmax_b = group32_allmax(rmax_b);         // some block of the wave straddles rows
+    const uint32_t mq_new = compress_m4(s.search, mt, s_new);
+    store_row1(tb, ok ? u.off4 + 16u * l : kRagNowhere, w, mq_new);
+    if (l == 0 && ok) {
+        s.blk_scale[u.slot] = s_new;
+        unsigned int* rbits = reinterpret_cast<unsigned int*>(&s.blk_vmax[kRagRowSlots + u.il]);
+        (void)__hip_atomic_fetch_max(rbits, __float_as_uint(rmax_a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (u.p + 128 > t.lim)
+            (void)__hip_atomic_fetch_max(rbits + 1, __float_as_uint(rmax_b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+template <bool BF16, bool ONE_STRIP>
+__device__ __forceinline__ void pass1_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    const RagTile t = rag_tile<ONE_STRIP>(a, wg);
+    const TileBase tb = rag_base<BF16>(a, t);
+    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+    auto unit = [&](int q) { return rag_unit<ONE_STRIP>(t, a, grp, q); };
+    auto fetch = [&](const RagUnit& u) { return rag_load1<BF16>(tb, u.off4 == kRagNowhere ? kRagNowhere : u.off4 + 16u * l); };
+    const int n = rag_units<ONE_STRIP>(t, a);
+    RagUnit u0 = unit(0), u1 = unit(1), u2;
+    Row1<BF16> r0 = fetch(u0), r1 = fetch(u1), r2;
+    bool tame = true;
+    for (int k = threadIdx.x; k < t.width + 128; k += kThreads) {
+        const float c = a.c[rag_col(t, a.cols, k)];
+        tame = bool(int(tame) & int(scale_is_tame(c)));
+        s.cold[k] = c * 0.0625f;
+        s.col[k] = 0.0f;
+    }
+    for (int k = threadIdx.x; k < kRagRowSlots; k += kThreads) {
+        s.blk_vmax[k] = k < t.n_rows && t.row0 + k < a.rows ? a.r[t.row0 + k] : 0.0f;
+        s.blk_vmax[kRagRowSlots + k] = 0.0f;
+    }
+    // old block scales into the slots of the new ones
+    if constexpr (ONE_STRIP) {
+        for (int k = threadIdx.x; k < t.n_blocks; k += kThreads) s.blk_scale[k] = tb.ms[k];
+    } else {
+        for (int k = threadIdx.x; k < t.own_rows * kFlatBlocks; k += kThreads) {
+            const int b = ((t.f0 + int(row_offset(k / kFlatBlocks, a.cols, 0u)) + 127) >> 7) + k % kFlatBlocks;
+            if (k % kFlatBlocks < t.per_row && b < t.end) s.blk_scale[k] = tb.ms[b];
+        }
+    }
+    const bool cols_tame = !__syncthreads_or(int(!tame));
+    load_tables(s);
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see pass 1)
+    auto none = [] {};
+    auto work = [&](const Row1<BF16>& cur, const RagUnit& u, auto mid) { rag_unit1<BF16>(a, h, tb, t, s, cur, u, l, cols_tame, mid); };
+    int q = 0;
+    while (q + 2 < n) {                                   // rounds of three units, no exit in the middle
+        work(r0, u0, [&] { u2 = unit(q + 2); r2 = fetch(u2); });
+        work(r1, u1, [&] { u0 = unit(q + 3); r0 = fetch(u0); });
+        work(r2, u2, [&] { u1 = unit(q + 4); r1 = fetch(u1); });
+        q += 3;
+    }
+    if (q < n) {
+        work(r0, u0, none);
+        if (q + 1 < n) work(r1, u1, none);
+    }
+    __syncthreads();
+    if constexpr (ONE_STRIP) {
+        for (int k = threadIdx.x; k < t.n_blocks; k += kThreads) tb.ms[k] = s.blk_scale[k];
+    } else {
+        for (int k = threadIdx.x; k < t.own_rows * kFlatBlocks; k += kThreads) {
+            const int f = t.f0 + int(row_offset(k / kFlatBlocks, a.cols, 0u));
+            const int b = ((f + 127) >> 7) + k % kFlatBlocks;
+            if (b * 128 - f < t.width && b < t.end) tb.ms[b] = s.blk_scale[k];
+        }
+    }
+    for (int k = threadIdx.x; k < t.n_rows; k += kThreads) {
+        const float m = s.blk_vmax[kRagRowSlots + k];
+        if (m > 0.0f) atomic_max_nonneg(a.r_new + t.row0 + k, m);
+    }
+    for (int k = threadIdx.x; k < t.width + 128; k += kThreads) {
+        const float m = s.col[k];
+        if (m > 0.0f) atomic_max_nonneg(a.c_new + rag_col(t, a.cols, k), m);
+    }
+}
+
+// Workgroups [0, n_wg) of pass 1; the last one takes the partial block, if any.
+template <bool BF16>
+__device__ __forceinline__ void pass1_ragged(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    if ((a.P & 127) && wg == a.n_wg - 1) pass1_general_range<BF16>(a, h, int64_t(a.nb) * 128, a.P, s);
+    else if (a.strips == 1) pass1_ragged_tile<BF16, true>(a, h, wg, s);
+    else pass1_ragged_tile<BF16, false>(a, h, wg, s);
+}
+
+// Workgroups [0, n_wg2) of pass 2: the tiles, then the parts of the last row if the tiles leave it out.
+template <bool BF16>
+__device__ __forceinline__ void pass2_ragged(const Tensor4& a, const Hyper& h, int wg) {
+    const int tiles = int((pass2_rows(a, true) + a.rw2 - 1) / a.rw2) * a.strips2;
+    if (wg < tiles) pass2_tile<BF16, true>(a, h, wg);
+    else pass2_last_row<BF16>(a, h, wg - tiles);
+}
+
+}  // namespace lpmm

@@ -1,0 +1,87 @@
+"""The ragged tiles of the rank-1 step: rows that are no multiple of 128 elements, at the edges of the tiling -- one strip
+(up to 1024 columns) and several, rows barely longer than a block, a last strip narrower than a block, a partial last
+block, fewer rows than groups, misaligned column maxima -- against the oracle, and against the general kernels."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2309_01507_amd as lpmm
+import workloads
+from gpu_util import DEV, download_state, gpu_step, run_parity, to_dev
+
+pytestmark = pytest.mark.gpu
+
+HP = oracle.Hyper()
+
+
+@pytest.mark.parametrize("rows,cols,recipe,bf16", [
+    (300, 129, "col_lognormal", False),      # shortest rows of the path: nearly every block straddles two rows
+    (260, 147, "col_lognormal", True),
+    (1, 129, "iid", False),                  # one whole block and one element
+    (5, 1023, "iid", True),                  # one strip, few blocks
+    (700, 1000, "outlier_sparse", False),    # one strip, several tiles, zero rows, scales far apart
+    (9, 1025, "col_lognormal", True),        # two strips
+    (67, 1030, "outlier_sparse", True),
+    (40, 2049, "iid", False),                # three strips
+    (33, 8193, "col_lognormal", True),       # the last strip holds one column: rows without a block in it
+    (6, 8321, "col_lognormal", False),       # the last strip is one column wider than a block
+    (3, 50257, "iid", True),
+])
+def test_step_matches_the_oracle(rows, cols, recipe, bf16):
+    print(f"[gpu-test] ragged {rows}x{cols} {recipe} bf16={bf16}", flush=True)
+    assert run_parity(rows, cols, steps=4, recipe=recipe, bf16=bf16, seed=71) == 0
+
+
+def test_extreme_scales_take_the_exact_route():
+    """Gradients around 1e-17 and 1e17: second moments beyond the reciprocal's range in some rows and columns."""
+    for rows, cols in ((40, 300), (20, 1300)):
+        lpmm.ensure_init(rows + cols)
+        rng = np.random.default_rng(5)
+        w_ref, st_ref = workloads.weights(72, 0, rows, cols).reshape(-1), oracle.state_zero(rows, cols)
+        w, st = to_dev(w_ref.copy()), lpmm.new_state(rows, cols, DEV)
+        for t in (1, 2, 3):
+            g = rng.standard_normal((rows, cols)).astype(np.float32)
+            g[: rows // 2] *= np.float32(1e-17)
+            g[:, ::7] *= np.float32(1e17)
+            g = g.reshape(-1)
+            oracle.adamw4_step(w_ref, g, st_ref, HP, t)
+            gpu_step(w, to_dev(g), st, HP, t)
+            got = download_state(st)
+            for x, y in ((got.m_codes, st_ref.m_codes), (got.m_scales, st_ref.m_scales), (got.v_codes, st_ref.v_codes),
+                         (got.v_r, st_ref.v_r), (got.v_c, st_ref.v_c)):
+                np.testing.assert_array_equal(x, y)
+
+
+def test_misaligned_column_maxima():
+    """Rows of whole blocks whose column maxima start 4 bytes off a 16-byte boundary: the ragged path, too."""
+    rows, cols = 70, 1280
+    lpmm.ensure_init(rows + cols)
+    w_ref, st_ref = workloads.weights(73, 0, rows, cols).reshape(-1), oracle.state_zero(rows, cols)
+    w, st = to_dev(w_ref.copy()), lpmm.new_state(rows, cols, DEV)
+    st.v_colmax = torch.zeros(cols + 4, device=DEV)[1:cols + 1]
+    for t in (1, 2, 3):
+        g = workloads.grads(73, 0, t, rows, cols, "col_lognormal").reshape(-1)
+        oracle.adamw4_step(w_ref, g, st_ref, HP, t)
+        gpu_step(w, to_dev(g), st, HP, t)
+    got = download_state(st)
+    np.testing.assert_array_equal(got.v_codes, st_ref.v_codes)
+    np.testing.assert_array_equal(got.m_codes, st_ref.m_codes)
+    np.testing.assert_array_equal(got.v_c, st_ref.v_c)
+
+
+@pytest.mark.parametrize("rows,cols,bf16", [(1500, 1001, False), (900, 3333, True)])
+def test_same_bits_as_the_general_kernels(monkeypatch, rows, cols, bf16):
+    lpmm.ensure_init(rows + cols)
+    w0 = workloads.weights(74, 0, rows, cols).reshape(-1)
+    grads = [workloads.grads(74, 0, t, rows, cols, "col_lognormal", bf16).reshape(-1) for t in (1, 2, 3)]
+    out = []
+    for general in ("0", "1"):
+        monkeypatch.setenv("LPMM_FORCE_GENERAL", general)
+        w, st = to_dev(w0.copy()), lpmm.new_state(rows, cols, DEV)
+        for t, g in enumerate(grads, 1):
+            gpu_step(w, to_dev(g, bf16), st, HP, t, bf16)
+        out.append((download_state(st), w.cpu().numpy()))
+    (a, wa), (b, wb) = out
+    for x, y in ((a.m_codes, b.m_codes), (a.m_scales, b.m_scales), (a.v_codes, b.v_codes), (a.v_r, b.v_r), (a.v_c, b.v_c), (wa, wb)):
+        np.testing.assert_array_equal(x, y)

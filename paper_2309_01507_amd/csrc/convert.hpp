@@ -148,20 +148,7 @@ __global__ __launch_bounds__(kThreads) void quant_m_kernel(const QuantArgs q) {
     for (int u = 0; u < kCvtUnits; ++u) {
         const int64_t base = first + u * kCvtUnitElems;
         const float sc = group32_allmax(fmaxf(fmaxf(fabsf(x[u][0]), fabsf(x[u][1])), fmaxf(fabsf(x[u][2]), fabsf(x[u][3]))));
-        // reciprocal and guard, exact division where some lane comes close to a threshold (as in the step kernels)
-        const float inv = approx_inv(sc);
-        uint32_t w = 0, dist = scale_is_tame(sc) ? 0xFFFFFFFFu : 0u, d;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            w |= quant_m_code_fast(s_search, x[u][e], inv, d) << (4 * e);
-            dist = min(dist, d);
-        }
-        if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
-            w = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w |= quant_m_code(s_search, x[u][e], sc) << (4 * e);
-        }
-        cvt_store_codes(q.q_out, base, q.P, w);
+        cvt_store_codes(q.q_out, base, q.P, compress_m4(s_search, x[u], sc));
         if ((threadIdx.x & 31) == 0 && base < q.P) q.sa[base >> 7] = sc;
     }
 }
@@ -176,11 +163,11 @@ __device__ __forceinline__ uint32_t linear_codes4(const float x[4], const float 
     bool tame = true;
 #pragma unroll
     for (int e = 0; e < 4; ++e) tame = bool(int(tame) & int(scale_is_tame(s[e])));
-    lo = quant_v_code_fast<0>(x[0], approx_inv(s[0]), lo, fa);
-    hi = quant_v_code_fast<0>(x[1], approx_inv(s[1]), hi, fb);
+    lo = quant_v_code_fast<0>(x[0], approx_inv16(s[0]), lo, fa);
+    hi = quant_v_code_fast<0>(x[1], approx_inv16(s[1]), hi, fb);
     closest = fminf(fminf(closest, fabsf(fa)), fabsf(fb));
-    lo = quant_v_code_fast<1>(x[2], approx_inv(s[2]), lo, fa);
-    hi = quant_v_code_fast<1>(x[3], approx_inv(s[3]), hi, fb);
+    lo = quant_v_code_fast<1>(x[2], approx_inv16(s[2]), lo, fa);
+    hi = quant_v_code_fast<1>(x[3], approx_inv16(s[3]), hi, fb);
     closest = fminf(fminf(closest, fabsf(fa)), fabsf(fb));
     uint32_t w = lo | (hi << 4);
     if (__builtin_expect(__ballot(closest < kMarginV || !tame) != 0, 0)) {

@@ -149,6 +149,10 @@ __device__ __forceinline__ bool scale_is_tame(float s) {
     constexpr uint32_t lo = 0x0D800000u, hi = 0x71800000u;     // 2^-100, 2^100
     return bool(int(u - lo <= hi - lo) | int(u == 0u));
 }
+__device__ __forceinline__ bool scale_is_tame_nonzero(float s) {
+    constexpr uint32_t lo = 0x0D800000u, hi = 0x71800000u;
+    return __float_as_uint(s) - lo <= hi - lo;
+}
 __device__ __forceinline__ float approx_inv(float s) {
     return s == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(s);
 }
@@ -165,12 +169,14 @@ __device__ __forceinline__ uint32_t quant_m_code_fast(const SearchEntry* s_searc
                                                       uint32_t& dist) {
     const float n = mt * inv_s;
     const SearchEntry e = search_entry(s_search, n);
-    dist = __usad(__float_as_uint(n), __float_as_uint(e.thr), 0u);
+    // one v_sad_u32; written out, the compiler makes a maximum, a minimum and a subtraction of it
+    asm("v_sad_u32 %0, %1, %2, 0" : "=v"(dist) : "v"(__float_as_uint(n)), "v"(__float_as_uint(e.thr)));
     return e.base + (n > e.thr ? 1u : 0u);
 }
 
 // second moment: boundaries of the Linear map are the integers of f = 16 n - 1.5 and the code is
-// ceil(f).  The approximate f' is within 2^-17 of the exact one; away from integers
+// ceil(f).  inv16_sc = 16 / scale, approximately: the approximate f' is within 2^-18 of the exact one (16 n <= 16 times
+// 1 ulp of the reciprocal, half an ulp of the sum, half an ulp of the exact quotient); away from integers
 // round-to-nearest(f' + 0.5) equals ceil(f), and the saturating byte convert both rounds that way and
 // clamps below at 0 (above, n <= 1 keeps the code at 15).  `off` returns fract(f' + 0.5) - 0.5, the
 // signed distance of f' from the integer it is closest to when that distance is small: a magnitude
@@ -178,11 +184,13 @@ __device__ __forceinline__ uint32_t quant_m_code_fast(const SearchEntry* s_searc
 constexpr float kMarginV = 0x1p-16f;
 
 template <int BYTE>
-__device__ __forceinline__ uint32_t quant_v_code_fast(float vt, float inv_sc, uint32_t packed, float& off) {
-    const float x = __builtin_fmaf(16.0f, vt * inv_sc, -1.0f);      // f' + 0.5
+__device__ __forceinline__ uint32_t quant_v_code_fast(float vt, float inv16_sc, uint32_t packed, float& off) {
+    const float x = __builtin_fmaf(vt, inv16_sc, -1.0f);            // f' + 0.5
     off = __builtin_amdgcn_fractf(x) - 0.5f;                       // 0 when f' sits on an integer
     return __builtin_amdgcn_cvt_pk_u8_f32(x, BYTE, packed);
 }
+// 16 / s for a scale in the tame range, 0 for 0
+__device__ __forceinline__ float approx_inv16(float s) { return 16.0f * approx_inv(s); }
 
 // second-moment decompress with the scale already divided by 16 (exact for tame scales):
 // (q+1) * s16 in one rounding == T_LIN[q] * scale

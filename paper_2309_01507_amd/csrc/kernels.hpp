@@ -76,6 +76,7 @@ struct Tensor4 {
                             // vq then points at the partial sums: float[strips2][round_up(rows, 64)] per strip and row,
                             // then float[tiles][round_up(cols, 64)] per row tile and column
     int sw;                 // kQuantRagged: columns of a strip
+    int deferred;           // plans stepped in one launch: the tensor's first entry in the list of deferred tiles
 };
 
 // The tensor table of a plan lives in device memory.  A pointer read from memory is a generic
@@ -97,7 +98,7 @@ struct Tensor4Table {
     float LPMM_AS_GLOBAL* c_new;
     unsigned int LPMM_AS_GLOBAL* counter;
     int64_t rows, cols, P;
-    int nb, gx, gy, rw, strips, n_wg, kind, strips2, rw2, n_wg2, rs, rs2, tot_slots, flat, no_decay, c_extra, nd_index, det, sw;
+    int nb, gx, gy, rw, strips, n_wg, kind, strips2, rw2, n_wg2, rs, rs2, tot_slots, flat, no_decay, c_extra, nd_index, det, sw, deferred;
 };
 static_assert(sizeof(Tensor4Table) == sizeof(Tensor4), "the table twin must mirror Tensor4");
 __device__ __forceinline__ Tensor4 from_table(const Tensor4Table& t) {
@@ -115,7 +116,7 @@ __device__ __forceinline__ Tensor4 from_table(const Tensor4Table& t) {
     a.rows = t.rows; a.cols = t.cols; a.P = t.P;
     a.nb = t.nb; a.gx = t.gx; a.gy = t.gy; a.rw = t.rw; a.strips = t.strips; a.n_wg = t.n_wg; a.kind = t.kind;
     a.strips2 = t.strips2; a.rw2 = t.rw2; a.n_wg2 = t.n_wg2; a.rs = t.rs; a.rs2 = t.rs2;
-    a.tot_slots = t.tot_slots; a.flat = t.flat; a.no_decay = t.no_decay; a.c_extra = t.c_extra; a.nd_index = t.nd_index; a.det = t.det; a.sw = t.sw;
+    a.tot_slots = t.tot_slots; a.flat = t.flat; a.no_decay = t.no_decay; a.c_extra = t.c_extra; a.nd_index = t.nd_index; a.det = t.det; a.sw = t.sw; a.deferred = t.deferred;
     return a;
 }
 #else
@@ -299,7 +300,21 @@ struct Geo {            // where this group works
     int64_t row0;
     int n_rows;         // rows of this tile
     uint32_t col0;      // first of the lane's 4 columns
-    bool active;
+};
+
+// The rows of a tile that the groups (waves) side by side take one after the other: group g takes rows (g << rs) +
+// walk(k), k = 0, 1, ...  walk(k) and the number of rounds are the same for all groups -- for group 0, which has the
+// most rows in a cut-off tile -- so the loop counter and everything derived from it stay in scalar registers; a group
+// whose row lies behind the tile's end reads zeros (with zero scales: see the tiles) and its stores are dropped by the
+// bounds check.  With a loop bound of its own per group the counter was a vector value and index arithmetic a fifth of
+// pass 1's vector instructions (three 32-bit multiplications per unit in the flat tiling).
+struct RowWalk {
+    int rs, hop;        // hop = groups << rs
+    __device__ __forceinline__ int at(int k) const { return (k & ((1 << rs) - 1)) + (k >> rs) * hop; }
+    __device__ __forceinline__ int rounds(int n) const {          // number of k with at(k) < n
+        const int rest = n % hop, run = 1 << rs;
+        return (n / hop) * run + (rest < run ? rest : run);
+    }
 };
 
 __device__ __forceinline__ Geo geometry(const Tensor4& a, int wg) {
@@ -315,7 +330,6 @@ __device__ __forceinline__ Geo geometry(const Tensor4& a, int wg) {
     const int64_t left = a.rows - g.row0;
     g.n_rows = left < a.rw ? int(left) : a.rw;
     g.col0 = uint32_t(g.cb) * 128u + uint32_t(g.l) * 4u;
-    g.active = g.cb < a.nb;
     return g;
 }
 
@@ -374,13 +388,13 @@ struct Row1 {                      // everything pass 1 prefetches for one row o
 // registers for a second set of base addresses)
 __device__ __forceinline__ void store_row1(const TileBase& tb, uint32_t off4, const float w[4], uint32_t mq_new);
 
-// il = row index inside the tile; rows at or beyond the tile's end read as zeros
-template <bool BF16>
-__device__ __forceinline__ Row1<BF16> load_row1(const TileBase& b, const Tensor4& a, const Geo& g, int il) {
+// off4: byte offset of the lane's 4 elements in the tile's fp32 array; offsets at or beyond the tile's end read as zeros.
+// POLICY: of the gradient.
+template <bool BF16, int POLICY = 0>
+__device__ __forceinline__ Row1<BF16> load_row1(const TileBase& b, uint32_t off4) {
     Row1<BF16> r;
-    const uint32_t off4 = row_offset(il, a.cols, g.col0) * 4u;   // byte offset, fp32 array
     r.p = buf_ld_f4_stream(b.rp, off4);
-    r.g = load_grad_regs4<BF16>(b.rg, off4);
+    r.g = load_grad_regs4<BF16, POLICY>(b.rg, off4);
     r.mq = buf_ld_u16(b.rmq, off4 >> 3);
     r.vq = buf_ld_u16(b.rvq, off4 >> 3);
     return r;
@@ -401,16 +415,38 @@ __device__ __forceinline__ void raise_max(float* addr, float v) {
         atomic_max_nonneg(addr, v);
 }
 
-// One row of pass 1 for one lane: `cur` holds what was loaded for row `il` of the tile.
+// Codes of 4 first moments against their block's scale: reciprocal and guard; the wave recomputes with IEEE division if
+// some lane came too close to a threshold or its block's scale is extreme.
+__device__ __forceinline__ uint32_t compress_m4(const SearchEntry* s_search, const float mt[4], float s_new) {
+    // an all-zero block (every mt is 0) takes any scale; with that out of the way one compare tells an extreme one
+    const float s_div = s_new == 0.0f ? 1.0f : s_new;
+    const float inv_s = __builtin_amdgcn_rcpf(s_div);
+    uint32_t q = 0, dist = 0xFFFFFFFFu;
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+        uint32_t da, db;
+        q |= quant_m_code_fast(s_search, mt[e], inv_s, da) << (4 * e);
+        q |= quant_m_code_fast(s_search, mt[e + 1], inv_s, db) << (4 * e + 4);
+        dist = min(min(dist, da), db);
+    }
+    if (__builtin_expect((__ballot(dist < kMinDistM) | __ballot(!scale_is_tame_nonzero(s_div))) != 0, 0)) {
+        q = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q |= quant_m_code(s_search, mt[e], s_new) << (4 * e);
+    }
+    return q;
+}
+
+// One row of pass 1 for one lane: `cur` holds what was loaded from byte offset `off4` of the tile, `slot` is the place of
+// the row's and the block's staged scales.
 template <bool BF16, class Mid>
 __device__ __forceinline__ void pass1_row(const Tensor4& a, const Hyper& h, const TileBase& tb, const Geo& geo,
-                                          Lds& s, const Row1<BF16>& cur, int il, const float cold16[4],
-                                          bool cols_tame, float cmax[4], Mid mid) {
+                                          Lds& s, const Row1<BF16>& cur, uint32_t off4, int slot, const float cold16[4],
+                                          bool tame, float cmax[4], Mid mid) {
     float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
     float g[4];
     unpack_grad4<BF16>(cur.g, g);
     float mt[4], vt[4], amax = 0.0f, rmax = 0.0f;
-    const int slot = il * a.gx + geo.gxi;
     const float s_old = s.blk_scale[slot], r_old = s.blk_vmax[slot];     // staged by the tile
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -418,9 +454,7 @@ __device__ __forceinline__ void pass1_row(const Tensor4& a, const Hyper& h, cons
         mt[2 * k] = t.x * s_old;              // decompress: T_DE[code] * block scale
         mt[2 * k + 1] = t.y * s_old;
     }
-    // the wave takes the exact route for this row if any of its scales is extreme
-    const bool tame_in = bool(int(cols_tame) & int(scale_is_tame(r_old)));
-    if (__builtin_expect(__ballot(!tame_in) == 0, 1)) {
+    if (__builtin_expect(tame, 1)) {                                      // no old scale of the tile is extreme
         float qf[4];
         codes_to_float4(cur.vq, qf);
         const float r16 = r_old * 0.0625f;
@@ -449,97 +483,76 @@ __device__ __forceinline__ void pass1_row(const Tensor4& a, const Hyper& h, cons
     const float s_new = group32_allmax(amax);     // block absmax of m_t
     rmax = group32_allmax(rmax);
 
-    uint32_t mq_new = 0;
-    uint32_t dist = scale_is_tame(s_new) ? 0xFFFFFFFFu : 0u;     // an extreme block scale forces the exact route
-    {
-        const float inv_s = approx_inv(s_new);
-#pragma unroll
-        for (int e = 0; e < 4; e += 2) {
-            uint32_t da, db;
-            mq_new |= quant_m_code_fast(s.search, mt[e], inv_s, da) << (4 * e);
-            mq_new |= quant_m_code_fast(s.search, mt[e + 1], inv_s, db) << (4 * e + 4);
-            dist = min(min(dist, da), db);
-        }
-    }
-    if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
-        mq_new = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mq_new |= quant_m_code(s.search, mt[e], s_new) << (4 * e);
-    }
-
-    store_row1(tb, row_offset(il, a.cols, geo.col0) * 4u, w, mq_new);
+    store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
     if (geo.l == 0) {
         s.blk_scale[slot] = s_new;
         s.blk_vmax[slot] = rmax;
     }
 }
 
-// TABLES_READY: the caller has loaded the lookup tables into `s` (and synchronized) already.
-template <bool BF16, bool TABLES_READY>
+template <bool BF16>
 __device__ __forceinline__ void pass1_fast_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
     const Geo geo = geometry(a, wg);
     const TileBase tb = tile_base<BF16>(a, geo.row0, geo.n_rows);
     float cmax[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 
-    // old block scales and old row maxima of the tile into the slots of the new ones
-    for (int t = threadIdx.x; t < geo.n_rows * a.gx; t += kThreads) {
+    // Rows of this group, in the order it takes them: (gyi << rs) + walk(k) with S = 2^rs.  With S = 1 these are gyi,
+    // gyi + gy, ...; in general the gy groups that work side by side are S rows apart.  The memory system likes the rows
+    // in flight at one time to lie 32 KiB apart (measured: up to 10 % more bandwidth than neighbouring rows for
+    // 4096-column tensors, whose rows are 16 KiB long), so the host picks S to make S rows a multiple of 32 KiB where it can.
+    // The loads of two rows are in flight while a third is computed (three register sets take turns, the loop is unrolled
+    // by three); the prefetch is unconditional, rows past the tile come back as zeros and are never used.
+    const RowWalk walk{a.rs, a.gy << a.rs};
+    const int n = walk.rounds(geo.n_rows);
+    const uint32_t lane4 = row_offset(geo.gyi << a.rs, a.cols, geo.col0) * 4u, pitch4 = uint32_t(a.cols) * 4u;
+    const int slot0 = (geo.gyi << a.rs) * a.gx + geo.gxi;
+    auto off = [&](int k) { return lane4 + uint32_t(walk.at(k)) * pitch4; };      // rows of the tile: below 2^31
+    auto fetch = [&](int k) { return load_row1<BF16>(tb, off(k)); };
+    Row1<BF16> r0 = fetch(0);
+    Row1<BF16> r1 = fetch(1);
+    Row1<BF16> r2;
+    // old block scales and old row maxima of the tile into the slots of the new ones, zeros for rows behind its end
+    bool lane_tame = true;
+    for (int t = threadIdx.x; t < a.rw * a.gx; t += kThreads) {
         const int il = t / a.gx, cbi = geo.strip * a.gx + t % a.gx;
-        s.blk_scale[t] = cbi < a.nb ? tb.ms[row_offset(il, a.nb, uint32_t(cbi))] : 0.0f;
-        s.blk_vmax[t] = tb.r[il];
+        const bool in = il < geo.n_rows;
+        const float r = in ? tb.r[il] : 0.0f;
+        s.blk_scale[t] = in ? tb.ms[row_offset(il, a.nb, uint32_t(cbi))] : 0.0f;
+        s.blk_vmax[t] = r;
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
     }
-    if (geo.active) {
-        float cold16[4];
-        load4(a.c + geo.col0, cold16);
-        bool cols_tame = true;
+    float cold16[4];
+    load4(a.c + geo.col0, cold16);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            cols_tame = bool(int(cols_tame) & int(scale_is_tame(cold16[e])));
-            cold16[e] *= 0.0625f;
-        }
-        // Rows of this group, in the order it takes them: row(k) = gyi * S + k % S + (k / S) * gy * S with
-        // S = 2^rs.  With S = 1 these are gyi, gyi + gy, ...; in general the gy groups that work side by
-        // side are S rows apart.  The memory system likes the rows in flight at one time to lie 32 KiB
-        // apart (measured: up to 10 % more bandwidth than neighbouring rows for 4096-column tensors, whose
-        // rows are 16 KiB long), so the host picks S to make S rows a multiple of 32 KiB where it can.
-        // The loads of two rows are in flight while a third is computed (three register sets take turns,
-        // the loop is unrolled by three); the prefetch is unconditional, rows past the tile come back as
-        // zeros and are never used.
-        const int n = geo.n_rows, rs = a.rs;
-        const int row_g = geo.gyi << rs, hop = a.gy << rs, low = (1 << rs) - 1;
-        auto row = [&](int k) { return row_g + (k & low) + (k >> rs) * hop; };    // increasing in k
-        int k = 0;
-        Row1<BF16> r0 = load_row1<BF16>(tb, a, geo, row(0));
-        Row1<BF16> r1 = load_row1<BF16>(tb, a, geo, row(1));
-        Row1<BF16> r2;
-        // the first rows' loads are in flight meanwhile; the barrier also publishes the staged scales
-        if constexpr (!TABLES_READY) load_tables(s);
-        else __syncthreads();
-        // Everything requested so far has to be here before the first row anyway.  Saying so with an
-        // explicit wait gives the loop a start-up state with nothing outstanding; otherwise the
-        // start-up's own (tight) wait counts are merged into the loop head and drain the prefetch
-        // in every round.
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        // Rounds of three rows while all three exist; the loop has no exit in its middle, so that
-        // every path through it sees the same queue of outstanding loads and the compiler's wait
-        // counts are exact (an early exit would join a path on which the newest prefetch is still
-        // pending, and the loop head would then wait for it).  At most two rows remain afterwards.
-        auto none = [] {};
-        while (row(k + 2) < n) {
-            pass1_row<BF16>(a, h, tb, geo, s, r0, row(k), cold16, cols_tame, cmax,
-                            [&] { r2 = load_row1<BF16>(tb, a, geo, row(k + 2)); });
-            pass1_row<BF16>(a, h, tb, geo, s, r1, row(k + 1), cold16, cols_tame, cmax,
-                            [&] { r0 = load_row1<BF16>(tb, a, geo, row(k + 3)); });
-            pass1_row<BF16>(a, h, tb, geo, s, r2, row(k + 2), cold16, cols_tame, cmax,
-                            [&] { r1 = load_row1<BF16>(tb, a, geo, row(k + 4)); });
-            k += 3;
-        }
-        if (row(k) < n) {
-            pass1_row<BF16>(a, h, tb, geo, s, r0, row(k), cold16, cols_tame, cmax, none);
-            if (row(k + 1) < n) pass1_row<BF16>(a, h, tb, geo, s, r1, row(k + 1), cold16, cols_tame, cmax, none);
-        }
-    } else {
-        if constexpr (!TABLES_READY) load_tables(s);   // keeps the workgroup's barriers matched
-        else __syncthreads();
+    for (int e = 0; e < 4; ++e) {
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(cold16[e])));
+        cold16[e] *= 0.0625f;
+    }
+    // the first rows' loads are in flight meanwhile; the barriers also publish the staged scales.  An extreme scale
+    // anywhere sends the whole tile to the exact route: one test per tile instead of one per row.
+    load_tables(s);
+    const bool tame = !__syncthreads_or(int(!lane_tame));
+    // Everything requested so far has to be here before the first row anyway.  Saying so with an explicit wait gives the
+    // loop a start-up state with nothing outstanding; otherwise the start-up's own (tight) wait counts are merged into
+    // the loop head and drain the prefetch in every round.
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    // Rounds of three rows while all three exist; the loop has no exit in its middle, so that every path through it sees
+    // the same queue of outstanding loads and the compiler's wait counts are exact (an early exit would join a path on
+    // which the newest prefetch is still pending, and the loop head would then wait for it).  At most two rows remain.
+    auto none = [] {};
+    auto work = [&](const Row1<BF16>& cur, int k, auto mid) {
+        pass1_row<BF16>(a, h, tb, geo, s, cur, off(k), slot0 + walk.at(k) * a.gx, cold16, tame, cmax, mid);
+    };
+    int k = 0;
+    while (k + 2 < n) {
+        work(r0, k, [&] { r2 = fetch(k + 2); });
+        work(r1, k + 1, [&] { r0 = fetch(k + 3); });
+        work(r2, k + 2, [&] { r1 = fetch(k + 4); });
+        k += 3;
+    }
+    if (k < n) {
+        work(r0, k, none);
+        if (k + 1 < n) work(r1, k + 1, none);
     }
 
     // column maxima: combine the gy groups that share a column block, then one atomic per column
@@ -549,20 +562,17 @@ __device__ __forceinline__ void pass1_fast_tile(const Tensor4& a, const Hyper& h
     // block scales to the state, block maxima of v_t into the row maxima
     for (int t = threadIdx.x; t < geo.n_rows * a.gx; t += kThreads) {
         const int il = t / a.gx, cbi = geo.strip * a.gx + t % a.gx;
-        if (cbi < a.nb) {
-            st<float>(tb.ms, row_offset(il, a.nb, uint32_t(cbi)) * 4u, s.blk_scale[t]);
-            const float m = s.blk_vmax[t];
-            if (m > 0.0f) atomic_max_nonneg(tb.r_new + il, m);     // unconditionally: reading the running
-            // maximum first (to skip atomics that cannot raise it) costs a round trip at the end of every tile
-            // and was measured to be slower
-        }
+        st<float>(tb.ms, row_offset(il, a.nb, uint32_t(cbi)) * 4u, s.blk_scale[t]);
+        const float m = s.blk_vmax[t];
+        if (m > 0.0f) atomic_max_nonneg(tb.r_new + il, m);     // unconditionally: reading the running maximum first (to
+        // skip atomics that cannot raise it) costs a round trip at the end of every tile and was measured to be slower
     }
     for (int t = threadIdx.x; t < a.gx * 128; t += kThreads) {
         const int gi = t >> 7;
         float m = 0.0f;
         for (int y = 0; y < a.gy; ++y) m = fmaxf(m, s.col[((y * a.gx + gi) << 7) + (t & 127)]);
         const int cbi = geo.strip * a.gx + gi;
-        if (cbi < a.nb && m > 0.0f) atomic_max_nonneg(a.c_new + int64_t(cbi) * 128 + (t & 127), m);
+        if (m > 0.0f) atomic_max_nonneg(a.c_new + int64_t(cbi) * 128 + (t & 127), m);
     }
 }
 
@@ -577,25 +587,13 @@ __device__ __forceinline__ void pass1_fast_tile(const Tensor4& a, const Hyper& h
 
 constexpr int kFlatBlocks = 8;
 
-template <bool BF16>
-__device__ __forceinline__ Row1<BF16> load_unit(const TileBase& b, const Tensor4& a, int il, int cb, int l) {
-    Row1<BF16> r;
-    const uint32_t off4 = row_offset(il, a.cols, uint32_t(cb) * 128u + uint32_t(l) * 4u) * 4u;
-    r.p = buf_ld_f4_stream(b.rp, off4);
-    // non-temporal although pass 2 reads the gradient again: the re-read comes from HBM either way (the set is far
-    // larger than the caches), and not keeping the line is 0.35 % per step on the 7B-shaped set (five A/B pairs)
-    r.g = load_grad_regs4<BF16, kPolicyNt>(b.rg, off4);
-    r.mq = buf_ld_u16(b.rmq, off4 >> 3);
-    r.vq = buf_ld_u16(b.rvq, off4 >> 3);
-    return r;
-}
-
-// One block of one row.  j = block inside the strip, cb = its column block in the tensor; row_run carries the
-// row's maximum of v_t from block to block.
+// One block of one row.  off4: byte offset of the lane's elements in the tile; il: the row; j = block inside the strip
+// (the same for all lanes), cb0 = the strip's first column block; row_run carries the lane's maximum of v_t in the row from
+// block to block, reduced over the lanes after the last one.
 template <bool BF16, class Mid>
 __device__ __forceinline__ void flat_unit(const Tensor4& a, const Hyper& h, const TileBase& tb, Lds& s,
-                                          const Row1<BF16>& cur, int il, int j, int cb, int l, int nbk,
-                                          bool cols_tame, float& row_run, Mid mid) {
+                                          const Row1<BF16>& cur, uint32_t off4, int il, int j, int cb0, int l, int nbk,
+                                          bool tame, float& row_run, Mid mid) {
     float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
     float g[4];
     unpack_grad4<BF16>(cur.g, g);
@@ -608,9 +606,7 @@ __device__ __forceinline__ void flat_unit(const Tensor4& a, const Hyper& h, cons
         mt[2 * k] = t.x * s_old;
         mt[2 * k + 1] = t.y * s_old;
     }
-    const uint32_t col0 = uint32_t(cb) * 128u + uint32_t(l) * 4u;
-    const bool tame_in = bool(int(cols_tame) & int(scale_is_tame(r_old)));
-    if (__builtin_expect(__ballot(!tame_in) == 0, 1)) {
+    if (__builtin_expect(tame, 1)) {
         float qf[4];
         codes_to_float4(cur.vq, qf);
         const float r16 = r_old * 0.0625f;
@@ -620,7 +616,7 @@ __device__ __forceinline__ void flat_unit(const Tensor4& a, const Hyper& h, cons
         for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(r16, cold16[e]));
     } else {
         float cold[4];
-        load4(a.c + col0, cold);
+        load4(a.c + (cb0 + j) * 128 + l * 4, cold);
 #pragma unroll
         for (int e = 0; e < 4; ++e) vt[e] = dequant_v((uint32_t(cur.vq) >> (4 * e)) & 15u, fminf(r_old, cold[e]));
     }
@@ -641,30 +637,14 @@ __device__ __forceinline__ void flat_unit(const Tensor4& a, const Hyper& h, cons
     for (int e = 0; e < 4; ++e)
         (void)__hip_atomic_fetch_max(cbits + e, __float_as_uint(vt[e]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     const float s_new = group32_allmax(amax);
-    rmax = group32_allmax(rmax);
     row_run = j == 0 ? rmax : max_nonneg(row_run, rmax);
+    const bool row_ends = j == nbk - 1;                       // the same for all lanes
+    if (row_ends) row_run = group32_allmax(row_run);
 
-    uint32_t mq_new = 0;
-    uint32_t dist = scale_is_tame(s_new) ? 0xFFFFFFFFu : 0u;
-    {
-        const float inv_s = approx_inv(s_new);
-#pragma unroll
-        for (int e = 0; e < 4; e += 2) {
-            uint32_t da, db;
-            mq_new |= quant_m_code_fast(s.search, mt[e], inv_s, da) << (4 * e);
-            mq_new |= quant_m_code_fast(s.search, mt[e + 1], inv_s, db) << (4 * e + 4);
-            dist = min(min(dist, da), db);
-        }
-    }
-    if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
-        mq_new = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mq_new |= quant_m_code(s.search, mt[e], s_new) << (4 * e);
-    }
-    store_row1(tb, row_offset(il, a.cols, col0) * 4u, w, mq_new);
+    store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
     if (l == 0) {
         s.blk_scale[il * kFlatBlocks + j] = s_new;
-        if (j == nbk - 1) s.blk_vmax[il] = row_run;
+        if (row_ends) s.blk_vmax[il] = row_run;
     }
 }
 
@@ -680,49 +660,57 @@ __device__ __forceinline__ void pass1_flat_tile(const Tensor4& a, const Hyper& h
     const int64_t left = a.rows - row0;
     const int n = left < a.rw ? int(left) : a.rw;
     const TileBase tb = tile_base<BF16>(a, row0, n);
-    // units of this group in the order it takes them: unit q = block q % nbk of its row number q / nbk
-    const int rs = a.rs;
-    const int row_g = grp << rs, hop = kGroups << rs, low = (1 << rs) - 1;
-    auto row = [&](int k) { return row_g + (k & low) + (k >> rs) * hop; };
+    // units in the order the groups take them: unit q = block q % nbk of the group's row number q / nbk
+    const RowWalk walk{a.rs, kGroups << a.rs};
+    const int nq = walk.rounds(n) * nbk;
     const uint32_t inv_nbk = (65536u + uint32_t(nbk) - 1u) / uint32_t(nbk);   // q / nbk == (q * inv_nbk) >> 16 for q < 9000
     auto krow = [&](int q) { return int((uint32_t(q) * inv_nbk) >> 16); };
-    auto blk = [&](int q) { return q - krow(q) * nbk; };
-    auto fetch = [&](int q) { return load_unit<BF16>(tb, a, row(krow(q)), cb0 + blk(q), l); };
+    const int row_g = grp << a.rs;
+    const uint32_t lane4 = row_offset(row_g, a.cols, uint32_t(cb0) * 128u + uint32_t(l) * 4u) * 4u, pitch4 = uint32_t(a.cols) * 4u;
+    auto off = [&](int q) { return lane4 + (uint32_t(walk.at(krow(q))) * pitch4 + uint32_t(q - krow(q) * nbk) * 512u); };
+    // the gradient's load is non-temporal although pass 2 reads it again: not keeping the line is 0.35 % per step on the
+    // 7B-shaped set (five A/B pairs)
+    auto fetch = [&](int q) { return load_row1<BF16, kPolicyNt>(tb, off(q)); };
     int q = 0;
     Row1<BF16> r0 = fetch(0);
     Row1<BF16> r1 = fetch(1);
     Row1<BF16> r2;
     // the strip's old column maxima (scaled) and zeroed running maxima into LDS, then the tables
-    bool tame = true;
+    bool lane_tame = true;
     for (int t = threadIdx.x; t < nbk * 128; t += kThreads) {
         const float c = a.c[cb0 * 128 + t];
-        tame = bool(int(tame) & int(scale_is_tame(c)));
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(c)));
         s.cold[t] = c * 0.0625f;
         s.col[t] = 0.0f;
     }
-    // old block scales and old row maxima of the tile into the slots of the new ones
-    for (int t = threadIdx.x; t < n * kFlatBlocks; t += kThreads) {
+    // old block scales and old row maxima of the tile into the slots of the new ones, zeros for rows behind its end
+    for (int t = threadIdx.x; t < a.rw * kFlatBlocks; t += kThreads) {
         const int il = t / kFlatBlocks, j = t % kFlatBlocks;
-        s.blk_scale[t] = j < nbk ? tb.ms[row_offset(il, a.nb, uint32_t(cb0 + j))] : 0.0f;
+        s.blk_scale[t] = il < n && j < nbk ? tb.ms[row_offset(il, a.nb, uint32_t(cb0 + j))] : 0.0f;
     }
-    for (int t = threadIdx.x; t < n; t += kThreads) s.blk_vmax[t] = tb.r[t];
-    const bool cols_tame = !__syncthreads_or(int(!tame));
+    for (int t = threadIdx.x; t < a.rw; t += kThreads) {
+        const float r = t < n ? tb.r[t] : 0.0f;
+        s.blk_vmax[t] = r;
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
+    }
     load_tables(s);
+    const bool tame = !__syncthreads_or(int(!lane_tame));     // an extreme scale anywhere: the exact route for the whole tile
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     float row_run = 0.0f;
     auto none = [] {};
     auto unit = [&](const Row1<BF16>& cur, int qq, auto mid) {
-        flat_unit<BF16>(a, h, tb, s, cur, row(krow(qq)), blk(qq), cb0 + blk(qq), l, nbk, cols_tame, row_run, mid);
+        const int k = krow(qq);
+        flat_unit<BF16>(a, h, tb, s, cur, off(qq), row_g + walk.at(k), qq - k * nbk, cb0, l, nbk, tame, row_run, mid);
     };
-    while (row(krow(q + 2)) < n) {
+    while (q + 2 < nq) {
         unit(r0, q, [&] { r2 = fetch(q + 2); });
         unit(r1, q + 1, [&] { r0 = fetch(q + 3); });
         unit(r2, q + 2, [&] { r1 = fetch(q + 4); });
         q += 3;
     }
-    if (row(krow(q)) < n) {
+    if (q < nq) {
         unit(r0, q, none);
-        if (row(krow(q + 1)) < n) unit(r1, q + 1, none);
+        if (q + 1 < nq) unit(r1, q + 1, none);
     }
     __syncthreads();
     for (int t = threadIdx.x; t < n * kFlatBlocks; t += kThreads) {
@@ -751,8 +739,18 @@ constexpr int kMaxTotSlots = 8;                                    // lines behi
                                                                    // factorized step's two float sums
 constexpr int kCounterWords = (1 + kTicketLanes + kMaxTotSlots) * kTicketStride;  // per tensor
 
+// A word of the workspace (the new maxima or sums) as the second pass reads it.  SAME_LAUNCH: the first pass of the
+// tensor ran in the same launch, on other XCDs, so the load has to see what their atomics left (agent scope: it does not
+// take the line from this XCD's L2); between launches the kernel boundary has done that and plain loads will do.
+template <bool SAME_LAUNCH>
+__device__ __forceinline__ float ld_ws(const float* p) {
+    if constexpr (SAME_LAUNCH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
+}
+
 // dst[i] = src[i]; src[i] = 0 by one workgroup.  It runs alone at the end of a tensor's pass 2, so
 // what counts is latency: 16 loads per thread are in flight before the first store.
+template <bool SAME_LAUNCH = false>
 __device__ __forceinline__ void move_and_clear(float* dst, float* src, int64_t n) {
     constexpr int kDepth = 16;
     for (int64_t base = threadIdx.x; base < n; base += int64_t(kThreads) * kDepth) {
@@ -760,7 +758,7 @@ __device__ __forceinline__ void move_and_clear(float* dst, float* src, int64_t n
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
             const int64_t i = base + int64_t(u) * kThreads;
-            v[u] = i < n ? src[i] : 0.0f;
+            v[u] = i < n ? ld_ws<SAME_LAUNCH>(src + i) : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
@@ -834,7 +832,7 @@ __device__ __forceinline__ float lane_value(float v, int lane) {      // lane: w
 }
 
 // The scalars of a wave's rows of one pass-2 tile, one row per lane (row k of the wave in lane k): the old and the new
-// row maximum, the old one / 16, the approximate reciprocal of the new one (0 for 0), and `wild`, the mask of the
+// row maximum, the old one / 16, 16 times the approximate reciprocal of the new one (0 for 0), and `wild`, the mask of the
 // rows that must take the exact route whatever their elements (a scale of the row or of the strip's columns outside
 // the range in which scale / 16 and the reciprocal keep all their bits).
 struct RowScalars {
@@ -852,7 +850,7 @@ struct NextRow {
 // keeps track of how close it came to a decision boundary; if the row is marked wild, or some lane came too close, the
 // whole wave computes the row again from its inputs with exact arithmetic (same bits where both apply).  The second
 // route shares no value with the first, so that nothing has to be kept in registers for it.
-template <bool BF16, bool RAGGED>
+template <bool BF16, bool RAGGED, bool SAME_LAUNCH>
 __device__ __forceinline__ uint32_t pass2_row(const Tensor4& a, const Hyper& h, const uint32_t col[4], const Row2<BF16>& row,
                                               const RowScalars& rs, const NextRow& nx, int k, const float cold16[4],
                                               const float inv_cnew[4]) {
@@ -897,7 +895,7 @@ __device__ __forceinline__ uint32_t pass2_row(const Tensor4& a, const Hyper& h, 
             r_old = nx.beyond[e] ? ron : r_old;
             r_new = nx.beyond[e] ? rnn : r_new;
         }
-        const float cold = a.c[col[e]], cnew = a.c_new[col[e]];
+        const float cold = a.c[col[e]], cnew = ld_ws<SAME_LAUNCH>(a.c_new + col[e]);
         const float vt = moment_v(h, dequant_v((uint32_t(row.vq) >> (4 * e)) & 15u, fminf(r_old, cold)), g[e]);
         out |= quant_v_code(vt, fminf(r_new, cnew)) << (4 * e);
     }
@@ -920,8 +918,14 @@ __host__ __device__ __forceinline__ int64_t pass2_rows(const Tensor4& a, bool ra
     return ragged && (a.P & 3) ? a.rows - 1 : a.rows;
 }
 
-template <bool BF16, bool RAGGED = false>
-__device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int wg) {
+// SAME_LAUNCH: pass 1 of the tensor runs in the same launch.  `ready` is called once by every wave, after the loads that
+// do not depend on pass 1 have been issued; false leaves the tile undone.
+struct AlwaysReady {
+    __device__ __forceinline__ bool operator()() const { return true; }
+};
+struct NoLds {};                 // pass 2 of a launch of its own needs none
+template <bool BF16, bool RAGGED = false, bool SAME_LAUNCH = false, class Ready = AlwaysReady, class S = NoLds>
+__device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int wg, Ready ready = Ready(), S&& s = S()) {
     const int strip = wg % a.strips2, tile = wg / a.strips2;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
@@ -933,10 +937,29 @@ __device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int
     const int rs = RAGGED ? 0 : a.rs2;
     const int row_w = wave << rs, hop = kWaves << rs, low = (1 << rs) - 1;
     auto row = [&](int k) { return row_w + (k & low) + (k >> rs) * hop; };
+    const int n_stat = RAGGED && row0 + n < a.rows ? n + 1 : n;   // ragged: the statistics of one row more
+    // SAME_LAUNCH: the new maxima of the strip's columns and of the tile's rows through LDS, one agent-scope load each.
+    // Such loads are not served by the L2; each wave fetching its columns and rows itself, as it does with plain loads,
+    // would make 150 requests per workgroup to lines that every tile of the strip reads (factorized GPT-2-medium set: 739
+    // us so, 728 with the vectors staged).
+    auto stage = [&] {
+        if constexpr (SAME_LAUNCH) {
+            for (int t = threadIdx.x; t < 256 + (RAGGED ? 8 : 0); t += kThreads) {
+                uint32_t c = uint32_t(strip) * 256u + uint32_t(t);
+                if (RAGGED && c >= cols) c -= cols;               // a row's last lane reaches into the next row
+                s.col[t] = c < cols ? ld_ws<true>(a.c_new + c) : 0.0f;
+            }
+            for (int t = threadIdx.x; t < n_stat; t += kThreads) s.blk_scale[t] = ld_ws<true>(a.r_new + row0 + t);
+            __syncthreads();
+        }
+    };
     int last = n - 1;
     uint32_t shift = 0;
     if constexpr (RAGGED) {
-        if (row_w >= n) return;                                   // no barrier in this function
+        if (row_w >= n) {                                         // no row for this wave, but the barriers count it
+            if (ready()) stage();
+            return;
+        }
         last -= (last - row_w) % kWaves;                          // the wave's own last row
         shift = (0u - uint32_t(wave) * cols) & 3u;
     }
@@ -953,17 +976,39 @@ __device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int
         nx.beyond[e] = RAGGED && col0 + e >= cols;
         col[e] = nx.beyond[e] ? col0 + e - cols : col0 + e;
     }
-    const int n_stat = RAGGED && row0 + n < a.rows ? n + 1 : n;   // ragged: the statistics of one row more
     const TileBase tb = tile_base<BF16>(a, row0, n_stat);
+    // kDepth register sets take turns, the loop is unrolled by as many: the loads of kDepth - 1 rows are in flight while
+    // one is computed; a prefetch past the tile takes the tile's last row again and is never used.  Three sets where pass 2
+    // runs by itself; beside pass 1 in one launch its waves hold slots that pass 1 could use, and four sets, issued before
+    // the wait for pass 1, took the GPT-2-medium set from 849 to 837 us (six: 841, eight: 844; BERT-base 310, 303, 303,
+    // 303).  Ragged: the scalar offset counts from the wave's first row and the lane's from the tile's, both multiples of 4
+    // elements.
+    const uint32_t lane_e = RAGGED ? col0 + uint32_t(wave) * cols : col0;
+    const uint32_t lane_g = lane_e * (BF16 ? 2u : 4u), lane_q = lane_e >> 1;
+    const int row_b = RAGGED ? wave : 0;
+    auto fetch = [&](int il) { return load_row2<BF16>(tb, uint32_t((il < last ? il : last) - row_b) * cols, lane_g, lane_q); };   // il * cols < 2^29
+        constexpr int kDepth = SAME_LAUNCH ? 4 : 3;
+    auto put = [&](int il, uint32_t codes) {
+        if (live) __builtin_amdgcn_raw_buffer_store_b16(short(codes), tb.rvq, int(lane_q), int((uint32_t(il - row_b) * cols) >> 1), 0);
+    };
+    Row2<BF16> r[kDepth];
+    auto fill_sets = [&] {
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) r[u] = fetch(row(u));
+    };
+    if constexpr (SAME_LAUNCH) fill_sets();      // the wait for pass 1 is time to fetch in
+    if (!ready()) return;
+    stage();
     // The scalars of the wave's rows (at most 64 per tile), one row per lane; the row loop fetches what it needs
     // with v_readlane instead of two loads, a reciprocal, a select and two range checks per row.  Rows past the
     // tile read as zeros through the bounds-checked resources.
     auto scalars = [&](uint32_t il) {
         RowScalars sc;
         sc.r_old = buf_ld_f(tb.rr, il * 4u);
-        sc.r_new = buf_ld_f(tb.rr_new, il * 4u);
+        if constexpr (SAME_LAUNCH) sc.r_new = il < uint32_t(n_stat) ? s.blk_scale[il] : 0.0f;
+        else sc.r_new = buf_ld_f(tb.rr_new, il * 4u);
         sc.r16 = sc.r_old * 0.0625f;
-        sc.inv = approx_inv(sc.r_new);
+        sc.inv = approx_inv16(sc.r_new);
         const bool row_tame = bool(int(scale_is_tame(sc.r_old)) & int(scale_is_tame(sc.r_new)));
         sc.wild = __ballot(!row_tame);
         return sc;
@@ -976,9 +1021,18 @@ __device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int
     float cold16[4], inv_cnew[4];
     if constexpr (RAGGED) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { cold16[e] = a.c[col[e]]; inv_cnew[e] = a.c_new[col[e]]; }
+        for (int e = 0; e < 4; ++e) cold16[e] = a.c[col[e]];
     } else {
         load4(a.c + col0, cold16);
+    }
+    if constexpr (SAME_LAUNCH) {
+        const uint32_t at = live ? col_own - uint32_t(strip) * 256u : 0u;         // other lanes: any column
+#pragma unroll
+        for (int e = 0; e < 4; ++e) inv_cnew[e] = s.col[at + e];
+    } else if constexpr (RAGGED) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) inv_cnew[e] = a.c_new[col[e]];
+    } else {
         load4(a.c_new + col0, inv_cnew);
     }
     bool lane_tame = true;
@@ -986,46 +1040,36 @@ __device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int
     for (int e = 0; e < 4; ++e) {
         lane_tame = bool(int(lane_tame) & int(scale_is_tame(cold16[e])) & int(scale_is_tame(inv_cnew[e])));
         cold16[e] *= 0.0625f;
-        inv_cnew[e] = approx_inv(inv_cnew[e]);
+        inv_cnew[e] = approx_inv16(inv_cnew[e]);
     }
     if (__ballot(!lane_tame) != 0) sc.wild = ~uint64_t(0);        // a wild column scale: every row takes the exact route
-    // the loads of two rows are in flight while a third is computed (three register sets take turns, the loop is
-    // unrolled by three); a prefetch past the tile takes the tile's last row again and is never used.  Ragged: the
-    // scalar offset counts from the wave's first row and the lane's from the tile's, both multiples of 4 elements.
-    const uint32_t lane_e = RAGGED ? col0 + uint32_t(wave) * cols : col0;
-    const uint32_t lane_g = lane_e * (BF16 ? 2u : 4u), lane_q = lane_e >> 1;
-    const int row_b = RAGGED ? wave : 0;
-    auto fetch = [&](int il) { return load_row2<BF16>(tb, uint32_t((il < last ? il : last) - row_b) * cols, lane_g, lane_q); };   // il * cols < 2^29
-    auto put = [&](int il, uint32_t codes) {
-        if (live) __builtin_amdgcn_raw_buffer_store_b16(short(codes), tb.rvq, int(lane_q), int((uint32_t(il - row_b) * cols) >> 1), 0);
-    };
-    auto codes_of = [&](const Row2<BF16>& r, int k) { return pass2_row<BF16, RAGGED>(a, h, col, r, sc, nx, k, cold16, inv_cnew); };
+    auto codes_of = [&](const Row2<BF16>& r, int k) { return pass2_row<BF16, RAGGED, SAME_LAUNCH>(a, h, col, r, sc, nx, k, cold16, inv_cnew); };
     int k = 0;
-    Row2<BF16> r0 = fetch(row(0));
-    Row2<BF16> r1 = fetch(row(1));
-    Row2<BF16> r2 = fetch(row(2));
+    if constexpr (!SAME_LAUNCH) fill_sets();     // behind the scalars' loads, whose results the lines above work on
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);     // loop start-up state: nothing outstanding (see pass 1)
-    // Rounds of three rows, no exit in the middle (see pass 1).  A register set is reloaded right after the row it
-    // held has been processed, two rows ahead of its next use; the loads are pinned there, after the last use of
-    // the values they replace.
-    if (row(k + 2) < n) do {
-        put(row(k), codes_of(r0, k));
-        __builtin_amdgcn_sched_barrier(0);
-        r0 = fetch(row(k + 3));
-        __builtin_amdgcn_sched_barrier(0);
-        put(row(k + 1), codes_of(r1, k + 1));
-        __builtin_amdgcn_sched_barrier(0);
-        r1 = fetch(row(k + 4));
-        __builtin_amdgcn_sched_barrier(0);
-        put(row(k + 2), codes_of(r2, k + 2));
-        __builtin_amdgcn_sched_barrier(0);
-        r2 = fetch(row(k + 5));
-        __builtin_amdgcn_sched_barrier(0);
-        k += 3;
-    } while (row(k + 2) < n);
-    if (row(k) < n) {
-        put(row(k), codes_of(r0, k));
-        if (row(k + 1) < n) put(row(k + 1), codes_of(r1, k + 1));
+    // Rounds of kDepth rows, no exit in the middle (see pass 1).  A register set is reloaded right after the row it held
+    // has been processed; the loads are pinned there, after the last use of the values they replace.
+    if (row(k + kDepth - 1) < n) do {
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            put(row(k + u), codes_of(r[u], k + u));
+            __builtin_amdgcn_sched_barrier(0);
+            r[u] = fetch(row(k + kDepth + u));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        k += kDepth;
+    } while (row(k + kDepth - 1) < n);
+    // The rows that do not fill a round.  Beside pass 1 in one launch, where the tiles are tall, they are fetched again
+    // one by one: taking them from their sets needs 102 registers in place of 95 (fp32), four waves on a SIMD in place
+    // of five, and cost the BERT-base set 6 us of 302.
+    if constexpr (SAME_LAUNCH) {
+        for (; row(k) < n; ++k) put(row(k), codes_of(fetch(row(k)), k));
+    } else {
+#pragma unroll
+        for (int u = 0; u < kDepth - 1; ++u) {
+            if (row(k + u) >= n) break;
+            put(row(k + u), codes_of(r[u], k + u));
+        }
     }
 }
 
@@ -1034,10 +1078,10 @@ __device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int
 constexpr int kLastRowElems = kThreads * 8;
 __host__ __device__ __forceinline__ int64_t pass2_last_row_begin(const Tensor4& a) { return ((a.rows - 1) * a.cols + 3) / 4 * 4; }
 
-template <bool BF16>
+template <bool BF16, bool SAME_LAUNCH>
 __device__ __forceinline__ void pass2_last_row(const Tensor4& a, const Hyper& h, int part) {
     const int64_t first = pass2_last_row_begin(a) + int64_t(part) * kLastRowElems;
-    const float r_old = a.r[a.rows - 1], r_new = a.r_new[a.rows - 1];
+    const float r_old = a.r[a.rows - 1], r_new = ld_ws<SAME_LAUNCH>(a.r_new + a.rows - 1);
     for (int u = 0; u < kLastRowElems / (2 * kThreads); ++u) {
         const int64_t e0 = first + 2 * (int64_t(u) * kThreads + threadIdx.x);
         if (e0 >= a.P) return;
@@ -1047,7 +1091,7 @@ __device__ __forceinline__ void pass2_last_row(const Tensor4& a, const Hyper& h,
         for (int k = 0; k < 2 && e0 + k < a.P; ++k) {
             const int64_t j = e0 + k - (a.rows - 1) * a.cols;
             const float vt = moment_v(h, dequant_v((q >> (4 * k)) & 15u, fminf(r_old, a.c[j])), load_grad1<BF16>(a.g, e0 + k));
-            out |= quant_v_code(vt, fminf(r_new, a.c_new[j])) << (4 * k);
+            out |= quant_v_code(vt, fminf(r_new, ld_ws<SAME_LAUNCH>(a.c_new + j))) << (4 * k);
         }
         *byte = uint8_t(out);
     }
@@ -1098,14 +1142,13 @@ struct RowB {                      // everything the step reads for one block, p
     uint16_t mq, vq;               // the lane's 4 codes of each moment
 };                                 // (the block's two old scales come from LDS, staged by the tile as in pass 1)
 
-constexpr int kNoBlock = 1 << 22;     // a block index whose offsets lie beyond any tile: loads return zeros
+constexpr uint32_t kNoBlock = 1u << 30;     // a byte offset beyond any tile: loads return zeros, stores are dropped
 
-// ib = block index inside the (super-)tile; blocks at or beyond its end read as zeros
+// off4: byte offset of the lane's elements in the (super-)tile; offsets at or beyond its end read as zeros
 // SGDM: the tensor has no second moment (SGD with momentum, App. E Alg. 2)
 template <bool BF16, bool SGDM = false>
-__device__ __forceinline__ RowB<BF16> load_rowb(const TileB& b, int ib, int l) {
+__device__ __forceinline__ RowB<BF16> load_rowb(const TileB& b, uint32_t off4) {
     RowB<BF16> r;
-    const uint32_t off4 = (uint32_t(ib) * 128u + uint32_t(l) * 4u) * 4u;
     r.p = buf_ld_f4_stream(b.rp, off4);
     r.g = load_grad_regs4<BF16, kPolicyNt>(b.rg, off4);              // read once per step
     r.mq = buf_ld_u16(b.rmq, off4 >> 3);
@@ -1116,7 +1159,7 @@ __device__ __forceinline__ RowB<BF16> load_rowb(const TileB& b, int ib, int l) {
 
 template <bool BF16, bool SGDM, class Mid>
 __device__ __forceinline__ void b128_row(const Hyper& h, const TileB& tb, Lds& s, const RowB<BF16>& cur,
-                                         int ib, int slot, int l, Mid mid) {
+                                         uint32_t off4, int slot, int l, bool tame, Mid mid) {
     float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
     float g[4];
     unpack_grad4<BF16>(cur.g, g);
@@ -1138,7 +1181,7 @@ __device__ __forceinline__ void b128_row(const Hyper& h, const TileB& tb, Lds& s
             vt[e] = 0.0f;
         }
     } else {
-        if (__builtin_expect(__ballot(!scale_is_tame(sv_old)) == 0, 1)) {
+        if (__builtin_expect(tame, 1)) {                      // no old scale of the tile is extreme
             float qf[4];
             codes_to_float4(cur.vq, qf);
             const float s16 = sv_old * 0.0625f;
@@ -1163,27 +1206,10 @@ __device__ __forceinline__ void b128_row(const Hyper& h, const TileB& tb, Lds& s
     const float sm_new = group32_allmax(amax);    // block absmax of m_t
     const float sv_new = SGDM ? 0.0f : group32_allmax(vmax);    // block maximum of v_t
 
-    uint32_t mq_new = 0;
-    uint32_t dist = scale_is_tame(sm_new) ? 0xFFFFFFFFu : 0u;
-    {
-        const float inv_s = approx_inv(sm_new);
-#pragma unroll
-        for (int e = 0; e < 4; e += 2) {
-            uint32_t da, db;
-            mq_new |= quant_m_code_fast(s.search, mt[e], inv_s, da) << (4 * e);
-            mq_new |= quant_m_code_fast(s.search, mt[e + 1], inv_s, db) << (4 * e + 4);
-            dist = min(min(dist, da), db);
-        }
-    }
-    if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
-        mq_new = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mq_new |= quant_m_code(s.search, mt[e], sm_new) << (4 * e);
-    }
-
+    const uint32_t mq_new = compress_m4(s.search, mt, sm_new);
     uint32_t vq_new = 0;
     if constexpr (!SGDM) {
-        const float inv_s = approx_inv(sv_new);
+        const float inv_s = approx_inv16(sv_new);
         uint32_t lo = 0, hi = 0;
         float closest = scale_is_tame(sv_new) ? 0.5f : 0.0f, fa, fb;
 #define LPMM_VB(K)                                                               \
@@ -1200,7 +1226,6 @@ __device__ __forceinline__ void b128_row(const Hyper& h, const TileB& tb, Lds& s
         }
     }
 
-    const uint32_t off4 = (uint32_t(ib) * 128u + uint32_t(l) * 4u) * 4u;
     {   // through the tile's bounds-checked resources: no registers for a second set of base addresses
         const v4f_t v = {w[0], w[1], w[2], w[3]};
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u_t, v), tb.rp, int(off4), 0, kPolicyNtSc1);
@@ -1229,35 +1254,43 @@ __device__ __forceinline__ void b128_tile(const Tensor4& a, const Hyper& h, int 
     const TileB tb = tile_b128<BF16>(a, sup0, n_sup > 0 ? n_sup : 0);
     const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
     const int slice0 = (wg % slices) * rounds;
-    const int first = grp * kB128Stride + slice0;                      // the group's first block in the super-tile
-    int nv = n_sup - first;                                            // the group's blocks: 0 .. rounds
-    nv = nv < 0 ? 0 : (nv > rounds ? rounds : nv);
-    // blocks past the group's share must not be fetched (inside the super-tile they are real blocks,
-    // another workgroup's): they get an index beyond every tile
-    auto blk = [&](int k) { return k < nv ? first + k : kNoBlock; };
+    // The group's blocks are grp * 64 + slice0 + k, k < rounds; those behind the tensor's last block lie beyond the tile's
+    // resources, and a prefetch past the group's share (a real block of another workgroup) gets an offset that does.  The
+    // round is the same for all groups and stays in scalar registers.
+    const uint32_t lane4 = uint32_t(grp * kB128Stride + slice0) * 512u + uint32_t(l) * 16u;
+    auto off = [&](int k) { return lane4 + (k < rounds ? uint32_t(k) * 512u : kNoBlock); };
+    auto fetch = [&](int k) { return load_rowb<BF16, SGDM>(tb, off(k)); };
     const int slot0 = grp * rounds;
     int k = 0;
-    RowB<BF16> r0 = load_rowb<BF16, SGDM>(tb, blk(0), l);
-    RowB<BF16> r1 = load_rowb<BF16, SGDM>(tb, blk(1), l);
+    RowB<BF16> r0 = fetch(0);
+    RowB<BF16> r1 = fetch(1);
     RowB<BF16> r2;
+    bool lane_tame = true;
     for (int t = threadIdx.x; t < kGroups * rounds; t += kThreads) {   // old block scales into the slots of the new ones
         const int b = (t / rounds) * kB128Stride + slice0 + t % rounds;
         s.blk_scale[t] = b < n_sup ? tb.ms[b] : 0.0f;
-        if constexpr (!SGDM) s.blk_vmax[t] = b < n_sup ? tb.vs[b] : 0.0f;
+        if constexpr (!SGDM) {
+            const float v = b < n_sup ? tb.vs[b] : 0.0f;
+            s.blk_vmax[t] = v;
+            lane_tame = bool(int(lane_tame) & int(scale_is_tame(v)));
+        }
     }
     load_tables(s);                                // the first blocks' loads are in flight meanwhile; its barrier
                                                    // also publishes the staged scales
+    bool tame = true;
+    if constexpr (!SGDM) tame = !__syncthreads_or(int(!lane_tame));
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);       // loop start-up state: nothing outstanding (see pass 1)
     auto none = [] {};
-    while (k + 2 < nv) {                           // rounds of three blocks, no exit in the middle
-        b128_row<BF16, SGDM>(h, tb, s, r0, first + k, slot0 + k, l, [&] { r2 = load_rowb<BF16, SGDM>(tb, blk(k + 2), l); });
-        b128_row<BF16, SGDM>(h, tb, s, r1, first + k + 1, slot0 + k + 1, l, [&] { r0 = load_rowb<BF16, SGDM>(tb, blk(k + 3), l); });
-        b128_row<BF16, SGDM>(h, tb, s, r2, first + k + 2, slot0 + k + 2, l, [&] { r1 = load_rowb<BF16, SGDM>(tb, blk(k + 4), l); });
+    auto work = [&](const RowB<BF16>& cur, int kk, auto mid) { b128_row<BF16, SGDM>(h, tb, s, cur, off(kk), slot0 + kk, l, tame, mid); };
+    while (k + 2 < rounds) {                       // rounds of three blocks, no exit in the middle
+        work(r0, k, [&] { r2 = fetch(k + 2); });
+        work(r1, k + 1, [&] { r0 = fetch(k + 3); });
+        work(r2, k + 2, [&] { r1 = fetch(k + 4); });
         k += 3;
     }
-    if (k < nv) {
-        b128_row<BF16, SGDM>(h, tb, s, r0, first + k, slot0 + k, l, none);
-        if (k + 1 < nv) b128_row<BF16, SGDM>(h, tb, s, r1, first + k + 1, slot0 + k + 1, l, none);
+    if (k < rounds) {
+        work(r0, k, none);
+        if (k + 1 < rounds) work(r1, k + 1, none);
     }
     __syncthreads();
     for (int t = threadIdx.x; t < kGroups * rounds; t += kThreads) {   // new block scales: 8 contiguous runs
@@ -1505,7 +1538,7 @@ __device__ __forceinline__ void pass1_general_tile(const Tensor4& a, const Hyper
 }
 
 // the 2048 elements from e_first (a multiple of 8) on
-template <bool BF16>
+template <bool BF16, bool SAME_LAUNCH = false>
 __device__ __forceinline__ void pass2_general_chunk(const Tensor4& a, const Hyper& h, int64_t e_first) {
     const LaneIo io = lane_io(a.P, a.cols, e_first / 8 + threadIdx.x);
     if (!io.nv) return;
@@ -1524,7 +1557,7 @@ __device__ __forceinline__ void pass2_general_chunk(const Tensor4& a, const Hype
         if (e < io.nv) {
             const float v_prev = dequant_v((vq >> (4 * e)) & 15u, fminf(a.r[i], a.c[j]));
             const float vt = moment_v(h, v_prev, g[e]);
-            vq_new |= quant_v_code(vt, fminf(a.r_new[i], a.c_new[j])) << (4 * e);
+            vq_new |= quant_v_code(vt, fminf(ld_ws<SAME_LAUNCH>(a.r_new + i), ld_ws<SAME_LAUNCH>(a.c_new + j))) << (4 * e);
             if (++j == a.cols) { j = 0; ++i; }
         }
     }
@@ -1564,12 +1597,13 @@ __device__ __forceinline__ void atomic_add_f32(float* addr, float v) { (void)uns
 __device__ __forceinline__ float stat_ema(const Hyper& h, float old, float sum_sq) {
     return __builtin_fmaf(h.beta2, old, h.omb2 * sum_sq);
 }
+template <bool SAME_LAUNCH = false>
 __device__ __forceinline__ float factor_inv_total(const Tensor4& a, const Hyper& h) {
     const float* tot = reinterpret_cast<const float*>(a.counter);
     float sum_new = 0.0f, sum_old = 0.0f;
     for (int k = 0; k < a.tot_slots; ++k) {
-        sum_new += tot[tot_new_word(k)];
-        sum_old += tot[tot_old_word(k)];
+        sum_new += ld_ws<SAME_LAUNCH>(tot + tot_new_word(k));
+        sum_old += ld_ws<SAME_LAUNCH>(tot + tot_old_word(k));
     }
     const float total = stat_ema(h, sum_old, sum_new);
     return total > 0.0f ? 1.0f / total : 0.0f;          // all-zero statistics: v_t = 0
@@ -1689,9 +1723,8 @@ struct RowF {                      // everything the update pass reads for one r
 };
 
 template <bool BF16>
-__device__ __forceinline__ RowF<BF16> load_rowf(const TileBase& b, const Tensor4& a, const Geo& g, int il) {
+__device__ __forceinline__ RowF<BF16> load_rowf(const TileBase& b, uint32_t off4) {
     RowF<BF16> r;
-    const uint32_t off4 = row_offset(il, a.cols, g.col0) * 4u;
     r.p = buf_ld_f4_stream(b.rp, off4);
     r.g = load_grad_regs4<BF16, kPolicyNt>(b.rg, off4);     // last use of the gradient in this step
     r.mq = buf_ld_u16(b.rmq, off4 >> 3);
@@ -1701,13 +1734,12 @@ __device__ __forceinline__ RowF<BF16> load_rowf(const TileBase& b, const Tensor4
 // One row of the update pass for one lane; ct[e] = C_t of the lane's columns.  The row's old block scale and
 // R_t[i] / sum R_t come from LDS, where the tile staged them (see pass 1).
 template <bool BF16, class Mid>
-__device__ __forceinline__ void factor_row(const Tensor4& a, const Hyper& h, const TileBase& tb, const Geo& geo,
-                                           Lds& s, const RowF<BF16>& cur, int il, const float ct[4], Mid mid) {
+__device__ __forceinline__ void factor_row(const Hyper& h, const TileBase& tb, const Geo& geo, Lds& s,
+                                           const RowF<BF16>& cur, uint32_t off4, int slot, const float ct[4], Mid mid) {
     float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
     float g[4];
     unpack_grad4<BF16>(cur.g, g);
     float mt[4], amax = 0.0f;
-    const int slot = il * a.gx + geo.gxi;
     const float s_old = s.blk_scale[slot], rn = s.blk_vmax[slot];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -1726,76 +1758,73 @@ __device__ __forceinline__ void factor_row(const Tensor4& a, const Hyper& h, con
     __builtin_amdgcn_sched_barrier(0);
     const float s_new = group32_allmax(amax);
 
-    uint32_t mq_new = 0;
-    uint32_t dist = scale_is_tame(s_new) ? 0xFFFFFFFFu : 0u;
-    {
-        const float inv_s = approx_inv(s_new);
-#pragma unroll
-        for (int e = 0; e < 4; e += 2) {
-            uint32_t da, db;
-            mq_new |= quant_m_code_fast(s.search, mt[e], inv_s, da) << (4 * e);
-            mq_new |= quant_m_code_fast(s.search, mt[e + 1], inv_s, db) << (4 * e + 4);
-            dist = min(min(dist, da), db);
-        }
-    }
-    if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
-        mq_new = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mq_new |= quant_m_code(s.search, mt[e], s_new) << (4 * e);
-    }
-    store_row1(tb, row_offset(il, a.cols, geo.col0) * 4u, w, mq_new);
+    store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
     if (geo.l == 0) s.blk_scale[slot] = s_new;
 }
 
-// Update pass, fast path: tiled and pipelined like pass 1.
-template <bool BF16>
-__device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+// Update pass, fast path: tiled and pipelined like pass 1.  SAME_LAUNCH, ready: as in pass2_tile.
+template <bool BF16, bool SAME_LAUNCH = false, class Ready = AlwaysReady>
+__device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s, Ready ready = Ready()) {
     const Geo geo = geometry(a, wg);
     const TileBase tb = tile_base<BF16>(a, geo.row0, geo.n_rows);
-    const int n = geo.n_rows, rs = a.rs;
-    const int row_g = geo.gyi << rs, hop = a.gy << rs, low = (1 << rs) - 1;
-    auto row = [&](int k) { return row_g + (k & low) + (k >> rs) * hop; };
-    float ct[4] = {0.0f, 0.0f, 0.0f, 0.0f}, csum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    RowF<BF16> r0{}, r1{}, r2;
-    if (geo.active) {
-        load4(a.c + geo.col0, ct);
+    const RowWalk walk{a.rs, a.gy << a.rs};
+    const int n = walk.rounds(geo.n_rows);
+    const uint32_t lane4 = row_offset(geo.gyi << a.rs, a.cols, geo.col0) * 4u, pitch4 = uint32_t(a.cols) * 4u;
+    const int slot0 = (geo.gyi << a.rs) * a.gx + geo.gxi;
+    auto off = [&](int k) { return lane4 + uint32_t(walk.at(k)) * pitch4; };
+    auto fetch = [&](int k) { return load_rowf<BF16>(tb, off(k)); };
+    float ct[4], csum[4];
+    RowF<BF16> r0 = fetch(0), r1 = fetch(1), r2;
+    load4(a.c + geo.col0, ct);
+    if (!ready()) return;
+    float inv_total;
+    if constexpr (SAME_LAUNCH) {                 // through LDS, one agent-scope load per word (see pass2_tile)
+        for (int t = threadIdx.x; t < a.gx * 128; t += kThreads) s.col[t] = ld_ws<true>(a.c_new + int64_t(geo.strip) * a.gx * 128 + t);
+        if (threadIdx.x == 0) s.cold[0] = factor_inv_total<true>(a, h);
+        __syncthreads();
+        inv_total = s.cold[0];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) csum[e] = s.col[geo.gxi * 128 + geo.l * 4 + e];
+    } else {
         load4(a.c_new + geo.col0, csum);
-        r0 = load_rowf<BF16>(tb, a, geo, row(0));
-        r1 = load_rowf<BF16>(tb, a, geo, row(1));
+        inv_total = factor_inv_total(a, h);
     }
-    // per row of the tile: the old block scales of m, and R_t[i] / sum R_t once instead of in every lane
-    const float inv_total = factor_inv_total(a, h);
-    for (int t = threadIdx.x; t < n * a.gx; t += kThreads) {
+    // per row of the tile: the old block scales of m, and R_t[i] / sum R_t once instead of in every lane; zeros for rows
+    // behind its end
+    for (int t = threadIdx.x; t < a.rw * a.gx; t += kThreads) {
         const int il = t / a.gx, cbi = geo.strip * a.gx + t % a.gx;
-        s.blk_scale[t] = cbi < a.nb ? tb.ms[row_offset(il, a.nb, uint32_t(cbi))] : 0.0f;
-        s.blk_vmax[t] = stat_ema(h, tb.r[il], tb.r_new[il]) * inv_total;
+        const bool in = il < geo.n_rows;
+        s.blk_scale[t] = in ? tb.ms[row_offset(il, a.nb, uint32_t(cbi))] : 0.0f;
+        s.blk_vmax[t] = in ? stat_ema(h, tb.r[il], ld_ws<SAME_LAUNCH>(tb.r_new + il)) * inv_total : 0.0f;
     }
     load_tables(s);          // its barrier also publishes the staged values
-    if (geo.active) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ct[e] = stat_ema(h, ct[e], csum[e]);
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        int k = 0;
-        auto none = [] {};
-        while (row(k + 2) < n) {
-            factor_row<BF16>(a, h, tb, geo, s, r0, row(k), ct, [&] { r2 = load_rowf<BF16>(tb, a, geo, row(k + 2)); });
-            factor_row<BF16>(a, h, tb, geo, s, r1, row(k + 1), ct, [&] { r0 = load_rowf<BF16>(tb, a, geo, row(k + 3)); });
-            factor_row<BF16>(a, h, tb, geo, s, r2, row(k + 2), ct, [&] { r1 = load_rowf<BF16>(tb, a, geo, row(k + 4)); });
-            k += 3;
-        }
-        if (row(k) < n) {
-            factor_row<BF16>(a, h, tb, geo, s, r0, row(k), ct, none);
-            if (row(k + 1) < n) factor_row<BF16>(a, h, tb, geo, s, r1, row(k + 1), ct, none);
-        }
+    for (int e = 0; e < 4; ++e) ct[e] = stat_ema(h, ct[e], csum[e]);
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    auto none = [] {};
+    auto work = [&](const RowF<BF16>& cur, int k, auto mid) {
+        factor_row<BF16>(h, tb, geo, s, cur, off(k), slot0 + walk.at(k) * a.gx, ct, mid);
+    };
+    int k = 0;
+    while (k + 2 < n) {
+        work(r0, k, [&] { r2 = fetch(k + 2); });
+        work(r1, k + 1, [&] { r0 = fetch(k + 3); });
+        work(r2, k + 2, [&] { r1 = fetch(k + 4); });
+        k += 3;
+    }
+    if (k < n) {
+        work(r0, k, none);
+        if (k + 1 < n) work(r1, k + 1, none);
     }
     __syncthreads();
     for (int t = threadIdx.x; t < geo.n_rows * a.gx; t += kThreads) {
         const int il = t / a.gx, cbi = geo.strip * a.gx + t % a.gx;
-        if (cbi < a.nb) st<float>(tb.ms, row_offset(il, a.nb, uint32_t(cbi)) * 4u, s.blk_scale[t]);
+        st<float>(tb.ms, row_offset(il, a.nb, uint32_t(cbi)) * 4u, s.blk_scale[t]);
     }
 }
 
 // stat[i] = stat_ema(stat[i], sum[i]); sum[i] = 0, by one workgroup (see move_and_clear)
+template <bool SAME_LAUNCH = false>
 __device__ __forceinline__ void ema_and_clear(const Hyper& h, float* stat, float* sum, int64_t n) {
     constexpr int kDepth = 8;
     for (int64_t base = threadIdx.x; base < n; base += int64_t(kThreads) * kDepth) {
@@ -1804,7 +1833,7 @@ __device__ __forceinline__ void ema_and_clear(const Hyper& h, float* stat, float
         for (int u = 0; u < kDepth; ++u) {
             const int64_t i = base + int64_t(u) * kThreads;
             o[u] = i < n ? stat[i] : 0.0f;
-            v[u] = i < n ? sum[i] : 0.0f;
+            v[u] = i < n ? ld_ws<SAME_LAUNCH>(sum + i) : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
@@ -2006,7 +2035,7 @@ __device__ __forceinline__ void factor_stats_general_tile(const Tensor4& a, int 
         }
 }
 
-template <bool BF16>
+template <bool BF16, bool SAME_LAUNCH = false>
 __device__ __forceinline__ void factor_update_general_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
     const int64_t t = int64_t(wg) * kThreads + threadIdx.x;
     const int64_t block = t >> 4;                       // uniform over the 16 lanes of a block
@@ -2025,7 +2054,7 @@ __device__ __forceinline__ void factor_update_general_tile(const Tensor4& a, con
     }
     const uint32_t mq = load_codes(a.mq, io);
     const float s_old = a.ms[block];
-    const float inv_total = factor_inv_total(a, h);
+    const float inv_total = factor_inv_total<SAME_LAUNCH>(a, h);
     float mt[8], amax = 0.0f;
     int64_t i = io.i, j = io.j;
 #pragma unroll
@@ -2034,8 +2063,8 @@ __device__ __forceinline__ void factor_update_general_tile(const Tensor4& a, con
             const float2 tt = s.deq[(mq >> (8 * (e >> 1))) & 255u];
             const float m_prev = ((e & 1) ? tt.y : tt.x) * s_old;
             mt[e] = moment_m(h, m_prev, g[e]);
-            const float rn = stat_ema(h, a.r[i], a.r_new[i]) * inv_total;
-            const float vt = rn * stat_ema(h, a.c[j], a.c_new[j]);
+            const float rn = stat_ema(h, a.r[i], ld_ws<SAME_LAUNCH>(a.r_new + i)) * inv_total;
+            const float vt = rn * stat_ema(h, a.c[j], ld_ws<SAME_LAUNCH>(a.c_new + j));
             w[e] = param_update(h, w[e], mt[e], vt);
             amax = fmaxf(amax, fabsf(mt[e]));
             if (++j == a.cols) { j = 0; ++i; }

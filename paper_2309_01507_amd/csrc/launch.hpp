@@ -17,7 +17,7 @@ __global__ __launch_bounds__(kThreads) void pass1_fast(const Tensor4 a, const Hy
     const int wg = logical_wg();
     if (wg >= a.n_wg) return;
     if (a.flat) pass1_flat_tile<BF16>(a, h, wg, s);
-    else pass1_fast_tile<BF16, false>(a, h, wg, s);
+    else pass1_fast_tile<BF16>(a, h, wg, s);
 }
 
 template <bool BF16>
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
             // not reached: the host launches this variant only for groups without rank-1 tensors
         } else if (a.kind == kQuantFast) {
             if (a.flat) pass1_flat_tile<BF16>(a, ht, wg, s);
-            else pass1_fast_tile<BF16, false>(a, ht, wg, s);
+            else pass1_fast_tile<BF16>(a, ht, wg, s);
         } else if (a.kind == kQuantRagged) {
             pass1_ragged<BF16>(a, ht, wg, s);
         } else {

@@ -10,10 +10,11 @@
 #include <memory>
 #include <mutex>
 #include <unordered_map>
+#include <numeric>
 #include <vector>
 
 #include "../../include/lpmm4.h"
-#include "launch.hpp"
+#include "flow.hpp"
 #include "convert.hpp"
 #include "ablation.hpp"
 
@@ -707,6 +708,8 @@ struct PlanHost {
     bool sgdm = false;                  // a plan of SGD-with-momentum tensors (lpmm_sgdm4_step_multi)
     bool flat = false;                  // large tensors, several groups: pass 1 uses the flat tiling
     bool serial = false;                // LPMM_MULTI_STREAMS=0: every pass a launch of its own on the caller's stream
+    bool flow = false;                  // the whole step is one launch (flow.hpp)
+    FlowArgs flow_args{};
     int64_t params = 0;                 // parameters of all tensors of the plan
     Hyper* d_hyper = nullptr;           // device slot inside the plan for the hyper-parameters of a captured step
     int device = 0;
@@ -731,8 +734,9 @@ struct PlanHost {
 std::unordered_map<void*, std::shared_ptr<PlanHost>> g_plans;
 
 struct PlanLayout {
-    size_t off_tensors, off_dims, off_hyper, off_counters, off_floats, total;
+    size_t off_tensors, off_dims, off_hyper, off_items, off_counters, off_deferred, off_floats, total;
     int64_t n_nd;
+    int64_t cap_items, cap_deferred;    // room for the work list and the deferred tiles of a one-launch step
 };
 
 bool desc_shape_ok(const lpmm_tensor_desc& d) {
@@ -756,6 +760,69 @@ bool plan_inner_dims(const lpmm_tensor_desc& d, int64_t i, const int64_t* inner_
     int64_t rows, cols;
     if (nd_shape(dims, 1 + k, &rows, &cols, ext, dm) != LPMM_OK) return false;
     return cols == d.cols;
+}
+
+// Tiles of one tensor of a plan that is stepped in one launch; `total`: parameters of the plan.  A function of the shapes
+// alone, because the size of the plan's memory follows from it.
+//
+// Pass 1 walks down its rows, 64 of them (GPT-2-medium set 837 us; 32 rows: 979, 128: 839, 256: 881; along the rows, 16 at
+// a time: 915), except in tensors of 2^24 parameters and more with wide rows, whose strips it walks along their rows, 16
+// rows at a time (7B-shaped set 16.85 ms; 8 rows 17.2, 32 rows 17.6, down 64 rows 17.03).  Pass 2 takes 128 rows (64 rows:
+// 851 us and 17.2 ms, 256 rows: 838 us and 16.84 ms, 128: 837 us and 16.80 ms; BERT-base 303, 303 and 322 us for 64, 128
+// and 256).  Sets of less than 2^25 parameters (they are here for the sake of their convolutions) take shorter tiles to
+// have enough of them: 7.4 million parameters 75, 70, 56 and 83 us with the rows divided by 1, 2, 4 and 8.
+constexpr int64_t kFlowMinParams = int64_t(1) << 25;
+void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int grad_bytes) {
+    constexpr int kCus = 256;
+    const int shrink = total >= kFlowMinParams ? 0 : total >= kFlowMinParams / 4 ? 1 : 2;
+    const bool flat = t->P >= (int64_t(1) << 24) && t->cols >= 2048;
+    const int rw = flat ? std::max(16 >> shrink, kGroups) : 64 >> shrink, rw2 = 128 >> shrink;
+    if (desc_kind == LPMM_KIND_FP32) {
+        t->kind = kFp32State;
+        t->n_wg = t->n_wg2 = int((t->P + kElemsPerWg32 - 1) / kElemsPerWg32);
+    } else if (desc_kind == LPMM_KIND_4BIT_B128) {
+        t->kind = kQuantBlockV;
+        b128_geometry(t, kCus, 8 >> shrink);
+    } else if (desc_kind == LPMM_KIND_4BIT_FACTOR) {
+        factor_geometry(t, kCus, 64 >> shrink, rw2, grad_bytes, (t->cols % LPMM_BLOCK) == 0 && aligned_c &&
+                        fast_eligible(t->cols, nullptr), 1);
+    } else if (aligned_c && fast_eligible(t->cols, nullptr)) {
+        t->kind = kQuantFast;
+        fast_geometry(t, kCus, rw, rw2, grad_bytes, flat);
+    } else if (ragged_eligible(t->rows, t->cols)) {
+        ragged_geometry(t, 0, shrink);
+    } else {
+        t->kind = kQuantGeneral;
+        general_geometry(t, kCus);
+    }
+}
+bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast || kind == kFactorGeneral; }
+
+// Whether a list of tensors is stepped in one launch: some tensor has two passes, no sums in a fixed order, and the
+// statistics of tensors with more than two dimensions are few enough for one workgroup.  Below 2^25 parameters the launches
+// by phases are faster: there is little in flight to hide a tensor's wait between the passes behind (us, phases / one
+// launch: 9.0 M parameters 38 / 38, 16.7 M 64 / 68, factorized 50 / 54; 56 M 156 / 152, 109 M 358 / 310, 143 M 461 / 408,
+// 294 M 1103 / 956, 501 M 1528 / 1352).  With convolutions, which take four dependent launches, one launch is faster
+// there, too (7.4 M parameters: 60 / 56).
+bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim) {
+    if (env_int("LPMM_FLOW", 1) == 0 || std::getenv("LPMM_MULTI_STREAMS") || std::getenv("LPMM_PHASE_MPARAMS")) return false;
+    bool second = false, nd = false;
+    int64_t total = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        const lpmm_tensor_desc& d = descs[i];
+        if (d.kind == LPMM_KIND_SGDM_4BIT || d.kind == LPMM_KIND_SGDM_FP32 || (d.flags & LPMM_FLAG_DETERMINISTIC)) return false;
+        if (d.rows * d.cols > (int64_t(1) << 37)) return false;
+        if (d.kind == LPMM_KIND_4BIT_ND) {
+            InnerDims dm;
+            int64_t ext;
+            if (!plan_inner_dims(d, i, inner_dims, inner_ndim, &dm, &ext)) return false;
+            if (d.cols > kFlowNdCols || ext > kFlowNdStats) return false;
+            nd = true;
+        }
+        total += d.rows * d.cols;
+        second = second || d.kind == LPMM_KIND_4BIT || d.kind == LPMM_KIND_4BIT_ND || d.kind == LPMM_KIND_4BIT_FACTOR;
+    }
+    return second && (nd || total >= env_int("LPMM_FLOW_MIN", int(kFlowMinParams)));
 }
 
 bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim,
@@ -785,14 +852,122 @@ bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_
         if (descs[i].kind == LPMM_KIND_SGDM_4BIT || descs[i].kind == LPMM_KIND_SGDM_FP32) ++n_sgdm;
     if (rank1 && factor) return false;       // two different optimizers: one plan holds one of them
     if (n_sgdm != 0 && n_sgdm != n) return false;
+    L->cap_items = L->cap_deferred = 0;
+    if (flow_possible(descs, n, inner_dims, inner_ndim)) {
+        int64_t total = 0;
+        for (int64_t i = 0; i < n; ++i) total += descs[i].rows * descs[i].cols;
+        for (int64_t i = 0; i < n; ++i) {
+            Tensor4 t{};
+            t.rows = descs[i].rows; t.cols = descs[i].cols; t.P = t.rows * t.cols;
+            flow_geometry(&t, descs[i].kind, true, total, 4);
+            L->cap_items += t.n_wg + 16;                          // lists are padded to multiples of 8
+            if (flow_kind_second(t.kind)) {
+                L->cap_items += t.n_wg2 + 16;
+                L->cap_deferred += t.n_wg2;
+            }
+        }
+        if (L->cap_items > (int64_t(1) << 28)) L->cap_items = L->cap_deferred = 0;
+    }
     size_t off = 0;
     L->off_tensors = off;   off += size_t(round_up(n * int64_t(sizeof(Tensor4)), 256));
     L->off_dims = off;      off += size_t(round_up(n_nd * int64_t(sizeof(InnerDims)), 256));
     L->off_hyper = off;     off += 256;                       // hyper-parameters of a captured step
+    L->off_items = off;     off += size_t(round_up(L->cap_items * int64_t(sizeof(FlowItem)), 256));
     L->off_counters = off;  off += size_t(n) * kCounterWords * sizeof(unsigned int);
+    L->off_deferred = off;  off += size_t(round_up(L->cap_deferred * int64_t(sizeof(int)), 256));
     L->off_floats = off;    off += size_t(floats) * sizeof(float);
     L->total = size_t(round_up(int64_t(off), 256));
     return true;
+}
+
+// The work list of a plan that is stepped in one launch, and the tensors' tiles for it; leaves the plan to the
+// launches by groups if the list does not fit (column maxima that turned out misaligned give more tiles).
+//
+// Both passes are laid on a time line in units of parameters: pass 1 of the tensors one after the other; pass 2 of a
+// tensor starts a lag after its pass 1 ends -- about what is in flight on the chip at a time, so that it finds the first
+// pass complete -- and takes as long as its pass 1 did.  2^23 parameters: with half and one and a half times as many the
+// GPT-2-medium set takes 845 and 846 us in place of 840.  Tensors with more than two dimensions come first, the widest
+// ones ahead: one workgroup turns their maxima into statistics between the passes, and that takes longest where there are
+// many columns.  Then the largest ones: what is left at the end, a pass 2 with no pass 1 beside it, is that of the
+// smallest (as listed, large embeddings last / by size: 56 M parameters 206 / 152 us, 143 M 469 / 408).
+//
+// The two are merged by time, eight workgroups at a time: ids are dealt to the 8 XCDs in turn, and the eight of a row take
+// their tiles from eight equal contiguous parts of the pass, so that neighbouring tiles, which share cache lines, stay on
+// one XCD.  (Merging in runs of up to 2^25 parameters instead of single rows makes no difference.)
+void build_flow(const lpmm_tensor_desc* descs, int64_t n, const PlanLayout& L, char* dplan, int gbytes, PlanHost* host,
+                Tensor4* tens) {
+    int64_t total = 0, n_def = 0;
+    for (int64_t i = 0; i < n; ++i) total += tens[i].P;
+    std::vector<Tensor4> flow(tens, tens + n);
+    for (int64_t i = 0; i < n; ++i) {
+        Tensor4& t = flow[i];
+        t.flat = 0;
+        flow_geometry(&t, descs[i].kind, aligned(descs[i].v_colmax, 16), total, gbytes);
+        if (flow_kind_second(t.kind)) {
+            t.deferred = int(n_def);
+            n_def += t.n_wg2;
+        }
+    }
+    if (n_def > L.cap_deferred) return;
+    struct Row { double time; FlowItem it[kXcds]; };
+    std::vector<Row> first, second;
+    // tiles of one pass in rows of 8; a pass of fewer than 8 workgroups shares its row with the following ones
+    auto add = [](std::vector<Row>& rows, int what, int n_wg, double begin, double length, int* fill) {
+        if (n_wg < kXcds) {
+            for (int w = 0; w < n_wg; ++w) {
+                if (*fill == 0) rows.push_back(Row{begin, {{-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}}});
+                rows.back().time = begin;                           // not before the last of its members may start
+                rows.back().it[*fill] = FlowItem{what, w};
+                *fill = (*fill + 1) % kXcds;
+            }
+            return;
+        }
+        *fill = 0;
+        const int part = (n_wg + kXcds - 1) / kXcds;
+        for (int k = 0; k < part; ++k) {
+            Row r{begin + length * k / part, {}};
+            for (int x = 0; x < kXcds; ++x) {
+                const int w = x * part + k;
+                r.it[x] = w < n_wg ? FlowItem{what, w} : FlowItem{-1, 0};
+            }
+            rows.push_back(r);
+        }
+    };
+    const double lag = double(int64_t(1) << 23);
+    double now = 0.0, now2 = 0.0;
+    int fill1 = 0, fill2 = 0;
+    std::vector<int64_t> order(static_cast<size_t>(n));
+    std::iota(order.begin(), order.end(), int64_t(0));
+    std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) {
+        const bool nx = descs[x].kind == LPMM_KIND_4BIT_ND, ny = descs[y].kind == LPMM_KIND_4BIT_ND;
+        return nx != ny ? nx : nx ? flow[x].cols > flow[y].cols : flow[x].P > flow[y].P;
+    });
+    for (const int64_t i : order) {
+        const double length = double(flow[i].P);
+        add(first, int(i), flow[i].n_wg, now, length, &fill1);
+        now += length;
+        if (!flow_kind_second(flow[i].kind)) continue;
+        now2 = std::max(now2, now + lag);
+        add(second, int(i) | kFlowSecond, flow[i].n_wg2, now2, length, &fill2);
+        now2 += length;
+    }
+    const int64_t n_items = int64_t(first.size() + second.size()) * kXcds;
+    if (n_items > L.cap_items) return;
+    FlowItem* items = reinterpret_cast<FlowItem*>(host->staging.data() + L.off_items);
+    size_t a = 0, b = 0;
+    while (a < first.size() || b < second.size()) {
+        const bool take_first = b == second.size() || (a < first.size() && first[a].time <= second[b].time);
+        const Row& r = take_first ? first[a++] : second[b++];
+        for (int x = 0; x < kXcds; ++x) *items++ = r.it[x];
+    }
+    std::copy(flow.begin(), flow.end(), tens);
+    host->flow = true;
+    host->flow_args.tensors = reinterpret_cast<const Tensor4Table*>(dplan + L.off_tensors);
+    host->flow_args.items = reinterpret_cast<const FlowItem*>(dplan + L.off_items);
+    host->flow_args.dims = reinterpret_cast<const InnerDims*>(dplan + L.off_dims);
+    host->flow_args.deferred = reinterpret_cast<int*>(dplan + L.off_deferred);
+    host->flow_args.n_items = int(n_items);
+    host->flow_args.spin_limit = env_int("LPMM_FLOW_SPIN", 20000);
 }
 
 int fill(void* dst, int64_t n, uint8_t value, int64_t last_index, uint8_t last, hipStream_t s) {
@@ -1530,6 +1705,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         host->params += t.P;
     }
 
+    if (L.cap_items > 0) build_flow(descs, n, L, dplan, gbytes, host.get(), tens);
+
     // groups of consecutive tensors; phase j = A work of group j + B work of group j-1
     std::vector<std::pair<int64_t, int64_t>> groups;      // [first, last)
     for (int64_t i = 0; i < n;) {
@@ -1541,6 +1718,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     // A group whose tensors are small would put few, long workgroups on the chip (one 1024 x 1024 matrix: 128 for
     // its first pass, 32 for its second, on 256 CUs): halve its tiles until each of its launches has two
     // workgroups per CU (measured on that matrix: 23.5 -> 13.8 us per step).
+    if (host->flow) groups.clear();
     for (const auto& gr : groups) {
         for (int shrink = 1; shrink <= 3; ++shrink) {
             int64_t n_a = 0, n_b = 0;
@@ -1555,7 +1733,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             for (int64_t i = gr.first; i < gr.second; ++i) set_geometry(tens[i], descs[i], shrink);
         }
     }
-    for (size_t j = 0; j <= groups.size(); ++j) {
+    for (size_t j = 0; j <= groups.size() && !host->flow; ++j) {
         PhaseLaunch pl{};
         pl.ph.tensors = reinterpret_cast<const Tensor4Table*>(d_tens);
         if (j < groups.size())
@@ -1603,7 +1781,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     host->serial = stream_mode == 0 && !host->sgdm;
     bool any_b = false;
     for (const PhaseLaunch& pl : host->phases) any_b = any_b || pl.ph.n_b > 0;
-    if (stream_mode >= 2 && groups.size() > 1 && !host->sgdm && any_b) {
+    if (stream_mode >= 2 && groups.size() > 1 && !host->sgdm && any_b && !host->flow) {
         LPMM_HIP(hipStreamCreateWithFlags(&host->side, hipStreamNonBlocking));
         LPMM_HIP(hipEventCreateWithFlags(&host->ev_fork, hipEventDisableTiming));
         LPMM_HIP(hipEventCreateWithFlags(&host->ev_join, hipEventDisableTiming));
@@ -1677,6 +1855,26 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
                            weight_decay, host->d_hyper);
         LPMM_HIP(hipGetLastError());
         h.dev = host->d_hyper;
+    }
+    if (host->flow) {
+        const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls;
+        const int64_t call = g_prof.calls;
+        if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), s));
+        const dim3 grid(unsigned(host->flow_args.n_items)), block(kThreads);
+        if (host->factor) {
+            if (bf16) hipLaunchKernelGGL((flow_kernel<true, true>), grid, block, 0, s, host->flow_args, h);
+            else hipLaunchKernelGGL((flow_kernel<false, true>), grid, block, 0, s, host->flow_args, h);
+        } else {
+            if (bf16) hipLaunchKernelGGL((flow_kernel<true, false>), grid, block, 0, s, host->flow_args, h);
+            else hipLaunchKernelGGL((flow_kernel<false, false>), grid, block, 0, s, host->flow_args, h);
+        }
+        LPMM_HIP(hipGetLastError());
+        if (rec) {
+            LPMM_HIP(hipEventRecord(prof_event(call, 1), s));
+            LPMM_HIP(hipEventRecord(prof_event(call, 2), s));
+            g_prof.calls = call + 1;
+        }
+        return LPMM_OK;
     }
     // Plans with the flat tiling of pass 1 run their pass-1 launches with unused dynamic LDS, so that three instead of
     // five workgroups share a CU: two waves per SIMD already saturate pass 1 on large tensors, and more of them only

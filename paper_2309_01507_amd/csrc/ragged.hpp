@@ -132,34 +132,6 @@ __device__ __forceinline__ void lds_load4(const float* s, float out[4]) {
 }
 __device__ __forceinline__ int rag_col(const RagTile& t, int64_t cols, int p) { return p < t.lim ? t.c0 + p : p - t.lim; }
 
-// codes of 4 first moments against their block's scale (see pass1_row)
-__device__ __forceinline__ uint32_t compress_m4(const SearchEntry* s_search, const float mt[4], float s_new) {
-    uint32_t q = 0, dist = scale_is_tame(s_new) ? 0xFFFFFFFFu : 0u;
-    const float inv_s = approx_inv(s_new);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        uint32_t d;
-        q |= quant_m_code_fast(s_search, mt[e], inv_s, d) << (4 * e);
-        dist = min(dist, d);
-    }
-    if (__builtin_expect(__ballot(dist < kMinDistM) != 0, 0)) {
-        q = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) q |= quant_m_code(s_search, mt[e], s_new) << (4 * e);
-    }
-    return q;
-}
-
-template <bool BF16>
-__device__ __forceinline__ Row1<BF16> rag_load1(const TileBase& b, uint32_t off4) {       // off4: the lane's
-    Row1<BF16> r;
-    r.p = buf_ld_f4_stream(b.rp, off4);
-    r.g = load_grad_regs4<BF16>(b.rg, off4);
-    r.mq = buf_ld_u16(b.rmq, off4 >> 3);
-    r.vq = buf_ld_u16(b.rvq, off4 >> 3);
-    return r;
-}
-
 template <bool BF16>
 __device__ __forceinline__ TileBase rag_base(const Tensor4& a, const RagTile& t) {
     TileBase b;
@@ -175,7 +147,7 @@ __device__ __forceinline__ TileBase rag_base(const Tensor4& a, const RagTile& t)
 // One block of pass 1.  l = lane of the group.
 template <bool BF16, class Mid>
 __device__ __forceinline__ void rag_unit1(const Tensor4& a, const Hyper& h, const TileBase& tb, const RagTile& t, Lds& s,
-                                          const Row1<BF16>& cur, const RagUnit& u, int l, bool cols_tame, Mid mid) {
+                                          const Row1<BF16>& cur, const RagUnit& u, int l, bool tame, Mid mid) {
     float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
     float g[4];
     unpack_grad4<BF16>(cur.g, g);
@@ -191,8 +163,7 @@ __device__ __forceinline__ void rag_unit1(const Tensor4& a, const Hyper& h, cons
         mt[2 * k] = d.x * s_old;
         mt[2 * k + 1] = d.y * s_old;
     }
-    const bool tame = bool(int(cols_tame) & int(scale_is_tame(r_a)) & int(scale_is_tame(r_b)));
-    if (__builtin_expect(__ballot(!tame) == 0, 1)) {
+    if (__builtin_expect(tame, 1)) {
         float qf[4], c16[4];
         codes_to_float4(cur.vq, qf);
         lds_load4(&s.cold[p4], c16);
@@ -241,19 +212,21 @@ __device__ __forceinline__ void pass1_ragged_tile(const Tensor4& a, const Hyper&
     const TileBase tb = rag_base<BF16>(a, t);
     const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
     auto unit = [&](int q) { return rag_unit<ONE_STRIP>(t, a, grp, q); };
-    auto fetch = [&](const RagUnit& u) { return rag_load1<BF16>(tb, u.off4 == kRagNowhere ? kRagNowhere : u.off4 + 16u * l); };
+    auto fetch = [&](const RagUnit& u) { return load_row1<BF16>(tb, u.off4 == kRagNowhere ? kRagNowhere : u.off4 + 16u * l); };
     const int n = rag_units<ONE_STRIP>(t, a);
     RagUnit u0 = unit(0), u1 = unit(1), u2;
     Row1<BF16> r0 = fetch(u0), r1 = fetch(u1), r2;
-    bool tame = true;
+    bool lane_tame = true;
     for (int k = threadIdx.x; k < t.width + 128; k += kThreads) {
         const float c = a.c[rag_col(t, a.cols, k)];
-        tame = bool(int(tame) & int(scale_is_tame(c)));
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(c)));
         s.cold[k] = c * 0.0625f;
         s.col[k] = 0.0f;
     }
     for (int k = threadIdx.x; k < kRagRowSlots; k += kThreads) {
-        s.blk_vmax[k] = k < t.n_rows && t.row0 + k < a.rows ? a.r[t.row0 + k] : 0.0f;
+        const float r = k < t.n_rows && t.row0 + k < a.rows ? a.r[t.row0 + k] : 0.0f;
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
+        s.blk_vmax[k] = r;
         s.blk_vmax[kRagRowSlots + k] = 0.0f;
     }
     // old block scales into the slots of the new ones
@@ -265,11 +238,11 @@ __device__ __forceinline__ void pass1_ragged_tile(const Tensor4& a, const Hyper&
             if (k % kFlatBlocks < t.per_row && b < t.end) s.blk_scale[k] = tb.ms[b];
         }
     }
-    const bool cols_tame = !__syncthreads_or(int(!tame));
     load_tables(s);
+    const bool tame = !__syncthreads_or(int(!lane_tame));
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see pass 1)
     auto none = [] {};
-    auto work = [&](const Row1<BF16>& cur, const RagUnit& u, auto mid) { rag_unit1<BF16>(a, h, tb, t, s, cur, u, l, cols_tame, mid); };
+    auto work = [&](const Row1<BF16>& cur, const RagUnit& u, auto mid) { rag_unit1<BF16>(a, h, tb, t, s, cur, u, l, tame, mid); };
     int q = 0;
     while (q + 2 < n) {                                   // rounds of three units, no exit in the middle
         work(r0, u0, [&] { u2 = unit(q + 2); r2 = fetch(u2); });
@@ -310,11 +283,11 @@ __device__ __forceinline__ void pass1_ragged(const Tensor4& a, const Hyper& h, i
 }
 
 // Workgroups [0, n_wg2) of pass 2: the tiles, then the parts of the last row if the tiles leave it out.
-template <bool BF16>
-__device__ __forceinline__ void pass2_ragged(const Tensor4& a, const Hyper& h, int wg) {
+template <bool BF16, bool SAME_LAUNCH = false, class Ready = AlwaysReady, class S = NoLds>
+__device__ __forceinline__ void pass2_ragged(const Tensor4& a, const Hyper& h, int wg, Ready ready = Ready(), S&& s = S()) {
     const int tiles = int((pass2_rows(a, true) + a.rw2 - 1) / a.rw2) * a.strips2;
-    if (wg < tiles) pass2_tile<BF16, true>(a, h, wg);
-    else pass2_last_row<BF16>(a, h, wg - tiles);
+    if (wg < tiles) pass2_tile<BF16, true, SAME_LAUNCH>(a, h, wg, ready, s);
+    else if (ready()) pass2_last_row<BF16, SAME_LAUNCH>(a, h, wg - tiles);
 }
 
 }  // namespace lpmm

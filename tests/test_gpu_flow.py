@@ -1,0 +1,124 @@
+"""Plans whose step is one launch with both passes of every tensor in it: the same sets through the launches by phases
+(LPMM_FLOW=0) and through the one launch (LPMM_FLOW_MIN=0: small sets, too), with the tiles of the second pass waiting for
+the first one, and with every tile that does not find it complete deferred to the tensor's last workgroup
+(LPMM_FLOW_SPIN=0).  The rank-1 results are the same bits on every route; the factorized statistics are sums in another
+order (tolerance: see test_gpu_factor)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2309_01507_amd as lpmm
+import workloads
+from gpu_util import DEV, PARAM_ATOL, PARAM_RTOL, to_dev
+from test_gpu_factor import STAT_RTOL
+from test_gpu_multi import _mini_transformer, _run_set
+
+pytestmark = pytest.mark.gpu
+HP = oracle.Hyper()
+PHASES = {"LPMM_FLOW": "0"}
+ONE = {"LPMM_FLOW_MIN": "0"}
+DEFERRED = {"LPMM_FLOW_MIN": "0", "LPMM_FLOW_SPIN": "0"}
+
+# every kind of tile: whole blocks, rows that are no multiple of 128, narrow ones, one workgroup and many, a wide one
+RANK1 = [("rank1", (300, 512)), ("rank1", (130, 4224)), ("rank1", (37, 200)), ("rank1", (1030, 129)), ("rank1", (40, 96)),
+         ("rank1", (1, 5000)), ("rank1", (257, 1023)), ("offset", (70, 1280)), ("nd", (24, 16, 3, 3)), ("nd", (8, 1, 2, 128)),
+         ("nd", (5, 3, 1024)), ("b128", (1, 70001)), ("fp32", (1, 3000)), ("rank1", (2050, 640))]
+FACTOR = [("factor", (300, 512)), ("factor", (37, 200)), ("factor", (1, 5000)), ("factor", (1030, 640)), ("fp32", (1, 768)),
+          ("b128", (1, 8192)), ("factor", (257, 1023))]
+
+
+def _steps(monkeypatch, env, tensors, bf16, steps=3, capture=False):
+    """`steps` steps of one plan; all parameters and states, as arrays."""
+    for k in ("LPMM_FLOW", "LPMM_FLOW_MIN", "LPMM_FLOW_SPIN"):
+        monkeypatch.delenv(k, raising=False)
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    lpmm.ensure_init(8192)
+    ws, gs, states, descs = [], [], [], []
+    for tid, (kind, shape) in enumerate(tensors):
+        rows, cols = shape[0], int(np.prod(shape[1:]))
+        w = to_dev(workloads.weights(81, tid, rows, cols).reshape(-1))
+        g = torch.empty(rows * cols, dtype=torch.bfloat16 if bf16 else torch.float32, device=DEV)
+        if kind == "nd":
+            st = lpmm.new_state_nd(shape, DEV)
+        elif kind == "b128":
+            st = lpmm.new_state_b128(cols, DEV)
+        elif kind == "factor":
+            st = lpmm.new_state_factor(rows, cols, DEV)
+        elif kind == "fp32":
+            st = (torch.zeros(cols, device=DEV), torch.zeros(cols, device=DEV))
+        else:
+            st = lpmm.new_state(rows, cols, DEV)
+            if kind == "offset":                    # column maxima off the 16-byte grid: no whole-block tiles
+                st.v_colmax = torch.zeros(cols + 4, device=DEV)[1:cols + 1]
+        descs.append(lpmm.make_desc(w, g, st, rows, cols) if kind == "fp32" else lpmm.make_desc(w, g, st))
+        ws.append(w)
+        gs.append(g)
+        states.append(st)
+    plan = lpmm.new_plan(descs, 1 if bf16 else 0, DEV)
+    lr, step = torch.full((1,), HP.lr, device=DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
+
+    def one():
+        lpmm.lpmm_adamw4_step_multi_capturable(plan, lr, step, HP.beta1, HP.beta2, HP.eps, HP.weight_decay)
+
+    graph = None
+    if capture:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            one()
+    for t in range(1, steps + 1):
+        for tid, ((kind, shape), g) in enumerate(zip(tensors, gs)):
+            x = workloads.grads(81, tid, t, shape[0], int(np.prod(shape[1:])), "outlier_sparse" if tid % 3 == 2 and shape[0] > 1
+                                else "col_lognormal", bf16)
+            g.copy_(to_dev(x.reshape(-1), bf16))
+        step.fill_(t)
+        graph.replay() if capture else one()
+        torch.cuda.synchronize()
+    lpmm.lpmm_adamw4_plan_release(plan)
+    out = []
+    for w, st in zip(ws, states):
+        parts = list(st) if isinstance(st, tuple) else [v for v in vars(st).values() if torch.is_tensor(v)]
+        out.append([w.cpu().numpy()] + [v.cpu().numpy() for v in parts])
+    return out
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("env", [ONE, DEFERRED], ids=["waiting", "deferred"])
+def test_the_oracle_step_by_step(env, bf16):
+    _run_set(_mini_transformer(), "col_lognormal", bf16, steps=3, seed=82, env=env)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("env,capture", [(ONE, False), (DEFERRED, False), (ONE, True)], ids=["waiting", "deferred", "graph"])
+def test_same_bits_as_the_launches_by_phases(monkeypatch, env, capture, bf16):
+    want = _steps(monkeypatch, PHASES, RANK1, bf16)
+    got = _steps(monkeypatch, env, RANK1, bf16, capture=capture)
+    for (kind, shape), a, b in zip(RANK1, want, got):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y, err_msg=f"{kind} {shape}")
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("env,capture", [(ONE, False), (DEFERRED, False), (ONE, True)], ids=["waiting", "deferred", "graph"])
+def test_factorized(monkeypatch, env, capture, bf16):
+    want = _steps(monkeypatch, PHASES, FACTOR, bf16)
+    got = _steps(monkeypatch, env, FACTOR, bf16, capture=capture)
+    for (kind, shape), a, b in zip(FACTOR, want, got):
+        np.testing.assert_allclose(b[0], a[0], rtol=PARAM_RTOL, atol=PARAM_ATOL, err_msg=f"{kind} {shape}")
+        for x, y in zip(a[1:], b[1:]):
+            if x.dtype == np.uint8 or kind != "factor" or x.size not in shape:      # first moment: nothing of it is a sum
+                np.testing.assert_array_equal(x, y, err_msg=f"{kind} {shape}")
+            else:
+                np.testing.assert_allclose(y, x, rtol=STAT_RTOL, atol=0, err_msg=f"{kind} {shape}")
+
+
+def test_statistics_beyond_one_workgroup_keep_the_phases(monkeypatch):
+    """Inner dimensions with more statistics than the one launch has room for: the plan is stepped by phases."""
+    tensors = [("nd", (4, 2400, 2)), ("rank1", (64, 256))]
+    want = _steps(monkeypatch, PHASES, tensors, False)
+    got = _steps(monkeypatch, ONE, tensors, False)
+    for a, b in zip(want, got):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)

@@ -351,7 +351,9 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
  * runs on `stream` while pass 2 of the previous group runs beside it on a second stream that the
  * plan owns (same priority; `stream` waits for it before the call's work counts as complete, so the
  * usual stream ordering holds for the caller).  Plans with a single group, plans of factorized tensors and
- * the one-pass kinds enqueue all their launches on `stream`.  Results are identical to calling the
+ * the one-pass kinds enqueue all their launches on `stream`.  Rank-1 and factorized plans of 2^25 parameters or more, or
+ * with LPMM_KIND_4BIT_ND tensors, enqueue ONE launch there, in which pass 2 of a tensor follows its pass 1 (not with
+ * LPMM_FLAG_DETERMINISTIC).  Results are identical to calling the
  * single-tensor entry points one tensor at a time. */
 
 #define LPMM_KIND_4BIT 0   /* quantized states as in lpmm_adamw4_step */
@@ -458,7 +460,7 @@ int lpmm_adamw4_plan_release(void* plan);
  * = summed duration in milliseconds of the recorded pass-1 launches, ms[1] = of the pass-2 launches,
  * *n_calls = recorded calls.  Multi-tensor steps: ms[0] = summed duration of the recorded launches
  * that carry pass 1 (their pass-2 companions run beside them on the plan's second stream; in a plan of
- * factorized tensors: of the update passes), ms[1] = 0, *n_calls = recorded launches.  (Do not mix the two kinds between one begin and end.)
+ * factorized tensors: of the update passes; in a plan that is stepped in one launch: of that launch), ms[1] = 0, *n_calls = recorded launches.  (Do not mix the two kinds between one begin and end.)
  * ms, n_calls: host.  Not thread-safe: begin, end and every step between them must come from one host thread. */
 int lpmm_profile_begin(int64_t max_calls);
 int lpmm_profile_end(double ms[2], int64_t* n_calls);

@@ -34,7 +34,7 @@ __device__ float d_byte_decode[512];          // entry b: {T_DE[b & 15], T_DE[b 
 __device__ SearchEntry d_search[kBucketsPadded];    // nearest-entry search for the DE map
 
 enum TensorKind : int { kQuantFast = 0, kQuantGeneral = 1, kFp32State = 2, kQuantBlockV = 3, kFactorFast = 4, kFactorGeneral = 5,
-                        kSgdmBlock = 6, kSgdmFp32 = 7, kQuantRagged = 8 };
+                        kSgdmBlock = 6, kSgdmFp32 = 7, kQuantRagged = 8, kFactorRagged = 9 };
 
 struct Tensor4 {
     float* p;               // parameters, fp32 [P]
@@ -2036,10 +2036,10 @@ __device__ __forceinline__ void factor_stats_general_tile(const Tensor4& a, int 
 }
 
 template <bool BF16, bool SAME_LAUNCH = false>
-__device__ __forceinline__ void factor_update_general_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+__device__ __forceinline__ void factor_update_general_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s, int64_t only = -1) {
     const int64_t t = int64_t(wg) * kThreads + threadIdx.x;
     const int64_t block = t >> 4;                       // uniform over the 16 lanes of a block
-    if (block * 128 >= a.P) return;
+    if (block * 128 >= a.P || (only >= 0 && block != only)) return;    // only: this block alone
     const LaneIo io = lane_io(a.P, a.cols, t);
     float w[8], g[8];
     if (io.nv == 8) {

@@ -67,6 +67,22 @@ __global__ __launch_bounds__(kThreads) void factor_update_general(const Tensor4 
 }
 
 template <bool BF16>
+__global__ __launch_bounds__(kThreads) void factor_stats_ragged_kernel(const Tensor4 a) {
+    __shared__ Lds s;
+    const int wg = logical_wg();
+    if (wg < a.n_wg) factor_stats_ragged<BF16>(a, wg, s);
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kThreads) void factor_update_ragged_kernel(const Tensor4 a, const Hyper h) {
+    __shared__ Lds s;
+    __shared__ int s_last;
+    const int wg = logical_wg();
+    if (wg < a.n_wg2) factor_update_ragged<BF16>(a, h, wg, s);
+    factor_publish_if_last(a, h, blockIdx.x, gridDim.x, s_last);
+}
+
+template <bool BF16>
 __global__ __launch_bounds__(kThreads) void sgdm4_kernel(const Tensor4 a, const Hyper h) {
     __shared__ Lds s;
     const int wg = logical_wg();
@@ -383,6 +399,8 @@ __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, 
         const int wg = b_before - sg.wg_begin;
         if (a.kind == kFactorFast) {
             factor_update_tile<BF16>(a, ht, wg, s);
+        } else if (a.kind == kFactorRagged) {
+            factor_update_ragged<BF16>(a, ht, wg, s);
         } else {
             load_tables(s);
             factor_update_general_tile<BF16>(a, ht, wg, s);
@@ -398,6 +416,7 @@ __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, 
             adamw32_tile<BF16>(a.p, a.g, reinterpret_cast<float*>(a.mq), reinterpret_cast<float*>(a.vq), a.P, ht, wg);
         else if (a.kind == kQuantBlockV) b128_work<BF16>(a, ht, wg, s);
         else if (a.kind == kFactorFast) factor_stats_tile<BF16>(a, wg, s);
+        else if (a.kind == kFactorRagged) factor_stats_ragged<BF16>(a, wg, s);
         else factor_stats_general_tile<BF16>(a, wg, a.n_wg, s);
     }
 }

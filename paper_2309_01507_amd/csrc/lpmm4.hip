@@ -607,7 +607,7 @@ int64_t det_partial_floats(int64_t rows, int64_t cols) {
 }
 
 void factor_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes, bool fast,
-                     int tot_slots) {
+                     int tot_slots, int shrink = 0) {
     a->tot_slots = tot_slots;
     a->kind = fast ? kFactorFast : kFactorGeneral;
     if (fast) {
@@ -624,6 +624,19 @@ void factor_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, in
         }
         std::swap(a->n_wg, a->n_wg2);
         a->kind = kFactorFast;
+    } else if (!a->det && ragged_eligible(a->rows, a->cols)) {
+        // The tiles of the rank-1 step, its pass 2's for the statistics.  Those end with an atomic per column here, and
+        // atomics on one address follow each other at about 18 ns, so a tall narrow matrix takes more rows to a tile than
+        // the filling of the chip alone would ask for: rows / rw2 of them against a quarter of rw2 rows, about 0.3 us each,
+        // one after the other in a wave balance at rw2 = sqrt(rows / 4) (2000 x 190 with
+        // fp32 gradients: 16.5 us per step, 29.8 without this, 19.7 on the general tiles).
+        ragged_geometry(a, rw_hint == 0 ? n_cu : 0, shrink);
+        const int64_t rows2 = pass2_rows(*a, true);
+        const int rest = a->n_wg2 - int(a->strips2 * ((rows2 + a->rw2 - 1) / a->rw2));     // parts of the last row
+        while (a->rw2 < 64 && int64_t(a->rw2) * a->rw2 < a->rows / 4 && a->rw2 * a->cols < (int64_t(1) << 28)) a->rw2 *= 2;
+        a->n_wg2 = int(a->strips2 * ((rows2 + a->rw2 - 1) / a->rw2)) + rest;
+        std::swap(a->n_wg, a->n_wg2);
+        a->kind = kFactorRagged;
     } else {
         general_geometry(a, n_cu);          // statistics pass: several chunks per workgroup; update pass: one
         a->kind = kFactorGeneral;
@@ -663,16 +676,19 @@ int factor_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes,
     t.P = rows * cols;
     const bool fast = fast_eligible(cols, v_col);
     factor_geometry(&t, ctx->n_cu, 0, 0, bf16 ? 2 : 4, fast, kMaxTotSlots);
+    const bool ragged = t.kind == kFactorRagged;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls;
     const int64_t call = g_prof.calls;
     if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), s));
 #define LPMM_LAUNCH_FACTOR(B)                                                                                      \
-    if (fast) hipLaunchKernelGGL(factor_stats_fast<B>, dim3(pad8(t.n_wg)), dim3(kThreads), 0, s, t);               \
+    if (ragged) hipLaunchKernelGGL(factor_stats_ragged_kernel<B>, dim3(pad8(t.n_wg)), dim3(kThreads), 0, s, t);    \
+    else if (fast) hipLaunchKernelGGL(factor_stats_fast<B>, dim3(pad8(t.n_wg)), dim3(kThreads), 0, s, t);               \
     else hipLaunchKernelGGL(factor_stats_general<B>, dim3(t.n_wg), dim3(kThreads), 0, s, t);                       \
     LPMM_HIP(hipGetLastError());                                                                                   \
     if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 1), s));                                                     \
-    if (fast) hipLaunchKernelGGL(factor_update_fast<B>, dim3(pad8(t.n_wg2)), dim3(kThreads), 0, s, t, h);          \
+    if (ragged) hipLaunchKernelGGL(factor_update_ragged_kernel<B>, dim3(pad8(t.n_wg2)), dim3(kThreads), 0, s, t, h); \
+    else if (fast) hipLaunchKernelGGL(factor_update_fast<B>, dim3(pad8(t.n_wg2)), dim3(kThreads), 0, s, t, h);          \
     else hipLaunchKernelGGL(factor_update_general<B>, dim3(t.n_wg2), dim3(kThreads), 0, s, t, h);                  \
     LPMM_HIP(hipGetLastError());
     if (bf16) { LPMM_LAUNCH_FACTOR(true) } else { LPMM_LAUNCH_FACTOR(false) }
@@ -785,7 +801,7 @@ void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int
         b128_geometry(t, kCus, 8 >> shrink);
     } else if (desc_kind == LPMM_KIND_4BIT_FACTOR) {
         factor_geometry(t, kCus, 64 >> shrink, rw2, grad_bytes, (t->cols % LPMM_BLOCK) == 0 && aligned_c &&
-                        fast_eligible(t->cols, nullptr), 1);
+                        fast_eligible(t->cols, nullptr), 1, shrink);
     } else if (aligned_c && fast_eligible(t->cols, nullptr)) {
         t->kind = kQuantFast;
         fast_geometry(t, kCus, rw, rw2, grad_bytes, flat);
@@ -812,6 +828,9 @@ bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inne
         const lpmm_tensor_desc& d = descs[i];
         if (d.kind == LPMM_KIND_SGDM_4BIT || d.kind == LPMM_KIND_SGDM_FP32 || (d.flags & LPMM_FLAG_DETERMINISTIC)) return false;
         if (d.rows * d.cols > (int64_t(1) << 37)) return false;
+        // ragged factorized tensors: their update in the same kernel takes 125 registers in place of 74, three or four
+        // waves on a SIMD in place of six
+        if (d.kind == LPMM_KIND_4BIT_FACTOR && !fast_eligible(d.cols, nullptr) && ragged_eligible(d.rows, d.cols)) return false;
         if (d.kind == LPMM_KIND_4BIT_ND) {
             InnerDims dm;
             int64_t ext;
@@ -903,6 +922,7 @@ void build_flow(const lpmm_tensor_desc* descs, int64_t n, const PlanLayout& L, c
         Tensor4& t = flow[i];
         t.flat = 0;
         flow_geometry(&t, descs[i].kind, aligned(descs[i].v_colmax, 16), total, gbytes);
+        if (t.kind == kFactorRagged) return;
         if (flow_kind_second(t.kind)) {
             t.deferred = int(n_def);
             n_def += t.n_wg2;
@@ -1592,7 +1612,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         } else if (d.kind == LPMM_KIND_4BIT_B128) {
             b128_geometry(&t, ctx->n_cu, rounds_s);
         } else if (d.kind == LPMM_KIND_4BIT_FACTOR) {
-            factor_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1);
+            factor_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1, shrink);
         } else if (t.kind == kQuantFast) {
             fast_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, plan_flat && t.P >= kFlatMinElems);
         } else if (t.kind == kQuantRagged) {
@@ -1726,7 +1746,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             for (int64_t i = gr.first; i < gr.second; ++i) {
                 n_a += tens[i].n_wg;
                 const bool has_b = is_rank1(tens[i].kind) ||
-                                   tens[i].kind == kFactorFast || tens[i].kind == kFactorGeneral;
+                                   tens[i].kind == kFactorFast || tens[i].kind == kFactorGeneral ||
+                                   tens[i].kind == kFactorRagged;
                 if (has_b) { n_b += tens[i].n_wg2; two_pass = true; }
             }
             if (n_a >= 2 * int64_t(ctx->n_cu) && (!two_pass || n_b >= 2 * int64_t(ctx->n_cu))) break;

@@ -290,4 +290,224 @@ __device__ __forceinline__ void pass2_ragged(const Tensor4& a, const Hyper& h, i
     else if (ready()) pass2_last_row<BF16, SAME_LAUNCH>(a, h, wg - tiles);
 }
 
+// ---- the factorized step on the same tiles ------------------------------------------------------------------------
+//
+// Memory-bound like the rank-1 form.  (Before, on the general tiles: a float atomic in LDS per element for the column sums,
+// an exact division and four loads of statistics per element for the update.  General / these, us per step: 4096 x 4000
+// bf16 907 / 49, 1024 x 50257 bf16 1747 / 147, 30000 x 1000 fp32 361 / 107, 600 x 147 fp32 15.7 / 13.9.)
+
+// Statistics pass: the row-class walk of pass2_tile (a wave's rows are a multiple of 4 apart, so its lanes keep their columns
+// down the tile).  Columns are counted on through the end of a row: positions cols, cols + 1, cols + 2 are the next row's
+// first ones, whose squares the row's last lane collects for that row.
+template <bool BF16>
+__device__ __forceinline__ void factor_stats_ragged_tile(const Tensor4& a, int wg, Lds& s) {
+    constexpr int kSpan = 264;                                    // positions of a strip: 256, a shift and a lane's 4
+    static_assert(4 * kSpan <= kColSlots && kMaxRw2 < kMaxRowSlots, "column and row sums of a tile are staged in LDS");
+    const int strip = wg % a.strips2, tile = wg / a.strips2;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int lane = threadIdx.x & 63;
+    const int64_t row0 = int64_t(tile) * a.rw2;                   // a multiple of 4
+    const int64_t left = pass2_rows(a, true) - row0;
+    const int n = left < a.rw2 ? int(left) : a.rw2;
+    const int n_stat = row0 + n < a.rows ? n + 1 : n;
+    const uint32_t cols = uint32_t(a.cols);
+    const uint32_t shift = (0u - uint32_t(wave) * cols) & 3u;
+    const uint32_t at = uint32_t(lane) * 4u + shift, col0 = uint32_t(strip) * 256u + at;
+    const bool live = col0 < cols;
+    const Rsrc rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + row0 * a.cols * (BF16 ? 2 : 4),
+                              uint32_t(n_stat) * cols * (BF16 ? 2u : 4u));
+    const int last = n - 1 - (n - 1 - wave) % kWaves;             // the wave's own last row, if it has any (wave < n)
+    auto ld = [&](int il) { return load_grad_regs4<BF16>(rg, live ? (uint32_t(il < last ? il : last) * cols + col0) * 4u : kRagNowhere); };
+    for (int t = threadIdx.x; t < 4 * kSpan; t += kThreads) s.col[t] = 0.0f;
+    for (int t = threadIdx.x; t <= n; t += kThreads) { s.blk_scale[t] = 0.0f; s.blk_vmax[t] = 0.0f; }
+    __syncthreads();
+    float cacc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto one = [&](const GradRegs4<BF16>& r, int il) {
+        float g[4];
+        unpack_grad4<BF16>(r, g);
+        float own = 0.0f, beyond = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float sq = live ? g[e] * g[e] : 0.0f;
+            cacc[e] += sq;
+            own += col0 + e < cols ? sq : 0.0f;
+            beyond += col0 + e < cols ? 0.0f : sq;
+        }
+        own = wave_sum(own);
+        if (lane == 0) s.blk_scale[il] = own;
+        if (live && col0 + 3u >= cols) s.blk_vmax[il + 1] = beyond;        // one lane of the last strip
+    };
+    constexpr int kDepth = 3;                                     // as in factor_stats_tile
+    GradRegs4<BF16> r[kDepth];
+    auto row = [&](int k) { return wave + k * kWaves; };
+    int k = 0;
+    if (wave < n) {
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) r[u] = ld(row(u));
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        if (row(k + kDepth - 1) < n) do {
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u) {
+                one(r[u], row(k + u));
+                __builtin_amdgcn_sched_barrier(0);
+                r[u] = ld(row(k + kDepth + u));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            k += kDepth;
+        } while (row(k + kDepth - 1) < n);
+#pragma unroll
+        for (int u = 0; u < kDepth - 1; ++u)
+            if (row(k + u) < n) one(r[u], row(k + u));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s.col[wave * kSpan + at + e] = cacc[e];
+    __syncthreads();
+    for (int t = threadIdx.x; t < n_stat; t += kThreads) atomic_add_f32(a.r_new + row0 + t, s.blk_scale[t] + s.blk_vmax[t]);
+    for (int t = threadIdx.x; t < kSpan; t += kThreads) {
+        const uint32_t c = uint32_t(strip) * 256u + uint32_t(t);
+        const float sum = (s.col[t] + s.col[kSpan + t]) + (s.col[2 * kSpan + t] + s.col[3 * kSpan + t]);
+        if (sum != 0.0f && c < cols + 3u) atomic_add_f32(a.c_new + (c < cols ? c : c - cols), sum);
+    }
+    float* tot = reinterpret_cast<float*>(a.counter);
+    if (wave == 0) {
+        float part = 0.0f;
+        for (int t = lane; t < n_stat; t += 64) part += s.blk_scale[t] + s.blk_vmax[t];
+        part = wave_sum(part);
+        if (lane == 0) atomic_add_f32(tot + tot_new_word(wg & (a.tot_slots - 1)), part);
+    } else if (wave == 1 && strip == 0) {
+        float part = 0.0f;
+        for (int t = lane; t < n; t += 64) part += a.r[row0 + t];
+        part = wave_sum(part);
+        if (lane == 0) atomic_add_f32(tot + tot_old_word(tile & (a.tot_slots - 1)), part);
+    }
+}
+
+// The part of the last row that the tiles leave out (see pass2_last_row).
+template <bool BF16>
+__device__ __forceinline__ void factor_stats_last_row(const Tensor4& a, int part, Lds& s) {
+    const int64_t first = pass2_last_row_begin(a) + int64_t(part) * kLastRowElems;
+    const int lane = threadIdx.x & 63;
+    float sum = 0.0f;
+    for (int u = 0; u < kLastRowElems / kThreads; ++u) {
+        const int64_t e = first + int64_t(u) * kThreads + threadIdx.x;
+        if (e >= a.P) break;
+        const float g = load_grad1<BF16>(a.g, e), sq = g * g;
+        atomic_add_f32(a.c_new + (e - (a.rows - 1) * a.cols), sq);
+        sum += sq;
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) s.col[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float* tot = reinterpret_cast<float*>(a.counter);
+        const float all = (s.col[0] + s.col[1]) + (s.col[2] + s.col[3]);
+        atomic_add_f32(a.r_new + a.rows - 1, all);
+        atomic_add_f32(tot + tot_new_word(part & (a.tot_slots - 1)), all);
+        if (part == 0) atomic_add_f32(tot + tot_old_word(0), a.r[a.rows - 1]);
+    }
+}
+
+template <bool BF16>
+__device__ __forceinline__ void factor_stats_ragged(const Tensor4& a, int wg, Lds& s) {
+    const int tiles = int((pass2_rows(a, true) + a.rw2 - 1) / a.rw2) * a.strips2;
+    if (wg < tiles) factor_stats_ragged_tile<BF16>(a, wg, s);
+    else factor_stats_last_row<BF16>(a, wg - tiles, s);
+}
+
+// Update pass: the blocks of pass1_ragged_tile; s.cold holds the columns' new statistics by position, s.blk_vmax the rows'
+// over their total.
+template <bool BF16, bool ONE_STRIP>
+__device__ __forceinline__ void factor_update_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    const RagTile t = rag_tile<ONE_STRIP>(a, wg);
+    const TileBase tb = rag_base<BF16>(a, t);
+    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+    auto unit = [&](int q) { return rag_unit<ONE_STRIP>(t, a, grp, q); };
+    auto fetch = [&](const RagUnit& u) { return load_rowf<BF16>(tb, u.off4 == kRagNowhere ? kRagNowhere : u.off4 + 16u * l); };
+    const int n = rag_units<ONE_STRIP>(t, a);
+    RagUnit u0 = unit(0), u1 = unit(1), u2;
+    RowF<BF16> r0 = fetch(u0), r1 = fetch(u1), r2;
+    const float inv_total = factor_inv_total(a, h);
+    for (int k = threadIdx.x; k < t.width + 128; k += kThreads) {
+        const int c = rag_col(t, a.cols, k);
+        s.cold[k] = stat_ema(h, a.c[c], a.c_new[c]);
+    }
+    for (int k = threadIdx.x; k < kRagRowSlots; k += kThreads) {
+        const int64_t i = t.row0 + k;
+        s.blk_vmax[k] = k < t.n_rows && i < a.rows ? stat_ema(h, a.r[i], a.r_new[i]) * inv_total : 0.0f;
+    }
+    if constexpr (ONE_STRIP) {
+        for (int k = threadIdx.x; k < t.n_blocks; k += kThreads) s.blk_scale[k] = tb.ms[k];
+    } else {
+        for (int k = threadIdx.x; k < t.own_rows * kFlatBlocks; k += kThreads) {
+            const int b = ((t.f0 + int(row_offset(k / kFlatBlocks, a.cols, 0u)) + 127) >> 7) + k % kFlatBlocks;
+            if (k % kFlatBlocks < t.per_row && b < t.end) s.blk_scale[k] = tb.ms[b];
+        }
+    }
+    load_tables(s);
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see pass 1)
+    auto none = [] {};
+    auto work = [&](const RowF<BF16>& cur, const RagUnit& u, auto mid) {
+        float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
+        float g[4], ct[4], mt[4], amax = 0.0f;
+        unpack_grad4<BF16>(cur.g, g);
+        const bool ok = u.off4 != kRagNowhere;            // a unit that does not exist: all moments zero
+        const float s_old = ok ? s.blk_scale[u.slot] : 0.0f;
+        const float r_a = ok ? s.blk_vmax[u.il] : 0.0f, r_b = ok ? s.blk_vmax[u.il + 1] : 0.0f;
+        const int p4 = ok ? u.p + 4 * l : 0;
+        lds_load4(&s.cold[p4], ct);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float2 d = s.deq[(uint32_t(cur.mq) >> (8 * k)) & 255u];
+            mt[2 * k] = d.x * s_old;
+            mt[2 * k + 1] = d.y * s_old;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            mt[e] = moment_m(h, mt[e], g[e]);
+            w[e] = param_update(h, w[e], mt[e], (p4 + e < t.lim ? r_a : r_b) * ct[e]);
+            amax = fmaxf(amax, fabsf(mt[e]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        mid();
+        __builtin_amdgcn_sched_barrier(0);
+        const float s_new = group32_allmax(amax);
+        store_row1(tb, ok ? u.off4 + 16u * l : kRagNowhere, w, compress_m4(s.search, mt, s_new));
+        if (l == 0 && ok) s.blk_scale[u.slot] = s_new;
+    };
+    int q = 0;
+    while (q + 2 < n) {                                   // rounds of three units, no exit in the middle
+        work(r0, u0, [&] { u2 = unit(q + 2); r2 = fetch(u2); });
+        work(r1, u1, [&] { u0 = unit(q + 3); r0 = fetch(u0); });
+        work(r2, u2, [&] { u1 = unit(q + 4); r1 = fetch(u1); });
+        q += 3;
+    }
+    if (q < n) {
+        work(r0, u0, none);
+        if (q + 1 < n) work(r1, u1, none);
+    }
+    __syncthreads();
+    if constexpr (ONE_STRIP) {
+        for (int k = threadIdx.x; k < t.n_blocks; k += kThreads) tb.ms[k] = s.blk_scale[k];
+    } else {
+        for (int k = threadIdx.x; k < t.own_rows * kFlatBlocks; k += kThreads) {
+            const int f = t.f0 + int(row_offset(k / kFlatBlocks, a.cols, 0u));
+            const int b = ((f + 127) >> 7) + k % kFlatBlocks;
+            if (b * 128 - f < t.width && b < t.end) tb.ms[b] = s.blk_scale[k];
+        }
+    }
+}
+
+// Workgroups [0, n_wg2) of the update pass; the last one takes the partial block, if any.
+template <bool BF16>
+__device__ __forceinline__ void factor_update_ragged(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    if ((a.P & 127) && wg == a.n_wg2 - 1) {
+        load_tables(s);
+        factor_update_general_tile<BF16>(a, h, a.nb / 16, s, a.nb);
+    } else if (a.strips == 1) {
+        factor_update_ragged_tile<BF16, true>(a, h, wg, s);
+    } else {
+        factor_update_ragged_tile<BF16, false>(a, h, wg, s);
+    }
+}
+
 }  // namespace lpmm

@@ -24,8 +24,9 @@ DEFERRED = {"LPMM_FLOW_MIN": "0", "LPMM_FLOW_SPIN": "0"}
 RANK1 = [("rank1", (300, 512)), ("rank1", (130, 4224)), ("rank1", (37, 200)), ("rank1", (1030, 129)), ("rank1", (40, 96)),
          ("rank1", (1, 5000)), ("rank1", (257, 1023)), ("offset", (70, 1280)), ("nd", (24, 16, 3, 3)), ("nd", (8, 1, 2, 128)),
          ("nd", (5, 3, 1024)), ("b128", (1, 70001)), ("fp32", (1, 3000)), ("rank1", (2050, 640))]
-FACTOR = [("factor", (300, 512)), ("factor", (37, 200)), ("factor", (1, 5000)), ("factor", (1030, 640)), ("fp32", (1, 768)),
-          ("b128", (1, 8192)), ("factor", (257, 1023))]
+FACTOR = [("factor", (300, 512)), ("factor", (37, 100)), ("factor", (1, 6400)), ("factor", (1030, 640)), ("fp32", (1, 768)),
+          ("b128", (1, 8192)), ("factor", (2057, 127))]
+RAGGED_FACTOR = [("factor", (300, 512)), ("factor", (37, 200))]       # ragged factorized matrices: by phases
 
 
 def _steps(monkeypatch, env, tensors, bf16, steps=3, capture=False):
@@ -101,11 +102,12 @@ def test_same_bits_as_the_launches_by_phases(monkeypatch, env, capture, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("env,capture", [(ONE, False), (DEFERRED, False), (ONE, True)], ids=["waiting", "deferred", "graph"])
-def test_factorized(monkeypatch, env, capture, bf16):
-    want = _steps(monkeypatch, PHASES, FACTOR, bf16)
-    got = _steps(monkeypatch, env, FACTOR, bf16, capture=capture)
-    for (kind, shape), a, b in zip(FACTOR, want, got):
+@pytest.mark.parametrize("env,capture,tensors", [(ONE, False, FACTOR), (DEFERRED, False, FACTOR), (ONE, True, FACTOR),
+                                                 (ONE, True, RAGGED_FACTOR)], ids=["waiting", "deferred", "graph", "ragged"])
+def test_factorized(monkeypatch, env, capture, tensors, bf16):
+    want = _steps(monkeypatch, PHASES, tensors, bf16)
+    got = _steps(monkeypatch, env, tensors, bf16, capture=capture)
+    for (kind, shape), a, b in zip(tensors, want, got):
         np.testing.assert_allclose(b[0], a[0], rtol=PARAM_RTOL, atol=PARAM_ATOL, err_msg=f"{kind} {shape}")
         for x, y in zip(a[1:], b[1:]):
             if x.dtype == np.uint8 or kind != "factor" or x.size not in shape:      # first moment: nothing of it is a sum

@@ -85,3 +85,21 @@ def test_same_bits_as_the_general_kernels(monkeypatch, rows, cols, bf16):
     (a, wa), (b, wb) = out
     for x, y in ((a.m_codes, b.m_codes), (a.m_scales, b.m_scales), (a.v_codes, b.v_codes), (a.v_r, b.v_r), (a.v_c, b.v_c), (wa, wb)):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("rows,cols,bf16", [
+    (300, 129, False),       # shortest rows of the path; the tensor's size is a multiple of 4
+    (261, 147, True),        # it is not: the last row apart
+    (1, 129, False),         # nothing but the last row
+    (5, 1023, True),
+    (258, 257, False),       # more rows than a statistics tile; the last strip holds one column
+    (700, 1000, True),
+    (67, 1030, False),       # two strips of the update, five of the statistics
+    (33, 8193, True),
+    (3, 50257, False),
+])
+def test_factorized_step_matches_the_oracle(rows, cols, bf16):
+    from test_gpu_factor import run
+    print(f"[gpu-test] ragged factorized {rows}x{cols} bf16={bf16}", flush=True)
+    assert run(rows, cols, steps=3, bf16=bf16) == 0
+    assert run(rows, cols, steps=2, recipe="outlier_sparse" if rows > 1 else "iid", bf16=bf16) == 0

@@ -288,6 +288,12 @@ def main():
     one_pass = b128 or sgdm
     n_q_tensors = sum(1 for x in tensors if x[0] == "q")
     n_tensors, has_plans = len(tensors), bool(plans)
+    # rank-1 and factorized plans from 2^25 parameters on are stepped in one launch that holds both passes, unless most of
+    # them are one tensor's (include/lpmm4.h)
+    share = max(x[1].numel for x in tensors) / wl.n_params
+    one_launch = has_plans and not one_pass and not args.deterministic and wl.n_params >= 1 << 25 and \
+        share <= (0.25 if factor else 0.75) and \
+        os.environ.get("LPMM_FLOW") != "0" and not {"LPMM_MULTI_STREAMS", "LPMM_PHASE_MPARAMS"} & set(os.environ)
     lpmm.lpmm_profile_begin(max(n_q_tensors, 64) * args.steps)
     for _ in range(args.steps):
         t += 1
@@ -302,26 +308,31 @@ def main():
         # tensors); pass 2 of the previous group runs beside them on the plan's second stream
         # (a factorized plan's recorded launches are its update passes; its launches run one after the other on the
         # caller's stream, and the fp32-state tensors ride with the statistics passes)
-        bytes_per_launch = (bp1 * n_quant + (0.0 if factor else small_bytes)) * args.steps / launches
+        # (one_launch: the recorded launch is the whole step)
+        bytes_per_launch = ((bp1 + bp2) * n_quant + small_bytes if one_launch else
+                            (bp1 * n_quant + (0.0 if factor else small_bytes)) * args.steps / launches)
         avg_ms = p1_ms / launches
         achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9
         roofline = {
             "bound": "hbm", "kernel": ("sgdm_phase_kernel (the whole step)" if sgdm else
                                        "phase_kernel<roles=3> (the whole block-wise step)" if b128 else
+                                       "flow_kernel (both passes)" if one_launch else
                                        "factor_phase_kernel<roles=2> (update pass)" if factor else
                                        "phase_kernel<roles=1> (pass 1)"),
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
-            "bytes_per_param": bp1, "launches": n_calls, "avg_launch_ms": round(avg_ms, 5),
+            "bytes_per_param": bp1 + bp2 if one_launch else bp1, "launches": n_calls, "avg_launch_ms": round(avg_ms, 5),
             "bytes_per_launch": round(bytes_per_launch),
             "traffic_source": None,
             "note": ("one pass: this kernel is the whole step" if one_pass else
+                     "one launch: this kernel is the whole step, pass 2 (%.1f B/param) of a tensor right behind its pass 1; its "
+                     "gradient reads are counted although part of them comes from the memory-side cache" % bp2 if one_launch else
                      "the statistics pass (%.1f B/param) is a launch of its own before it on the same stream; "
                      "whole-step figures are in config" % bp2 if factor else
                      "pass 2 of the neighbouring tensor group (%.1f B/param) runs concurrently and shares "
                      "the bandwidth; whole-step figures are in config" % bp2),
         }
-        if not one_pass and not factor and not args.no_secondary:
+        if not one_pass and not factor and not one_launch and not args.no_secondary:
             # The same steps once more with every launch on the caller's stream, one after the other (plans built
             # under LPMM_MULTI_STREAMS=0): the dominant kernel's rate when it has the chip to itself.  The step as a
             # whole is slower that way, which is why the timed region above overlaps the passes.
@@ -352,7 +363,7 @@ def main():
                                              "the other: this kernel with the chip to itself (events included in the step time)"}
         # HBM bytes per launch measured offline with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (see profiles/)
         tpath = os.path.join(ROOT, "profiles", "traffic_phase_kernel_%s%s.json" % (args.config, "_sgdm" if sgdm else "_b128" if b128 else "_factor" if factor else ""))
-        if os.path.exists(tpath):
+        if os.path.exists(tpath) and not one_launch:
             tr = json.load(open(tpath))
             if tr.get("launches_per_step") == n_calls // max(args.steps, 1):
                 roofline["traffic"] = tr["hbm_bytes_per_launch"]
@@ -443,7 +454,7 @@ def main():
     floor_bpp = 8.0 + (2.0 if bf16 else 4.0) + (1.0 if factor or sgdm else 2.0) + (16.0 if b128 else 8.0) / 128.0
     floor_gbps = (floor_bpp * n_quant + small_bytes) / (elapsed / args.steps) / 1e9
     if has_plans:
-        kernels_per_step = (n_calls // max(args.steps, 1)) * (1 if one_pass else 2)     # as many A as B launches
+        kernels_per_step = (n_calls // max(args.steps, 1)) * (1 if one_pass or one_launch else 2)     # as many A as B launches
     else:
         kernels_per_step = n_q_tensors * (1 if one_pass else 2) + (n_tensors - n_q_tensors)
     out = {
@@ -459,6 +470,7 @@ def main():
                    else "rank-1/Linear, two passes",
                    "grad_recipe": recipe,
                    "launch": (("multi-tensor plan, %d launches per step" if one_pass else
+                               "multi-tensor plan, %d launch per step with both passes in it" if one_launch else
                                "multi-tensor plan, %d update launches per step, each behind its statistics launch "
                                "on the caller's stream" if factor else
                                "multi-tensor plan, %d pass-1 launches per step on the caller's stream, "

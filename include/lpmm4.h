@@ -353,7 +353,7 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
  * usual stream ordering holds for the caller).  Plans with a single group, plans of factorized tensors and
  * the one-pass kinds enqueue all their launches on `stream`.  Rank-1 and factorized plans of 2^25 parameters or more, or
  * with LPMM_KIND_4BIT_ND tensors, enqueue ONE launch there, in which pass 2 of a tensor follows its pass 1 (not with
- * LPMM_FLAG_DETERMINISTIC).  Results are identical to calling the
+ * LPMM_FLAG_DETERMINISTIC, nor where one tensor is most of the set).  Results are identical to calling the
  * single-tensor entry points one tensor at a time. */
 
 #define LPMM_KIND_4BIT 0   /* quantized states as in lpmm_adamw4_step */

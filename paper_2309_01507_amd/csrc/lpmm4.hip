@@ -820,10 +820,14 @@ bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast |
 // launch: 9.0 M parameters 38 / 38, 16.7 M 64 / 68, factorized 50 / 54; 56 M 156 / 152, 109 M 358 / 310, 143 M 461 / 408,
 // 294 M 1103 / 956, 501 M 1528 / 1352).  With convolutions, which take four dependent launches, one launch is faster
 // there, too (7.4 M parameters: 60 / 56).
+// The largest tensor's second pass finds little to run beside if it is most of the set: rank-1 up to three quarters of it
+// (share of the largest, phases / one launch: 0.58 231 / 218, 0.74 190 / 175, 0.85 165 / 167, one tensor alone 416 / 469),
+// factorized, whose second pass is the heavy one, up to a quarter (0.14 790 / 731, 0.40 294 / 298, 0.58 183 / 192, 0.85
+// 164 / 209).
 bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim) {
     if (env_int("LPMM_FLOW", 1) == 0 || std::getenv("LPMM_MULTI_STREAMS") || std::getenv("LPMM_PHASE_MPARAMS")) return false;
-    bool second = false, nd = false;
-    int64_t total = 0;
+    bool second = false, nd = false, factor = false;
+    int64_t total = 0, largest = 0;
     for (int64_t i = 0; i < n; ++i) {
         const lpmm_tensor_desc& d = descs[i];
         if (d.kind == LPMM_KIND_SGDM_4BIT || d.kind == LPMM_KIND_SGDM_FP32 || (d.flags & LPMM_FLAG_DETERMINISTIC)) return false;
@@ -839,9 +843,13 @@ bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inne
             nd = true;
         }
         total += d.rows * d.cols;
+        largest = std::max(largest, d.rows * d.cols);
+        factor = factor || d.kind == LPMM_KIND_4BIT_FACTOR;
         second = second || d.kind == LPMM_KIND_4BIT || d.kind == LPMM_KIND_4BIT_ND || d.kind == LPMM_KIND_4BIT_FACTOR;
     }
-    return second && (nd || total >= env_int("LPMM_FLOW_MIN", int(kFlowMinParams)));
+    if (!second || nd) return second;
+    const int64_t least = env_int("LPMM_FLOW_MIN", int(kFlowMinParams));
+    return total >= least && (least == 0 || (factor ? largest <= total / 4 : largest <= total / 4 * 3));
 }
 
 bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim,

@@ -217,6 +217,7 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const FlowArgs f, const 
                 __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
             }
             if (!last_to_arrive(a, unsigned(wg), unsigned(a.n_wg2), s_flag)) return;
+            __syncthreads();                              // every wave has read the flag before it is written again
             if (threadIdx.x == 0) s_flag = atomicAdd(flow_word(a, kFlowFinal), 1u) == 1u;
             __syncthreads();
             if (!s_flag) return;

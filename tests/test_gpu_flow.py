@@ -1,8 +1,8 @@
 """Plans whose step is one launch with both passes of every tensor in it: the same sets through the launches by phases
 (LPMM_FLOW=0) and through the one launch (LPMM_FLOW_MIN=0: small sets, too), with the tiles of the second pass waiting for
-the first one, and with every tile that does not find it complete deferred to the tensor's last workgroup
-(LPMM_FLOW_SPIN=0).  The rank-1 results are the same bits on every route; the factorized statistics are sums in another
-order (tolerance: see test_gpu_factor)."""
+the first one, and with every tile of it deferred to the tensor's last workgroup (LPMM_FLOW_SPIN=-1: no poll at all).
+The rank-1 results are the same bits on every route; the factorized statistics are sums in another order (tolerance: see
+test_gpu_factor)."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 HP = oracle.Hyper()
 PHASES = {"LPMM_FLOW": "0"}
 ONE = {"LPMM_FLOW_MIN": "0"}
-DEFERRED = {"LPMM_FLOW_MIN": "0", "LPMM_FLOW_SPIN": "0"}
+DEFERRED = {"LPMM_FLOW_MIN": "0", "LPMM_FLOW_SPIN": "-1"}
 
 # every kind of tile: whole blocks, rows that are no multiple of 128, narrow ones, one workgroup and many, a wide one
 RANK1 = [("rank1", (300, 512)), ("rank1", (130, 4224)), ("rank1", (37, 200)), ("rank1", (1030, 129)), ("rank1", (40, 96)),

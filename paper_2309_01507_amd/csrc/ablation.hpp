@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs
     abl_load_map(s_map, m);
 #pragma unroll
     for (int u = 0; u < kCvtUnits; ++u)
-        sc[u] = group32_allmax(fmaxf(fmaxf(fabsf(x[u][0]), fabsf(x[u][1])), fmaxf(fabsf(x[u][2]), fabsf(x[u][3]))));
+        sc[u] = group32_allmax(cvt_absmax4(x[u]));
     if constexpr (BLOCK == 2048) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) {

@@ -73,6 +73,12 @@ __device__ __forceinline__ void cvt_store_codes(uint32_t* q, int64_t base, int64
     }
 }
 
+// Largest magnitude of a lane's 4 elements, from 0 on: a NaN raises nothing, also where all four are NaN, so that it costs
+// its block its own code and not the scale.
+__device__ __forceinline__ float cvt_absmax4(const float x[4]) {
+    return fmaxf(fmaxf(fmaxf(fmaxf(0.0f, fabsf(x[0])), fabsf(x[1])), fabsf(x[2])), fabsf(x[3]));
+}
+
 // Row and column of a workgroup's first element; rows and columns of its other elements follow by 32-bit arithmetic
 // (cols <= 2^31, and a workgroup spans kCvtElems elements).
 struct CvtOrigin {
@@ -147,7 +153,7 @@ __global__ __launch_bounds__(kThreads) void quant_m_kernel(const QuantArgs q) {
 #pragma unroll
     for (int u = 0; u < kCvtUnits; ++u) {
         const int64_t base = first + u * kCvtUnitElems;
-        const float sc = group32_allmax(fmaxf(fmaxf(fabsf(x[u][0]), fabsf(x[u][1])), fmaxf(fabsf(x[u][2]), fabsf(x[u][3]))));
+        const float sc = group32_allmax(cvt_absmax4(x[u]));
         cvt_store_codes(q.q_out, base, q.P, compress_m4(s_search, x[u], sc));
         if ((threadIdx.x & 31) == 0 && base < q.P) q.sa[base >> 7] = sc;
     }
@@ -227,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void quant_vb_kernel(const QuantArgs q) {
 #pragma unroll
     for (int u = 0; u < kCvtUnits; ++u) {
         const int64_t base = first + u * kCvtUnitElems;
-        const float sc = group32_allmax(fmaxf(fmaxf(fabsf(x[u][0]), fabsf(x[u][1])), fmaxf(fabsf(x[u][2]), fabsf(x[u][3]))));
+        const float sc = group32_allmax(cvt_absmax4(x[u]));
         const float s[4] = {sc, sc, sc, sc};
         cvt_store_codes(q.q_out, base, q.P, linear_codes4(x[u], s));
         if ((threadIdx.x & 31) == 0 && base < q.P) q.sa[base >> 7] = sc;

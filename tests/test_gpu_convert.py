@@ -1,5 +1,6 @@
 """Stand-alone compress / decompress at the edges of their tiles: 4 elements per lane, 4096 per workgroup, strips of 64 to
-1024 columns and up to 512 rows for the maxima; arrays at 4-byte alignment; nothing written behind a buffer's end."""
+1024 columns and up to 512 rows for the maxima; arrays at 4-byte alignment; nothing written behind a buffer's end; a NaN
+costs no other element its code."""
 import numpy as np
 import pytest
 import torch
@@ -72,3 +73,40 @@ def test_compress_and_decompress_match_the_oracle(rows, cols):
             else:
                 dec = (oracle.dequant_m if which == 0 else oracle.dequant_v_block)(w[0], w[1], P)
             np.testing.assert_array_equal(out.cpu().numpy(), dec)
+
+
+@pytest.mark.parametrize("what", ["state", "b128/de", "b2048/de", "b128/de signed", "b2048/de0 stochastic"])
+def test_nan_raises_no_block_scale(what):
+    """NaNs in a block, a whole lane's 4 elements among them: scales and all other codes as with zeros in their place.
+    (The block-wise second moment and the ablation quantizers: they search no table by the value's bits.)"""
+    lpmm.ensure_init(4096)
+    rows, cols = 9, 1000
+    P = rows * cols
+    rng = np.random.default_rng(17)
+    x = (rng.standard_normal((rows, cols)) * np.exp(rng.standard_normal((rows, cols)))).astype(np.float32)
+    if "signed" not in what:
+        x = np.abs(x)
+    bad = np.zeros(P, bool)
+    for lo, n in ((0, 4), (132, 4), (257, 1), (700, 12), (2048, 8), (4099, 5), (P - 4, 4)):
+        bad[lo:lo + n] = True
+    bad = bad.reshape(rows, cols)
+    clean = np.where(bad, np.float32(0.0), x)
+    dirty = torch.from_numpy(np.where(bad, np.float32("nan"), x)).to(DEV).reshape(-1)
+    codes = torch.full(((P + 1) // 2,), 0xEE, dtype=torch.uint8, device=DEV)
+    if what == "state":
+        want_codes, want_scales = oracle.quant_v_block(clean)
+        sa = torch.full((want_scales.size,), -1.0, device=DEV)
+        lpmm.lpmm_quant_state(2, dirty, rows, cols, codes, sa, None)
+    else:
+        norm, map_name = what.split()[0].split("/")
+        signed, stochastic = "signed" in what, "stochastic" in what
+        want_codes, want_scales, _ = oracle.quant_ablation(clean, norm, map_name, signed, stochastic, 5)
+        sa = torch.full((want_scales.size,), -1.0, device=DEV)
+        lpmm.lpmm_quant_ablation(lpmm.NORM_B128 if norm == "b128" else lpmm.NORM_B2048,
+                                 lpmm.MAP_DE if map_name == "de" else lpmm.MAP_DE0, signed, int(stochastic), 5, dirty, rows,
+                                 cols, codes, sa, None)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(sa.cpu().numpy(), want_scales)
+    got, want = (oracle.unpack_codes(c, P) for c in (codes.cpu().numpy(), want_codes))
+    np.testing.assert_array_equal(got[~bad.reshape(-1)], want[~bad.reshape(-1)])
+    assert (got[bad.reshape(-1)] == 0).all()

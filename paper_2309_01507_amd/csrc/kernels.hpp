@@ -738,6 +738,10 @@ constexpr int kTicketStride = 32;                                  // in 32-bit 
 constexpr int kMaxTotSlots = 8;                                    // lines behind the ticket counters, for the
                                                                    // factorized step's two float sums
 constexpr int kCounterWords = (1 + kTicketLanes + kMaxTotSlots) * kTicketStride;  // per tensor
+// first-level counters that `participants` workgroups use = what the top counter ends at
+__device__ __forceinline__ unsigned int lanes_used(unsigned int participants) {
+    return participants < kTicketLanes ? participants : unsigned(kTicketLanes);
+}
 
 // A word of the workspace (the new maxima or sums) as the second pass reads it.  SAME_LAUNCH: the first pass of the
 // tensor ran in the same launch, on other XCDs, so the load has to see what their atomics left (agent scope: it does not
@@ -768,8 +772,9 @@ __device__ __forceinline__ void move_and_clear(float* dst, float* src, int64_t n
     }
 }
 
-// true in every thread of the one workgroup that arrives last
-__device__ __forceinline__ bool last_to_arrive(const Tensor4& a, unsigned int me, unsigned int participants,
+// true in every thread of the one workgroup that arrives last; `counter`: the top counter, the first-level ones on the
+// following lines
+__device__ __forceinline__ bool last_to_arrive(unsigned int* counter, unsigned int me, unsigned int participants,
                                                int& s_last) {
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -779,10 +784,10 @@ __device__ __forceinline__ bool last_to_arrive(const Tensor4& a, unsigned int me
         const unsigned int lane = me % kTicketLanes;
         const unsigned int in_lane = participants / kTicketLanes + (lane < participants % kTicketLanes ? 1u : 0u);
         int last = 0;
-        if (atomicAdd(a.counter + (1 + lane) * kTicketStride, 1u) == in_lane - 1) {
-            a.counter[(1 + lane) * kTicketStride] = 0u;      // this lane is complete: reset it
-            const unsigned int lanes_used = participants < kTicketLanes ? participants : kTicketLanes;
-            last = atomicAdd(a.counter, 1u) == lanes_used - 1;
+        if (atomicAdd(counter + (1 + lane) * kTicketStride, 1u) == in_lane - 1) {
+            // this lane is complete: reset it (past the L2: its line holds words that other workgroups still count on)
+            __hip_atomic_store(counter + (1 + lane) * kTicketStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = atomicAdd(counter, 1u) == lanes_used(participants) - 1;
         }
         s_last = last;
     }
@@ -792,7 +797,7 @@ __device__ __forceinline__ bool last_to_arrive(const Tensor4& a, unsigned int me
 
 __device__ __forceinline__ void publish_if_last(const Tensor4& a, unsigned int me, unsigned int participants,
                                                 int& s_last) {
-    if (!last_to_arrive(a, me, participants, s_last)) return;
+    if (!last_to_arrive(a.counter, me, participants, s_last)) return;
     move_and_clear(a.r, a.r_new, a.rows);
     move_and_clear(a.c, a.c_new, a.cols + a.c_extra);
     if (threadIdx.x == 0) *a.counter = 0u;
@@ -1847,7 +1852,7 @@ __device__ __forceinline__ void ema_and_clear(const Hyper& h, float* stat, float
 // every other workgroup has read the old statistics and the sums before it took its ticket.
 __device__ __forceinline__ void factor_publish_if_last(const Tensor4& a, const Hyper& h, unsigned int me,
                                                        unsigned int participants, int& s_last) {
-    if (!last_to_arrive(a, me, participants, s_last)) return;
+    if (!last_to_arrive(a.counter, me, participants, s_last)) return;
     ema_and_clear(h, a.r, a.r_new, a.rows);
     ema_and_clear(h, a.c, a.c_new, a.cols);
     if (threadIdx.x == 0) *a.counter = 0u;

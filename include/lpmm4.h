@@ -351,9 +351,11 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
  * runs on `stream` while pass 2 of the previous group runs beside it on a second stream that the
  * plan owns (same priority; `stream` waits for it before the call's work counts as complete, so the
  * usual stream ordering holds for the caller).  Plans with a single group, plans of factorized tensors and
- * the one-pass kinds enqueue all their launches on `stream`.  Rank-1 and factorized plans of 2^25 parameters or more, or
- * with LPMM_KIND_4BIT_ND tensors, enqueue ONE launch there, in which pass 2 of a tensor follows its pass 1 (not with
- * LPMM_FLAG_DETERMINISTIC, nor where one tensor is most of the set).  Results are identical to calling the
+ * the one-pass kinds enqueue all their launches on `stream`.  Rank-1 and factorized plans for which it is the faster way
+ * enqueue ONE launch there, in which pass 2 of a tensor follows its pass 1: sets of 2^25 parameters or more, unless most
+ * of them are in one tensor (rank-1: more than 3/4, factorized: 1/4), in two to eight equal ones, or in rows shorter than
+ * 128; and sets with LPMM_KIND_4BIT_ND tensors, unless that is one large tensor alone.  (Not with
+ * LPMM_FLAG_DETERMINISTIC.)  Results are identical to calling the
  * single-tensor entry points one tensor at a time. */
 
 #define LPMM_KIND_4BIT 0   /* quantized states as in lpmm_adamw4_step */

@@ -814,24 +814,38 @@ void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int
 }
 bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast || kind == kFactorGeneral; }
 
-// Whether a list of tensors is stepped in one launch: some tensor has two passes, no sums in a fixed order, and the
-// statistics of tensors with more than two dimensions are few enough for one workgroup.  Below 2^25 parameters the launches
-// by phases are faster: there is little in flight to hide a tensor's wait between the passes behind (us, phases / one
-// launch: 9.0 M parameters 38 / 38, 16.7 M 64 / 68, factorized 50 / 54; 56 M 156 / 152, 109 M 358 / 310, 143 M 461 / 408,
-// 294 M 1103 / 956, 501 M 1528 / 1352).  With convolutions, which take four dependent launches, one launch is faster
-// there, too (7.4 M parameters: 60 / 56).
-// The largest tensor's second pass finds little to run beside if it is most of the set: rank-1 up to three quarters of it
-// (share of the largest, phases / one launch: 0.58 231 / 218, 0.74 190 / 175, 0.85 165 / 167, one tensor alone 416 / 469),
-// factorized, whose second pass is the heavy one, up to a quarter (0.14 790 / 731, 0.40 294 / 298, 0.58 183 / 192, 0.85
-// 164 / 209).
+// Whether a list of tensors is stepped in one launch.  It can be where some tensor has two passes, no sums are wanted in a
+// fixed order, and the statistics of tensors with more than two dimensions are few enough for one workgroup.  It is where
+// that is faster (us, phases / one launch; where two pairs are given, fp32 and bf16 gradients):
+// - Sets of 2^25 parameters or more: 56 M parameters 156 / 152, 109 M 358 / 303, 143 M 461 / 408, 294 M 1103 / 956.  Below,
+//   there is little in flight to hide a tensor's wait between the passes behind: 9.0 M 38 / 38, 16.7 M 64 / 68, factorized
+//   50 / 54.
+// - Not sets of which one tensor is most, whose second pass finds little to run beside: rank-1 up to three quarters,
+//   factorized up to a quarter.  Alone, one launch is the slower way (8192 x 4096 106 / 129, 91 / 109; 50257 x 1024 171 / 173,
+//   144 / 149); beside other tensors it is by now the faster one on both sides of these lines (rank-1, 99 M, 0.75 of it in
+//   one tensor 326 / 303, 259 / 243; 0.87 323 / 307, 259 / 251; factorized, 106 M, 0.28 296 / 277, 229 / 224), but the lines
+//   were drawn when the waiting workgroups slowed the counting ones, and no call has been moved across them since.
+// - Not sets of nothing but two to eight matrices of about one size, up to 2^25 parameters each: 2 of 4096 x 4096 105 / 128,
+//   90 / 110; 4 of them 197 / 224, 164 / 187; 8 398 / 412, 313 / 341; 12 604 / 596, 482 / 493; 4 of 8192 x 8192 817 / 768,
+//   654 / 623.  Launches by phases lose time to unequal tiles, and these have none.
+// - Not sets of which the general tiles (rows shorter than 128) are a large part: in one kernel with the others they have
+//   fewer waves in flight.  Rank-1 up to two fifths of the parameters (3000 x 100: 0.3 635 / 469, 506 / 436; 0.4 676 / 518,
+//   551 / 499; 0.5 567 / 592, 516 / 580; all 762 / 885, 735 / 900), factorized up to half (adapters 64 x 4096 and 4096 x 64:
+//   406 / 354, 394 / 337; all narrow 1006 / 1140, 1007 / 1138).
+// - Sets with tensors of more than two dimensions, which by phases take four dependent launches, also below 2^25 parameters
+//   (7.4 M 60 / 56; 8 of 128 x 128 x 3 x 3 34 / 24; 2048 x 4096 and one of 64 x 64 x 3 x 3 46 / 42), unless it is one large tensor
+//   alone (1024 x 1024 x 3 x 3 67 / 73; 640 x 640 x 3 x 3 44 / 44).  From 2^25 on the lines above hold for them, too, where such
+//   tensors are few (two of 4096 x 4096 and one of 64 x 64 x 3 x 3 117 / 124, 102 / 110; with one of 512 x 512 x 3 x 3, a
+//   fifteenth of the parameters, 130 / 128, 113 / 113; with four 162 / 146, 137 / 127).
 bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim) {
     if (env_int("LPMM_FLOW", 1) == 0 || std::getenv("LPMM_MULTI_STREAMS") || std::getenv("LPMM_PHASE_MPARAMS")) return false;
-    bool second = false, nd = false, factor = false;
-    int64_t total = 0, largest = 0;
+    bool factor = false;
+    int64_t total = 0, largest = 0, n_second = 0, general = 0, nd = 0;
     for (int64_t i = 0; i < n; ++i) {
         const lpmm_tensor_desc& d = descs[i];
+        const int64_t P = d.rows * d.cols;
         if (d.kind == LPMM_KIND_SGDM_4BIT || d.kind == LPMM_KIND_SGDM_FP32 || (d.flags & LPMM_FLAG_DETERMINISTIC)) return false;
-        if (d.rows * d.cols > (int64_t(1) << 37)) return false;
+        if (P > (int64_t(1) << 37)) return false;
         // ragged factorized tensors: their update in the same kernel takes 125 registers in place of 74, three or four
         // waves on a SIMD in place of six
         if (d.kind == LPMM_KIND_4BIT_FACTOR && !fast_eligible(d.cols, nullptr) && ragged_eligible(d.rows, d.cols)) return false;
@@ -840,16 +854,28 @@ bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inne
             int64_t ext;
             if (!plan_inner_dims(d, i, inner_dims, inner_ndim, &dm, &ext)) return false;
             if (d.cols > kFlowNdCols || ext > kFlowNdStats) return false;
-            nd = true;
+            nd += P;
         }
-        total += d.rows * d.cols;
-        largest = std::max(largest, d.rows * d.cols);
-        factor = factor || d.kind == LPMM_KIND_4BIT_FACTOR;
-        second = second || d.kind == LPMM_KIND_4BIT || d.kind == LPMM_KIND_4BIT_ND || d.kind == LPMM_KIND_4BIT_FACTOR;
+        total += P;
+        largest = std::max(largest, P);
+        if (d.kind == LPMM_KIND_4BIT || d.kind == LPMM_KIND_4BIT_ND || d.kind == LPMM_KIND_4BIT_FACTOR) {
+            ++n_second;
+            factor = factor || d.kind == LPMM_KIND_4BIT_FACTOR;
+            if (!fast_eligible(d.cols, nullptr) && !ragged_eligible(d.rows, d.cols)) general += P;
+        }
     }
-    if (!second || nd) return second;
+    if (n_second == 0) return false;
     const int64_t least = env_int("LPMM_FLOW_MIN", int(kFlowMinParams));
-    return total >= least && (least == 0 || (factor ? largest <= total / 4 : largest <= total / 4 * 3));
+    if (least == 0) return true;
+    if (factor ? general > total / 2 : general > total / 5 * 2) return false;
+    if (nd > 0 && (total < least || nd >= total / 32)) return n_second > 1 || total <= (int64_t(1) << 22);
+    if (total < least || largest > (factor ? total / 4 : total / 4 * 3)) return false;
+    int64_t n_large = 0, large = 0;                  // tensors of about the largest one's size
+    for (int64_t i = 0; i < n; ++i) {
+        const int64_t P = descs[i].rows * descs[i].cols;
+        if (P >= largest / 2) { ++n_large; large += P; }
+    }
+    return factor || n_large > 8 || large < total / 16 * 15 || largest > (int64_t(1) << 25);
 }
 
 bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim,

@@ -239,3 +239,60 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode == 2
     assert "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def _plan_set(tensors):
+    """Descriptors of a set of (kind, shape), for calls that read shapes and kinds only."""
+    buf = ctypes.create_string_buffer(4096 + 256)
+    p = (ctypes.addressof(buf) + 255) // 256 * 256
+    out = []
+    for kind, shape in tensors:
+        d = lpmm.TensorDesc(p, p, p, p, p, p, p, shape[0], int(np.prod(shape[1:])), kind, 0)
+        if kind == lpmm.KIND_4BIT_ND:
+            d.inner = tuple(shape[1:])
+        out.append(d)
+    return out
+
+
+M, ND, FAC = lpmm.KIND_4BIT, lpmm.KIND_4BIT_ND, lpmm.KIND_4BIT_FACTOR
+_BLOCK = [(1024, 3072), (1024, 1024), (1024, 4096), (4096, 1024)]
+_BERT = [(M, (30522, 768))] + [(M, s) for s in ((768, 2304), (768, 768), (768, 3072), (3072, 768))] * 12
+_CONV = (ND, (64, 64, 3, 3))
+
+
+@pytest.mark.parametrize("name,tensors,one", [
+    ("transformer", _BERT, True),
+    ("transformer, factorized", [(FAC, s) for s in _BLOCK] * 8, True),
+    ("small transformer", [(M, s) for s in _BLOCK] * 2, False),
+    ("one matrix is most of it", [(M, (32000, 4096))] + [(M, s) for s in _BLOCK], False),
+    ("embedding of two thirds", [(M, (40000, 1024))] + [(M, s) for s in _BLOCK] * 2, True),
+    ("factorized, one matrix a third", [(FAC, (50257, 1024))] + [(FAC, s) for s in _BLOCK] * 8, False),
+    ("two large matrices", [(M, (4096, 4096))] * 2, False),
+    ("eight large matrices", [(M, (4096, 4096))] * 8, False),
+    ("nine large matrices", [(M, (4096, 4096))] * 9, True),
+    ("four very large matrices", [(M, (8192, 8192))] * 4, True),
+    ("narrow matrices", [(M, (30000, 96))] * 16, False),
+    ("some narrow matrices", [(M, (30000, 96))] * 8 + [(M, s) for s in _BLOCK] * 4, True),
+    ("adapters", [(M, (64, 4096)), (M, (4096, 64))] * 128, False),
+    ("adapters, factorized", [(FAC, (64, 4096)), (FAC, (4096, 64))] * 128, True),
+    ("narrow matrices, factorized", [(FAC, (30000, 96))] * 16, False),
+    ("convolutions", [(ND, (128, 128, 3, 3))] * 8, True),
+    ("one small convolution", [_CONV], True),
+    ("one large convolution", [(ND, (1024, 1024, 3, 3))], False),
+    ("small matrices and a convolution", [_CONV, (M, (512, 512))], True),
+    ("one matrix and a convolution", [_CONV, (M, (32000, 4096))], False),
+    ("two large matrices and a convolution", [_CONV] + [(M, (4096, 4096))] * 2, False),
+    ("two large matrices and convolutions", [(ND, (512, 512, 3, 3))] * 4 + [(M, (4096, 4096))] * 2, True),
+    ("transformer and a convolution", [(ND, (768, 3, 16, 16))] + _BERT, True),
+    ("narrow matrices and a convolution", [_CONV] + [(M, (30000, 96))] * 16, False),
+    ("more columns than one workgroup turns into statistics", [(ND, (64, 32768, 2))] * 16, False),
+])
+def test_which_plans_are_stepped_in_one_launch(monkeypatch, name, tensors, one):
+    """The rule on sizes and kinds, seen from the plan's memory: the work list of the one launch is part of it."""
+    for k in ("LPMM_FLOW_MIN", "LPMM_MULTI_STREAMS", "LPMM_PHASE_MPARAMS", "LPMM_FORCE_GENERAL"):
+        monkeypatch.delenv(k, raising=False)
+    descs = _plan_set(tensors)
+    monkeypatch.setenv("LPMM_FLOW", "0")
+    phases = lpmm.lpmm_adamw4_plan_bytes(descs)
+    monkeypatch.delenv("LPMM_FLOW")
+    assert phases > 0 and (lpmm.lpmm_adamw4_plan_bytes(descs) > phases) == one

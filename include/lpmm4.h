@@ -453,6 +453,10 @@ int lpmm_sgdm4_step_multi_capturable(void* plan, const float* lr, float momentum
  * synchronize first if the plan's device memory is going to be reused. */
 int lpmm_adamw4_plan_release(void* plan);
 
+/* Kernels that one step of the plan enqueues (host call; the capturable form enqueues one more in front), or LPMM_EINVAL
+ * if `plan` is not a plan.  1 for a plan that holds tensors with two passes: it is stepped in one launch. */
+int lpmm_adamw4_plan_launches(const void* plan);
+
 /* Per-kernel timing for benchmarks, with HIP events recorded on each call's own stream.
  * lpmm_profile_begin(max_calls): from now on every lpmm_adamw4_step / _step_bf16g call in this process
  * records an event before pass 1, between the two passes and after pass 2, and every

@@ -10,7 +10,7 @@ from .binding import (  # noqa: F401
     ablation_scale_sizes, NORM_B128, NORM_B2048, NORM_RANK1, MAP_DE, MAP_DE0, MAP_LINEAR, ROUND_NEAREST, ROUND_STOCHASTIC,
     lpmm_adamw32_step, lpmm_dequant_state, lpmm_quant_state, ensure_init, new_state,
     lpmm_profile_begin, lpmm_profile_end, TensorDesc, make_desc, new_plan, KIND_4BIT, KIND_FP32,
-    lpmm_adamw4_plan_bytes, lpmm_adamw4_plan_build, lpmm_adamw4_step_multi, lpmm_adamw4_plan_release,
+    lpmm_adamw4_plan_bytes, lpmm_adamw4_plan_build, lpmm_adamw4_step_multi, lpmm_adamw4_plan_launches, lpmm_adamw4_plan_release,
     StateB128, new_state_b128, KIND_4BIT_B128, lpmm_adamw4_b128_state_sizes, lpmm_adamw4_b128_state_zero,
     lpmm_adamw4_b128_step, lpmm_adamw4_b128_step_bf16g,
     StateFactor, new_state_factor, lpmm_adamw4_factor_state_sizes, lpmm_adamw4_factor_state_zero,

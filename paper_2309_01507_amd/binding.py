@@ -111,6 +111,7 @@ def lib() -> ctypes.CDLL:
         L.lpmm_adamw4_plan_build.argtypes = [_VP, _I64, ctypes.c_int, _VP, ctypes.c_size_t, _VP]
         L.lpmm_adamw4_step_multi.argtypes = [_VP] + [_F] * 5 + [_I64, _VP]
         L.lpmm_adamw4_plan_release.argtypes = [_VP]
+        L.lpmm_adamw4_plan_launches.argtypes = [_VP]
         L.lpmm_profile_begin.argtypes = [_I64]
         L.lpmm_profile_end.argtypes = [_VP, _VP]
         _lib = L
@@ -670,6 +671,13 @@ def lpmm_sgdm4_step_multi_capturable(plan, lr_dev, momentum, stream=None) -> Non
 
 def lpmm_adamw4_plan_release(plan) -> None:
     _check(lib().lpmm_adamw4_plan_release(_ptr(plan)), "lpmm_adamw4_plan_release")
+
+
+def lpmm_adamw4_plan_launches(plan) -> int:
+    """Kernels that one step of the plan enqueues; 1 with two-pass tensors in it: both passes in one launch."""
+    n = lib().lpmm_adamw4_plan_launches(_ptr(plan))
+    _check(min(n, 0), "lpmm_adamw4_plan_launches")
+    return n
 
 
 def new_plan(descs, grad_dtype: int, device="cuda"):

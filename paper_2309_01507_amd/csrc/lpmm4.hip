@@ -2109,6 +2109,22 @@ int lpmm_adamw4_plan_release(void* plan) {
     return g_plans.erase(plan) ? LPMM_OK : LPMM_EINVAL;
 }
 
+int lpmm_adamw4_plan_launches(const void* plan) {
+    std::lock_guard<std::mutex> lock(g_mu);
+    auto it = g_plans.find(const_cast<void*>(plan));
+    if (it == g_plans.end()) return LPMM_EINVAL;
+    const PlanHost& host = *it->second;
+    if (host.flow) return 1;
+    int n = 0;
+    for (const PhaseLaunch& pl : host.phases) {
+        const int between = (pl.has_nd ? 2 : 0) + (pl.has_det ? 2 : 0);
+        if (host.sgdm) n += pl.ph.n_a > 0;
+        else if (host.side || host.serial) n += (pl.ph.n_a > 0) + (pl.ph.n_b > 0) + between;
+        else n += 1 + between;
+    }
+    return n;
+}
+
 int lpmm_profile_begin(int64_t max_calls) {
     if (max_calls < 1 || max_calls > (int64_t(1) << 20)) return LPMM_EINVAL;
     while (int64_t(g_prof.ev.size()) < 3 * max_calls) {

@@ -16,6 +16,7 @@ from test_gpu_multi import _mini_transformer, _run_set
 
 pytestmark = pytest.mark.gpu
 HP = oracle.Hyper()
+ROUTE = ("LPMM_FLOW", "LPMM_FLOW_MIN", "LPMM_FLOW_SPIN", "LPMM_MULTI_STREAMS", "LPMM_PHASE_MPARAMS", "LPMM_FORCE_GENERAL")
 PHASES = {"LPMM_FLOW": "0"}
 ONE = {"LPMM_FLOW_MIN": "0"}
 DEFERRED = {"LPMM_FLOW_MIN": "0", "LPMM_FLOW_SPIN": "-1"}
@@ -29,9 +30,10 @@ FACTOR = [("factor", (300, 512)), ("factor", (37, 100)), ("factor", (1, 6400)), 
 RAGGED_FACTOR = [("factor", (300, 512)), ("factor", (37, 200))]       # ragged factorized matrices: by phases
 
 
-def _steps(monkeypatch, env, tensors, bf16, steps=3, capture=False):
-    """`steps` steps of one plan; all parameters and states, as arrays."""
-    for k in ("LPMM_FLOW", "LPMM_FLOW_MIN", "LPMM_FLOW_SPIN"):
+def _steps(monkeypatch, env, tensors, bf16, steps=3, capture=False, one_launch=None):
+    """`steps` steps of one plan; all parameters and states, as arrays.  one_launch: the route that the plan has to take,
+    by default the one that the environment asks for."""
+    for k in ROUTE:
         monkeypatch.delenv(k, raising=False)
     for k, v in env.items():
         monkeypatch.setenv(k, v)
@@ -58,6 +60,7 @@ def _steps(monkeypatch, env, tensors, bf16, steps=3, capture=False):
         gs.append(g)
         states.append(st)
     plan = lpmm.new_plan(descs, 1 if bf16 else 0, DEV)
+    assert (lpmm.lpmm_adamw4_plan_launches(plan) == 1) == (env is not PHASES if one_launch is None else one_launch)
     lr, step = torch.full((1,), HP.lr, device=DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
 
     def one():
@@ -87,8 +90,14 @@ def _steps(monkeypatch, env, tensors, bf16, steps=3, capture=False):
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("env", [ONE, DEFERRED], ids=["waiting", "deferred"])
-def test_the_oracle_step_by_step(env, bf16):
+def test_the_oracle_step_by_step(monkeypatch, env, bf16):
+    for k in ROUTE:
+        monkeypatch.delenv(k, raising=False)
+    launches, release = [], lpmm.lpmm_adamw4_plan_release
+    monkeypatch.setattr(lpmm, "lpmm_adamw4_plan_release",
+                        lambda plan: (launches.append(lpmm.lpmm_adamw4_plan_launches(plan)), release(plan)))
     _run_set(_mini_transformer(), "col_lognormal", bf16, steps=3, seed=82, env=env)
+    assert launches == [1]
 
 
 @pytest.mark.parametrize("bf16", [False, True])
@@ -105,8 +114,9 @@ def test_same_bits_as_the_launches_by_phases(monkeypatch, env, capture, bf16):
 @pytest.mark.parametrize("env,capture,tensors", [(ONE, False, FACTOR), (DEFERRED, False, FACTOR), (ONE, True, FACTOR),
                                                  (ONE, True, RAGGED_FACTOR)], ids=["waiting", "deferred", "graph", "ragged"])
 def test_factorized(monkeypatch, env, capture, tensors, bf16):
+    """With a ragged matrix in the set the plan keeps the launches by phases (see flow_possible), here from a graph."""
     want = _steps(monkeypatch, PHASES, tensors, bf16)
-    got = _steps(monkeypatch, env, tensors, bf16, capture=capture)
+    got = _steps(monkeypatch, env, tensors, bf16, capture=capture, one_launch=tensors is FACTOR)
     for (kind, shape), a, b in zip(tensors, want, got):
         np.testing.assert_allclose(b[0], a[0], rtol=PARAM_RTOL, atol=PARAM_ATOL, err_msg=f"{kind} {shape}")
         for x, y in zip(a[1:], b[1:]):
@@ -120,7 +130,7 @@ def test_statistics_beyond_one_workgroup_keep_the_phases(monkeypatch):
     """Inner dimensions with more statistics than the one launch has room for: the plan is stepped by phases."""
     tensors = [("nd", (4, 2400, 2)), ("rank1", (64, 256))]
     want = _steps(monkeypatch, PHASES, tensors, False)
-    got = _steps(monkeypatch, ONE, tensors, False)
+    got = _steps(monkeypatch, ONE, tensors, False, one_launch=False)
     for a, b in zip(want, got):
         for x, y in zip(a, b):
             np.testing.assert_array_equal(x, y)
@@ -137,3 +147,38 @@ def test_counts_of_finished_workgroups(monkeypatch, rows, n_first):
     for a, b in zip(want, got):
         for x, y in zip(a, b):
             np.testing.assert_array_equal(x, y, err_msg=n_first)
+
+
+def test_launches_of_a_step(monkeypatch):
+    """The host's count of a step's kernels on every route: both passes of one group, with two kernels between them for
+    tensors of more than two dimensions; groups on two streams, one after the other and fused; and no plan at all."""
+    lpmm.ensure_init(8192)
+    keep = []
+
+    def launches(tensors, **env):
+        for k in ROUTE:
+            monkeypatch.delenv(k, raising=False)
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        descs = []
+        for kind, shape in tensors:
+            n = int(np.prod(shape))
+            w, g = torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
+            st = {"nd": lambda: lpmm.new_state_nd(shape, DEV), "b128": lambda: lpmm.new_state_b128(n, DEV),
+                  "rank1": lambda: lpmm.new_state(*shape, DEV), "sgdm": lambda: lpmm.new_state_sgdm(n, DEV)}[kind]()
+            keep.append((w, g, st))
+            descs.append(lpmm.make_desc_sgdm(w, g, st) if kind == "sgdm" else lpmm.make_desc(w, g, st))
+        plan = lpmm.new_plan(descs, 0, DEV)
+        n = lpmm.lpmm_adamw4_plan_launches(plan)
+        lpmm.lpmm_adamw4_plan_release(plan)
+        with pytest.raises(lpmm.LpmmError):
+            lpmm.lpmm_adamw4_plan_launches(plan)
+        return n
+
+    two, nd = [("rank1", (1024, 1024)), ("rank1", (1024, 512))], [("nd", (16, 16, 3, 3))]
+    assert launches(two) == 2 and launches(two, LPMM_FLOW_MIN="0") == 1
+    assert launches(nd) == 1 and launches(nd, LPMM_FLOW="0") == 4
+    assert launches([("b128", (1, 5000))]) == 1 and launches([("sgdm", (1, 5000))]) == 1
+    groups = {"LPMM_PHASE_MPARAMS": "1"}
+    assert launches(two, **groups) == 4 and launches(two, LPMM_MULTI_STREAMS="0", **groups) == 4
+    assert launches(two, LPMM_MULTI_STREAMS="1", **groups) == 3

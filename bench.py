@@ -288,12 +288,10 @@ def main():
     one_pass = b128 or sgdm
     n_q_tensors = sum(1 for x in tensors if x[0] == "q")
     n_tensors, has_plans = len(tensors), bool(plans)
-    # rank-1 and factorized plans from 2^25 parameters on are stepped in one launch that holds both passes, unless most of
-    # them are one tensor's (include/lpmm4.h)
-    share = max(x[1].numel for x in tensors) / wl.n_params
-    one_launch = has_plans and not one_pass and not args.deterministic and wl.n_params >= 1 << 25 and \
-        share <= (0.25 if factor else 0.75) and \
-        os.environ.get("LPMM_FLOW") != "0" and not {"LPMM_MULTI_STREAMS", "LPMM_PHASE_MPARAMS"} & set(os.environ)
+    # kernels per step as the library counts them (a step takes one of the plans); a two-pass plan with one holds both
+    # passes in it
+    plan_launches = lpmm.lpmm_adamw4_plan_launches(plans[0]) if has_plans else 0
+    one_launch = has_plans and not one_pass and plan_launches == 1
     lpmm.lpmm_profile_begin(max(n_q_tensors, 64) * args.steps)
     for _ in range(args.steps):
         t += 1
@@ -326,9 +324,11 @@ def main():
             "traffic_source": None,
             "note": ("one pass: this kernel is the whole step" if one_pass else
                      "one launch: this kernel is the whole step, pass 2 (%.1f B/param) of a tensor right behind its pass 1; its "
-                     "gradient reads are counted although part of them comes from the memory-side cache" % bp2 if one_launch else
+                     "gradient reads are counted, the ones that the memory-side cache answers among them" % bp2 if one_launch else
                      "the statistics pass (%.1f B/param) is a launch of its own before it on the same stream; "
                      "whole-step figures are in config" % bp2 if factor else
+                     "one tensor group: pass 2 (%.1f B/param) is a launch of its own behind it on the same stream; "
+                     "whole-step figures are in config" % bp2 if n_calls == args.steps else
                      "pass 2 of the neighbouring tensor group (%.1f B/param) runs concurrently and shares "
                      "the bandwidth; whole-step figures are in config" % bp2),
         }
@@ -362,8 +362,9 @@ def main():
                                      "note": "same kernels and tiles, every launch on the caller's stream one after "
                                              "the other: this kernel with the chip to itself (events included in the step time)"}
         # HBM bytes per launch measured offline with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (see profiles/)
-        tpath = os.path.join(ROOT, "profiles", "traffic_phase_kernel_%s%s.json" % (args.config, "_sgdm" if sgdm else "_b128" if b128 else "_factor" if factor else ""))
-        if os.path.exists(tpath) and not one_launch:
+        tpath = os.path.join(ROOT, "profiles", "traffic_%s_kernel_%s%s.json" % (
+            "flow" if one_launch else "phase", args.config, "_sgdm" if sgdm else "_b128" if b128 else "_factor" if factor else ""))
+        if os.path.exists(tpath):
             tr = json.load(open(tpath))
             if tr.get("launches_per_step") == n_calls // max(args.steps, 1):
                 roofline["traffic"] = tr["hbm_bytes_per_launch"]
@@ -454,7 +455,7 @@ def main():
     floor_bpp = 8.0 + (2.0 if bf16 else 4.0) + (1.0 if factor or sgdm else 2.0) + (16.0 if b128 else 8.0) / 128.0
     floor_gbps = (floor_bpp * n_quant + small_bytes) / (elapsed / args.steps) / 1e9
     if has_plans:
-        kernels_per_step = (n_calls // max(args.steps, 1)) * (1 if one_pass or one_launch else 2)     # as many A as B launches
+        kernels_per_step = plan_launches
     else:
         kernels_per_step = n_q_tensors * (1 if one_pass else 2) + (n_tensors - n_q_tensors)
     out = {
@@ -473,6 +474,8 @@ def main():
                                "multi-tensor plan, %d launch per step with both passes in it" if one_launch else
                                "multi-tensor plan, %d update launches per step, each behind its statistics launch "
                                "on the caller's stream" if factor else
+                               "multi-tensor plan, %d pass-1 launch per step with pass 2 behind it on the caller's stream"
+                               if n_calls == args.steps else
                                "multi-tensor plan, %d pass-1 launches per step on the caller's stream, "
                                "pass 2 on a second stream") % (n_calls // max(args.steps, 1)))
                    if has_plans else "per-tensor, %d kernel%s per quantized tensor" % ((1, "") if one_pass else (2, "s")),

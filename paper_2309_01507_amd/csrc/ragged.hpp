@@ -182,6 +182,7 @@ __device__ __forceinline__ void rag_unit1(const Tensor4& a, const Hyper& h, cons
         w[e] = param_update(h, w[e], mt[e], vt[e]);
         amax = fmaxf(amax, fabsf(mt[e]));
         const bool here = p4 + e < t.lim;
+        vt[e] = fmaxf(vt[e], 0.0f);                       // a NaN raises no maximum, as on the general path
         rmax_a = max_nonneg(rmax_a, here ? vt[e] : 0.0f);
         rmax_b = max_nonneg(rmax_b, here ? 0.0f : vt[e]);
     }

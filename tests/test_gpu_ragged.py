@@ -103,3 +103,36 @@ def test_factorized_step_matches_the_oracle(rows, cols, bf16):
     print(f"[gpu-test] ragged factorized {rows}x{cols} bf16={bf16}", flush=True)
     assert run(rows, cols, steps=3, bf16=bf16) == 0
     assert run(rows, cols, steps=2, recipe="outlier_sparse" if rows > 1 else "iid", bf16=bf16) == 0
+
+
+@pytest.mark.parametrize("rows,cols,bf16", [(40, 2100, False), (67, 2305, True), (300, 777, False)])
+def test_nan_in_one_second_moment_costs_that_element_only(monkeypatch, rows, cols, bf16):
+    """One row's and one column's old maximum NaN, so that exactly one element's second moment is: it raises neither its
+    row's nor its column's new maximum, and every state comes out as from the general kernels (rows of more than 2048
+    elements; below, those record the NaN as the column's maximum).  The first moment, whose codes are searched by the
+    value's bits, stays finite."""
+    lpmm.ensure_init(rows + cols)
+    i, j = rows // 2, cols // 3
+    w0 = workloads.weights(75, 0, rows, cols).reshape(-1)
+    grads = [workloads.grads(75, 0, t, rows, cols, "col_lognormal", bf16).reshape(-1) for t in (1, 2, 3)]
+    out = []
+    for general in ("0", "1"):
+        monkeypatch.setenv("LPMM_FORCE_GENERAL", general)
+        w, st = to_dev(w0.copy()), lpmm.new_state(rows, cols, DEV)
+        gpu_step(w, to_dev(grads[0], bf16), st, HP, 1, bf16)
+        st.v_rowmax[i] = float("nan")
+        st.v_colmax[j] = float("nan")
+        for t in (2, 3):
+            gpu_step(w, to_dev(grads[t - 1], bf16), st, HP, t, bf16)
+            if t == 2:
+                first = st.v_rowmax.cpu().numpy(), st.v_colmax.cpu().numpy()
+        out.append((download_state(st), w.cpu().numpy(), *first))
+    (a, wa, ra, ca), (b, wb, rb, cb) = out
+    assert np.isnan(wa[i * cols + j]) and np.isfinite(np.delete(wa, i * cols + j)).all()
+    assert np.isfinite(ra).all() and np.isfinite(ca).all() and (ra > 0).all()
+    np.testing.assert_array_equal(ra, rb)
+    np.testing.assert_array_equal(a.m_codes, b.m_codes)
+    np.testing.assert_array_equal(a.m_scales, b.m_scales)
+    if cols > 2048:
+        for x, y in ((ca, cb), (a.v_codes, b.v_codes), (a.v_r, b.v_r), (a.v_c, b.v_c), (wa, wb)):
+            np.testing.assert_array_equal(x, y)

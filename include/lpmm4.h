@@ -404,8 +404,10 @@ typedef struct lpmm_tensor_desc {
 } lpmm_tensor_desc;
 
 /* Bytes of device memory a plan for these tensors needs (descriptor tables, per-tensor row/column
- * maxima of the updated second moment, ticket counters).  descs: host array of n entries; only
- * rows, cols, kind and flags are read.  Returns 0 for invalid input. */
+ * maxima of the updated second moment, ticket counters, and the work list of a step in one launch).  descs: host array
+ * of n entries; only rows, cols, kind and flags are read.  Returns 0 for invalid input.  Environment variables that
+ * choose the launches (LPMM_FLOW and others, for experiments) change the size: a plan built into memory that has no
+ * room for the work list is stepped by the other launches. */
 size_t lpmm_adamw4_plan_bytes(const lpmm_tensor_desc* descs, int64_t n);
 
 /* Builds the plan into `plan` (device memory, 256-byte aligned, plan_bytes long, owned by the caller
@@ -418,7 +420,8 @@ int lpmm_adamw4_plan_build(const lpmm_tensor_desc* descs, int64_t n, int grad_dt
 
 /* The same two calls for lists that hold LPMM_KIND_4BIT_ND tensors.  inner_dims: host array of 7 sizes per tensor
  * (d_2 .. d_p, unused entries ignored), inner_ndim: host array with p - 1 per tensor, 0 for tensors of other kinds.
- * Two small kernels per tensor group are enqueued in addition (see lpmm_adamw4_nd_step). */
+ * What lpmm_adamw4_nd_step's two small kernels do is part of the one launch; plans that are not stepped in one enqueue
+ * two such kernels per tensor group. */
 size_t lpmm_adamw4_plan_bytes_nd(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims,
                                  const int32_t* inner_ndim);
 int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims,

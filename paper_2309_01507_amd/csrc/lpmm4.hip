@@ -878,8 +878,9 @@ bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inne
     return factor || n_large > 8 || large < total / 16 * 15 || largest > (int64_t(1) << 25);
 }
 
+// one_launch: with room for a work list, if the plan is one for a single launch
 bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim,
-                 PlanLayout* L) {
+                 PlanLayout* L, bool one_launch = true) {
     if (!descs || n < 1 || n > (1 << 20)) return false;
     int64_t floats = 0, n_nd = 0;
     bool rank1 = false, factor = false;
@@ -906,7 +907,7 @@ bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_
     if (rank1 && factor) return false;       // two different optimizers: one plan holds one of them
     if (n_sgdm != 0 && n_sgdm != n) return false;
     L->cap_items = L->cap_deferred = 0;
-    if (flow_possible(descs, n, inner_dims, inner_ndim)) {
+    if (one_launch && flow_possible(descs, n, inner_dims, inner_ndim)) {
         int64_t total = 0;
         for (int64_t i = 0; i < n; ++i) total += descs[i].rows * descs[i].cols;
         for (int64_t i = 0; i < n; ++i) {
@@ -1571,6 +1572,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
                               void* stream) {
     PlanLayout L;
     if (!plan_layout(descs, n, inner_dims, inner_ndim, &L)) return LPMM_EINVAL;
+    // memory sized without a work list (under other settings of the environment): launches by phases
+    if (plan_bytes < L.total) (void)plan_layout(descs, n, inner_dims, inner_ndim, &L, false);
     if (!plan || !aligned(plan, 256) || plan_bytes < L.total) return LPMM_EINVAL;
     if (grad_dtype != LPMM_GRAD_F32 && grad_dtype != LPMM_GRAD_BF16) return LPMM_EINVAL;
     DeviceCtx* ctx;

@@ -182,3 +182,21 @@ def test_launches_of_a_step(monkeypatch):
     groups = {"LPMM_PHASE_MPARAMS": "1"}
     assert launches(two, **groups) == 4 and launches(two, LPMM_MULTI_STREAMS="0", **groups) == 4
     assert launches(two, LPMM_MULTI_STREAMS="1", **groups) == 3
+
+
+def test_memory_without_a_work_list(monkeypatch):
+    """A plan built into memory that was sized with the one launch switched off: by phases, the same bits."""
+    tensors = [("rank1", (300, 512)), ("nd", (24, 16, 3, 3)), ("rank1", (37, 200))]
+    want = _steps(monkeypatch, PHASES, tensors, False)
+    sized = lpmm.binding.lpmm_adamw4_plan_bytes
+
+    def without(descs):
+        with monkeypatch.context() as m:
+            m.setenv("LPMM_FLOW", "0")
+            return sized(descs)
+
+    monkeypatch.setattr(lpmm.binding, "lpmm_adamw4_plan_bytes", without)
+    got = _steps(monkeypatch, ONE, tensors, False, one_launch=False)
+    for a, b in zip(want, got):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)

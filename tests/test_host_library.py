@@ -296,3 +296,20 @@ def test_which_plans_are_stepped_in_one_launch(monkeypatch, name, tensors, one):
     phases = lpmm.lpmm_adamw4_plan_bytes(descs)
     monkeypatch.delenv("LPMM_FLOW")
     assert phases > 0 and (lpmm.lpmm_adamw4_plan_bytes(descs) > phases) == one
+
+
+def test_plan_memory_sized_without_a_work_list_is_accepted(monkeypatch):
+    """Memory that plan_bytes sized with the one launch switched off is enough to build the plan with it on (the plan is
+    then stepped by phases); a byte less is not.  No GPU here: an accepted call gets as far as looking for one."""
+    for k in ("LPMM_FLOW_MIN", "LPMM_MULTI_STREAMS", "LPMM_PHASE_MPARAMS"):
+        monkeypatch.delenv(k, raising=False)
+    descs = _plan_set(_BERT)
+    monkeypatch.setenv("LPMM_FLOW", "0")
+    phases = lpmm.lpmm_adamw4_plan_bytes(descs)
+    monkeypatch.delenv("LPMM_FLOW")
+    assert lpmm.lpmm_adamw4_plan_bytes(descs) > phases
+    arr = (lpmm.TensorDesc * len(descs))(*descs)
+    plan = ctypes.create_string_buffer(512)
+    p = (ctypes.addressof(plan) + 255) // 256 * 256
+    build = lambda nbytes: lpmm.lib().lpmm_adamw4_plan_build(ctypes.addressof(arr), len(descs), 0, p, nbytes, None)
+    assert build(phases) in (-2, -3) and build(phases - 1) == -1

@@ -103,39 +103,43 @@ __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, u
     return w;
 }
 
-// Block-wise normalization: a workgroup takes two blocks of 2048 elements or 32 blocks of 128.
-template <int BLOCK, bool SR>
+// Block-wise normalization: a workgroup takes UNITS runs of 1024 elements, four (two blocks of 2048 or 32 of 128) or, with
+// stochastic rounding in tensors of at most 2^21 elements, two: there the chain of a lane's 16 roundings is what the call
+// takes (64 x 64: 8.8 us with four, 7.8 with two; 4096 x 100: 9.1, 7.9).
+constexpr int64_t kAblShortElems = int64_t(1) << 21;
+template <int BLOCK, bool SR, int UNITS>
 __global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs a, const AblMap m) {
     static_assert(BLOCK == 128 || BLOCK == 2048, "block sizes of Tab. 1");
-    static_assert(kCvtElems == 2 * 2048 && kCvtUnitElems == 1024, "two units of a workgroup make one block of 2048");
+    static_assert(UNITS % 2 == 0 && kCvtUnitElems == 1024, "two units of a workgroup make one block of 2048");
+    constexpr int kBlocks = UNITS / 2;                    // of 2048
     __shared__ AblLds s_map;
-    __shared__ float s_part[2][kThreads / 64];
-    const int64_t first = int64_t(blockIdx.x) * kCvtElems + threadIdx.x * 4;
-    float x[kCvtUnits][4], sc[kCvtUnits];
+    __shared__ float s_part[kBlocks][kThreads / 64];
+    const int64_t first = int64_t(blockIdx.x) * (UNITS * kCvtUnitElems) + threadIdx.x * 4;
+    float x[UNITS][4], sc[UNITS];
 #pragma unroll
-    for (int u = 0; u < kCvtUnits; ++u) cvt_load4(a.x_in, first + u * kCvtUnitElems, a.P, x[u]);
+    for (int u = 0; u < UNITS; ++u) cvt_load4(a.x_in, first + u * kCvtUnitElems, a.P, x[u]);
     abl_load_map(s_map, m);
 #pragma unroll
-    for (int u = 0; u < kCvtUnits; ++u)
+    for (int u = 0; u < UNITS; ++u)
         sc[u] = group32_allmax(cvt_absmax4(x[u]));
     if constexpr (BLOCK == 2048) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < kBlocks; ++b) {
             float v = fmaxf(sc[2 * b], sc[2 * b + 1]);
             v = fmaxf(v, __shfl_xor(v, 32));
             if ((threadIdx.x & 63) == 0) s_part[b][threadIdx.x >> 6] = v;
         }
         __syncthreads();
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < kBlocks; ++b)
             sc[2 * b] = sc[2 * b + 1] = fmaxf(fmaxf(s_part[b][0], s_part[b][1]), fmaxf(s_part[b][2], s_part[b][3]));
-        if (threadIdx.x < 2) {
-            const int64_t blk = int64_t(blockIdx.x) * 2 + threadIdx.x;
-            if (blk * 2048 < a.P) a.sa[blk] = threadIdx.x ? sc[2] : sc[0];
+        if (threadIdx.x < kBlocks) {
+            const int64_t blk = int64_t(blockIdx.x) * kBlocks + threadIdx.x;
+            if (blk * 2048 < a.P) a.sa[blk] = threadIdx.x ? sc[2 * (kBlocks - 1)] : sc[0];
         }
     }
 #pragma unroll
-    for (int u = 0; u < kCvtUnits; ++u) {
+    for (int u = 0; u < UNITS; ++u) {
         const int64_t base = first + u * kCvtUnitElems;
         if (base >= a.P) continue;
         const float s[4] = {sc[u], sc[u], sc[u], sc[u]};

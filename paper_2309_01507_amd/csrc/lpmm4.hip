@@ -1521,12 +1521,18 @@ int lpmm_quant_ablation(int norm, int map, int is_signed, int rounding, uint64_t
         const int r = launch_maxima(q, 256, s);       // this call needs no init, hence no device context
         if (r) return r;
     }
-#define LPMM_ABL_LAUNCH(SR)                                                                                            \
-    if (norm == LPMM_NORM_RANK1) hipLaunchKernelGGL(abl_quant_rank1_kernel<SR>, dim3(grid), dim3(kThreads), 0, s, a, m); \
-    else if (norm == LPMM_NORM_B128) hipLaunchKernelGGL((abl_quant_block_kernel<128, SR>), dim3(grid), dim3(kThreads), 0, s, a, m); \
-    else hipLaunchKernelGGL((abl_quant_block_kernel<2048, SR>), dim3(grid), dim3(kThreads), 0, s, a, m);
-    if (a.stochastic) { LPMM_ABL_LAUNCH(true) } else { LPMM_ABL_LAUNCH(false) }
-#undef LPMM_ABL_LAUNCH
+#define LPMM_ABL_BLOCK(SR, UNITS)                                                                                      \
+    if (norm == LPMM_NORM_B128) hipLaunchKernelGGL((abl_quant_block_kernel<128, SR, UNITS>), dim3(blocks), dim3(kThreads), 0, s, a, m); \
+    else hipLaunchKernelGGL((abl_quant_block_kernel<2048, SR, UNITS>), dim3(blocks), dim3(kThreads), 0, s, a, m);
+    const bool shorter = a.stochastic && a.P <= kAblShortElems;
+    const int blocks = shorter ? grid_for(a.P, 2 * kCvtUnitElems / kThreads) : grid;
+    if (norm == LPMM_NORM_RANK1) {
+        if (a.stochastic) hipLaunchKernelGGL(abl_quant_rank1_kernel<true>, dim3(grid), dim3(kThreads), 0, s, a, m);
+        else hipLaunchKernelGGL(abl_quant_rank1_kernel<false>, dim3(grid), dim3(kThreads), 0, s, a, m);
+    } else if (shorter) { LPMM_ABL_BLOCK(true, 2) }
+    else if (a.stochastic) { LPMM_ABL_BLOCK(true, kCvtUnits) }
+    else { LPMM_ABL_BLOCK(false, kCvtUnits) }
+#undef LPMM_ABL_BLOCK
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
 }

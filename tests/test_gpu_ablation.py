@@ -67,6 +67,17 @@ def test_ablation_quantizers_match_the_oracle(norm, map_name, signed, shape, sto
     np.testing.assert_array_equal(out.cpu().numpy().reshape(rows, cols), want)
 
 
+@pytest.mark.parametrize("norm", ["b128", "b2048"])
+@pytest.mark.parametrize("shape", [(1, 2048), (1, 2049), (3, 1365), (2048, 1024), (2048, 1025)])
+def test_stochastic_rounding_in_short_and_long_workgroups(norm, shape):
+    """Up to 2^21 elements a workgroup takes one block of 2048 with stochastic rounding, beyond two."""
+    x = _input(*shape, False, seed=shape[0] + shape[1])
+    want_codes, want_sa, _ = oracle.quant_ablation(x, norm, "de", False, True, 99)
+    codes, sa, _ = _gpu_quant(x, norm, "de", False, True, 99)
+    np.testing.assert_array_equal(sa.cpu().numpy(), want_sa)
+    np.testing.assert_array_equal(oracle.unpack_codes(codes.cpu().numpy(), x.size), oracle.unpack_codes(want_codes, x.size))
+
+
 def test_stochastic_rounding_depends_on_the_seed_only():
     """Same seed, same codes, whatever was launched before; another seed, other codes; each code is the nearest
     entry or its neighbour."""

@@ -106,7 +106,10 @@ def test_step_parity_fast_path(rows, cols):
 @pytest.mark.parametrize("rows,cols", [(37, 200), (5, 7), (1, 999), (1000, 3), (129, 127), (2, 4100), (700, 192),
                                        (9, 2100), (40000, 3), (2000, 9)])
 def test_step_parity_general_path(rows, cols):
+    """As they come (rows of 128 and more on the ragged tiles), and all on the general kernels."""
     assert run(rows, cols, steps=3) == 0
+    if cols >= 128:
+        assert run(rows, cols, steps=3, env={"LPMM_FORCE_GENERAL": "1"}) == 0
 
 
 def test_bf16_gradients():
@@ -115,9 +118,10 @@ def test_bf16_gradients():
 
 
 def test_long_run_stays_in_step():
-    """150 steps with a gradient mean that persists and then dies away, fast and general path."""
+    """150 steps with a gradient mean that persists and then dies away, fast, ragged and general path."""
     assert run(192, 256, steps=150, recipe="drift") == 0
     assert run(37, 200, steps=100, recipe="drift") == 0
+    assert run(70, 100, steps=100, recipe="drift") == 0
 
 
 def test_outliers_and_zero_rows():

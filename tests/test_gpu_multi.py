@@ -73,7 +73,7 @@ def _mini_transformer():
     for l in range(3):
         out += [T(f"l{l}.qkv", 256, 768), T(f"l{l}.out", 256, 256), T(f"l{l}.fc1", 256, 1024),
                 T(f"l{l}.fc2", 1024, 256), T(f"l{l}.b1", 1, 768, 1), T(f"l{l}.ln", 1, 256, 1)]
-    out += [T("odd", 37, 200), T("head", 300, 384)]       # one tensor that takes the general path
+    out += [T("odd", 37, 200), T("head", 300, 384), T("narrow", 90, 100)]       # ragged tiles, general path
     return out
 
 

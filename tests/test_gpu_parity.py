@@ -110,8 +110,8 @@ def test_zero_state_matches_oracle():
     (256, 512, "iid"),                 # fast path, several tiles
     (203, 384, "col_lognormal"),       # fast path, ragged last row tile, 3 column blocks
     (64, 128, "iid"),                  # fast path, one column block
-    (37, 200, "col_lognormal"),        # general path: blocks straddle rows
-    (13, 77, "iid"),                   # general path, odd element count, short last block
+    (37, 200, "col_lognormal"),        # ragged path: blocks straddle rows
+    (13, 77, "iid"),                   # general path (rows shorter than 128), odd element count, short last block
     (1, 5000, "iid"),                  # one row
     (300, 1, "iid"),                   # one column
     (1, 1, "iid"), (1, 2, "iid"),      # degenerate
@@ -123,8 +123,8 @@ def test_zero_state_matches_oracle():
     (3, 128, "col_lognormal"),         # fast path, one column block, fewer rows than groups
     (5000, 128, "iid"),                # tall and one block wide: many row tiles of one strip
     (2, 1280, "iid"),                  # 10 column blocks: fine for pass 2; see (203, 384) for a half-empty last strip
-    (700, 192, "col_lognormal"),       # general path, narrow: several chunks per workgroup, maxima combined in LDS
-    (9, 2100, "iid"),                  # general path, more columns than the LDS column array holds
+    (700, 192, "col_lognormal"),       # ragged path, one strip
+    (9, 2100, "iid"),                  # ragged path, several strips
     (40000, 3, "iid"),                 # general path, more rows per workgroup than the LDS row array holds
     (2000, 9, "col_lognormal"),        # general path, rows of 9 elements: lanes straddle rows
 ])
@@ -132,9 +132,23 @@ def test_step_parity_small(rows, cols, recipe):
     assert run_parity(rows, cols, steps=6, recipe=recipe, seed=3) == 0
 
 
+@pytest.mark.parametrize("rows,cols,recipe", [
+    (37, 200, "col_lognormal"),        # blocks straddle rows
+    (700, 192, "col_lognormal"),       # several chunks per workgroup, maxima combined in LDS
+    (9, 2100, "iid"),                  # more columns than the LDS column array holds
+    (150, 150, "outlier_sparse"),      # zero rows, scales far apart
+])
+def test_step_parity_general_kernels(monkeypatch, rows, cols, recipe):
+    """The general kernels on rows of 128 and more, which take the ragged tiles by themselves."""
+    monkeypatch.setenv("LPMM_FORCE_GENERAL", "1")
+    assert run_parity(rows, cols, steps=6, recipe=recipe, seed=3) == 0
+    assert run_parity(rows, cols, steps=3, recipe=recipe, bf16=True, seed=4) == 0
+
+
 def test_step_parity_bf16_gradients():
     assert run_parity(256, 384, steps=6, recipe="col_lognormal", bf16=True, seed=4) == 0
     assert run_parity(37, 200, steps=4, recipe="col_lognormal", bf16=True, seed=4) == 0
+    assert run_parity(300, 100, steps=4, recipe="col_lognormal", bf16=True, seed=4) == 0
 
 
 def test_config1_full():
@@ -142,9 +156,9 @@ def test_config1_full():
     assert run_parity(1024, 1024, steps=10, recipe="iid", seed=1) == 0
 
 
-@pytest.mark.parametrize("rows,cols,steps", [(192, 256, 300), (37, 200, 150)])
+@pytest.mark.parametrize("rows,cols,steps", [(192, 256, 300), (37, 200, 150), (70, 100, 150)])
 def test_long_run_stays_in_step(rows, cols, steps):
-    """Hundreds of steps, fast and general path: a gradient mean that persists and then dies away takes the
+    """Hundreds of steps, fast, ragged and general path: a gradient mean that persists and then dies away takes the
     moments through growth, sign-stable first moments and shrinking scales; codes and scales stay bit for bit
     with the oracle's at every step."""
     assert run_parity(rows, cols, steps=steps, recipe="drift", seed=8) == 0

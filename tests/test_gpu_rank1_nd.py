@@ -93,8 +93,8 @@ def test_zero_state_matches_oracle():
 @pytest.mark.parametrize("shape", [(64, 8, 16), (96, 32, 3, 3), (40, 4, 4, 8), (256, 64, 2), (3, 5, 7), (16, 3, 3, 3),
                                    (10, 2, 3, 4, 5), (5, 1, 128), (7, 128, 1), (2, 2, 2, 2, 2, 2, 2, 2)])
 def test_step_parity(shape):
-    # inner sizes whose product is a multiple of 128 take the tiled kernels, the others the general ones; conv-like
-    # shapes, unit dimensions, the maximum number of dimensions
+    # inner sizes whose product is a multiple of 128 take the tiles of whole blocks, other products from 128 on the ragged
+    # ones, smaller ones the general kernels; conv-like shapes, unit dimensions, the maximum number of dimensions
     assert run(shape, steps=3) == 0
 
 

@@ -364,7 +364,7 @@ def main():
         # HBM bytes per launch measured offline with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (see profiles/)
         tpath = os.path.join(ROOT, "profiles", "traffic_%s_kernel_%s%s.json" % (
             "flow" if one_launch else "phase", args.config, "_sgdm" if sgdm else "_b128" if b128 else "_factor" if factor else ""))
-        if os.path.exists(tpath):
+        if os.path.exists(tpath) and args.grad_dtype == "config":           # measured with the configuration's gradient type
             tr = json.load(open(tpath))
             if tr.get("launches_per_step") == n_calls // max(args.steps, 1):
                 roofline["traffic"] = tr["hbm_bytes_per_launch"]

@@ -17,10 +17,10 @@
 // code without a second moment is SGD with momentum (App. E Alg. 2).  With a factorized second
 // moment (Sec. 4.3, factor_*) the two passes are: row / column sums of g^2, then the update.  Tensors
 // with more than two dimensions (App. F Alg. 4, nd_*) run the two matrix passes on derived column scales.
-// The bodies are "tile" functions; thin __global__ wrappers run them for one tensor (two launches
-// per step, one for the block-wise form), and the phase kernels run pass 1 of one set of tensors
-// next to pass 2 of the previous set, so that the arithmetic-heavy pass 2 hides under the
-// memory-bound pass 1.
+// The bodies are "tile" functions, here and (rows that are no multiple of 128 elements) in ragged.hpp.  Thin __global__
+// wrappers run them for one tensor (two launches per step, one for the block-wise form); for many tensors they run from a
+// work list in one launch with pass 2 of a tensor behind its pass 1 (flow.hpp), or by phases, pass 1 of one set of tensors
+// next to pass 2 of the previous set (launch.hpp).
 #pragma once
 
 #include <cstddef>
@@ -668,8 +668,9 @@ __device__ __forceinline__ void pass1_flat_tile(const Tensor4& a, const Hyper& h
     const int row_g = grp << a.rs;
     const uint32_t lane4 = row_offset(row_g, a.cols, uint32_t(cb0) * 128u + uint32_t(l) * 4u) * 4u, pitch4 = uint32_t(a.cols) * 4u;
     auto off = [&](int q) { return lane4 + (uint32_t(walk.at(krow(q))) * pitch4 + uint32_t(q - krow(q) * nbk) * 512u); };
-    // the gradient's load is non-temporal although pass 2 reads it again: not keeping the line is 0.35 % per step on the
-    // 7B-shaped set (five A/B pairs)
+    // the gradient's load is non-temporal although pass 2 reads it again: tensors large enough for this tiling are not
+    // served from the memory-side cache the second time, and not keeping the line is 0.35 % per step by phases (five A/B
+    // pairs) and 0.7 % in one launch (7B-shaped set 16.43 against 16.54 ms, with fp32 gradients 20.51 against 20.73)
     auto fetch = [&](int q) { return load_row1<BF16, kPolicyNt>(tb, off(q)); };
     int q = 0;
     Row1<BF16> r0 = fetch(0);
@@ -992,7 +993,7 @@ __device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int
     const uint32_t lane_g = lane_e * (BF16 ? 2u : 4u), lane_q = lane_e >> 1;
     const int row_b = RAGGED ? wave : 0;
     auto fetch = [&](int il) { return load_row2<BF16>(tb, uint32_t((il < last ? il : last) - row_b) * cols, lane_g, lane_q); };   // il * cols < 2^29
-        constexpr int kDepth = SAME_LAUNCH ? 4 : 3;
+    constexpr int kDepth = SAME_LAUNCH ? 4 : 3;
     auto put = [&](int il, uint32_t codes) {
         if (live) __builtin_amdgcn_raw_buffer_store_b16(short(codes), tb.rvq, int(lane_q), int((uint32_t(il - row_b) * cols) >> 1), 0);
     };

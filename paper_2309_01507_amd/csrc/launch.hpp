@@ -179,7 +179,7 @@ struct Segment {        // a run of workgroups that work on one tensor
 
 // Tensors per kind in one phase; the tables travel as kernel arguments (3 KiB of the 4 KiB a launch may carry).
 // As many as fit: sets of a few hundred small tensors run fastest as a single group (the 108 M-parameter set of 197
-// tensors: 0.361 ms per step as one group against 0.397 as two with their passes overlapped).
+// tensors by phases: 0.361 ms per step as one group against 0.397 as two with their passes overlapped).
 constexpr int kMaxSeg = 192;
 
 struct Phase {

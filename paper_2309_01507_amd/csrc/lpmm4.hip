@@ -1,6 +1,6 @@
 // lpmm4.so -- C ABI and launch logic of the 4-bit AdamW step (declared in include/lpmm4.h).
-// Host side only: argument checks, launch geometry, bias corrections.  All arithmetic of the
-// method runs in the kernels of kernels.hpp.
+// Host side only: argument checks, launch geometry, work lists, bias corrections.  All arithmetic of the
+// method runs in the kernels of kernels.hpp, ragged.hpp, launch.hpp, flow.hpp, convert.hpp and ablation.hpp.
 
 #include <hip/hip_runtime.h>
 
@@ -781,12 +781,13 @@ bool plan_inner_dims(const lpmm_tensor_desc& d, int64_t i, const int64_t* inner_
 // Tiles of one tensor of a plan that is stepped in one launch; `total`: parameters of the plan.  A function of the shapes
 // alone, because the size of the plan's memory follows from it.
 //
-// Pass 1 walks down its rows, 64 of them (GPT-2-medium set 837 us; 32 rows: 979, 128: 839, 256: 881; along the rows, 16 at
-// a time: 915), except in tensors of 2^24 parameters and more with wide rows, whose strips it walks along their rows, 16
-// rows at a time (7B-shaped set 16.85 ms; 8 rows 17.2, 32 rows 17.6, down 64 rows 17.03).  Pass 2 takes 128 rows (64 rows:
-// 851 us and 17.2 ms, 256 rows: 838 us and 16.84 ms, 128: 837 us and 16.80 ms; BERT-base 303, 303 and 322 us for 64, 128
-// and 256).  Sets of less than 2^25 parameters (they are here for the sake of their convolutions) take shorter tiles to
-// have enough of them: 7.4 million parameters 75, 70, 56 and 83 us with the rows divided by 1, 2, 4 and 8.
+// Pass 1 walks down its rows, 64 of them (GPT-2-medium set 838 us, BERT-base 305; 32 rows: 918 and 328, 128: 817 and 314),
+// except in tensors of 2^24 parameters and more with wide rows, whose strips it walks along their rows, 16 rows at a time
+// (7B-shaped set 16.4 ms, with fp32 gradients 20.4; 8 rows 16.8 and 20.7, 32 rows 17.4 and 21.0, down 64 rows 16.6 and 20.6).
+// Pass 2 takes 128 rows (64 rows: GPT-2-medium 846 us, BERT-base 303, 7B-shaped 17.5 ms; 256: 841, 314, 16.2 to 16.5).  Sets of
+// less than 2^25 parameters (they are here for the sake of their convolutions) take shorter tiles to have enough of them:
+// vision sets of 7.4 million parameters 58, 44, 41 and 52 us with the rows divided by 1, 2, 4 and 8, of 20 million 83, 75, 88
+// and 124.
 constexpr int64_t kFlowMinParams = int64_t(1) << 25;
 void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int grad_bytes) {
     constexpr int kCus = 256;
@@ -817,9 +818,10 @@ bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast |
 // Whether a list of tensors is stepped in one launch.  It can be where some tensor has two passes, no sums are wanted in a
 // fixed order, and the statistics of tensors with more than two dimensions are few enough for one workgroup.  It is where
 // that is faster (us, phases / one launch; where two pairs are given, fp32 and bf16 gradients):
-// - Sets of 2^25 parameters or more: 56 M parameters 156 / 152, 109 M 358 / 303, 143 M 461 / 408, 294 M 1103 / 956.  Below,
-//   there is little in flight to hide a tensor's wait between the passes behind: 9.0 M 38 / 38, 16.7 M 64 / 68, factorized
-//   50 / 54.
+// - Sets of 2^25 parameters or more (transformers with an embedding: 35 M 116 / 110, 99 / 98; 66 M 220 / 189, 180 / 162;
+//   131 M 408 / 363, 328 / 297; 498 M 1708 / 1418, 1356 / 1187).  Below, there is little in flight to hide a tensor's wait
+//   between the passes behind (8.4 M 43 / 49, 39 / 47; 16.7 M 63 / 61, 55 / 56; 24 M 82 / 82, 72 / 75; factorized 29 M 88 /
+//   89, 74 / 80).
 // - Not sets of which one tensor is most, whose second pass finds little to run beside: rank-1 up to three quarters,
 //   factorized up to a quarter.  Alone, one launch is the slower way (8192 x 4096 106 / 129, 91 / 109; 50257 x 1024 171 / 173,
 //   144 / 149); beside other tensors it is by now the faster one on both sides of these lines (rank-1, 99 M, 0.75 of it in
@@ -833,10 +835,11 @@ bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast |
 //   551 / 499; 0.5 567 / 592, 516 / 580; all 762 / 885, 735 / 900), factorized up to half (adapters 64 x 4096 and 4096 x 64:
 //   406 / 354, 394 / 337; all narrow 1006 / 1140, 1007 / 1138).
 // - Sets with tensors of more than two dimensions, which by phases take four dependent launches, also below 2^25 parameters
-//   (7.4 M 60 / 56; 8 of 128 x 128 x 3 x 3 34 / 24; 2048 x 4096 and one of 64 x 64 x 3 x 3 46 / 42), unless it is one large tensor
-//   alone (1024 x 1024 x 3 x 3 67 / 73; 640 x 640 x 3 x 3 44 / 44).  From 2^25 on the lines above hold for them, too, where such
-//   tensors are few (two of 4096 x 4096 and one of 64 x 64 x 3 x 3 117 / 124, 102 / 110; with one of 512 x 512 x 3 x 3, a
-//   fifteenth of the parameters, 130 / 128, 113 / 113; with four 162 / 146, 137 / 127).
+//   (a vision set of 7.4 M 61 / 41, 56 / 38; 8 of 128 x 128 x 3 x 3 34 / 24; 2048 x 4096 and one of 64 x 64 x 3 x 3 46 /
+//   42), unless it is one large tensor alone (1024 x 1024 x 3 x 3 67 / 73; 640 x 640 x 3 x 3 44 / 44).  From 2^25 on the
+//   lines above hold for them, too, where such tensors are few (two of 4096 x 4096 and one of 64 x 64 x 3 x 3 117 / 124,
+//   102 / 110; with one of 512 x 512 x 3 x 3, a fifteenth of the parameters, 130 / 128, 113 / 113; with four 162 / 146, 137
+//   / 127).
 bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_dims, const int32_t* inner_ndim) {
     if (env_int("LPMM_FLOW", 1) == 0 || std::getenv("LPMM_MULTI_STREAMS") || std::getenv("LPMM_PHASE_MPARAMS")) return false;
     bool factor = false;
@@ -937,13 +940,15 @@ bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_
 // The work list of a plan that is stepped in one launch, and the tensors' tiles for it; leaves the plan to the
 // launches by groups if the list does not fit (column maxima that turned out misaligned give more tiles).
 //
-// Both passes are laid on a time line in units of parameters: pass 1 of the tensors one after the other; pass 2 of a
-// tensor starts a lag after its pass 1 ends -- about what is in flight on the chip at a time, so that it finds the first
-// pass complete -- and takes as long as its pass 1 did.  2^23 parameters: with half and one and a half times as many the
-// GPT-2-medium set takes 845 and 846 us in place of 840.  Tensors with more than two dimensions come first, the widest
-// ones ahead: one workgroup turns their maxima into statistics between the passes, and that takes longest where there are
-// many columns.  Then the largest ones: what is left at the end, a pass 2 with no pass 1 beside it, is that of the
-// smallest (as listed, large embeddings last / by size: 56 M parameters 206 / 152 us, 143 M 469 / 408).
+// Both passes are laid on a time line in units of parameters: pass 1 of the tensors one after the other; pass 2 of a tensor
+// starts a lag after its pass 1 ends -- about what is in flight on the chip at a time, so that it finds the first pass
+// complete -- and takes as long as its pass 1 did.  2^23 parameters: with 2^22, 2^23, 2^24 and 2^25 the BERT-base set takes
+// 306, 309, 317 and 335 us, the GPT-2-medium set 835, 836, 853 and 873, the 7B-shaped one 16.42, 16.45, 16.50 and 16.56 ms;
+// 16 matrices of 4096 x 4096 825, 791, 780 and 767 us, their bf16 form 693, 659, 634 and 623.  Tensors with more than two
+// dimensions come first, the widest ones ahead: one workgroup turns their maxima into statistics between the passes, and
+// that takes longest where there are many columns.  Then the largest ones: what is left at the end, a pass 2 with no pass 1
+// beside it, is that of the smallest (as listed, large embeddings last / by size: 56 M parameters 206 / 152 us, 143 M 469 /
+// 408).
 //
 // The two are merged by time, eight workgroups at a time: ids are dealt to the 8 XCDs in turn, and the eight of a row take
 // their tiles from eight equal contiguous parts of the pass, so that neighbouring tiles, which share cache lines, stay on
@@ -1604,7 +1609,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
 
     const int64_t rw_hint = env_int("LPMM_MULTI_RW", -1);      // -1: the plan defaults (64 rows, 32 for the flat tiling)
     const int64_t rw2_hint = env_int("LPMM_MULTI_RW2", 128);
-    // Flat tiling of pass 1 for the large tensors of this plan?  Measured: 3-4 % faster on the 7B-shaped set, where
+    // Flat tiling of pass 1 for the large tensors of this plan, if it is stepped by phases (a plan stepped in one launch
+    // takes its tiles from flow_geometry)?  Measured: 3-4 % faster on the 7B-shaped set stepped that way, where
     // pass 1 runs beside pass 2 of the previous group; 4 % slower for one large tensor alone (one group, the passes
     // run one after the other); slower on sets of small tensors, whose tiles become too few; and a launch that
     // mixes many cheap tiles with a few four times more expensive flat ones loses 20 % to imbalance between the
@@ -1940,10 +1946,10 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         }
         return LPMM_OK;
     }
-    // Plans with the flat tiling of pass 1 run their pass-1 launches with unused dynamic LDS, so that three instead of
-    // five workgroups share a CU: two waves per SIMD already saturate pass 1 on large tensors, and more of them only
-    // take issue slots and memory queues from the pass 2 that runs beside (measured on the 7B-shaped set: 1 % less
-    // time per step with bf16 gradients, 1-3 % with fp32 gradients; sets of small tensors lose 4 %, so not there).
+    // Plans stepped by phases with the flat tiling run their pass-1 launches with unused dynamic LDS, so that three instead
+    // of five workgroups share a CU: two waves per SIMD already saturate pass 1 on large tensors, and more of them only
+    // take issue slots and memory queues from the pass 2 that runs beside (measured on the 7B-shaped set: 1 % less time per
+    // step with bf16 gradients, 1-3 % with fp32 gradients; sets of small tensors lose 4 %, so not there).
     const unsigned lds_pad = unsigned(std::clamp(env_int("LPMM_P1_LDS_PAD", host->flat ? 22528 : 0), 0, 45056));
     const unsigned pad3 = one_pass_lds_pad(*host);
     // roles: 0 = A and B work in one launch, 1 = A only, 2 = B only, 3 = A only without rank-1 tensors

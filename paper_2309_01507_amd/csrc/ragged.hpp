@@ -1,6 +1,6 @@
-// Pass 1 of the rank-1 step for matrices whose rows are no multiple of 128 elements long (or whose column maxima
-// are not 16-byte aligned).  First-moment blocks are 128 elements of the row-major FLATTENING, so here they start
-// anywhere in a row and may straddle the end of one.
+// Pass 1 of the rank-1 step, and further down both passes of the factorized one, for matrices whose rows are no multiple of
+// 128 elements long (or whose column maxima are not 16-byte aligned).  First-moment blocks are 128 elements of the
+// row-major FLATTENING, so here they start anywhere in a row and may straddle the end of one.
 //
 // What bounds the step is memory, as on the fast path, so the work unit is the fast path's: 32 lanes own one block, 4
 // consecutive elements per lane, and every access is aligned because blocks start at multiples of 128 elements.  A

@@ -25,14 +25,11 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E peak
 # Algorithmic bytes per quantized parameter (every stream touched once per kernel):
-#   pass 1: param read+write 8, grad 4 or 2, m codes read+write 1, v codes read 0.5, block scales
-#           read+write 8/128
-#   pass 2: grad 4 or 2 again, v codes read+write 1
+#   update pass: param read+write 8, grad 4 or 2, both moments' codes read+write 2, block scales read+write 8/128
+#   maxima pass: grad 4 or 2, v codes read 0.5
 def bytes_per_param(bf16: bool):
     g = 2.0 if bf16 else 4.0
-    p1 = 8.0 + g + 1.0 + 0.5 + 8.0 / 128.0
-    p2 = g + 1.0
-    return p1, p2
+    return 8.0 + g + 2.0 + 8.0 / 128.0, g + 0.5
 
 
 # block-wise second moment, one pass: param read+write 8, grad 4 or 2, both moments' codes read+write 2,
@@ -245,7 +242,7 @@ def main():
     ap.add_argument("--deterministic", action="store_true",
                     help="with --second-moment factor: row / column sums in a fixed order instead of float atomics")
     ap.add_argument("--launch", choices=["multi", "per-tensor"], default="multi",
-                    help="multi: one plan, pass 1 / pass 2 of neighbouring tensor groups share launches; "
+                    help="multi: one plan; "
                          "per-tensor: two launches per quantized tensor")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
@@ -299,16 +296,14 @@ def main():
     torch.cuda.synchronize()
     p1_ms, p2_ms, n_calls = lpmm.lpmm_profile_end()
     launches = max(n_calls, 1)
-    if factor and not plans:
+    if not one_pass and not plans:
         p1_ms, p2_ms = p2_ms, p1_ms          # per tensor the statistics pass is recorded first; the update pass dominates
     if plans:
-        # the recorded launches are the pass-1 kernels (pass 1 of a tensor group plus the fp32-state
-        # tensors); pass 2 of the previous group runs beside them on the plan's second stream
-        # (a factorized plan's recorded launches are its update passes; its launches run one after the other on the
-        # caller's stream, and the fp32-state tensors ride with the statistics passes)
-        # (one_launch: the recorded launch is the whole step)
+        # the recorded launches are the update passes; the launches of a plan run one after the other on the caller's stream,
+        # and the fp32-state tensors ride with the maxima / statistics passes (one_launch: the recorded launch is the whole
+        # step; one_pass: the only kernels there are)
         bytes_per_launch = ((bp1 + bp2) * n_quant + small_bytes if one_launch else
-                            (bp1 * n_quant + (0.0 if factor else small_bytes)) * args.steps / launches)
+                            (bp1 * n_quant + (small_bytes if one_pass else 0.0)) * args.steps / launches)
         avg_ms = p1_ms / launches
         achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9
         roofline = {
@@ -316,51 +311,18 @@ def main():
                                        "phase_kernel<roles=3> (the whole block-wise step)" if b128 else
                                        "flow_kernel (both passes)" if one_launch else
                                        "factor_phase_kernel<roles=2> (update pass)" if factor else
-                                       "phase_kernel<roles=1> (pass 1)"),
+                                       "phase_kernel<roles=2> (update pass)"),
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
             "bytes_per_param": bp1 + bp2 if one_launch else bp1, "launches": n_calls, "avg_launch_ms": round(avg_ms, 5),
             "bytes_per_launch": round(bytes_per_launch),
             "traffic_source": None,
             "note": ("one pass: this kernel is the whole step" if one_pass else
-                     "one launch: this kernel is the whole step, pass 2 (%.1f B/param) of a tensor right behind its pass 1; its "
-                     "gradient reads are counted, the ones that the memory-side cache answers among them" % bp2 if one_launch else
-                     "the statistics pass (%.1f B/param) is a launch of its own before it on the same stream; "
-                     "whole-step figures are in config" % bp2 if factor else
-                     "one tensor group: pass 2 (%.1f B/param) is a launch of its own behind it on the same stream; "
-                     "whole-step figures are in config" % bp2 if n_calls == args.steps else
-                     "pass 2 of the neighbouring tensor group (%.1f B/param) runs concurrently and shares "
-                     "the bandwidth; whole-step figures are in config" % bp2),
+                     "one launch: this kernel is the whole step, the maxima / statistics pass (%.1f B/param) of a tensor ahead of "
+                     "its update; what the second reading gets from the memory-side cache is counted" % bp2 if one_launch else
+                     "the maxima / statistics pass (%.1f B/param) is a launch of its own before it on the same stream; "
+                     "whole-step figures are in config" % bp2),
         }
-        if not one_pass and not factor and not one_launch and not args.no_secondary:
-            # The same steps once more with every launch on the caller's stream, one after the other (plans built
-            # under LPMM_MULTI_STREAMS=0): the dominant kernel's rate when it has the chip to itself.  The step as a
-            # whole is slower that way, which is why the timed region above overlaps the passes.
-            os.environ["LPMM_MULTI_STREAMS"] = "0"
-            try:
-                serial = wl.make_plans()
-            finally:
-                del os.environ["LPMM_MULTI_STREAMS"]
-            for _ in range(2):
-                t += 1
-                one_step(t, serial)
-            torch.cuda.synchronize()
-            lpmm.lpmm_profile_begin(max(n_q_tensors, 64) * args.steps)
-            c0 = time.perf_counter()
-            for _ in range(args.steps):
-                t += 1
-                one_step(t, serial)
-            torch.cuda.synchronize()
-            serial_ms = (time.perf_counter() - c0) * 1e3 / args.steps
-            s1_ms, _, s_calls = lpmm.lpmm_profile_end()
-            for pl in serial:
-                lpmm.lpmm_adamw4_plan_release(pl)
-            if s_calls == n_calls and s1_ms > 0:
-                alone = bytes_per_launch / (s1_ms / s_calls * 1e-3) / 1e9
-                roofline["alone"] = {"achieved": round(alone, 1), "frac": round(alone / HBM_PEAK_GBPS, 4),
-                                     "avg_launch_ms": round(s1_ms / s_calls, 5), "ms_per_step": round(serial_ms, 4),
-                                     "note": "same kernels and tiles, every launch on the caller's stream one after "
-                                             "the other: this kernel with the chip to itself (events included in the step time)"}
         # HBM bytes per launch measured offline with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (see profiles/)
         tpath = os.path.join(ROOT, "profiles", "traffic_%s_kernel_%s%s.json" % (
             "flow" if one_launch else "phase", args.config, "_sgdm" if sgdm else "_b128" if b128 else "_factor" if factor else ""))
@@ -374,13 +336,13 @@ def main():
         p1_bytes_per_launch = bp1 * n_quant * args.steps / launches
         achieved = p1_bytes_per_launch / (p1_avg_ms * 1e-3) / 1e9
         roofline = {
-            "bound": "hbm", "kernel": "sgdm4_kernel" if sgdm else "b128_kernel" if b128 else "factor_update_fast" if factor else "pass1_fast",
+            "bound": "hbm", "kernel": "sgdm4_kernel" if sgdm else "b128_kernel" if b128 else "factor_update_fast" if factor else "update_fast",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
             "bytes_per_param": bp1, "launches": n_calls, "avg_launch_ms": round(p1_avg_ms, 5),
             "bytes_per_launch": round(p1_bytes_per_launch),
-            ("statistics_pass" if factor else "pass2"): {"bytes_per_param": bp2, "avg_launch_ms": round(p2_ms / launches, 5),
+            ("statistics_pass" if factor else "maxima_pass"): {"bytes_per_param": bp2, "avg_launch_ms": round(p2_ms / launches, 5),
                       "achieved": round(bp2 * n_quant * args.steps / max(p2_ms, 1e-9) / 1e6, 1)},
         }
 
@@ -473,11 +435,7 @@ def main():
                    "launch": (("multi-tensor plan, %d launches per step" if one_pass else
                                "multi-tensor plan, %d launch per step with both passes in it" if one_launch else
                                "multi-tensor plan, %d update launches per step, each behind its statistics launch "
-                               "on the caller's stream" if factor else
-                               "multi-tensor plan, %d pass-1 launch per step with pass 2 behind it on the caller's stream"
-                               if n_calls == args.steps else
-                               "multi-tensor plan, %d pass-1 launches per step on the caller's stream, "
-                               "pass 2 on a second stream") % (n_calls // max(args.steps, 1)))
+                               "on the caller's stream") % (n_calls // max(args.steps, 1)))
                    if has_plans else "per-tensor, %d kernel%s per quantized tensor" % ((1, "") if one_pass else (2, "s")),
                    "kernels_per_step": kernels_per_step,
                    "hbm_gbps_one_touch_floor": round(floor_gbps, 1),

@@ -1,14 +1,13 @@
 // One launch for a whole plan step.
 //
-// The rank-1 and the factorized step read every gradient twice, once per pass (2 or 4 of their 13 to 19 bytes per
-// parameter).  As launches of their own the passes of a large group are gigabytes apart and the second reading comes from
-// HBM.  Here both passes of all tensors are ONE launch whose work list (built with the plan) puts pass 2 of a tensor a
-// little behind its pass 1: the gradient and the codes of a tensor of a few million parameters are then still in the
-// memory-side cache, whose reads cost nothing beside the HBM traffic of the following tensors' pass 1.  (Probe without
-// arithmetic: an in-place stream of 8 GB takes 1.575 ms, with 4.3 GB of re-reads from a region of at most 128 MB beside it
-// 1.58, from HBM 2.26; pass 1's and pass 2's streams over 2^31 parameters in tensors of at most 8.4 M 4.98 ms, of 50 M 5.2, of
-// 134 M 5.65, the same as by phases.)  It also spares the step the starts and the tails of its launches, and tiles of unequal
-// cost do not leave XCDs idle.
+// The rank-1 and the factorized step read every gradient twice, once per pass (2 or 4 of their 13 to 19 bytes per parameter).
+// As launches of their own the passes of a large group are gigabytes apart and the second reading comes from HBM.  Here both
+// passes of all tensors are ONE launch whose work list (built with the plan) puts the first pass of a tensor, which only reads
+// gradients and codes and leaves its statistics, a little ahead of its second one, which does everything else: what the first
+// one read is still in the memory-side cache then, where the parameters' streams leave no trace (non-temporal).  (Probe without
+// arithmetic, 2^31 parameters with bf16 gradients: second passes alone 3.98 ms, first ones 0.83, both in turn 4.10 to 4.43 for
+// tensors of 2^22 to 2^26, 4.67 for 2^27; the update first and the codes 2^23 parameters behind 4.83.)  It also spares the step
+// the starts and the tails of its launches, and tiles of unequal cost do not leave XCDs idle.
 //
 // Order inside the launch.  Pass 2 of a tensor needs its complete maxima (sums): a workgroup of pass 1 waits for its own
 // atomics and then raises the tensor's count, a workgroup of pass 2 polls that count.  Workgroups are started in the order
@@ -24,6 +23,8 @@
 // parameters are read and written by one workgroup each per pass; pass 2 overwrites codes that pass 1 of the tensor has
 // finished reading.
 #pragma once
+
+#include <type_traits>
 
 #include "launch.hpp"
 
@@ -123,43 +124,57 @@ __device__ __forceinline__ void flow_drain() {
     __syncthreads();
 }
 
-template <bool BF16, bool FACTOR>
-__global__ __launch_bounds__(kThreads) void flow_kernel(const FlowArgs f, const HyperArg ha) {
-    __shared__ Lds s;
+// FORM: which tensors the plan has.  Rank-1 plans without ragged matrices and without rows shorter than 128 elements take
+// a kernel of their own: with the tiles of those in it, it needs 128 registers in place of 96, four waves on a SIMD in place
+// of five.  (Launch bounds: at 80 registers and six waves the plain form spills, 8 llama-like layers 4.44 ms, 4.27 at five,
+// 4.31 at four; the other form at 96 registers 597 us for rows of 1088, 576 at 128.)
+enum { kFlowFactor = 0, kFlowRank1 = 1, kFlowRank1Any = 2 };
+template <bool BF16, int FORM>
+__global__ __launch_bounds__(kThreads, FORM == kFlowRank1 ? 5 : FORM == kFlowRank1Any ? 4 : 6) void flow_kernel(const FlowArgs f, const HyperArg ha) {
+    constexpr bool FACTOR = FORM == kFlowFactor;
+    constexpr bool kAny = FORM == kFlowRank1Any;
+    __shared__ std::conditional_t<FACTOR, Lds, LdsRank1> s;
     __shared__ int s_flag;
-    const Hyper h = resolve(ha);
-    const FlowItem it = f.items[blockIdx.x];
+    // what lies in LDS differs from lane to lane as far as the compiler knows: say that it does not, so that branches on it
+    // are scalar and what the tiles address with stays in scalar registers
+    auto flag = [&] { return __builtin_amdgcn_readfirstlane(s_flag) != 0; };
+    const Constant<FlowItem> item = as_constant(f.items + blockIdx.x);
+    const FlowItem it{item->what, item->wg};
     if (it.what < 0) return;
     const bool second = it.what & kFlowSecond;
-    const Tensor4 a = from_table(f.tensors[it.what & (kFlowSecond - 1)]);
-    const Hyper ht = for_tensor(h, a);
-    const bool nd = !FACTOR && a.nd_index >= 0 && a.kind != kFp32State && a.kind != kQuantBlockV;
-    const unsigned int target = lanes_used(unsigned(a.n_wg)) + (nd ? 1u : 0u);
+    // Read again wherever it is needed, not kept: a tile needs most of the scalar registers for itself.
+    auto tensor = [&] {
+        Constant<Tensor4Table> entry = as_constant(f.tensors + (it.what & (kFlowSecond - 1)));
+        asm volatile("" : "+s"(entry));
+        return from_table(*entry);
+    };
+    auto is_nd = [](const Tensor4& a) { return !FACTOR && a.nd_index >= 0 && a.kind != kFp32State && a.kind != kQuantBlockV; };
 
     if (!second) {
-        if (a.kind == kFp32State) {
-            adamw32_tile<BF16>(a.p, a.g, reinterpret_cast<float*>(a.mq), reinterpret_cast<float*>(a.vq), a.P, ht, it.wg);
-            return;
-        }
-        if (a.kind == kQuantBlockV) {
-            b128_work<BF16>(a, ht, it.wg, s);
-            return;
-        }
-        if constexpr (FACTOR) {
-            if (a.kind == kFactorFast) factor_stats_tile<BF16>(a, it.wg, s);
-            else factor_stats_general_tile<BF16>(a, it.wg, a.n_wg, s);
-        } else {
-            if (a.kind == kQuantFast) {
-                if (a.flat) pass1_flat_tile<BF16>(a, ht, it.wg, s);
-                else pass1_fast_tile<BF16>(a, ht, it.wg, s);
-            } else if (a.kind == kQuantRagged) {
-                pass1_ragged<BF16>(a, ht, it.wg, s);
+        {
+            const Tensor4 a = tensor();
+            const Hyper h = for_tensor(resolve(ha), a);
+            if (a.kind == kFp32State) {
+                adamw32_tile<BF16>(a.p, a.g, reinterpret_cast<float*>(a.mq), reinterpret_cast<float*>(a.vq), a.P, h, it.wg);
+                return;
+            }
+            if (a.kind == kQuantBlockV) {
+                b128_work<BF16>(a, h, it.wg, s);
+                return;
+            }
+            if constexpr (FACTOR) {
+                if (a.kind == kFactorFast) factor_stats_tile<BF16>(a, it.wg, s);
+                else factor_stats_general_tile<BF16>(a, it.wg, a.n_wg, s);
             } else {
-                pass1_general_tile<BF16>(a, ht, it.wg, s);
+                if (!kAny || a.kind == kQuantFast) maxima_tile<BF16>(a, h, it.wg, s);
+                else if (a.kind == kQuantRagged) maxima_ragged<BF16>(a, h, it.wg, s);
+                else pass1_general_tile<BF16>(a, h, it.wg, s);
             }
         }
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);          // the maxima and sums have been sent: count this workgroup
+        const Tensor4 a = tensor();
         if (!last_to_arrive(flow_done(a), unsigned(it.wg), unsigned(a.n_wg), s_flag)) return;
+        const bool nd = is_nd(a);
         if (nd) {
             flow_nd(a, f.dims[a.nd_index], s);
             flow_drain();
@@ -170,70 +185,105 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const FlowArgs f, const 
             s_flag = atomicAdd(flow_word(a, kFlowFinal), 1u) == 1u;
         }
         __syncthreads();
-        if (!s_flag) return;
+        if (!flag()) return;
     }
     // Second pass: this workgroup's tile if it is one of that pass, and, in the workgroup that finishes the tensor, the
     // tiles that were deferred.
     int wg = it.wg, n_left = 0;
     bool mine = second;
-    int* deferred = f.deferred + a.deferred;
     // the same value in every lane: say so, the tile functions address through scalar registers
-    auto n_deferred = [&] { return __builtin_amdgcn_readfirstlane(int(flow_peek(flow_word(a, kFlowDeferred)))); };
-    auto take = [&](int k) {
-        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(deferred + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    auto n_deferred = [&](const Tensor4& a) { return __builtin_amdgcn_readfirstlane(int(flow_peek(flow_word(a, kFlowDeferred)))); };
+    auto take = [&](const Tensor4& a, int k) {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(f.deferred + a.deferred + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     };
     if (!second) {
-        n_left = n_deferred();
-        if (n_left > 0) wg = take(n_left - 1);
+        const Tensor4 a = tensor();
+        n_left = n_deferred(a);
+        if (n_left > 0) wg = take(a, n_left - 1);
     }
     while (mine || n_left > 0) {
-        // polls for the tensor's first pass (a deferred tile's is complete); the same answer in every thread
-        auto ready = [&]() -> bool {
-            if (!mine) return true;
-            if (threadIdx.x == 0) {
-                int ok = 0;
-                for (int k = 0; k <= f.spin_limit; ++k) {
-                    ok = flow_peek(flow_done(a)) == target;
-                    if (ok) break;
-                    __builtin_amdgcn_s_sleep(64);
+        // ready(): the tensor's first pass is complete (a deferred tile's is); the same answer in every thread.  It usually is long
+        // before, and the word read when the tile began says so; only else it is polled.
+        struct Sync {
+            const Tensor4& a;
+            const FlowArgs& f;
+            int& s_flag;
+            const bool mine;
+            const int wg;
+            const unsigned int target, early;
+            bool done = true;
+            unsigned int ticket = 0u;
+            __device__ __forceinline__ bool ready() {
+                if (!mine || __syncthreads_and(int(early == target))) return true;
+                if (threadIdx.x == 0) {
+                    int ok = 0;
+                    for (int k = 0; k <= f.spin_limit; ++k) {
+                        ok = flow_peek(flow_done(a)) == target;
+                        if (ok) break;
+                        __builtin_amdgcn_s_sleep(64);
+                    }
+                    s_flag = ok;
                 }
-                s_flag = ok;
+                __syncthreads();
+                done = __builtin_amdgcn_readfirstlane(s_flag) != 0;
+                return done;
             }
-            __syncthreads();
-            return s_flag != 0;
+            __device__ __forceinline__ void staged() {
+                if (mine) ticket = take_ticket(a.counter, unsigned(wg));
+            }
         };
-        if constexpr (FACTOR) {
-            if (a.kind == kFactorFast) {
-                factor_update_tile<BF16, true>(a, ht, wg, s, ready);
-            } else if (ready()) {
-                load_tables(s);
-                factor_update_general_tile<BF16, true>(a, ht, wg, s);
+        unsigned int ticket;
+        bool done;
+        {
+            const Tensor4 a = tensor();
+            const Hyper h = for_tensor(resolve(ha), a);
+            Sync sync{a, f, s_flag, mine, wg, lanes_used(unsigned(a.n_wg)) + (is_nd(a) ? 1u : 0u), flow_peek(flow_done(a))};
+            auto behind = [&](auto tile) {                // tiles that read the statistics all along
+                if (!sync.ready()) return;
+                tile();
+                __syncthreads();
+                sync.staged();
+            };
+            if constexpr (FACTOR) {
+                if (a.kind == kFactorFast) factor_update_tile<BF16, true>(a, h, wg, s, sync);
+                else behind([&] {
+                    load_tables(s);
+                    factor_update_general_tile<BF16, true>(a, h, wg, s);
+                });
+            } else {
+                if (!kAny || a.kind == kQuantFast) update_tile<BF16, true>(a, h, wg, s, sync);
+                else if (a.kind == kQuantRagged) update_ragged<BF16, true>(a, h, wg, s, sync);
+                else behind([&] { pass2_general_chunk<BF16, true>(a, h, int64_t(wg) * kGenChunkElems); });
             }
-        } else {
-            if (a.kind == kQuantFast) pass2_tile<BF16, false, true>(a, h, wg, ready, s);
-            else if (a.kind == kQuantRagged) pass2_ragged<BF16, true>(a, h, wg, ready, s);
-            else if (ready()) pass2_general_chunk<BF16, true>(a, h, int64_t(wg) * kGenChunkElems);
+            ticket = sync.ticket;
+            done = sync.done;
         }
+        const Tensor4 a = tensor();
         if (mine) {
             mine = false;
-            if (!s_flag && threadIdx.x == 0) {
-                const unsigned int k = atomicAdd(flow_word(a, kFlowDeferred), 1u);
-                __hip_atomic_store(deferred + k, wg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+            if (!done) {
+                if (threadIdx.x == 0) {
+                    const unsigned int k = atomicAdd(flow_word(a, kFlowDeferred), 1u);
+                    __hip_atomic_store(f.deferred + a.deferred + k, wg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+                }
+                ticket = take_ticket(a.counter, unsigned(wg));
             }
-            if (!last_to_arrive(a.counter, unsigned(wg), unsigned(a.n_wg2), s_flag)) return;
+            if (!ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), ticket, s_flag)) return;
             __syncthreads();                              // every wave has read the flag before it is written again
             if (threadIdx.x == 0) s_flag = atomicAdd(flow_word(a, kFlowFinal), 1u) == 1u;
             __syncthreads();
-            if (!s_flag) return;
-            n_left = n_deferred();
+            if (!flag()) return;
+            n_left = n_deferred(a);
         } else {
             --n_left;
             __syncthreads();                              // LDS of the tile just done is free again
         }
-        if (n_left > 0) wg = take(n_left - 1);
+        if (n_left > 0) wg = take(a, n_left - 1);
     }
+    const Tensor4 a = tensor();
     if constexpr (FACTOR) {
+        const Hyper h = resolve(ha);
         ema_and_clear<true>(h, a.r, a.r_new, a.rows);
         ema_and_clear<true>(h, a.c, a.c_new, a.cols);
         if (int(threadIdx.x) < a.tot_slots) {
@@ -241,8 +291,7 @@ __global__ __launch_bounds__(kThreads) void flow_kernel(const FlowArgs f, const 
             a.counter[tot_old_word(threadIdx.x)] = 0u;
         }
     } else {
-        move_and_clear<true>(a.r, a.r_new, a.rows);
-        move_and_clear<true>(a.c, a.c_new, a.cols + a.c_extra);
+        move_statistics<true>(a);
     }
     if (threadIdx.x == 0) {
         *a.counter = 0u;

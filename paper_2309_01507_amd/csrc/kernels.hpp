@@ -6,12 +6,14 @@
 //
 // One step is two passes, because every v code needs the complete row and column maxima of the
 // updated second moment (rank-1 normalization, paper Sec. 4.2):
-//   pass 1: decompress m, v -> Adam moments (Eq. 1) -> parameter update -> block absmax of m_t,
-//           compress m_t (B128 + signed dynamic-exponent map) -> row/column maxima of v_t into
-//           the workspace (LDS combine, then integer atomic max on the float bits).
-//   pass 2: recompute v_t with the identical operation sequence, compress it against
-//           min(r'_i, c'_j) (Linear map), and let the last workgroup publish r', c' as the new
-//           state and clear the workspace.
+//   first pass:  decompress v -> v_t (Eq. 1) -> row/column maxima of v_t into the workspace (LDS combine, then integer
+//                atomic max on the float bits).  It reads the gradient and the codes, 2.5 or 4.5 bytes per parameter.
+//   second pass: decompress m, v -> Adam moments -> parameter update -> block absmax of m_t, compress m_t (B128 + signed
+//                dynamic-exponent map), compress v_t against min(r'_i, c'_j) (Linear map); the last workgroup publishes
+//                r', c' as the new state and clears the workspace.
+// (The other way about -- the update first, then the codes of v -- moves the same bytes, but leaves the gradient of a
+// tensor behind 11.6 bytes per parameter of other traffic instead of 2.5, out of reach of the memory-side cache; it
+// stays for rows shorter than 128 elements, the general path.)
 // For 1-dimensional or flattened tensors the second moment is block-wise like the first (Sec. 4.2,
 // last paragraph); then nothing crosses a block and the step is ONE pass (b128_*).  The same one-pass
 // code without a second moment is SGD with momentum (App. E Alg. 2).  With a factorized second
@@ -19,8 +21,7 @@
 // with more than two dimensions (App. F Alg. 4, nd_*) run the two matrix passes on derived column scales.
 // The bodies are "tile" functions, here and (rows that are no multiple of 128 elements) in ragged.hpp.  Thin __global__
 // wrappers run them for one tensor (two launches per step, one for the block-wise form); for many tensors they run from a
-// work list in one launch with pass 2 of a tensor behind its pass 1 (flow.hpp), or by phases, pass 1 of one set of tensors
-// next to pass 2 of the previous set (launch.hpp).
+// work list in one launch with the first pass of a tensor ahead of its second one (flow.hpp), or by phases (launch.hpp).
 #pragma once
 
 #include <cstddef>
@@ -30,8 +31,8 @@
 namespace lpmm {
 
 // Lookup tables, uploaded once per device at init.
-__device__ float d_byte_decode[512];          // entry b: {T_DE[b & 15], T_DE[b >> 4]}
-__device__ SearchEntry d_search[kBucketsPadded];    // nearest-entry search for the DE map
+__device__ __align__(16) float d_byte_decode[512];          // entry b: {T_DE[b & 15], T_DE[b >> 4]}
+__device__ __align__(16) SearchEntry d_search[kBucketsPadded];    // nearest-entry search for the DE map
 
 enum TensorKind : int { kQuantFast = 0, kQuantGeneral = 1, kFp32State = 2, kQuantBlockV = 3, kFactorFast = 4, kFactorGeneral = 5,
                         kSgdmBlock = 6, kSgdmFp32 = 7, kQuantRagged = 8, kFactorRagged = 9 };
@@ -48,26 +49,23 @@ struct Tensor4 {
     float* c_new;           // workspace: column maxima of v_t (zero between steps)   (kFactor*: column sums of g^2)
     unsigned int* counter;  // workspace: ticket counters of pass 2 (zero between steps); kFactor*: also two float sums
     int64_t rows, cols, P;
-    // geometry of the fast path (cols % 128 == 0)
+    // second pass (update) of the fast path (cols % 128 == 0)
     int nb;                 // column blocks per row = cols / 128    (kQuantBlockV: whole blocks of the tensor)
-    int gx, gy;             // a workgroup's 8 groups: gx column blocks x gy row phases
+    int gx, gy;             // kQuantFast: column blocks of a strip; kFactorFast: a workgroup's 8 groups are gx blocks x gy rows
     int rw;                 // rows per workgroup tile; rw * cols < 2^29   (kQuantBlockV, kSgdmBlock: blocks a group takes in
                             // a row; general path: chunks of 2048 elements a workgroup of the first pass takes;
-                            // kQuantRagged: blocks of a tile if strips == 1, else rows of a tile, both passes)
-    int strips;             // nb / gx
-    int n_wg;               // workgroups of pass 1 (kQuantBlockV, kSgdmBlock: of the step;
-                            // kFactor*: of the statistics pass, which is tiled like pass 2)
+                            // *Ragged: blocks of a tile if strips == 1, else rows of a tile)
+    int strips;             // strips of gx blocks
+    int n_wg;               // workgroups of the first pass (kQuantBlockV, kSgdmBlock: of the step)
     int kind;
-    // pass 2 of the fast path has its own tiling: strips of 256 columns, rw2 rows per workgroup
+    // first pass (maxima or sums): strips of 256 columns, rw2 rows per workgroup
     int strips2;            // ceil(nb / 2)
     int rw2;                // rw2 * cols < 2^29
-    int n_wg2;              // workgroups of pass 2                 (kQuantBlockV: workgroups on whole blocks;
-                            // kFactor*: of the update pass, which is tiled like pass 1)
-    // log2 of the row spacing of pass 1 / pass 2: the 2^rs (2^rs2) rows that a group (a wave) takes in a
-    // row are consecutive, and the groups (waves) that run side by side are 2^rs rows apart
+    int n_wg2;              // workgroups of the second pass        (kQuantBlockV: workgroups on whole blocks)
+    // log2 of the row spacing of the second / first pass: the groups (waves) that run side by side are 2^rs (2^rs2)
+    // rows apart
     int rs, rs2;
     int tot_slots;          // kFactor*: slots that each of the two float sums is spread over (1, 2, 4 or 8)
-    int flat;               // kQuantFast: pass 1 uses the flat tiling (a group walks along a row)
     int no_decay;           // plans: this tensor takes no weight decay
     int c_extra;            // floats behind c_new (and room behind c) that the publishing workgroup moves and clears
                             // along with the column maxima (tensors with more than two dimensions)
@@ -77,6 +75,7 @@ struct Tensor4 {
                             // then float[tiles][round_up(cols, 64)] per row tile and column
     int sw;                 // kQuantRagged: columns of a strip
     int deferred;           // plans stepped in one launch: the tensor's first entry in the list of deferred tiles
+    int skew, skew2;        // logical_wg's skew for the workgroups of the first and of the second pass
 };
 
 // The tensor table of a plan lives in device memory.  A pointer read from memory is a generic
@@ -98,10 +97,11 @@ struct Tensor4Table {
     float LPMM_AS_GLOBAL* c_new;
     unsigned int LPMM_AS_GLOBAL* counter;
     int64_t rows, cols, P;
-    int nb, gx, gy, rw, strips, n_wg, kind, strips2, rw2, n_wg2, rs, rs2, tot_slots, flat, no_decay, c_extra, nd_index, det, sw, deferred;
+    int nb, gx, gy, rw, strips, n_wg, kind, strips2, rw2, n_wg2, rs, rs2, tot_slots, no_decay, c_extra, nd_index, det, sw, deferred, skew, skew2;
 };
 static_assert(sizeof(Tensor4Table) == sizeof(Tensor4), "the table twin must mirror Tensor4");
-__device__ __forceinline__ Tensor4 from_table(const Tensor4Table& t) {
+template <class T>
+__device__ __forceinline__ Tensor4 from_table(const T& t) {
     Tensor4 a;
     a.p = (float*)t.p;
     a.g = (const void*)t.g;
@@ -116,7 +116,7 @@ __device__ __forceinline__ Tensor4 from_table(const Tensor4Table& t) {
     a.rows = t.rows; a.cols = t.cols; a.P = t.P;
     a.nb = t.nb; a.gx = t.gx; a.gy = t.gy; a.rw = t.rw; a.strips = t.strips; a.n_wg = t.n_wg; a.kind = t.kind;
     a.strips2 = t.strips2; a.rw2 = t.rw2; a.n_wg2 = t.n_wg2; a.rs = t.rs; a.rs2 = t.rs2;
-    a.tot_slots = t.tot_slots; a.flat = t.flat; a.no_decay = t.no_decay; a.c_extra = t.c_extra; a.nd_index = t.nd_index; a.det = t.det; a.sw = t.sw; a.deferred = t.deferred;
+    a.tot_slots = t.tot_slots; a.no_decay = t.no_decay; a.c_extra = t.c_extra; a.nd_index = t.nd_index; a.det = t.det; a.sw = t.sw; a.deferred = t.deferred; a.skew = t.skew; a.skew2 = t.skew2;
     return a;
 }
 #else
@@ -124,15 +124,37 @@ typedef Tensor4 Tensor4Table;
 __host__ __device__ inline Tensor4 from_table(const Tensor4& t) { return t; }   // host pass: only parsed, never run
 #endif
 
+// A pointer to memory that nothing writes while the kernel runs, typed so that the compiler reads it through the scalar cache
+// wherever the address is uniform -- also behind stores, where it would take a vector load and vector registers otherwise.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class T> using Constant = const T __attribute__((address_space(4)))*;
+template <class T> __device__ __forceinline__ Constant<T> as_constant(const T* p) { return (Constant<T>)(p); }
+#else
+template <class T> using Constant = const T*;
+template <class T> __device__ __forceinline__ Constant<T> as_constant(const T* p) { return p; }
+#endif
+
 constexpr int kThreads = 256;
 constexpr int kXcds = 8;
 constexpr int kElemsPerWg32 = kThreads * 16;   // fp32-state path: elements per workgroup
 
 // Workgroups are dealt to the 8 XCDs round-robin by their id.  Remap so that consecutive logical
-// ids -- which touch neighbouring memory -- run on the same XCD and share its L2.
-__device__ __forceinline__ int logical_wg() {
-    const int per_xcd = gridDim.x / kXcds;   // the grid is padded to a multiple of 8
-    return (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
+// ids -- which touch neighbouring memory -- run on the same XCD and share its L2: XCD x works through the x-th eighth.
+// It does not begin at its eighth's start but x * skew workgroups behind it, and comes to the start last: the XCDs keep pace
+// with each other, and eight streams at equal distances that are a multiple of a large power of two get in each other's way
+// in the memory system.  skew: the workgroups of 2^19 elements (2 MiB of parameters).  Block-wise step of 2^25, 2^26 and 2^27
+// elements 5.72, 6.05 and 6.58 TB/s with skew 0, 6.15, 6.62, 6.80 with half of it, 6.43, 6.80, 6.92 with it, 6.45, 6.80, 6.94
+// with the double; sizes whose eighths lie at other distances are the same with and without (45 M elements 6.45 / 6.49).
+constexpr int64_t kSkewElems = int64_t(1) << 19;
+__device__ __forceinline__ int skewed(int x, int i, int per_xcd, int skew) {
+    return x * per_xcd + int((unsigned(i) + unsigned(x) * unsigned(skew)) % unsigned(per_xcd));
+}
+// skew < 0: workgroups of very unequal cost, dealt to the XCDs in runs of kDealRun instead (the grid: a multiple of 8 of them).
+constexpr int kDealRun = 32;
+__device__ __forceinline__ int logical_wg(int skew) {
+    const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
+    if (skew < 0) return (i / kDealRun * kXcds + x) * kDealRun + i % kDealRun;
+    return skewed(x, i, gridDim.x / kXcds, skew);   // the grid is padded to a multiple of 8
 }
 
 constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0) only: expcnt and lgkmcnt fields at their maxima
@@ -140,11 +162,11 @@ constexpr int kMaxRowSlots = 512;    // rows of a pass-1 tile x column blocks of
 
 constexpr int kColSlots = 9 * 128;   // columns of a strip; a ragged strip's last block may reach 127 columns beyond it
 
-struct Lds {
+struct alignas(16) Lds {
     float2 deq[256];
     SearchEntry search[kBucketsPadded];
     float col[kColSlots];
-    float cold[kColSlots];      // flat tiling of pass 1: the strip's old column maxima / 16
+    float cold[kColSlots];      // update tiles: the strip's old column maxima / 16
     // per row and column block of the tile: new block scale of m and the block's maximum of v_t.
     // They leave for global memory at the end of the tile, so that the row loop issues the same
     // memory instructions on every path (loads, the parameter store, the code store) and nothing
@@ -152,13 +174,31 @@ struct Lds {
     float blk_scale[kMaxRowSlots];
     float blk_vmax[kMaxRowSlots];
 };
+struct LdsRank1 : Lds {         // second pass of the rank-1 step
+    float cnew[kColSlots];      // the strip's new column maxima (s.col: 16 / them, approximately)
+};
 
+// The lookup tables on their way to LDS: requested first and put down once the rest of a tile's start-up has been requested,
+// too, so that a workgroup waits for one round trip and not for one per loop iteration.
+struct TableRegs { uint4 deq, search, rest; };
+constexpr int kDeqQuads = 512 / 4, kSearchQuads = kBucketsPadded / 2;
+static_assert(kDeqQuads <= kThreads && kSearchQuads <= 2 * kThreads && kBucketsPadded % 2 == 0, "one thread, one 16-byte piece");
+__device__ __forceinline__ TableRegs request_tables() {
+    TableRegs r{};
+    const int t = threadIdx.x;
+    if (t < kDeqQuads) r.deq = reinterpret_cast<const uint4*>(d_byte_decode)[t];
+    r.search = reinterpret_cast<const uint4*>(d_search)[t];
+    if (t < kSearchQuads - kThreads) r.rest = reinterpret_cast<const uint4*>(d_search)[kThreads + t];
+    return r;
+}
+__device__ __forceinline__ void put_tables(Lds& s, const TableRegs& r) {       // the caller's barrier publishes them
+    const int t = threadIdx.x;
+    if (t < kDeqQuads) reinterpret_cast<uint4*>(s.deq)[t] = r.deq;
+    reinterpret_cast<uint4*>(s.search)[t] = r.search;
+    if (t < kSearchQuads - kThreads) reinterpret_cast<uint4*>(s.search)[kThreads + t] = r.rest;
+}
 __device__ __forceinline__ void load_tables(Lds& s) {
-    const float2* gd = reinterpret_cast<const float2*>(d_byte_decode);
-    for (int i = threadIdx.x; i < 256; i += kThreads) s.deq[i] = gd[i];
-    const uint2* gs = reinterpret_cast<const uint2*>(d_search);
-    uint2* ss = reinterpret_cast<uint2*>(s.search);
-    for (int i = threadIdx.x; i < kBucketsPadded; i += kThreads) ss[i] = gs[i];
+    put_tables(s, request_tables());
     __syncthreads();
 }
 
@@ -190,6 +230,7 @@ constexpr int kRawBufferWord3 = 0x00020000;     // untyped 32-bit data format, n
 typedef uint32_t v2u_t __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 constexpr int kPolicyNt = 2;
+constexpr uint32_t kNowhere = 0x7FFFFF00u;      // a byte offset beyond every tile (also after >> 1 and >> 3)
 __device__ __forceinline__ Rsrc tile_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kRawBufferWord3);
 }
@@ -211,9 +252,6 @@ __device__ __forceinline__ uint2 buf_ld_u2(Rsrc r, uint32_t off) {
 // value directly behind the load, and with it a wait for a row that was only just requested.
 __device__ __forceinline__ uint16_t buf_ld_u16(Rsrc r, uint32_t off) {
     return uint16_t(__builtin_amdgcn_raw_buffer_load_b16(r, int(off), 0, 0));
-}
-__device__ __forceinline__ float buf_ld_f(Rsrc r, uint32_t off) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, int(off), 0, 0));
 }
 
 template <typename T>
@@ -307,7 +345,7 @@ struct Geo {            // where this group works
 // most rows in a cut-off tile -- so the loop counter and everything derived from it stay in scalar registers; a group
 // whose row lies behind the tile's end reads zeros (with zero scales: see the tiles) and its stores are dropped by the
 // bounds check.  With a loop bound of its own per group the counter was a vector value and index arithmetic a fifth of
-// pass 1's vector instructions (three 32-bit multiplications per unit in the flat tiling).
+// the vector instructions.
 struct RowWalk {
     int rs, hop;        // hop = groups << rs
     __device__ __forceinline__ int at(int k) const { return (k & ((1 << rs) - 1)) + (k >> rs) * hop; }
@@ -343,7 +381,7 @@ struct TileBase {
     const float* r;
     float* r_new;
     // the same arrays as bounds-checked resources of n_rows rows, for the loads and the row stores
-    Rsrc rp, rg, rmq, rvq, rr, rr_new;
+    Rsrc rp, rg, rmq, rvq;
 };
 
 template <bool BF16>
@@ -362,8 +400,6 @@ __device__ __forceinline__ TileBase tile_base(const Tensor4& a, int64_t row0, in
     b.rg = tile_rsrc(b.g, elems * (BF16 ? 2u : 4u));
     b.rmq = tile_rsrc(b.mq, elems >> 1);
     b.rvq = tile_rsrc(b.vq, elems >> 1);
-    b.rr = tile_rsrc(b.r, uint32_t(n_rows) * 4u);
-    b.rr_new = tile_rsrc(b.r_new, uint32_t(n_rows) * 4u);
     return b;
 }
 
@@ -373,7 +409,7 @@ __device__ __forceinline__ void load4(const float* p, float out[4]) {
 }
 
 template <bool BF16>
-struct Row1 {                      // everything pass 1 prefetches for one row of one lane
+struct Row1 {                      // everything the second pass prefetches for one unit of one lane
     float4 p;
     GradRegs4<BF16> g;
     uint16_t mq, vq;               // the lane's 4 codes of each moment
@@ -437,298 +473,137 @@ __device__ __forceinline__ uint32_t compress_m4(const SearchEntry* s_search, con
     return q;
 }
 
-// One row of pass 1 for one lane: `cur` holds what was loaded from byte offset `off4` of the tile, `slot` is the place of
-// the row's and the block's staged scales.
-template <bool BF16, class Mid>
-__device__ __forceinline__ void pass1_row(const Tensor4& a, const Hyper& h, const TileBase& tb, const Geo& geo,
-                                          Lds& s, const Row1<BF16>& cur, uint32_t off4, int slot, const float cold16[4],
-                                          bool tame, float cmax[4], Mid mid) {
-    float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
-    float g[4];
-    unpack_grad4<BF16>(cur.g, g);
-    float mt[4], vt[4], amax = 0.0f, rmax = 0.0f;
-    const float s_old = s.blk_scale[slot], r_old = s.blk_vmax[slot];     // staged by the tile
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const float2 t = s.deq[(uint32_t(cur.mq) >> (8 * k)) & 255u];
-        mt[2 * k] = t.x * s_old;              // decompress: T_DE[code] * block scale
-        mt[2 * k + 1] = t.y * s_old;
-    }
-    if (__builtin_expect(tame, 1)) {                                      // no old scale of the tile is extreme
-        float qf[4];
-        codes_to_float4(cur.vq, qf);
-        const float r16 = r_old * 0.0625f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(r16, cold16[e]));
-    } else {
-        float cold[4];
-        load4(a.c + geo.col0, cold);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vt[e] = dequant_v((uint32_t(cur.vq) >> (4 * e)) & 15u, fminf(r_old, cold[e]));
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        mt[e] = moment_m(h, mt[e], g[e]);
-        vt[e] = moment_v(h, vt[e], g[e]);
-        w[e] = param_update(h, w[e], mt[e], vt[e]);
-        amax = fmaxf(amax, fabsf(mt[e]));
-        rmax = max_nonneg(rmax, vt[e]);
-        cmax[e] = max_nonneg(cmax[e], vt[e]);
-    }
-    // the caller's prefetch of a later row is issued here, in the middle of the row's arithmetic:
-    // by now the previous row's stores have been acknowledged, and loads queue behind older stores
-    __builtin_amdgcn_sched_barrier(0);
-    mid();
-    __builtin_amdgcn_sched_barrier(0);
-    const float s_new = group32_allmax(amax);     // block absmax of m_t
-    rmax = group32_allmax(rmax);
+constexpr int kFlatBlocks = 8;             // column blocks of an update tile's strip at most
 
-    store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
-    if (geo.l == 0) {
-        s.blk_scale[slot] = s_new;
-        s.blk_vmax[slot] = rmax;
-    }
-}
+// ---- first pass: row and column maxima of v_t ------------------------------------------------------------------------
+// A workgroup takes a strip of 256 columns of rw2 rows.  A group's 32 lanes take 8 consecutive columns each of one row,
+// so a row costs a lane one 4-byte load of codes and one or two 16-byte loads of the gradient.  Column maxima stay in
+// registers down the tile, row maxima go through LDS; one atomic per row and column of the tile follows at its end.
+template <bool BF16>
+struct Row8 {
+    float4 g[BF16 ? 1 : 2];
+    uint32_t vq;
+};
 
 template <bool BF16>
-__device__ __forceinline__ void pass1_fast_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
-    const Geo geo = geometry(a, wg);
-    const TileBase tb = tile_base<BF16>(a, geo.row0, geo.n_rows);
-    float cmax[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-
-    // Rows of this group, in the order it takes them: (gyi << rs) + walk(k) with S = 2^rs.  With S = 1 these are gyi,
-    // gyi + gy, ...; in general the gy groups that work side by side are S rows apart.  The memory system likes the rows
-    // in flight at one time to lie 32 KiB apart (measured: up to 10 % more bandwidth than neighbouring rows for
-    // 4096-column tensors, whose rows are 16 KiB long), so the host picks S to make S rows a multiple of 32 KiB where it can.
-    // The loads of two rows are in flight while a third is computed (three register sets take turns, the loop is unrolled
-    // by three); the prefetch is unconditional, rows past the tile come back as zeros and are never used.
-    const RowWalk walk{a.rs, a.gy << a.rs};
-    const int n = walk.rounds(geo.n_rows);
-    const uint32_t lane4 = row_offset(geo.gyi << a.rs, a.cols, geo.col0) * 4u, pitch4 = uint32_t(a.cols) * 4u;
-    const int slot0 = (geo.gyi << a.rs) * a.gx + geo.gxi;
-    auto off = [&](int k) { return lane4 + uint32_t(walk.at(k)) * pitch4; };      // rows of the tile: below 2^31
-    auto fetch = [&](int k) { return load_row1<BF16>(tb, off(k)); };
-    Row1<BF16> r0 = fetch(0);
-    Row1<BF16> r1 = fetch(1);
-    Row1<BF16> r2;
-    // old block scales and old row maxima of the tile into the slots of the new ones, zeros for rows behind its end
-    bool lane_tame = true;
-    for (int t = threadIdx.x; t < a.rw * a.gx; t += kThreads) {
-        const int il = t / a.gx, cbi = geo.strip * a.gx + t % a.gx;
-        const bool in = il < geo.n_rows;
-        const float r = in ? tb.r[il] : 0.0f;
-        s.blk_scale[t] = in ? tb.ms[row_offset(il, a.nb, uint32_t(cbi))] : 0.0f;
-        s.blk_vmax[t] = r;
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
-    }
-    float cold16[4];
-    load4(a.c + geo.col0, cold16);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(cold16[e])));
-        cold16[e] *= 0.0625f;
-    }
-    // the first rows' loads are in flight meanwhile; the barriers also publish the staged scales.  An extreme scale
-    // anywhere sends the whole tile to the exact route: one test per tile instead of one per row.
-    load_tables(s);
-    const bool tame = !__syncthreads_or(int(!lane_tame));
-    // Everything requested so far has to be here before the first row anyway.  Saying so with an explicit wait gives the
-    // loop a start-up state with nothing outstanding; otherwise the start-up's own (tight) wait counts are merged into
-    // the loop head and drain the prefetch in every round.
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-    // Rounds of three rows while all three exist; the loop has no exit in its middle, so that every path through it sees
-    // the same queue of outstanding loads and the compiler's wait counts are exact (an early exit would join a path on
-    // which the newest prefetch is still pending, and the loop head would then wait for it).  At most two rows remain.
-    auto none = [] {};
-    auto work = [&](const Row1<BF16>& cur, int k, auto mid) {
-        pass1_row<BF16>(a, h, tb, geo, s, cur, off(k), slot0 + walk.at(k) * a.gx, cold16, tame, cmax, mid);
-    };
-    int k = 0;
-    while (k + 2 < n) {
-        work(r0, k, [&] { r2 = fetch(k + 2); });
-        work(r1, k + 1, [&] { r0 = fetch(k + 3); });
-        work(r2, k + 2, [&] { r1 = fetch(k + 4); });
-        k += 3;
-    }
-    if (k < n) {
-        work(r0, k, none);
-        if (k + 1 < n) work(r1, k + 1, none);
-    }
-
-    // column maxima: combine the gy groups that share a column block, then one atomic per column
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s.col[geo.grp * 128 + geo.l * 4 + e] = cmax[e];
-    __syncthreads();
-    // block scales to the state, block maxima of v_t into the row maxima
-    for (int t = threadIdx.x; t < geo.n_rows * a.gx; t += kThreads) {
-        const int il = t / a.gx, cbi = geo.strip * a.gx + t % a.gx;
-        st<float>(tb.ms, row_offset(il, a.nb, uint32_t(cbi)) * 4u, s.blk_scale[t]);
-        const float m = s.blk_vmax[t];
-        if (m > 0.0f) atomic_max_nonneg(tb.r_new + il, m);     // unconditionally: reading the running maximum first (to
-        // skip atomics that cannot raise it) costs a round trip at the end of every tile and was measured to be slower
-    }
-    for (int t = threadIdx.x; t < a.gx * 128; t += kThreads) {
-        const int gi = t >> 7;
-        float m = 0.0f;
-        for (int y = 0; y < a.gy; ++y) m = fmaxf(m, s.col[((y * a.gx + gi) << 7) + (t & 127)]);
-        const int cbi = geo.strip * a.gx + gi;
-        if (m > 0.0f) atomic_max_nonneg(a.c_new + int64_t(cbi) * 128 + (t & 127), m);
-    }
-}
-
-// =====================================================================================================
-// Pass 1, "flat" tiling: a workgroup's tile is rw rows x up to 8 column blocks (4 KiB of parameters
-// per row), and a group walks ALONG a row -- the strip's blocks one after the other, then its next
-// row -- so that each of the 8 groups reads and writes runs of 4 KiB instead of 512 bytes per row.
-// The price: a lane's 4 columns change with every block, so the old column maxima of the strip sit in
-// LDS (read per block) and the running new ones are raised there with LDS atomics.  Rows are dealt to
-// the groups as in the tiling above (spacing 2^rs).  Everything else is pass1_row's arithmetic.
-// =====================================================================================================
-
-constexpr int kFlatBlocks = 8;
-
-// One block of one row.  off4: byte offset of the lane's elements in the tile; il: the row; j = block inside the strip
-// (the same for all lanes), cb0 = the strip's first column block; row_run carries the lane's maximum of v_t in the row from
-// block to block, reduced over the lanes after the last one.
-template <bool BF16, class Mid>
-__device__ __forceinline__ void flat_unit(const Tensor4& a, const Hyper& h, const TileBase& tb, Lds& s,
-                                          const Row1<BF16>& cur, uint32_t off4, int il, int j, int cb0, int l, int nbk,
-                                          bool tame, float& row_run, Mid mid) {
-    float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
-    float g[4];
-    unpack_grad4<BF16>(cur.g, g);
-    float mt[4], vt[4], amax = 0.0f, rmax = 0.0f;
-    const float s_old = s.blk_scale[il * kFlatBlocks + j];     // staged by the tile; replaced below
-    const float r_old = s.blk_vmax[il];                        // likewise; replaced after the row's last block
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const float2 t = s.deq[(uint32_t(cur.mq) >> (8 * k)) & 255u];
-        mt[2 * k] = t.x * s_old;
-        mt[2 * k + 1] = t.y * s_old;
-    }
-    if (__builtin_expect(tame, 1)) {
-        float qf[4];
-        codes_to_float4(cur.vq, qf);
-        const float r16 = r_old * 0.0625f;
-        const float4 c16 = *reinterpret_cast<const float4*>(&s.cold[j * 128 + l * 4]);
-        const float cold16[4] = {c16.x, c16.y, c16.z, c16.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(r16, cold16[e]));
-    } else {
-        float cold[4];
-        load4(a.c + (cb0 + j) * 128 + l * 4, cold);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vt[e] = dequant_v((uint32_t(cur.vq) >> (4 * e)) & 15u, fminf(r_old, cold[e]));
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        mt[e] = moment_m(h, mt[e], g[e]);
-        vt[e] = moment_v(h, vt[e], g[e]);
-        w[e] = param_update(h, w[e], mt[e], vt[e]);
-        amax = fmaxf(amax, fabsf(mt[e]));
-        rmax = max_nonneg(rmax, vt[e]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    mid();
-    __builtin_amdgcn_sched_barrier(0);
-    // running column maxima of the strip: LDS atomics on the float bits (values are >= +0)
-    unsigned int* cbits = reinterpret_cast<unsigned int*>(&s.col[j * 128 + l * 4]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        (void)__hip_atomic_fetch_max(cbits + e, __float_as_uint(vt[e]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    const float s_new = group32_allmax(amax);
-    row_run = j == 0 ? rmax : max_nonneg(row_run, rmax);
-    const bool row_ends = j == nbk - 1;                       // the same for all lanes
-    if (row_ends) row_run = group32_allmax(row_run);
-
-    store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
-    if (l == 0) {
-        s.blk_scale[il * kFlatBlocks + j] = s_new;
-        if (row_ends) s.blk_vmax[il] = row_run;
-    }
-}
-
-// a.strips = ceil(nb / 8) strips, a.rw rows per tile (at most 64), a.rs the row spacing, a.n_wg workgroups
-template <bool BF16>
-__device__ __forceinline__ void pass1_flat_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
-    const int strip = wg % a.strips, tile = wg / a.strips;
+__device__ __forceinline__ void maxima_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    static_assert(offsetof(Lds, cold) == offsetof(Lds, col) + sizeof(float) * kColSlots && 2 * kColSlots >= kGroups * 256,
+                  "col and cold hold the groups' column maxima here");
+    const int strip = wg % a.strips2, tile = wg / a.strips2;
     const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
-    const int cb0 = strip * kFlatBlocks;
-    const int left_b = a.nb - cb0;
-    const int nbk = left_b < kFlatBlocks ? left_b : kFlatBlocks;         // blocks of this strip, 1..8
-    const int64_t row0 = int64_t(tile) * a.rw;
-    const int64_t left = a.rows - row0;
-    const int n = left < a.rw ? int(left) : a.rw;
-    const TileBase tb = tile_base<BF16>(a, row0, n);
-    // units in the order the groups take them: unit q = block q % nbk of the group's row number q / nbk
-    const RowWalk walk{a.rs, kGroups << a.rs};
-    const int nq = walk.rounds(n) * nbk;
-    const uint32_t inv_nbk = (65536u + uint32_t(nbk) - 1u) / uint32_t(nbk);   // q / nbk == (q * inv_nbk) >> 16 for q < 9000
-    auto krow = [&](int q) { return int((uint32_t(q) * inv_nbk) >> 16); };
-    const int row_g = grp << a.rs;
-    const uint32_t lane4 = row_offset(row_g, a.cols, uint32_t(cb0) * 128u + uint32_t(l) * 4u) * 4u, pitch4 = uint32_t(a.cols) * 4u;
-    auto off = [&](int q) { return lane4 + (uint32_t(walk.at(krow(q))) * pitch4 + uint32_t(q - krow(q) * nbk) * 512u); };
-    // the gradient's load is non-temporal although pass 2 reads it again: tensors large enough for this tiling are not
-    // served from the memory-side cache the second time, and not keeping the line is 0.35 % per step by phases (five A/B
-    // pairs) and 0.7 % in one launch (7B-shaped set 16.43 against 16.54 ms, with fp32 gradients 20.51 against 20.73)
-    auto fetch = [&](int q) { return load_row1<BF16, kPolicyNt>(tb, off(q)); };
-    int q = 0;
-    Row1<BF16> r0 = fetch(0);
-    Row1<BF16> r1 = fetch(1);
-    Row1<BF16> r2;
-    // the strip's old column maxima (scaled) and zeroed running maxima into LDS, then the tables
-    bool lane_tame = true;
-    for (int t = threadIdx.x; t < nbk * 128; t += kThreads) {
-        const float c = a.c[cb0 * 128 + t];
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(c)));
-        s.cold[t] = c * 0.0625f;
-        s.col[t] = 0.0f;
-    }
-    // old block scales and old row maxima of the tile into the slots of the new ones, zeros for rows behind its end
-    for (int t = threadIdx.x; t < a.rw * kFlatBlocks; t += kThreads) {
-        const int il = t / kFlatBlocks, j = t % kFlatBlocks;
-        s.blk_scale[t] = il < n && j < nbk ? tb.ms[row_offset(il, a.nb, uint32_t(cb0 + j))] : 0.0f;
-    }
-    for (int t = threadIdx.x; t < a.rw; t += kThreads) {
-        const float r = t < n ? tb.r[t] : 0.0f;
-        s.blk_vmax[t] = r;
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
-    }
-    load_tables(s);
-    const bool tame = !__syncthreads_or(int(!lane_tame));     // an extreme scale anywhere: the exact route for the whole tile
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-    float row_run = 0.0f;
-    auto none = [] {};
-    auto unit = [&](const Row1<BF16>& cur, int qq, auto mid) {
-        const int k = krow(qq);
-        flat_unit<BF16>(a, h, tb, s, cur, off(qq), row_g + walk.at(k), qq - k * nbk, cb0, l, nbk, tame, row_run, mid);
+    const int64_t row0 = int64_t(tile) * a.rw2, left = a.rows - row0;
+    const int n = left < a.rw2 ? int(left) : a.rw2;
+    // with an odd number of column blocks the upper half of the last strip repeats the lower half's columns
+    const uint32_t col_own = uint32_t(strip) * 256u + uint32_t(l) * 8u;
+    const uint32_t col0 = col_own < uint32_t(a.cols) ? col_own : col_own - 128u;
+    const int64_t e0 = row0 * a.cols;
+    const uint32_t elems = uint32_t(n) * uint32_t(a.cols);                    // < 2^29
+    const Rsrc rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + e0 * (BF16 ? 2 : 4), elems * (BF16 ? 2u : 4u));
+    const Rsrc rv = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (e0 >> 1), elems >> 1);
+    const RowWalk walk{a.rs2, kGroups << a.rs2};
+    const int rounds = walk.rounds(n);
+    const int row_g = grp << a.rs2;
+    const uint32_t lane_e = row_offset(row_g, a.cols, col0), pitch = uint32_t(a.cols);
+    auto fetch = [&](int k) {
+        const uint32_t e = lane_e + uint32_t(walk.at(k)) * pitch;             // behind the tile: zeros
+        Row8<BF16> r;
+        r.g[0] = buf_ld_f4(rg, e * (BF16 ? 2u : 4u));
+        if constexpr (!BF16) r.g[1] = buf_ld_f4(rg, e * 4u + 16u);
+        r.vq = __builtin_amdgcn_raw_buffer_load_b32(rv, int(e >> 1), 0, 0);
+        return r;
     };
-    while (q + 2 < nq) {
-        unit(r0, q, [&] { r2 = fetch(q + 2); });
-        unit(r1, q + 1, [&] { r0 = fetch(q + 3); });
-        unit(r2, q + 2, [&] { r1 = fetch(q + 4); });
-        q += 3;
+    constexpr int kDepth = BF16 ? 3 : 2;                  // about the same bytes in flight
+    Row8<BF16> r[kDepth];
+#pragma unroll
+    for (int u = 0; u < kDepth; ++u) r[u] = fetch(u);
+    float c16[8], cmax[8];
+    load8(a.c + col0, c16);
+    bool lane_tame = true;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(c16[e])));
+        c16[e] *= 0.0625f;
+        cmax[e] = 0.0f;
     }
-    if (q < nq) {
-        unit(r0, q, none);
-        if (q + 1 < nq) unit(r1, q + 1, none);
+    for (int t = threadIdx.x; t < kMaxRowSlots && t < a.rw2 + kGroups; t += kThreads) {     // zeros for rows behind the tile's end
+        const float x = t < n ? a.r[row0 + t] : 0.0f;
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(x)));
+        s.blk_scale[t] = x * 0.0625f;
     }
+    const bool tame = !__syncthreads_or(int(!lane_tame));                     // else the exact route for the whole tile
+    auto one = [&](const Row8<BF16>& x, int k) {
+        const int il = row_g + walk.at(k);
+        const float r16 = s.blk_scale[il];
+        float g[8], vt[8];
+        if constexpr (BF16) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t w = __float_as_uint(q == 0 ? x.g[0].x : q == 1 ? x.g[0].y : q == 2 ? x.g[0].z : x.g[0].w);
+                g[2 * q] = bf16_lo(w);
+                g[2 * q + 1] = bf16_hi(w);
+            }
+        } else {
+            g[0] = x.g[0].x; g[1] = x.g[0].y; g[2] = x.g[0].z; g[3] = x.g[0].w;
+            g[4] = x.g[1].x; g[5] = x.g[1].y; g[6] = x.g[1].z; g[7] = x.g[1].w;
+        }
+        if (__builtin_expect(tame, 1)) {
+            uint32_t lo = x.vq & 0x0F0F0F0Fu, hi = (x.vq >> 4) & 0x0F0F0F0Fu;
+            asm("" : "+v"(lo));
+            asm("" : "+v"(hi));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float q = float((e & 1 ? hi : lo) >> (8 * (e >> 1)) & 255u);
+                vt[e] = dequant_v16(q, min_nonneg(r16, c16[e]));
+            }
+        } else {
+            const float r_old = il < n ? a.r[row0 + il] : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vt[e] = dequant_v((x.vq >> (4 * e)) & 15u, fminf(r_old, a.c[col0 + e]));
+        }
+        float rmax = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            vt[e] = moment_v(h, vt[e], g[e]);
+            cmax[e] = fmaxf(cmax[e], vt[e]);              // a NaN raises no maximum
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) rmax = fmaxf(fmaxf(rmax, vt[e]), vt[e + 1]);
+        rmax = group32_allmax(rmax);
+        if (l == 0) s.blk_vmax[il] = rmax;
+    };
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding
+    int k = 0;
+    while (k + kDepth - 1 < rounds) {                     // a register set is reloaded right after its row
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            one(r[u], k + u);
+            __builtin_amdgcn_sched_barrier(0);
+            r[u] = fetch(k + kDepth + u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        k += kDepth;
+    }
+#pragma unroll
+    for (int u = 0; u < kDepth - 1; ++u)
+        if (k + u < rounds) one(r[u], k + u);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.col[grp * 256 + l * 8 + e] = cmax[e];
     __syncthreads();
-    for (int t = threadIdx.x; t < n * kFlatBlocks; t += kThreads) {
-        const int il = t / kFlatBlocks, j = t % kFlatBlocks;
-        if (j < nbk) st<float>(tb.ms, row_offset(il, a.nb, uint32_t(cb0 + j)) * 4u, s.blk_scale[t]);
-    }
     for (int t = threadIdx.x; t < n; t += kThreads) {
         const float m = s.blk_vmax[t];
-        if (m > 0.0f) atomic_max_nonneg(tb.r_new + t, m);
+        if (m > 0.0f) atomic_max_nonneg(a.r_new + row0 + t, m);
     }
-    for (int t = threadIdx.x; t < nbk * 128; t += kThreads) {
-        const float m = s.col[t];
-        if (m > 0.0f) atomic_max_nonneg(a.c_new + cb0 * 128 + t, m);
+    {
+        const int t = threadIdx.x;
+        const int64_t col = int64_t(strip) * 256 + t;
+        float m = 0.0f;
+#pragma unroll
+        for (int y = 0; y < kGroups; ++y) m = fmaxf(m, s.col[y * 256 + t]);
+        if (col < a.cols && m > 0.0f) atomic_max_nonneg(a.c_new + col, m);
     }
 }
 
-// The last workgroup of a tensor's pass 2 to finish makes r', c' the state and clears the
+// The workgroup of a tensor's second pass that takes the last ticket makes r', c' the state and clears the
 // workspace.  Every other workgroup has read the old r, c before it took its ticket, so
 // overwriting them is safe.  Tickets are taken in two levels (kTicketLanes first-level counters, one
 // cache line apart, then one top counter) so that thousands of workgroups do not queue up on a
@@ -753,39 +628,62 @@ __device__ __forceinline__ float ld_ws(const float* p) {
     else return *p;
 }
 
-// dst[i] = src[i]; src[i] = 0 by one workgroup.  It runs alone at the end of a tensor's pass 2, so
-// what counts is latency: 16 loads per thread are in flight before the first store.
+// The same for four consecutive words at a byte offset of a bounds-checked array of the workspace: a 16-byte load with the
+// cache policy of an agent-scope one.
+constexpr int kPolicySc1 = 16;
+template <bool SAME_LAUNCH>
+__device__ __forceinline__ float4 ld_ws4(Rsrc r, uint32_t off) { return buf_ld_f4<SAME_LAUNCH ? kPolicySc1 : 0>(r, off); }
+
+// The new statistics become the state and the workspace is cleared, by one workgroup: dst[i] = src[i]; src[i] = 0 for the rows and
+// the columns.  (src is 16-byte aligned and padded to whole quads.)  It runs alone at the end of a tensor's step, so what
+// counts is latency: 16 words of the rows and 16 of the columns per thread are on their way before the first store (16 words
+// of one of them before: 32000 rows and 4096 columns 9 round trips, now 8; 1024 and 1024 two, now one).
 template <bool SAME_LAUNCH = false>
-__device__ __forceinline__ void move_and_clear(float* dst, float* src, int64_t n) {
-    constexpr int kDepth = 16;
-    for (int64_t base = threadIdx.x; base < n; base += int64_t(kThreads) * kDepth) {
-        float v[kDepth];
+__device__ __forceinline__ void move_statistics(const Tensor4& a) {
+    constexpr int kDepth = 4, kChunk = kThreads * 4 * kDepth;
+    const int64_t cols = a.cols + a.c_extra;
+    for (int64_t base = 0; base < a.rows || base < cols; base += kChunk) {
+        auto left = [&](int64_t n) { return n - base < kChunk ? (n > base ? int(n - base) : 0) : kChunk; };
+        const int mr = left(a.rows), mc = left(cols);
+        const Rsrc rr = tile_rsrc(a.r_new + base, uint32_t(mr + 3) / 4u * 16u), rc = tile_rsrc(a.c_new + base, uint32_t(mc + 3) / 4u * 16u);
+        float4 vr[kDepth], vc[kDepth];
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
-            const int64_t i = base + int64_t(u) * kThreads;
-            v[u] = i < n ? ld_ws<SAME_LAUNCH>(src + i) : 0.0f;
+            const uint32_t off = uint32_t(u * kThreads + int(threadIdx.x)) * 16u;
+            vr[u] = ld_ws4<SAME_LAUNCH>(rr, off);
+            vc[u] = ld_ws4<SAME_LAUNCH>(rc, off);
         }
+        auto put = [&](float* dst, float* src, int m, const float4& v, int i) {
+            if (i >= m) return;
+            dst[i] = v.x;
+            if (i + 1 < m) dst[i + 1] = v.y;
+            if (i + 2 < m) dst[i + 2] = v.z;
+            if (i + 3 < m) dst[i + 3] = v.w;
+            *reinterpret_cast<float4*>(src + i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        };
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
-            const int64_t i = base + int64_t(u) * kThreads;
-            if (i < n) { dst[i] = v[u]; src[i] = 0.0f; }
+            const int i = (u * kThreads + int(threadIdx.x)) * 4;
+            put(a.r + base, a.r_new + base, mr, vr[u], i);
+            put(a.c + base, a.c_new + base, mc, vc[u], i);
         }
     }
 }
 
-// true in every thread of the one workgroup that arrives last; `counter`: the top counter, the first-level ones on the
-// following lines
-__device__ __forceinline__ bool last_to_arrive(unsigned int* counter, unsigned int me, unsigned int participants,
-                                               int& s_last) {
-    __syncthreads();
+// Tickets in two steps.  take_ticket: thread 0 raises the first-level counter and returns what it held; the answer is not
+// needed before ticket_is_last, so a tile that is done with the old and new statistics takes its ticket and works on.
+__device__ __forceinline__ unsigned int take_ticket(unsigned int* counter, unsigned int me) {
+    return threadIdx.x == 0 ? atomicAdd(counter + (1 + me % kTicketLanes) * kTicketStride, 1u) : 0u;
+}
+// true in every thread of the one workgroup that took the last ticket; `counter`: the top counter, the first-level ones on
+// the following lines
+__device__ __forceinline__ bool ticket_is_last(unsigned int* counter, unsigned int me, unsigned int participants,
+                                               unsigned int ticket, int& s_last) {
     if (threadIdx.x == 0) {
-        // No fence: the ticket orders nothing but "this workgroup's loads of r, c have returned",
-        // which holds once its waves have computed their codes and reached the barrier above.  (An
-        // agent-scope release here would write back the XCD's whole L2 once per workgroup.)
         const unsigned int lane = me % kTicketLanes;
         const unsigned int in_lane = participants / kTicketLanes + (lane < participants % kTicketLanes ? 1u : 0u);
         int last = 0;
-        if (atomicAdd(counter + (1 + lane) * kTicketStride, 1u) == in_lane - 1) {
+        if (ticket == in_lane - 1) {
             // this lane is complete: reset it (past the L2: its line holds words that other workgroups still count on)
             __hip_atomic_store(counter + (1 + lane) * kTicketStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             last = atomicAdd(counter, 1u) == lanes_used(participants) - 1;
@@ -793,322 +691,258 @@ __device__ __forceinline__ bool last_to_arrive(unsigned int* counter, unsigned i
         s_last = last;
     }
     __syncthreads();
-    return s_last != 0;
+    return __builtin_amdgcn_readfirstlane(s_last) != 0;       // a scalar branch: the same in every lane
+}
+__device__ __forceinline__ bool last_to_arrive(unsigned int* counter, unsigned int me, unsigned int participants,
+                                               int& s_last) {
+    // No fence: the ticket orders nothing but "this workgroup's loads of r, c have returned", which holds once its waves
+    // have computed with them and reached the barrier.  (An agent-scope release here would write back the XCD's whole L2
+    // once per workgroup.)
+    __syncthreads();
+    return ticket_is_last(counter, me, participants, take_ticket(counter, me), s_last);
 }
 
-__device__ __forceinline__ void publish_if_last(const Tensor4& a, unsigned int me, unsigned int participants,
-                                                int& s_last) {
-    if (!last_to_arrive(a.counter, me, participants, s_last)) return;
-    move_and_clear(a.r, a.r_new, a.rows);
-    move_and_clear(a.c, a.c_new, a.cols + a.c_extra);
+__device__ __forceinline__ void publish(const Tensor4& a) {
+    move_statistics(a);
     if (threadIdx.x == 0) *a.counter = 0u;
 }
-
-// Pass 2 of the fast path.  Nothing here is reduced over a block, so the layout is chosen for the
-// memory system and for cheap row bookkeeping instead: a wave works on 256 consecutive columns of
-// ONE row (lane l owns columns 4l .. 4l+3 of the strip; 128 contiguous bytes of codes, 512 of bf16
-// gradient), the four waves of a workgroup take rows w, w+4, ... of the tile.  The row index, the two
-// row maxima and everything derived from them are wave-uniform and live in scalar registers.
-template <bool BF16>
-struct Row2 {                      // what pass 2 reads per element for one row of one lane
-    GradRegs4<BF16> g;
-    uint16_t vq;                   // the lane's 4 codes
-};
-
-// row_elems = il * cols, wave-uniform: it travels as the scalar offset of the buffer instructions, so a row costs no
-// vector arithmetic for its addresses.  lane_g / lane_q: the lane's byte offsets inside a row of the gradient / of the
-// codes, fixed for the tile.  (Callers pass rows inside the tile only: the scalar offset may not take part in the
-// range check of the resource.)
-template <bool BF16>
-__device__ __forceinline__ Row2<BF16> load_row2(const TileBase& b, uint32_t row_elems, uint32_t lane_g, uint32_t lane_q) {
-    Row2<BF16> r;
-    if constexpr (BF16) {                                       // last use of the gradient in this step
-        const v2u_t w = __builtin_amdgcn_raw_buffer_load_b64(b.rg, int(lane_g), int(row_elems * 2u), kPolicyNt);
-        r.g.w = make_uint2(w.x, w.y);
-    } else {
-        const v4f_t v = __builtin_bit_cast(v4f_t, __builtin_amdgcn_raw_buffer_load_b128(b.rg, int(lane_g), int(row_elems * 4u), kPolicyNt));
-        r.g.a = make_float4(v.x, v.y, v.z, v.w);
-    }
-    r.vq = uint16_t(__builtin_amdgcn_raw_buffer_load_b16(b.rvq, int(lane_q), int(row_elems >> 1), 0));
-    return r;
+__device__ __forceinline__ void publish_if_last(const Tensor4& a, unsigned int me, unsigned int participants,
+                                                int& s_last) {
+    if (last_to_arrive(a.counter, me, participants, s_last)) publish(a);
 }
 
-__device__ __forceinline__ float lane_value(float v, int lane) {      // lane: wave-uniform
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+// What a tile of a second pass is told and tells.  ready(): called once by every thread, after everything that does not
+// depend on the first pass has been requested; false leaves the tile undone.  staged(): called once by every thread, behind a
+// barrier, when the workgroup has read all it needs of the old and the new statistics.
+struct NoSync {
+    __device__ __forceinline__ bool ready() { return true; }
+    __device__ __forceinline__ void staged() {}
+};
+// a launch of its own: the ticket of the publishing workgroup
+struct TicketSync {
+    unsigned int* counter;
+    unsigned int me, ticket;
+    __device__ __forceinline__ bool ready() { return true; }
+    __device__ __forceinline__ void staged() { ticket = take_ticket(counter, me); }
+};
+
+// ---- second pass: the whole update ----------------------------------------------------------------------------------
+// decompress m and v, Eq. 1, parameter update, compress m against its block's maximum and v against min(r', c').
+// A workgroup's tile is gx (1..8) column blocks of rw rows; a group takes rw / 8 consecutive rows and walks ALONG each, block
+// after block, so that it reads and writes runs of up to 4 KiB.  The groups' rows are 2^rs rows apart, 32 KiB of parameters
+// where rows of a power of two of elements allow it: a super-tile of 8 << rs rows is dealt to (8 << rs) / rw workgroups.  The
+// memory system serves accesses side by side at exactly that distance fastest (this pass by itself, bf16 gradients, 246 M
+// parameters: 8192 columns 6.5 TB/s 32 KiB apart, 5.9 next to each other's double distance or farther; 4096 columns 6.4, 6.0 at 16
+// KiB, 5.8 at 64 KiB; 11008 columns, whose rows never are that far apart, 5.8 for neighbouring rows and 5.5 at 32 of them).
+// What a lane needs of its 4 columns (old maxima / 16, approximate inverses of the new ones) sits in LDS, and so do the rows'
+// scalars and the blocks' scales.  The loads of two units (one block of one row) are in flight while a third is computed
+// (three register sets take turns, the loop is unrolled by three); the prefetch is unconditional, units behind the tile come
+// back as zeros or are never used.
+
+// The rows' scalars of an update tile, in s.blk_vmax: {old maximum / 16, approx. 16 / new maximum} per row, then the new maxima.
+constexpr int kRowSlots = 160;
+static_assert(3 * kRowSlots <= kMaxRowSlots, "row scalars of an update tile");
+__device__ __forceinline__ void stage_row_old(Lds& s, int t, float r) { s.blk_vmax[2 * t] = r * 0.0625f; }
+__device__ __forceinline__ void stage_row_new(Lds& s, int t, float r) {
+    s.blk_vmax[2 * t + 1] = approx_inv16(r);
+    s.blk_vmax[2 * kRowSlots + t] = r;
 }
+__device__ __forceinline__ float2 row_scalars(const Lds& s, int t) { return *reinterpret_cast<const float2*>(&s.blk_vmax[2 * t]); }
+__device__ __forceinline__ float row_new(const Lds& s, int t) { return s.blk_vmax[2 * kRowSlots + t]; }
 
-// The scalars of a wave's rows of one pass-2 tile, one row per lane (row k of the wave in lane k): the old and the new
-// row maximum, the old one / 16, 16 times the approximate reciprocal of the new one (0 for 0), and `wild`, the mask of the
-// rows that must take the exact route whatever their elements (a scale of the row or of the strip's columns outside
-// the range in which scale / 16 and the reciprocal keep all their bits).
-struct RowScalars {
-    float r_old, r_new, r16, inv;
-    uint64_t wild;
-};
-// The same of the rows that follow the wave's rows, and which of the lane's 4 elements lie in the following row (ragged
-// tensors only, see pass2_tile).
-struct NextRow {
-    RowScalars sc;
-    bool beyond[4];
-};
-
-// New codes of the lane's 4 elements of row k of the wave.  The usual route multiplies by approximate reciprocals and
-// keeps track of how close it came to a decision boundary; if the row is marked wild, or some lane came too close, the
-// whole wave computes the row again from its inputs with exact arithmetic (same bits where both apply).  The second
-// route shares no value with the first, so that nothing has to be kept in registers for it.
-template <bool BF16, bool RAGGED, bool SAME_LAUNCH>
-__device__ __forceinline__ uint32_t pass2_row(const Tensor4& a, const Hyper& h, const uint32_t col[4], const Row2<BF16>& row,
-                                              const RowScalars& rs, const NextRow& nx, int k, const float cold16[4],
-                                              const float inv_cnew[4]) {
-    float g[4];
-    unpack_grad4<BF16>(row.g, g);
-    // wave-uniform: the whole wave takes one route
-    if (__builtin_expect(((rs.wild >> k) & 1u) == 0u, 1)) {
-        float qf[4], vt[4], r16[4], inv_r[4];
-        codes_to_float4(row.vq, qf);
-        r16[0] = lane_value(rs.r16, k);
-        inv_r[0] = lane_value(rs.inv, k);
-        if constexpr (RAGGED) {
-            const float r16n = lane_value(nx.sc.r16, k), invn = lane_value(nx.sc.inv, k);
-#pragma unroll
-            for (int e = 3; e >= 0; --e) {                       // an element beyond the row's end has one before it
-                r16[e] = nx.beyond[e] ? r16n : r16[0];
-                inv_r[e] = nx.beyond[e] ? invn : inv_r[0];
-            }
-        } else {
-#pragma unroll
-            for (int e = 1; e < 4; ++e) { r16[e] = r16[0]; inv_r[e] = inv_r[0]; }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vt[e] = moment_v(h, dequant_v16(qf[e], min_nonneg(r16[e], cold16[e])), g[e]);
-        // even elements collect in the bytes of `lo`, odd ones in `hi`; word = lo | hi << 4
-        uint32_t lo = 0, hi = 0;
-        float closest = 0.5f, fa, fb;
+// Codes of 4 second moments against their scales, inv[e] = 16 / scale approximately; false in `sure` if some lane of the wave
+// came too close to a boundary.
+__device__ __forceinline__ uint32_t compress_v4(const float vt[4], const float inv[4], bool& sure) {
+    // even elements collect in the bytes of `lo`, odd ones in `hi`; word = lo | hi << 4
+    uint32_t lo = 0, hi = 0;
+    float closest = 0.5f, fa, fb;
 #define LPMM_V2(K)                                                                                        \
-        lo = quant_v_code_fast<K>(vt[2 * K], max_nonneg(inv_r[2 * K], inv_cnew[2 * K]), lo, fa);          \
-        hi = quant_v_code_fast<K>(vt[2 * K + 1], max_nonneg(inv_r[2 * K + 1], inv_cnew[2 * K + 1]), hi, fb); \
-        closest = fminf(fminf(closest, fabsf(fa)), fabsf(fb));
-        LPMM_V2(0) LPMM_V2(1)
+    lo = quant_v_code_fast<K>(vt[2 * K], inv[2 * K], lo, fa);                                             \
+    hi = quant_v_code_fast<K>(vt[2 * K + 1], inv[2 * K + 1], hi, fb);                                     \
+    closest = fminf(fminf(closest, fabsf(fa)), fabsf(fb));
+    LPMM_V2(0) LPMM_V2(1)
 #undef LPMM_V2
-        if (__builtin_expect(__ballot(closest < kMarginV) == 0, 1)) return lo | (hi << 4);
+    sure = __ballot(closest < kMarginV) == 0;
+    return lo | (hi << 4);
+}
+
+__device__ __forceinline__ void store_vq(const TileBase& tb, uint32_t off4, uint32_t vq_new) {
+    __builtin_amdgcn_raw_buffer_store_b16(short(vq_new), tb.rvq, int(off4 >> 3), 0, 0);
+}
+
+// One unit.  off4: byte offset of the lane's elements in the tile; row, il: the row, in the tensor and in the tile; j = block inside the strip (the same for all
+// lanes), cb0 = the strip's first column block.
+template <bool BF16, class Mid>
+__device__ __forceinline__ void update_unit(const Tensor4& a, const Hyper& h, const TileBase& tb, LdsRank1& s,
+                                            const Row1<BF16>& cur, uint32_t off4, int64_t row, int il, int j, int cb0, int l,
+                                            bool tame, Mid mid) {
+    float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
+    float g[4];
+    unpack_grad4<BF16>(cur.g, g);
+    float mt[4], vt[4], amax = 0.0f;
+    const float s_old = s.blk_scale[il * kFlatBlocks + j];     // staged by the tile; replaced below
+    const float2 rs = row_scalars(s, il);
+    const int at = j * 128 + l * 4;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const float2 t = s.deq[(uint32_t(cur.mq) >> (8 * k)) & 255u];
+        mt[2 * k] = t.x * s_old;              // decompress: T_DE[code] * block scale
+        mt[2 * k + 1] = t.y * s_old;
     }
-    uint32_t out = 0;
+    if (__builtin_expect(tame, 1)) {          // no old or new scale of the tile is extreme
+        float qf[4];
+        codes_to_float4(cur.vq, qf);
+        const float4 c16 = *reinterpret_cast<const float4*>(&s.cold[at]);
+        const float cold16[4] = {c16.x, c16.y, c16.z, c16.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(rs.x, cold16[e]));
+    } else {
+        const float r_old = row < a.rows ? a.r[row] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vt[e] = dequant_v((uint32_t(cur.vq) >> (4 * e)) & 15u, fminf(r_old, a.c[cb0 * 128 + at + e]));
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        float r_old = lane_value(rs.r_old, k), r_new = lane_value(rs.r_new, k);
-        if constexpr (RAGGED) {
-            const float ron = lane_value(nx.sc.r_old, k), rnn = lane_value(nx.sc.r_new, k);
-            r_old = nx.beyond[e] ? ron : r_old;
-            r_new = nx.beyond[e] ? rnn : r_new;
-        }
-        const float cold = a.c[col[e]], cnew = ld_ws<SAME_LAUNCH>(a.c_new + col[e]);
-        const float vt = moment_v(h, dequant_v((uint32_t(row.vq) >> (4 * e)) & 15u, fminf(r_old, cold)), g[e]);
-        out |= quant_v_code(vt, fminf(r_new, cnew)) << (4 * e);
+        mt[e] = moment_m(h, mt[e], g[e]);
+        vt[e] = moment_v(h, vt[e], g[e]);
+        w[e] = param_update(h, w[e], mt[e], vt[e]);
+        amax = fmaxf(amax, fabsf(mt[e]));
     }
-    return out;
+    // the caller's prefetch of a later unit is issued here, in the middle of the arithmetic: by now the previous unit's
+    // stores have been acknowledged, and loads queue behind older stores
+    __builtin_amdgcn_sched_barrier(0);
+    mid();
+    __builtin_amdgcn_sched_barrier(0);
+    const float s_new = group32_allmax(amax);     // block absmax of m_t
+    uint32_t vq_new = 0;
+    bool sure = false;
+    if (__builtin_expect(tame, 1)) {
+        const float4 ic = *reinterpret_cast<const float4*>(&s.col[at]);
+        const float inv[4] = {max_nonneg(rs.y, ic.x), max_nonneg(rs.y, ic.y), max_nonneg(rs.y, ic.z), max_nonneg(rs.y, ic.w)};
+        vq_new = compress_v4(vt, inv, sure);
+    }
+    if (__builtin_expect(!sure, 0)) {
+        const float r_new = row_new(s, il);
+        vq_new = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vq_new |= quant_v_code(vt[e], fminf(r_new, s.cnew[at + e])) << (4 * e);
+    }
+    store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
+    store_vq(tb, off4, vq_new);
+    if (l == 0) s.blk_scale[il * kFlatBlocks + j] = s_new;
+}
+
+// SAME_LAUNCH: the first pass of the tensor runs in the same launch.
+template <bool BF16, bool SAME_LAUNCH, class Sync>
+__device__ __forceinline__ void update_tile(const Tensor4& a, const Hyper& h, int wg, LdsRank1& s, Sync& sync) {
+    const TableRegs tables = request_tables();
+    const int strip = wg % a.strips, tile = wg / a.strips;
+    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+    const int cb0 = strip * a.gx;
+    const int nbk = a.nb - cb0 < a.gx ? a.nb - cb0 : a.gx;               // blocks of this strip, 1..8
+    const int pl = __builtin_ctz(a.rw) - 3, per = 1 << pl;               // rows of a group, a power of two
+    const int64_t row0 = int64_t(tile >> (a.rs - pl)) << (a.rs + 3);     // 2^(rs - pl) workgroups share a super-tile
+    const int slice0 = (tile & ((1 << (a.rs - pl)) - 1)) << pl;
+    const int64_t left = a.rows - row0;
+    const int n = left < (kGroups << a.rs) ? int(left) : kGroups << a.rs;    // rows of the super-tile
+    const TileBase tb = tile_base<BF16>(a, row0, n);
+    auto row_of = [&](int il) { return (il >> pl << a.rs) + slice0 + (il & (per - 1)); };    // of the tile's il-th row, in the super-tile
+    // units in the order the groups take them: unit q = block q % nbk of the group's row number q / nbk
+    const int nq = per * nbk;
+    const uint32_t inv_nbk = (65536u + uint32_t(nbk) - 1u) / uint32_t(nbk);   // q / nbk == (q * inv_nbk) >> 16 for q < 9000
+    auto krow = [&](int q) { return int((uint32_t(q) * inv_nbk) >> 16); };
+    const int row_g = grp * per;
+    const uint32_t lane4 = row_offset((grp << a.rs) + slice0, a.cols, uint32_t(cb0) * 128u + uint32_t(l) * 4u) * 4u, pitch4 = uint32_t(a.cols) * 4u;
+    auto off = [&](int q) { return q < nq ? lane4 + (uint32_t(krow(q)) * pitch4 + uint32_t(q - krow(q) * nbk) * 512u) : kNowhere; };
+    auto fetch = [&](int q) { return load_row1<BF16, kPolicyNt>(tb, off(q)); };        // the gradient's last use in the step
+    // Start-up: everything a workgroup needs before its first unit is requested before any of it is waited for, one round
+    // trip in front of ready() and one behind it.  Thread t takes columns 4t .. 4t+3 of the strip, blocks t and t + 256 and row t.
+    const int t = threadIdx.x;
+    static_assert(kFlatBlocks * 128 <= 4 * kThreads && 64 * kFlatBlocks <= 2 * kThreads, "start-up of an update tile");
+    const uint32_t strip_bytes = uint32_t(nbk) * 512u;
+    const float4 c_old = buf_ld_f4(tile_rsrc(a.c + cb0 * 128, strip_bytes), uint32_t(t) * 16u);
+    float ms_old[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int il = (t + u * kThreads) / kFlatBlocks, j = t % kFlatBlocks, row = row_of(il);
+        ms_old[u] = il < a.rw && row < n && j < nbk ? tb.ms[row_offset(row, a.nb, uint32_t(cb0 + j))] : 0.0f;
+    }
+    const bool row_in = t < a.rw && row_of(t) < n;
+    const float r_old = row_in ? tb.r[row_of(t)] : 0.0f;
+    float4 c_new;
+    float r_new;
+    auto request_new = [&] {
+        c_new = ld_ws4<SAME_LAUNCH>(tile_rsrc(a.c_new + cb0 * 128, strip_bytes), uint32_t(t) * 16u);
+        r_new = row_in ? ld_ws<SAME_LAUNCH>(tb.r_new + row_of(t)) : 0.0f;
+    };
+    if constexpr (!SAME_LAUNCH) request_new();
+    Row1<BF16> r0 = fetch(0);
+    Row1<BF16> r1 = fetch(1);
+    Row1<BF16> r2;
+    put_tables(s, tables);
+    bool lane_tame = true;
+    auto tame_too = [&](float x) { lane_tame = bool(int(lane_tame) & int(scale_is_tame(x))); return x; };
+    reinterpret_cast<float4*>(s.cold)[t] = make_float4(tame_too(c_old.x) * 0.0625f, tame_too(c_old.y) * 0.0625f,
+                                                       tame_too(c_old.z) * 0.0625f, tame_too(c_old.w) * 0.0625f);
+    // old block scales of m into the slots of the new ones; zeros for rows behind the tile's end
+    s.blk_scale[t] = ms_old[0];
+    s.blk_scale[t + kThreads] = ms_old[1];
+    if (t < a.rw) stage_row_old(s, t, tame_too(r_old));
+    if (!sync.ready()) return;
+    if constexpr (SAME_LAUNCH) request_new();
+    reinterpret_cast<float4*>(s.cnew)[t] = make_float4(tame_too(c_new.x), tame_too(c_new.y), tame_too(c_new.z), tame_too(c_new.w));
+    reinterpret_cast<float4*>(s.col)[t] = make_float4(approx_inv16(c_new.x), approx_inv16(c_new.y), approx_inv16(c_new.z), approx_inv16(c_new.w));
+    if (t < a.rw) stage_row_new(s, t, tame_too(r_new));
+    const bool tame = !__syncthreads_or(int(!lane_tame));     // an extreme scale anywhere: the exact route for the whole tile
+    // Everything requested so far has to be here before the first unit anyway.  Saying so with an explicit wait gives the
+    // loop a start-up state with nothing outstanding; otherwise the start-up's own (tight) wait counts are merged into
+    // the loop head and drain the prefetch in every round.
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    if (tame) sync.staged();                                  // the exact route reads old statistics all along
+    auto none = [] {};
+    auto unit = [&](const Row1<BF16>& cur, int qq, auto mid) {
+        const int k = krow(qq);
+        update_unit<BF16>(a, h, tb, s, cur, off(qq), row0 + row_of(row_g + k), row_g + k, qq - k * nbk, cb0, l, tame, mid);
+    };
+    // Rounds of three units while all three exist; the loop has no exit in its middle, so that every path through it sees
+    // the same queue of outstanding loads and the compiler's wait counts are exact (an early exit would join a path on
+    // which the newest prefetch is still pending, and the loop head would then wait for it).  At most two units remain.
+    int q = 0;
+    while (q + 2 < nq) {
+        unit(r0, q, [&] { r2 = fetch(q + 2); });
+        unit(r1, q + 1, [&] { r0 = fetch(q + 3); });
+        unit(r2, q + 2, [&] { r1 = fetch(q + 4); });
+        q += 3;
+    }
+    if (q < nq) {
+        unit(r0, q, none);
+        if (q + 1 < nq) unit(r1, q + 1, none);
+    }
+    __syncthreads();
+    if (!tame) sync.staged();
+    for (int k = t; k < a.rw * kFlatBlocks; k += kThreads) {
+        const int row = row_of(k / kFlatBlocks), j = k % kFlatBlocks;
+        if (row < n && j < nbk) st<float>(tb.ms, row_offset(row, a.nb, uint32_t(cb0 + j)) * 4u, s.blk_scale[k]);
+    }
 }
 
 constexpr int kWaves = kThreads / 64;
-constexpr int kMaxRw2 = 64 * kWaves;      // rows of a pass-2 tile: a wave keeps its rows' scalars one per lane
+constexpr int kMaxRw2 = 64 * kWaves;      // rows of a statistics tile of the ragged and the factorized forms
 
-// RAGGED: rows that are no multiple of 128 elements long, so that a row's first element need not be the first of its
-// code byte.  Nothing in pass 2 knows about blocks; all that has to be aligned is a lane's 4 elements in the flattening.
-// The lanes of row i therefore start at the first multiple of 4 at or behind i * cols, `shift` = -i * cols mod 4 columns
-// into the row, and that shift is the same for all rows a wave takes (they are a multiple of 4 apart): a lane's columns
-// are fixed down the tile here, too.  The last lane of a row may reach up to 3 elements into the next row; its columns
-// are those of the next row's beginning, and only the row's scalars have to be chosen per element.  Where that would
-// reach beyond the tensor (its size is no multiple of 4) the last row is left to pass2_last_row.  Measured on 4096 x 4000
-// with bf16 gradients: 19 us, 15 for 4096 x 4096 on the plain form.  (Blocks of 128 with the column vectors in LDS, as
-// pass 1 has to take them: 28 us; the general kernel: more than 100.)
-__host__ __device__ __forceinline__ int64_t pass2_rows(const Tensor4& a, bool ragged) {
-    return ragged && (a.P & 3) ? a.rows - 1 : a.rows;
-}
-
-// SAME_LAUNCH: pass 1 of the tensor runs in the same launch.  `ready` is called once by every wave, after the loads that
-// do not depend on pass 1 have been issued; false leaves the tile undone.
-struct AlwaysReady {
-    __device__ __forceinline__ bool operator()() const { return true; }
-};
-struct NoLds {};                 // pass 2 of a launch of its own needs none
-template <bool BF16, bool RAGGED = false, bool SAME_LAUNCH = false, class Ready = AlwaysReady, class S = NoLds>
-__device__ __forceinline__ void pass2_tile(const Tensor4& a, const Hyper& h, int wg, Ready ready = Ready(), S&& s = S()) {
-    const int strip = wg % a.strips2, tile = wg / a.strips2;
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    const int64_t row0 = int64_t(tile) * a.rw2;                   // ragged: a multiple of 4
-    const int64_t left = pass2_rows(a, RAGGED) - row0;
-    const int n = left < a.rw2 ? int(left) : a.rw2;
-    const uint32_t cols = uint32_t(a.cols);
-    // rows of this wave in the order it takes them, as in pass 1: the four waves are 2^rs2 rows apart
-    const int rs = RAGGED ? 0 : a.rs2;
-    const int row_w = wave << rs, hop = kWaves << rs, low = (1 << rs) - 1;
-    auto row = [&](int k) { return row_w + (k & low) + (k >> rs) * hop; };
-    const int n_stat = RAGGED && row0 + n < a.rows ? n + 1 : n;   // ragged: the statistics of one row more
-    // SAME_LAUNCH: the new maxima of the strip's columns and of the tile's rows through LDS, one agent-scope load each.
-    // Such loads are not served by the L2; each wave fetching its columns and rows itself, as it does with plain loads,
-    // would make 150 requests per workgroup to lines that every tile of the strip reads (factorized GPT-2-medium set: 739
-    // us so, 728 with the vectors staged).
-    auto stage = [&] {
-        if constexpr (SAME_LAUNCH) {
-            for (int t = threadIdx.x; t < 256 + (RAGGED ? 8 : 0); t += kThreads) {
-                uint32_t c = uint32_t(strip) * 256u + uint32_t(t);
-                if (RAGGED && c >= cols) c -= cols;               // a row's last lane reaches into the next row
-                s.col[t] = c < cols ? ld_ws<true>(a.c_new + c) : 0.0f;
-            }
-            for (int t = threadIdx.x; t < n_stat; t += kThreads) s.blk_scale[t] = ld_ws<true>(a.r_new + row0 + t);
-            __syncthreads();
-        }
-    };
-    int last = n - 1;
-    uint32_t shift = 0;
-    if constexpr (RAGGED) {
-        if (row_w >= n) {                                         // no row for this wave, but the barriers count it
-            if (ready()) stage();
-            return;
-        }
-        last -= (last - row_w) % kWaves;                          // the wave's own last row
-        shift = (0u - uint32_t(wave) * cols) & 3u;
-    }
-    // With an odd number of column blocks the upper half-wave of the last strip has no columns (ragged: any number of
-    // its lanes).  Those lanes stay in the loop all the same, because every lane of the wave holds the scalars of one
-    // of its rows (below): they work on other columns a second time and only their stores are left out.
-    const uint32_t col_own = uint32_t(strip) * 256u + uint32_t(lane) * 4u + shift;
-    const bool live = col_own < cols;
-    const uint32_t col0 = live ? col_own : (RAGGED ? shift : col_own - 128u);
-    uint32_t col[4];
-    NextRow nx;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        nx.beyond[e] = RAGGED && col0 + e >= cols;
-        col[e] = nx.beyond[e] ? col0 + e - cols : col0 + e;
-    }
-    const TileBase tb = tile_base<BF16>(a, row0, n_stat);
-    // kDepth register sets take turns, the loop is unrolled by as many: the loads of kDepth - 1 rows are in flight while
-    // one is computed; a prefetch past the tile takes the tile's last row again and is never used.  Three sets where pass 2
-    // runs by itself; beside pass 1 in one launch its waves hold slots that pass 1 could use, and four sets, issued before
-    // the wait for pass 1, took the GPT-2-medium set from 849 to 837 us (six: 841, eight: 844; BERT-base 310, 303, 303,
-    // 303).  Ragged: the scalar offset counts from the wave's first row and the lane's from the tile's, both multiples of 4
-    // elements.
-    const uint32_t lane_e = RAGGED ? col0 + uint32_t(wave) * cols : col0;
-    const uint32_t lane_g = lane_e * (BF16 ? 2u : 4u), lane_q = lane_e >> 1;
-    const int row_b = RAGGED ? wave : 0;
-    auto fetch = [&](int il) { return load_row2<BF16>(tb, uint32_t((il < last ? il : last) - row_b) * cols, lane_g, lane_q); };   // il * cols < 2^29
-    constexpr int kDepth = SAME_LAUNCH ? 4 : 3;
-    auto put = [&](int il, uint32_t codes) {
-        if (live) __builtin_amdgcn_raw_buffer_store_b16(short(codes), tb.rvq, int(lane_q), int((uint32_t(il - row_b) * cols) >> 1), 0);
-    };
-    Row2<BF16> r[kDepth];
-    auto fill_sets = [&] {
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) r[u] = fetch(row(u));
-    };
-    if constexpr (SAME_LAUNCH) fill_sets();      // the wait for pass 1 is time to fetch in
-    if (!ready()) return;
-    stage();
-    // The scalars of the wave's rows (at most 64 per tile), one row per lane; the row loop fetches what it needs
-    // with v_readlane instead of two loads, a reciprocal, a select and two range checks per row.  Rows past the
-    // tile read as zeros through the bounds-checked resources.
-    auto scalars = [&](uint32_t il) {
-        RowScalars sc;
-        sc.r_old = buf_ld_f(tb.rr, il * 4u);
-        if constexpr (SAME_LAUNCH) sc.r_new = il < uint32_t(n_stat) ? s.blk_scale[il] : 0.0f;
-        else sc.r_new = buf_ld_f(tb.rr_new, il * 4u);
-        sc.r16 = sc.r_old * 0.0625f;
-        sc.inv = approx_inv16(sc.r_new);
-        const bool row_tame = bool(int(scale_is_tame(sc.r_old)) & int(scale_is_tame(sc.r_new)));
-        sc.wild = __ballot(!row_tame);
-        return sc;
-    };
-    RowScalars sc = scalars(uint32_t(row(lane)));
-    if constexpr (RAGGED) {
-        nx.sc = scalars(uint32_t(row(lane)) + 1u);
-        sc.wild |= nx.sc.wild;
-    }
-    float cold16[4], inv_cnew[4];
-    if constexpr (RAGGED) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cold16[e] = a.c[col[e]];
-    } else {
-        load4(a.c + col0, cold16);
-    }
-    if constexpr (SAME_LAUNCH) {
-        const uint32_t at = live ? col_own - uint32_t(strip) * 256u : 0u;         // other lanes: any column
-#pragma unroll
-        for (int e = 0; e < 4; ++e) inv_cnew[e] = s.col[at + e];
-    } else if constexpr (RAGGED) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) inv_cnew[e] = a.c_new[col[e]];
-    } else {
-        load4(a.c_new + col0, inv_cnew);
-    }
-    bool lane_tame = true;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(cold16[e])) & int(scale_is_tame(inv_cnew[e])));
-        cold16[e] *= 0.0625f;
-        inv_cnew[e] = approx_inv16(inv_cnew[e]);
-    }
-    if (__ballot(!lane_tame) != 0) sc.wild = ~uint64_t(0);        // a wild column scale: every row takes the exact route
-    auto codes_of = [&](const Row2<BF16>& r, int k) { return pass2_row<BF16, RAGGED, SAME_LAUNCH>(a, h, col, r, sc, nx, k, cold16, inv_cnew); };
-    int k = 0;
-    if constexpr (!SAME_LAUNCH) fill_sets();     // behind the scalars' loads, whose results the lines above work on
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);     // loop start-up state: nothing outstanding (see pass 1)
-    // Rounds of kDepth rows, no exit in the middle (see pass 1).  A register set is reloaded right after the row it held
-    // has been processed; the loads are pinned there, after the last use of the values they replace.
-    if (row(k + kDepth - 1) < n) do {
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) {
-            put(row(k + u), codes_of(r[u], k + u));
-            __builtin_amdgcn_sched_barrier(0);
-            r[u] = fetch(row(k + kDepth + u));
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        k += kDepth;
-    } while (row(k + kDepth - 1) < n);
-    // The rows that do not fill a round.  Beside pass 1 in one launch, where the tiles are tall, they are fetched again
-    // one by one: taking them from their sets needs 102 registers in place of 95 (fp32), four waves on a SIMD in place
-    // of five, and cost the BERT-base set 6 us of 302.
-    if constexpr (SAME_LAUNCH) {
-        for (; row(k) < n; ++k) put(row(k), codes_of(fetch(row(k)), k));
-    } else {
-#pragma unroll
-        for (int u = 0; u < kDepth - 1; ++u) {
-            if (row(k + u) >= n) break;
-            put(row(k + u), codes_of(r[u], k + u));
-        }
-    }
-}
-
-// The last row of a ragged tensor whose size is no multiple of 4, from the first multiple of 4 elements in it on: a
-// thread per byte of codes, exact arithmetic.  `part` counts workgroups of kLastRowElems elements.
+// Statistics tiles of ragged matrices (rows that are no multiple of 128 elements long) take groups of 4 consecutive elements,
+// aligned in the flattening; the last such group of a row may reach up to 3 elements into the next row.  Where that would
+// reach beyond the tensor (its size is no multiple of 4) the last row is left to workgroups of its own.
+__host__ __device__ __forceinline__ int64_t class_rows(const Tensor4& a) { return (a.P & 3) ? a.rows - 1 : a.rows; }
+// The last row of such a tensor, from the first multiple of 4 elements in it on, in parts of kLastRowElems elements.
 constexpr int kLastRowElems = kThreads * 8;
-__host__ __device__ __forceinline__ int64_t pass2_last_row_begin(const Tensor4& a) { return ((a.rows - 1) * a.cols + 3) / 4 * 4; }
-
-template <bool BF16, bool SAME_LAUNCH>
-__device__ __forceinline__ void pass2_last_row(const Tensor4& a, const Hyper& h, int part) {
-    const int64_t first = pass2_last_row_begin(a) + int64_t(part) * kLastRowElems;
-    const float r_old = a.r[a.rows - 1], r_new = ld_ws<SAME_LAUNCH>(a.r_new + a.rows - 1);
-    for (int u = 0; u < kLastRowElems / (2 * kThreads); ++u) {
-        const int64_t e0 = first + 2 * (int64_t(u) * kThreads + threadIdx.x);
-        if (e0 >= a.P) return;
-        uint8_t* byte = reinterpret_cast<uint8_t*>(a.vq) + (e0 >> 1);
-        const uint32_t q = *byte;
-        uint32_t out = 0;
-        for (int k = 0; k < 2 && e0 + k < a.P; ++k) {
-            const int64_t j = e0 + k - (a.rows - 1) * a.cols;
-            const float vt = moment_v(h, dequant_v((q >> (4 * k)) & 15u, fminf(r_old, a.c[j])), load_grad1<BF16>(a.g, e0 + k));
-            out |= quant_v_code(vt, fminf(r_new, ld_ws<SAME_LAUNCH>(a.c_new + j))) << (4 * k);
-        }
-        *byte = uint8_t(out);
-    }
-}
+__host__ __device__ __forceinline__ int64_t last_row_begin(const Tensor4& a) { return ((a.rows - 1) * a.cols + 3) / 4 * 4; }
 
 // =====================================================================================================
 // Block-wise second moment (1-dimensional or flattened tensors; Sec. 4.2, last paragraph): both
 // moments are normalized per block of 128 elements, nothing crosses a block, and the whole step is
-// ONE pass.  Same lane layout as pass 1 (4 elements per lane, 32 lanes per block).  The 8 groups of a
+// ONE pass.  Same lane layout as update_tile (4 elements per lane, 32 lanes per block).  The 8 groups of a
 // workgroup work 64 blocks = 32 KiB of parameters apart (the distance the memory system serves
-// fastest, as for the rows of pass 1): the tensor is cut into super-tiles of 8 x 64 blocks, group g
+// fastest, as for the rows there): the tensor is cut into super-tiles of 8 x 64 blocks, group g
 // owns blocks [64 g, 64 g + 64) of a super-tile, and a workgroup takes `rounds` consecutive blocks of
 // each of the 8 ranges, so 64 / rounds workgroups share a super-tile.  The tensor is a.P elements,
 // a.r holds the second moment's block scales.  The tile routine covers whole blocks; a ragged last
@@ -1268,6 +1102,7 @@ __device__ __forceinline__ void b128_tile(const Tensor4& a, const Hyper& h, int 
     auto fetch = [&](int k) { return load_rowb<BF16, SGDM>(tb, off(k)); };
     const int slot0 = grp * rounds;
     int k = 0;
+    const TableRegs tables = request_tables();
     RowB<BF16> r0 = fetch(0);
     RowB<BF16> r1 = fetch(1);
     RowB<BF16> r2;
@@ -1281,11 +1116,11 @@ __device__ __forceinline__ void b128_tile(const Tensor4& a, const Hyper& h, int 
             lane_tame = bool(int(lane_tame) & int(scale_is_tame(v)));
         }
     }
-    load_tables(s);                                // the first blocks' loads are in flight meanwhile; its barrier
-                                                   // also publishes the staged scales
+    put_tables(s, tables);
+    __syncthreads();                               // the first blocks' loads are in flight meanwhile
     bool tame = true;
     if constexpr (!SGDM) tame = !__syncthreads_or(int(!lane_tame));
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);       // loop start-up state: nothing outstanding (see pass 1)
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);       // loop start-up state: nothing outstanding (see update_tile)
     auto none = [] {};
     auto work = [&](const RowB<BF16>& cur, int kk, auto mid) { b128_row<BF16, SGDM>(h, tb, s, cur, off(kk), slot0 + kk, l, tame, mid); };
     while (k + 2 < rounds) {                       // rounds of three blocks, no exit in the middle
@@ -1422,10 +1257,10 @@ constexpr int kGenMaxChunks = 16;
 constexpr int kGenColsLds = 2048;                        // s.col and s.cold together
 constexpr int kGenRowsLds = 2 * kMaxRowSlots;            // s.blk_scale and s.blk_vmax together
 
-// elements [e_first, e_end) of the tensor; e_first is a multiple of 128, e_end the tensor's end or a multiple of 2048 behind
-// e_first
 template <bool BF16>
-__device__ __forceinline__ void pass1_general_range(const Tensor4& a, const Hyper& h, int64_t e_first, int64_t e_end, Lds& s) {
+__device__ __forceinline__ void pass1_general_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    const int64_t e_first = int64_t(wg) * a.rw * kGenChunkElems;
+    const int64_t e_end = e_first + int64_t(a.rw) * kGenChunkElems < a.P ? e_first + int64_t(a.rw) * kGenChunkElems : a.P;
     static_assert(offsetof(Lds, cold) == offsetof(Lds, col) + sizeof(float) * kColSlots, "col and cold are one array here");
     static_assert(offsetof(Lds, blk_vmax) == offsetof(Lds, blk_scale) + sizeof(float) * kMaxRowSlots, "row slots");
     unsigned int* col_l = reinterpret_cast<unsigned int*>(s.col);          // [kGenColsLds]
@@ -1536,13 +1371,6 @@ __device__ __forceinline__ void pass1_general_range(const Tensor4& a, const Hype
         }
 }
 
-template <bool BF16>
-__device__ __forceinline__ void pass1_general_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
-    const int64_t e_first = int64_t(wg) * a.rw * kGenChunkElems;
-    const int64_t e_end = e_first + int64_t(a.rw) * kGenChunkElems;
-    pass1_general_range<BF16>(a, h, e_first, e_end < a.P ? e_end : a.P, s);
-}
-
 // the 2048 elements from e_first (a multiple of 8) on
 template <bool BF16, bool SAME_LAUNCH = false>
 __device__ __forceinline__ void pass2_general_chunk(const Tensor4& a, const Hyper& h, int64_t e_first) {
@@ -1630,7 +1458,7 @@ __device__ __forceinline__ float wave_sum(float v) {
            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
 }
 
-// Statistics pass, fast path (cols % 128 == 0).  Tiled like pass 2: a wave works on 256 consecutive
+// Statistics pass, fast path (cols % 128 == 0): a wave works on 256 consecutive
 // columns of one row, the four waves of a workgroup take rows w, w+4, ... of a tile of rw2 rows.  Row
 // sums are staged in LDS, column sums are combined over the four waves in LDS; one atomic per row and
 // per column of the tile.
@@ -1660,7 +1488,7 @@ __device__ __forceinline__ void factor_stats_tile(const Tensor4& a, int wg, Lds&
         const float rsum = wave_sum((sq[0] + sq[1]) + (sq[2] + sq[3]));
         if (lane == 0) s.blk_scale[il] = rsum;
     };
-    // rows in the order of pass 2; three register sets take turns: a set is reloaded right after its row has been
+    // the waves' rows are 2^rs2 rows apart; three register sets take turns: a set is reloaded right after its row has been
     // summed, so the loads of two rows are in flight while a third is summed (more sets in flight measured slower)
     const int rs = a.rs2;
     const int row_w = wave << rs, hop = kWaves << rs, low = (1 << rs) - 1;
@@ -1738,7 +1566,7 @@ __device__ __forceinline__ RowF<BF16> load_rowf(const TileBase& b, uint32_t off4
 }
 
 // One row of the update pass for one lane; ct[e] = C_t of the lane's columns.  The row's old block scale and
-// R_t[i] / sum R_t come from LDS, where the tile staged them (see pass 1).
+// R_t[i] / sum R_t come from LDS, where the tile staged them (see update_tile).
 template <bool BF16, class Mid>
 __device__ __forceinline__ void factor_row(const Hyper& h, const TileBase& tb, const Geo& geo, Lds& s,
                                            const RowF<BF16>& cur, uint32_t off4, int slot, const float ct[4], Mid mid) {
@@ -1760,7 +1588,7 @@ __device__ __forceinline__ void factor_row(const Hyper& h, const TileBase& tb, c
         amax = fmaxf(amax, fabsf(mt[e]));
     }
     __builtin_amdgcn_sched_barrier(0);
-    mid();                                    // the caller's prefetch (see pass 1)
+    mid();                                    // the caller's prefetch (see update_tile)
     __builtin_amdgcn_sched_barrier(0);
     const float s_new = group32_allmax(amax);
 
@@ -1768,9 +1596,10 @@ __device__ __forceinline__ void factor_row(const Hyper& h, const TileBase& tb, c
     if (geo.l == 0) s.blk_scale[slot] = s_new;
 }
 
-// Update pass, fast path: tiled and pipelined like pass 1.  SAME_LAUNCH, ready: as in pass2_tile.
-template <bool BF16, bool SAME_LAUNCH = false, class Ready = AlwaysReady>
-__device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s, Ready ready = Ready()) {
+// Update pass, fast path: a group walks down the rows of one column block.
+template <bool BF16, bool SAME_LAUNCH, class Sync>
+__device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s, Sync& sync) {
+    const TableRegs tables = request_tables();
     const Geo geo = geometry(a, wg);
     const TileBase tb = tile_base<BF16>(a, geo.row0, geo.n_rows);
     const RowWalk walk{a.rs, a.gy << a.rs};
@@ -1782,9 +1611,9 @@ __device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper
     float ct[4], csum[4];
     RowF<BF16> r0 = fetch(0), r1 = fetch(1), r2;
     load4(a.c + geo.col0, ct);
-    if (!ready()) return;
+    if (!sync.ready()) return;
     float inv_total;
-    if constexpr (SAME_LAUNCH) {                 // through LDS, one agent-scope load per word (see pass2_tile)
+    if constexpr (SAME_LAUNCH) {                 // through LDS, one agent-scope load per word
         for (int t = threadIdx.x; t < a.gx * 128; t += kThreads) s.col[t] = ld_ws<true>(a.c_new + int64_t(geo.strip) * a.gx * 128 + t);
         if (threadIdx.x == 0) s.cold[0] = factor_inv_total<true>(a, h);
         __syncthreads();
@@ -1803,10 +1632,14 @@ __device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper
         s.blk_scale[t] = in ? tb.ms[row_offset(il, a.nb, uint32_t(cbi))] : 0.0f;
         s.blk_vmax[t] = in ? stat_ema(h, tb.r[il], ld_ws<SAME_LAUNCH>(tb.r_new + il)) * inv_total : 0.0f;
     }
-    load_tables(s);          // its barrier also publishes the staged values
+    put_tables(s, tables);
+    // every thread's statistics are here before the ticket is taken; and nothing is outstanding when the loop starts (see
+    // update_tile)
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
 #pragma unroll
     for (int e = 0; e < 4; ++e) ct[e] = stat_ema(h, ct[e], csum[e]);
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    sync.staged();
     auto none = [] {};
     auto work = [&](const RowF<BF16>& cur, int k, auto mid) {
         factor_row<BF16>(h, tb, geo, s, cur, off(k), slot0 + walk.at(k) * a.gx, ct, mid);
@@ -1829,7 +1662,8 @@ __device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper
     }
 }
 
-// stat[i] = stat_ema(stat[i], sum[i]); sum[i] = 0, by one workgroup (see move_and_clear)
+// stat[i] = stat_ema(stat[i], sum[i]); sum[i] = 0, by one workgroup (see move_statistics; reading the sums four at a time, which
+// takes the statistics apart into strided words, is the slower way here)
 template <bool SAME_LAUNCH = false>
 __device__ __forceinline__ void ema_and_clear(const Hyper& h, float* stat, float* sum, int64_t n) {
     constexpr int kDepth = 8;
@@ -1851,9 +1685,7 @@ __device__ __forceinline__ void ema_and_clear(const Hyper& h, float* stat, float
 
 // The last workgroup of a tensor's update pass makes R_t, C_t the state and clears the workspace;
 // every other workgroup has read the old statistics and the sums before it took its ticket.
-__device__ __forceinline__ void factor_publish_if_last(const Tensor4& a, const Hyper& h, unsigned int me,
-                                                       unsigned int participants, int& s_last) {
-    if (!last_to_arrive(a.counter, me, participants, s_last)) return;
+__device__ __forceinline__ void factor_publish(const Tensor4& a, const Hyper& h) {
     ema_and_clear(h, a.r, a.r_new, a.rows);
     ema_and_clear(h, a.c, a.c_new, a.cols);
     if (threadIdx.x == 0) *a.counter = 0u;

@@ -12,33 +12,34 @@ namespace lpmm {
 // =====================================================================================================
 
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass1_fast(const Tensor4 a, const Hyper h) {
+__global__ __launch_bounds__(kThreads) void maxima_fast(const Tensor4 a, const Hyper h) {
     __shared__ Lds s;
-    const int wg = logical_wg();
-    if (wg >= a.n_wg) return;
-    if (a.flat) pass1_flat_tile<BF16>(a, h, wg, s);
-    else pass1_fast_tile<BF16>(a, h, wg, s);
+    const int wg = logical_wg(a.skew);
+    if (wg < a.n_wg) maxima_tile<BF16>(a, h, wg, s);
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass2_fast(const Tensor4 a, const Hyper h) {
+__global__ __launch_bounds__(kThreads) void update_fast(const Tensor4 a, const Hyper h) {
+    __shared__ LdsRank1 s;
     __shared__ int s_last;
-    const int wg = logical_wg();
-    if (wg < a.n_wg2) pass2_tile<BF16>(a, h, wg);
-    publish_if_last(a, blockIdx.x, gridDim.x, s_last);
+    const int wg = logical_wg(a.skew2);
+    if (wg >= a.n_wg2) return;
+    TicketSync sync{a.counter, unsigned(wg), 0u};
+    update_tile<BF16, false>(a, h, wg, s, sync);
+    if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) publish(a);
 }
 
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void b128_kernel(const Tensor4 a, const Hyper h) {
     __shared__ Lds s;
-    const int wg = logical_wg();
+    const int wg = logical_wg(a.skew);
     if (wg < a.n_wg) b128_work<BF16>(a, h, wg, s);
 }
 
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void factor_stats_fast(const Tensor4 a) {
     __shared__ Lds s;
-    const int wg = logical_wg();
+    const int wg = logical_wg(a.skew);
     if (wg < a.n_wg) factor_stats_tile<BF16>(a, wg, s);
 }
 
@@ -46,9 +47,11 @@ template <bool BF16>
 __global__ __launch_bounds__(kThreads) void factor_update_fast(const Tensor4 a, const Hyper h) {
     __shared__ Lds s;
     __shared__ int s_last;
-    const int wg = logical_wg();
-    if (wg < a.n_wg2) factor_update_tile<BF16>(a, h, wg, s);
-    factor_publish_if_last(a, h, blockIdx.x, gridDim.x, s_last);
+    const int wg = logical_wg(a.skew2);
+    if (wg >= a.n_wg2) return;
+    TicketSync sync{a.counter, unsigned(wg), 0u};
+    factor_update_tile<BF16, false>(a, h, wg, s, sync);
+    if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) factor_publish(a, h);
 }
 
 template <bool BF16>
@@ -63,13 +66,13 @@ __global__ __launch_bounds__(kThreads) void factor_update_general(const Tensor4 
     __shared__ int s_last;
     load_tables(s);
     factor_update_general_tile<BF16>(a, h, blockIdx.x, s);
-    factor_publish_if_last(a, h, blockIdx.x, gridDim.x, s_last);
+    if (last_to_arrive(a.counter, blockIdx.x, gridDim.x, s_last)) factor_publish(a, h);
 }
 
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void factor_stats_ragged_kernel(const Tensor4 a) {
     __shared__ Lds s;
-    const int wg = logical_wg();
+    const int wg = logical_wg(a.skew);
     if (wg < a.n_wg) factor_stats_ragged<BF16>(a, wg, s);
 }
 
@@ -77,15 +80,15 @@ template <bool BF16>
 __global__ __launch_bounds__(kThreads) void factor_update_ragged_kernel(const Tensor4 a, const Hyper h) {
     __shared__ Lds s;
     __shared__ int s_last;
-    const int wg = logical_wg();
+    const int wg = logical_wg(a.skew2);
     if (wg < a.n_wg2) factor_update_ragged<BF16>(a, h, wg, s);
-    factor_publish_if_last(a, h, blockIdx.x, gridDim.x, s_last);
+    if (last_to_arrive(a.counter, blockIdx.x, gridDim.x, s_last)) factor_publish(a, h);
 }
 
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void sgdm4_kernel(const Tensor4 a, const Hyper h) {
     __shared__ Lds s;
-    const int wg = logical_wg();
+    const int wg = logical_wg(a.skew);
     if (wg < a.n_wg) b128_work<BF16, true>(a, h, wg, s);
 }
 
@@ -108,18 +111,21 @@ __global__ __launch_bounds__(kThreads) void pass2_general(const Tensor4 a, const
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass1_ragged_kernel(const Tensor4 a, const Hyper h) {
+__global__ __launch_bounds__(kThreads) void maxima_ragged_kernel(const Tensor4 a, const Hyper h) {
     __shared__ Lds s;
-    const int wg = logical_wg();
-    if (wg < a.n_wg) pass1_ragged<BF16>(a, h, wg, s);
+    const int wg = logical_wg(a.skew);
+    if (wg < a.n_wg) maxima_ragged<BF16>(a, h, wg, s);
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void pass2_ragged_kernel(const Tensor4 a, const Hyper h) {
+__global__ __launch_bounds__(kThreads) void update_ragged_kernel(const Tensor4 a, const Hyper h) {
+    __shared__ LdsRank1 s;
     __shared__ int s_last;
-    const int wg = logical_wg();
-    if (wg < a.n_wg2) pass2_ragged<BF16>(a, h, wg);
-    publish_if_last(a, blockIdx.x, gridDim.x, s_last);
+    const int wg = logical_wg(a.skew2);
+    if (wg >= a.n_wg2) return;
+    TicketSync sync{a.counter, unsigned(wg), 0u};
+    update_ragged<BF16, false>(a, h, wg, s, sync);
+    if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) publish(a);
 }
 
 template <bool BF16>
@@ -186,6 +192,7 @@ struct Phase {
     const Tensor4Table* tensors;
     int n_seg_a, n_seg_b;
     int n_a, n_b;           // workgroups of each kind
+    int skew_a, skew_b;     // of a launch of one kind, see logical_wg
     Segment seg_a[kMaxSeg];
     Segment seg_b[kMaxSeg];
 };
@@ -218,7 +225,8 @@ __device__ __forceinline__ Segment find_segment(const Segment* seg, int n_seg, i
 template <bool BF16, int ROLES>
 __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);
-    const int x = logical_wg();
+    __shared__ LdsRank1 s;
+    const int x = logical_wg(ROLES == 2 ? ph.skew_b : ph.skew_a);
     constexpr bool kOnlyA = ROLES == 1 || ROLES == 3;
     constexpr bool kOnlyB = ROLES == 2;
     const int n = (kOnlyB ? 0 : ph.n_a) + (kOnlyA ? 0 : ph.n_b);
@@ -230,13 +238,20 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
         __shared__ int s_last;
         const Segment sg = find_segment(ph.seg_b, ph.n_seg_b, b_before);
         const Tensor4 a = from_table(ph.tensors[sg.tensor]);
+        const Hyper ht = for_tensor(h, a);
         const int wg = b_before - sg.wg_begin;
-        if (a.kind == kQuantFast) pass2_tile<BF16>(a, h, wg);
-        else if (a.kind == kQuantRagged) pass2_ragged<BF16>(a, h, wg);
-        else pass2_general_chunk<BF16>(a, h, int64_t(wg) * kGenChunkElems);
-        publish_if_last(a, wg, a.n_wg2, s_last);
+        TicketSync sync{a.counter, unsigned(wg), 0u};
+        if (a.kind == kQuantFast) {
+            update_tile<BF16, false>(a, ht, wg, s, sync);
+        } else if (a.kind == kQuantRagged) {
+            update_ragged<BF16, false>(a, ht, wg, s, sync);
+        } else {
+            pass2_general_chunk<BF16>(a, h, int64_t(wg) * kGenChunkElems);
+            __syncthreads();
+            sync.staged();
+        }
+        if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) publish(a);
     } else if (!kOnlyB) {
-        __shared__ Lds s;
         const int xa = x - b_before;
         const Segment sg = find_segment(ph.seg_a, ph.n_seg_a, xa);
         const Tensor4 a = from_table(ph.tensors[sg.tensor]);
@@ -249,10 +264,9 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
         } else if (ROLES == 3) {
             // not reached: the host launches this variant only for groups without rank-1 tensors
         } else if (a.kind == kQuantFast) {
-            if (a.flat) pass1_flat_tile<BF16>(a, ht, wg, s);
-            else pass1_fast_tile<BF16>(a, ht, wg, s);
+            maxima_tile<BF16>(a, ht, wg, s);
         } else if (a.kind == kQuantRagged) {
-            pass1_ragged<BF16>(a, ht, wg, s);
+            maxima_ragged<BF16>(a, ht, wg, s);
         } else {
             pass1_general_tile<BF16>(a, ht, wg, s);
         }
@@ -386,7 +400,7 @@ template <bool BF16, int ROLES>
 __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);
     __shared__ Lds s;
-    const int x = logical_wg();
+    const int x = logical_wg(ROLES == 2 ? ph.skew_b : ph.skew_a);
     const int n = (ROLES == 2 ? 0 : ph.n_a) + (ROLES == 1 ? 0 : ph.n_b);
     if (x >= n) return;
     const int b_before = ROLES == 1 ? 0 : (ROLES == 2 ? x : int((int64_t(x) * ph.n_b) / n));
@@ -397,15 +411,20 @@ __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, 
         const Tensor4 a = from_table(ph.tensors[sg.tensor]);
         const Hyper ht = for_tensor(h, a);
         const int wg = b_before - sg.wg_begin;
+        TicketSync sync{a.counter, unsigned(wg), 0u};
         if (a.kind == kFactorFast) {
-            factor_update_tile<BF16>(a, ht, wg, s);
-        } else if (a.kind == kFactorRagged) {
-            factor_update_ragged<BF16>(a, ht, wg, s);
+            factor_update_tile<BF16, false>(a, ht, wg, s, sync);
         } else {
-            load_tables(s);
-            factor_update_general_tile<BF16>(a, ht, wg, s);
+            if (a.kind == kFactorRagged) {
+                factor_update_ragged<BF16>(a, ht, wg, s);
+            } else {
+                load_tables(s);
+                factor_update_general_tile<BF16>(a, ht, wg, s);
+            }
+            __syncthreads();
+            sync.staged();
         }
-        factor_publish_if_last(a, h, wg, a.n_wg2, s_last);
+        if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) factor_publish(a, h);
     } else if (ROLES != 2) {
         const int xa = x - b_before;
         const Segment sg = find_segment(ph.seg_a, ph.n_seg_a, xa);
@@ -426,7 +445,7 @@ template <bool BF16>
 __global__ __launch_bounds__(kThreads) void sgdm_phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);
     __shared__ Lds s;
-    const int x = logical_wg();
+    const int x = logical_wg(ph.skew_a);
     if (x >= ph.n_a) return;
     const Segment sg = find_segment(ph.seg_a, ph.n_seg_a, x);
     const Tensor4 a = from_table(ph.tensors[sg.tensor]);

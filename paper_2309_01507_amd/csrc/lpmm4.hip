@@ -124,9 +124,15 @@ bool is_rank1(int kind) { return kind == kQuantFast || kind == kQuantRagged || k
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 int pad8(int64_t n) { return int(round_up(n, kXcds)); }
 
-// Geometry of the fast path.  gx column blocks share a workgroup (so that one workgroup touches
-// whole 128-byte lines of codes and runs of block scales), gy = 8/gx groups walk interleaved
-// rows of the same column blocks and combine their column maxima in LDS.  rw_hint > 0 fixes the
+// workgroups (of n, for `elems` elements) that make up kSkewElems elements, at least 1
+int skew_of(int64_t n, int64_t elems) { return int(std::max<int64_t>(1, int64_t(double(n) * double(kSkewElems) / double(std::max<int64_t>(elems, 1)) + 0.5))); }
+void set_skew(Tensor4* t) {
+    t->skew = skew_of(t->n_wg, t->P);
+    t->skew2 = skew_of(t->n_wg2, t->P);
+}
+
+// Geometry of the factorized form's fast path (its update tiles in the members of the first pass; the caller swaps them).  gx
+// column blocks share a workgroup, gy = 8/gx groups walk interleaved rows of the same column blocks.  rw_hint > 0 fixes the
 // rows per workgroup; otherwise they are chosen so that the tensor alone fills the chip.
 // log2 of the smallest S in {1, 2, 4, 8} for which S rows of `row_bytes` bytes are a multiple of 32 KiB; 0 if
 // there is none.  Rows in flight side by side then lie 32 KiB apart, which is what the memory system serves
@@ -143,7 +149,7 @@ int row_spacing_log2(int64_t row_bytes, int64_t rows_per_tile, int groups, const
     return 0;
 }
 
-void fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes, bool flat_default = false) {
+void fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes) {
     a->nb = int(a->cols / LPMM_BLOCK);
     int gx = env_int("LPMM_GX", 1);
     if (gx < 1 || gx > kGroups || (gx & (gx - 1))) gx = 1;
@@ -169,28 +175,6 @@ void fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int 
     a->rw = int(rw);
     a->n_wg = int(a->strips * ((a->rows + rw - 1) / rw));
     a->rs = row_spacing_log2(a->cols * 4, rw, a->gy, "LPMM_RS");      // the parameters' rows
-    a->flat = 0;
-    // Flat tiling of pass 1 (strips of 8 column blocks, the 8 groups take rows, each walks along its row): the
-    // caller decides (flat_default); LPMM_FLAT = 0 / 1 overrides.
-    const int flat_env = env_int("LPMM_FLAT", -1);
-    const bool want_flat = flat_env >= 0 ? flat_env != 0 : flat_default;
-    if (want_flat && a->kind == kQuantFast) {
-        a->flat = 1;
-        a->gx = 1; a->gy = kGroups;
-        a->strips = (a->nb + kFlatBlocks - 1) / kFlatBlocks;
-        int64_t rwf = env_int("LPMM_RW", 0);
-        if (rwf <= 0) rwf = rw_hint > 0 ? rw_hint : 32;
-        if (rwf > 64) rwf = 64;                                   // rw * 8 block results are staged in LDS
-        const int64_t capf = (int64_t(1) << 29) / a->cols;
-        if (rwf > capf) rwf = capf;
-        rwf = round_up(rwf, kGroups);
-        if (rwf > capf || rwf > 64) rwf -= kGroups;
-        if (rwf > a->rows) rwf = round_up(a->rows, kGroups);
-        if (rwf < kGroups) rwf = kGroups;
-        a->rw = int(rwf);
-        a->n_wg = int(a->strips * ((a->rows + rwf - 1) / rwf));
-        a->rs = row_spacing_log2(a->cols * 4, rwf, kGroups, "LPMM_RS");
-    }
     // pass 2: strips of 256 columns, a wave per row
     a->strips2 = (a->nb + 1) / 2;
     int64_t rw2 = env_int("LPMM_RW2", 0);
@@ -200,12 +184,70 @@ void fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int 
         while (rw2 > kWaves && a->strips2 * ((a->rows + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 >>= 1;
     }
     if (rw2 > cap) rw2 = cap;
-    if (rw2 > kMaxRw2) rw2 = kMaxRw2;                       // a wave of pass 2 keeps its rows' scalars one per lane
+    if (rw2 > kMaxRw2) rw2 = kMaxRw2;
     if (rw2 > a->rows) rw2 = a->rows;
     if (rw2 < 1) rw2 = 1;
     a->rw2 = int(rw2);
     a->n_wg2 = int(a->strips2 * ((a->rows + rw2 - 1) / rw2));
     a->rs2 = row_spacing_log2(a->cols * grad_bytes, rw2, kWaves, "LPMM_RS2");   // pass 2 mostly reads the gradient
+}
+
+// Geometry of the rank-1 step on the fast path.
+// First pass (maxima): strips of 256 columns by rw2 rows.  Second pass (update): strips of gx (at most 8) column blocks by rw
+// rows.  n_cu > 0: a tensor stepped on its own, whose tiles are cut until each pass has two workgroups per CU; else `shrink`
+// halvings of a plan's tiles.
+void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes, int shrink = 0) {
+    a->nb = int(a->cols / LPMM_BLOCK);
+    const int64_t cap = std::max<int64_t>((int64_t(1) << 29) / a->cols, kGroups);     // lane offsets inside a tile stay below 2^31 bytes
+    const int n_strips = (a->nb + kFlatBlocks - 1) / kFlatBlocks;
+    int gx = (a->nb + n_strips - 1) / n_strips;
+    const int gx_env = env_int("LPMM_GX", 0);
+    if (gx_env > 0) gx = std::min(gx_env, kFlatBlocks);
+    // rows of a group: a power of two
+    int per_log2 = 0;
+    // two of them; one where a large matrix is stepped on its own (32000 x 4096 fp32 400 us, with two 405; 11008 x 4096 bf16 111.5
+    // and 113.8; 4096 x 4096 bf16 46.9 and 46.2)
+    const int64_t rw_want = env_int("LPMM_RW", 0) > 0 ? env_int("LPMM_RW", 0) : rw_hint > 0 ? rw_hint : n_cu > 0 && a->P >= int64_t(1) << 25 ? 8 : 16;
+    const bool fixed = env_int("LPMM_RW", 0) > 0;
+    while (per_log2 < 3 && (kGroups << (per_log2 + 1)) <= rw_want) ++per_log2;
+    // Rows between the groups: 32 KiB of parameters where a power of two of rows is exactly that long (rows of 128 to 8192
+    // elements, a power of two), unless a super-tile of 8 times as many would leave much of itself empty; else next to each
+    // other.
+    int rs = 0;
+    const int forced = env_int("LPMM_RS", -1);
+    if (forced >= 0) rs = std::min(forced, 6);
+    else if (a->cols <= 8192 && (a->cols & (a->cols - 1)) == 0) {
+        while ((a->cols << rs) < 8192) ++rs;
+        per_log2 = std::min(per_log2, rs);
+        if (round_up(a->rows, int64_t(kGroups) << rs) > a->rows + a->rows / 16) rs = 0;
+    }
+    while (rs > 0 && (int64_t(kGroups) << rs) * a->cols > (int64_t(1) << 29)) --rs;
+    while (per_log2 > 0 && (kGroups << per_log2) >= 2 * a->rows) --per_log2;
+    auto tiles = [&] { return int64_t((a->nb + gx - 1) / gx) * (((a->rows + (kGroups << std::max(rs, per_log2)) - 1) >> (3 + std::max(rs, per_log2))) << (std::max(rs, per_log2) - per_log2)); };
+    auto cut = [&] {
+        if (per_log2 > 0 && !fixed) --per_log2;
+        else if (gx > 1 && gx_env <= 0) gx = (gx + 1) / 2;
+        else return false;
+        return true;
+    };
+    while (per_log2 > 0 && ((int64_t(kGroups) << per_log2) * a->cols) > (int64_t(1) << 29)) --per_log2;
+    if (n_cu > 0) { while (tiles() < 2 * int64_t(n_cu) && cut()) {} }
+    for (int k = 0; k < shrink && cut(); ++k) {}
+    a->gx = gx;
+    a->gy = kGroups;
+    a->rw = kGroups << per_log2;
+    a->rs = std::max(rs, per_log2);
+    a->strips = (a->nb + gx - 1) / gx;
+    a->n_wg2 = int(tiles());
+    a->strips2 = (a->nb + 1) / 2;
+    int64_t rw2 = env_int("LPMM_RW2", 0);
+    const bool fixed2 = rw2 > 0;
+    if (rw2 <= 0) rw2 = rw2_hint > 0 ? rw2_hint : 128;
+    rw2 = std::clamp<int64_t>(rw2, 1, std::min<int64_t>({cap, kMaxRowSlots, a->rows}));
+    while (n_cu > 0 && !fixed2 && rw2 > 2 * kGroups && a->strips2 * ((a->rows + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 = round_up(rw2 / 2, kGroups);
+    a->rw2 = int(rw2);
+    a->n_wg = int(a->strips2 * ((a->rows + rw2 - 1) / rw2));
+    a->rs2 = row_spacing_log2(a->cols * grad_bytes, rw2, kGroups, "LPMM_RS2");
 }
 
 // Tiling of a tensor whose second moment is block-wise: super-tiles of 8 x 64 blocks, each shared by
@@ -256,28 +298,27 @@ bool ragged_eligible(int64_t rows, int64_t cols) {
            !env_int("LPMM_FORCE_GENERAL", 0);
 }
 
-// Tiling of the ragged path (see ragged.hpp).
-// Pass 1, one strip: a tile touches every column, so every tile ends with an atomic per column, and atomics on one
-// address follow each other at about 18 ns (measured: 648 tiles of a 2304 x 576 tensor took 31 us, whatever they held).
-// With T tiles that is 18 ns x T against blocks / (8 T) units of about half a microsecond one after the other in a
-// group: T = sqrt(3.5 x blocks) balances the two, in tiles of 8 to 128 blocks (a power of two).
-// Wider: strips of equal width, at most 1024 columns, by 32 rows; the rows are halved down to one per group and then
-// the strips down to 256 columns while the tensor would give the chip fewer than two workgroups per CU (n_cu = 0: `shrink` halvings
-// of the rows instead, for plans).
-// Pass 2: strips of 256 columns by 64 rows (plans: 128), halved down to 4 in the same way; a multiple of 4.
+// Tiling of the ragged path (see ragged.hpp): the first pass takes statistics of strips of 256 columns by rw2 rows, the second
+// updates whole blocks.
+// Update, cols <= 1024: tiles of 8 to 128 consecutive blocks.  Wider: strips of equal width, at most 1024 columns, by 32
+// rows; the rows are halved down to one per group and then the strips down to 256 columns.  Both shrink while the tensor
+// would give the chip fewer than two workgroups per CU (n_cu = 0: `shrink` halvings instead, for plans).
+// Statistics: 64 rows (plans: 128), halved down to 4 in the same way; a multiple of 4.  Every tile ends with an atomic per
+// column, and atomics on one address follow each other at about 18 ns, so a tall narrow matrix takes more rows to a tile
+// than the filling of the chip alone would ask for: rows / rw2 of them against a quarter of rw2 rows, about 0.3 us each, one
+// after the other in a wave balance at rw2 = sqrt(rows / 4) (factorized form of 2000 x 190 with fp32 gradients: 16.5 us per
+// step, 29.8 without this).
 void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
-    a->kind = kQuantRagged;
     a->nb = int(a->P / LPMM_BLOCK);
     const int tail = (a->P % LPMM_BLOCK) ? 1 : 0;
     constexpr int64_t kWide = kFlatBlocks * LPMM_BLOCK;
     if (a->cols <= kWide) {
         a->strips = 1;
         a->sw = int(a->cols);
-        const double tiles = std::sqrt(3.5 * double(a->nb));
-        int64_t rw = 128;
-        while (rw > kGroups && double(rw) * tiles > double(a->nb) * 1.4) rw /= 2;
+        int64_t rw = std::max<int64_t>(128 >> shrink, kGroups);
+        while (rw > kGroups && (a->nb + rw - 1) / rw < 2 * int64_t(n_cu)) rw /= 2;
         a->rw = int(rw);
-        a->n_wg = int((a->nb + rw - 1) / rw) + tail;
+        a->n_wg2 = int((a->nb + rw - 1) / rw) + tail;
     } else {
         int64_t rw = 32, sw = kWide, tiles;
         while (rw > kGroups && rw * a->cols > (int64_t(1) << 28)) rw /= 2;        // byte offsets inside a tile stay below 2^30
@@ -293,17 +334,18 @@ void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
             else break;
         }
         a->rw = int(rw);
-        a->n_wg = int(tiles) + tail;
+        a->n_wg2 = int(tiles) + tail;
     }
     a->strips2 = int((a->cols + 255) / 256);
-    const int64_t rows2 = pass2_rows(*a, true);
+    const int64_t rows2 = class_rows(*a);
     int64_t rw2 = n_cu ? 64 : std::max<int64_t>(128 >> shrink, kWaves);
     while (rw2 > kWaves && rw2 * a->cols >= (int64_t(1) << 29)) rw2 /= 2;
     while (n_cu && rw2 > kWaves && a->strips2 * ((rows2 + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 /= 2;
+    while (rw2 < 64 && rw2 * rw2 < a->rows / 4 && rw2 * a->cols < (int64_t(1) << 28)) rw2 *= 2;
     a->rw2 = int(rw2);
     a->rs2 = 0;
-    a->n_wg2 = int(a->strips2 * ((rows2 + rw2 - 1) / rw2));
-    if (rows2 != a->rows) a->n_wg2 += int((a->P - pass2_last_row_begin(*a) + kLastRowElems - 1) / kLastRowElems);
+    a->n_wg = int(a->strips2 * ((rows2 + rw2 - 1) / rw2));
+    if (rows2 != a->rows) a->n_wg += int((a->P - last_row_begin(*a) + kLastRowElems - 1) / kLastRowElems);
 }
 
 // pass 1 or 2 of the rank-1 step on one tensor
@@ -312,11 +354,11 @@ void launch_pass(int pass, const Tensor4& t, const Hyper& h, hipStream_t s) {
     const int n = pass == 1 ? t.n_wg : t.n_wg2;
     const dim3 grid(t.kind == kQuantGeneral ? n : pad8(n)), block(kThreads);
     if (t.kind == kQuantFast) {
-        if (pass == 1) hipLaunchKernelGGL(pass1_fast<BF16>, grid, block, 0, s, t, h);
-        else hipLaunchKernelGGL(pass2_fast<BF16>, grid, block, 0, s, t, h);
+        if (pass == 1) hipLaunchKernelGGL(maxima_fast<BF16>, grid, block, 0, s, t, h);
+        else hipLaunchKernelGGL(update_fast<BF16>, grid, block, 0, s, t, h);
     } else if (t.kind == kQuantRagged) {
-        if (pass == 1) hipLaunchKernelGGL(pass1_ragged_kernel<BF16>, grid, block, 0, s, t, h);
-        else hipLaunchKernelGGL(pass2_ragged_kernel<BF16>, grid, block, 0, s, t, h);
+        if (pass == 1) hipLaunchKernelGGL(maxima_ragged_kernel<BF16>, grid, block, 0, s, t, h);
+        else hipLaunchKernelGGL(update_ragged_kernel<BF16>, grid, block, 0, s, t, h);
     } else {
         if (pass == 1) hipLaunchKernelGGL(pass1_general<BF16>, grid, block, 0, s, t, h);
         else hipLaunchKernelGGL(pass2_general<BF16>, grid, block, 0, s, t, h);
@@ -327,8 +369,9 @@ void launch_pass(int pass, const Tensor4& t, const Hyper& h, hipStream_t s) {
 void rank1_geometry(Tensor4* t, int n_cu, int grad_bytes) {
     if (fast_eligible(t->cols, t->c)) {
         t->kind = kQuantFast;
-        fast_geometry(t, n_cu, 0, 0, grad_bytes);
+        rank1_fast_geometry(t, n_cu, 0, 0, grad_bytes);
     } else if (ragged_eligible(t->rows, t->cols)) {
+        t->kind = kQuantRagged;
         ragged_geometry(t, n_cu, 0);
     } else {
         t->kind = kQuantGeneral;
@@ -422,6 +465,7 @@ int step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, float*
     t.cols = cols;
     t.P = rows * cols;
     rank1_geometry(&t, ctx->n_cu, bf16 ? 2 : 4);
+    set_skew(&t);
     return bf16 ? launch_step<true>(t, h, s) : launch_step<false>(t, h, s);
 }
 
@@ -451,6 +495,7 @@ int b128_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, f
     t.P = numel;
     t.kind = kQuantBlockV;
     b128_geometry(&t, ctx->n_cu, 0);
+    set_skew(&t);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls;
     const int64_t call = g_prof.calls;
@@ -505,6 +550,7 @@ int sgdm4_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, 
     t.cols = numel;
     t.P = numel;
     b128_geometry(&t, ctx->n_cu, 0);
+    set_skew(&t);
     t.kind = kSgdmBlock;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls;
@@ -578,6 +624,7 @@ int nd_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, flo
     t.cols = cols;
     t.P = rows * cols;
     rank1_geometry(&t, ctx->n_cu, bf16 ? 2 : 4);
+    set_skew(&t);
     hipStream_t s = static_cast<hipStream_t>(stream);
     auto pass = [&](int p) -> int {
         if (bf16) launch_pass<true>(p, t, h, s); else launch_pass<false>(p, t, h, s);
@@ -625,17 +672,7 @@ void factor_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, in
         std::swap(a->n_wg, a->n_wg2);
         a->kind = kFactorFast;
     } else if (!a->det && ragged_eligible(a->rows, a->cols)) {
-        // The tiles of the rank-1 step, its pass 2's for the statistics.  Those end with an atomic per column here, and
-        // atomics on one address follow each other at about 18 ns, so a tall narrow matrix takes more rows to a tile than
-        // the filling of the chip alone would ask for: rows / rw2 of them against a quarter of rw2 rows, about 0.3 us each,
-        // one after the other in a wave balance at rw2 = sqrt(rows / 4) (2000 x 190 with
-        // fp32 gradients: 16.5 us per step, 29.8 without this, 19.7 on the general tiles).
         ragged_geometry(a, rw_hint == 0 ? n_cu : 0, shrink);
-        const int64_t rows2 = pass2_rows(*a, true);
-        const int rest = a->n_wg2 - int(a->strips2 * ((rows2 + a->rw2 - 1) / a->rw2));     // parts of the last row
-        while (a->rw2 < 64 && int64_t(a->rw2) * a->rw2 < a->rows / 4 && a->rw2 * a->cols < (int64_t(1) << 28)) a->rw2 *= 2;
-        a->n_wg2 = int(a->strips2 * ((rows2 + a->rw2 - 1) / a->rw2)) + rest;
-        std::swap(a->n_wg, a->n_wg2);
         a->kind = kFactorRagged;
     } else {
         general_geometry(a, n_cu);          // statistics pass: several chunks per workgroup; update pass: one
@@ -676,6 +713,7 @@ int factor_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes,
     t.P = rows * cols;
     const bool fast = fast_eligible(cols, v_col);
     factor_geometry(&t, ctx->n_cu, 0, 0, bf16 ? 2 : 4, fast, kMaxTotSlots);
+    set_skew(&t);
     const bool ragged = t.kind == kFactorRagged;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls;
@@ -722,9 +760,9 @@ struct PlanHost {
     bool bf16 = false;
     bool factor = false;                // the plan's 2-dimensional tensors keep a factorized second moment
     bool sgdm = false;                  // a plan of SGD-with-momentum tensors (lpmm_sgdm4_step_multi)
-    bool flat = false;                  // large tensors, several groups: pass 1 uses the flat tiling
     bool serial = false;                // LPMM_MULTI_STREAMS=0: every pass a launch of its own on the caller's stream
     bool flow = false;                  // the whole step is one launch (flow.hpp)
+    bool flow_any = false;              // ... with ragged matrices or rows shorter than 128 elements
     FlowArgs flow_args{};
     int64_t params = 0;                 // parameters of all tensors of the plan
     Hyper* d_hyper = nullptr;           // device slot inside the plan for the hyper-parameters of a captured step
@@ -781,19 +819,27 @@ bool plan_inner_dims(const lpmm_tensor_desc& d, int64_t i, const int64_t* inner_
 // Tiles of one tensor of a plan that is stepped in one launch; `total`: parameters of the plan.  A function of the shapes
 // alone, because the size of the plan's memory follows from it.
 //
-// Pass 1 walks down its rows, 64 of them (GPT-2-medium set 838 us, BERT-base 305; 32 rows: 918 and 328, 128: 817 and 314),
-// except in tensors of 2^24 parameters and more with wide rows, whose strips it walks along their rows, 16 rows at a time
-// (7B-shaped set 16.4 ms, with fp32 gradients 20.4; 8 rows 16.8 and 20.7, 32 rows 17.4 and 21.0, down 64 rows 16.6 and 20.6).
-// Pass 2 takes 128 rows (64 rows: GPT-2-medium 846 us, BERT-base 303, 7B-shaped 17.5 ms; 256: 841, 314, 16.2 to 16.5).  Sets of
-// less than 2^25 parameters (they are here for the sake of their convolutions) take shorter tiles to have enough of them:
-// vision sets of 7.4 million parameters 58, 44, 41 and 52 us with the rows divided by 1, 2, 4 and 8, of 20 million 83, 75, 88
-// and 124.
+// Statistics tiles are 256 rows tall (8 x llama-like layers of 4096, bf16 gradients 4.24 ms, GPT-2-medium set 792 us, BERT-base
+// 302; 128 rows: 4.28, 811, 305; 512: 4.56, 836, 333): every tile ends with an atomic per row and column.  Update tiles hold
+// two rows per group (one row: 4.33 ms and 821 us; four: 4.62 ms, since rows of 4096 cannot be 32 KiB apart then).
+// Sets of less than 2^25 parameters (they are here for the sake of their convolutions) take shorter tiles to have enough of
+// them: a vision set of 7.4 million parameters takes 45, 38, 42 and 44 us with statistics tiles of 128, 32, 16 rows and of 64
+// rows.
 constexpr int64_t kFlowMinParams = int64_t(1) << 25;
+// Parameters of second passes between the first pass of a tensor and its own second pass: what is in flight on the chip at a
+// time, and a little more, so that a second pass finds its first one complete.  In one piece, 12, 16, 20 and 24 million:
+// GPT-2-medium set 793, 790, 794 and 796 us, BERT-base 324, 303, 307 and 303, 8 llama layers 4.31, 4.24, 4.24 and 4.25 ms.
+// Spread, 12, 16, 20 and 24: factorized GPT-2-medium 790, 711, 717 and 717, factorized BERT-base 313, 284, 276 and 275, 8
+// factorized llama layers 3.94, 3.82, 3.82 and 3.84 ms, rank-1 with rows of 1472 1344, 1297, 1272 and 1273.
+constexpr double kFlowLead = 16.0 * (1 << 20), kFlowLeadSpread = 20.0 * (1 << 20);
+// Unused dynamic LDS of the one launch: four workgroups on a CU instead of five (rank-1, plain rows: GPT-2-medium 799 us without,
+// 790 with), five instead of six (factorized: 747 us at six, 711 at five, 730 at four).  More of them only move the point up to
+// which the list has been handed out further ahead of the first passes that the second ones wait for.
+constexpr unsigned kFlowLdsPad = 16000, kFlowLdsPadFactor = 8000;
 void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int grad_bytes) {
     constexpr int kCus = 256;
     const int shrink = total >= kFlowMinParams ? 0 : total >= kFlowMinParams / 4 ? 1 : 2;
-    const bool flat = t->P >= (int64_t(1) << 24) && t->cols >= 2048;
-    const int rw = flat ? std::max(16 >> shrink, kGroups) : 64 >> shrink, rw2 = 128 >> shrink;
+    const int rw = 16, rw2 = shrink ? 32 : 256;
     if (desc_kind == LPMM_KIND_FP32) {
         t->kind = kFp32State;
         t->n_wg = t->n_wg2 = int((t->P + kElemsPerWg32 - 1) / kElemsPerWg32);
@@ -805,9 +851,10 @@ void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int
                         fast_eligible(t->cols, nullptr), 1, shrink);
     } else if (aligned_c && fast_eligible(t->cols, nullptr)) {
         t->kind = kQuantFast;
-        fast_geometry(t, kCus, rw, rw2, grad_bytes, flat);
+        rank1_fast_geometry(t, 0, rw, rw2, grad_bytes, shrink ? 1 : 0);
     } else if (ragged_eligible(t->rows, t->cols)) {
-        ragged_geometry(t, 0, shrink);
+        t->kind = kQuantRagged;
+        ragged_geometry(t, 0, shrink ? 3 : 0);
     } else {
         t->kind = kQuantGeneral;
         general_geometry(t, kCus);
@@ -819,7 +866,7 @@ bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast |
 // fixed order, and the statistics of tensors with more than two dimensions are few enough for one workgroup.  It is where
 // that is faster (us, phases / one launch; where two pairs are given, fp32 and bf16 gradients):
 // - Sets of 2^25 parameters or more (transformers with an embedding: 35 M 116 / 110, 99 / 98; 66 M 220 / 189, 180 / 162;
-//   131 M 408 / 363, 328 / 297; 498 M 1708 / 1418, 1356 / 1187).  Below, there is little in flight to hide a tensor's wait
+//   131 M 408 / 363, 328 / 297; 498 M 1708 / 1418, 1356 / 1187; measured when the first pass still was the update).  Below, there is little in flight to hide a tensor's wait
 //   between the passes behind (8.4 M 43 / 49, 39 / 47; 16.7 M 63 / 61, 55 / 56; 24 M 82 / 82, 72 / 75; factorized 29 M 88 /
 //   89, 74 / 80).
 // - Not sets of which one tensor is most, whose second pass finds little to run beside: rank-1 up to three quarters,
@@ -830,10 +877,10 @@ bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast |
 // - Not sets of nothing but two to eight matrices of about one size, up to 2^25 parameters each: 2 of 4096 x 4096 105 / 128,
 //   90 / 110; 4 of them 197 / 224, 164 / 187; 8 398 / 412, 313 / 341; 12 604 / 596, 482 / 493; 4 of 8192 x 8192 817 / 768,
 //   654 / 623.  Launches by phases lose time to unequal tiles, and these have none.
-// - Not sets of which the general tiles (rows shorter than 128) are a large part: in one kernel with the others they have
-//   fewer waves in flight.  Rank-1 up to two fifths of the parameters (3000 x 100: 0.3 635 / 469, 506 / 436; 0.4 676 / 518,
-//   551 / 499; 0.5 567 / 592, 516 / 580; all 762 / 885, 735 / 900), factorized up to half (adapters 64 x 4096 and 4096 x 64:
-//   406 / 354, 394 / 337; all narrow 1006 / 1140, 1007 / 1138).
+// - Not sets of which the general tiles (rows shorter than 128) are most: in one kernel with the others they have fewer waves
+//   in flight.  Rank-1 up to three fifths of the parameters (30000 x 96 beside 1024 x 4096, bf16 and fp32 gradients: 0.25 233
+//   / 203, 297 / 218; 0.4 376 / 298, 470 / 327; 0.58 282 / 277, 336 / 275; 0.85 401 / 456, 436 / 470; all 352 / 460, 363 /
+//   469), factorized up to half (adapters 64 x 4096 and 4096 x 64: 406 / 354, 394 / 337; all narrow 486 / 571, 478 / 572).
 // - Sets with tensors of more than two dimensions, which by phases take four dependent launches, also below 2^25 parameters
 //   (a vision set of 7.4 M 61 / 41, 56 / 38; 8 of 128 x 128 x 3 x 3 34 / 24; 2048 x 4096 and one of 64 x 64 x 3 x 3 46 /
 //   42), unless it is one large tensor alone (1024 x 1024 x 3 x 3 67 / 73; 640 x 640 x 3 x 3 44 / 44).  From 2^25 on the
@@ -870,7 +917,7 @@ bool flow_possible(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inne
     if (n_second == 0) return false;
     const int64_t least = env_int("LPMM_FLOW_MIN", int(kFlowMinParams));
     if (least == 0) return true;
-    if (factor ? general > total / 2 : general > total / 5 * 2) return false;
+    if (factor ? general > total / 2 : general >= total / 2) return false;
     if (nd > 0 && (total < least || nd >= total / 32)) return n_second > 1 || total <= (int64_t(1) << 22);
     if (total < least || largest > (factor ? total / 4 : total / 4 * 3)) return false;
     int64_t n_large = 0, large = 0;                  // tensors of about the largest one's size
@@ -940,19 +987,20 @@ bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_
 // The work list of a plan that is stepped in one launch, and the tensors' tiles for it; leaves the plan to the
 // launches by groups if the list does not fit (column maxima that turned out misaligned give more tiles).
 //
-// Both passes are laid on a time line in units of parameters: pass 1 of the tensors one after the other; pass 2 of a tensor
-// starts a lag after its pass 1 ends -- about what is in flight on the chip at a time, so that it finds the first pass
-// complete -- and takes as long as its pass 1 did.  2^23 parameters: with 2^22, 2^23, 2^24 and 2^25 the BERT-base set takes
-// 306, 309, 317 and 335 us, the GPT-2-medium set 835, 836, 853 and 873, the 7B-shaped one 16.42, 16.45, 16.50 and 16.56 ms;
-// 16 matrices of 4096 x 4096 825, 791, 780 and 767 us, their bf16 form 693, 659, 634 and 623.  Tensors with more than two
-// dimensions come first, the widest ones ahead: one workgroup turns their maxima into statistics between the passes, and
-// that takes longest where there are many columns.  Then the largest ones: what is left at the end, a pass 2 with no pass 1
-// beside it, is that of the smallest (as listed, large embeddings last / by size: 56 M parameters 206 / 152 us, 143 M 469 /
-// 408).
+// The second passes follow each other; the first pass of a tensor is put kFlowLead parameters of second passes in front of its own
+// one.  It reads little (the gradient and, rank-1, the second moment's codes), nothing else of the step stays in the memory-side
+// cache (parameters pass it by: non-temporal), and so the second pass reads what the first one read from there.  In place of that
+// the first passes were the updates before, with the codes' second pass 2^23 parameters behind: 7B-shaped set 16.5 ms, now 14.9;
+// GPT-2-medium 843 us, now 790; with all first passes ahead of all second ones 949.
+// The first pass of a tensor on the plain tiles goes in one piece, others spread over the length of the tensor (spread / in one
+// piece: factorized GPT-2-medium 711 / 738 us; rank-1 with rows of 1472 1272 / 1297; but rank-1 with rows of 4096 4.29 / 4.24
+// ms).  Tensors with more than two dimensions come first, the widest ones ahead: one workgroup turns their maxima into
+// statistics between the passes, and that takes longest where there are many columns.  Then the largest ones: what is left at
+// the end is the second pass of the smallest.
 //
-// The two are merged by time, eight workgroups at a time: ids are dealt to the 8 XCDs in turn, and the eight of a row take
-// their tiles from eight equal contiguous parts of the pass, so that neighbouring tiles, which share cache lines, stay on
-// one XCD.  (Merging in runs of up to 2^25 parameters instead of single rows makes no difference.)
+// Workgroups are laid out eight at a time: ids are dealt to the 8 XCDs in turn, and the eight of a row take their tiles from eight
+// equal contiguous parts of the pass (skewed as in logical_wg), so that neighbouring tiles, which share cache lines, stay on one
+// XCD.
 void build_flow(const lpmm_tensor_desc* descs, int64_t n, const PlanLayout& L, char* dplan, int gbytes, PlanHost* host,
                 Tensor4* tens) {
     int64_t total = 0, n_def = 0;
@@ -960,7 +1008,6 @@ void build_flow(const lpmm_tensor_desc* descs, int64_t n, const PlanLayout& L, c
     std::vector<Tensor4> flow(tens, tens + n);
     for (int64_t i = 0; i < n; ++i) {
         Tensor4& t = flow[i];
-        t.flat = 0;
         flow_geometry(&t, descs[i].kind, aligned(descs[i].v_colmax, 16), total, gbytes);
         if (t.kind == kFactorRagged) return;
         if (flow_kind_second(t.kind)) {
@@ -969,59 +1016,78 @@ void build_flow(const lpmm_tensor_desc* descs, int64_t n, const PlanLayout& L, c
         }
     }
     if (n_def > L.cap_deferred) return;
-    struct Row { double time; FlowItem it[kXcds]; };
-    std::vector<Row> first, second;
-    // tiles of one pass in rows of 8; a pass of fewer than 8 workgroups shares its row with the following ones
-    auto add = [](std::vector<Row>& rows, int what, int n_wg, double begin, double length, int* fill) {
+    struct Row { FlowItem it[kXcds]; };
+    // tiles of one pass in rows of 8; a pass of fewer than 8 workgroups shares the row of the ones before it
+    struct Open { std::vector<Row>* rows = nullptr; int fill = 0; };
+    auto add = [](std::vector<Row>& rows, int what, int n_wg, int64_t elems, Open* open) {
         if (n_wg < kXcds) {
             for (int w = 0; w < n_wg; ++w) {
-                if (*fill == 0) rows.push_back(Row{begin, {{-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}}});
-                rows.back().time = begin;                           // not before the last of its members may start
-                rows.back().it[*fill] = FlowItem{what, w};
-                *fill = (*fill + 1) % kXcds;
+                if (open->fill == 0) {
+                    rows.push_back(Row{{{-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}, {-1, 0}}});
+                    open->rows = &rows;
+                }
+                open->rows->back().it[open->fill] = FlowItem{what, w};
+                open->fill = (open->fill + 1) % kXcds;
             }
             return;
         }
-        *fill = 0;
-        const int part = (n_wg + kXcds - 1) / kXcds;
+        open->fill = 0;
+        const int part = (n_wg + kXcds - 1) / kXcds, skew = skew_of(n_wg, elems);
         for (int k = 0; k < part; ++k) {
-            Row r{begin + length * k / part, {}};
+            Row r{};
             for (int x = 0; x < kXcds; ++x) {
-                const int w = x * part + k;
+                const int w = x * part + (k + x * skew) % part;            // as in logical_wg
                 r.it[x] = w < n_wg ? FlowItem{what, w} : FlowItem{-1, 0};
             }
             rows.push_back(r);
         }
     };
-    const double lag = double(int64_t(1) << 23);
-    double now = 0.0, now2 = 0.0;
-    int fill1 = 0, fill2 = 0;
     std::vector<int64_t> order(static_cast<size_t>(n));
     std::iota(order.begin(), order.end(), int64_t(0));
     std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) {
         const bool nx = descs[x].kind == LPMM_KIND_4BIT_ND, ny = descs[y].kind == LPMM_KIND_4BIT_ND;
         return nx != ny ? nx : nx ? flow[x].cols > flow[y].cols : flow[x].P > flow[y].P;
     });
-    for (const int64_t i : order) {
-        const double length = double(flow[i].P);
-        add(first, int(i), flow[i].n_wg, now, length, &fill1);
-        now += length;
-        if (!flow_kind_second(flow[i].kind)) continue;
-        now2 = std::max(now2, now + lag);
-        add(second, int(i) | kFlowSecond, flow[i].n_wg2, now2, length, &fill2);
-        now2 += length;
+    struct Passes { std::vector<Row> first, second; };
+    std::vector<Passes> passes(order.size());
+    Open open1, open2;
+    for (size_t k = 0; k < order.size(); ++k) {
+        const Tensor4& t = flow[order[k]];
+        const int id = int(order[k]);
+        if (flow_kind_second(t.kind)) {
+            add(passes[k].first, id, t.n_wg, t.P, &open1);
+            add(passes[k].second, id | kFlowSecond, t.n_wg2, t.P, &open2);
+        } else {
+            add(passes[k].second, id, t.n_wg, t.P, &open2);
+        }
     }
-    const int64_t n_items = int64_t(first.size() + second.size()) * kXcds;
-    if (n_items > L.cap_items) return;
-    FlowItem* items = reinterpret_cast<FlowItem*>(host->staging.data() + L.off_items);
+    struct Timed { double time; Row row; };
+    std::vector<Timed> first, second;
+    double begin = 0.0;
+    for (size_t k = 0; k < order.size(); ++k) {
+        const Tensor4& t = flow[order[k]];
+        const double length = double(t.P), n1 = double(passes[k].first.size()), n2 = double(passes[k].second.size());
+        const double spread = t.kind == kQuantFast ? 0.0 : length;
+        for (const Row& r : passes[k].first)
+            first.push_back(Timed{begin - (spread > 0.0 ? kFlowLeadSpread : kFlowLead) - spread * (1.0 - double(&r - passes[k].first.data()) / n1), r});
+        for (const Row& r : passes[k].second) second.push_back(Timed{begin + length * double(&r - passes[k].second.data()) / n2, r});
+        begin += length;
+    }
+    std::stable_sort(first.begin(), first.end(), [](const Timed& x, const Timed& y) { return x.time < y.time; });
+    std::vector<Row> rows;
     size_t a = 0, b = 0;
     while (a < first.size() || b < second.size()) {
         const bool take_first = b == second.size() || (a < first.size() && first[a].time <= second[b].time);
-        const Row& r = take_first ? first[a++] : second[b++];
-        for (int x = 0; x < kXcds; ++x) *items++ = r.it[x];
+        rows.push_back(take_first ? first[a++].row : second[b++].row);
     }
+    const int64_t n_items = int64_t(rows.size()) * kXcds;
+    if (n_items > L.cap_items) return;
+    FlowItem* items = reinterpret_cast<FlowItem*>(host->staging.data() + L.off_items);
+    for (const Row& r : rows)
+        for (int x = 0; x < kXcds; ++x) *items++ = r.it[x];
     std::copy(flow.begin(), flow.end(), tens);
     host->flow = true;
+    for (const Tensor4& t : flow) host->flow_any = host->flow_any || t.kind == kQuantRagged || t.kind == kQuantGeneral || t.kind == kFactorGeneral;
     host->flow_args.tensors = reinterpret_cast<const Tensor4Table*>(dplan + L.off_tensors);
     host->flow_args.items = reinterpret_cast<const FlowItem*>(dplan + L.off_items);
     host->flow_args.dims = reinterpret_cast<const InnerDims*>(dplan + L.off_dims);
@@ -1609,13 +1675,6 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
 
     const int64_t rw_hint = env_int("LPMM_MULTI_RW", -1);      // -1: the plan defaults (64 rows, 32 for the flat tiling)
     const int64_t rw2_hint = env_int("LPMM_MULTI_RW2", 128);
-    // Flat tiling of pass 1 for the large tensors of this plan, if it is stepped by phases (a plan stepped in one launch
-    // takes its tiles from flow_geometry)?  Measured: 3-4 % faster on the 7B-shaped set stepped that way, where
-    // pass 1 runs beside pass 2 of the previous group; 4 % slower for one large tensor alone (one group, the passes
-    // run one after the other); slower on sets of small tensors, whose tiles become too few; and a launch that
-    // mixes many cheap tiles with a few four times more expensive flat ones loses 20 % to imbalance between the
-    // XCDs.  So: only in plans with several groups whose rank-1 parameters are at least 90 % in large tensors.
-    constexpr int64_t kFlatMinElems = int64_t(1) << 23;
     // parameters per group of consecutive tensors: large groups win (fewer kernel tails); cutting a set that fits
     // one group into three so that its pass 2 has a pass 1 to run beside gave -3 % on the 108 M set, nothing on
     // the 354 M set and +1.4 % on its factorized form, so it is not done
@@ -1629,23 +1688,6 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         for (int64_t i = 0; i < n; ++i) total += descs[i].rows * descs[i].cols;
         const int64_t k = (n + kMaxSeg - 1) / kMaxSeg;
         group_params = std::min(group_params, total / k + total / (10 * k) + 1);
-    }
-    bool plan_flat = false;
-    {
-        const int64_t gp = group_params;
-        int64_t p_rank1 = 0, p_big = 0, acc = 0, in_group = 0, n_groups = 0;
-        for (int64_t i = 0; i < n; ++i) {
-            const int64_t P = descs[i].rows * descs[i].cols;
-            if ((descs[i].kind == LPMM_KIND_4BIT || descs[i].kind == LPMM_KIND_4BIT_ND) &&
-                fast_eligible(descs[i].cols, descs[i].v_colmax)) {
-                p_rank1 += P;
-                if (P >= kFlatMinElems) p_big += P;
-            }
-            if (in_group == 0 || in_group >= kMaxSeg || acc + P > gp) { ++n_groups; acc = 0; in_group = 0; }
-            acc += P;
-            ++in_group;
-        }
-        plan_flat = n_groups > 1 && p_rank1 > 0 && p_big * 10 >= p_rank1 * 9;
     }
     // Tiling of one quantized tensor of the plan.  shrink = 0 gives the plan's default tiles (sized for sets that
     // fill the chip many times over); each further level halves the rows (blocks) a workgroup takes, for groups of
@@ -1663,7 +1705,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         } else if (d.kind == LPMM_KIND_4BIT_FACTOR) {
             factor_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1, shrink);
         } else if (t.kind == kQuantFast) {
-            fast_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, plan_flat && t.P >= kFlatMinElems);
+            rank1_fast_geometry(&t, 0, rw_hint > 0 ? rw_hint : 0, std::max<int64_t>(rw2_hint >> shrink, kGroups), gbytes, shrink);
         } else if (t.kind == kQuantRagged) {
             ragged_geometry(&t, 0, shrink);
         }
@@ -1761,7 +1803,6 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             if (fast_eligible(d.cols, d.v_colmax)) {
                 t.kind = kQuantFast;
                 set_geometry(t, d, 0);
-                if (t.flat) host->flat = true;
             } else if (ragged_eligible(d.rows, d.cols)) {
                 t.kind = kQuantRagged;
                 set_geometry(t, d, 0);
@@ -1805,12 +1846,17 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     }
     for (size_t j = 0; j <= groups.size() && !host->flow; ++j) {
         PhaseLaunch pl{};
+        int64_t elems_a = 0, elems_b = 0;
+        int64_t general = 0;                // of the parameters, those on the rank-1 form's general tiles
+        auto count = [&](const Tensor4& t) { if (t.kind == kQuantGeneral) general += t.P; };
         pl.ph.tensors = reinterpret_cast<const Tensor4Table*>(d_tens);
         if (j < groups.size())
             for (int64_t i = groups[j].first; i < groups[j].second; ++i) {
                 pl.ph.seg_a[pl.ph.n_seg_a++] = Segment{pl.ph.n_a, int(i)};
                 if (is_rank1(tens[i].kind)) pl.a_has_rank1 = true;
                 pl.ph.n_a += tens[i].n_wg;
+                elems_a += tens[i].P;
+                count(tens[i]);
             }
         if (j >= 1)
             for (int64_t i = groups[j - 1].first; i < groups[j - 1].second; ++i) {
@@ -1819,6 +1865,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
                     continue;
                 pl.ph.seg_b[pl.ph.n_seg_b++] = Segment{pl.ph.n_b, int(i)};
                 pl.ph.n_b += tens[i].n_wg2;
+                elems_b += tens[i].P;
+                count(tens[i]);
                 if (tens[i].det) {
                     pl.has_det = true;
                     pl.det.seg_r[pl.det.n_seg++] = Segment{pl.det.n_r, int(i)};
@@ -1837,17 +1885,24 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         pl.nd.dims = d_dims;
         pl.det.tensors = pl.ph.tensors;
         if (pl.ph.n_a + pl.ph.n_b == 0) continue;
+        // The general tiles' first pass is most of their work, the other tiles' second pass is: eighths of a launch that has both
+        // give some XCDs several times the work of others (30000 x 96 beside 1024 x 4096, bf16 gradients: 0.4 of the parameters
+        // in the narrow ones 376 us in eighths, 319 in runs; 0.58 282 and 267; 0.85 401 and 422).
+        const bool mixed = general > 0 && general * 3 < (elems_a + elems_b) * 2;
+        pl.ph.skew_a = mixed ? -1 : skew_of(pl.ph.n_a, elems_a);
+        pl.ph.skew_b = mixed ? -1 : skew_of(pl.ph.n_b, elems_b);
         if (int64_t(pl.ph.n_a) + pl.ph.n_b > (int64_t(1) << 30)) return LPMM_EINVAL;
-        pl.grid = pad8(int64_t(pl.ph.n_a) + pl.ph.n_b);
-        pl.grid_a = pad8(pl.ph.n_a);
-        pl.grid_b = pad8(pl.ph.n_b);
+        auto grid_of = [&](int64_t n) { return mixed ? int(round_up(n, kXcds * kDealRun)) : pad8(n); };
+        pl.grid = grid_of(int64_t(pl.ph.n_a) + pl.ph.n_b);
+        pl.grid_a = grid_of(pl.ph.n_a);
+        pl.grid_b = grid_of(pl.ph.n_b);
         host->phases.push_back(pl);
     }
     // A second stream pays only if some pass 2 has a pass 1 of another group to run beside.  Factorized plans take
     // their launches one after the other on the caller's stream by default: the statistics pass (read-only) and the
     // update pass each run at the memory system's rate alone, and side by side they only get in each other's way
     // (7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
-    const int stream_mode = env_int("LPMM_MULTI_STREAMS", host->factor ? 0 : 2);
+    const int stream_mode = env_int("LPMM_MULTI_STREAMS", 0);
     host->serial = stream_mode == 0 && !host->sgdm;
     bool any_b = false;
     for (const PhaseLaunch& pl : host->phases) any_b = any_b || pl.ph.n_b > 0;
@@ -1931,13 +1986,13 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         const int64_t call = g_prof.calls;
         if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), s));
         const dim3 grid(unsigned(host->flow_args.n_items)), block(kThreads);
-        if (host->factor) {
-            if (bf16) hipLaunchKernelGGL((flow_kernel<true, true>), grid, block, 0, s, host->flow_args, h);
-            else hipLaunchKernelGGL((flow_kernel<false, true>), grid, block, 0, s, host->flow_args, h);
-        } else {
-            if (bf16) hipLaunchKernelGGL((flow_kernel<true, false>), grid, block, 0, s, host->flow_args, h);
-            else hipLaunchKernelGGL((flow_kernel<false, false>), grid, block, 0, s, host->flow_args, h);
-        }
+#define LPMM_FLOW_CASE(F)                                                                                   \
+        if (bf16) hipLaunchKernelGGL((flow_kernel<true, F>), grid, block, host->flow_any ? 0 : host->factor ? kFlowLdsPadFactor : kFlowLdsPad, s, host->flow_args, h);        \
+        else hipLaunchKernelGGL((flow_kernel<false, F>), grid, block, host->flow_any ? 0 : host->factor ? kFlowLdsPadFactor : kFlowLdsPad, s, host->flow_args, h);
+        if (host->factor) { LPMM_FLOW_CASE(kFlowFactor) }
+        else if (host->flow_any) { LPMM_FLOW_CASE(kFlowRank1Any) }
+        else { LPMM_FLOW_CASE(kFlowRank1) }
+#undef LPMM_FLOW_CASE
         LPMM_HIP(hipGetLastError());
         if (rec) {
             LPMM_HIP(hipEventRecord(prof_event(call, 1), s));
@@ -1946,17 +2001,12 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         }
         return LPMM_OK;
     }
-    // Plans stepped by phases with the flat tiling run their pass-1 launches with unused dynamic LDS, so that three instead
-    // of five workgroups share a CU: two waves per SIMD already saturate pass 1 on large tensors, and more of them only
-    // take issue slots and memory queues from the pass 2 that runs beside (measured on the 7B-shaped set: 1 % less time per
-    // step with bf16 gradients, 1-3 % with fp32 gradients; sets of small tensors lose 4 %, so not there).
-    const unsigned lds_pad = unsigned(std::clamp(env_int("LPMM_P1_LDS_PAD", host->flat ? 22528 : 0), 0, 45056));
     const unsigned pad3 = one_pass_lds_pad(*host);
     // roles: 0 = A and B work in one launch, 1 = A only, 2 = B only, 3 = A only without rank-1 tensors
     auto launch = [&](int roles, int grid, hipStream_t on, const PhaseLaunch& pl) {
 #define LPMM_PHASE_CASE(K, R)                                                                               \
-        if (bf16) hipLaunchKernelGGL((K<true, R>), dim3(grid), dim3(kThreads), (R == 1 ? lds_pad : R == 3 ? pad3 : 0), on, pl.ph, h);            \
-        else hipLaunchKernelGGL((K<false, R>), dim3(grid), dim3(kThreads), (R == 1 ? lds_pad : R == 3 ? pad3 : 0), on, pl.ph, h);
+        if (bf16) hipLaunchKernelGGL((K<true, R>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);            \
+        else hipLaunchKernelGGL((K<false, R>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);
         if (host->factor) {
             if (roles == 0) { LPMM_PHASE_CASE(factor_phase_kernel, 0) }
             else if (roles == 2) { LPMM_PHASE_CASE(factor_phase_kernel, 2) }
@@ -1969,6 +2019,8 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         }
 #undef LPMM_PHASE_CASE
     };
+    bool two_pass = false;
+    for (const PhaseLaunch& pl : host->phases) two_pass = two_pass || pl.ph.n_b > 0;
     if (host->side || host->serial) {
         // A work of phase j on the caller's stream, B work (pass 2 of the tensors whose pass 1 ran
         // in phase j-1) on the side stream behind an event; the caller's stream rejoins at the end.
@@ -1996,8 +2048,8 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
             }
             if (pl.ph.n_b > 0) {
                 if (two && !tail) LPMM_HIP(hipStreamWaitEvent(s2, host->ev_a[j - 1], 0));
-                // a factorized plan's heavy kernel is its B work (the update pass): that one is timed
-                const bool rec = host->factor && g_prof.on && g_prof.calls < g_prof.max_calls;
+                // the heavy kernel of a plan with two passes is its B work (the update pass): that one is timed
+                const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls;
                 const int64_t call = g_prof.calls;
                 if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), s2));
                 if (pl.has_nd) LPMM_CHECK(launch_nd(pl, s2));
@@ -2012,7 +2064,7 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
             }
             hipStream_t sa = (host->side_a && (j & 1)) ? host->side_a : s;
             if (pl.ph.n_a > 0) {
-                const bool rec = !host->factor && g_prof.on && g_prof.calls < g_prof.max_calls;
+                const bool rec = !two_pass && g_prof.on && g_prof.calls < g_prof.max_calls;
                 const int64_t call = g_prof.calls;
                 if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), sa));
                 launch(pl.a_has_rank1 ? 1 : 3, pl.grid_a, sa, pl);
@@ -2038,8 +2090,8 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         return LPMM_OK;
     }
     for (const PhaseLaunch& pl : host->phases) {
-        // as on the two-stream route, only launches that carry pass 1 (factorized plans: the update pass) are timed
-        const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls && (host->factor ? pl.ph.n_b > 0 : pl.ph.n_a > 0);
+        // as on the other route, only launches that carry the update are timed
+        const bool rec = g_prof.on && g_prof.calls < g_prof.max_calls && (two_pass ? pl.ph.n_b > 0 : pl.ph.n_a > 0);
         const int64_t call = g_prof.calls;
         if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), s));
         // a launch that holds only one kind of work takes that kind's (lighter) kernel

@@ -1,16 +1,14 @@
-// Pass 1 of the rank-1 step, and further down both passes of the factorized one, for matrices whose rows are no multiple of
-// 128 elements long (or whose column maxima are not 16-byte aligned).  First-moment blocks are 128 elements of the
-// row-major FLATTENING, so here they start anywhere in a row and may straddle the end of one.
+// Both passes of the rank-1 and of the factorized step for matrices whose rows are no multiple of 128 elements long (or
+// whose column maxima are not 16-byte aligned).  First-moment blocks are 128 elements of the row-major FLATTENING, so here
+// they start anywhere in a row and may straddle the end of one.
 //
-// What bounds the step is memory, as on the fast path, so the work unit is the fast path's: 32 lanes own one block, 4
-// consecutive elements per lane, and every access is aligned because blocks start at multiples of 128 elements.  A
+// What bounds the step is memory, as on the fast path, so the second pass' work unit is the fast path's: 32 lanes own one
+// block, 4 consecutive elements per lane, and every access is aligned because blocks start at multiples of 128 elements.  A
 // block belongs to the row and to the strip of columns in which it STARTS.  Positions inside a tile are counted from
 // the strip's first column, p = 0 .. width + 127: a block that starts in the strip may reach up to 127 columns beyond
-// it, and beyond the end of the row position p continues with the next row's first columns.  The strip's old column
-// maxima and the running new ones sit in LDS indexed by p, so only the row of an element needs a compare per element.
-// (Before, a lane owned 8 elements, tracked row and column of each with 64-bit arithmetic, divided exactly, and for
-// more than 2048 columns sent every maximum to a global atomic: 554 + 225 us for 1024 x 50257 with bf16 gradients, now
-// 120 + 55 us, 4.9 TB/s in this pass.)
+// it, and beyond the end of the row position p continues with the next row's first columns.  The strip's column vectors sit in
+// LDS indexed by p, so only the row of an element needs a compare per element.  (1024 x 50257 with bf16 gradients: 779 us per
+// step on the general kernels, 170 with the maxima taken per element in the update, 161 with the passes as they are.)
 //
 // Two ways to cut a matrix (chosen by the host):
 //   cols <= 1024:  one strip; a tile is a run of a.rw consecutive blocks, each of the 8 groups of a workgroup takes an
@@ -19,8 +17,8 @@
 //                  of its row that start in the strip.  In the last strip their number varies by one from row to row;
 //                  a unit that does not exist gets an offset beyond the tile, where loads return zeros and stores are
 //                  dropped.
-// The partial last block of a tensor whose size is no multiple of 128 is left to one workgroup of the general path.
-// (Pass 2 needs none of this: nothing in it is reduced over a block, see pass2_tile.)
+// The partial last block of a tensor whose size is no multiple of 128 is left to one workgroup with exact arithmetic.
+// The first pass needs none of this: nothing in it is reduced over a block, see maxima_ragged_tile.
 #pragma once
 
 #include "kernels.hpp"
@@ -28,7 +26,6 @@
 namespace lpmm {
 
 constexpr int kRagRowSlots = kMaxRowSlots / 2;            // s.blk_vmax: old row maxima, then the new ones
-constexpr uint32_t kRagNowhere = 0x7FFFFF00u;             // a byte offset beyond every tile (also after >> 1 and >> 3)
 
 struct RagTile {
     int64_t e0;          // first element of the tile's first block (a multiple of 128)
@@ -46,7 +43,7 @@ struct RagTile {
 };
 
 struct RagUnit {         // one block
-    uint32_t off4;       // byte offset of the block in the tile's fp32 array, kRagNowhere if it does not exist
+    uint32_t off4;       // byte offset of the block in the tile's fp32 array, kNowhere if it does not exist
     int il;              // its row in the tile
     int p;               // position of its first element in that row
     int slot;            // its slot among the staged block scales
@@ -102,7 +99,7 @@ __device__ __forceinline__ RagUnit rag_unit(const RagTile& t, const Tensor4& a, 
         const uint32_t x = ok ? uint32_t(b) * 128u - uint32_t(t.f0) : 0u;
         u.il = int(__umulhi(x, t.inv_cols));
         u.p = int(x) - u.il * t.width;
-        u.off4 = ok ? uint32_t(b) * 512u : kRagNowhere;
+        u.off4 = ok ? uint32_t(b) * 512u : kNowhere;
         u.slot = b;
     } else {
         const int k = int((uint32_t(q) * ((65536u + uint32_t(t.per_row) - 1u) / uint32_t(t.per_row))) >> 16);   // q / per_row
@@ -112,7 +109,7 @@ __device__ __forceinline__ RagUnit rag_unit(const RagTile& t, const Tensor4& a, 
         const int b = ((f + 127) >> 7) + j;
         u.p = b * 128 - f;
         const bool ok = u.il < t.own_rows && u.p < t.width && b < t.end;
-        u.off4 = ok ? uint32_t(b) * 512u : kRagNowhere;
+        u.off4 = ok ? uint32_t(b) * 512u : kNowhere;
         u.slot = u.il * kFlatBlocks + j;
     }
     return u;
@@ -144,19 +141,162 @@ __device__ __forceinline__ TileBase rag_base(const Tensor4& a, const RagTile& t)
     return b;
 }
 
-// One block of pass 1.  l = lane of the group.
+// First pass: row and column maxima of v_t.  A wave takes 256 consecutive columns of one row, a lane 4 elements aligned in
+// the flattening: the lanes of row i start at the first multiple of 4 at or behind i * cols, `shift` = -i * cols mod 4 columns
+// into the row, and that shift is the same for all rows a wave takes (they are a multiple of 4 apart), so that a lane's
+// columns are fixed down the tile.  Columns are counted on through the end of a row: positions cols, cols + 1, cols + 2 are
+// the next row's first ones, whose maxima the row's last lane collects for that row.
+constexpr int kSpan = 264;                                        // positions of a strip: 256, a shift and a lane's 4
+static_assert(4 * kSpan <= kColSlots && kMaxRw2 + 1 < kColSlots && kMaxRw2 < kMaxRowSlots, "statistics of a tile are staged in LDS");
+
+template <bool BF16>
+__device__ __forceinline__ void maxima_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    const int strip = wg % a.strips2, tile = wg / a.strips2;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int lane = threadIdx.x & 63;
+    const int64_t row0 = int64_t(tile) * a.rw2;                   // a multiple of 4
+    const int64_t left = class_rows(a) - row0;
+    const int n = left < a.rw2 ? int(left) : a.rw2;
+    const int n_stat = row0 + n < a.rows ? n + 1 : n;
+    const uint32_t cols = uint32_t(a.cols);
+    const uint32_t shift = (0u - uint32_t(wave) * cols) & 3u;
+    const uint32_t at = uint32_t(lane) * 4u + shift, col0 = uint32_t(strip) * 256u + at;
+    const bool live = col0 < cols;
+    const int64_t e0 = row0 * a.cols;
+    const uint32_t elems = uint32_t(n_stat) * cols;
+    const Rsrc rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + e0 * (BF16 ? 2 : 4), elems * (BF16 ? 2u : 4u));
+    const Rsrc rv = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (e0 >> 1), elems >> 1);
+    const int last = n - 1 - (n - 1 - wave) % kWaves;             // the wave's own last row, if it has any (wave < n)
+    struct Row { GradRegs4<BF16> g; uint16_t vq; };
+    auto ld = [&](int il) {
+        Row r;
+        const uint32_t e = uint32_t(il < last ? il : last) * cols + col0;
+        r.g = load_grad_regs4<BF16>(rg, live ? e * 4u : kNowhere);
+        r.vq = buf_ld_u16(rv, live ? e >> 1 : kNowhere);
+        return r;
+    };
+    // columns of the lane's elements, zeros for lanes without any: their moments are zero then
+    float c16[4], cmax[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    uint32_t col[4];
+    bool lane_tame = true, beyond[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        beyond[e] = col0 + e >= cols;
+        col[e] = live ? (beyond[e] ? col0 + e - cols : col0 + e) : 0u;
+        const float c = live ? a.c[col[e]] : 0.0f;
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(c)));
+        c16[e] = c * 0.0625f;
+    }
+    for (int t = threadIdx.x; t < 4 * kSpan; t += kThreads) s.col[t] = 0.0f;
+    for (int t = threadIdx.x; t <= n; t += kThreads) {
+        const float r = t < n_stat ? a.r[row0 + t] : 0.0f;
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
+        s.blk_scale[t] = r * 0.0625f;
+        s.blk_vmax[t] = 0.0f;
+        s.cold[t] = 0.0f;
+    }
+    const bool tame = !__syncthreads_or(int(!lane_tame));         // else the exact route for the whole tile
+    auto one = [&](const Row& x, int il) {
+        float g[4], vt[4], own = 0.0f, next = 0.0f;
+        unpack_grad4<BF16>(x.g, g);
+        if (__builtin_expect(tame, 1)) {
+            float qf[4];
+            codes_to_float4(x.vq, qf);
+            const float ra = s.blk_scale[il], rb = s.blk_scale[il + 1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(beyond[e] ? rb : ra, c16[e]));
+        } else {
+            const float ra = a.r[row0 + il], rb = il + 1 < n_stat ? a.r[row0 + il + 1] : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) vt[e] = live ? dequant_v((uint32_t(x.vq) >> (4 * e)) & 15u, fminf(beyond[e] ? rb : ra, a.c[col[e]])) : 0.0f;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            vt[e] = fmaxf(moment_v(h, vt[e], g[e]), 0.0f);        // a NaN raises no maximum
+            cmax[e] = fmaxf(cmax[e], vt[e]);
+            own = fmaxf(own, beyond[e] ? 0.0f : vt[e]);
+            next = fmaxf(next, beyond[e] ? vt[e] : 0.0f);
+        }
+        own = group32_allmax(own);
+        own = fmaxf(own, __shfl_xor(own, 32));
+        if (lane == 0) s.blk_vmax[il] = own;
+        if (live && col0 + 3u >= cols) s.cold[il + 1] = next;     // one lane of the last strip
+    };
+    constexpr int kDepth = 3;
+    Row r[kDepth];
+    auto row = [&](int k) { return wave + k * kWaves; };
+    int k = 0;
+    if (wave < n) {
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) r[u] = ld(row(u));
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        if (row(k + kDepth - 1) < n) do {
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u) {
+                one(r[u], row(k + u));
+                __builtin_amdgcn_sched_barrier(0);
+                r[u] = ld(row(k + kDepth + u));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            k += kDepth;
+        } while (row(k + kDepth - 1) < n);
+#pragma unroll
+        for (int u = 0; u < kDepth - 1; ++u)
+            if (row(k + u) < n) one(r[u], row(k + u));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s.col[wave * kSpan + at + e] = cmax[e];
+    __syncthreads();
+    for (int t = threadIdx.x; t < n_stat; t += kThreads) {
+        const float m = fmaxf(s.blk_vmax[t], s.cold[t]);
+        if (m > 0.0f) atomic_max_nonneg(a.r_new + row0 + t, m);
+    }
+    for (int t = threadIdx.x; t < kSpan; t += kThreads) {
+        const uint32_t c = uint32_t(strip) * 256u + uint32_t(t);
+        const float m = fmaxf(fmaxf(s.col[t], s.col[kSpan + t]), fmaxf(s.col[2 * kSpan + t], s.col[3 * kSpan + t]));
+        if (m > 0.0f && c < cols + 3u) atomic_max_nonneg(a.c_new + (c < cols ? c : c - cols), m);
+    }
+}
+
+// The part of the last row that the tiles leave out.
+template <bool BF16>
+__device__ __forceinline__ void maxima_last_row(const Tensor4& a, const Hyper& h, int part) {
+    const int64_t first = last_row_begin(a) + int64_t(part) * kLastRowElems;
+    const float r_old = a.r[a.rows - 1];
+    float rmax = 0.0f;
+    for (int u = 0; u < kLastRowElems / kThreads; ++u) {
+        const int64_t e = first + int64_t(u) * kThreads + threadIdx.x;
+        if (e >= a.P) break;
+        const int64_t j = e - (a.rows - 1) * a.cols;
+        const uint32_t q = (reinterpret_cast<const uint8_t*>(a.vq)[e >> 1] >> (4 * (e & 1))) & 15u;
+        const float vt = fmaxf(moment_v(h, dequant_v(q, fminf(r_old, a.c[j])), load_grad1<BF16>(a.g, e)), 0.0f);
+        if (vt > 0.0f) atomic_max_nonneg(a.c_new + j, vt);
+        rmax = fmaxf(rmax, vt);
+    }
+    for (int d = 1; d < 64; d <<= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, d));
+    if ((threadIdx.x & 63) == 0 && rmax > 0.0f) atomic_max_nonneg(a.r_new + a.rows - 1, rmax);
+}
+
+template <bool BF16>
+__device__ __forceinline__ void maxima_ragged(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    const int tiles = int((class_rows(a) + a.rw2 - 1) / a.rw2) * a.strips2;
+    if (wg < tiles) maxima_ragged_tile<BF16>(a, h, wg, s);
+    else maxima_last_row<BF16>(a, h, wg - tiles);
+}
+
+// One block of the second pass.  l = lane of the group.
 template <bool BF16, class Mid>
-__device__ __forceinline__ void rag_unit1(const Tensor4& a, const Hyper& h, const TileBase& tb, const RagTile& t, Lds& s,
-                                          const Row1<BF16>& cur, const RagUnit& u, int l, bool tame, Mid mid) {
+__device__ __forceinline__ void update_ragged_unit(const Tensor4& a, const Hyper& h, const TileBase& tb, const RagTile& t, LdsRank1& s,
+                                                   const Row1<BF16>& cur, const RagUnit& u, int l, bool tame, Mid mid) {
     float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
     float g[4];
     unpack_grad4<BF16>(cur.g, g);
-    const bool ok = u.off4 != kRagNowhere;
-    // a unit that does not exist has zero gradients, and with zero scales all its moments are zero
+    const bool ok = u.off4 != kNowhere;
+    // a unit that does not exist works on the tile's first slots; its stores are dropped
+    const int il = ok ? u.il : 0, p4 = ok ? u.p + 4 * l : 0;
     const float s_old = ok ? s.blk_scale[u.slot] : 0.0f;
-    const float r_a = ok ? s.blk_vmax[u.il] : 0.0f, r_b = ok ? s.blk_vmax[u.il + 1] : 0.0f;
-    const int p4 = ok ? u.p + 4 * l : 0;
-    float mt[4], vt[4], amax = 0.0f, rmax_a = 0.0f, rmax_b = 0.0f;
+    const float2 ra = row_scalars(s, il), rb = row_scalars(s, il + 1);
+    float mt[4], vt[4], amax = 0.0f;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const float2 d = s.deq[(uint32_t(cur.mq) >> (8 * k)) & 255u];
@@ -167,10 +307,10 @@ __device__ __forceinline__ void rag_unit1(const Tensor4& a, const Hyper& h, cons
         float qf[4], c16[4];
         codes_to_float4(cur.vq, qf);
         lds_load4(&s.cold[p4], c16);
-        const float ra16 = r_a * 0.0625f, rb16 = r_b * 0.0625f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(p4 + e < t.lim ? ra16 : rb16, c16[e]));
+        for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(p4 + e < t.lim ? ra.x : rb.x, c16[e]));
     } else {
+        const float r_a = a.r[t.row0 + il], r_b = t.row0 + il + 1 < a.rows ? a.r[t.row0 + il + 1] : 0.0f;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             vt[e] = dequant_v((uint32_t(cur.vq) >> (4 * e)) & 15u, fminf(p4 + e < t.lim ? r_a : r_b, a.c[rag_col(t, a.cols, p4 + e)]));
@@ -181,69 +321,100 @@ __device__ __forceinline__ void rag_unit1(const Tensor4& a, const Hyper& h, cons
         vt[e] = moment_v(h, vt[e], g[e]);
         w[e] = param_update(h, w[e], mt[e], vt[e]);
         amax = fmaxf(amax, fabsf(mt[e]));
-        const bool here = p4 + e < t.lim;
-        vt[e] = fmaxf(vt[e], 0.0f);                       // a NaN raises no maximum, as on the general path
-        rmax_a = max_nonneg(rmax_a, here ? vt[e] : 0.0f);
-        rmax_b = max_nonneg(rmax_b, here ? 0.0f : vt[e]);
     }
     __builtin_amdgcn_sched_barrier(0);
     mid();
     __builtin_amdgcn_sched_barrier(0);
-    unsigned int* cbits = reinterpret_cast<unsigned int*>(&s.col[p4]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        (void)__hip_atomic_fetch_max(cbits + e, __float_as_uint(vt[e]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     const float s_new = group32_allmax(amax);
-    rmax_a = group32_allmax(rmax_a);
-    if (__ballot(u.p + 128 > t.lim) != 0) rmax_b = group32_allmax(rmax_b);         // some block of the wave straddles rows
-    const uint32_t mq_new = compress_m4(s.search, mt, s_new);
-    store_row1(tb, ok ? u.off4 + 16u * l : kRagNowhere, w, mq_new);
-    if (l == 0 && ok) {
-        s.blk_scale[u.slot] = s_new;
-        unsigned int* rbits = reinterpret_cast<unsigned int*>(&s.blk_vmax[kRagRowSlots + u.il]);
-        (void)__hip_atomic_fetch_max(rbits, __float_as_uint(rmax_a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (u.p + 128 > t.lim)
-            (void)__hip_atomic_fetch_max(rbits + 1, __float_as_uint(rmax_b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    uint32_t vq_new = 0;
+    bool sure = false;
+    if (__builtin_expect(tame, 1)) {
+        float inv[4];
+        lds_load4(&s.col[p4], inv);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) inv[e] = max_nonneg(p4 + e < t.lim ? ra.y : rb.y, inv[e]);
+        vq_new = compress_v4(vt, inv, sure);
     }
+    if (__builtin_expect(!sure, 0)) {
+        vq_new = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            vq_new |= quant_v_code(vt[e], fminf(row_new(s, p4 + e < t.lim ? il : il + 1), s.cnew[p4 + e])) << (4 * e);
+    }
+    const uint32_t off4 = ok ? u.off4 + 16u * l : kNowhere;
+    store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
+    store_vq(tb, off4, vq_new);
+    if (l == 0 && ok) s.blk_scale[u.slot] = s_new;
 }
 
-template <bool BF16, bool ONE_STRIP>
-__device__ __forceinline__ void pass1_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+// Positions of a strip as a thread takes them, kThreads apart; rows and block scales likewise.
+constexpr int kRagPos = (kFlatBlocks * 128 + 128 + kThreads - 1) / kThreads;
+static_assert(kRowSlots <= kThreads && kRagPos * kThreads >= kFlatBlocks * 128 + 128, "start-up of a ragged update tile");
+
+template <bool BF16, bool ONE_STRIP, bool SAME_LAUNCH, class Sync>
+__device__ __forceinline__ void update_ragged_tile(const Tensor4& a, const Hyper& h, int wg, LdsRank1& s, Sync& sync) {
+    const TableRegs tables = request_tables();
     const RagTile t = rag_tile<ONE_STRIP>(a, wg);
     const TileBase tb = rag_base<BF16>(a, t);
-    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31, tid = threadIdx.x;
     auto unit = [&](int q) { return rag_unit<ONE_STRIP>(t, a, grp, q); };
-    auto fetch = [&](const RagUnit& u) { return load_row1<BF16>(tb, u.off4 == kRagNowhere ? kRagNowhere : u.off4 + 16u * l); };
+    auto fetch = [&](const RagUnit& u) { return load_row1<BF16, kPolicyNt>(tb, u.off4 == kNowhere ? kNowhere : u.off4 + 16u * l); };
     const int n = rag_units<ONE_STRIP>(t, a);
+    // start-up as in update_tile
+    float c_old[kRagPos], c_new[kRagPos];
+#pragma unroll
+    for (int u = 0; u < kRagPos; ++u) {
+        const int k = tid + u * kThreads;
+        c_old[u] = k < t.width + 128 ? a.c[rag_col(t, a.cols, k)] : 0.0f;
+    }
+    const bool row_in = tid < t.n_rows && t.row0 + tid < a.rows;  // a unit looks at its row and the next
+    const float r_old = row_in ? a.r[t.row0 + tid] : 0.0f;
+    // old block scales into the slots of the new ones
+    float ms_old = 0.0f;
+    if constexpr (ONE_STRIP) {
+        if (tid < t.n_blocks) ms_old = tb.ms[tid];
+    } else if (tid < t.own_rows * kFlatBlocks) {
+        const int b = ((t.f0 + int(row_offset(tid / kFlatBlocks, a.cols, 0u)) + 127) >> 7) + tid % kFlatBlocks;
+        if (tid % kFlatBlocks < t.per_row && b < t.end) ms_old = tb.ms[b];
+    }
+    float r_new;
+    auto request_new = [&] {
+#pragma unroll
+        for (int u = 0; u < kRagPos; ++u) {
+            const int k = tid + u * kThreads;
+            c_new[u] = k < t.width + 128 ? ld_ws<SAME_LAUNCH>(a.c_new + rag_col(t, a.cols, k)) : 0.0f;
+        }
+        r_new = row_in ? ld_ws<SAME_LAUNCH>(a.r_new + t.row0 + tid) : 0.0f;
+    };
+    if constexpr (!SAME_LAUNCH) request_new();
     RagUnit u0 = unit(0), u1 = unit(1), u2;
     Row1<BF16> r0 = fetch(u0), r1 = fetch(u1), r2;
+    put_tables(s, tables);
     bool lane_tame = true;
-    for (int k = threadIdx.x; k < t.width + 128; k += kThreads) {
-        const float c = a.c[rag_col(t, a.cols, k)];
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(c)));
-        s.cold[k] = c * 0.0625f;
-        s.col[k] = 0.0f;
+    auto tame_too = [&](float x) { lane_tame = bool(int(lane_tame) & int(scale_is_tame(x))); return x; };
+#pragma unroll
+    for (int u = 0; u < kRagPos; ++u) {
+        const int k = tid + u * kThreads;
+        if (k < t.width + 128) s.cold[k] = tame_too(c_old[u]) * 0.0625f;
     }
-    for (int k = threadIdx.x; k < kRagRowSlots; k += kThreads) {
-        const float r = k < t.n_rows && t.row0 + k < a.rows ? a.r[t.row0 + k] : 0.0f;
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
-        s.blk_vmax[k] = r;
-        s.blk_vmax[kRagRowSlots + k] = 0.0f;
-    }
-    // old block scales into the slots of the new ones
-    if constexpr (ONE_STRIP) {
-        for (int k = threadIdx.x; k < t.n_blocks; k += kThreads) s.blk_scale[k] = tb.ms[k];
-    } else {
-        for (int k = threadIdx.x; k < t.own_rows * kFlatBlocks; k += kThreads) {
-            const int b = ((t.f0 + int(row_offset(k / kFlatBlocks, a.cols, 0u)) + 127) >> 7) + k % kFlatBlocks;
-            if (k % kFlatBlocks < t.per_row && b < t.end) s.blk_scale[k] = tb.ms[b];
+    if (tid <= t.n_rows) stage_row_old(s, tid, tame_too(r_old));
+    s.blk_scale[tid] = ms_old;
+    if (!sync.ready()) return;
+    if constexpr (SAME_LAUNCH) request_new();
+#pragma unroll
+    for (int u = 0; u < kRagPos; ++u) {
+        const int k = tid + u * kThreads;
+        if (k < t.width + 128) {
+            s.cnew[k] = tame_too(c_new[u]);
+            s.col[k] = approx_inv16(c_new[u]);
         }
     }
-    load_tables(s);
+    if (tid <= t.n_rows) stage_row_new(s, tid, tame_too(r_new));
     const bool tame = !__syncthreads_or(int(!lane_tame));
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see pass 1)
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see update_tile)
+    if (tame) sync.staged();
     auto none = [] {};
-    auto work = [&](const Row1<BF16>& cur, const RagUnit& u, auto mid) { rag_unit1<BF16>(a, h, tb, t, s, cur, u, l, tame, mid); };
+    auto work = [&](const Row1<BF16>& cur, const RagUnit& u, auto mid) { update_ragged_unit<BF16>(a, h, tb, t, s, cur, u, l, tame, mid); };
     int q = 0;
     while (q + 2 < n) {                                   // rounds of three units, no exit in the middle
         work(r0, u0, [&] { u2 = unit(q + 2); r2 = fetch(u2); });
@@ -256,6 +427,7 @@ __device__ __forceinline__ void pass1_ragged_tile(const Tensor4& a, const Hyper&
         if (q + 1 < n) work(r1, u1, none);
     }
     __syncthreads();
+    if (!tame) sync.staged();
     if constexpr (ONE_STRIP) {
         for (int k = threadIdx.x; k < t.n_blocks; k += kThreads) tb.ms[k] = s.blk_scale[k];
     } else {
@@ -265,30 +437,65 @@ __device__ __forceinline__ void pass1_ragged_tile(const Tensor4& a, const Hyper&
             if (b * 128 - f < t.width && b < t.end) tb.ms[b] = s.blk_scale[k];
         }
     }
-    for (int k = threadIdx.x; k < t.n_rows; k += kThreads) {
-        const float m = s.blk_vmax[kRagRowSlots + k];
-        if (m > 0.0f) atomic_max_nonneg(a.r_new + t.row0 + k, m);
-    }
-    for (int k = threadIdx.x; k < t.width + 128; k += kThreads) {
-        const float m = s.col[k];
-        if (m > 0.0f) atomic_max_nonneg(a.c_new + rag_col(t, a.cols, k), m);
-    }
 }
 
-// Workgroups [0, n_wg) of pass 1; the last one takes the partial block, if any.
-template <bool BF16>
-__device__ __forceinline__ void pass1_ragged(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
-    if ((a.P & 127) && wg == a.n_wg - 1) pass1_general_range<BF16>(a, h, int64_t(a.nb) * 128, a.P, s);
-    else if (a.strips == 1) pass1_ragged_tile<BF16, true>(a, h, wg, s);
-    else pass1_ragged_tile<BF16, false>(a, h, wg, s);
+// The partial last block of a tensor whose size is no multiple of 128: a thread per byte of codes, exact arithmetic.
+template <bool BF16, bool SAME_LAUNCH>
+__device__ __forceinline__ void update_last_block(const Tensor4& a, const Hyper& h, LdsRank1& s) {
+    const int64_t e0 = int64_t(a.nb) * 128;
+    const int t = threadIdx.x;
+    const float s_old = a.ms[a.nb];
+    const bool on = e0 + 2 * t < a.P;                     // fewer than 64 threads
+    uint32_t bm = 0, bv = 0;
+    float mt[2] = {0.0f, 0.0f}, vt[2] = {0.0f, 0.0f};
+    if (on) {
+        bm = reinterpret_cast<const uint8_t*>(a.mq)[(e0 >> 1) + t];
+        bv = reinterpret_cast<const uint8_t*>(a.vq)[(e0 >> 1) + t];
+    }
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int64_t e = e0 + 2 * t + k;
+            if (e < a.P) f(k, e, e / a.cols, e % a.cols);
+        }
+    };
+    each([&](int k, int64_t e, int64_t i, int64_t j) {
+        const float2 dq = s.deq[bm];
+        const float g = load_grad1<BF16>(a.g, e);
+        mt[k] = moment_m(h, (k ? dq.y : dq.x) * s_old, g);
+        vt[k] = moment_v(h, dequant_v((bv >> (4 * k)) & 15u, fminf(a.r[i], a.c[j])), g);
+        a.p[e] = param_update(h, a.p[e], mt[k], vt[k]);
+    });
+    s.col[t] = fmaxf(fabsf(mt[0]), fabsf(mt[1]));
+    __syncthreads();
+    float s_new = 0.0f;
+    for (int i = 0; i < 64; ++i) s_new = fmaxf(s_new, s.col[i]);
+    uint32_t qm = 0, qv = 0;
+    each([&](int k, int64_t, int64_t i, int64_t j) {
+        qm |= quant_m_code(s.search, mt[k], s_new) << (4 * k);
+        qv |= quant_v_code(vt[k], fminf(ld_ws<SAME_LAUNCH>(a.r_new + i), ld_ws<SAME_LAUNCH>(a.c_new + j))) << (4 * k);
+    });
+    if (on) {
+        reinterpret_cast<uint8_t*>(a.mq)[(e0 >> 1) + t] = uint8_t(qm);
+        reinterpret_cast<uint8_t*>(a.vq)[(e0 >> 1) + t] = uint8_t(qv);
+    }
+    if (t == 0) a.ms[a.nb] = s_new;
 }
 
-// Workgroups [0, n_wg2) of pass 2: the tiles, then the parts of the last row if the tiles leave it out.
-template <bool BF16, bool SAME_LAUNCH = false, class Ready = AlwaysReady, class S = NoLds>
-__device__ __forceinline__ void pass2_ragged(const Tensor4& a, const Hyper& h, int wg, Ready ready = Ready(), S&& s = S()) {
-    const int tiles = int((pass2_rows(a, true) + a.rw2 - 1) / a.rw2) * a.strips2;
-    if (wg < tiles) pass2_tile<BF16, true, SAME_LAUNCH>(a, h, wg, ready, s);
-    else if (ready()) pass2_last_row<BF16, SAME_LAUNCH>(a, h, wg - tiles);
+// Workgroups [0, n_wg2) of the second pass; the last one takes the partial block, if any.
+template <bool BF16, bool SAME_LAUNCH, class Sync>
+__device__ __forceinline__ void update_ragged(const Tensor4& a, const Hyper& h, int wg, LdsRank1& s, Sync& sync) {
+    if ((a.P & 127) && wg == a.n_wg2 - 1) {
+        load_tables(s);
+        if (!sync.ready()) return;
+        update_last_block<BF16, SAME_LAUNCH>(a, h, s);
+        __syncthreads();
+        sync.staged();
+    } else if (a.strips == 1) {
+        update_ragged_tile<BF16, true, SAME_LAUNCH>(a, h, wg, s, sync);
+    } else {
+        update_ragged_tile<BF16, false, SAME_LAUNCH>(a, h, wg, s, sync);
+    }
 }
 
 // ---- the factorized step on the same tiles ------------------------------------------------------------------------
@@ -297,18 +504,16 @@ __device__ __forceinline__ void pass2_ragged(const Tensor4& a, const Hyper& h, i
 // an exact division and four loads of statistics per element for the update.  General / these, us per step: 4096 x 4000
 // bf16 907 / 49, 1024 x 50257 bf16 1747 / 147, 30000 x 1000 fp32 361 / 107, 600 x 147 fp32 15.7 / 13.9.)
 
-// Statistics pass: the row-class walk of pass2_tile (a wave's rows are a multiple of 4 apart, so its lanes keep their columns
+// Statistics pass: the row-class walk of maxima_ragged_tile (a wave's rows are a multiple of 4 apart, so its lanes keep their columns
 // down the tile).  Columns are counted on through the end of a row: positions cols, cols + 1, cols + 2 are the next row's
 // first ones, whose squares the row's last lane collects for that row.
 template <bool BF16>
 __device__ __forceinline__ void factor_stats_ragged_tile(const Tensor4& a, int wg, Lds& s) {
-    constexpr int kSpan = 264;                                    // positions of a strip: 256, a shift and a lane's 4
-    static_assert(4 * kSpan <= kColSlots && kMaxRw2 < kMaxRowSlots, "column and row sums of a tile are staged in LDS");
     const int strip = wg % a.strips2, tile = wg / a.strips2;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
     const int64_t row0 = int64_t(tile) * a.rw2;                   // a multiple of 4
-    const int64_t left = pass2_rows(a, true) - row0;
+    const int64_t left = class_rows(a) - row0;
     const int n = left < a.rw2 ? int(left) : a.rw2;
     const int n_stat = row0 + n < a.rows ? n + 1 : n;
     const uint32_t cols = uint32_t(a.cols);
@@ -318,7 +523,7 @@ __device__ __forceinline__ void factor_stats_ragged_tile(const Tensor4& a, int w
     const Rsrc rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + row0 * a.cols * (BF16 ? 2 : 4),
                               uint32_t(n_stat) * cols * (BF16 ? 2u : 4u));
     const int last = n - 1 - (n - 1 - wave) % kWaves;             // the wave's own last row, if it has any (wave < n)
-    auto ld = [&](int il) { return load_grad_regs4<BF16>(rg, live ? (uint32_t(il < last ? il : last) * cols + col0) * 4u : kRagNowhere); };
+    auto ld = [&](int il) { return load_grad_regs4<BF16>(rg, live ? (uint32_t(il < last ? il : last) * cols + col0) * 4u : kNowhere); };
     for (int t = threadIdx.x; t < 4 * kSpan; t += kThreads) s.col[t] = 0.0f;
     for (int t = threadIdx.x; t <= n; t += kThreads) { s.blk_scale[t] = 0.0f; s.blk_vmax[t] = 0.0f; }
     __syncthreads();
@@ -383,10 +588,10 @@ __device__ __forceinline__ void factor_stats_ragged_tile(const Tensor4& a, int w
     }
 }
 
-// The part of the last row that the tiles leave out (see pass2_last_row).
+// The part of the last row that the tiles leave out (see class_rows).
 template <bool BF16>
 __device__ __forceinline__ void factor_stats_last_row(const Tensor4& a, int part, Lds& s) {
-    const int64_t first = pass2_last_row_begin(a) + int64_t(part) * kLastRowElems;
+    const int64_t first = last_row_begin(a) + int64_t(part) * kLastRowElems;
     const int lane = threadIdx.x & 63;
     float sum = 0.0f;
     for (int u = 0; u < kLastRowElems / kThreads; ++u) {
@@ -410,7 +615,7 @@ __device__ __forceinline__ void factor_stats_last_row(const Tensor4& a, int part
 
 template <bool BF16>
 __device__ __forceinline__ void factor_stats_ragged(const Tensor4& a, int wg, Lds& s) {
-    const int tiles = int((pass2_rows(a, true) + a.rw2 - 1) / a.rw2) * a.strips2;
+    const int tiles = int((class_rows(a) + a.rw2 - 1) / a.rw2) * a.strips2;
     if (wg < tiles) factor_stats_ragged_tile<BF16>(a, wg, s);
     else factor_stats_last_row<BF16>(a, wg - tiles, s);
 }
@@ -423,7 +628,7 @@ __device__ __forceinline__ void factor_update_ragged_tile(const Tensor4& a, cons
     const TileBase tb = rag_base<BF16>(a, t);
     const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
     auto unit = [&](int q) { return rag_unit<ONE_STRIP>(t, a, grp, q); };
-    auto fetch = [&](const RagUnit& u) { return load_rowf<BF16>(tb, u.off4 == kRagNowhere ? kRagNowhere : u.off4 + 16u * l); };
+    auto fetch = [&](const RagUnit& u) { return load_rowf<BF16>(tb, u.off4 == kNowhere ? kNowhere : u.off4 + 16u * l); };
     const int n = rag_units<ONE_STRIP>(t, a);
     RagUnit u0 = unit(0), u1 = unit(1), u2;
     RowF<BF16> r0 = fetch(u0), r1 = fetch(u1), r2;
@@ -445,13 +650,13 @@ __device__ __forceinline__ void factor_update_ragged_tile(const Tensor4& a, cons
         }
     }
     load_tables(s);
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see pass 1)
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see update_tile)
     auto none = [] {};
     auto work = [&](const RowF<BF16>& cur, const RagUnit& u, auto mid) {
         float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
         float g[4], ct[4], mt[4], amax = 0.0f;
         unpack_grad4<BF16>(cur.g, g);
-        const bool ok = u.off4 != kRagNowhere;            // a unit that does not exist: all moments zero
+        const bool ok = u.off4 != kNowhere;            // a unit that does not exist: all moments zero
         const float s_old = ok ? s.blk_scale[u.slot] : 0.0f;
         const float r_a = ok ? s.blk_vmax[u.il] : 0.0f, r_b = ok ? s.blk_vmax[u.il + 1] : 0.0f;
         const int p4 = ok ? u.p + 4 * l : 0;
@@ -472,7 +677,7 @@ __device__ __forceinline__ void factor_update_ragged_tile(const Tensor4& a, cons
         mid();
         __builtin_amdgcn_sched_barrier(0);
         const float s_new = group32_allmax(amax);
-        store_row1(tb, ok ? u.off4 + 16u * l : kRagNowhere, w, compress_m4(s.search, mt, s_new));
+        store_row1(tb, ok ? u.off4 + 16u * l : kNowhere, w, compress_m4(s.search, mt, s_new));
         if (l == 0 && ok) s.blk_scale[u.slot] = s_new;
     };
     int q = 0;

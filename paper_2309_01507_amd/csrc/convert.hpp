@@ -9,6 +9,9 @@
 // compress the first moment 106 -> 55 us, its codes alone for the second 170 -> 39 us, decompress the first 111 -> 37 us,
 // the second 139 -> 55 us.  The fp32 arrays and the
 // scales need only be 4-byte aligned: the wide accesses are typed so.
+// What is read for the last time and the decompressed values pass by the memory-side cache (non-temporal), which then still
+// holds what a later kernel reads again: the second moment for its codes, the codes and scales for the way back.  Both moments
+// of an 11008 x 4096 matrix there and back 230 -> 174 us (one-touch bytes at 4.7 TB/s), of 16384 x 8192 636 -> 520.
 #pragma once
 
 #include "kernels.hpp"
@@ -33,9 +36,12 @@ constexpr int kCvtElems = kCvtUnits * kCvtUnitElems;      // elements per workgr
 
 // ---- accesses of a lane's 4 elements; `base` is a multiple of 4, elements at or beyond P do not exist ----
 
+// STREAM: the array is not read again soon (non-temporal: it takes no room in the memory-side cache from what is).
+template <bool STREAM = false>
 __device__ __forceinline__ void cvt_load4(const float* x, int64_t base, int64_t P, float out[4]) {
     if (base + 4 <= P) {
-        const v4f_a4 v = *reinterpret_cast<const v4f_a4*>(x + base);
+        const v4f_a4* p = reinterpret_cast<const v4f_a4*>(x + base);
+        const v4f_a4 v = STREAM ? __builtin_nontemporal_load(p) : *p;
         out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
     } else {
 #pragma unroll
@@ -45,7 +51,7 @@ __device__ __forceinline__ void cvt_load4(const float* x, int64_t base, int64_t 
 __device__ __forceinline__ void cvt_store4(float* x, int64_t base, int64_t P, const float v[4]) {
     if (base + 4 <= P) {
         const v4f_a4 w = {v[0], v[1], v[2], v[3]};
-        *reinterpret_cast<v4f_a4*>(x + base) = w;
+        __builtin_nontemporal_store(w, reinterpret_cast<v4f_a4*>(x + base));
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -145,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void quant_m_kernel(const QuantArgs q) {
     const int64_t first = int64_t(blockIdx.x) * kCvtElems + threadIdx.x * 4;
     float x[kCvtUnits][4];
 #pragma unroll
-    for (int u = 0; u < kCvtUnits; ++u) cvt_load4(q.x_in, first + u * kCvtUnitElems, q.P, x[u]);
+    for (int u = 0; u < kCvtUnits; ++u) cvt_load4<true>(q.x_in, first + u * kCvtUnitElems, q.P, x[u]);
     const uint2* gs = reinterpret_cast<const uint2*>(d_search);
     uint2* ss = reinterpret_cast<uint2*>(s_search);
     for (int i = threadIdx.x; i < kBucketsPadded; i += kThreads) ss[i] = gs[i];
@@ -229,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void quant_vb_kernel(const QuantArgs q) {
     const int64_t first = int64_t(blockIdx.x) * kCvtElems + threadIdx.x * 4;
     float x[kCvtUnits][4];
 #pragma unroll
-    for (int u = 0; u < kCvtUnits; ++u) cvt_load4(q.x_in, first + u * kCvtUnitElems, q.P, x[u]);
+    for (int u = 0; u < kCvtUnits; ++u) cvt_load4<true>(q.x_in, first + u * kCvtUnitElems, q.P, x[u]);
 #pragma unroll
     for (int u = 0; u < kCvtUnits; ++u) {
         const int64_t base = first + u * kCvtUnitElems;
@@ -331,7 +337,7 @@ __global__ __launch_bounds__(kThreads) void quant_v_code_kernel(const QuantArgs 
 #pragma unroll
     for (int u = 0; u < kCvtUnits; ++u) {
         const uint32_t off = u * kCvtUnitElems + threadIdx.x * 4;
-        cvt_load4(q.x_in, wg_first + off, q.P, x[u]);
+        cvt_load4<true>(q.x_in, wg_first + off, q.P, x[u]);
         rank1_scales4(o, off, q.rows, q.sa, q.sb, s[u]);
     }
 #pragma unroll

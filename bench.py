@@ -228,8 +228,7 @@ def main():
     ap.add_argument("--seed", type=int, default=1)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-secondary", action="store_true",
-                    help="skip what is timed after the headline leg: the other configurations and variants, and the serial "
-                         "leg behind roofline.alone")
+                    help="skip what is timed after the headline leg: the other configurations and variants")
     ap.add_argument("--grad-dtype", choices=["config", "bf16", "f32"], default="config",
                     help="override the gradient type of the configuration (experiments)")
     ap.add_argument("--second-moment", choices=["rank1", "b128", "factor"], default="rank1",

@@ -347,14 +347,12 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
 /* ---- many tensors in one call ---------------------------------------------------------------------
  * The same step for a whole parameter set (Alg. 1: "perform the optimizer steps separately for each
  * layer" -- here all layers are enqueued by one call).  A plan is built once for a list of tensors;
- * lpmm_adamw4_step_multi then enqueues a short sequence of launches: pass 1 of one group of tensors
- * runs on `stream` while pass 2 of the previous group runs beside it on a second stream that the
- * plan owns (same priority; `stream` waits for it before the call's work counts as complete, so the
- * usual stream ordering holds for the caller).  Plans with a single group, plans of factorized tensors and
- * the one-pass kinds enqueue all their launches on `stream`.  Rank-1 and factorized plans for which it is the faster way
- * enqueue ONE launch there, in which pass 2 of a tensor follows its pass 1: sets of 2^25 parameters or more, unless most
- * of them are in one tensor (rank-1: more than 3/4, factorized: 1/4), in two to eight equal ones, or in rows shorter than
- * 128; and sets with LPMM_KIND_4BIT_ND tensors, unless that is one large tensor alone.  (Not with
+ * lpmm_adamw4_step_multi then enqueues a short sequence of launches on `stream`: per group of
+ * tensors the first pass (which only reads: the new statistics of the second moment), then the update.
+ * Rank-1 and factorized plans for which it is the faster way
+ * enqueue ONE launch there, in which the update of a tensor follows its first pass: sets of 2^25 parameters or more, unless most
+ * of them are in one tensor (rank-1: more than 3/4, factorized: 1/4), in two to eight equal ones, or half of them in rows shorter
+ * than 128; and sets with LPMM_KIND_4BIT_ND tensors, unless that is one large tensor alone.  (Not with
  * LPMM_FLAG_DETERMINISTIC.)  Results are identical to calling the
  * single-tensor entry points one tensor at a time. */
 
@@ -462,14 +460,13 @@ int lpmm_adamw4_plan_launches(const void* plan);
 
 /* Per-kernel timing for benchmarks, with HIP events recorded on each call's own stream.
  * lpmm_profile_begin(max_calls): from now on every lpmm_adamw4_step / _step_bf16g call in this process
- * records an event before pass 1, between the two passes and after pass 2, and every
+ * records an event before the first pass, between the two and after the second, and every
  * lpmm_adamw4_step_multi call an event before and after each of its launches, for at most max_calls
  * recorded launches pairs / launches (later ones run unrecorded).  Creates host-side event objects only.
  * lpmm_profile_end: waits for the recorded events and stops recording.  Single-tensor steps: ms[0]
- * = summed duration in milliseconds of the recorded pass-1 launches, ms[1] = of the pass-2 launches,
+ * = summed duration in milliseconds of the recorded first passes, ms[1] = of the second ones,
  * *n_calls = recorded calls.  Multi-tensor steps: ms[0] = summed duration of the recorded launches
- * that carry pass 1 (their pass-2 companions run beside them on the plan's second stream; in a plan of
- * factorized tensors: of the update passes; in a plan that is stepped in one launch: of that launch), ms[1] = 0, *n_calls = recorded launches.  (Do not mix the two kinds between one begin and end.)
+ * that carry the updates (in a plan that is stepped in one launch: of that launch), ms[1] = 0, *n_calls = recorded launches.  (Do not mix the two kinds between one begin and end.)
  * ms, n_calls: host.  Not thread-safe: begin, end and every step between them must come from one host thread. */
 int lpmm_profile_begin(int64_t max_calls);
 int lpmm_profile_end(double ms[2], int64_t* n_calls);

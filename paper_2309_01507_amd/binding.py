@@ -697,7 +697,7 @@ def lpmm_profile_begin(max_calls: int) -> None:
 
 
 def lpmm_profile_end():
-    """Returns (sum of pass-1 ms, sum of pass-2 ms, recorded calls)."""
+    """Returns (sum of first-pass ms, sum of second-pass ms, recorded calls)."""
     ms = (ctypes.c_double * 2)()
     n = ctypes.c_int64()
     _check(lib().lpmm_profile_end(ctypes.addressof(ms), ctypes.addressof(n)), "lpmm_profile_end")

@@ -9,12 +9,12 @@
 // tensors of 2^22 to 2^26, 4.67 for 2^27; the update first and the codes 2^23 parameters behind 4.83.)  It also spares the step
 // the starts and the tails of its launches, and tiles of unequal cost do not leave XCDs idle.
 //
-// Order inside the launch.  Pass 2 of a tensor needs its complete maxima (sums): a workgroup of pass 1 waits for its own
-// atomics and then raises the tensor's count, a workgroup of pass 2 polls that count.  Workgroups are started in the order
+// Order inside the launch.  The second pass of a tensor needs its complete maxima (sums): a workgroup of the first waits for its own
+// atomics and then raises the tensor's count, a workgroup of the second polls that count.  Workgroups are started in the order
 // of their ids as far as the hardware is known to do it, so the count is usually complete long before; but nothing
 // promises that order, so the polling is BOUNDED and no workgroup ever waits for one that might not run: a workgroup that
 // has polled `spin_limit` times writes its tile to the tensor's list of deferred tiles and leaves.  The last workgroup of
-// the tensor to finish -- of either pass: `final` counts "pass 1 complete" and "pass 2 complete" -- does the deferred
+// the tensor to finish -- of either pass: `final` counts "first pass complete" and "second pass complete" -- does the deferred
 // tiles, then publishes the new statistics and clears the workspace.  Every workgroup ends after a bounded time in any
 // order of execution, and the results do not depend on it.
 //
@@ -50,8 +50,8 @@ __device__ __forceinline__ unsigned int* flow_word(const Tensor4& a, int k) {
     return a.counter + (1 + kTicketLanes + kMaxTotSlots - 1) * kTicketStride + k;
 }
 enum { kFlowFinal = 0, kFlowDeferred = 1 };
-// The finished workgroups of pass 1 are counted in two levels like those of pass 2, in words of their own next to theirs.
-// All of them on one word, the one that pass 2 polls, made the memory system serve the polls of several hundred waiting
+// The finished workgroups of first passes are counted in two levels like those of second ones, in words of their own next to theirs.
+// All of them on one word, the one that is polled, made the memory system serve the polls of several hundred waiting
 // workgroups between the counts: one 4096 x 4096 matrix 147 us, 69 this way, and 90 us more than now in any plan whose last
 // tensors are of that size.
 __device__ __forceinline__ unsigned int* flow_done(const Tensor4& a) { return a.counter + kTicketStride / 2; }
@@ -60,7 +60,7 @@ __device__ __forceinline__ unsigned int flow_peek(const unsigned int* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Tensors with more than two dimensions, between the passes, by the workgroup that completes pass 1: statistics of the
+// Tensors with more than two dimensions, between the passes, by the workgroup that completes the first: statistics of the
 // inner dimensions from the column maxima (LDS atomics), then the new column scales in place of the maxima.
 constexpr int kFlowNdCols = 16384;                    // columns up to which one workgroup does this
 constexpr int kFlowNdStats = 2 * kColSlots;           // statistics that fit s.col and s.cold

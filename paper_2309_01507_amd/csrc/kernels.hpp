@@ -47,7 +47,7 @@ struct Tensor4 {
     float* c;               // column maxima (state)            (kFactor*: column statistics)
     float* r_new;           // workspace: row maxima of v_t (zero between steps)      (kFactor*: row sums of g^2)
     float* c_new;           // workspace: column maxima of v_t (zero between steps)   (kFactor*: column sums of g^2)
-    unsigned int* counter;  // workspace: ticket counters of pass 2 (zero between steps); kFactor*: also two float sums
+    unsigned int* counter;  // workspace: ticket counters of the second pass (zero between steps); kFactor*: also two float sums
     int64_t rows, cols, P;
     // second pass (update) of the fast path (cols % 128 == 0)
     int nb;                 // column blocks per row = cols / 128    (kQuantBlockV: whole blocks of the tensor)
@@ -158,7 +158,7 @@ __device__ __forceinline__ int logical_wg(int skew) {
 }
 
 constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0) only: expcnt and lgkmcnt fields at their maxima
-constexpr int kMaxRowSlots = 512;    // rows of a pass-1 tile x column blocks of its strip (rw * gx)
+constexpr int kMaxRowSlots = 512;    // rows of a tile, or x column blocks of its strip (rw * gx) for the row walk
 
 constexpr int kColSlots = 9 * 128;   // columns of a strip; a ragged strip's last block may reach 127 columns beyond it
 
@@ -217,7 +217,8 @@ __device__ __forceinline__ float max_nonneg(float a, float b) {
 // Streaming 128-bit access for the parameters: they are read and written exactly once per step.
 // The loads carry the non-temporal hint; the stores go out with the nt and sc1 cache-policy bits (write
 // through, do not keep the line).  Measured on the 7B-shaped set: about 9 % less time per step than plain
-// accesses for nt on both, and a further 2-3 % of pass 1 for sc1 on the store.
+// accesses for nt on both, and a further 2-3 % of the update (then without v's codes) for sc1 on the
+// store.
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
 constexpr int kPolicyNtSc1 = 2 | 16;            // gfx94x/gfx950 cache-policy bits: 1 = sc0, 2 = nt, 16 = sc1
@@ -980,7 +981,7 @@ struct RowB {                      // everything the step reads for one block, p
     float4 p;
     GradRegs4<BF16> g;
     uint16_t mq, vq;               // the lane's 4 codes of each moment
-};                                 // (the block's two old scales come from LDS, staged by the tile as in pass 1)
+};                                 // (the block's two old scales come from LDS, staged by the tile)
 
 constexpr uint32_t kNoBlock = 1u << 30;     // a byte offset beyond any tile: loads return zeros, stores are dropped
 
@@ -1246,7 +1247,7 @@ __device__ __forceinline__ void store_codes(uint32_t* q, const LaneIo& io, uint3
     for (int k = 0; k < (io.nv + 1) / 2; ++k) b[k] = uint8_t(w >> (8 * k));
 }
 
-// A workgroup of the general pass 1 takes a.rw (1..16, chosen by the host) consecutive chunks of 2048 elements.  The maxima of v_t
+// A workgroup of the general first pass takes a.rw (1..16, chosen by the host) consecutive chunks of 2048 elements.  The maxima of v_t
 // are first combined in LDS (integer atomics on the float bits), indexed by the column -- possible when the
 // tensor has at most kGenColsLds columns, which is the usual case for shapes that miss the fast path (narrow
 // matrices) -- and by the row relative to the workgroup's first row; one global atomic per column and row
@@ -1785,7 +1786,7 @@ __device__ __forceinline__ void factor_totals_one(const Tensor4& a, float* s_par
 }
 
 // General path of the factorized form (any rows x cols): lane t owns flat elements [8t, 8t+8), row and
-// column tracked per element.  The statistics pass works like the general pass 1: a.rw consecutive chunks of
+// column tracked per element.  The statistics pass works like the general first pass: a.rw consecutive chunks of
 // 2048 elements per workgroup, sums combined in LDS (float atomics) by column (tensors of at most 2048
 // columns) and by row relative to the workgroup's first row, one global atomic per touched column and row at
 // the end; wider tensors add straight to global memory.

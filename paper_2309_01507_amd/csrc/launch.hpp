@@ -135,10 +135,9 @@ __global__ __launch_bounds__(kThreads) void adamw32_kernel(float* p, const void*
 }
 
 // =====================================================================================================
-// Phase kernel of the multi-tensor step.  A phase runs the "A" work of one set of tensors (pass 1
-// of quantized tensors, the whole update of fp32-state tensors) together with the "B" work of the
-// previous set (pass 2).  The two kinds are interleaved in proportion, so that at any time each CU
-// holds memory-bound pass-1 workgroups next to arithmetic-bound pass-2 workgroups.
+// Phase kernel of the multi-tensor step.  A phase has the "A" work of one set of tensors (first passes
+// of tensors with two, the whole step of the others) and the "B" work of the previous set (second
+// passes).  By default each is a launch of its own; in one launch they are interleaved in proportion.
 // =====================================================================================================
 
 // Hyper-parameters of a plan's launches: by value, or -- for a step that is captured into a graph and replayed
@@ -218,10 +217,9 @@ __device__ __forceinline__ Segment find_segment(const Segment* seg, int n_seg, i
 }
 
 // ROLES: 0 = A and B work interleaved in one launch; 1 = A work only; 2 = B work only; 3 = A work
-// only of a group without rank-1 tensors (block-wise and fp32-state tensors: no pass-1 code).  The
+// only of a group without rank-1 tensors (block-wise and fp32-state tensors: no rank-1 code).  The
 // single-role kernels exist because a kernel's register and LDS footprint is that of its heaviest
-// path: launched on their own (on a second stream), the light pass-2 workgroups fit into the
-// register space that the resident pass-1 workgroups leave free.
+// path.
 template <bool BF16, int ROLES>
 __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);

@@ -24,7 +24,7 @@ using namespace lpmm;
 
 constexpr int kMaxDevices = 16;
 static_assert(kCounterWords * 4 <= 8192, "counter block");
-constexpr size_t kCounterBytes = 8192;  // tail of the workspace: ticket counters of pass 2, one cache line apart
+constexpr size_t kCounterBytes = 8192;  // tail of the workspace: ticket counters of the second pass, one cache line apart
 
 struct DeviceCtx {
     bool ready = false;
@@ -35,7 +35,7 @@ struct DeviceCtx {
     unsigned char* scratch = nullptr;   // this device's copy of `scratch` below (its address on this device)
 };
 
-// Device memory of the library's own for lpmm_adamw4_step_noalloc: the ticket counters of pass 2, then the row
+// Device memory of the library's own for lpmm_adamw4_step_noalloc: the ticket counters of the second pass, then the row
 // and column maxima of the updated second moment.  Every GPU that loads the library holds one copy until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress; the address of a device's
 // copy is DeviceCtx::scratch, looked up once per device by lpmm_adamw4_init.
@@ -175,7 +175,7 @@ void fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int 
     a->rw = int(rw);
     a->n_wg = int(a->strips * ((a->rows + rw - 1) / rw));
     a->rs = row_spacing_log2(a->cols * 4, rw, a->gy, "LPMM_RS");      // the parameters' rows
-    // pass 2: strips of 256 columns, a wave per row
+    // statistics pass: strips of 256 columns, a wave per row
     a->strips2 = (a->nb + 1) / 2;
     int64_t rw2 = env_int("LPMM_RW2", 0);
     if (rw2 <= 0) rw2 = rw2_hint;
@@ -189,7 +189,7 @@ void fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int 
     if (rw2 < 1) rw2 = 1;
     a->rw2 = int(rw2);
     a->n_wg2 = int(a->strips2 * ((a->rows + rw2 - 1) / rw2));
-    a->rs2 = row_spacing_log2(a->cols * grad_bytes, rw2, kWaves, "LPMM_RS2");   // pass 2 mostly reads the gradient
+    a->rs2 = row_spacing_log2(a->cols * grad_bytes, rw2, kWaves, "LPMM_RS2");   // that pass only reads the gradient
 }
 
 // Geometry of the rank-1 step on the fast path.
@@ -276,7 +276,7 @@ bool fast_eligible(int64_t cols, const float* v_colmax) {
            !env_int("LPMM_FORCE_GENERAL", 0);
 }
 
-// general path: pass 2 takes one chunk of 2048 elements per workgroup, pass 1 several consecutive ones (the
+// general path: the second pass takes one chunk of 2048 elements per workgroup, the first several consecutive ones (the
 // more, the fewer atomics leave the workgroup; few enough that the tensor alone still fills the chip)
 void general_geometry(Tensor4* a, int n_cu) {
     const int64_t chunks = (a->P + kGenChunkElems - 1) / kGenChunkElems;
@@ -348,7 +348,7 @@ void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
     if (rows2 != a->rows) a->n_wg += int((a->P - last_row_begin(*a) + kLastRowElems - 1) / kLastRowElems);
 }
 
-// pass 1 or 2 of the rank-1 step on one tensor
+// first or second pass of the rank-1 step on one tensor
 template <bool BF16>
 void launch_pass(int pass, const Tensor4& t, const Hyper& h, hipStream_t s) {
     const int n = pass == 1 ? t.n_wg : t.n_wg2;
@@ -640,8 +640,8 @@ int nd_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes, flo
     return pass(2);
 }
 
-// Tiling of a tensor with a factorized second moment: the statistics pass is tiled like pass 2 and is the
-// step's first ("A") launch, the update pass is tiled like pass 1 and is the second ("B") one.
+// Tiling of a tensor with a factorized second moment: the statistics pass, the step's first ("A") launch, in strips of 256
+// columns, the update pass, the second ("B") one, in column blocks.
 // rows per tile of the statistics pass when its sums are reduced in a fixed order: fixed, because the size of the
 // partial-sum buffer (part of the plan's memory) follows from it
 constexpr int64_t kDetStatRows = 128;
@@ -745,8 +745,8 @@ struct PhaseLaunch {
     int grid;        // both kinds in one launch
     int grid_a;      // A work alone
     int grid_b;      // B work alone
-    bool a_has_rank1;   // some A tensor takes pass 1 of the rank-1 path (else the lighter kernel variant runs)
-    // tensors with more than two dimensions among the B tensors: two small kernels run before their pass 2
+    bool a_has_rank1;   // some A tensor takes the first pass of the rank-1 path (else the lighter kernel variant runs)
+    // tensors with more than two dimensions among the B tensors: two small kernels run before their second pass
     NdPhase nd;
     bool has_nd;
     // tensors with deterministic sums among the B tensors (factorized plans): two small kernels before their update pass
@@ -767,9 +767,9 @@ struct PlanHost {
     int64_t params = 0;                 // parameters of all tensors of the plan
     Hyper* d_hyper = nullptr;           // device slot inside the plan for the hyper-parameters of a captured step
     int device = 0;
-    // second stream for pass 2 (same priority as any other stream), with its ordering events
+    // LPMM_MULTI_STREAMS=2: second stream for second passes (same priority as any other stream), with its ordering events
     hipStream_t side = nullptr;
-    hipStream_t side_a = nullptr;       // optional: pass 1 of odd phases, so that consecutive pass-1 launches overlap their tails
+    hipStream_t side_a = nullptr;       // =3: first passes of odd phases, so that consecutive launches of first passes overlap their tails
     hipEvent_t ev_join_a = nullptr;
     std::vector<hipEvent_t> ev_a;       // ev_a[j]: phase j's A work is complete
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -878,7 +878,7 @@ bool flow_kind_second(int kind) { return is_rank1(kind) || kind == kFactorFast |
 //   90 / 110; 4 of them 197 / 224, 164 / 187; 8 398 / 412, 313 / 341; 12 604 / 596, 482 / 493; 4 of 8192 x 8192 817 / 768,
 //   654 / 623.  Launches by phases lose time to unequal tiles, and these have none.
 // - Not sets of which the general tiles (rows shorter than 128) are most: in one kernel with the others they have fewer waves
-//   in flight.  Rank-1 up to three fifths of the parameters (30000 x 96 beside 1024 x 4096, bf16 and fp32 gradients: 0.25 233
+//   in flight.  Rank-1 below half of the parameters (30000 x 96 beside 1024 x 4096, bf16 and fp32 gradients: 0.25 233
 //   / 203, 297 / 218; 0.4 376 / 298, 470 / 327; 0.58 282 / 277, 336 / 275; 0.85 401 / 456, 436 / 470; all 352 / 460, 363 /
 //   469), factorized up to half (adapters 64 x 4096 and 4096 x 64: 406 / 354, 394 / 337; all narrow 486 / 571, 478 / 572).
 // - Sets with tensors of more than two dimensions, which by phases take four dependent launches, also below 2^25 parameters
@@ -1673,11 +1673,9 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     host->d_hyper = reinterpret_cast<Hyper*>(dplan + L.off_hyper);
     unsigned int* d_counters = reinterpret_cast<unsigned int*>(dplan + L.off_counters);
 
-    const int64_t rw_hint = env_int("LPMM_MULTI_RW", -1);      // -1: the plan defaults (64 rows, 32 for the flat tiling)
+    const int64_t rw_hint = env_int("LPMM_MULTI_RW", -1);      // -1: the plan defaults (see the geometries)
     const int64_t rw2_hint = env_int("LPMM_MULTI_RW2", 128);
-    // parameters per group of consecutive tensors: large groups win (fewer kernel tails); cutting a set that fits
-    // one group into three so that its pass 2 has a pass 1 to run beside gave -3 % on the 108 M set, nothing on
-    // the 354 M set and +1.4 % on its factorized form, so it is not done
+    // parameters per group of consecutive tensors: large groups win (fewer kernel tails)
     int64_t group_params = int64_t(env_int("LPMM_PHASE_MPARAMS", 2048)) << 20;
     if (n > kMaxSeg && env_int("LPMM_PHASE_MPARAMS", 0) <= 0) {
         // More tensors than one group's tables hold: cut by parameters, into about equal parts, instead of filling
@@ -1898,10 +1896,9 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         pl.grid_b = grid_of(pl.ph.n_b);
         host->phases.push_back(pl);
     }
-    // A second stream pays only if some pass 2 has a pass 1 of another group to run beside.  Factorized plans take
-    // their launches one after the other on the caller's stream by default: the statistics pass (read-only) and the
-    // update pass each run at the memory system's rate alone, and side by side they only get in each other's way
-    // (7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
+    // Plans take their launches one after the other on the caller's stream by default: a first pass (read-only) and an
+    // update each run at the memory system's rate alone, and side by side they only get in each other's way (factorized
+    // 7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
     const int stream_mode = env_int("LPMM_MULTI_STREAMS", 0);
     host->serial = stream_mode == 0 && !host->sgdm;
     bool any_b = false;
@@ -2022,19 +2019,19 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
     bool two_pass = false;
     for (const PhaseLaunch& pl : host->phases) two_pass = two_pass || pl.ph.n_b > 0;
     if (host->side || host->serial) {
-        // A work of phase j on the caller's stream, B work (pass 2 of the tensors whose pass 1 ran
-        // in phase j-1) on the side stream behind an event; the caller's stream rejoins at the end.
+        // A work of phase j on the caller's stream, B work (second pass of the tensors whose first pass
+        // ran in phase j-1) on the side stream behind an event; the caller's stream rejoins at the end.
         // Serial plans take the same launches one after the other on the caller's stream, without events.
         const bool two = host->side != nullptr;
         hipStream_t s2 = two ? host->side : s;
         // The side stream's first work waits for the event behind the first A launch, which also puts it behind
         // everything that was on the caller's stream before this call (and into a capture of that stream): no fork
-        // event is needed for it.  A second stream for pass 1 starts with work of its own and does need one.
+        // event is needed for it.  A second stream for first passes starts with work of its own and does need one.
         if (host->side_a) {
             LPMM_HIP(hipEventRecord(host->ev_fork, s));
             LPMM_HIP(hipStreamWaitEvent(host->side_a, host->ev_fork, 0));
         }
-        // The last phase holds B work only, with no pass 1 left to run beside: it goes on the caller's stream,
+        // The last phase holds B work only, with no first pass left to run beside: it goes on the caller's stream,
         // straight behind the A work it depends on, and spares the step one hand-over between the streams (a
         // dependent launch on another stream starts 10-15 us later than one on the same stream).
         const size_t n_ph = host->phases.size();

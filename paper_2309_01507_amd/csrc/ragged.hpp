@@ -620,7 +620,7 @@ __device__ __forceinline__ void factor_stats_ragged(const Tensor4& a, int wg, Ld
     else factor_stats_last_row<BF16>(a, wg - tiles, s);
 }
 
-// Update pass: the blocks of pass1_ragged_tile; s.cold holds the columns' new statistics by position, s.blk_vmax the rows'
+// Update pass: the blocks of update_ragged_tile; s.cold holds the columns' new statistics by position, s.blk_vmax the rows'
 // over their total.
 template <bool BF16, bool ONE_STRIP>
 __device__ __forceinline__ void factor_update_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {

@@ -154,7 +154,8 @@ constexpr int kDealRun = 32;
 __device__ __forceinline__ int logical_wg(int skew) {
     const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
     if (skew < 0) return (i / kDealRun * kXcds + x) * kDealRun + i % kDealRun;
-    return skewed(x, i, gridDim.x / kXcds, skew);   // the grid is padded to a multiple of 8
+    const int per_xcd = gridDim.x / kXcds;                                 // the grid is padded to a multiple of 8
+    return skew == 0 ? x * per_xcd + i : skewed(x, i, per_xcd, skew);
 }
 
 constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0) only: expcnt and lgkmcnt fields at their maxima

@@ -262,6 +262,7 @@ __global__ __launch_bounds__(kThreads, FORM == kFlowRank1 ? 5 : FORM == kFlowRan
         if (mine) {
             mine = false;
             if (!done) {
+                __syncthreads();                          // every wave has read the answer in s_flag before the ticket writes it
                 if (threadIdx.x == 0) {
                     const unsigned int k = atomicAdd(flow_word(a, kFlowDeferred), 1u);
                     __hip_atomic_store(f.deferred + a.deferred + k, wg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -149,6 +149,19 @@ def test_counts_of_finished_workgroups(monkeypatch, rows, n_first):
             np.testing.assert_array_equal(x, y, err_msg=n_first)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+def test_deferred_by_the_workgroup_with_the_last_ticket(monkeypatch, bf16):
+    """Tensors of one or two update tiles: the workgroup that defers a tile takes the tensor's last ticket, too, and so
+    writes the word again from which its waves have just read that the tile is deferred."""
+    tensors = [("rank1", (8, 128)), ("rank1", (8, 256)), ("rank1", (3, 128)), ("rank1", (5, 130)), ("rank1", (20, 96)),
+               ("rank1", (24, 128))] * 8
+    want = _steps(monkeypatch, PHASES, tensors, bf16)
+    got = _steps(monkeypatch, DEFERRED, tensors, bf16)
+    for (kind, shape), a, b in zip(tensors, want, got):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y, err_msg=f"{kind} {shape}")
+
+
 def test_launches_of_a_step(monkeypatch):
     """The host's count of a step's kernels on every route: both passes of one group, with two kernels between them for
     tensors of more than two dimensions; groups on two streams, one after the other and fused; and no plan at all."""

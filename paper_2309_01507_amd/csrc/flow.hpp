@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kThreads, FORM == kFlowRank1 ? 5 : FORM == kFlowRan
     }
     while (mine || n_left > 0) {
         // ready(): the tensor's first pass is complete (a deferred tile's is); the same answer in every thread.  It usually is long
-        // before, and the word read when the tile began says so; only else it is polled.
+        // before, and the word read when the tile began says so; only else it is polled.  spin_limit < 0: never, every tile is deferred.
         struct Sync {
             const Tensor4& a;
             const FlowArgs& f;
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kThreads, FORM == kFlowRank1 ? 5 : FORM == kFlowRan
             bool done = true;
             unsigned int ticket = 0u;
             __device__ __forceinline__ bool ready() {
-                if (!mine || __syncthreads_and(int(early == target))) return true;
+                if (!mine || __syncthreads_and(int(f.spin_limit >= 0 && early == target))) return true;
                 if (threadIdx.x == 0) {
                     int ok = 0;
                     for (int k = 0; k <= f.spin_limit; ++k) {

@@ -162,6 +162,34 @@ def test_deferred_by_the_workgroup_with_the_last_ticket(monkeypatch, bf16):
             np.testing.assert_array_equal(x, y, err_msg=f"{kind} {shape}")
 
 
+@pytest.mark.parametrize("kind,shape", [("rank1", (300, 512)), ("rank1", (257, 1023)), ("rank1", (300, 96)), ("nd", (24, 16, 3, 3)),
+                                        ("factor", (300, 512)), ("factor", (300, 96))])
+@pytest.mark.parametrize("spin,deferred", [("-1", True), ("20000", False)])
+def test_which_tiles_are_deferred(monkeypatch, kind, shape, spin, deferred):
+    """LPMM_FLOW_SPIN=-1 defers every tile of the second pass: the plan's list of them, zeros when it is built and not cleared by a
+    step, holds every number of a workgroup of that pass once afterwards (0 cannot be told from an empty place), and the rest
+    of the plan's workspace is zeros again.  With polls a second pass that waits is not deferred."""
+    for k in ROUTE:
+        monkeypatch.delenv(k, raising=False)
+    monkeypatch.setenv("LPMM_FLOW_MIN", "0")
+    monkeypatch.setenv("LPMM_FLOW_SPIN", spin)
+    lpmm.ensure_init(8192)
+    rows, cols = shape[0], int(np.prod(shape[1:]))
+    w, g = torch.zeros(rows * cols, device=DEV), torch.ones(rows * cols, device=DEV)
+    st = {"rank1": lambda: lpmm.new_state(rows, cols, DEV), "nd": lambda: lpmm.new_state_nd(shape, DEV),
+          "factor": lambda: lpmm.new_state_factor(rows, cols, DEV)}[kind]()
+    plan = lpmm.new_plan([lpmm.make_desc(w, g, st)], 0, DEV)
+    assert lpmm.lpmm_adamw4_plan_launches(plan) == 1
+    words = plan[:plan.numel() // 4 * 4].view(torch.int32)
+    before = words.clone()
+    lpmm.lpmm_adamw4_step_multi(plan, HP.lr, HP.beta1, HP.beta2, HP.eps, HP.weight_decay, 1)
+    torch.cuda.synchronize()
+    listed = sorted(words[words != before].tolist())
+    lpmm.lpmm_adamw4_plan_release(plan)
+    least = rows * cols // (8 * 1024)                     # no update tile of a set this small has more elements
+    assert listed == list(range(1, len(listed) + 1)) and (len(listed) + 1 >= max(2, least) if deferred else not listed)
+
+
 def test_launches_of_a_step(monkeypatch):
     """The host's count of a step's kernels on every route: both passes of one group, with two kernels between them for
     tensors of more than two dimensions; groups on two streams, one after the other and fused; and no plan at all."""

@@ -232,7 +232,7 @@ constexpr int kRawBufferWord3 = 0x00020000;     // untyped 32-bit data format, n
 typedef uint32_t v2u_t __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 constexpr int kPolicyNt = 2;
-constexpr uint32_t kNowhere = 0x7FFFFF00u;      // a byte offset beyond every tile (also after >> 1 and >> 3)
+constexpr uint32_t kNowhere = 0x7FFFFF00u;      // a byte offset beyond every tile (also after >> 1 and >> 3); the geometries see to it
 __device__ __forceinline__ Rsrc tile_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, int(bytes), kRawBufferWord3);
 }

@@ -225,7 +225,7 @@ void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint
         per_log2 = std::min(per_log2, rs);
         if (round_up(a->rows, int64_t(kGroups) << rs) > a->rows + a->rows / 16) rs = 0;
     }
-    while (rs > 0 && (int64_t(kGroups) << rs) * a->cols > (int64_t(1) << 29)) --rs;
+    while (rs > 0 && (int64_t(kGroups) << rs) * a->cols >= (int64_t(1) << 29)) --rs;
     while (per_log2 > 0 && (kGroups << per_log2) >= 2 * a->rows) --per_log2;
     auto tiles = [&] { return int64_t((a->nb + gx - 1) / gx) * (((a->rows + (kGroups << std::max(rs, per_log2)) - 1) >> (3 + std::max(rs, per_log2))) << (std::max(rs, per_log2) - per_log2)); };
     auto cut = [&] {
@@ -234,7 +234,7 @@ void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint
         else return false;
         return true;
     };
-    while (per_log2 > 0 && ((int64_t(kGroups) << per_log2) * a->cols) > (int64_t(1) << 29)) --per_log2;
+    while (per_log2 > 0 && ((int64_t(kGroups) << per_log2) * a->cols) >= (int64_t(1) << 29)) --per_log2;
     if (n_cu > 0) { while (tiles() < 2 * int64_t(n_cu) && cut()) {} }
     for (int k = 0; k < shrink && cut(); ++k) {}
     a->gx = gx;
@@ -343,9 +343,11 @@ void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
     a->strips2 = int((a->cols + 255) / 256);
     const int64_t rows2 = class_rows(*a);
     int64_t rw2 = n_cu ? 64 : std::max<int64_t>(128 >> shrink, kWaves);
-    while (rw2 > kWaves && rw2 * a->cols >= (int64_t(1) << 29)) rw2 /= 2;
+    // a tile reads its own rows and the one behind them, and kNowhere lies beyond all of them
+    auto fits = [&](int64_t r) { return (r + 1) * a->cols * 4 <= int64_t(kNowhere); };
+    while (rw2 > kWaves && !fits(rw2)) rw2 /= 2;
     while (n_cu && rw2 > kWaves && a->strips2 * ((rows2 + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 /= 2;
-    while (rw2 < 64 && rw2 * rw2 < a->rows / 4 && rw2 * a->cols < (int64_t(1) << 28)) rw2 *= 2;
+    while (rw2 < 64 && rw2 * rw2 < a->rows / 4 && fits(2 * rw2)) rw2 *= 2;
     a->rw2 = int(rw2);
     a->rs2 = 0;
     a->n_wg = int(a->strips2 * ((rows2 + rw2 - 1) / rw2));

@@ -136,3 +136,34 @@ def test_nan_in_one_second_moment_costs_that_element_only(monkeypatch, rows, col
     if cols > 2048:
         for x, y in ((ca, cb), (a.v_codes, b.v_codes), (a.v_r, b.v_r), (a.v_c, b.v_c), (wa, wb)):
             np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("rows,cols,plan,bf16", [(67, 8300001, False, False), (40, 16500001, False, True), (140, 4190001, True, True)])
+def test_tiles_near_two_gigabytes(monkeypatch, rows, cols, plan, bf16):
+    """Statistics tiles whose rows, with the one behind them, reach 2^31 bytes of fp32 elements, where the offset lies from which
+    lanes without columns read: it has to stay beyond the tile.  A large gradient at that element; from a state of zeros v_t is
+    (1 - beta2) g g, whose maxima are taken here by torch in the same operations."""
+    monkeypatch.setenv("LPMM_FLOW", "0")
+    n, hp = rows * cols, oracle.Hyper()
+    lpmm.ensure_init(rows + cols)
+    g = torch.rand(n, device=DEV, generator=torch.Generator(device=DEV).manual_seed(3))
+    g[0x7FFFFF00 // 4] = 64.0
+    if bf16:
+        g = g.to(torch.bfloat16)
+    w, st = torch.zeros(n, device=DEV), lpmm.new_state(rows, cols, DEV)
+    h = (hp.lr, hp.beta1, hp.beta2, hp.eps, hp.weight_decay, 1)
+    if plan:
+        buffer = lpmm.new_plan([lpmm.make_desc(w, g, st)], 1 if bf16 else 0, DEV)
+        lpmm.lpmm_adamw4_step_multi(buffer, *h)
+        torch.cuda.synchronize()
+        lpmm.lpmm_adamw4_plan_release(buffer)
+    else:
+        (lpmm.lpmm_adamw4_step_bf16g if bf16 else lpmm.lpmm_adamw4_step)(w, g, st, *h)
+    row, col = [], torch.zeros(cols, device=DEV)
+    omb2 = float(np.float32(1.0) - np.float32(hp.beta2))
+    for x in g.view(rows, cols):
+        x = x.float()
+        v = (omb2 * x) * x
+        row.append(v.max())
+        torch.maximum(col, v, out=col)
+    assert torch.equal(st.v_rowmax, torch.stack(row)) and torch.equal(st.v_colmax, col)

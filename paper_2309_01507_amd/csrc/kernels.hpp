@@ -146,16 +146,23 @@ constexpr int kElemsPerWg32 = kThreads * 16;   // fp32-state path: elements per 
 // elements 5.72, 6.05 and 6.58 TB/s with skew 0, 6.15, 6.62, 6.80 with half of it, 6.43, 6.80, 6.92 with it, 6.45, 6.80, 6.94
 // with the double; sizes whose eighths lie at other distances are the same with and without (45 M elements 6.45 / 6.49).
 constexpr int64_t kSkewElems = int64_t(1) << 19;
-__device__ __forceinline__ int skewed(int x, int i, int per_xcd, int skew) {
-    return x * per_xcd + int((unsigned(i) + unsigned(x) * unsigned(skew)) % unsigned(per_xcd));
-}
-// skew < 0: workgroups of very unequal cost, dealt to the XCDs in runs of kDealRun instead (the grid: a multiple of 8 of them).
-constexpr int kDealRun = 32;
+// skew < per_xcd (the host sees to it), so i + x * skew < 8 per_xcd and three conditional subtractions are the remainder: a
+// division here, in front of everything else a workgroup does, cost every kernel 0.3 us (statistics pass of 512 x 512 5.80 us
+// without a skew, 6.08 with the division, 5.64 as it is; step of 1024 x 1024 12.6 and 11.7).
 __device__ __forceinline__ int logical_wg(int skew) {
+    const unsigned x = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds;     // the grid is padded to a multiple of 8
+    unsigned i = blockIdx.x / kXcds + x * unsigned(skew);
+#pragma unroll
+    for (unsigned f = kXcds / 2; f >= 1; f /= 2) i -= i >= f * per_xcd ? f * per_xcd : 0u;
+    return int(x * per_xcd + i);
+}
+// Launches of workgroups of very unequal cost (kDealt in place of a skew) are dealt to the XCDs in runs of kDealRun instead; the
+// grid is a multiple of 8 of them.
+constexpr int kDealRun = 32, kDealt = -1;
+__device__ __forceinline__ int logical_wg_or_dealt(int skew) {
+    if (skew != kDealt) return logical_wg(skew);
     const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
-    if (skew < 0) return (i / kDealRun * kXcds + x) * kDealRun + i % kDealRun;
-    const int per_xcd = gridDim.x / kXcds;                                 // the grid is padded to a multiple of 8
-    return skew == 0 ? x * per_xcd + i : skewed(x, i, per_xcd, skew);
+    return (i / kDealRun * kXcds + x) * kDealRun + i % kDealRun;
 }
 
 constexpr int kWaitVmcnt0 = 0x0F70;   // s_waitcnt vmcnt(0) only: expcnt and lgkmcnt fields at their maxima

@@ -224,7 +224,7 @@ template <bool BF16, int ROLES>
 __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);
     __shared__ LdsRank1 s;
-    const int x = logical_wg(ROLES == 2 ? ph.skew_b : ph.skew_a);
+    const int x = logical_wg_or_dealt(ROLES == 2 ? ph.skew_b : ph.skew_a);
     constexpr bool kOnlyA = ROLES == 1 || ROLES == 3;
     constexpr bool kOnlyB = ROLES == 2;
     const int n = (kOnlyB ? 0 : ph.n_a) + (kOnlyA ? 0 : ph.n_b);

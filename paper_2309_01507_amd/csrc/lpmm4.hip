@@ -124,10 +124,12 @@ bool is_rank1(int kind) { return kind == kQuantFast || kind == kQuantRagged || k
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 int pad8(int64_t n) { return int(round_up(n, kXcds)); }
 
-// workgroups (of n, for `elems` elements) that make up kSkewElems elements, at least 1
-int skew_of(int64_t n, int64_t elems) { return int(std::max<int64_t>(1, int64_t(double(n) * double(kSkewElems) / double(std::max<int64_t>(elems, 1)) + 0.5))); }
-// a launch for one tensor: none below 2^23 elements, whose eighths two or fewer such distances fill, and where the division in
-// front of everything else a workgroup does is part of the step's time (1024 x 1024 fp32 rank-1 12.51 us with it, 12.40 without)
+// workgroups (of n, for `elems` elements) that make up kSkewElems elements, at least 1; less than an eighth of them all
+int skew_of(int64_t n, int64_t elems) {
+    const int64_t skew = int64_t(double(n) * double(kSkewElems) / double(std::max<int64_t>(elems, 1)) + 0.5);
+    return int(std::max<int64_t>(1, skew) % std::max<int64_t>(1, round_up(n, kXcds) / kXcds));
+}
+// a launch for one tensor: none below 2^23 elements, whose eighths two or fewer such distances fill
 void set_skew(Tensor4* t) {
     const bool some = t->P >= int64_t(1) << 23;
     t->skew = some ? skew_of(t->n_wg, t->P) : 0;
@@ -1893,8 +1895,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         // give some XCDs several times the work of others (30000 x 96 beside 1024 x 4096, bf16 gradients: 0.4 of the parameters
         // in the narrow ones 376 us in eighths, 319 in runs; 0.58 282 and 267; 0.85 401 and 422).
         const bool mixed = general > 0 && general * 3 < (elems_a + elems_b) * 2;
-        pl.ph.skew_a = mixed ? -1 : skew_of(pl.ph.n_a, elems_a);
-        pl.ph.skew_b = mixed ? -1 : skew_of(pl.ph.n_b, elems_b);
+        pl.ph.skew_a = mixed ? kDealt : skew_of(pl.ph.n_a, elems_a);
+        pl.ph.skew_b = mixed ? kDealt : skew_of(pl.ph.n_b, elems_b);
         if (int64_t(pl.ph.n_a) + pl.ph.n_b > (int64_t(1) << 30)) return LPMM_EINVAL;
         auto grid_of = [&](int64_t n) { return mixed ? int(round_up(n, kXcds * kDealRun)) : pad8(n); };
         pl.grid = grid_of(int64_t(pl.ph.n_a) + pl.ph.n_b);

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kThreads, FORM == kFlowRank1 ? 5 : FORM == kFlowRan
             a.counter[tot_old_word(threadIdx.x)] = 0u;
         }
     } else {
-        move_statistics<true>(a);
+        move_statistics<true>(a, request_statistics<true>(a, 0));
     }
     if (threadIdx.x == 0) {
         *a.counter = 0u;

@@ -21,12 +21,12 @@ __global__ __launch_bounds__(kThreads) void maxima_fast(const Tensor4 a, const H
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void update_fast(const Tensor4 a, const Hyper h) {
     __shared__ LdsRank1 s;
-    __shared__ int s_last;
+    __shared__ int s_last[2];
     const int wg = logical_wg(a.skew2);
     if (wg >= a.n_wg2) return;
     TicketSync sync{a.counter, unsigned(wg), 0u};
     update_tile<BF16, false>(a, h, wg, s, sync);
-    if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) publish(a);
+    finish_rank1(a, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last);
 }
 
 template <bool BF16>
@@ -105,9 +105,10 @@ __global__ __launch_bounds__(kThreads) void pass1_general(const Tensor4 a, const
 
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void pass2_general(const Tensor4 a, const Hyper h) {
-    __shared__ int s_last;
+    __shared__ int s_last[2];
     pass2_general_chunk<BF16>(a, h, int64_t(blockIdx.x) * kGenChunkElems);
-    publish_if_last(a, blockIdx.x, gridDim.x, s_last);
+    __syncthreads();
+    finish_rank1(a, blockIdx.x, gridDim.x, take_ticket(a.counter, blockIdx.x), s_last);
 }
 
 template <bool BF16>
@@ -120,12 +121,12 @@ __global__ __launch_bounds__(kThreads) void maxima_ragged_kernel(const Tensor4 a
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void update_ragged_kernel(const Tensor4 a, const Hyper h) {
     __shared__ LdsRank1 s;
-    __shared__ int s_last;
+    __shared__ int s_last[2];
     const int wg = logical_wg(a.skew2);
     if (wg >= a.n_wg2) return;
     TicketSync sync{a.counter, unsigned(wg), 0u};
     update_ragged<BF16, false>(a, h, wg, s, sync);
-    if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) publish(a);
+    finish_rank1(a, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last);
 }
 
 template <bool BF16>
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
     const int b_before = kOnlyA ? 0 : (kOnlyB ? x : int((int64_t(x) * ph.n_b) / n));
     const int b_after = kOnlyA ? 0 : (kOnlyB ? x + 1 : int((int64_t(x + 1) * ph.n_b) / n));
     if (!kOnlyA && b_after > b_before) {
-        __shared__ int s_last;
+        __shared__ int s_last[2];
         const Segment sg = find_segment(ph.seg_b, ph.n_seg_b, b_before);
         const Tensor4 a = from_table(ph.tensors[sg.tensor]);
         const Hyper ht = for_tensor(h, a);
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
             __syncthreads();
             sync.staged();
         }
-        if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) publish(a);
+        finish_rank1(a, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last);
     } else if (!kOnlyB) {
         const int xa = x - b_before;
         const Segment sg = find_segment(ph.seg_a, ph.n_seg_a, xa);

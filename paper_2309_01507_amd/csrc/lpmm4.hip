@@ -212,8 +212,10 @@ void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint
     // rows of a group: a power of two
     int per_log2 = 0;
     // two of them; one where a large matrix is stepped on its own (32000 x 4096 fp32 400 us, with two 405; 11008 x 4096 bf16 111.5
-    // and 113.8; 4096 x 4096 bf16 46.9 and 46.2)
-    const int64_t rw_want = env_int("LPMM_RW", 0) > 0 ? env_int("LPMM_RW", 0) : rw_hint > 0 ? rw_hint : n_cu > 0 && a->P >= int64_t(1) << 25 ? 8 : 16;
+    // and 113.8; 4096 x 4096 bf16 46.9 and 46.2); narrow matrices, on their own, as many as give a group 8 blocks (bf16, with one row
+    // and with 8 / gx: 1000000 x 128 895 and 710 us, 131072 x 384 179 and 176, 262144 x 512 373 and 362)
+    const int64_t rw_one = std::max(n_cu > 0 && a->P >= int64_t(1) << 25 ? kGroups : 2 * kGroups, n_cu > 0 ? kGroups * kFlatBlocks / gx : 0);
+    const int64_t rw_want = env_int("LPMM_RW", 0) > 0 ? env_int("LPMM_RW", 0) : rw_hint > 0 ? rw_hint : rw_one;
     const bool fixed = env_int("LPMM_RW", 0) > 0;
     while (per_log2 < 3 && (kGroups << (per_log2 + 1)) <= rw_want) ++per_log2;
     // Rows between the groups: 32 KiB of parameters where a power of two of rows is exactly that long (rows of 128 to 8192
@@ -237,7 +239,9 @@ void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint
         return true;
     };
     while (per_log2 > 0 && ((int64_t(kGroups) << per_log2) * a->cols) >= (int64_t(1) << 29)) --per_log2;
-    if (n_cu > 0) { while (tiles() < 2 * int64_t(n_cu) && cut()) {} }
+    // two workgroups per CU, three while a group has more than 8 blocks (3072 x 3072 bf16 576 tiles 35.3 us, 1152 32.8; 4096 x 2048
+    // 512 27.8, 1024 26.5)
+    if (n_cu > 0) { while (tiles() < ((gx << per_log2) > kFlatBlocks ? 3 : 2) * int64_t(n_cu) && cut()) {} }
     for (int k = 0; k < shrink && cut(); ++k) {}
     a->gx = gx;
     a->gy = kGroups;
@@ -251,6 +255,10 @@ void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint
     if (rw2 <= 0) rw2 = rw2_hint > 0 ? rw2_hint : 128;
     rw2 = std::clamp<int64_t>(rw2, 1, std::min<int64_t>({cap, kMaxRowSlots, a->rows}));
     while (n_cu > 0 && !fixed2 && rw2 > 2 * kGroups && a->strips2 * ((a->rows + rw2 - 1) / rw2) < int64_t(n_cu)) rw2 = round_up(rw2 / 2, kGroups);
+    // Tall narrow ones take more rows: every tile ends with an atomic per column, and atomics on one address follow each other (at
+    // 128 rows and at 512: 262144 x 128 fp32 211 and 196 us, 1000000 x 128 bf16 711 and 633; 262144 x 256 fp32 287 and, at 256, 283).
+    if (n_cu > 0 && !fixed2)
+        while (rw2 < kMaxRowSlots && rw2 * a->cols < 1 << 16 && a->strips2 * (a->rows / (2 * rw2)) >= 2 * int64_t(n_cu)) rw2 *= 2;
     a->rw2 = int(rw2);
     a->n_wg = int(a->strips2 * ((a->rows + rw2 - 1) / rw2));
     a->rs2 = row_spacing_log2(a->cols * grad_bytes, rw2, kGroups, "LPMM_RS2");

@@ -44,6 +44,12 @@ def test_tile_edges(rows, cols, bf16):
     _check(rows, cols, bf16)
 
 
+@pytest.mark.parametrize("rows,cols,bf16", [(131333, 128, False), (66000, 256, True), (2900, 3072, True)])
+def test_tall_and_narrow(rows, cols, bf16):
+    """Tiles of 64 rows in the second pass, up to 512 rows in the first; 3 workgroups of the second pass per CU."""
+    _check(rows, cols, bf16, steps=2)
+
+
 @pytest.mark.parametrize("rows,cols", [(40, 1152), (70, 257)])
 def test_extreme_scales(rows, cols):
     """Second moments around 2^-120: scales below 2^-100, which neither a reciprocal nor a sixteenth keeps whole."""

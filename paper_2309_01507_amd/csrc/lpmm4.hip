@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <limits>
 #include <memory>
 #include <mutex>
 #include <unordered_map>
@@ -852,6 +853,11 @@ constexpr double kFlowLead = 16.0 * (1 << 20), kFlowLeadSpread = 20.0 * (1 << 20
 // 790 with), five instead of six (factorized: 747 us at six, 711 at five, 730 at four).  More of them only move the point up to
 // which the list has been handed out further ahead of the first passes that the second ones wait for.
 constexpr unsigned kFlowLdsPad = 16000, kFlowLdsPadFactor = 8000;
+// From here to kFlowMinParams the updates of tensors with more than two dimensions come after all others (see build_flow), and
+// ragged tiles are twice as tall: vision sets, fp32, us before both / with the order alone / with both: 9.8 M parameters 48.1 /
+// 51.0 / 49.1, 12.8 M 53.5 / 51.5 / 51.8, 16 M 71.7 / 67.6 / 64.3, 24 M 101.6 / 93.7 / 90.6, 31 M 125 / 118.6 / 113.1; 7.4 M
+// 37.0 / 40.2.
+constexpr int64_t kFlowNdLate = kFlowMinParams / 8 * 3;
 void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int grad_bytes) {
     constexpr int kCus = 256;
     const int shrink = total >= kFlowMinParams ? 0 : total >= kFlowMinParams / 4 ? 1 : 2;
@@ -870,7 +876,7 @@ void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int
         rank1_fast_geometry(t, 0, rw, rw2, grad_bytes, shrink ? 1 : 0);
     } else if (ragged_eligible(t->rows, t->cols)) {
         t->kind = kQuantRagged;
-        ragged_geometry(t, 0, shrink ? 3 : 0);
+        ragged_geometry(t, 0, !shrink ? 0 : total >= kFlowNdLate ? 2 : 3);
     } else {
         t->kind = kQuantGeneral;
         general_geometry(t, kCus);
@@ -1012,7 +1018,8 @@ bool plan_layout(const lpmm_tensor_desc* descs, int64_t n, const int64_t* inner_
 // piece: factorized GPT-2-medium 711 / 738 us; rank-1 with rows of 1472 1272 / 1297; but rank-1 with rows of 4096 4.29 / 4.24
 // ms).  Tensors with more than two dimensions come first, the widest ones ahead: one workgroup turns their maxima into
 // statistics between the passes, and that takes longest where there are many columns.  Then the largest ones: what is left at
-// the end is the second pass of the smallest.
+// the end is the second pass of the smallest.  In sets of kFlowNdLate to kFlowMinParams parameters, whose first passes all
+// together are short beside that one workgroup, the others' updates run meanwhile and those of such tensors follow at the end.
 //
 // Workgroups are laid out eight at a time: ids are dealt to the 8 XCDs in turn, and the eight of a row take their tiles from eight
 // equal contiguous parts of the pass (skewed as in logical_wg), so that neighbouring tiles, which share cache lines, stay on one
@@ -1079,13 +1086,20 @@ void build_flow(const lpmm_tensor_desc* descs, int64_t n, const PlanLayout& L, c
     }
     struct Timed { double time; Row row; };
     std::vector<Timed> first, second;
+    auto is_nd = [&](size_t k) { return descs[order[k]].kind == LPMM_KIND_4BIT_ND; };
+    const bool late = total >= kFlowNdLate && total < kFlowMinParams;
+    std::vector<size_t> updates(order.size());              // the tensors in the order of their second passes
+    std::iota(updates.begin(), updates.end(), size_t(0));
+    if (late) std::stable_partition(updates.begin(), updates.end(), [&](size_t k) { return !is_nd(k); });
     double begin = 0.0;
-    for (size_t k = 0; k < order.size(); ++k) {
+    for (const size_t k : updates) {
         const Tensor4& t = flow[order[k]];
         const double length = double(t.P), n1 = double(passes[k].first.size()), n2 = double(passes[k].second.size());
-        const double spread = t.kind == kQuantFast ? 0.0 : length;
-        for (const Row& r : passes[k].first)
-            first.push_back(Timed{begin - (spread > 0.0 ? kFlowLeadSpread : kFlowLead) - spread * (1.0 - double(&r - passes[k].first.data()) / n1), r});
+        const double spread = t.kind == kQuantFast ? 0.0 : length, lead = spread > 0.0 ? kFlowLeadSpread : kFlowLead;
+        for (const Row& r : passes[k].first) {
+            const double at = begin - lead - spread * (1.0 - double(&r - passes[k].first.data()) / n1);
+            first.push_back(Timed{late && is_nd(k) ? std::numeric_limits<double>::lowest() : at, r});    // ahead of everything
+        }
         for (const Row& r : passes[k].second) second.push_back(Timed{begin + length * double(&r - passes[k].second.data()) / n2, r});
         begin += length;
     }

@@ -162,6 +162,19 @@ def test_deferred_by_the_workgroup_with_the_last_ticket(monkeypatch, bf16):
             np.testing.assert_array_equal(x, y, err_msg=f"{kind} {shape}")
 
 
+@pytest.mark.parametrize("env", [{}, {"LPMM_FLOW_SPIN": "-1"}], ids=["waiting", "deferred"])
+def test_updates_of_convolutions_at_the_end(monkeypatch, env):
+    """A set between 12.6 and 33.5 million parameters: all updates but the convolutions' come first, ragged tiles are of middle
+    height."""
+    tensors = [("nd", (512, 256, 3, 3)), ("rank1", (2944, 2944)), ("nd", (736, 368, 3, 3)), ("rank1", (1000, 1472)), ("fp32", (1, 736)),
+               ("nd", (16, 3, 7, 7))]
+    want = _steps(monkeypatch, PHASES, tensors, False, steps=2)
+    got = _steps(monkeypatch, env, tensors, False, steps=2)
+    for (kind, shape), a, b in zip(tensors, want, got):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y, err_msg=f"{kind} {shape}")
+
+
 @pytest.mark.parametrize("kind,shape", [("rank1", (300, 512)), ("rank1", (257, 1023)), ("rank1", (300, 96)), ("nd", (24, 16, 3, 3)),
                                         ("factor", (300, 512)), ("factor", (300, 96)), ("rank1", (8192, 2048)),
                                         ("rank1", (16000, 1000)), ("factor", (8192, 2048))])

@@ -727,24 +727,32 @@ __device__ __forceinline__ bool last_to_arrive(unsigned int* counter, unsigned i
 // The end of a second pass that is a launch of its own: every workgroup calls this with its ticket, and the one with the last
 // makes r', c' the state.  A workgroup whose ticket completed a first-level counter (32 of them at most) requests what is to be
 // published, final since the first pass ended, beside the top counter's answer: one round trip to the memory less in the chain
-// at the step's end (fp32, us per step: 768 x 3072 15.2 -> 14.6, 4096 x 1024 19.7 -> 18.8).  The factorized form, which reads the old
-// statistics, too, gains nothing from it.
+// at the step's end (fp32, us per step: 768 x 3072 15.2 -> 14.6, 4096 x 1024 19.7 -> 18.8).  Not below four workgroups to a
+// first-level counter: there most workgroups would request it in vain (200 tensors of 256 x 512, bf16 gradients: 87.8 us, without 85.0).  The
+// factorized form, which reads the old statistics, too, gains nothing from it.
+constexpr unsigned int kFinishMany = 4 * kTicketLanes;
 __device__ __forceinline__ void finish_rank1(const Tensor4& a, unsigned int me, unsigned int participants, unsigned int ticket,
                                              int (&s_last)[2]) {
-    const unsigned int lane = me % kTicketLanes;
-    const unsigned int in_lane = participants / kTicketLanes + (lane < participants % kTicketLanes ? 1u : 0u);
-    if (threadIdx.x == 0) s_last[0] = ticket == in_lane - 1;
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(s_last[0]) == 0) return;
-    unsigned int top = 0u;
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(a.counter + (1 + lane) * kTicketStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        top = atomicAdd(a.counter, 1u);
+    StatRegs v;
+    if (participants < kFinishMany) {
+        if (!ticket_is_last(a.counter, me, participants, ticket, s_last[0])) return;
+        v = request_statistics<false>(a, 0);
+    } else {
+        const unsigned int lane = me % kTicketLanes;
+        const unsigned int in_lane = participants / kTicketLanes + (lane < participants % kTicketLanes ? 1u : 0u);
+        if (threadIdx.x == 0) s_last[0] = ticket == in_lane - 1;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(s_last[0]) == 0) return;
+        unsigned int top = 0u;
+        if (threadIdx.x == 0) {
+            __hip_atomic_store(a.counter + (1 + lane) * kTicketStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            top = atomicAdd(a.counter, 1u);
+        }
+        v = request_statistics<false>(a, 0);
+        if (threadIdx.x == 0) s_last[1] = top == lanes_used(participants) - 1;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(s_last[1]) == 0) return;
     }
-    const StatRegs v = request_statistics<false>(a, 0);
-    if (threadIdx.x == 0) s_last[1] = top == lanes_used(participants) - 1;
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(s_last[1]) == 0) return;
     move_statistics<false>(a, v);
     if (threadIdx.x == 0) *a.counter = 0u;
 }

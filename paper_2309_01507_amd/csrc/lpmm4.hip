@@ -213,9 +213,10 @@ void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint
     // rows of a group: a power of two
     int per_log2 = 0;
     // two of them; one where a large matrix is stepped on its own (32000 x 4096 fp32 400 us, with two 405; 11008 x 4096 bf16 111.5
-    // and 113.8; 4096 x 4096 bf16 46.9 and 46.2); narrow matrices, on their own, as many as give a group 8 blocks (bf16, with one row
-    // and with 8 / gx: 1000000 x 128 895 and 710 us, 131072 x 384 179 and 176, 262144 x 512 373 and 362)
-    const int64_t rw_one = std::max(n_cu > 0 && a->P >= int64_t(1) << 25 ? kGroups : 2 * kGroups, n_cu > 0 ? kGroups * kFlatBlocks / gx : 0);
+    // and 113.8; 4096 x 4096 bf16 46.9 and 46.2); narrow matrices as many as give a group 8 blocks (bf16, with one row and with 8 /
+    // gx: 1000000 x 128 895 and 710 us, 131072 x 384 179 and 176, 262144 x 512 373 and 362; in plans, with two: 8 of 131072 x 128 419 and
+    // 334, 289 tensors of a transformer of width 256 111 and 96)
+    const int64_t rw_one = std::max(n_cu > 0 && a->P >= int64_t(1) << 25 ? kGroups : 2 * kGroups, kGroups * kFlatBlocks / gx);
     const int64_t rw_want = env_int("LPMM_RW", 0) > 0 ? env_int("LPMM_RW", 0) : rw_hint > 0 ? rw_hint : rw_one;
     const bool fixed = env_int("LPMM_RW", 0) > 0;
     while (per_log2 < 3 && (kGroups << (per_log2 + 1)) <= rw_want) ++per_log2;

@@ -1927,10 +1927,13 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         pl.grid_b = grid_of(pl.ph.n_b);
         host->phases.push_back(pl);
     }
-    // Plans take their launches one after the other on the caller's stream by default: a first pass (read-only) and an
-    // update each run at the memory system's rate alone, and side by side they only get in each other's way (factorized
-    // 7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
-    const int stream_mode = env_int("LPMM_MULTI_STREAMS", 0);
+    // Rank-1 plans of several groups run second passes on a stream of their own beside the next group's first pass: what takes
+    // launches by phases is mostly many small tensors, whose launches leave the chip half empty (one after the other / on two
+    // streams, bf16 gradients: 300 of 200 x 300 108 / 103 us, 224 adapters of 8 x 4096 and 4096 x 8 139 / 119, 256 of 64 x 4096 and 4096 x
+    // 64 326 / 314).  A group's passes follow each other in any case.  Factorized plans take their launches one after the other: a
+    // statistics pass and an update each run at the memory system's rate alone, and side by side they only get in each other's way
+    // (7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
+    const int stream_mode = env_int("LPMM_MULTI_STREAMS", host->factor || host->sgdm ? 0 : 2);
     host->serial = stream_mode == 0 && !host->sgdm;
     bool any_b = false;
     for (const PhaseLaunch& pl : host->phases) any_b = any_b || pl.ph.n_b > 0;

@@ -2,6 +2,8 @@
 // one tensor, the phase kernels of the multi-tensor plans, and the small kernels between and around them.
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "ragged.hpp"
 
@@ -218,16 +220,16 @@ __device__ __forceinline__ Segment find_segment(const Segment* seg, int n_seg, i
 }
 
 // ROLES: 0 = A and B work interleaved in one launch; 1 = A work only; 2 = B work only; 3 = A work
-// only of a group without rank-1 tensors (block-wise and fp32-state tensors: no rank-1 code).  The
-// single-role kernels exist because a kernel's register and LDS footprint is that of its heaviest
+// only of a group without rank-1 tensors (block-wise and fp32-state tensors: no rank-1 code); 4 = B work only of tensors on
+// the general tiles.  The single-role kernels exist because a kernel's register and LDS footprint is that of its heaviest
 // path.
 template <bool BF16, int ROLES>
 __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);
-    __shared__ LdsRank1 s;
-    const int x = logical_wg_or_dealt(ROLES == 2 ? ph.skew_b : ph.skew_a);
     constexpr bool kOnlyA = ROLES == 1 || ROLES == 3;
-    constexpr bool kOnlyB = ROLES == 2;
+    constexpr bool kOnlyB = ROLES == 2 || ROLES == 4;
+    __shared__ std::conditional_t<kOnlyA, Lds, LdsRank1> s;
+    const int x = ROLES == 2 ? logical_wg_or_dealt(ph.skew_b) : logical_wg(kOnlyB ? ph.skew_b : ph.skew_a);
     const int n = (kOnlyB ? 0 : ph.n_a) + (kOnlyA ? 0 : ph.n_b);
     if (x >= n) return;
     // B workgroups sit at the positions where floor(x * n_b / n) steps up
@@ -240,14 +242,13 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
         const Hyper ht = for_tensor(h, a);
         const int wg = b_before - sg.wg_begin;
         TicketSync sync{a.counter, unsigned(wg), 0u};
-        if (a.kind == kQuantFast) {
-            update_tile<BF16, false>(a, ht, wg, s, sync);
-        } else if (a.kind == kQuantRagged) {
-            update_ragged<BF16, false>(a, ht, wg, s, sync);
-        } else {
+        if (ROLES == 4 || a.kind == kQuantGeneral) {
             pass2_general_chunk<BF16>(a, h, int64_t(wg) * kGenChunkElems);
             __syncthreads();
             sync.staged();
+        } else if constexpr (!kOnlyA && ROLES != 4) {
+            if (a.kind == kQuantFast) update_tile<BF16, false>(a, ht, wg, s, sync);
+            else update_ragged<BF16, false>(a, ht, wg, s, sync);
         }
         finish_rank1(a, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last);
     } else if (!kOnlyB) {

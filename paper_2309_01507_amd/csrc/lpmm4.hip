@@ -763,6 +763,10 @@ struct PhaseLaunch {
     int grid;        // both kinds in one launch
     int grid_a;      // A work alone
     int grid_b;      // B work alone
+    bool b_general;     // every B tensor of `ph` is on the general tiles (a lighter kernel variant runs)
+    // the B tensors on the general tiles where they have a launch of their own, behind that of the others
+    Phase gen;
+    int grid_gen;
     bool a_has_rank1;   // some A tensor takes the first pass of the rank-1 path (else the lighter kernel variant runs)
     // tensors with more than two dimensions among the B tensors: two small kernels run before their second pass
     NdPhase nd;
@@ -1873,11 +1877,17 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             for (int64_t i = gr.first; i < gr.second; ++i) set_geometry(tens[i], descs[i], shrink);
         }
     }
+    // Rank-1 plans of several groups run second passes on a stream of their own beside the next group's first pass: what takes
+    // launches by phases is mostly many small tensors, whose launches leave the chip half empty (one after the other / on two
+    // streams, bf16 gradients: 300 of 200 x 300 108 / 103 us, 224 adapters of 8 x 4096 and 4096 x 8 139 / 119, 256 of 64 x 4096 and 4096 x
+    // 64 326 / 314).  A group's passes follow each other in any case.  Factorized plans take their launches one after the other: a
+    // statistics pass and an update each run at the memory system's rate alone, and side by side they only get in each other's way
+    // (7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
+    const int stream_mode = env_int("LPMM_MULTI_STREAMS", host->factor || host->sgdm ? 0 : 2);
     for (size_t j = 0; j <= groups.size() && !host->flow; ++j) {
         PhaseLaunch pl{};
-        int64_t elems_a = 0, elems_b = 0;
-        int64_t general = 0;                // of the parameters, those on the rank-1 form's general tiles
-        auto count = [&](const Tensor4& t) { if (t.kind == kQuantGeneral) general += t.P; };
+        int64_t elems_a = 0, elems_b = 0, elems_gen = 0;
+        int64_t general_b = 0;              // of elems_b, those on the rank-1 form's general tiles
         pl.ph.tensors = reinterpret_cast<const Tensor4Table*>(d_tens);
         if (j < groups.size())
             for (int64_t i = groups[j].first; i < groups[j].second; ++i) {
@@ -1885,17 +1895,31 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
                 if (is_rank1(tens[i].kind)) pl.a_has_rank1 = true;
                 pl.ph.n_a += tens[i].n_wg;
                 elems_a += tens[i].P;
-                count(tens[i]);
             }
+        // The second pass of the general tiles gathers, and what it needs is many waves: 62 registers and no LDS, where the others'
+        // update takes 85 and 24 KB.  Beside others it gets a launch of its own where that saves more than the launch and its tail
+        // cost, from 2^23 parameters on and where it is two thirds of the group (seven of 30000 x 96 and two of 1024 x 4096, fp32: together
+        // 242 us, apart 197; three and one 126 and 110; twelve and six, 0.58, 407 and 412; half, 64 x 4096 and 4096 x 64, 149 and 159; 5.8 M
+        // and 2 M parameters 87 and 91).
+        bool split = false;
+        if (j >= 1 && (stream_mode == 0 || stream_mode >= 2)) {
+            int64_t narrow = 0, others = 0;
+            for (int64_t i = groups[j - 1].first; i < groups[j - 1].second; ++i)
+                (tens[i].kind == kQuantGeneral ? narrow : others) += is_rank1(tens[i].kind) ? tens[i].P : 0;
+            split = narrow >= int64_t(1) << 23 && others > 0 && narrow >= 2 * others;
+        }
         if (j >= 1)
             for (int64_t i = groups[j - 1].first; i < groups[j - 1].second; ++i) {
                 if (tens[i].kind == kFp32State || tens[i].kind == kQuantBlockV || tens[i].kind == kSgdmBlock ||
                     tens[i].kind == kSgdmFp32)
                     continue;
-                pl.ph.seg_b[pl.ph.n_seg_b++] = Segment{pl.ph.n_b, int(i)};
-                pl.ph.n_b += tens[i].n_wg2;
-                elems_b += tens[i].P;
-                count(tens[i]);
+                const bool apart = split && tens[i].kind == kQuantGeneral;
+                Phase& to = apart ? pl.gen : pl.ph;
+                if (!apart) pl.b_general = (pl.ph.n_b == 0 || pl.b_general) && tens[i].kind == kQuantGeneral;
+                to.seg_b[to.n_seg_b++] = Segment{to.n_b, int(i)};
+                to.n_b += tens[i].n_wg2;
+                (apart ? elems_gen : elems_b) += tens[i].P;
+                if (!apart && tens[i].kind == kQuantGeneral) general_b += tens[i].P;
                 if (tens[i].det) {
                     pl.has_det = true;
                     pl.det.seg_r[pl.det.n_seg++] = Segment{pl.det.n_r, int(i)};
@@ -1914,26 +1938,35 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         pl.nd.dims = d_dims;
         pl.det.tensors = pl.ph.tensors;
         if (pl.ph.n_a + pl.ph.n_b == 0) continue;
-        // The general tiles' first pass is most of their work, the other tiles' second pass is: eighths of a launch that has both
-        // give some XCDs several times the work of others (30000 x 96 beside 1024 x 4096, bf16 gradients: 0.4 of the parameters
-        // in the narrow ones 376 us in eighths, 319 in runs; 0.58 282 and 267; 0.85 401 and 422).
-        const bool mixed = general > 0 && general * 3 < (elems_a + elems_b) * 2;
-        pl.ph.skew_a = mixed ? kDealt : skew_of(pl.ph.n_a, elems_a);
-        pl.ph.skew_b = mixed ? kDealt : skew_of(pl.ph.n_b, elems_b);
+        // A workgroup of the general tiles' second pass takes 2048 elements, of the other tiles' up to 16384: where the list has the
+        // narrow tensors in one place, eighths of the launch would give one XCD most of the others' work, and it is dealt in runs (three
+        // of 30000 x 96 before three of 1024 x 4096, fp32 and bf16 gradients: 190 and 158 us in eighths, 138 and 116 in runs; 64 x 4096
+        // and 4096 x 64 in turn, 268 M parameters, even as they are: 1251 and 1251, in runs 1287 and 1280).  First passes keep the
+        // eighths: in runs all XCDs raise the same tensor's column maxima at a time (157 and 146 in place of 138 and 116).
+        bool dealt = false;
+        if (general_b > 0) {
+            double part[kXcds] = {};
+            const double eighth = double(std::max(pad8(pl.ph.n_b), kXcds)) / kXcds;
+            for (int k = 0; k < pl.ph.n_seg_b; ++k) {
+                const Tensor4& t = tens[pl.ph.seg_b[k].tensor];
+                const double begin = pl.ph.seg_b[k].wg_begin, end = begin + t.n_wg2;
+                for (int x = 0; x < kXcds; ++x)
+                    part[x] += double(t.P) * std::max(0.0, std::min(end, (x + 1) * eighth) - std::max(begin, x * eighth)) / (end - begin);
+            }
+            dealt = *std::max_element(part, part + kXcds) > 1.25 * double(elems_b) / kXcds;
+        }
+        auto skew = [](int n, int64_t elems) { return elems < int64_t(1) << 23 ? 0 : skew_of(n, elems); };       // as in set_skew
+        pl.ph.skew_a = skew(pl.ph.n_a, elems_a);
+        pl.ph.skew_b = dealt ? kDealt : skew(pl.ph.n_b, elems_b);
         if (int64_t(pl.ph.n_a) + pl.ph.n_b > (int64_t(1) << 30)) return LPMM_EINVAL;
-        auto grid_of = [&](int64_t n) { return mixed ? int(round_up(n, kXcds * kDealRun)) : pad8(n); };
-        pl.grid = grid_of(int64_t(pl.ph.n_a) + pl.ph.n_b);
-        pl.grid_a = grid_of(pl.ph.n_a);
-        pl.grid_b = grid_of(pl.ph.n_b);
+        pl.grid_a = pad8(pl.ph.n_a);
+        pl.grid_b = dealt ? int(round_up(pl.ph.n_b, kXcds * kDealRun)) : pad8(pl.ph.n_b);
+        pl.grid = pl.ph.n_a == 0 ? pl.grid_b : pad8(int64_t(pl.ph.n_a) + pl.ph.n_b);
+        pl.gen.tensors = pl.ph.tensors;
+        pl.gen.skew_b = skew(pl.gen.n_b, elems_gen);
+        pl.grid_gen = pad8(pl.gen.n_b);
         host->phases.push_back(pl);
     }
-    // Rank-1 plans of several groups run second passes on a stream of their own beside the next group's first pass: what takes
-    // launches by phases is mostly many small tensors, whose launches leave the chip half empty (one after the other / on two
-    // streams, bf16 gradients: 300 of 200 x 300 108 / 103 us, 224 adapters of 8 x 4096 and 4096 x 8 139 / 119, 256 of 64 x 4096 and 4096 x
-    // 64 326 / 314).  A group's passes follow each other in any case.  Factorized plans take their launches one after the other: a
-    // statistics pass and an update each run at the memory system's rate alone, and side by side they only get in each other's way
-    // (7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
-    const int stream_mode = env_int("LPMM_MULTI_STREAMS", host->factor || host->sgdm ? 0 : 2);
     host->serial = stream_mode == 0 && !host->sgdm;
     bool any_b = false;
     for (const PhaseLaunch& pl : host->phases) any_b = any_b || pl.ph.n_b > 0;
@@ -2034,7 +2067,8 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
     }
     const unsigned pad3 = one_pass_lds_pad(*host);
     // roles: 0 = A and B work in one launch, 1 = A only, 2 = B only, 3 = A only without rank-1 tensors
-    auto launch = [&](int roles, int grid, hipStream_t on, const PhaseLaunch& pl) {
+    // B work: behind it, where they are apart, the tensors on the general tiles
+    auto launch = [&](int roles, int grid, hipStream_t on, const PhaseLaunch& pl) -> int {
 #define LPMM_PHASE_CASE(K, R)                                                                               \
         if (bf16) hipLaunchKernelGGL((K<true, R>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);            \
         else hipLaunchKernelGGL((K<false, R>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);
@@ -2045,10 +2079,18 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         } else {
             if (roles == 0) { LPMM_PHASE_CASE(phase_kernel, 0) }
             else if (roles == 1) { LPMM_PHASE_CASE(phase_kernel, 1) }
+            else if (roles == 2 && pl.b_general) { LPMM_PHASE_CASE(phase_kernel, 4) }
             else if (roles == 2) { LPMM_PHASE_CASE(phase_kernel, 2) }
             else { LPMM_PHASE_CASE(phase_kernel, 3) }
         }
 #undef LPMM_PHASE_CASE
+        LPMM_HIP(hipGetLastError());
+        if (roles == 2 && pl.grid_gen > 0) {
+            if (bf16) hipLaunchKernelGGL((phase_kernel<true, 4>), dim3(pl.grid_gen), dim3(kThreads), 0, on, pl.gen, h);
+            else hipLaunchKernelGGL((phase_kernel<false, 4>), dim3(pl.grid_gen), dim3(kThreads), 0, on, pl.gen, h);
+            LPMM_HIP(hipGetLastError());
+        }
+        return LPMM_OK;
     };
     bool two_pass = false;
     for (const PhaseLaunch& pl : host->phases) two_pass = two_pass || pl.ph.n_b > 0;
@@ -2085,8 +2127,7 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
                 if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), s2));
                 if (pl.has_nd) LPMM_CHECK(launch_nd(pl, s2));
                 if (pl.has_det) LPMM_CHECK(launch_det(pl, s2));
-                launch(2, pl.grid_b, s2, pl);
-                LPMM_HIP(hipGetLastError());
+                LPMM_CHECK(launch(2, pl.grid_b, s2, pl));
                 if (rec) {
                     LPMM_HIP(hipEventRecord(prof_event(call, 1), s2));
                     LPMM_HIP(hipEventRecord(prof_event(call, 2), s2));
@@ -2098,8 +2139,7 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
                 const bool rec = !two_pass && g_prof.on && g_prof.calls < g_prof.max_calls;
                 const int64_t call = g_prof.calls;
                 if (rec) LPMM_HIP(hipEventRecord(prof_event(call, 0), sa));
-                launch(pl.a_has_rank1 ? 1 : 3, pl.grid_a, sa, pl);
-                LPMM_HIP(hipGetLastError());
+                LPMM_CHECK(launch(pl.a_has_rank1 ? 1 : 3, pl.grid_a, sa, pl));
                 if (rec) {
                     LPMM_HIP(hipEventRecord(prof_event(call, 1), sa));
                     LPMM_HIP(hipEventRecord(prof_event(call, 2), sa));
@@ -2129,8 +2169,7 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         if (pl.has_nd) LPMM_CHECK(launch_nd(pl, s));      // the A work of these tensors ran in the previous launch
         if (pl.has_det) LPMM_CHECK(launch_det(pl, s));
         const int roles = pl.ph.n_b == 0 ? (pl.a_has_rank1 ? 1 : 3) : (pl.ph.n_a == 0 ? 2 : 0);
-        launch(roles, pl.grid, s, pl);
-        LPMM_HIP(hipGetLastError());
+        LPMM_CHECK(launch(roles, pl.grid, s, pl));
         if (rec) {
             LPMM_HIP(hipEventRecord(prof_event(call, 1), s));
             LPMM_HIP(hipEventRecord(prof_event(call, 2), s));
@@ -2215,7 +2254,7 @@ int lpmm_adamw4_plan_launches(const void* plan) {
     if (host.flow) return 1;
     int n = 0;
     for (const PhaseLaunch& pl : host.phases) {
-        const int between = (pl.has_nd ? 2 : 0) + (pl.has_det ? 2 : 0);
+        const int between = (pl.has_nd ? 2 : 0) + (pl.has_det ? 2 : 0) + (pl.grid_gen > 0 ? 1 : 0);
         if (host.sgdm) n += pl.ph.n_a > 0;
         else if (host.side || host.serial) n += (pl.ph.n_a > 0) + (pl.ph.n_b > 0) + between;
         else n += 1 + between;

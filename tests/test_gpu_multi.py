@@ -93,6 +93,20 @@ def test_multi_matches_oracle_bf16_grads():
     _run_set(_mini_transformer(), "col_lognormal", True, steps=4, seed=12, env={"LPMM_PHASE_MPARAMS": "1"})
 
 
+@pytest.mark.parametrize("env", [{}, {"LPMM_MULTI_STREAMS": "0"}, {"LPMM_MULTI_STREAMS": "1"}], ids=["default", "serial", "fused"])
+@pytest.mark.parametrize("shapes,launches", [([(3000, 96)] * 4 + [(256, 1024)] * 4, 2), ([(30000, 96)] * 3 + [(512, 640)], 3),
+                                             ([(700, 96), (33, 100)], 2)], ids=["dealt", "apart", "alone"])
+def test_narrow_tensors_by_phases(monkeypatch, env, shapes, launches):
+    """Rows shorter than 128 elements ahead of others, whose second pass is then dealt to the XCDs in runs; two thirds of the
+    parameters and more than 2^23 of them, whose second pass is a launch of its own; and alone."""
+    counted, release = [], lpmm.lpmm_adamw4_plan_release
+    monkeypatch.setattr(lpmm, "lpmm_adamw4_plan_release",
+                        lambda plan: (counted.append(lpmm.lpmm_adamw4_plan_launches(plan)), release(plan)))
+    T = workloads.TensorSpec
+    _run_set([T(f"t{i}", r, c) for i, (r, c) in enumerate(shapes)], "col_lognormal", False, steps=2, seed=14, env=env)
+    assert counted == [2 if env.get("LPMM_MULTI_STREAMS") == "1" else launches]
+
+
 def test_multi_single_tensor_plan():
     _run_set([workloads.TensorSpec("w", 512, 512)], "iid", False, steps=3, seed=13)
 

@@ -760,6 +760,7 @@ __device__ __forceinline__ void finish_rank1(const Tensor4& a, unsigned int me, 
 // What a tile of a second pass is told and tells.  ready(): called once by every thread, after everything that does not
 // depend on the first pass has been requested; false leaves the tile undone.  staged(): called once by every thread, behind a
 // barrier, when the workgroup has read all it needs of the old and the new statistics.
+// nothing of both
 struct NoSync {
     __device__ __forceinline__ bool ready() { return true; }
     __device__ __forceinline__ void staged() {}

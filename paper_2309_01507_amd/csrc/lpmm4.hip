@@ -852,8 +852,10 @@ constexpr int64_t kFlowMinParams = int64_t(1) << 25;
 // time, and a little more, so that a second pass finds its first one complete.  In one piece, 12, 16, 20 and 24 million:
 // GPT-2-medium set 793, 790, 794 and 796 us, BERT-base 324, 303, 307 and 303, 8 llama layers 4.31, 4.24, 4.24 and 4.25 ms.
 // Spread, 12, 16, 20 and 24: factorized GPT-2-medium 790, 711, 717 and 717, factorized BERT-base 313, 284, 276 and 275, 8
-// factorized llama layers 3.94, 3.82, 3.82 and 3.84 ms, rank-1 with rows of 1472 1344, 1297, 1272 and 1273.
-constexpr double kFlowLead = 16.0 * (1 << 20), kFlowLeadSpread = 20.0 * (1 << 20);
+// factorized llama layers 3.94, 3.82, 3.82 and 3.84 ms, rank-1 with rows of 1472 1344, 1297, 1272 and 1273.  Factorized plans with
+// rows shorter than 128 elements, 10, 14 and 20 million: adapters 64 x 4096 and 4096 x 64 181, 183 and 188 us, 30000 x 96 beside 1024
+// x 4096 389, 369 and 380.
+constexpr double kFlowLead = 16.0 * (1 << 20), kFlowLeadSpread = 20.0 * (1 << 20), kFlowLeadNarrow = 14.0 * (1 << 20);
 // Unused dynamic LDS of the one launch: four workgroups on a CU instead of five (rank-1, plain rows: GPT-2-medium 799 us without,
 // 790 with), five instead of six (factorized: 747 us at six, 711 at five, 730 at four).  More of them only move the point up to
 // which the list has been handed out further ahead of the first passes that the second ones wait for.
@@ -1096,11 +1098,12 @@ void build_flow(const lpmm_tensor_desc* descs, int64_t n, const PlanLayout& L, c
     std::vector<size_t> updates(order.size());              // the tensors in the order of their second passes
     std::iota(updates.begin(), updates.end(), size_t(0));
     if (late) std::stable_partition(updates.begin(), updates.end(), [&](size_t k) { return !is_nd(k); });
+    const bool narrow_factor = std::any_of(flow.begin(), flow.end(), [](const Tensor4& t) { return t.kind == kFactorGeneral; });
     double begin = 0.0;
     for (const size_t k : updates) {
         const Tensor4& t = flow[order[k]];
         const double length = double(t.P), n1 = double(passes[k].first.size()), n2 = double(passes[k].second.size());
-        const double spread = t.kind == kQuantFast ? 0.0 : length, lead = spread > 0.0 ? kFlowLeadSpread : kFlowLead;
+        const double spread = t.kind == kQuantFast ? 0.0 : length, lead = spread == 0.0 ? kFlowLead : narrow_factor ? kFlowLeadNarrow : kFlowLeadSpread;
         for (const Row& r : passes[k].first) {
             const double at = begin - lead - spread * (1.0 - double(&r - passes[k].first.data()) / n1);
             first.push_back(Timed{late && is_nd(k) ? std::numeric_limits<double>::lowest() : at, r});    // ahead of everything
@@ -1887,7 +1890,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     for (size_t j = 0; j <= groups.size() && !host->flow; ++j) {
         PhaseLaunch pl{};
         int64_t elems_a = 0, elems_b = 0, elems_gen = 0;
-        int64_t general_b = 0;              // of elems_b, those on the rank-1 form's general tiles
+        int64_t narrow_a = 0, narrow_b = 0;     // of elems_a and elems_b, those on the general tiles of either form
+        auto narrow_kind = [](int kind) { return kind == kQuantGeneral || kind == kFactorGeneral; };
         pl.ph.tensors = reinterpret_cast<const Tensor4Table*>(d_tens);
         if (j < groups.size())
             for (int64_t i = groups[j].first; i < groups[j].second; ++i) {
@@ -1895,6 +1899,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
                 if (is_rank1(tens[i].kind)) pl.a_has_rank1 = true;
                 pl.ph.n_a += tens[i].n_wg;
                 elems_a += tens[i].P;
+                narrow_a += narrow_kind(tens[i].kind) ? tens[i].P : 0;
             }
         // The second pass of the general tiles gathers, and what it needs is many waves: 62 registers and no LDS, where the others'
         // update takes 85 and 24 KB.  Beside others it gets a launch of its own where that saves more than the launch and its tail
@@ -1919,7 +1924,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
                 to.seg_b[to.n_seg_b++] = Segment{to.n_b, int(i)};
                 to.n_b += tens[i].n_wg2;
                 (apart ? elems_gen : elems_b) += tens[i].P;
-                if (!apart && tens[i].kind == kQuantGeneral) general_b += tens[i].P;
+                narrow_b += !apart && narrow_kind(tens[i].kind) ? tens[i].P : 0;
                 if (tens[i].det) {
                     pl.has_det = true;
                     pl.det.seg_r[pl.det.n_seg++] = Segment{pl.det.n_r, int(i)};
@@ -1944,7 +1949,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         // and 4096 x 64 in turn, 268 M parameters, even as they are: 1251 and 1251, in runs 1287 and 1280).  First passes keep the
         // eighths: in runs all XCDs raise the same tensor's column maxima at a time (157 and 146 in place of 138 and 116).
         bool dealt = false;
-        if (general_b > 0) {
+        if (narrow_b > 0 && !host->factor) {
             double part[kXcds] = {};
             const double eighth = double(std::max(pad8(pl.ph.n_b), kXcds)) / kXcds;
             for (int k = 0; k < pl.ph.n_seg_b; ++k) {
@@ -1955,15 +1960,17 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             }
             dealt = *std::max_element(part, part + kXcds) > 1.25 * double(elems_b) / kXcds;
         }
-        auto skew = [](int n, int64_t elems) { return elems < int64_t(1) << 23 ? 0 : skew_of(n, elems); };       // as in set_skew
-        pl.ph.skew_a = skew(pl.ph.n_a, elems_a);
-        pl.ph.skew_b = dealt ? kDealt : skew(pl.ph.n_b, elems_b);
+        // No skew below 2^23 elements, as in set_skew, nor where the general tiles are most of a launch (30000 x 96 as 0.85 of the
+        // parameters, factorized, fp32 gradients, 625 us with it, 611 without; as 0.4, rank-1, 138 and 143).
+        auto skew = [](int n, int64_t elems, int64_t narrow) { return narrow > elems / 4 * 3 || elems < int64_t(1) << 23 ? 0 : skew_of(n, elems); };
+        pl.ph.skew_a = skew(pl.ph.n_a, elems_a, narrow_a);
+        pl.ph.skew_b = dealt ? kDealt : skew(pl.ph.n_b, elems_b, narrow_b);
         if (int64_t(pl.ph.n_a) + pl.ph.n_b > (int64_t(1) << 30)) return LPMM_EINVAL;
         pl.grid_a = pad8(pl.ph.n_a);
         pl.grid_b = dealt ? int(round_up(pl.ph.n_b, kXcds * kDealRun)) : pad8(pl.ph.n_b);
         pl.grid = pl.ph.n_a == 0 ? pl.grid_b : pad8(int64_t(pl.ph.n_a) + pl.ph.n_b);
         pl.gen.tensors = pl.ph.tensors;
-        pl.gen.skew_b = skew(pl.gen.n_b, elems_gen);
+        pl.gen.skew_b = skew(pl.gen.n_b, elems_gen, elems_gen);
         pl.grid_gen = pad8(pl.gen.n_b);
         host->phases.push_back(pl);
     }

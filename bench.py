@@ -24,6 +24,14 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E peak
+def same_kernel(recorded: str, reported: str) -> bool:
+    """Whether a profile's kernel, "phase_kernel<true, 2>", is the reported one, "phase_kernel<roles=2> (update pass)": the same
+    name and, where the report names one, the same role."""
+    role = reported.partition("<roles=")[2].partition(">")[0]
+    name = reported.partition("<")[0].split()[0]
+    return recorded.partition("<")[0] == name and (not role or recorded.rstrip(">").split(",")[-1].strip() == role)
+
+
 # Algorithmic bytes per quantized parameter (every stream touched once per kernel):
 #   update pass: param read+write 8, grad 4 or 2, both moments' codes read+write 2, block scales read+write 8/128
 #   maxima pass: grad 4 or 2, v codes read 0.5
@@ -298,9 +306,10 @@ def main():
     if not one_pass and not plans:
         p1_ms, p2_ms = p2_ms, p1_ms          # per tensor the statistics pass is recorded first; the update pass dominates
     if plans:
-        # the recorded launches are the update passes; the launches of a plan run one after the other on the caller's stream,
-        # and the fp32-state tensors ride with the maxima / statistics passes (one_launch: the recorded launch is the whole
-        # step; one_pass: the only kernels there are)
+        # the recorded launches are the update passes, and the fp32-state tensors ride with the maxima / statistics passes
+        # (one_launch: the recorded launch is the whole step; one_pass: the only kernels there are).  The launches of a plan run one
+        # after the other; where a rank-1 plan has several groups, updates run beside the next group's maxima pass.
+        beside = not one_pass and not one_launch and not factor and n_calls > args.steps
         bytes_per_launch = ((bp1 + bp2) * n_quant + small_bytes if one_launch else
                             (bp1 * n_quant + (small_bytes if one_pass else 0.0)) * args.steps / launches)
         avg_ms = p1_ms / launches
@@ -319,6 +328,8 @@ def main():
             "note": ("one pass: this kernel is the whole step" if one_pass else
                      "one launch: this kernel is the whole step, the maxima / statistics pass (%.1f B/param) of a tensor ahead of "
                      "its update; what the second reading gets from the memory-side cache is counted" % bp2 if one_launch else
+                     "the maxima pass (%.1f B/param) of the next tensor group runs beside it on another stream and shares the "
+                     "bandwidth; whole-step figures are in config" % bp2 if beside else
                      "the maxima / statistics pass (%.1f B/param) is a launch of its own before it on the same stream; "
                      "whole-step figures are in config" % bp2),
         }
@@ -327,7 +338,7 @@ def main():
             "flow" if one_launch else "phase", args.config, "_sgdm" if sgdm else "_b128" if b128 else "_factor" if factor else ""))
         if os.path.exists(tpath) and args.grad_dtype == "config":           # measured with the configuration's gradient type
             tr = json.load(open(tpath))
-            if tr.get("launches_per_step") == n_calls // max(args.steps, 1):
+            if tr.get("launches_per_step") == n_calls // max(args.steps, 1) and same_kernel(tr.get("kernel", ""), roofline["kernel"]):
                 roofline["traffic"] = tr["hbm_bytes_per_launch"]
                 roofline["traffic_source"] = "profiles/" + os.path.basename(tpath)
     else:
@@ -433,8 +444,8 @@ def main():
                    "grad_recipe": recipe,
                    "launch": (("multi-tensor plan, %d launches per step" if one_pass else
                                "multi-tensor plan, %d launch per step with both passes in it" if one_launch else
-                               "multi-tensor plan, %d update launches per step, each behind its statistics launch "
-                               "on the caller's stream") % (n_calls // max(args.steps, 1)))
+                               "multi-tensor plan, %d update launches per step, each behind its maxima / statistics launch")
+                              % (n_calls // max(args.steps, 1)))
                    if has_plans else "per-tensor, %d kernel%s per quantized tensor" % ((1, "") if one_pass else (2, "s")),
                    "kernels_per_step": kernels_per_step,
                    "hbm_gbps_one_touch_floor": round(floor_gbps, 1),

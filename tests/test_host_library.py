@@ -313,3 +313,28 @@ def test_plan_memory_sized_without_a_work_list_is_accepted(monkeypatch):
     p = (ctypes.addressof(plan) + 255) // 256 * 256
     build = lambda nbytes: lpmm.lib().lpmm_adamw4_plan_build(ctypes.addressof(arr), len(descs), 0, p, nbytes, None)
     assert build(phases) in (-2, -3) and build(phases - 1) == -1
+
+
+def test_bench_reports_the_traffic_of_the_kernel_it_timed():
+    """The profiles' byte counts belong to one kernel each; bench.py takes none that was recorded for another."""
+    import glob
+    import importlib.util
+    import json
+    import os
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(root, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    reported = {"flow_kernel_c5_llama_7b": "flow_kernel (both passes)", "flow_kernel_c5_llama_7b_factor": "flow_kernel (both passes)",
+                "phase_kernel_c5_llama_7b_b128": "phase_kernel<roles=3> (the whole block-wise step)",
+                "phase_kernel_c5_llama_7b_factor": "factor_phase_kernel<roles=2> (update pass)",
+                "phase_kernel_c5_llama_7b_sgdm": "sgdm_phase_kernel (the whole step)"}
+    files = glob.glob(os.path.join(root, "profiles", "traffic_*.json"))
+    assert {os.path.basename(f)[len("traffic_"):-len(".json")] for f in files} == set(reported)
+    for f in files:
+        kernel = json.load(open(f))["kernel"]
+        matches = {k for k, v in reported.items() if bench.same_kernel(kernel, v)}
+        name = os.path.basename(f)[len("traffic_"):-len(".json")]
+        assert name in matches and all(reported[k] == reported[name] for k in matches)
+    for old in ("phase_kernel<true, 1>", "phase_kernel<true, 3>", "factor_phase_kernel<true, 2>"):
+        assert not bench.same_kernel(old, "phase_kernel<roles=2> (update pass)")

@@ -136,11 +136,11 @@ def test_statistics_beyond_one_workgroup_keep_the_phases(monkeypatch):
             np.testing.assert_array_equal(x, y)
 
 
-@pytest.mark.parametrize("rows,n_first", [(40, "fewer than"), (512, "as many as"), (528, "one more than"), (9000, "many more than")])
+@pytest.mark.parametrize("rows,n_first", [(40, "fewer than"), (1024, "as many as"), (1056, "one more than"), (9000, "many more than")])
 def test_counts_of_finished_workgroups(monkeypatch, rows, n_first):
     """First passes of fewer workgroups than the counters of the first level (32), as many, one more and many more, with
     the tiles of the second pass waiting: the last one in is the one that lets the second pass go on, step after step.
-    (16 rows to a tile of the first pass in a set this small.)"""
+    (32 rows to a tile of the first pass in a set this small, one strip.)"""
     tensors = [("rank1", (rows, 128)), ("rank1", (64, 256))]
     want = _steps(monkeypatch, PHASES, tensors, True, steps=4)
     got = _steps(monkeypatch, ONE, tensors, True, steps=4)

@@ -194,8 +194,7 @@ def _check_invariants(sp, st, tag):
 def test_config5_llama_7b_plan_sampled_tensors_and_invariants():
     config, seed, steps = "c5_llama_7b", 24, 2
     specs = workloads.param_set(config)
-    # every distinct layer shape, and both 32000 x 4096 matrices (the largest tensors; with bf16 gradients and
-    # several groups in the plan they take the flat tiling of pass 1)
+    # every distinct layer shape, and both 32000 x 4096 matrices (the largest tensors)
     sampled = {"l0.q": None, "l0.gate": None, "l0.down": None, "embed": None, "lm_head": None}
     lpmm.ensure_init(4096)
     gen = torch.Generator(device=DEV)

@@ -24,7 +24,7 @@ def _announce(request):
 
 def _run_set(specs, recipe, bf16, steps, seed, env=None):
     """specs: list of workloads.TensorSpec.  Runs `steps` multi-tensor steps and the oracle side by side."""
-    for k in ("LPMM_PHASE_MPARAMS", "LPMM_MULTI_RW", "LPMM_FLAT"):
+    for k in ("LPMM_PHASE_MPARAMS", "LPMM_MULTI_RW", "LPMM_MULTI_RW2", "LPMM_MULTI_STREAMS", "LPMM_GX", "LPMM_RS"):
         os.environ.pop(k, None)
     os.environ.update(env or {})
     try:
@@ -78,14 +78,16 @@ def _mini_transformer():
 
 
 @pytest.mark.parametrize("env", [{}, {"LPMM_PHASE_MPARAMS": "1"}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_RW": "8"},
-                                 {"LPMM_PHASE_MPARAMS": "1", "LPMM_FLAT": "1"}, {"LPMM_FLAT": "1", "LPMM_MULTI_RW": "24"},
+                                 {"LPMM_PHASE_MPARAMS": "1", "LPMM_GX": "3", "LPMM_RS": "2"}, {"LPMM_MULTI_RW": "24", "LPMM_MULTI_RW2": "40"},
+                                 {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "2"},
                                  {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "1"},
                                  {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "0"},
                                  {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "3"}])
 def test_multi_matches_oracle_fp32_grads(env):
     """Default grouping (everything in one group), and tiny groups so that many phases overlap
-    pass 1 of one group with pass 2 of the previous one; the last three: both passes of a phase in one launch,
-    every pass a launch of its own on the caller's stream, and pass 1 alternating between two streams."""
+    the first pass of one group with the second of the previous one; other tiles; the last four: second passes on a second stream,
+    both passes of a phase in one launch, every pass a launch of its own on the caller's stream, and first passes alternating
+    between two streams."""
     _run_set(_mini_transformer(), "col_lognormal", False, steps=4, seed=11, env=env)
 
 

@@ -175,7 +175,7 @@ def test_other_hyperparameters(hp):
     assert run_parity(128, 256, steps=5, recipe="col_lognormal", seed=6, hp=hp) == 0
 
 
-ALL_KNOBS = ("LPMM_GX", "LPMM_RW", "LPMM_RW2", "LPMM_RS", "LPMM_RS2", "LPMM_FORCE_GENERAL", "LPMM_FLAT", "LPMM_GEN_CHUNKS")
+ALL_KNOBS = ("LPMM_GX", "LPMM_RW", "LPMM_RW2", "LPMM_RS", "LPMM_RS2", "LPMM_FORCE_GENERAL", "LPMM_GEN_CHUNKS")
 
 
 def test_launch_geometry_does_not_change_results():
@@ -189,7 +189,7 @@ def test_launch_geometry_does_not_change_results():
     knobs = [{}, {"LPMM_GX": "1"}, {"LPMM_GX": "8", "LPMM_RW": "16"}, {"LPMM_GX": "2", "LPMM_RW": "300"},
              {"LPMM_RS": "0", "LPMM_RS2": "0"}, {"LPMM_RW": "64", "LPMM_RS": "3", "LPMM_RW2": "32", "LPMM_RS2": "3"},
              {"LPMM_RW": "40", "LPMM_RS": "2", "LPMM_RW2": "24", "LPMM_RS2": "1"},
-             {"LPMM_FLAT": "1"}, {"LPMM_FLAT": "1", "LPMM_RW": "16", "LPMM_RS": "1"}, {"LPMM_FLAT": "1", "LPMM_RW": "300"},
+             {"LPMM_GX": "5"}, {"LPMM_RW": "16", "LPMM_RS": "1"}, {"LPMM_GX": "8", "LPMM_RW": "64", "LPMM_RS": "6"},
              {"LPMM_FORCE_GENERAL": "1"}, {"LPMM_FORCE_GENERAL": "1", "LPMM_GEN_CHUNKS": "1"},
              {"LPMM_FORCE_GENERAL": "1", "LPMM_GEN_CHUNKS": "16"}]
     try:
@@ -218,11 +218,10 @@ def test_launch_geometry_does_not_change_results():
 
 @pytest.mark.parametrize("env", [{"LPMM_RW2": "256"}, {"LPMM_RW2": "512", "LPMM_RS2": "0"}, {"LPMM_RW2": "200", "LPMM_RS2": "2"},
                                  {"LPMM_RW2": "256", "LPMM_RS2": "3"}])
-def test_pass2_tall_tiles_and_a_half_empty_last_strip(env):
-    """A wave of pass 2 keeps the scalars of its rows one per lane, up to 64 rows (tiles of 256 rows; taller ones are
-    cut down to that).  With an odd number of column blocks the upper half of the last strip's lanes has no columns
-    but still holds rows 32 to 63: tall tiles on such shapes, against the oracle, with outlier rows (so that rows
-    differ), bf16 and fp32 gradients."""
+def test_tall_first_pass_tiles_and_a_half_empty_last_strip(env):
+    """The first pass takes up to 512 rows to a tile, whose old maxima it stages; with an odd number of column blocks the upper
+    half of the last strip's lanes repeats the lower half's columns: tall tiles on such shapes, against the oracle, with
+    outlier rows (so that rows differ), bf16 and fp32 gradients."""
     for k in ALL_KNOBS:
         os.environ.pop(k, None)
     os.environ.update(env)

@@ -71,8 +71,8 @@ def test_nd_random_shapes():
         assert tn.run(shape, steps=2, seed=500 + k) == 0
 
 
-@pytest.mark.parametrize("env", [{}, {"LPMM_PHASE_MPARAMS": "1"}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_FLAT": "1"}],
-                         ids=["one-group", "many-groups", "many-groups-flat"])
+@pytest.mark.parametrize("env", [{}, {"LPMM_PHASE_MPARAMS": "1"}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_GX": "2", "LPMM_RS": "2"}],
+                         ids=["one-group", "many-groups", "many-groups-other-tiles"])
 def test_random_plans(env):
     from test_gpu_multi import _run_set
     T = workloads.TensorSpec

@@ -172,15 +172,15 @@ def test_bad_arguments_are_rejected():
         lpmm.lpmm_adamw4_nd_step(w, g, huge, 1e-3, 0.9, 0.999, 1e-8, 0.0, 1)
 
 
-@pytest.mark.parametrize("env", [{}, {"LPMM_PHASE_MPARAMS": "1"}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "1"},
-                                 {"LPMM_PHASE_MPARAMS": "1", "LPMM_FLAT": "1"}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "0"}],
-                         ids=["one-group", "two-streams", "fused-launches", "flat", "serial-launches"])
+@pytest.mark.parametrize("env", [{}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "2"},
+                                 {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "1"}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_RW2": "16"}, {"LPMM_PHASE_MPARAMS": "1", "LPMM_MULTI_STREAMS": "0"}],
+                         ids=["one-group", "two-streams", "fused-launches", "short-tiles", "serial-launches"])
 def test_plan_with_n_dimensional_tensors(env):
     """Convolution-shaped tensors, matrices and small fp32-state tensors in one plan."""
     seed = 64
     items = [("conv1", (64, 32, 3, 3)), ("fc", (256, 384)), ("bias", (384,)), ("conv2", (96, 16, 4, 4)),
              ("odd", (40, 5, 7)), ("cube", (128, 8, 16)), ("fc2", (300, 256))]
-    for k in ("LPMM_PHASE_MPARAMS", "LPMM_MULTI_STREAMS", "LPMM_FLAT"):
+    for k in ("LPMM_PHASE_MPARAMS", "LPMM_MULTI_STREAMS", "LPMM_MULTI_RW2"):
         os.environ.pop(k, None)
     os.environ.update(env)
     try:

@@ -349,6 +349,9 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
  * layer" -- here all layers are enqueued by one call).  A plan is built once for a list of tensors;
  * lpmm_adamw4_step_multi then enqueues a short sequence of launches on `stream`: per group of
  * tensors the first pass (which only reads: the new statistics of the second moment), then the update.
+ * Rank-1 plans of several groups (more than some 190 tensors, or 2^31 parameters, that do not take one launch, see below) run
+ * updates beside the next group's first pass on a second stream that the plan owns (same priority; `stream` waits for it before
+ * the call's work counts as complete, so the usual stream ordering holds for the caller).
  * Rank-1 and factorized plans for which it is the faster way
  * enqueue ONE launch there, in which the update of a tensor follows its first pass: sets of 2^25 parameters or more, unless most
  * of them are in one tensor (rank-1: more than 3/4, factorized: 1/4), in two to eight equal ones, or half of them in rows shorter

@@ -144,7 +144,8 @@ constexpr int kElemsPerWg32 = kThreads * 16;   // fp32-state path: elements per 
 // with each other, and eight streams at equal distances that are a multiple of a large power of two get in each other's way
 // in the memory system.  skew: the workgroups of 2^19 elements (2 MiB of parameters).  Block-wise step of 2^25, 2^26 and 2^27
 // elements 5.72, 6.05 and 6.58 TB/s with skew 0, 6.15, 6.62, 6.80 with half of it, 6.43, 6.80, 6.92 with it, 6.45, 6.80, 6.94
-// with the double; sizes whose eighths lie at other distances are the same with and without (45 M elements 6.45 / 6.49).
+// with the double; sizes whose eighths lie at other distances are the same with and without (45 M elements 6.45 / 6.49) or, where
+// the skew itself brings them to such a distance, slower with it (the host's launch_skew).
 constexpr int64_t kSkewElems = int64_t(1) << 19;
 // skew < per_xcd (the host sees to it), so i + x * skew < 8 per_xcd and three conditional subtractions are the remainder: a
 // division here, in front of everything else a workgroup does, cost every kernel 0.3 us (statistics pass of 512 x 512 5.80 us

@@ -130,11 +130,18 @@ int skew_of(int64_t n, int64_t elems) {
     const int64_t skew = int64_t(double(n) * double(kSkewElems) / double(std::max<int64_t>(elems, 1)) + 0.5);
     return int(std::max<int64_t>(1, skew) % std::max<int64_t>(1, round_up(n, kXcds) / kXcds));
 }
-// a launch for one tensor: none below 2^23 elements, whose eighths two or fewer such distances fill
+// The skew of a launch on its own: none below 2^23 elements, whose eighths two or fewer such distances fill, and none where it
+// would bring the eighths' distance (of their parameters) closer to a multiple of 8 MiB instead of farther from one (SGDM with
+// bf16 gradients, us with and without: 2^25 elements, 16 MiB apart, 58.2 and 65.3; 2^24, 8 MiB, 29.1 and 30.0; 30000001, 14.3 MiB,
+// 58.8 and 54.0; 60000001, 28.6 MiB, 103.9 and 101.4; factorized 30000 x 1000 103.5 and 93.9).
+int launch_skew(int64_t n, int64_t elems) {
+    const double mib = 1024.0 * 1024.0, distance = double(elems) * 4.0 / kXcds;
+    auto off = [&](double d) { const double r = std::fmod(d, 8.0 * mib); return std::min(r, 8.0 * mib - r); };
+    return elems >= int64_t(1) << 23 && off(distance + double(kSkewElems) * 4.0) > off(distance) ? skew_of(n, elems) : 0;
+}
 void set_skew(Tensor4* t) {
-    const bool some = t->P >= int64_t(1) << 23;
-    t->skew = some ? skew_of(t->n_wg, t->P) : 0;
-    t->skew2 = some ? skew_of(t->n_wg2, t->P) : 0;
+    t->skew = launch_skew(t->n_wg, t->P);
+    t->skew2 = launch_skew(t->n_wg2, t->P);
 }
 
 // Geometry of the factorized form's fast path (its update tiles in the members of the first pass; the caller swaps them).  gx
@@ -1960,9 +1967,9 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
             }
             dealt = *std::max_element(part, part + kXcds) > 1.25 * double(elems_b) / kXcds;
         }
-        // No skew below 2^23 elements, as in set_skew, nor where the general tiles are most of a launch (30000 x 96 as 0.85 of the
-        // parameters, factorized, fp32 gradients, 625 us with it, 611 without; as 0.4, rank-1, 138 and 143).
-        auto skew = [](int n, int64_t elems, int64_t narrow) { return narrow > elems / 4 * 3 || elems < int64_t(1) << 23 ? 0 : skew_of(n, elems); };
+        // No skew where the general tiles are most of a launch (30000 x 96 as 0.85 of the parameters, factorized, fp32 gradients, 625 us
+        // with it, 611 without; as 0.4, rank-1, 138 and 143).
+        auto skew = [](int n, int64_t elems, int64_t narrow) { return narrow > elems / 4 * 3 ? 0 : launch_skew(n, elems); };
         pl.ph.skew_a = skew(pl.ph.n_a, elems_a, narrow_a);
         pl.ph.skew_b = dealt ? kDealt : skew(pl.ph.n_b, elems_b, narrow_b);
         if (int64_t(pl.ph.n_a) + pl.ph.n_b > (int64_t(1) << 30)) return LPMM_EINVAL;

@@ -214,7 +214,11 @@ __global__ __launch_bounds__(kThreads, FORM == kFlowRank1 ? 5 : FORM == kFlowRan
             bool done = true;
             unsigned int ticket = 0u;
             __device__ __forceinline__ bool ready() {
-                if (!mine || __syncthreads_and(int(f.spin_limit >= 0 && early == target))) return true;
+                if (!mine) return true;
+                if (threadIdx.x == 0) s_flag = f.spin_limit >= 0 && early == target;
+                __syncthreads();
+                if (__builtin_amdgcn_readfirstlane(s_flag) != 0) return true;
+                __syncthreads();                          // every wave has read the flag before it is written again
                 if (threadIdx.x == 0) {
                     int ok = 0;
                     for (int k = 0; k <= f.spin_limit; ++k) {

@@ -182,6 +182,7 @@ struct alignas(16) Lds {
     // that depends on the lane.
     float blk_scale[kMaxRowSlots];
     float blk_vmax[kMaxRowSlots];
+    uint32_t not_all[kThreads / 64];     // all_threads
 };
 struct LdsRank1 : Lds {         // second pass of the rank-1 step
     float cnew[kColSlots];      // the strip's new column maxima (s.col: 16 / them, approximately)
@@ -209,6 +210,18 @@ __device__ __forceinline__ void put_tables(Lds& s, const TableRegs& r) {       /
 __device__ __forceinline__ void load_tables(Lds& s) {
     put_tables(s, request_tables());
     __syncthreads();
+}
+
+// Whether `ok` holds in every thread, the same answer in all of them, and a barrier: what was put into LDS before is there.  (The
+// runtime's __syncthreads_or has three barriers and waits for a load of the workgroup's size: fp32 steps of 512 x 512 and 1024 x 1024
+// 9.5 and 11.4 us, 9.1 and 11.0 so.)
+// Between two calls there is another barrier.
+__device__ __forceinline__ bool all_threads(Lds& s, bool ok) {
+    static_assert(kThreads == 256, "one word per wave, four of them");
+    const bool bad = __ballot(!ok) != 0;
+    if ((threadIdx.x & 63) == 0) s.not_all[threadIdx.x >> 6] = bad;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(int((s.not_all[0] | s.not_all[1]) | (s.not_all[2] | s.not_all[3]))) == 0;
 }
 
 // ---- small helpers -----------------------------------------------------------------------------------
@@ -247,6 +260,9 @@ __device__ __forceinline__ Rsrc tile_rsrc(const void* base, uint32_t bytes) {
 __device__ __forceinline__ float4 buf_ld_f4_stream(Rsrc r, uint32_t off) {
     const v4f_t v = __builtin_bit_cast(v4f_t, __builtin_amdgcn_raw_buffer_load_b128(r, int(off), 0, kPolicyNt));
     return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float buf_ld_f1(Rsrc r, uint32_t off) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, int(off), 0, 0));
 }
 template <int POLICY = 0>
 __device__ __forceinline__ float4 buf_ld_f4(Rsrc r, uint32_t off) {
@@ -495,6 +511,29 @@ struct Row8 {
     uint32_t vq;
 };
 
+// a lane's 8 gradients, and float(code) of its 8 codes (see codes_to_float4)
+template <bool BF16>
+__device__ __forceinline__ void unpack_grad8(const float4 (&x)[BF16 ? 1 : 2], float g[8]) {
+    if constexpr (BF16) {
+        const float w[4] = {x[0].x, x[0].y, x[0].z, x[0].w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            g[2 * q] = bf16_lo(__float_as_uint(w[q]));
+            g[2 * q + 1] = bf16_hi(__float_as_uint(w[q]));
+        }
+    } else {
+        g[0] = x[0].x; g[1] = x[0].y; g[2] = x[0].z; g[3] = x[0].w;
+        g[4] = x[1].x; g[5] = x[1].y; g[6] = x[1].z; g[7] = x[1].w;
+    }
+}
+__device__ __forceinline__ void codes_to_float8(uint32_t w, float qf[8]) {
+    uint32_t lo = w & 0x0F0F0F0Fu, hi = (w >> 4) & 0x0F0F0F0Fu;
+    asm("" : "+v"(lo));
+    asm("" : "+v"(hi));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) qf[e] = float((e & 1 ? hi : lo) >> (8 * (e >> 1)) & 255u);
+}
+
 template <bool BF16>
 __device__ __forceinline__ void maxima_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
     static_assert(offsetof(Lds, cold) == offsetof(Lds, col) + sizeof(float) * kColSlots && 2 * kColSlots >= kGroups * 256,
@@ -526,8 +565,15 @@ __device__ __forceinline__ void maxima_tile(const Tensor4& a, const Hyper& h, in
     Row8<BF16> r[kDepth];
 #pragma unroll
     for (int u = 0; u < kDepth; ++u) r[u] = fetch(u);
-    float c16[8], cmax[8];
+    // old statistics, requested with the first rows: one round trip to the memory in front of the loop.  Zeros for rows behind the
+    // tile's end.
+    float c16[8], cmax[8], r_old[kMaxRowSlots / kThreads];
     load8(a.c + col0, c16);
+    const Rsrc rr = tile_rsrc(a.r + row0, uint32_t(n) * 4u);
+#pragma unroll
+    for (int u = 0; u < kMaxRowSlots / kThreads; ++u)
+        r_old[u] = u * kThreads < a.rw2 + kGroups ? buf_ld_f1(rr, (threadIdx.x + u * kThreads) * 4u) : 0.0f;
+    __builtin_amdgcn_sched_barrier(0);                    // the columns' wait does not move in front of the rows' request
     bool lane_tame = true;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -535,36 +581,23 @@ __device__ __forceinline__ void maxima_tile(const Tensor4& a, const Hyper& h, in
         c16[e] *= 0.0625f;
         cmax[e] = 0.0f;
     }
-    for (int t = threadIdx.x; t < kMaxRowSlots && t < a.rw2 + kGroups; t += kThreads) {     // zeros for rows behind the tile's end
-        const float x = t < n ? a.r[row0 + t] : 0.0f;
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(x)));
-        s.blk_scale[t] = x * 0.0625f;
+#pragma unroll
+    for (int u = 0; u < kMaxRowSlots / kThreads; ++u) {
+        if (u * kThreads >= a.rw2 + kGroups) break;
+        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r_old[u])));
+        s.blk_scale[threadIdx.x + u * kThreads] = r_old[u] * 0.0625f;
     }
-    const bool tame = !__syncthreads_or(int(!lane_tame));                     // else the exact route for the whole tile
+    const bool tame = all_threads(s, lane_tame);                     // else the exact route for the whole tile
     auto one = [&](const Row8<BF16>& x, int k) {
         const int il = row_g + walk.at(k);
         const float r16 = s.blk_scale[il];
         float g[8], vt[8];
-        if constexpr (BF16) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t w = __float_as_uint(q == 0 ? x.g[0].x : q == 1 ? x.g[0].y : q == 2 ? x.g[0].z : x.g[0].w);
-                g[2 * q] = bf16_lo(w);
-                g[2 * q + 1] = bf16_hi(w);
-            }
-        } else {
-            g[0] = x.g[0].x; g[1] = x.g[0].y; g[2] = x.g[0].z; g[3] = x.g[0].w;
-            g[4] = x.g[1].x; g[5] = x.g[1].y; g[6] = x.g[1].z; g[7] = x.g[1].w;
-        }
+        unpack_grad8<BF16>(x.g, g);
         if (__builtin_expect(tame, 1)) {
-            uint32_t lo = x.vq & 0x0F0F0F0Fu, hi = (x.vq >> 4) & 0x0F0F0F0Fu;
-            asm("" : "+v"(lo));
-            asm("" : "+v"(hi));
+            float qf[8];
+            codes_to_float8(x.vq, qf);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float q = float((e & 1 ? hi : lo) >> (8 * (e >> 1)) & 255u);
-                vt[e] = dequant_v16(q, min_nonneg(r16, c16[e]));
-            }
+            for (int e = 0; e < 8; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(r16, c16[e]));
         } else {
             const float r_old = il < n ? a.r[row0 + il] : 0.0f;
 #pragma unroll
@@ -941,7 +974,7 @@ __device__ __forceinline__ void update_tile(const Tensor4& a, const Hyper& h, in
     reinterpret_cast<float4*>(s.cnew)[t] = make_float4(tame_too(c_new.x), tame_too(c_new.y), tame_too(c_new.z), tame_too(c_new.w));
     reinterpret_cast<float4*>(s.col)[t] = make_float4(approx_inv16(c_new.x), approx_inv16(c_new.y), approx_inv16(c_new.z), approx_inv16(c_new.w));
     if (t < a.rw) stage_row_new(s, t, tame_too(r_new));
-    const bool tame = !__syncthreads_or(int(!lane_tame));     // an extreme scale anywhere: the exact route for the whole tile
+    const bool tame = all_threads(s, lane_tame);     // an extreme scale anywhere: the exact route for the whole tile
     // Everything requested so far has to be here before the first unit anyway.  Saying so with an explicit wait gives the
     // loop a start-up state with nothing outstanding; otherwise the start-up's own (tight) wait counts are merged into
     // the loop head and drain the prefetch in every round.
@@ -977,13 +1010,13 @@ __device__ __forceinline__ void update_tile(const Tensor4& a, const Hyper& h, in
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxRw2 = 64 * kWaves;      // rows of a statistics tile of the ragged and the factorized forms
 
-// Statistics tiles of ragged matrices (rows that are no multiple of 128 elements long) take groups of 4 consecutive elements,
-// aligned in the flattening; the last such group of a row may reach up to 3 elements into the next row.  Where that would
-// reach beyond the tensor (its size is no multiple of 4) the last row is left to workgroups of its own.
-__host__ __device__ __forceinline__ int64_t class_rows(const Tensor4& a) { return (a.P & 3) ? a.rows - 1 : a.rows; }
-// The last row of such a tensor, from the first multiple of 4 elements in it on, in parts of kLastRowElems elements.
+// Statistics tiles of ragged matrices (rows that are no multiple of 128 elements long) take groups of 8 consecutive elements,
+// aligned in the flattening; the last such group of a row may reach up to 7 elements into the next row.  Where that would
+// reach beyond the tensor (its size is no multiple of 8) the last row is left to workgroups of its own.
+__host__ __device__ __forceinline__ int64_t class_rows(const Tensor4& a) { return (a.P & 7) ? a.rows - 1 : a.rows; }
+// The last row of such a tensor, from the first multiple of 8 elements in it on, in parts of kLastRowElems elements.
 constexpr int kLastRowElems = kThreads * 8;
-__host__ __device__ __forceinline__ int64_t last_row_begin(const Tensor4& a) { return ((a.rows - 1) * a.cols + 3) / 4 * 4; }
+__host__ __device__ __forceinline__ int64_t last_row_begin(const Tensor4& a) { return ((a.rows - 1) * a.cols + 7) / 8 * 8; }
 
 // =====================================================================================================
 // Block-wise second moment (1-dimensional or flattened tensors; Sec. 4.2, last paragraph): both
@@ -1167,7 +1200,7 @@ __device__ __forceinline__ void b128_tile(const Tensor4& a, const Hyper& h, int 
     put_tables(s, tables);
     __syncthreads();                               // the first blocks' loads are in flight meanwhile
     bool tame = true;
-    if constexpr (!SGDM) tame = !__syncthreads_or(int(!lane_tame));
+    if constexpr (!SGDM) tame = all_threads(s, lane_tame);
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);       // loop start-up state: nothing outstanding (see update_tile)
     auto none = [] {};
     auto work = [&](const RowB<BF16>& cur, int kk, auto mid) { b128_row<BF16, SGDM>(h, tb, s, cur, off(kk), slot0 + kk, l, tame, mid); };
@@ -1495,13 +1528,17 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_fadd(float x) {
     return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
-// sum over the 64 lanes of a wave, the same value in every lane (fixed order)
-__device__ __forceinline__ float wave_sum(float v) {
+// sum over the 32 lanes of a half-wave, the same value in every lane (fixed order)
+__device__ __forceinline__ float group32_sum(float v) {
     v = dpp_fadd<0xB1>(v);      // lane ^ 1
     v = dpp_fadd<0x4E>(v);      // lane ^ 2
     v = dpp_fadd<0x141>(v);     // other quad of the half row
     v = dpp_fadd<0x140>(v);     // other half of the row of 16
-    v += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x401F));     // lane ^ 16
+    return v + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x401F));     // lane ^ 16
+}
+// the same over the 64 lanes of a wave
+__device__ __forceinline__ float wave_sum(float v) {
+    v = group32_sum(v);
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)) +
            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
 }

@@ -326,9 +326,11 @@ bool ragged_eligible(int64_t rows, int64_t cols) {
 // Update, cols <= 1024: tiles of 8 to 128 consecutive blocks.  Wider: strips of equal width, at most 1024 columns, by 32
 // rows; the rows are halved down to one per group and then the strips down to 256 columns.  Both shrink while the tensor
 // would give the chip fewer than two workgroups per CU (n_cu = 0: `shrink` halvings instead, for plans).
-// Statistics: 64 rows (plans: 128), halved down to 4 in the same way; a multiple of 4.  Every tile ends with an atomic per
-// column, and atomics on one address follow each other at about 18 ns, so a tall narrow matrix takes more rows to a tile
-// than the filling of the chip alone would ask for: rows / rw2 of them against a quarter of rw2 rows, about 0.3 us each, one
+// Statistics: 256 rows (plans: 128), halved down to 64 while there are fewer than 11/4 workgroups per CU (24178 x 808 bf16, 64 and 128
+// rows, 1512 and 756 tiles: 63.3 and 60.8 us per step; 50257 x 1088 bf16, 64, 128 and 256, the last 985 tiles: 161.9, 160.7, 158.6; but
+// 6025 x 6840 bf16, 64 and 256, 648 tiles: 123.3 and 125.9; 8678 x 776 bf16, 64 and 128, 272 tiles: 30.0 and 31.6), then down to 8 while
+// there are fewer than two; a multiple of 8.  Every tile ends with an atomic per column, and atomics on one address follow each other
+// at about 18 ns, so a tall narrow matrix takes more rows to a tile than the filling of the chip alone would ask for: rows / rw2 of them against a quarter of rw2 rows, about 0.3 us each, one
 // after the other in a wave balance at rw2 = sqrt(rows / 4) (factorized form of 2000 x 190 with fp32 gradients: 16.5 us per
 // step, 29.8 without this).
 void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
@@ -361,12 +363,14 @@ void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
     }
     a->strips2 = int((a->cols + 255) / 256);
     const int64_t rows2 = class_rows(*a);
-    int64_t rw2 = n_cu ? 64 : std::max<int64_t>(128 >> shrink, kWaves);
+    int64_t rw2 = n_cu ? kMaxRw2 : std::max<int64_t>(128 >> shrink, kGroups);
     // a tile reads its own rows and the one behind them, and kNowhere lies beyond all of them
     auto fits = [&](int64_t r) { return (r + 1) * a->cols * 4 <= int64_t(kNowhere); };
-    while (rw2 > kWaves && !fits(rw2)) rw2 /= 2;
-    while (n_cu && rw2 > kWaves && a->strips2 * ((rows2 + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 /= 2;
+    while (rw2 > kGroups && !fits(rw2)) rw2 /= 2;
+    while (n_cu && rw2 > kGroups && a->strips2 * ((rows2 + rw2 - 1) / rw2) < (rw2 > 64 ? 11 : 8) * int64_t(n_cu) / 4) rw2 /= 2;
     while (rw2 < 64 && rw2 * rw2 < a->rows / 4 && fits(2 * rw2)) rw2 *= 2;
+    if (const int forced = env_int("LPMM_RW2", 0); forced > 0) rw2 = std::clamp(forced / kGroups * kGroups, kGroups, kMaxRw2);
+    while (rw2 > kGroups && !fits(rw2)) rw2 -= kGroups;
     a->rw2 = int(rw2);
     a->rs2 = 0;
     a->n_wg = int(a->strips2 * ((rows2 + rw2 - 1) / rw2));

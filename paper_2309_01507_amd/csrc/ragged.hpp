@@ -21,6 +21,8 @@
 // The first pass needs none of this: nothing in it is reduced over a block, see maxima_ragged_tile.
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace lpmm {
@@ -141,136 +143,236 @@ __device__ __forceinline__ TileBase rag_base(const Tensor4& a, const RagTile& t)
     return b;
 }
 
-// First pass: row and column maxima of v_t.  A wave takes 256 consecutive columns of one row, a lane 4 elements aligned in
-// the flattening: the lanes of row i start at the first multiple of 4 at or behind i * cols, `shift` = -i * cols mod 4 columns
-// into the row, and that shift is the same for all rows a wave takes (they are a multiple of 4 apart), so that a lane's
-// columns are fixed down the tile.  Columns are counted on through the end of a row: positions cols, cols + 1, cols + 2 are
-// the next row's first ones, whose maxima the row's last lane collects for that row.
-constexpr int kSpan = 264;                                        // positions of a strip: 256, a shift and a lane's 4
-static_assert(4 * kSpan <= kColSlots && kMaxRw2 + 1 < kColSlots && kMaxRw2 < kMaxRowSlots, "statistics of a tile are staged in LDS");
+// Statistics tiles (the maxima of the rank-1 form, the sums of the factorized one): strips of 256 columns by rw2 rows, a multiple
+// of 8.  A half-wave of 32 lanes takes 256 consecutive columns of one row, a lane 8 elements aligned in the flattening (one
+// 16-byte load of a bf16 gradient, 4 bytes of codes): the lanes of row i start at the first multiple of 8 at or behind i * cols,
+// `shift` = -i * cols mod 8 columns into the row, and that shift is the same for all rows a half-wave takes (they are 8 apart), so
+// that a lane's columns are fixed down the tile.  Columns are counted on through the end of a row: positions cols .. cols + 6 are
+// the next row's first ones, whose statistics the row's last lane collects for that row.  Only a tile that has that lane (`edge`)
+// looks at which row an element belongs to.
+// Bound by the latency of memory: few and wide accesses, and one round trip in front of the loop.  With 4 elements a lane, a wave per
+// row and two dependent round trips at the start the maxima of 1024 x 50257 bf16 took 42 us (3.1 TB/s), 31 this way.
+constexpr int kSpan = 264;                                        // positions of a strip: 256, and a shift of at most 7
+static_assert(offsetof(Lds, cold) == offsetof(Lds, col) + sizeof(float) * kColSlots && kGroups * kSpan <= 2 * kColSlots,
+              "col and cold hold the half-waves' column statistics");
+static_assert(kMaxRw2 + kGroups + 1 < kMaxRowSlots && kMaxRw2 + kGroups + 1 < 512, "a tile's row statistics are staged in LDS");
 
 template <bool BF16>
-__device__ __forceinline__ void maxima_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
-    const int strip = wg % a.strips2, tile = wg / a.strips2;
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    const int64_t row0 = int64_t(tile) * a.rw2;                   // a multiple of 4
-    const int64_t left = class_rows(a) - row0;
-    const int n = left < a.rw2 ? int(left) : a.rw2;
-    const int n_stat = row0 + n < a.rows ? n + 1 : n;
-    const uint32_t cols = uint32_t(a.cols);
-    const uint32_t shift = (0u - uint32_t(wave) * cols) & 3u;
-    const uint32_t at = uint32_t(lane) * 4u + shift, col0 = uint32_t(strip) * 256u + at;
-    const bool live = col0 < cols;
-    const int64_t e0 = row0 * a.cols;
-    const uint32_t elems = uint32_t(n_stat) * cols;
-    const Rsrc rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + e0 * (BF16 ? 2 : 4), elems * (BF16 ? 2u : 4u));
-    const Rsrc rv = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (e0 >> 1), elems >> 1);
-    const int last = n - 1 - (n - 1 - wave) % kWaves;             // the wave's own last row, if it has any (wave < n)
-    struct Row { GradRegs4<BF16> g; uint16_t vq; };
-    auto ld = [&](int il) {
-        Row r;
-        const uint32_t e = uint32_t(il < last ? il : last) * cols + col0;
-        r.g = load_grad_regs4<BF16>(rg, live ? e * 4u : kNowhere);
-        r.vq = buf_ld_u16(rv, live ? e >> 1 : kNowhere);
-        return r;
-    };
-    // columns of the lane's elements, zeros for lanes without any: their moments are zero then
-    float c16[4], cmax[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    uint32_t col[4];
-    bool lane_tame = true, beyond[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        beyond[e] = col0 + e >= cols;
-        col[e] = live ? (beyond[e] ? col0 + e - cols : col0 + e) : 0u;
-        const float c = live ? a.c[col[e]] : 0.0f;
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(c)));
-        c16[e] = c * 0.0625f;
+struct RagStats {
+    static constexpr uint32_t kBytes = BF16 ? 2u : 4u;
+    static constexpr int kDepth = BF16 ? 3 : 2;                   // about the same bytes in flight
+    int strip, tile, grp, l, n, n_stat, rounds;
+    int64_t row0;
+    uint32_t cols, at, col0;      // the lane's first position in the strip and column
+    bool live, edge;
+    Rsrc rg, rv;
+    uint32_t off_g, off_v;        // byte offsets of the lane's elements in the half-wave's first row
+
+    __device__ __forceinline__ RagStats(const Tensor4& a, int wg) {
+        strip = wg % a.strips2, tile = wg / a.strips2;
+        grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+        row0 = int64_t(tile) * a.rw2;
+        const int64_t left = class_rows(a) - row0;
+        n = left < a.rw2 ? int(left) : a.rw2;
+        n_stat = row0 + n < a.rows ? n + 1 : n;
+        rounds = (n + kGroups - 1) / kGroups;
+        cols = uint32_t(a.cols);
+        at = uint32_t(l) * 8u + ((0u - uint32_t(grp) * cols) & 7u);
+        col0 = uint32_t(strip) * 256u + at;
+        live = col0 < cols;
+        edge = uint32_t(strip) * 256u + 262u >= cols;
+        const int64_t e0 = row0 * a.cols;
+        // what the tile's lanes own: up to where the lanes of the row behind its last one begin, so that those read zeros
+        const uint32_t elems = (uint32_t(n) * cols + 7u) / 8u * 8u;
+        rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + e0 * int(kBytes), elems * kBytes);
+        const uint32_t e = uint32_t(grp) * cols + col0;
+        off_g = live ? e * kBytes : kNowhere;
+        off_v = live ? e >> 1 : kNowhere;
+        if (a.vq) rv = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (e0 >> 1), elems >> 1);
     }
-    for (int t = threadIdx.x; t < 4 * kSpan; t += kThreads) s.col[t] = 0.0f;
-    for (int t = threadIdx.x; t <= n; t += kThreads) {
-        const float r = t < n_stat ? a.r[row0 + t] : 0.0f;
-        lane_tame = bool(int(lane_tame) & int(scale_is_tame(r)));
-        s.blk_scale[t] = r * 0.0625f;
-        s.blk_vmax[t] = 0.0f;
-        s.cold[t] = 0.0f;
+    __device__ __forceinline__ bool next_row(int e) const { return col0 + uint32_t(e) >= cols; }      // of element e, if edge
+    __device__ __forceinline__ void load_grad(int k, float4 (&g)[BF16 ? 1 : 2]) const {
+        const uint32_t off = off_g + uint32_t(k) * (cols * 8u * kBytes);
+        g[0] = buf_ld_f4(rg, off);
+        if constexpr (!BF16) g[1] = buf_ld_f4(rg, off + 16u);
     }
-    const bool tame = !__syncthreads_or(int(!lane_tame));         // else the exact route for the whole tile
-    auto one = [&](const Row& x, int il) {
-        float g[4], vt[4], own = 0.0f, next = 0.0f;
-        unpack_grad4<BF16>(x.g, g);
-        if (__builtin_expect(tame, 1)) {
-            float qf[4];
-            codes_to_float4(x.vq, qf);
-            const float ra = s.blk_scale[il], rb = s.blk_scale[il + 1];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(beyond[e] ? rb : ra, c16[e]));
-        } else {
-            const float ra = a.r[row0 + il], rb = il + 1 < n_stat ? a.r[row0 + il + 1] : 0.0f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) vt[e] = live ? dequant_v((uint32_t(x.vq) >> (4 * e)) & 15u, fminf(beyond[e] ? rb : ra, a.c[col[e]])) : 0.0f;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            vt[e] = fmaxf(moment_v(h, vt[e], g[e]), 0.0f);        // a NaN raises no maximum
-            cmax[e] = fmaxf(cmax[e], vt[e]);
-            own = fmaxf(own, beyond[e] ? 0.0f : vt[e]);
-            next = fmaxf(next, beyond[e] ? vt[e] : 0.0f);
-        }
-        own = group32_allmax(own);
-        own = fmaxf(own, __shfl_xor(own, 32));
-        if (lane == 0) s.blk_vmax[il] = own;
-        if (live && col0 + 3u >= cols) s.cold[il + 1] = next;     // one lane of the last strip
-    };
-    constexpr int kDepth = 3;
-    Row r[kDepth];
-    auto row = [&](int k) { return wave + k * kWaves; };
-    int k = 0;
-    if (wave < n) {
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) r[u] = ld(row(u));
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        if (row(k + kDepth - 1) < n) do {
+    __device__ __forceinline__ uint32_t load_codes(int k) const {
+        return __builtin_amdgcn_raw_buffer_load_b32(rv, int(off_v + uint32_t(k) * (cols * 4u)), 0, 0);
+    }
+    // the positions that a half-wave of some other shift has and one of this has not, in each half-wave's kSpan column statistics
+    static __device__ __forceinline__ void clear_ends(float* span) {
+        const int t = threadIdx.x;
+        if (t < kGroups * 16) span[(t >> 4) * kSpan + ((t & 15) < 8 ? t & 15 : 248 + (t & 15))] = 0.0f;
+    }
+    // one(set, k) for the half-wave's rows k = 0 .. rounds - 1, of which the first kDepth have been fetched; a register set is
+    // reloaded right after its row
+    template <class Row, class Fetch, class One>
+    __device__ __forceinline__ void run(Row (&r)[kDepth], Fetch fetch, One one) const {
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);          // loop start-up state: nothing outstanding
+        int k = 0;
+        while (k + kDepth - 1 < rounds) {
 #pragma unroll
             for (int u = 0; u < kDepth; ++u) {
-                one(r[u], row(k + u));
+                one(r[u], k + u);
                 __builtin_amdgcn_sched_barrier(0);
-                r[u] = ld(row(k + kDepth + u));
+                r[u] = fetch(k + kDepth + u);
                 __builtin_amdgcn_sched_barrier(0);
             }
             k += kDepth;
-        } while (row(k + kDepth - 1) < n);
+        }
 #pragma unroll
         for (int u = 0; u < kDepth - 1; ++u)
-            if (row(k + u) < n) one(r[u], row(k + u));
+            if (k + u < rounds) one(r[u], k + u);
     }
+};
+
+template <bool BF16>
+__device__ __forceinline__ void maxima_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    const RagStats<BF16> t(a, wg);
+    auto fetch = [&](int k) {
+        Row8<BF16> r;
+        t.load_grad(k, r.g);
+        r.vq = t.load_codes(k);
+        return r;
+    };
+    Row8<BF16> r[t.kDepth];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s.col[wave * kSpan + at + e] = cmax[e];
-    __syncthreads();
-    for (int t = threadIdx.x; t < n_stat; t += kThreads) {
-        const float m = fmaxf(s.blk_vmax[t], s.cold[t]);
-        if (m > 0.0f) atomic_max_nonneg(a.r_new + row0 + t, m);
+    for (int u = 0; u < t.kDepth; ++u) r[u] = fetch(u);
+    // Old statistics, requested with the first rows, so that one round trip to the memory stands in front of the loop: thread p takes
+    // position p of the strip (and 256 + p) and row p.  Lanes without columns get zeros: their moments are zero then.
+    float* const stage = reinterpret_cast<float*>(s.search);
+    float* const rows = stage + kSpan;                            // for the exact route
+    static_assert(kBucketsPadded * sizeof(SearchEntry) >= (kSpan + kThreads + 1) * sizeof(float) && kSpan <= 2 * kThreads, "old statistics");
+    auto col = [&](uint32_t c) { return c < t.cols ? c : c - t.cols; };
+    const int tid = threadIdx.x;
+    const uint32_t c_own = uint32_t(t.strip) * 256u + uint32_t(tid);
+    const float c_a = c_own < t.cols + 7u ? a.c[col(c_own)] : 0.0f;
+    const float c_b = tid < kSpan - kThreads && c_own + 256u < t.cols + 7u ? a.c[col(c_own + 256u)] : 0.0f;
+    const Rsrc rr = tile_rsrc(a.r + t.row0, uint32_t(t.n_stat) * 4u);
+    const float r_a = buf_ld_f1(rr, uint32_t(tid) * 4u), r_b = tid == 0 ? buf_ld_f1(rr, kThreads * 4u) : 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
+    float* const next = reinterpret_cast<float*>(s.deq);          // maxima of rows' first elements, from the row in front
+    stage[tid] = c_a;
+    if (tid < kSpan - kThreads) stage[tid + kThreads] = c_b;
+    rows[tid] = r_a;
+    s.blk_scale[tid] = r_a * 0.0625f;
+    s.blk_vmax[tid] = next[tid] = 0.0f;
+    static_assert(kMaxRw2 == kThreads, "rows of a tile and the one behind");
+    if (tid == 0) {
+        rows[kThreads] = r_b;
+        s.blk_scale[kThreads] = r_b * 0.0625f;
+        s.blk_vmax[kThreads] = next[kThreads] = 0.0f;
     }
-    for (int t = threadIdx.x; t < kSpan; t += kThreads) {
-        const uint32_t c = uint32_t(strip) * 256u + uint32_t(t);
-        const float m = fmaxf(fmaxf(s.col[t], s.col[kSpan + t]), fmaxf(s.col[2 * kSpan + t], s.col[3 * kSpan + t]));
-        if (m > 0.0f && c < cols + 3u) atomic_max_nonneg(a.c_new + (c < cols ? c : c - cols), m);
+    t.clear_ends(s.col);
+    const bool lane_tame = scale_is_tame(c_a) && scale_is_tame(c_b) && scale_is_tame(r_a) && scale_is_tame(r_b);
+    const bool tame = all_threads(s, lane_tame);         // else the exact route for the whole tile
+    float c16[8], cmax[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        c16[e] = t.live ? stage[t.at + e] * 0.0625f : 0.0f;
+        cmax[e] = 0.0f;
+    }
+    auto one = [&](const Row8<BF16>& x, int k, auto edge) {
+        constexpr bool kEdge = decltype(edge)::value;
+        const int il = t.grp + k * kGroups;
+        const bool in = il < t.n;                                 // behind the tile: zeros
+        float g[8], vt[8];
+        unpack_grad8<BF16>(x.g, g);
+        if (__builtin_expect(tame, 1)) {
+            float qf[8];
+            codes_to_float8(x.vq, qf);
+            const float ra = in ? s.blk_scale[il] : 0.0f, rb = kEdge && in ? s.blk_scale[il + 1] : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vt[e] = dequant_v16(qf[e], min_nonneg(kEdge && t.next_row(e) ? rb : ra, c16[e]));
+        } else {
+            const float ra = in ? rows[il] : 0.0f, rb = kEdge && in ? rows[il + 1] : 0.0f;
+            uint32_t at = t.at;
+            asm volatile("" : "+v"(at));                          // these columns are not worth registers all along
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                vt[e] = dequant_v((x.vq >> (4 * e)) & 15u, t.live ? fminf(kEdge && t.next_row(e) ? rb : ra, stage[at + e]) : 0.0f);
+        }
+        float own = 0.0f, behind = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            vt[e] = moment_v(h, vt[e], g[e]);
+            cmax[e] = fmaxf(cmax[e], vt[e]);                      // a NaN raises no maximum
+        }
+        if constexpr (kEdge) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                own = fmaxf(own, t.next_row(e) ? 0.0f : vt[e]);
+                behind = fmaxf(behind, t.next_row(e) ? vt[e] : 0.0f);
+            }
+            if (t.live && t.next_row(7)) next[il + 1] = behind;   // one lane of the row
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) own = fmaxf(fmaxf(own, vt[e]), vt[e + 1]);
+        }
+        own = group32_allmax(own);
+        if (t.l == 0) s.blk_vmax[il] = own;
+    };
+    if (t.edge) t.run(r, fetch, [&](const Row8<BF16>& x, int k) { one(x, k, std::true_type{}); });
+    else t.run(r, fetch, [&](const Row8<BF16>& x, int k) { one(x, k, std::false_type{}); });
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.col[t.grp * kSpan + int(t.at) + e] = cmax[e];
+    __syncthreads();
+    for (int k = threadIdx.x; k < t.n_stat; k += kThreads) {
+        const float m = fmaxf(s.blk_vmax[k], next[k]);
+        if (m > 0.0f) atomic_max_nonneg(a.r_new + t.row0 + k, m);
+    }
+    for (int k = threadIdx.x; k < kSpan; k += kThreads) {
+        const uint32_t c = uint32_t(t.strip) * 256u + uint32_t(k);
+        float m = 0.0f;
+#pragma unroll
+        for (int y = 0; y < kGroups; ++y) m = fmaxf(m, s.col[y * kSpan + k]);
+        if (m > 0.0f && c < t.cols + 7u) atomic_max_nonneg(a.c_new + (c < t.cols ? c : c - t.cols), m);
     }
 }
 
-// The part of the last row that the tiles leave out.
+// The part of the last row that the tiles leave out.  A workgroup requests its elements all at once (one after the other, two
+// round trips each, they were the end of the pass: 847 x 4973 bf16 9.1 us, 6.7 so).
+constexpr int kLastEach = kLastRowElems / kThreads;
+template <bool BF16>
+struct LastRow {
+    int64_t first, col0, left;      // first element, its column, elements from there on
+    __device__ __forceinline__ LastRow(const Tensor4& a, int part) {
+        first = last_row_begin(a) + int64_t(part) * kLastRowElems;
+        col0 = first - (a.rows - 1) * a.cols;
+        left = a.P - first;
+    }
+    __device__ __forceinline__ int at(int u) const { return u * kThreads + int(threadIdx.x); }
+    __device__ __forceinline__ bool on(int u) const { return at(u) < left; }
+    __device__ __forceinline__ void grads(const Tensor4& a, uint32_t raw[kLastEach]) const {      // zeros behind the end
+        const Rsrc r = tile_rsrc(reinterpret_cast<const char*>(a.g) + first * (BF16 ? 2 : 4), uint32_t(left) * (BF16 ? 2u : 4u));
+#pragma unroll
+        for (int u = 0; u < kLastEach; ++u) {
+            if constexpr (BF16) raw[u] = uint16_t(__builtin_amdgcn_raw_buffer_load_b16(r, at(u) * 2, 0, 0));
+            else raw[u] = __builtin_amdgcn_raw_buffer_load_b32(r, at(u) * 4, 0, 0);
+        }
+    }
+    static __device__ __forceinline__ float value(uint32_t raw) { return __uint_as_float(BF16 ? raw << 16 : raw); }
+};
+
 template <bool BF16>
 __device__ __forceinline__ void maxima_last_row(const Tensor4& a, const Hyper& h, int part) {
-    const int64_t first = last_row_begin(a) + int64_t(part) * kLastRowElems;
+    const LastRow<BF16> t(a, part);
     const float r_old = a.r[a.rows - 1];
-    float rmax = 0.0f;
-    for (int u = 0; u < kLastRowElems / kThreads; ++u) {
-        const int64_t e = first + int64_t(u) * kThreads + threadIdx.x;
-        if (e >= a.P) break;
-        const int64_t j = e - (a.rows - 1) * a.cols;
-        const uint32_t q = (reinterpret_cast<const uint8_t*>(a.vq)[e >> 1] >> (4 * (e & 1))) & 15u;
-        const float vt = fmaxf(moment_v(h, dequant_v(q, fminf(r_old, a.c[j])), load_grad1<BF16>(a.g, e)), 0.0f);
-        if (vt > 0.0f) atomic_max_nonneg(a.c_new + j, vt);
+    float c[kLastEach], rmax = 0.0f;
+    uint32_t g[kLastEach], q[kLastEach];
+    t.grads(a, g);
+    const Rsrc rc = tile_rsrc(a.c + t.col0, uint32_t(t.left) * 4u), rq = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (t.first >> 1), uint32_t(t.left + 1) / 2u);
+#pragma unroll
+    for (int u = 0; u < kLastEach; ++u) {
+        c[u] = buf_ld_f1(rc, uint32_t(t.at(u)) * 4u);
+        q[u] = uint8_t(__builtin_amdgcn_raw_buffer_load_b8(rq, t.at(u) >> 1, 0, 0));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kLastEach; ++u) {
+        const float v = dequant_v((q[u] >> (4 * (threadIdx.x & 1))) & 15u, fminf(r_old, c[u]));      // behind the end: 0
+        const float vt = fmaxf(moment_v(h, v, t.value(g[u])), 0.0f);
+        if (vt > 0.0f) atomic_max_nonneg(a.c_new + t.col0 + t.at(u), vt);
         rmax = fmaxf(rmax, vt);
     }
     for (int d = 1; d < 64; d <<= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, d));
@@ -410,7 +512,7 @@ __device__ __forceinline__ void update_ragged_tile(const Tensor4& a, const Hyper
         }
     }
     if (tid <= t.n_rows) stage_row_new(s, tid, tame_too(r_new));
-    const bool tame = !__syncthreads_or(int(!lane_tame));
+    const bool tame = all_threads(s, lane_tame);
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see update_tile)
     if (tame) sync.staged();
     auto none = [] {};
@@ -504,101 +606,86 @@ __device__ __forceinline__ void update_ragged(const Tensor4& a, const Hyper& h, 
 // an exact division and four loads of statistics per element for the update.  General / these, us per step: 4096 x 4000
 // bf16 907 / 49, 1024 x 50257 bf16 1747 / 147, 30000 x 1000 fp32 361 / 107, 600 x 147 fp32 15.7 / 13.9.)
 
-// Statistics pass: the row-class walk of maxima_ragged_tile (a wave's rows are a multiple of 4 apart, so its lanes keep their columns
-// down the tile).  Columns are counted on through the end of a row: positions cols, cols + 1, cols + 2 are the next row's
-// first ones, whose squares the row's last lane collects for that row.
+// Statistics pass: the tiles of maxima_ragged_tile, sums of squares in place of maxima.
 template <bool BF16>
 __device__ __forceinline__ void factor_stats_ragged_tile(const Tensor4& a, int wg, Lds& s) {
-    const int strip = wg % a.strips2, tile = wg / a.strips2;
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    const int64_t row0 = int64_t(tile) * a.rw2;                   // a multiple of 4
-    const int64_t left = class_rows(a) - row0;
-    const int n = left < a.rw2 ? int(left) : a.rw2;
-    const int n_stat = row0 + n < a.rows ? n + 1 : n;
-    const uint32_t cols = uint32_t(a.cols);
-    const uint32_t shift = (0u - uint32_t(wave) * cols) & 3u;
-    const uint32_t at = uint32_t(lane) * 4u + shift, col0 = uint32_t(strip) * 256u + at;
-    const bool live = col0 < cols;
-    const Rsrc rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + row0 * a.cols * (BF16 ? 2 : 4),
-                              uint32_t(n_stat) * cols * (BF16 ? 2u : 4u));
-    const int last = n - 1 - (n - 1 - wave) % kWaves;             // the wave's own last row, if it has any (wave < n)
-    auto ld = [&](int il) { return load_grad_regs4<BF16>(rg, live ? (uint32_t(il < last ? il : last) * cols + col0) * 4u : kNowhere); };
-    for (int t = threadIdx.x; t < 4 * kSpan; t += kThreads) s.col[t] = 0.0f;
-    for (int t = threadIdx.x; t <= n; t += kThreads) { s.blk_scale[t] = 0.0f; s.blk_vmax[t] = 0.0f; }
-    __syncthreads();
-    float cacc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    auto one = [&](const GradRegs4<BF16>& r, int il) {
-        float g[4];
-        unpack_grad4<BF16>(r, g);
-        float own = 0.0f, beyond = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float sq = live ? g[e] * g[e] : 0.0f;
-            cacc[e] += sq;
-            own += col0 + e < cols ? sq : 0.0f;
-            beyond += col0 + e < cols ? 0.0f : sq;
-        }
-        own = wave_sum(own);
-        if (lane == 0) s.blk_scale[il] = own;
-        if (live && col0 + 3u >= cols) s.blk_vmax[il + 1] = beyond;        // one lane of the last strip
+    const RagStats<BF16> t(a, wg);
+    struct Row { float4 g[BF16 ? 1 : 2]; };
+    auto fetch = [&](int k) {
+        Row r;
+        t.load_grad(k, r.g);
+        return r;
     };
-    constexpr int kDepth = 3;                                     // as in factor_stats_tile
-    GradRegs4<BF16> r[kDepth];
-    auto row = [&](int k) { return wave + k * kWaves; };
-    int k = 0;
-    if (wave < n) {
+    Row r[t.kDepth];
 #pragma unroll
-        for (int u = 0; u < kDepth; ++u) r[u] = ld(row(u));
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        if (row(k + kDepth - 1) < n) do {
-#pragma unroll
-            for (int u = 0; u < kDepth; ++u) {
-                one(r[u], row(k + u));
-                __builtin_amdgcn_sched_barrier(0);
-                r[u] = ld(row(k + kDepth + u));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            k += kDepth;
-        } while (row(k + kDepth - 1) < n);
-#pragma unroll
-        for (int u = 0; u < kDepth - 1; ++u)
-            if (row(k + u) < n) one(r[u], row(k + u));
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s.col[wave * kSpan + at + e] = cacc[e];
+    for (int u = 0; u < t.kDepth; ++u) r[u] = fetch(u);
+    float* const next = reinterpret_cast<float*>(s.deq);          // sums of rows' first elements, from the row in front
+    for (int k = threadIdx.x; k <= t.n; k += kThreads) { s.blk_scale[k] = 0.0f; next[k] = 0.0f; }
+    t.clear_ends(s.col);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    float old = 0.0f;                                             // of the tile's rows, once per row
+    if (wave == 1 && t.strip == 0)
+        for (int k = lane; k < t.n; k += 64) old += a.r[t.row0 + k];
     __syncthreads();
-    for (int t = threadIdx.x; t < n_stat; t += kThreads) atomic_add_f32(a.r_new + row0 + t, s.blk_scale[t] + s.blk_vmax[t]);
-    for (int t = threadIdx.x; t < kSpan; t += kThreads) {
-        const uint32_t c = uint32_t(strip) * 256u + uint32_t(t);
-        const float sum = (s.col[t] + s.col[kSpan + t]) + (s.col[2 * kSpan + t] + s.col[3 * kSpan + t]);
-        if (sum != 0.0f && c < cols + 3u) atomic_add_f32(a.c_new + (c < cols ? c : c - cols), sum);
+    float cacc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    auto one = [&](const Row& x, int k, auto edge) {
+        constexpr bool kEdge = decltype(edge)::value;
+        const int il = t.grp + k * kGroups;
+        float g[8], sq[8], own[8];
+        unpack_grad8<BF16>(x.g, g);                               // zeros in lanes without columns and behind the tile
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            sq[e] = g[e] * g[e];
+            cacc[e] += sq[e];
+            own[e] = kEdge && t.next_row(e) ? 0.0f : sq[e];
+        }
+        auto sum8 = [](const float (&v)[8]) { return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])); };
+        if constexpr (kEdge) {
+            if (t.live && t.next_row(7)) {                        // one lane of the row
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sq[e] = t.next_row(e) ? sq[e] : 0.0f;
+                next[il + 1] = sum8(sq);
+            }
+        }
+        const float sum = group32_sum(sum8(own));
+        if (t.l == 0) s.blk_scale[il] = sum;
+    };
+    if (t.edge) t.run(r, fetch, [&](const Row& x, int k) { one(x, k, std::true_type{}); });
+    else t.run(r, fetch, [&](const Row& x, int k) { one(x, k, std::false_type{}); });
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.col[t.grp * kSpan + int(t.at) + e] = cacc[e];
+    __syncthreads();
+    for (int k = threadIdx.x; k < t.n_stat; k += kThreads) atomic_add_f32(a.r_new + t.row0 + k, s.blk_scale[k] + next[k]);
+    for (int k = threadIdx.x; k < kSpan; k += kThreads) {
+        const uint32_t c = uint32_t(t.strip) * 256u + uint32_t(k);
+        auto at = [&](int y) { return s.col[y * kSpan + k]; };
+        const float sum = ((at(0) + at(1)) + (at(2) + at(3))) + ((at(4) + at(5)) + (at(6) + at(7)));
+        if (sum != 0.0f && c < t.cols + 7u) atomic_add_f32(a.c_new + (c < t.cols ? c : c - t.cols), sum);
     }
     float* tot = reinterpret_cast<float*>(a.counter);
     if (wave == 0) {
         float part = 0.0f;
-        for (int t = lane; t < n_stat; t += 64) part += s.blk_scale[t] + s.blk_vmax[t];
+        for (int k = lane; k < t.n_stat; k += 64) part += s.blk_scale[k] + next[k];
         part = wave_sum(part);
         if (lane == 0) atomic_add_f32(tot + tot_new_word(wg & (a.tot_slots - 1)), part);
-    } else if (wave == 1 && strip == 0) {
-        float part = 0.0f;
-        for (int t = lane; t < n; t += 64) part += a.r[row0 + t];
-        part = wave_sum(part);
-        if (lane == 0) atomic_add_f32(tot + tot_old_word(tile & (a.tot_slots - 1)), part);
+    } else if (wave == 1 && t.strip == 0) {
+        old = wave_sum(old);
+        if (lane == 0) atomic_add_f32(tot + tot_old_word(t.tile & (a.tot_slots - 1)), old);
     }
 }
 
-// The part of the last row that the tiles leave out (see class_rows).
+// The part of the last row that the tiles leave out.
 template <bool BF16>
 __device__ __forceinline__ void factor_stats_last_row(const Tensor4& a, int part, Lds& s) {
-    const int64_t first = last_row_begin(a) + int64_t(part) * kLastRowElems;
+    const LastRow<BF16> t(a, part);
     const int lane = threadIdx.x & 63;
+    uint32_t g[kLastEach];
     float sum = 0.0f;
-    for (int u = 0; u < kLastRowElems / kThreads; ++u) {
-        const int64_t e = first + int64_t(u) * kThreads + threadIdx.x;
-        if (e >= a.P) break;
-        const float g = load_grad1<BF16>(a.g, e), sq = g * g;
-        atomic_add_f32(a.c_new + (e - (a.rows - 1) * a.cols), sq);
+    t.grads(a, g);
+#pragma unroll
+    for (int u = 0; u < kLastEach; ++u) {
+        const float sq = t.value(g[u]) * t.value(g[u]);
+        if (t.on(u)) atomic_add_f32(a.c_new + t.col0 + t.at(u), sq);
         sum += sq;
     }
     sum = wave_sum(sum);
@@ -624,32 +711,46 @@ __device__ __forceinline__ void factor_stats_ragged(const Tensor4& a, int wg, Ld
 // over their total.
 template <bool BF16, bool ONE_STRIP>
 __device__ __forceinline__ void factor_update_ragged_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
+    // start-up as in update_ragged_tile: everything is requested before any of it is waited for
+    const TableRegs tables = request_tables();
     const RagTile t = rag_tile<ONE_STRIP>(a, wg);
     const TileBase tb = rag_base<BF16>(a, t);
-    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31, tid = threadIdx.x;
     auto unit = [&](int q) { return rag_unit<ONE_STRIP>(t, a, grp, q); };
     auto fetch = [&](const RagUnit& u) { return load_rowf<BF16>(tb, u.off4 == kNowhere ? kNowhere : u.off4 + 16u * l); };
     const int n = rag_units<ONE_STRIP>(t, a);
+    float c_old[kRagPos], c_sum[kRagPos];
+#pragma unroll
+    for (int u = 0; u < kRagPos; ++u) {
+        const int k = tid + u * kThreads;
+        const bool in = k < t.width + 128;
+        const int c = in ? rag_col(t, a.cols, k) : 0;
+        c_old[u] = in ? a.c[c] : 0.0f;
+        c_sum[u] = in ? a.c_new[c] : 0.0f;
+    }
+    const bool row_in = tid < t.n_rows && t.row0 + tid < a.rows;
+    const float r_old = row_in ? a.r[t.row0 + tid] : 0.0f, r_sum = row_in ? a.r_new[t.row0 + tid] : 0.0f;
+    float ms_old = 0.0f;
+    if constexpr (ONE_STRIP) {
+        if (tid < t.n_blocks) ms_old = tb.ms[tid];
+    } else if (tid < t.own_rows * kFlatBlocks) {
+        const int b = ((t.f0 + int(row_offset(tid / kFlatBlocks, a.cols, 0u)) + 127) >> 7) + tid % kFlatBlocks;
+        if (tid % kFlatBlocks < t.per_row && b < t.end) ms_old = tb.ms[b];
+    }
     RagUnit u0 = unit(0), u1 = unit(1), u2;
     RowF<BF16> r0 = fetch(u0), r1 = fetch(u1), r2;
     const float inv_total = factor_inv_total(a, h);
-    for (int k = threadIdx.x; k < t.width + 128; k += kThreads) {
-        const int c = rag_col(t, a.cols, k);
-        s.cold[k] = stat_ema(h, a.c[c], a.c_new[c]);
+    __builtin_amdgcn_sched_barrier(0);
+    put_tables(s, tables);
+#pragma unroll
+    for (int u = 0; u < kRagPos; ++u) {
+        const int k = tid + u * kThreads;
+        if (k < t.width + 128) s.cold[k] = stat_ema(h, c_old[u], c_sum[u]);
     }
-    for (int k = threadIdx.x; k < kRagRowSlots; k += kThreads) {
-        const int64_t i = t.row0 + k;
-        s.blk_vmax[k] = k < t.n_rows && i < a.rows ? stat_ema(h, a.r[i], a.r_new[i]) * inv_total : 0.0f;
-    }
-    if constexpr (ONE_STRIP) {
-        for (int k = threadIdx.x; k < t.n_blocks; k += kThreads) s.blk_scale[k] = tb.ms[k];
-    } else {
-        for (int k = threadIdx.x; k < t.own_rows * kFlatBlocks; k += kThreads) {
-            const int b = ((t.f0 + int(row_offset(k / kFlatBlocks, a.cols, 0u)) + 127) >> 7) + k % kFlatBlocks;
-            if (k % kFlatBlocks < t.per_row && b < t.end) s.blk_scale[k] = tb.ms[b];
-        }
-    }
-    load_tables(s);
+    static_assert(kRagRowSlots == kThreads, "a thread per row");
+    s.blk_vmax[tid] = stat_ema(h, r_old, r_sum) * inv_total;
+    s.blk_scale[tid] = ms_old;
+    __syncthreads();
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see update_tile)
     auto none = [] {};
     auto work = [&](const RowF<BF16>& cur, const RagUnit& u, auto mid) {

@@ -167,3 +167,23 @@ def test_tiles_near_two_gigabytes(monkeypatch, rows, cols, plan, bf16):
         row.append(v.max())
         torch.maximum(col, v, out=col)
     assert torch.equal(st.v_rowmax, torch.stack(row)) and torch.equal(st.v_colmax, col)
+
+
+@pytest.mark.parametrize("rows,cols,bf16", [
+    (17, 263, False),        # a row's last lane ends in the strip in front of the last one, by shift
+    (25, 262, True),
+    (24, 513, True),
+    (9, 519, False),
+    (8, 1290, True),         # tiles of 8 rows, whole
+    (520, 131, True),        # several tall tiles, one strip
+    (31, 2308, False),       # P = 4 (mod 8): a last row of its own, in two parts
+    (2, 4099, True),
+    (66, 776, True),         # P = 0 (mod 8): no last row
+])
+def test_statistics_tiles_at_their_edges(rows, cols, bf16):
+    """Lanes of 8 elements that start a shift into their row and end in the next one, for both forms of the second moment.  The
+    maxima are exact; the sums' bound is test_gpu_factor's."""
+    from test_gpu_factor import run
+    print(f"[gpu-test] ragged statistics {rows}x{cols} bf16={bf16}", flush=True)
+    assert run_parity(rows, cols, steps=3, recipe="col_lognormal", bf16=bf16, seed=76) == 0
+    assert run(rows, cols, steps=2, bf16=bf16) == 0

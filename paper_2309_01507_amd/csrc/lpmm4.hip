@@ -1576,8 +1576,8 @@ int lpmm_quant_state(int which, const float* in, const int64_t shape[2], uint8_t
 
 namespace {
 
-// the map of an ablation quantizer, with its decision thresholds; false for a combination that does not exist
-bool ablation_map(int map, int is_signed, AblMap* m) {
+// the map of an ablation quantizer with what its kernels search it by; false for a combination that does not exist
+bool build_ablation_map(int map, int is_signed, AblMap* m) {
     float T[kCodes];
     int n = kCodes;
     if (map == LPMM_MAP_DE) {
@@ -1594,8 +1594,35 @@ bool ablation_map(int map, int is_signed, AblMap* m) {
     }
     *m = AblMap{};
     m->n = n;
+    m->least = is_signed ? -1.0f : 0.0f;
     for (int i = 0; i < n; ++i) m->T[i] = T[i];
     build_thresholds_n(T, n, m->thr);
+    bool ok = one_per_bucket(T, n, m->entry_bucket) && one_per_bucket(m->thr, n - 1, m->thr_bucket);
+    for (int i = 0; i < kCodes; ++i) {
+        if (i >= n) m->entry_bucket[i] = kBuckets;
+        if (i >= n - 1) m->thr_bucket[i] = kBuckets;
+        const int k = std::clamp(i, 1, n - 1);              // the gap between entries k - 1 and k
+        m->lo[i] = T[k - 1];
+        float inv = float(0x1p24 / (double(T[k]) - double(T[k - 1])));
+        while ((T[k] - T[k - 1]) * inv < 0x1p24f) inv = std::nextafterf(inv, std::numeric_limits<float>::infinity());
+        m->inv_gap[i] = inv;
+        // what the kernels' margins rest on
+        ok = ok && std::fabs(double(T[k])) <= 17.9 * (double(T[k]) - double(T[k - 1]));
+    }
+    return ok;
+}
+bool ablation_map(int map, int is_signed, AblMap* m) {
+    struct Maps {
+        AblMap m[3][2];
+        bool ok[3][2];
+        Maps() {
+            for (int k = 0; k < 3; ++k)
+                for (int s = 0; s < 2; ++s) ok[k][s] = build_ablation_map(k, s, &m[k][s]);
+        }
+    };
+    static const Maps maps;
+    if (map < 0 || map > 2 || !maps.ok[map][is_signed ? 1 : 0]) return false;
+    *m = maps.m[map][is_signed ? 1 : 0];
     return true;
 }
 

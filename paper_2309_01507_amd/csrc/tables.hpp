@@ -113,6 +113,19 @@ inline int search_bucket(float n) {
     return int(f2u(x) - kBucketMagicBits) + kBucketHalf;
 }
 
+// The buckets of n increasing values of [-1, 1]; false if two share one, or if one lies so close to a bucket's edge that a value that
+// is looked up could be on one side and its approximation on the other (see build_search).
+inline bool one_per_bucket(const float* v, int n, int* bucket) {
+    for (int k = 0; k < n; ++k) {
+        if (!(std::fabs(v[k]) <= 1.0f)) return false;
+        bucket[k] = search_bucket(v[k]);
+        if (k > 0 && bucket[k] <= bucket[k - 1]) return false;
+        const double pos = double(v[k]) * kBucketHalf + 0.5;
+        if (std::fabs(pos - std::nearbyint(pos)) < std::ldexp(std::fabs(double(v[k])) * kBucketHalf, -20)) return false;
+    }
+    return true;
+}
+
 // Returns false if some bucket would need two thresholds (then the buckets are too coarse for this
 // map) or a threshold lies outside [-1, 1].
 inline bool build_search(const float thr[kCodes - 1], SearchEntry tab[kBucketsPadded]) {

@@ -108,3 +108,30 @@ def test_bad_arguments_are_refused():
     assert L.lpmm_quant_ablation(2, 0, 0, 0, 0, p, ctypes.addressof(shape), p, p, None, None) == -1     # rank-1 without column maxima
     assert L.lpmm_dequant_ablation(0, 5, 0, p, p, None, ctypes.addressof(shape), p, None) == -1
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("norm,map_name,signed", COMBOS)
+@pytest.mark.parametrize("stochastic", [False, True])
+def test_values_around_entries_and_thresholds(norm, map_name, signed, stochastic):
+    """Normalized values on, and a few units in the last place around, every entry and decision threshold, under scales that are
+    and are not powers of two, tiny and huge ones and zero; for rank-1, under row maxima that hold for the row alone."""
+    T = lpmm.lpmm_ablation_table(MAP[map_name], signed).astype(np.float64)
+    at = np.concatenate([T, (T[1:] + T[:-1]) / 2, [0.0]]).astype(np.float32)
+    n = np.concatenate([at] + [np.nextafter(at, np.float32(s), dtype=np.float32) for s in (-4, 4)] +
+                       [at * np.float32(1 + k * 2.0 ** -22) for k in (-9, -3, 3, 9)])
+    n = n[(np.abs(n) <= 1) & ((n >= 0) | signed)]
+    rng = np.random.default_rng(17)
+    rows = []
+    for s in (1.0, 0.37, 3.1e-7, 1.9999999, 2.0 ** -99.5, 1.7e29, 1e-33, 3e38, 0.0):
+        x = rng.choice(n, 4096) * np.float32(s)
+        x[::128] = s                                    # every block, of either size, and every row and column block holds its scale
+        rows.append(x.astype(np.float32))
+    x = np.stack(rows)
+    if norm == "rank1":
+        x[:, 1::2] = np.where(x[:, 1::2] > 0, x[:, 1::2], 0)
+    want_codes, want_sa, want_sb = oracle.quant_ablation(x, norm, map_name, signed, stochastic, 4711)
+    codes, sa, sb = _gpu_quant(x, norm, map_name, signed, stochastic, 4711)
+    np.testing.assert_array_equal(sa.cpu().numpy(), want_sa)
+    if norm == "rank1":
+        np.testing.assert_array_equal(sb.cpu().numpy(), want_sb)
+    np.testing.assert_array_equal(oracle.unpack_codes(codes.cpu().numpy(), x.size), oracle.unpack_codes(want_codes, x.size))

@@ -135,10 +135,19 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+_torch = None
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        global _torch
+        if _torch is None:
+            import torch
+            _torch = torch
+        # the current stream's handle, without the Stream object around it (2.8 us of a call's 9 to 13)
+        if _torch.cuda.is_initialized():
+            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice()) or None
+        return _torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None

@@ -41,9 +41,9 @@ class _PlanOptimizer:
     def _ensure_plan(self):
         grads = []
         for p in self.params:
-            if p.grad is None:
-                raise ValueError("every parameter needs a gradient (frozen parameters: requires_grad=False)")
             g = p.grad
+            if g is None:
+                raise ValueError("every parameter needs a gradient (frozen parameters: requires_grad=False)")
             if not g.is_contiguous() or g.dtype not in (torch.float32, torch.bfloat16):
                 raise ValueError("gradients must be contiguous fp32 or bf16")
             grads.append(g)
@@ -68,8 +68,11 @@ class _PlanOptimizer:
     def step(self):
         self._ensure_plan()
         self.t += 1
-        with torch.cuda.device(self.device):
+        if torch._C._cuda_getDevice() == self.device.index:
             self._step(self._plan)
+        else:
+            with torch.cuda.device(self.device):
+                self._step(self._plan)
 
     def zero_grad(self, set_to_none: bool = False):
         for p in self.params:

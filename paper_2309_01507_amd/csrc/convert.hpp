@@ -253,85 +253,83 @@ __global__ __launch_bounds__(kThreads) void quant_vb_kernel(const QuantArgs q) {
 
 // Row and column maxima of a rows x cols matrix into sa / sb (zero on entry), for rank-1 normalization.
 //
-// A workgroup takes `rows_per_wg` rows x a strip of 4 * tx columns, tx = 2^tx_log2 lanes of 4 columns side by side and
-// 256 / tx rows at a time: a lane keeps its columns' maxima in registers, a row's maximum is reduced over its lanes and
-// combined in LDS, and one global atomic per row and per column of the tile follows at the end.  An atomic per element
-// -- read first and skipped where it cannot raise the value -- made the atomics' queues the bound: 2.96 ms for
-// 11008 x 4096, 54 us this way.
+// A workgroup takes rows_per_wg rows x a strip of 8 * TX columns: TX lanes take 8 columns each of one row, 256 / TX rows side by
+// side.  Column maxima stay in registers down the tile, a row's maximum is reduced over its lanes, and one global atomic per row and
+// per column of the tile follows at the end.  A maximum may be taken twice, so nothing needs a branch at the edges: lanes beyond the
+// last column repeat the last 8 of them, rows beyond the last one repeat that.
+// Bound by those atomics and by latency where the matrix is small, else by memory.  Strips of 1024 columns by 4 to 32 rows, as the
+// filling of the chip asked for them, sent two to three times as many atomics, which were what the pass took: 3000 x 1001 18.6 us, 6.3
+// so, 1000 x 1001 8.0 and 4.2, 4096 x 4096 15.3 and 13.8, 11008 x 4096 43 and 35.5 (5.1 TB/s).
 constexpr int kMaxTileRows = 512;
-constexpr int kMaxMinTxLog2 = 4;          // 16 lanes: a DPP row
+constexpr int kMaxCols = 8;               // of a lane
 
 struct MaxTiling {
-    int tx_log2;          // 4..8
-    int rows_per_wg;      // <= kMaxTileRows, a multiple of 256 >> tx_log2
-    int strips;           // ceil(cols / (4 << tx_log2))
+    int rows_per_wg;      // <= kMaxTileRows
+    int strips;           // ceil(cols / (8 * TX))
 };
 
+template <int TX>
 __global__ __launch_bounds__(kThreads) void quant_v_max_kernel(const QuantArgs q, const MaxTiling t) {
-    __shared__ unsigned int s_row[kMaxTileRows];
-    __shared__ unsigned int s_col[kThreads * 4];
-    const int strip = blockIdx.x % t.strips;
+    static_assert(TX == 16 || TX == 32, "lanes of a row: a DPP row or a half-wave");
+    constexpr int kTy = kThreads / TX, kDepth = 4;
+    __shared__ uint32_t s_row[kMaxTileRows];
+    __shared__ uint32_t s_col[kTy][TX * kMaxCols];
+    const int64_t strip0 = int64_t(blockIdx.x % t.strips) * (TX * kMaxCols);
     const int64_t row0 = int64_t(blockIdx.x / t.strips) * t.rows_per_wg;
     const int64_t left = q.rows - row0;
     const int n = left < t.rows_per_wg ? int(left) : t.rows_per_wg;
-    const int tx = 1 << t.tx_log2, ty = kThreads >> t.tx_log2;
-    const int x = threadIdx.x & (tx - 1), y = threadIdx.x >> t.tx_log2;
-    for (int k = threadIdx.x; k < n; k += kThreads) s_row[k] = 0u;
-    for (int k = threadIdx.x; k < 4 * tx; k += kThreads) s_col[k] = 0u;
-    __syncthreads();
-    const int64_t col0 = int64_t(strip) * (4 << t.tx_log2) + 4 * x;
-    const int nc = q.cols - col0 >= 4 ? 4 : (q.cols > col0 ? int(q.cols - col0) : 0);      // the lane's columns
-    const float* p = q.x_in + row0 * q.cols + col0;
-    float cm[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    constexpr int kDepth = 4;
-    // n and ty are uniform: every lane of a wave runs the same rounds, so the cross-lane steps see whole waves
-    for (int base = 0; base < n; base += ty * kDepth) {
-        float v[kDepth][4];
+    const int x = threadIdx.x % TX, y = threadIdx.x / TX;
+    const int64_t own = strip0 + kMaxCols * x, last = q.cols > kMaxCols ? q.cols - kMaxCols : 0;
+    const float* p = q.x_in + row0 * q.cols + (own < last ? own : last);
+    const bool wide = q.cols >= kMaxCols;
+    const int last_col = int(q.cols < kMaxCols ? q.cols : kMaxCols) - 1;
+    // a value's bits, 0 unless it is above 0 (a NaN raises no maximum)
+    auto bits = [](float v) { return v > 0.0f ? __float_as_uint(v) : 0u; };
+    uint32_t cm[kMaxCols];
+#pragma unroll
+    for (int e = 0; e < kMaxCols; ++e) cm[e] = 0u;
+    for (int base = 0; base < n; base += kTy * kDepth) {          // the same rounds in all lanes
+        float v[kDepth][kMaxCols];
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
-            const int il = base + u * ty + y;
+            const int il = base + u * kTy + y;
+            const float* pr = p + int64_t(il < n ? il : n - 1) * q.cols;
+            if (wide) {
+                const v4f_a4 a = reinterpret_cast<const v4f_a4*>(pr)[0], b = *reinterpret_cast<const v4f_a4*>(pr + 4);
+                v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
+                v[u][4] = b.x; v[u][5] = b.y; v[u][6] = b.z; v[u][7] = b.w;
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[u][e] = 0.0f;
-            if (il < n) {
-                const float* pr = p + int64_t(il) * q.cols;
-                if (nc == 4) {
-                    const v4f_a4 w = *reinterpret_cast<const v4f_a4*>(pr);
-                    v[u][0] = w.x; v[u][1] = w.y; v[u][2] = w.z; v[u][3] = w.w;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 3; ++e)
-                        if (e < nc) v[u][e] = pr[e];
-                }
+                for (int e = 0; e < kMaxCols; ++e) v[u][e] = pr[e < last_col ? e : last_col];
             }
         }
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
-            const int il = base + u * ty + y;
-            float rm = 0.0f;
+            const int il = base + u * kTy + y;
+            uint32_t rm = 0u;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float z = v[u][e] > 0.0f ? v[u][e] : 0.0f;
-                cm[e] = max_nonneg(cm[e], z);
-                rm = max_nonneg(rm, z);
+            for (int e = 0; e < kMaxCols; ++e) {
+                const uint32_t z = bits(v[u][e]);
+                cm[e] = max(cm[e], z);
+                rm = max(rm, z);
             }
-            if (t.tx_log2 == 4) {
-                rm = row16_allmax(rm);
-            } else {
-                rm = group32_allmax(rm);
-                if (t.tx_log2 > 5) rm = max_nonneg(rm, __shfl_xor(rm, 32));
-            }
-            if ((threadIdx.x & ((tx < 64 ? tx : 64) - 1)) == 0 && il < n && rm > 0.0f)
-                (void)__hip_atomic_fetch_max(&s_row[il], __float_as_uint(rm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const float all = TX == 16 ? row16_allmax(__uint_as_float(rm)) : group32_allmax(__uint_as_float(rm));
+            if (x == 0 && il < n) s_row[il] = __float_as_uint(all);
         }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        (void)__hip_atomic_fetch_max(&s_col[4 * x + e], __float_as_uint(cm[e]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int e = 0; e < kMaxCols; ++e) s_col[y][x * kMaxCols + e] = cm[e];
     __syncthreads();
     for (int k = threadIdx.x; k < n; k += kThreads)
         if (s_row[k]) atomicMax(reinterpret_cast<unsigned int*>(q.sa) + row0 + k, s_row[k]);
-    for (int k = threadIdx.x; k < 4 * tx; k += kThreads)
-        if (s_col[k]) atomicMax(reinterpret_cast<unsigned int*>(q.sb) + int64_t(strip) * (4 << t.tx_log2) + k, s_col[k]);
+    if (int(threadIdx.x) < TX * kMaxCols) {
+        const int64_t lane_own = strip0 + (threadIdx.x & ~(kMaxCols - 1)), lane0 = lane_own < last ? lane_own : last;
+        const int64_t col = lane0 + threadIdx.x % kMaxCols;
+        uint32_t m = 0u;
+#pragma unroll
+        for (int k = 0; k < kTy; ++k) m = max(m, s_col[k][threadIdx.x]);
+        if (m && lane_own < q.cols && col < q.cols) atomicMax(reinterpret_cast<unsigned int*>(q.sb) + col, m);
+    }
 }
 
 // second moment, after the maxima: codes against min(r_i, c_j)

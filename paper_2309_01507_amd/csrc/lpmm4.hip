@@ -1153,23 +1153,26 @@ int fill(void* dst, int64_t n, uint8_t value, int64_t last_index, uint8_t last, 
     return LPMM_OK;
 }
 
-// Row and column maxima of q.x_in into q.sa / q.sb.  As many lanes side by side as the columns need, rounded up to a
-// power of two between 16 and 256; 32 rows per group of lanes, halved down to 4 (one batch of loads) while the tensor
-// would give the chip fewer than four workgroups per CU.
+// Row and column maxima of q.x_in into q.sa / q.sb.  Tiles of 64 rows, halved down to 16 while the tensor would give the chip fewer
+// than two workgroups per CU (11008 x 4096: 16, 32 and 64 rows 35.5 us, 128, the last of whose workgroups run alone, 45; 4096 x 4096 at
+// 32, 64 and 128 14.4, 13.8, 19; 200 x 16000 at 16, 32 and 64 5.8, 5.6, 6.4).  Tall ones take more: atomics on one column's maximum
+// follow each other (3000 x 1001 at 16, 32 and 64 8.2, 6.3, 6.5 us; 16384 x 80 at 64, 128 and 256 7.8, 6.5, 7.6).
 int launch_maxima(const QuantArgs& q, int n_cu, hipStream_t s) {
     hipLaunchKernelGGL(clear_two_kernel, dim3(grid_for(q.rows + q.cols, 4, 1024)), dim3(kThreads), 0, s, q.sa, q.rows, q.sb,
                        q.cols);
     LPMM_HIP(hipGetLastError());
+    const bool narrow = q.cols <= 16 * kMaxCols;
+    const int64_t strip = (narrow ? 16 : 32) * kMaxCols;
     MaxTiling t;
-    t.tx_log2 = kMaxMinTxLog2;
-    while (t.tx_log2 < 8 && (int64_t(4) << t.tx_log2) < q.cols) ++t.tx_log2;
-    const int ty = kThreads >> t.tx_log2;
-    const int64_t strips = (q.cols + (4 << t.tx_log2) - 1) / (4 << t.tx_log2);
-    int64_t per = std::min<int64_t>(32 * ty, kMaxTileRows);
-    while (per > 4 * ty && strips * ((q.rows + per - 1) / per) < 4 * int64_t(n_cu)) per /= 2;
-    t.strips = int(strips);
+    t.strips = int((q.cols + strip - 1) / strip);
+    auto tiles = [&](int64_t per) { return t.strips * ((q.rows + per - 1) / per); };
+    int64_t per = 64;
+    while (per > 16 && tiles(per) < 2 * int64_t(n_cu)) per /= 2;
+    while (per < kMaxTileRows && per * per < q.rows / 3) per *= 2;
     t.rows_per_wg = int(per);
-    hipLaunchKernelGGL(quant_v_max_kernel, dim3(unsigned(strips * ((q.rows + per - 1) / per))), dim3(kThreads), 0, s, q, t);
+    const dim3 grid(unsigned(tiles(per))), block(kThreads);
+    if (narrow) hipLaunchKernelGGL(quant_v_max_kernel<16>, grid, block, 0, s, q, t);
+    else hipLaunchKernelGGL(quant_v_max_kernel<32>, grid, block, 0, s, q, t);
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
 }

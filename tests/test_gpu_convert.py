@@ -1,5 +1,5 @@
-"""Stand-alone compress / decompress at the edges of their tiles: 4 elements per lane, 4096 per workgroup, strips of 64 to
-1024 columns and up to 512 rows for the maxima; arrays at 4-byte alignment; nothing written behind a buffer's end; a NaN
+"""Stand-alone compress / decompress at the edges of their tiles: 4 elements per lane, 4096 per workgroup, strips of 128 or
+256 columns and 16 to 512 rows for the maxima; arrays at 4-byte alignment; nothing written behind a buffer's end; a NaN
 costs no other element its code."""
 import numpy as np
 import pytest
@@ -110,3 +110,27 @@ def test_nan_raises_no_block_scale(what):
     got, want = (oracle.unpack_codes(c, P) for c in (codes.cpu().numpy(), want_codes))
     np.testing.assert_array_equal(got[~bad.reshape(-1)], want[~bad.reshape(-1)])
     assert (got[bad.reshape(-1)] == 0).all()
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (16, 8), (17, 9), (33, 128), (31, 136), (65, 264), (300, 519), (5, 2049), (12289, 129), (800001, 3)])
+def test_maxima_at_the_edges_of_their_tiles(rows, cols):
+    """Lanes repeat the last 8 columns and rows the last one; 16 lanes a row up to 128 columns, 32 beyond; 16 to 512 rows a tile."""
+    print(f"[gpu-test] maxima {rows}x{cols}", flush=True)
+    lpmm.ensure_init(4096)
+    gen = torch.Generator(device=DEV).manual_seed(rows + cols)
+    v = torch.rand(rows, cols, generator=gen, device=DEV)
+    v[torch.rand(rows, cols, generator=gen, device=DEV) < 0.01] = float("nan")
+    v[torch.rand(rows, cols, generator=gen, device=DEV) < 0.01] = -0.0
+    v[rows // 2] = -1.0
+    v[:, cols // 3] *= -1.0
+    v[-1, -1], v[0, 0] = 3.0, 2.0
+    z = torch.where(v > 0, v, torch.zeros_like(v))
+    for words in (0, 1):
+        buf = torch.empty(rows * cols + 8, device=DEV)
+        x = buf[words:words + rows * cols]
+        x.copy_(v.reshape(-1))
+        codes = torch.zeros((rows * cols + 7) // 8 * 4, dtype=torch.uint8, device=DEV)[:(rows * cols + 1) // 2]
+        r, c = torch.full((rows + 1,), -5.0, device=DEV), torch.full((cols + 1,), -5.0, device=DEV)
+        lpmm.lpmm_quant_state(1, x, rows, cols, codes, r[:rows], c[:cols])
+        assert torch.equal(r[:rows], z.amax(1)) and torch.equal(c[:cols], z.amax(0))
+        assert r[rows] == -5.0 and c[cols] == -5.0

@@ -323,9 +323,15 @@ bool ragged_eligible(int64_t rows, int64_t cols) {
 
 // Tiling of the ragged path (see ragged.hpp): the first pass takes statistics of strips of 256 columns by rw2 rows, the second
 // updates whole blocks.
-// Update, cols <= 1024: tiles of 8 to 128 consecutive blocks.  Wider: strips of equal width, at most 1024 columns, by 32
+// Update, cols <= 1024: tiles of 8 to 128 consecutive blocks.  Wider: strips of equal width, at most 1024 columns, by `tall`
 // rows; the rows are halved down to one per group and then the strips down to 256 columns.  Both shrink while the tensor
-// would give the chip fewer than two workgroups per CU (n_cu = 0: `shrink` halvings instead, for plans).
+// would give the chip fewer than two workgroups per CU (n_cu = 0: `shrink` halvings instead, for plans, of 32 rows).
+// Low tiles end more evenly and touch fewer distant rows at a time, but a workgroup stages its columns' statistics for fewer of them.
+// A tensor on its own takes 8 rows (update alone, bf16 gradients, us at 8 / 16 / 32: 1024 x 50257 111 / 114 / 122, 12288 x 4099 102 / 103 /
+// 112, 3000 x 3001 23.4 / 27.2 / 27.1, 2000 x 3001 17.2 / 17.6 / 17.6; factorized 1024 x 50257 109 / 113 / 121, 4096 x 4099 37.2 / 36.0 / 42.2);
+// a plan by phases 16 from 3 * 2^22 parameters on (transformers of width 1088, 65 M, 148 / 138 / 150; 704, 15 M, 46 / 42 / 45;
+// 448, 12 M, 33.6 / 33.3 / 32.4; factorized 1472, 528 M, 1266 / 1276 / 1330 a step, 1088, 204 M, 501 / 506 / 558, 448 43.2 / 43.4 / 41.7);
+// one launch, where other tensors' tiles fill every gap, 32 (width 1088, 204 M, 647 / 608 / 583 a step; 704, fp32, 93 M, 306 / 297 / 292).
 // Statistics: 256 rows (plans: 128), halved down to 64 while there are fewer than 11/4 workgroups per CU (24178 x 808 bf16, 64 and 128
 // rows, 1512 and 756 tiles: 63.3 and 60.8 us per step; 50257 x 1088 bf16, 64, 128 and 256, the last 985 tiles: 161.9, 160.7, 158.6; but
 // 6025 x 6840 bf16, 64 and 256, 648 tiles: 123.3 and 125.9; 8678 x 776 bf16, 64 and 128, 272 tiles: 30.0 and 31.6), then down to 8 while
@@ -333,7 +339,8 @@ bool ragged_eligible(int64_t rows, int64_t cols) {
 // at about 18 ns, so a tall narrow matrix takes more rows to a tile than the filling of the chip alone would ask for: rows / rw2 of them against a quarter of rw2 rows, about 0.3 us each, one
 // after the other in a wave balance at rw2 = sqrt(rows / 4) (factorized form of 2000 x 190 with fp32 gradients: 16.5 us per
 // step, 29.8 without this).
-void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
+constexpr int64_t kRagTall = 32, kRagPhase = 16, kRagAlone = kGroups, kRagPhaseParams = int64_t(3) << 22;
+void ragged_geometry(Tensor4* a, int n_cu, int64_t tall, int shrink = 0) {
     a->nb = int(a->P / LPMM_BLOCK);
     const int tail = (a->P % LPMM_BLOCK) ? 1 : 0;
     constexpr int64_t kWide = kFlatBlocks * LPMM_BLOCK;
@@ -345,9 +352,9 @@ void ragged_geometry(Tensor4* a, int n_cu, int shrink) {
         a->rw = int(rw);
         a->n_wg2 = int((a->nb + rw - 1) / rw) + tail;
     } else {
-        int64_t rw = 32, sw = kWide, tiles;
+        int64_t rw = tall, sw = kWide, tiles;
         while (rw > kGroups && rw * a->cols > (int64_t(1) << 28)) rw /= 2;        // byte offsets inside a tile stay below 2^30
-        for (int k = 0; k < shrink && rw > kGroups; ++k) rw /= 2;
+        rw = std::max<int64_t>(std::min<int64_t>(rw, kRagTall >> shrink), kGroups);
         for (;;) {
             const int64_t want = (a->cols + sw - 1) / sw;
             a->sw = int(round_up((a->cols + want - 1) / want, LPMM_BLOCK));
@@ -401,7 +408,7 @@ void rank1_geometry(Tensor4* t, int n_cu, int grad_bytes) {
         rank1_fast_geometry(t, n_cu, 0, 0, grad_bytes);
     } else if (ragged_eligible(t->rows, t->cols)) {
         t->kind = kQuantRagged;
-        ragged_geometry(t, n_cu, 0);
+        ragged_geometry(t, n_cu, kRagAlone);
     } else {
         t->kind = kQuantGeneral;
         general_geometry(t, n_cu);
@@ -683,7 +690,7 @@ int64_t det_partial_floats(int64_t rows, int64_t cols) {
 }
 
 void factor_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes, bool fast,
-                     int tot_slots, int shrink = 0) {
+                     int tot_slots, int shrink = 0, int64_t tall = kRagTall) {
     a->tot_slots = tot_slots;
     a->kind = fast ? kFactorFast : kFactorGeneral;
     if (fast) {
@@ -701,7 +708,7 @@ void factor_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, in
         std::swap(a->n_wg, a->n_wg2);
         a->kind = kFactorFast;
     } else if (!a->det && ragged_eligible(a->rows, a->cols)) {
-        ragged_geometry(a, rw_hint == 0 ? n_cu : 0, shrink);
+        ragged_geometry(a, rw_hint == 0 ? n_cu : 0, tall, shrink);
         a->kind = kFactorRagged;
     } else {
         general_geometry(a, n_cu);          // statistics pass: several chunks per workgroup; update pass: one
@@ -741,7 +748,7 @@ int factor_step_impl(bool bf16, void* param, const void* grad, uint8_t* m_codes,
     t.cols = cols;
     t.P = rows * cols;
     const bool fast = fast_eligible(cols, v_col);
-    factor_geometry(&t, ctx->n_cu, 0, 0, bf16 ? 2 : 4, fast, kMaxTotSlots);
+    factor_geometry(&t, ctx->n_cu, 0, 0, bf16 ? 2 : 4, fast, kMaxTotSlots, 0, kRagAlone);
     set_skew(&t);
     const bool ragged = t.kind == kFactorRagged;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -894,7 +901,7 @@ void flow_geometry(Tensor4* t, int desc_kind, bool aligned_c, int64_t total, int
         rank1_fast_geometry(t, 0, rw, rw2, grad_bytes, shrink ? 1 : 0);
     } else if (ragged_eligible(t->rows, t->cols)) {
         t->kind = kQuantRagged;
-        ragged_geometry(t, 0, !shrink ? 0 : total >= kFlowNdLate ? 2 : 3);
+        ragged_geometry(t, 0, kRagTall, !shrink ? 0 : total >= kFlowNdLate ? 2 : 3);
     } else {
         t->kind = kQuantGeneral;
         general_geometry(t, kCus);
@@ -1752,6 +1759,9 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     host->d_hyper = reinterpret_cast<Hyper*>(dplan + L.off_hyper);
     unsigned int* d_counters = reinterpret_cast<unsigned int*>(dplan + L.off_counters);
 
+    int64_t all_params = 0;
+    for (int64_t i = 0; i < n; ++i) all_params += descs[i].rows * descs[i].cols;
+    const int64_t tall = all_params >= kRagPhaseParams ? kRagPhase : kRagTall;      // ragged_geometry
     const int64_t rw_hint = env_int("LPMM_MULTI_RW", -1);      // -1: the plan defaults (see the geometries)
     const int64_t rw2_hint = env_int("LPMM_MULTI_RW2", 128);
     // parameters per group of consecutive tensors: large groups win (fewer kernel tails)
@@ -1761,10 +1771,8 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         // every group up to the table size (292 tensors of 354 M parameters: 190 M + 164 M parameters measured 0.895
         // ms per step, the first 192 tensors + the rest, 254 M + 100 M, 0.905).  The tenth on top keeps the greedy fill
         // below from leaving a small group over.
-        int64_t total = 0;
-        for (int64_t i = 0; i < n; ++i) total += descs[i].rows * descs[i].cols;
         const int64_t k = (n + kMaxSeg - 1) / kMaxSeg;
-        group_params = std::min(group_params, total / k + total / (10 * k) + 1);
+        group_params = std::min(group_params, all_params / k + all_params / (10 * k) + 1);
     }
     // Tiling of one quantized tensor of the plan.  shrink = 0 gives the plan's default tiles (sized for sets that
     // fill the chip many times over); each further level halves the rows (blocks) a workgroup takes, for groups of
@@ -1780,11 +1788,11 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         } else if (d.kind == LPMM_KIND_4BIT_B128) {
             b128_geometry(&t, ctx->n_cu, rounds_s);
         } else if (d.kind == LPMM_KIND_4BIT_FACTOR) {
-            factor_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1, shrink);
+            factor_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1, shrink, tall);
         } else if (t.kind == kQuantFast) {
             rank1_fast_geometry(&t, 0, rw_hint > 0 ? rw_hint : 0, std::max<int64_t>(rw2_hint >> shrink, kGroups), gbytes, shrink);
         } else if (t.kind == kQuantRagged) {
-            ragged_geometry(&t, 0, shrink);
+            ragged_geometry(&t, 0, tall, shrink);
         }
     };
     int64_t fofs = 0;

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kThreads, FORM == kFlowRank1 ? 5 : FORM == kFlowRan
                 sync.staged();
             };
             if constexpr (FACTOR) {
-                if (a.kind == kFactorFast) factor_update_tile<BF16, true>(a, h, wg, s, sync);
+                if (a.kind == kFactorFast) factor_update_tile_down<BF16, true>(a, h, wg, s, sync);
                 else behind([&] {
                     load_tables(s);
                     factor_update_general_tile<BF16, true>(a, h, wg, s);

@@ -913,28 +913,50 @@ __device__ __forceinline__ void update_unit(const Tensor4& a, const Hyper& h, co
     if (l == 0) s.blk_scale[il * kFlatBlocks + j] = s_new;
 }
 
+// Where a workgroup of an update works, and the units in the order its groups take them: unit q = block q % nbk of the group's row
+// number q / nbk.
+struct FlatTile {
+    int cb0, nbk;                // the strip's first column block, and its blocks, 1..8
+    int pl, per, rs, slice0;     // rows of a group, a power of two; 2^(rs - pl) workgroups share a super-tile
+    int n;                       // rows of the super-tile
+    int grp, l, row_g, nq;
+    int64_t row0;
+    uint32_t inv_nbk, lane4, pitch4;
+    __device__ __forceinline__ FlatTile(const Tensor4& a, int wg) {
+        const int strip = wg % a.strips, tile = wg / a.strips;
+        grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+        cb0 = strip * a.gx;
+        nbk = a.nb - cb0 < a.gx ? a.nb - cb0 : a.gx;
+        pl = __builtin_ctz(a.rw) - 3, per = 1 << pl, rs = a.rs;
+        row0 = int64_t(tile >> (rs - pl)) << (rs + 3);
+        slice0 = (tile & ((1 << (rs - pl)) - 1)) << pl;
+        const int64_t left = a.rows - row0;
+        n = left < (kGroups << rs) ? int(left) : kGroups << rs;
+        nq = per * nbk;
+        inv_nbk = (65536u + uint32_t(nbk) - 1u) / uint32_t(nbk);         // q / nbk == (q * inv_nbk) >> 16 for q < 9000
+        row_g = grp * per;
+        lane4 = row_offset((grp << rs) + slice0, a.cols, uint32_t(cb0) * 128u + uint32_t(l) * 4u) * 4u;
+        pitch4 = uint32_t(a.cols) * 4u;
+    }
+    // of the tile's il-th row, in the super-tile
+    __device__ __forceinline__ int row_of(int il) const { return (il >> pl << rs) + slice0 + (il & (per - 1)); }
+    __device__ __forceinline__ int krow(int q) const { return int((uint32_t(q) * inv_nbk) >> 16); }
+    __device__ __forceinline__ uint32_t off(int q) const {
+        return q < nq ? lane4 + (uint32_t(krow(q)) * pitch4 + uint32_t(q - krow(q) * nbk) * 512u) : kNowhere;
+    }
+};
+
 // SAME_LAUNCH: the first pass of the tensor runs in the same launch.
 template <bool BF16, bool SAME_LAUNCH, class Sync>
 __device__ __forceinline__ void update_tile(const Tensor4& a, const Hyper& h, int wg, LdsRank1& s, Sync& sync) {
     const TableRegs tables = request_tables();
-    const int strip = wg % a.strips, tile = wg / a.strips;
-    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
-    const int cb0 = strip * a.gx;
-    const int nbk = a.nb - cb0 < a.gx ? a.nb - cb0 : a.gx;               // blocks of this strip, 1..8
-    const int pl = __builtin_ctz(a.rw) - 3, per = 1 << pl;               // rows of a group, a power of two
-    const int64_t row0 = int64_t(tile >> (a.rs - pl)) << (a.rs + 3);     // 2^(rs - pl) workgroups share a super-tile
-    const int slice0 = (tile & ((1 << (a.rs - pl)) - 1)) << pl;
-    const int64_t left = a.rows - row0;
-    const int n = left < (kGroups << a.rs) ? int(left) : kGroups << a.rs;    // rows of the super-tile
+    const FlatTile f(a, wg);
+    const int cb0 = f.cb0, nbk = f.nbk, n = f.n, nq = f.nq, l = f.l, row_g = f.row_g;
+    const int64_t row0 = f.row0;
     const TileBase tb = tile_base<BF16>(a, row0, n);
-    auto row_of = [&](int il) { return (il >> pl << a.rs) + slice0 + (il & (per - 1)); };    // of the tile's il-th row, in the super-tile
-    // units in the order the groups take them: unit q = block q % nbk of the group's row number q / nbk
-    const int nq = per * nbk;
-    const uint32_t inv_nbk = (65536u + uint32_t(nbk) - 1u) / uint32_t(nbk);   // q / nbk == (q * inv_nbk) >> 16 for q < 9000
-    auto krow = [&](int q) { return int((uint32_t(q) * inv_nbk) >> 16); };
-    const int row_g = grp * per;
-    const uint32_t lane4 = row_offset((grp << a.rs) + slice0, a.cols, uint32_t(cb0) * 128u + uint32_t(l) * 4u) * 4u, pitch4 = uint32_t(a.cols) * 4u;
-    auto off = [&](int q) { return q < nq ? lane4 + (uint32_t(krow(q)) * pitch4 + uint32_t(q - krow(q) * nbk) * 512u) : kNowhere; };
+    auto row_of = [&](int il) { return f.row_of(il); };
+    auto krow = [&](int q) { return f.krow(q); };
+    auto off = [&](int q) { return f.off(q); };
     auto fetch = [&](int q) { return load_row1<BF16, kPolicyNt>(tb, off(q)); };        // the gradient's last use in the step
     // Start-up: everything a workgroup needs before its first unit is requested before any of it is waited for, one round
     // trip in front of ready() and one behind it.  Thread t takes columns 4t .. 4t+3 of the strip, blocks t and t + 256 and row t.
@@ -1650,16 +1672,16 @@ __device__ __forceinline__ RowF<BF16> load_rowf(const TileBase& b, uint32_t off4
     return r;
 }
 
-// One row of the update pass for one lane; ct[e] = C_t of the lane's columns.  The row's old block scale and
-// R_t[i] / sum R_t come from LDS, where the tile staged them (see update_tile).
+// One unit (a row of one column block) of the update pass for one lane; ct[e] = C_t of the lane's columns.  The unit's old block scale
+// and the row's R_t[i] / sum R_t (rn) come from LDS, where the tile staged them (see update_tile).
 template <bool BF16, class Mid>
-__device__ __forceinline__ void factor_row(const Hyper& h, const TileBase& tb, const Geo& geo, Lds& s,
-                                           const RowF<BF16>& cur, uint32_t off4, int slot, const float ct[4], Mid mid) {
+__device__ __forceinline__ void factor_unit(const Hyper& h, const TileBase& tb, Lds& s, const RowF<BF16>& cur, uint32_t off4, int slot,
+                                            float rn, const float ct[4], int l, Mid mid) {
     float w[4] = {cur.p.x, cur.p.y, cur.p.z, cur.p.w};
     float g[4];
     unpack_grad4<BF16>(cur.g, g);
     float mt[4], amax = 0.0f;
-    const float s_old = s.blk_scale[slot], rn = s.blk_vmax[slot];
+    const float s_old = s.blk_scale[slot];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const float2 t = s.deq[(uint32_t(cur.mq) >> (8 * k)) & 255u];
@@ -1673,17 +1695,76 @@ __device__ __forceinline__ void factor_row(const Hyper& h, const TileBase& tb, c
         amax = fmaxf(amax, fabsf(mt[e]));
     }
     __builtin_amdgcn_sched_barrier(0);
-    mid();                                    // the caller's prefetch (see update_tile)
+    mid();                                    // the caller's prefetch (see update_unit)
     __builtin_amdgcn_sched_barrier(0);
     const float s_new = group32_allmax(amax);
-
     store_row1(tb, off4, w, compress_m4(s.search, mt, s_new));
-    if (geo.l == 0) s.blk_scale[slot] = s_new;
+    if (l == 0) s.blk_scale[slot] = s_new;
 }
 
-// Update pass, fast path: a group walks down the rows of one column block.
-template <bool BF16, bool SAME_LAUNCH, class Sync>
+// Update pass, fast path, of a tensor stepped on its own: the tiles of update_tile.  s.cold holds C_t of the strip's columns, s.blk_vmax
+// R_t[i] / sum R_t of the tile's rows.
+template <bool BF16, class Sync>
 __device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper& h, int wg, Lds& s, Sync& sync) {
+    const TableRegs tables = request_tables();
+    const FlatTile f(a, wg);
+    const TileBase tb = tile_base<BF16>(a, f.row0, f.n);
+    auto fetch = [&](int q) { return load_rowf<BF16>(tb, f.off(q)); };
+    // start-up as in update_tile: thread t takes columns 4t .. 4t+3 of the strip, blocks t and t + 256 and row t
+    const int t = threadIdx.x;
+    const uint32_t strip_bytes = uint32_t(f.nbk) * 512u;
+    const float4 c_old = buf_ld_f4(tile_rsrc(a.c + f.cb0 * 128, strip_bytes), uint32_t(t) * 16u);
+    float ms_old[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int il = (t + u * kThreads) / kFlatBlocks, j = t % kFlatBlocks, row = f.row_of(il);
+        ms_old[u] = il < a.rw && row < f.n && j < f.nbk ? tb.ms[row_offset(row, a.nb, uint32_t(f.cb0 + j))] : 0.0f;
+    }
+    const bool row_in = t < a.rw && f.row_of(t) < f.n;
+    const float r_old = row_in ? tb.r[f.row_of(t)] : 0.0f;
+    const float4 c_sum = buf_ld_f4(tile_rsrc(a.c_new + f.cb0 * 128, strip_bytes), uint32_t(t) * 16u);
+    const float r_sum = row_in ? tb.r_new[f.row_of(t)] : 0.0f;
+    RowF<BF16> r0 = fetch(0), r1 = fetch(1), r2;
+    put_tables(s, tables);
+    s.blk_scale[t] = ms_old[0];
+    s.blk_scale[t + kThreads] = ms_old[1];
+    const float inv_total = factor_inv_total(a, h);
+    reinterpret_cast<float4*>(s.cold)[t] = make_float4(stat_ema(h, c_old.x, c_sum.x), stat_ema(h, c_old.y, c_sum.y),
+                                                       stat_ema(h, c_old.z, c_sum.z), stat_ema(h, c_old.w, c_sum.w));
+    if (t < a.rw) s.blk_vmax[t] = stat_ema(h, r_old, r_sum) * inv_total;
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);              // loop start-up state: nothing outstanding (see update_tile)
+    __syncthreads();
+    sync.staged();
+    auto none = [] {};
+    auto unit = [&](const RowF<BF16>& cur, int q, auto mid) {
+        const int k = f.krow(q), il = f.row_g + k, j = q - k * f.nbk;
+        float ct[4];
+        load4(&s.cold[j * 128 + f.l * 4], ct);
+        factor_unit<BF16>(h, tb, s, cur, f.off(q), il * kFlatBlocks + j, s.blk_vmax[il], ct, f.l, mid);
+    };
+    int q = 0;
+    while (q + 2 < f.nq) {                                // rounds of three units, no exit in the middle
+        unit(r0, q, [&] { r2 = fetch(q + 2); });
+        unit(r1, q + 1, [&] { r0 = fetch(q + 3); });
+        unit(r2, q + 2, [&] { r1 = fetch(q + 4); });
+        q += 3;
+    }
+    if (q < f.nq) {
+        unit(r0, q, none);
+        if (q + 1 < f.nq) unit(r1, q + 1, none);
+    }
+    __syncthreads();
+    for (int k = t; k < a.rw * kFlatBlocks; k += kThreads) {
+        const int row = f.row_of(k / kFlatBlocks), j = k % kFlatBlocks;
+        if (row < f.n && j < f.nbk) st<float>(tb.ms, row_offset(row, a.nb, uint32_t(f.cb0 + j)) * 4u, s.blk_scale[k]);
+    }
+}
+
+// The same in plans: a group walks down the rows of one column block.  (Along the rows, as above, a step takes in one launch with fp32
+// gradients, us, down / along: 354 M parameters 877 / 891, 380 M 975 / 1007, bert-like, 131 M, 338 / 354, llama-like, 75 M, 192 / 201, with bf16
+// ones 717 / 717, 821 / 816, 280 / 279; by phases, 640 wide, 71 / 74, 896 80 / 82, 1152 205 / 208, 512 75 / 72.5, 1280 369 / 354.)
+template <bool BF16, bool SAME_LAUNCH, class Sync>
+__device__ __forceinline__ void factor_update_tile_down(const Tensor4& a, const Hyper& h, int wg, Lds& s, Sync& sync) {
     const TableRegs tables = request_tables();
     const Geo geo = geometry(a, wg);
     const TileBase tb = tile_base<BF16>(a, geo.row0, geo.n_rows);
@@ -1727,7 +1808,8 @@ __device__ __forceinline__ void factor_update_tile(const Tensor4& a, const Hyper
     sync.staged();
     auto none = [] {};
     auto work = [&](const RowF<BF16>& cur, int k, auto mid) {
-        factor_row<BF16>(h, tb, geo, s, cur, off(k), slot0 + walk.at(k) * a.gx, ct, mid);
+        const int slot = slot0 + walk.at(k) * a.gx;
+        factor_unit<BF16>(h, tb, s, cur, off(k), slot, s.blk_vmax[slot], ct, geo.l, mid);
     };
     int k = 0;
     while (k + 2 < n) {

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kThreads) void factor_update_fast(const Tensor4 a, 
     const int wg = logical_wg(a.skew2);
     if (wg >= a.n_wg2) return;
     TicketSync sync{a.counter, unsigned(wg), 0u};
-    factor_update_tile<BF16, false>(a, h, wg, s, sync);
+    factor_update_tile<BF16>(a, h, wg, s, sync);
     if (ticket_is_last(a.counter, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last)) factor_publish(a, h);
 }
 
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, 
         const int wg = b_before - sg.wg_begin;
         NoSync sync;            // the ticket at the end: six of 1024 x 1024 fp32 26.1 us, 26.5 with it in the tile's middle
         if (a.kind == kFactorFast) {
-            factor_update_tile<BF16, false>(a, ht, wg, s, sync);
+            factor_update_tile_down<BF16, false>(a, ht, wg, s, sync);
         } else if (a.kind == kFactorRagged) {
             factor_update_ragged<BF16>(a, ht, wg, s);
         } else {

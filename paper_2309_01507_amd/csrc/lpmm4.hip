@@ -144,9 +144,6 @@ void set_skew(Tensor4* t) {
     t->skew2 = launch_skew(t->n_wg2, t->P);
 }
 
-// Geometry of the factorized form's fast path (its update tiles in the members of the first pass; the caller swaps them).  gx
-// column blocks share a workgroup, gy = 8/gx groups walk interleaved rows of the same column blocks.  rw_hint > 0 fixes the
-// rows per workgroup; otherwise they are chosen so that the tensor alone fills the chip.
 // log2 of the smallest S in {1, 2, 4, 8} for which S rows of `row_bytes` bytes are a multiple of 32 KiB; 0 if
 // there is none.  Rows in flight side by side then lie 32 KiB apart, which is what the memory system serves
 // fastest (measured).  S must divide `per_group`, the rows of a tile that one group (or wave) takes: only
@@ -162,58 +159,15 @@ int row_spacing_log2(int64_t row_bytes, int64_t rows_per_tile, int groups, const
     return 0;
 }
 
-void fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes) {
-    a->nb = int(a->cols / LPMM_BLOCK);
-    int gx = env_int("LPMM_GX", 1);
-    if (gx < 1 || gx > kGroups || (gx & (gx - 1))) gx = 1;
-    while (gx > 1 && (a->nb % gx) != 0) gx >>= 1;
-    a->gx = gx;
-    a->gy = kGroups / gx;
-    a->strips = a->nb / gx;
-    int64_t rw = env_int("LPMM_RW", 0);
-    if (rw <= 0) rw = rw_hint < 0 ? 64 : rw_hint;       // rw_hint: 0 = a tensor on its own (sized below), -1 = in a plan
-    if (rw <= 0) {
-        // tall tiles amortize a workgroup's start-up and its column atomics; shrink them only as
-        // far as needed to give every CU a couple of workgroups
-        rw = 64;
-        while (rw > a->gy && a->strips * ((a->rows + rw - 1) / rw) < 2 * int64_t(n_cu)) rw >>= 1;
-    }
-    const int64_t cap = (int64_t(1) << 29) / a->cols;     // lane offsets inside a tile stay below 2^31 bytes
-    if (rw > cap) rw = cap;
-    if (rw * gx > kMaxRowSlots) rw = kMaxRowSlots / gx;    // per-row results of a tile are staged in LDS
-    rw = round_up(rw, a->gy);
-    if (rw > cap || rw * gx > kMaxRowSlots) rw -= a->gy;
-    if (rw > a->rows) rw = round_up(a->rows, a->gy);
-    if (rw < a->gy) rw = a->gy;
-    a->rw = int(rw);
-    a->n_wg = int(a->strips * ((a->rows + rw - 1) / rw));
-    a->rs = row_spacing_log2(a->cols * 4, rw, a->gy, "LPMM_RS");      // the parameters' rows
-    // statistics pass: strips of 256 columns, a wave per row
-    a->strips2 = (a->nb + 1) / 2;
-    int64_t rw2 = env_int("LPMM_RW2", 0);
-    if (rw2 <= 0) rw2 = rw2_hint;
-    if (rw2 <= 0) {
-        rw2 = 64;
-        while (rw2 > kWaves && a->strips2 * ((a->rows + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 >>= 1;
-    }
-    if (rw2 > cap) rw2 = cap;
-    if (rw2 > kMaxRw2) rw2 = kMaxRw2;
-    if (rw2 > a->rows) rw2 = a->rows;
-    if (rw2 < 1) rw2 = 1;
-    a->rw2 = int(rw2);
-    a->n_wg2 = int(a->strips2 * ((a->rows + rw2 - 1) / rw2));
-    a->rs2 = row_spacing_log2(a->cols * grad_bytes, rw2, kWaves, "LPMM_RS2");   // that pass only reads the gradient
-}
-
 // Geometry of the rank-1 step on the fast path.
 // First pass (maxima): strips of 256 columns by rw2 rows.  Second pass (update): strips of gx (at most 8) column blocks by rw
 // rows.  n_cu > 0: a tensor stepped on its own, whose tiles are cut until the update has two workgroups per CU and the first pass
 // one (two of shorter tiles end with twice the column atomics: 2048 x 1024 bf16 15.8 us per step with two, 15.1 with one; 768 x
 // 3072 and 1024 x 1024 the same); else `shrink` halvings of a plan's tiles.
-void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes, int shrink = 0) {
+void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes, int shrink = 0, int widest = kFlatBlocks) {
     a->nb = int(a->cols / LPMM_BLOCK);
     const int64_t cap = std::max<int64_t>((int64_t(1) << 29) / a->cols, kGroups);     // lane offsets inside a tile stay below 2^31 bytes
-    const int n_strips = (a->nb + kFlatBlocks - 1) / kFlatBlocks;
+    const int n_strips = (a->nb + widest - 1) / widest;
     int gx = (a->nb + n_strips - 1) / n_strips;
     const int gx_env = env_int("LPMM_GX", 0);
     if (gx_env > 0) gx = std::min(gx_env, kFlatBlocks);
@@ -250,7 +204,7 @@ void rank1_fast_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint
     while (per_log2 > 0 && ((int64_t(kGroups) << per_log2) * a->cols) >= (int64_t(1) << 29)) --per_log2;
     // two workgroups per CU, three while a group has more than 8 blocks (3072 x 3072 bf16 576 tiles 35.3 us, 1152 32.8; 4096 x 2048
     // 512 27.8, 1024 26.5)
-    if (n_cu > 0) { while (tiles() < ((gx << per_log2) > kFlatBlocks ? 3 : 2) * int64_t(n_cu) && cut()) {} }
+    if (n_cu > 0) { while (tiles() < ((gx << per_log2) > kFlatBlocks || widest < kFlatBlocks ? 3 : 2) * int64_t(n_cu) && cut()) {} }
     for (int k = 0; k < shrink && cut(); ++k) {}
     a->gx = gx;
     a->gy = kGroups;
@@ -689,24 +643,62 @@ int64_t det_partial_floats(int64_t rows, int64_t cols) {
     return strips2 * round_up(rows, 64) + tiles * round_up(cols, 64) + round_up(2 * row_wgs, 64);
 }
 
+// Tiles of the factorized form's update in plans, see factor_update_tile_down: gx column blocks share a workgroup, gy = 8 / gx groups walk
+// interleaved rows of the same column blocks.
+void factor_down_geometry(Tensor4* a, int64_t rw, int64_t cap) {
+    int gx = env_int("LPMM_GX", 1);
+    if (gx < 1 || gx > kGroups || (gx & (gx - 1))) gx = 1;
+    while (gx > 1 && (a->nb % gx) != 0) gx >>= 1;
+    a->gx = gx;
+    a->gy = kGroups / gx;
+    a->strips = a->nb / gx;
+    if (const int forced = env_int("LPMM_RW", 0); forced > 0) rw = forced;
+    if (rw > cap) rw = cap;
+    if (rw * gx > kMaxRowSlots) rw = kMaxRowSlots / gx;    // per-row results of a tile are staged in LDS
+    rw = round_up(rw, a->gy);
+    if (rw > cap || rw * gx > kMaxRowSlots) rw -= a->gy;
+    if (rw > a->rows) rw = round_up(a->rows, a->gy);
+    if (rw < a->gy) rw = a->gy;
+    a->rw = int(rw);
+    a->n_wg2 = int(a->strips * ((a->rows + rw - 1) / rw));
+    a->rs = row_spacing_log2(a->cols * 4, rw, a->gy, "LPMM_RS");      // the parameters' rows
+}
+
+// Widest strips, in column blocks, of the update of a tensor on its own, whose tiles are those of the rank-1 form: 8 from 2^25 elements on,
+// else 4 (us at 4 and 8, bf16: 3000 x 3072 23.1, 24.1; 4096 x 4096 33.6, 33.5; 12288 x 4096 90.5, 89.3).  Strips of unequal width cost more
+// than that: the widest that wastes at most a sixteenth, from 3 blocks on, or else a wider one (fp32, a step: 20000 x 640 in strips of 3 + 2
+// 54.4, of 5 51.0; 30000 x 1152 of 5 + 4 111.1, of 3 107.4).
+// A step walking down the rows of one column block, as in plans, and now: 1024 x 1024 bf16 15.0, 14.4; 2500 x 1024 18.4, 16.9; 12288 x
+// 4096 112.3, 109.9; 4096 x 11008 109.6, 105.8; 200 x 25600 34.0, 28.7.
+int factor_widest(const Tensor4& a) {
+    const int most = a.P >= int64_t(1) << 25 ? kFlatBlocks : kFlatBlocks / 2;
+    auto even = [&](int w) { return round_up(a.nb, w) - a.nb <= a.nb / 16; };
+    for (int w = most; w >= 3; --w) if (even(w)) return w;
+    for (int w = most + 1; w <= kFlatBlocks; ++w) if (even(w)) return w;
+    return most;
+}
+
+// rw_hint: rows of a plan's update tiles, 0 for a tensor on its own.  Statistics: strips of 256 columns by rw2 rows, a wave per row.
 void factor_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, int grad_bytes, bool fast,
                      int tot_slots, int shrink = 0, int64_t tall = kRagTall) {
     a->tot_slots = tot_slots;
     a->kind = fast ? kFactorFast : kFactorGeneral;
     if (fast) {
-        fast_geometry(a, n_cu, rw_hint, rw2_hint, grad_bytes);
-        if (a->det) {
-            a->rw2 = int(std::min<int64_t>(kDetStatRows, a->rows));
-            a->n_wg2 = int(a->strips2 * ((a->rows + kDetStatRows - 1) / kDetStatRows));
-            a->rs2 = row_spacing_log2(a->cols * grad_bytes, a->rw2, kWaves, "LPMM_RS2");
+        const int64_t cap = (int64_t(1) << 29) / a->cols;         // lane offsets inside a tile stay below 2^31 bytes
+        a->nb = int(a->cols / LPMM_BLOCK);
+        if (rw_hint > 0) factor_down_geometry(a, rw_hint, cap);
+        else rank1_fast_geometry(a, n_cu, 0, 0, grad_bytes, 0, factor_widest(*a));
+        a->strips2 = (a->nb + 1) / 2;
+        int64_t rw2 = env_int("LPMM_RW2", 0);
+        if (rw2 <= 0) rw2 = rw2_hint;
+        if (rw2 <= 0) {
+            rw2 = 64;
+            while (rw2 > kWaves && a->strips2 * ((a->rows + rw2 - 1) / rw2) < 2 * int64_t(n_cu)) rw2 >>= 1;
         }
-        if (a->rw2 > kMaxRowSlots) {          // row sums of a statistics tile are staged in LDS
-            a->rw2 = kMaxRowSlots;
-            a->n_wg2 = int(a->strips2 * ((a->rows + a->rw2 - 1) / a->rw2));
-            a->rs2 = row_spacing_log2(a->cols * grad_bytes, a->rw2, kWaves, "LPMM_RS2");
-        }
-        std::swap(a->n_wg, a->n_wg2);
-        a->kind = kFactorFast;
+        rw2 = a->det ? std::min<int64_t>(kDetStatRows, a->rows) : std::max<int64_t>(std::min<int64_t>({rw2, cap, kMaxRw2, a->rows}), 1);
+        a->rw2 = int(rw2);
+        a->n_wg = int(a->strips2 * ((a->rows + rw2 - 1) / rw2));
+        a->rs2 = row_spacing_log2(a->cols * grad_bytes, rw2, kWaves, "LPMM_RS2");     // that pass only reads the gradient
     } else if (!a->det && ragged_eligible(a->rows, a->cols)) {
         ragged_geometry(a, rw_hint == 0 ? n_cu : 0, tall, shrink);
         a->kind = kFactorRagged;
@@ -1779,7 +1771,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     // tensors that are too small to give every CU a couple of workgroups (see below).
     const int gbytes = grad_dtype == LPMM_GRAD_BF16 ? 2 : 4;
     auto set_geometry = [&](Tensor4& t, const lpmm_tensor_desc& d, int shrink) {
-        const int64_t rw_s = std::max<int64_t>((rw_hint < 0 ? 64 : rw_hint) >> shrink, 8);
+        const int64_t rw_s = std::max<int64_t>((rw_hint <= 0 ? 64 : rw_hint) >> shrink, 8);
         const int64_t rw2_s = std::max<int64_t>(rw2_hint >> shrink, 4);
         const int64_t rounds_s = std::max<int64_t>(int64_t(env_int("LPMM_MULTI_B128_ROUNDS", 8)) >> shrink, 1);
         if (d.kind == LPMM_KIND_SGDM_4BIT) {
@@ -1788,7 +1780,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         } else if (d.kind == LPMM_KIND_4BIT_B128) {
             b128_geometry(&t, ctx->n_cu, rounds_s);
         } else if (d.kind == LPMM_KIND_4BIT_FACTOR) {
-            factor_geometry(&t, ctx->n_cu, shrink ? rw_s : rw_hint, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1, shrink, tall);
+            factor_geometry(&t, ctx->n_cu, rw_s, rw2_s, gbytes, fast_eligible(d.cols, d.v_colmax), 1, shrink, tall);
         } else if (t.kind == kQuantFast) {
             rank1_fast_geometry(&t, 0, rw_hint > 0 ? rw_hint : 0, std::max<int64_t>(rw2_hint >> shrink, kGroups), gbytes, shrink);
         } else if (t.kind == kQuantRagged) {

@@ -151,6 +151,13 @@ def test_other_launch_geometries(env):
     assert run(300, 1024, steps=3, env=env) == 0
 
 
+@pytest.mark.parametrize("rows,cols,bf16", [(1, 128, False), (9, 640, True), (67, 1152, False), (130, 1408, True), (33, 4224, False),
+                                            (1030, 512, True), (8200, 4224, False)])
+def test_strips_of_all_widths(rows, cols, bf16):
+    """Update tiles of a tensor on its own: strips of 3, 4, 5 and 8 blocks, of unequal width, super-tiles cut off."""
+    assert run(rows, cols, steps=2, bf16=bf16) == 0
+
+
 def test_first_moment_does_not_depend_on_the_launch_geometry():
     """The sums' order changes with the tiling, the first moment's bits must not."""
     rows, cols = 300, 1024

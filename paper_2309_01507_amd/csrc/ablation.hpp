@@ -11,7 +11,8 @@
 // that leaves a doubt does its four elements again with IEEE divisions and a search.  Of the rest most is SplitMix64: six 32-bit
 // multiplications, which run at a quarter of the rate.
 // Measured on 4096 x 4096, DE-0, stochastic rounding: compress under the three normalizations 43, 43 and 45 us with a division and a
-// search of four dependent LDS reads per element, 32, 32 and 38 this way (42 vector instructions an element); decompress 13.
+// search of four dependent LDS reads per element, 32, 32 and 38 this way (42 vector instructions an element); decompress 13.  SplitMix64
+// with its cross products as dot products of 16-bit halves, at the full rate, takes as long (all six calls 152.4 us, 153.3).
 #pragma once
 
 #include "convert.hpp"
@@ -220,15 +221,16 @@ __global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs
     }
 }
 
-// Rank-1 normalization, second stage: codes against min(r_i, c_j) (the maxima are complete in sa / sb)
-template <bool SR>
+// Rank-1 normalization, second stage: codes against min(r_i, c_j) (the maxima are complete in sa / sb).  Two runs in short tensors, whatever
+// the rounding (all six calls on 1000 x 1001 40.0 us with four, 37.9 so; 300 x 16000 to nearest 46.4 and 47.5, 7484 x 4483 265.4 and 267.2).
+template <bool SR, int UNITS>
 __global__ __launch_bounds__(kThreads) void abl_quant_rank1_kernel(const AblArgs a, const AblMap m) {
     __shared__ AblLds s_map;
-    const int64_t wg_first = int64_t(blockIdx.x) * kCvtElems;
+    const int64_t wg_first = int64_t(blockIdx.x) * (UNITS * kCvtUnitElems);
     const CvtOrigin o = cvt_origin(wg_first, a.cols);
-    float x[kCvtUnits][4], s[kCvtUnits][4];
+    float x[UNITS][4], s[UNITS][4];
 #pragma unroll
-    for (int u = 0; u < kCvtUnits; ++u) {
+    for (int u = 0; u < UNITS; ++u) {
         const uint32_t off = u * kCvtUnitElems + threadIdx.x * 4;
         cvt_load4(a.x_in, wg_first + off, a.P, x[u]);
         rank1_scales4(o, off, a.rows, a.sa, a.sb, s[u]);
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void abl_quant_rank1_kernel(const AblArgs
     abl_load_map(s_map, m);
     abl_load_buckets<SR>(s_map, m);
 #pragma unroll
-    for (int u = 0; u < kCvtUnits; ++u) {
+    for (int u = 0; u < UNITS; ++u) {
         const int64_t base = wg_first + u * kCvtUnitElems + threadIdx.x * 4;
         if (base >= a.P) continue;
         float inv[4];

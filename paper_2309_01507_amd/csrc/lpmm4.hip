@@ -1152,6 +1152,8 @@ int fill(void* dst, int64_t n, uint8_t value, int64_t last_index, uint8_t last, 
     return LPMM_OK;
 }
 
+int rank_grid(int64_t elems, int units) { return grid_for(elems, units * kCvtUnitElems / kThreads); }
+
 // Row and column maxima of q.x_in into q.sa / q.sb.  Tiles of 64 rows, halved down to 16 while the tensor would give the chip fewer
 // than two workgroups per CU (11008 x 4096: 16, 32 and 64 rows 35.5 us, 128, the last of whose workgroups run alone, 45; 4096 x 4096 at
 // 32, 64 and 128 14.4, 13.8, 19; 200 x 16000 at 16, 32 and 64 5.8, 5.6, 6.4).  Tall ones take more: atomics on one column's maximum
@@ -1534,7 +1536,8 @@ int lpmm_dequant_state(int which, const uint8_t* codes, const float* scale_a, co
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int grid = grid_for(q.P, kCvtElems / kThreads);
     if (which == 0) hipLaunchKernelGGL(dequant_m_kernel, dim3(grid), dim3(kThreads), 0, s, q);
-    else if (which == 1) hipLaunchKernelGGL(dequant_v_kernel, dim3(grid), dim3(kThreads), 0, s, q);
+    else if (which == 1 && q.P <= kRankShortElems) hipLaunchKernelGGL(dequant_v_kernel<2>, dim3(rank_grid(q.P, 2)), dim3(kThreads), 0, s, q);
+    else if (which == 1) hipLaunchKernelGGL(dequant_v_kernel<4>, dim3(rank_grid(q.P, 4)), dim3(kThreads), 0, s, q);
     else hipLaunchKernelGGL(dequant_vb_kernel, dim3(grid), dim3(kThreads), 0, s, q);
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
@@ -1568,7 +1571,8 @@ int lpmm_quant_state(int which, const float* in, const int64_t shape[2], uint8_t
     } else {
         const int r = launch_maxima(q, ctx->n_cu, s);
         if (r) return r;
-        hipLaunchKernelGGL(quant_v_code_kernel, dim3(grid), dim3(kThreads), 0, s, q);
+        if (q.P <= kRankShortElems) hipLaunchKernelGGL(quant_v_code_kernel<2>, dim3(rank_grid(q.P, 2)), dim3(kThreads), 0, s, q);
+        else hipLaunchKernelGGL(quant_v_code_kernel<4>, dim3(rank_grid(q.P, 4)), dim3(kThreads), 0, s, q);
         LPMM_HIP(hipGetLastError());
     }
     return LPMM_OK;
@@ -1676,8 +1680,11 @@ int lpmm_quant_ablation(int norm, int map, int is_signed, int rounding, uint64_t
     const bool shorter = a.stochastic && a.P <= kAblShortElems;
     const int blocks = shorter ? grid_for(a.P, 2 * kCvtUnitElems / kThreads) : grid;
     if (norm == LPMM_NORM_RANK1) {
-        if (a.stochastic) hipLaunchKernelGGL(abl_quant_rank1_kernel<true>, dim3(grid), dim3(kThreads), 0, s, a, m);
-        else hipLaunchKernelGGL(abl_quant_rank1_kernel<false>, dim3(grid), dim3(kThreads), 0, s, a, m);
+#define LPMM_RANK1(SR)                                                                                                                  \
+    if (a.P <= kAblShortElems) hipLaunchKernelGGL((abl_quant_rank1_kernel<SR, 2>), dim3(rank_grid(a.P, 2)), dim3(kThreads), 0, s, a, m); \
+    else hipLaunchKernelGGL((abl_quant_rank1_kernel<SR, kCvtUnits>), dim3(grid), dim3(kThreads), 0, s, a, m);
+        if (a.stochastic) { LPMM_RANK1(true) } else { LPMM_RANK1(false) }
+#undef LPMM_RANK1
     } else if (shorter) { LPMM_ABL_BLOCK(true, 2) }
     else if (a.stochastic) { LPMM_ABL_BLOCK(true, kCvtUnits) }
     else { LPMM_ABL_BLOCK(false, kCvtUnits) }

@@ -135,3 +135,15 @@ def test_values_around_entries_and_thresholds(norm, map_name, signed, stochastic
     if norm == "rank1":
         np.testing.assert_array_equal(sb.cpu().numpy(), want_sb)
     np.testing.assert_array_equal(oracle.unpack_codes(codes.cpu().numpy(), x.size), oracle.unpack_codes(want_codes, x.size))
+
+
+@pytest.mark.parametrize("stochastic", [False, True])
+@pytest.mark.parametrize("shape", [(3, 683), (2048, 1024), (2048, 1025)])
+def test_rank1_in_short_and_long_workgroups(shape, stochastic):
+    """Up to 2^21 elements a workgroup takes two runs of 1024, beyond four."""
+    x = _input(*shape, False, seed=shape[0] + shape[1])
+    want_codes, want_sa, want_sb = oracle.quant_ablation(x, "rank1", "de0", False, stochastic, 99)
+    codes, sa, sb = _gpu_quant(x, "rank1", "de0", False, stochastic, 99)
+    np.testing.assert_array_equal(sa.cpu().numpy(), want_sa)
+    np.testing.assert_array_equal(sb.cpu().numpy(), want_sb)
+    np.testing.assert_array_equal(oracle.unpack_codes(codes.cpu().numpy(), x.size), oracle.unpack_codes(want_codes, x.size))

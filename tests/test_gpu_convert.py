@@ -134,3 +134,23 @@ def test_maxima_at_the_edges_of_their_tiles(rows, cols):
         lpmm.lpmm_quant_state(1, x, rows, cols, codes, r[:rows], c[:cols])
         assert torch.equal(r[:rows], z.amax(1)) and torch.equal(c[:cols], z.amax(0))
         assert r[rows] == -5.0 and c[cols] == -5.0
+
+
+@pytest.mark.parametrize("rows,cols", [(3, 683), (2, 1025), (16384, 8192), (16385, 8193)])
+def test_second_moment_in_short_and_long_workgroups(rows, cols):
+    """Two runs of 1024 elements a workgroup up to 2^27 elements, four beyond.  Against the definitions in fp32: decompressed values
+    exactly, codes but for values within rounding of a boundary (two roundings of 2^-24 in 16 n, boundaries 1 apart: below 1e-6 of them)."""
+    print(f"[gpu-test] second moment {rows}x{cols}", flush=True)
+    lpmm.ensure_init(4096)
+    gen = torch.Generator(device=DEV).manual_seed(cols)
+    v = torch.rand(rows, cols, generator=gen, device=DEV)
+    n = rows * cols
+    codes = torch.zeros((n + 7) // 8 * 4, dtype=torch.uint8, device=DEV)[:(n + 1) // 2]
+    r, c, out = torch.zeros(rows, device=DEV), torch.zeros(cols, device=DEV), torch.full((n + 1,), -5.0, device=DEV)
+    lpmm.lpmm_quant_state(1, v, rows, cols, codes, r, c)
+    lpmm.lpmm_dequant_state(1, codes, r, c, rows, cols, out[:n])
+    q = torch.stack((codes & 15, codes >> 4), 1).reshape(-1)[:n].view(rows, cols).float()
+    scale = torch.minimum(r[:, None], c[None, :])
+    assert torch.equal(out[:n].view(rows, cols), (q + 1) * 0.0625 * scale) and out[n] == -5.0
+    want = torch.clamp(torch.ceil(16 * (v / scale) - 1.5), 0, 15)
+    assert int((want != q).sum()) <= 1e-6 * n

@@ -11,7 +11,8 @@
 // scales need only be 4-byte aligned: the wide accesses are typed so.
 // What is read for the last time and the decompressed values pass by the memory-side cache (non-temporal), which then still
 // holds what a later kernel reads again: the second moment for its codes, the codes and scales for the way back.  Both moments
-// of an 11008 x 4096 matrix there and back 232 -> 183 us (one-touch bytes at 4.5 TB/s), of 16384 x 8192 636 -> 520.
+// of an 11008 x 4096 matrix there and back 232 -> 183 us (one-touch bytes at 4.5 TB/s), of 16384 x 8192 636 -> 520; with the maxima's tiles
+// and the shorter workgroups below 170 (4.8 TB/s) and 505.
 // The decompressed values do so at every size: kept, they are written back during the kernels that follow.  Plain / non-temporal
 // stores: there and back 2048 x 2048 40 / 38 us, 4096 x 4096 92 / 79, 8192 x 4096 164 / 137, 11008 x 4096 231 / 183; decompression and a
 // kernel that scales the values into another array 16.6 / 16.8, 38.8 / 39.9, 69.9 / 65.2, 90.8 / 96.0.  Who only reads them, right

@@ -120,11 +120,15 @@ __device__ __forceinline__ uint32_t abl_stochastic(const AblLds& m, int n_entrie
 // Codes of 4 elements with scales s[e]; idx = row-major index of the first.
 //
 // The approximate n' = x * rcp(s) is within 2^-22 of the exact n, relatively; to nearest, the guard is that of the step's first
-// moment (kMinDistM).  For stochastic rounding the reciprocal is raised by 2^-22, so that n' of a block's largest element, once
-// clamped, is exactly 1, and n' is within 2^-21.  With the distance of neighbouring entries at least n / 17.8 everywhere, the
-// probability p' is then within 2^-16.8 of the exact one; the code can differ only if the random number is that close to it, or if
-// n' and n lie on different sides of an entry, which makes one of the two probabilities that close to 0 or 1.  Where x is its
-// own scale n' is exact and nothing is in doubt.  About one element in 10^4 is; extreme scales and NaN count as doubts.
+// moment (kMinDistM).  For stochastic rounding the reciprocal is raised by 2^-22, so that n' of a block's largest element comes out
+// as 1, and n' is within 2^-21.  With the distance of neighbouring entries at least n / 17.9 everywhere, the probability p' is then
+// within 2^-16.8 of the exact one, and the code can differ only if the random number is that close to it.  If n' and n lie on
+// different sides of an entry, one of the two probabilities is that close to 1 and the other to 0: either way the entry between them
+// is taken unless the random number itself is that close to 0 or 1.  So what counts as a doubt hangs on the random number alone, about
+// one element in 10^4 whatever the values; one that is 0, next to 0 or its own scale (n is an entry, or all but one) is no likelier.
+// (Where closeness of p' to 0 or 1 was a doubt, one zero under a map that has one sent its wave both ways: DE, 4096 x 4096,
+// stochastic rounding, block 128, 1 % zeros 47.7 us, 30 without; with division and search for everything 39.)  NaN comes out as
+// the first entry both ways; extreme scales count as doubts.
 constexpr float kMarginSr = 256.0f;          // 2^-16 in units of 2^-24
 template <bool SR>
 __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, float least, uint64_t seed, int64_t idx, const float x[4],
@@ -138,6 +142,7 @@ __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, f
         for (int e = 0; e < 4; ++e) u[e] = abl_uniform24(z0 + uint64_t(e) * kSplitMixStep);
     }
     uint32_t dist = 0xFFFFFFFFu;
+    float close = 0x1p24f, off_centre = 0.0f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float n = __builtin_amdgcn_fmed3f(x[e] * inv[e], least, 1.0f);
@@ -146,8 +151,8 @@ __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, f
         if constexpr (SR) {
             const float2 g = m.gap[below];          // n <= 1, the last entry, so below < kCodes
             const float p = (n - g.x) * g.y;
-            const float close = fminf(fminf(fabsf(u[e] - p), fabsf(p)), fabsf(0x1p24f - p));
-            doubt = bool(int(doubt) | (int(!(close >= kMarginSr)) & int(x[e] != s[e])));
+            close = fminf(close, fabsf(u[e] - p));
+            off_centre = fmaxf(off_centre, fabsf(u[e] - 0x1p23f));
             w |= (__builtin_elementwise_sub_sat(below, 1u) + (u[e] < p ? 1u : 0u)) << (4 * e);
         } else {
             uint32_t d;
@@ -156,6 +161,7 @@ __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, f
             w |= below << (4 * e);
         }
     }
+    if constexpr (SR) doubt = bool(int(doubt) | int(close < kMarginSr) | int(off_centre > 0x1p23f - kMarginSr));
     if constexpr (!SR) doubt = bool(int(doubt) | int(dist < kMinDistM));
     if (__builtin_expect(__ballot(doubt) != 0, 0)) {
         w = 0;

@@ -1613,7 +1613,7 @@ bool build_ablation_map(int map, int is_signed, AblMap* m) {
         while ((T[k] - T[k - 1]) * inv < 0x1p24f) inv = std::nextafterf(inv, std::numeric_limits<float>::infinity());
         m->inv_gap[i] = inv;
         // what the kernels' margins rest on
-        ok = ok && std::fabs(double(T[k])) <= 17.9 * (double(T[k]) - double(T[k - 1]));
+        ok = ok && std::max(std::fabs(double(T[k])), std::fabs(double(T[k - 1]))) <= 17.9 * (double(T[k]) - double(T[k - 1]));
     }
     return ok;
 }

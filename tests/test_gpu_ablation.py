@@ -147,3 +147,63 @@ def test_rank1_in_short_and_long_workgroups(shape, stochastic):
     np.testing.assert_array_equal(sa.cpu().numpy(), want_sa)
     np.testing.assert_array_equal(sb.cpu().numpy(), want_sb)
     np.testing.assert_array_equal(oracle.unpack_codes(codes.cpu().numpy(), x.size), oracle.unpack_codes(want_codes, x.size))
+
+
+@pytest.mark.parametrize("norm,map_name,signed", COMBOS)
+def test_stochastic_rounding_of_zeros_and_values_next_to_zero(norm, map_name, signed):
+    """Zeros of both signs, values down to the smallest subnormal ones, values a few units in the last place from an entry and NaN
+    among ordinary ones, under scales that let n = x / s underflow and such that do not: 2^21 elements, so that random numbers next to
+    0 and 1 (64 within 2^-16) meet all of them."""
+    print(f"[gpu-test] ablation next to zero {norm}/{map_name} signed={signed}", flush=True)
+    rng = np.random.default_rng(23)
+    T = lpmm.lpmm_ablation_table(MAP[map_name], signed)
+    rows, cols = 1024, 2048
+    n = np.exp2(-150 * rng.random((rows, cols))).astype(np.float32)
+    kind = rng.integers(0, 5, (rows, cols))
+    n[kind == 0] = 0
+    near = rng.choice(T, (rows, cols)) * (1 + rng.integers(-6, 7, (rows, cols)) * np.float32(2.0 ** -23))
+    n = np.where(kind == 1, np.minimum(near, 1), n).astype(np.float32)
+    n[kind == 2] = rng.random(int((kind == 2).sum()), dtype=np.float32)
+    if signed:
+        n = np.where(rng.random((rows, cols)) < 0.5, -n, n)
+    n[(kind == 0) & (rng.random((rows, cols)) < 0.5)] = -0.0
+    x = n * np.exp2(rng.integers(-90, 91, (rows, 1))).astype(np.float32)
+    if not signed:
+        x = np.maximum(x, np.float32(-0.0))
+    x[rng.random((rows, cols)) < 0.001] = np.nan
+    want_codes, want_sa, want_sb = oracle.quant_ablation(x, norm, map_name, signed, True, 4712)
+    codes, sa, sb = _gpu_quant(x, norm, map_name, signed, True, 4712)
+    np.testing.assert_array_equal(sa.cpu().numpy(), want_sa)
+    if norm == "rank1":
+        np.testing.assert_array_equal(sb.cpu().numpy(), want_sb)
+    np.testing.assert_array_equal(oracle.unpack_codes(codes.cpu().numpy(), x.size), oracle.unpack_codes(want_codes, x.size))
+
+
+@pytest.mark.parametrize("signed", [False, True])
+def test_zeros_cost_stochastic_rounding_no_second_route(signed):
+    """A value that is 0, or small against its scale, takes no longer than another: half of them zeros 30 us as without any, 48 where
+    every wave with one did its elements twice.  The best of several runs of 20, so that other work on the machine does not count."""
+    rows, cols = 4096, 4096
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    dense = torch.rand(rows, cols, generator=gen, device=DEV) + 0.01
+    if signed:
+        dense *= torch.where(torch.rand(rows, cols, generator=gen, device=DEV) < 0.5, -1.0, 1.0)
+    half = torch.where(torch.rand(rows, cols, generator=gen, device=DEV) < 0.5, dense, torch.zeros_like(dense))
+    small = dense * torch.where(torch.rand(rows, cols, generator=gen, device=DEV) < 0.5, 1.0, 1e-9)
+    codes, sa = torch.zeros(rows * cols // 2, dtype=torch.uint8, device=DEV), torch.zeros(rows * cols // 128, device=DEV)
+
+    def best(x):
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                lpmm.lpmm_quant_ablation(lpmm.NORM_B128, lpmm.MAP_DE, signed, lpmm.ROUND_STOCHASTIC, 7, x, rows, cols, codes, sa, None)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times[1:])
+
+    lpmm.ensure_init(4096)
+    t = {name: best(x) for name, x in (("dense", dense), ("half", half), ("small", small), ("dense again", dense))}
+    assert max(t["half"], t["small"]) < 1.25 * max(t["dense"], t["dense again"]), t

@@ -19,16 +19,25 @@
 
 namespace lpmm {
 
+// What a compress kernel searches by.  Kernels are handed what they use and no more, and set up with one barrier: a call on a small
+// tensor takes little else (64 x 64, block 128, to nearest 4.15 us with all tables of both roundings in the arguments, a barrier in
+// front of the buckets and another behind, 3.29 so).
 struct AblMap {
-    float T[kCodes];          // increasing; n entries
-    float thr[kCodes - 1];    // largest float not above the midpoint of neighbouring entries
-    int n;
+    float v[kCodes];          // increasing, +inf beyond the last.  Stochastic rounding: the entries; to nearest: the largest floats not
+                              // above the midpoints of neighbouring entries
+    int bucket[kCodes];       // of v, kBuckets beyond the last one
+    int n;                    // entries
     float least;              // of the normalized values: 0, signed maps -1
-    // for the buckets: those of the thresholds and of the entries, kBuckets beyond the last one
-    int thr_bucket[kCodes], entry_bucket[kCodes];
-    // stochastic rounding, by the number of entries below a value: the entry below it (the first one where there is none), and 2^24
-    // over the distance to the next, so that the next entry itself gives no less than 2^24
-    float lo[kCodes], inv_gap[kCodes];
+};
+// stochastic rounding, by the number of entries below a value: 2^24 over the distance from the entry below it to the next, so that the
+// next entry itself gives no less than 2^24
+struct AblGaps {
+    float inv[kCodes];
+};
+template <bool SR> struct AblSearch : AblMap {};
+template <> struct AblSearch<true> : AblMap, AblGaps {};
+struct AblEntries {           // what the decompress kernel looks up
+    float T[kCodes];          // 0 beyond the last
 };
 
 struct AblArgs {
@@ -43,35 +52,29 @@ struct AblArgs {
     uint64_t seed;
 };
 
-// The map in LDS, padded to 16 entries that no normalized value reaches.
 struct AblLds {
-    SearchEntry bucket[kBucketsPadded];      // of thresholds or entries: how many lie in the buckets below, and the next one
-    float2 gap[kCodes];       // {lo, inv_gap}
-    float T[kCodes];          // entries, 0 beyond the last (decompress)
-    float Ts[kCodes + 1];     // entries, +inf beyond the last (search)
-    float thr[kCodes + 1];    // thresholds, +inf beyond the last
+    SearchEntry bucket[kBucketsPadded];      // how many of v lie in the buckets below, and the next one
+    float2 gap[kCodes];       // {entry below, AblGaps::inv}; the first entry where there is none below
+    float v[kCodes];
 };
-__device__ __forceinline__ void abl_load_map(AblLds& s, const AblMap& m) {
-    const int k = threadIdx.x;
-    if (k <= kCodes) {
-        s.Ts[k] = k < m.n ? m.T[k] : __builtin_inff();
-        s.thr[k] = k < m.n - 1 ? m.thr[k] : __builtin_inff();
-        if (k < kCodes) {
-            s.T[k] = k < m.n ? m.T[k] : 0.0f;
-            s.gap[k] = make_float2(m.lo[k], m.inv_gap[k]);
-        }
-    }
-    __syncthreads();
-}
-// The buckets of entries (stochastic rounding) or thresholds (to nearest); a barrier behind abl_load_map's.  A bucket without one
-// compares with the next one above, which is larger than everything in the bucket.
+// A bucket without one of v compares with the next one above, which is larger than everything in the bucket.
 template <bool SR>
-__device__ __forceinline__ void abl_load_buckets(AblLds& s, const AblMap& m) {
-    for (int b = (m.least < 0.0f ? 0 : kBucketHalf) + int(threadIdx.x); b < kBuckets; b += kThreads) {
+__device__ __forceinline__ void abl_load_map(AblLds& s, const AblSearch<SR>& m) {
+    const int t = threadIdx.x;
+    if (t < kCodes) {
+        s.v[t] = m.v[t];
+        if constexpr (SR) s.gap[t] = make_float2(m.v[t > 0 ? t - 1 : 0], m.inv[t]);
+    }
+    for (int b = (m.least < 0.0f ? 0 : kBucketHalf) + t; b < kBuckets; b += kThreads) {
         uint32_t below = 0;
+        float next = m.v[0];
 #pragma unroll
-        for (int k = 0; k < kCodes; ++k) below += (SR ? m.entry_bucket[k] : m.thr_bucket[k]) < b ? 1u : 0u;
-        s.bucket[b] = SearchEntry{SR ? s.Ts[below] : s.thr[below], below};
+        for (int k = 0; k < kCodes; ++k) {
+            const bool under = m.bucket[k] < b;
+            below += under ? 1u : 0u;
+            next = under ? (k + 1 < kCodes ? m.v[k + 1] : __builtin_inff()) : next;
+        }
+        s.bucket[b] = SearchEntry{next, below};
     }
     __syncthreads();
 }
@@ -104,14 +107,14 @@ __device__ __forceinline__ float abl_uniform24(uint64_t z) {
 // division.  The quotient is first taken with the approximate reciprocal, which is within 2^-21 of p; only where that
 // does not settle u < p is the division done.
 __device__ __forceinline__ uint32_t abl_stochastic(const AblLds& m, int n_entries, float n, float u) {
-    int lt = abl_count_below(m.Ts, n);                       // entries below n
-    if (lt == 15 && n > m.Ts[15]) lt = 16;
-    const float hi = m.Ts[lt < 15 ? lt : 15];
+    int lt = abl_count_below(m.v, n);                       // entries below n
+    if (lt == 15 && n > m.v[15]) lt = 16;
+    const float hi = m.v[lt < 15 ? lt : 15];
     const int le = lt + (lt < n_entries && hi == n ? 1 : 0);     // entries at or below n
     const int q1 = le - 1, q2 = lt;
     if (q1 < 0) return uint32_t(q2 < n_entries ? q2 : 0);
     if (q2 >= n_entries || q1 == q2) return uint32_t(q1);
-    const float d = n - m.Ts[q1], w = hi - m.Ts[q1];
+    const float d = n - m.v[q1], w = hi - m.v[q1];
     float p = d * __builtin_amdgcn_rcpf(w);
     if (fabsf(u - p) < 0x1p-18f) p = d / w;
     return uint32_t(u < p ? q2 : q1);
@@ -170,7 +173,7 @@ __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, f
             const float n = (s[e] == 0.0f) ? 0.0f : x[e] / s[e];
             uint32_t q;
             if constexpr (SR) q = abl_stochastic(m, n_entries, n, u[e] * 0x1p-24f);
-            else q = uint32_t(abl_count_below(m.thr, n));        // nearest entry, ties to the lower index
+            else q = uint32_t(abl_count_below(m.v, n));        // nearest entry, ties to the lower index
             w |= q << (4 * e);
         }
     }
@@ -185,7 +188,7 @@ __device__ __forceinline__ float abl_inverse(float s) { return approx_inv(s) * (
 // takes (64 x 64: 8.8 us with four, 7.8 with two; 4096 x 100: 9.1, 7.9).
 constexpr int64_t kAblShortElems = int64_t(1) << 21;
 template <int BLOCK, bool SR, int UNITS>
-__global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs a, const AblMap m) {
+__global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs a, const AblSearch<SR> m) {
     static_assert(BLOCK == 128 || BLOCK == 2048, "block sizes of Tab. 1");
     static_assert(UNITS % 2 == 0 && kCvtUnitElems == 1024, "two units of a workgroup make one block of 2048");
     constexpr int kBlocks = UNITS / 2;                    // of 2048
@@ -195,8 +198,7 @@ __global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs
     float x[UNITS][4], sc[UNITS];
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) cvt_load4(a.x_in, first + u * kCvtUnitElems, a.P, x[u]);
-    abl_load_map(s_map, m);
-    abl_load_buckets<SR>(s_map, m);
+    abl_load_map<SR>(s_map, m);
 #pragma unroll
     for (int u = 0; u < UNITS; ++u)
         sc[u] = group32_allmax(cvt_absmax4(x[u]));
@@ -230,7 +232,7 @@ __global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs
 // Rank-1 normalization, second stage: codes against min(r_i, c_j) (the maxima are complete in sa / sb).  Two runs in short tensors, whatever
 // the rounding (all six calls on 1000 x 1001 40.0 us with four, 37.9 so; 300 x 16000 to nearest 46.4 and 47.5, 7484 x 4483 265.4 and 267.2).
 template <bool SR, int UNITS>
-__global__ __launch_bounds__(kThreads) void abl_quant_rank1_kernel(const AblArgs a, const AblMap m) {
+__global__ __launch_bounds__(kThreads) void abl_quant_rank1_kernel(const AblArgs a, const AblSearch<SR> m) {
     __shared__ AblLds s_map;
     const int64_t wg_first = int64_t(blockIdx.x) * (UNITS * kCvtUnitElems);
     const CvtOrigin o = cvt_origin(wg_first, a.cols);
@@ -241,8 +243,7 @@ __global__ __launch_bounds__(kThreads) void abl_quant_rank1_kernel(const AblArgs
         cvt_load4(a.x_in, wg_first + off, a.P, x[u]);
         rank1_scales4(o, off, a.rows, a.sa, a.sb, s[u]);
     }
-    abl_load_map(s_map, m);
-    abl_load_buckets<SR>(s_map, m);
+    abl_load_map<SR>(s_map, m);
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
         const int64_t base = wg_first + u * kCvtUnitElems + threadIdx.x * 4;
@@ -259,8 +260,8 @@ __global__ __launch_bounds__(kThreads) void abl_quant_rank1_kernel(const AblArgs
 }
 
 // norm: 0 = block 128, 1 = block 2048, 2 = rank-1
-__global__ __launch_bounds__(kThreads) void abl_dequant_kernel(const AblArgs a, const AblMap m, int norm) {
-    __shared__ AblLds s_map;
+__global__ __launch_bounds__(kThreads) void abl_dequant_kernel(const AblArgs a, const AblEntries m, int norm) {
+    __shared__ float s_T[kCodes];
     const int64_t wg_first = int64_t(blockIdx.x) * kCvtElems;
     uint32_t w[kCvtUnits];
     float s[kCvtUnits][4];
@@ -278,12 +279,13 @@ __global__ __launch_bounds__(kThreads) void abl_dequant_kernel(const AblArgs a, 
     }
 #pragma unroll
     for (int u = 0; u < kCvtUnits; ++u) w[u] = cvt_load_codes(a.q_in, wg_first + u * kCvtUnitElems + threadIdx.x * 4, a.P);
-    abl_load_map(s_map, m);
+    if (threadIdx.x < kCodes) s_T[threadIdx.x] = m.T[threadIdx.x];
+    __syncthreads();
 #pragma unroll
     for (int u = 0; u < kCvtUnits; ++u) {
         float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = s_map.T[(w[u] >> (4 * e)) & 15u] * s[u][e];
+        for (int e = 0; e < 4; ++e) v[e] = s_T[(w[u] >> (4 * e)) & 15u] * s[u][e];
         cvt_store4(a.x_out, wg_first + u * kCvtUnitElems + threadIdx.x * 4, a.P, v);
     }
 }

@@ -1582,9 +1582,15 @@ int lpmm_quant_state(int which, const float* in, const int64_t shape[2], uint8_t
 
 namespace {
 
-// the map of an ablation quantizer with what its kernels search it by; false for a combination that does not exist
-bool build_ablation_map(int map, int is_signed, AblMap* m) {
-    float T[kCodes];
+// the map of an ablation quantizer with what its kernels search it by
+struct AblationMap {
+    AblEntries entries;
+    AblSearch<false> nearest;
+    AblSearch<true> stochastic;
+};
+// false for a combination that does not exist
+bool build_ablation_map(int map, int is_signed, AblationMap* m) {
+    float T[kCodes], thr[kCodes];
     int n = kCodes;
     if (map == LPMM_MAP_DE) {
         if (is_signed) build_de_signed(T); else build_de_unsigned(T);
@@ -1598,28 +1604,31 @@ bool build_ablation_map(int map, int is_signed, AblMap* m) {
     } else {
         return false;
     }
-    *m = AblMap{};
-    m->n = n;
-    m->least = is_signed ? -1.0f : 0.0f;
-    for (int i = 0; i < n; ++i) m->T[i] = T[i];
-    build_thresholds_n(T, n, m->thr);
-    bool ok = one_per_bucket(T, n, m->entry_bucket) && one_per_bucket(m->thr, n - 1, m->thr_bucket);
+    *m = AblationMap{};
+    std::copy(T, T + n, m->entries.T);
+    build_thresholds_n(T, n, thr);
+    auto fill_search = [&](AblMap* s, const float* v, int count) {
+        for (int i = 0; i < kCodes; ++i) s->v[i] = i < count ? v[i] : std::numeric_limits<float>::infinity();
+        std::fill(s->bucket, s->bucket + kCodes, kBuckets);
+        s->n = n;
+        s->least = is_signed ? -1.0f : 0.0f;
+        return one_per_bucket(v, count, s->bucket);
+    };
+    bool ok = fill_search(&m->stochastic, T, n) && fill_search(&m->nearest, thr, n - 1);
     for (int i = 0; i < kCodes; ++i) {
-        if (i >= n) m->entry_bucket[i] = kBuckets;
-        if (i >= n - 1) m->thr_bucket[i] = kBuckets;
         const int k = std::clamp(i, 1, n - 1);              // the gap between entries k - 1 and k
-        m->lo[i] = T[k - 1];
         float inv = float(0x1p24 / (double(T[k]) - double(T[k - 1])));
         while ((T[k] - T[k - 1]) * inv < 0x1p24f) inv = std::nextafterf(inv, std::numeric_limits<float>::infinity());
-        m->inv_gap[i] = inv;
+        m->stochastic.inv[i] = inv;
         // what the kernels' margins rest on
         ok = ok && std::max(std::fabs(double(T[k])), std::fabs(double(T[k - 1]))) <= 17.9 * (double(T[k]) - double(T[k - 1]));
     }
     return ok;
 }
-bool ablation_map(int map, int is_signed, AblMap* m) {
+// null for a combination that does not exist
+const AblationMap* ablation_map(int map, int is_signed) {
     struct Maps {
-        AblMap m[3][2];
+        AblationMap m[3][2];
         bool ok[3][2];
         Maps() {
             for (int k = 0; k < 3; ++k)
@@ -1627,9 +1636,8 @@ bool ablation_map(int map, int is_signed, AblMap* m) {
         }
     };
     static const Maps maps;
-    if (map < 0 || map > 2 || !maps.ok[map][is_signed ? 1 : 0]) return false;
-    *m = maps.m[map][is_signed ? 1 : 0];
-    return true;
+    const int s = is_signed ? 1 : 0;
+    return map >= 0 && map <= 2 && maps.ok[map][s] ? &maps.m[map][s] : nullptr;
 }
 
 bool ablation_valid(int norm, int is_signed) {
@@ -1641,10 +1649,10 @@ bool ablation_valid(int norm, int is_signed) {
 extern "C" {
 
 int lpmm_ablation_table(int map, int is_signed, float out[16]) {
-    AblMap m;
-    if (!out || !ablation_map(map, is_signed, &m)) return LPMM_EINVAL;
-    for (int i = 0; i < kCodes; ++i) out[i] = i < m.n ? m.T[i] : 0.0f;
-    return m.n;
+    const AblationMap* m = ablation_map(map, is_signed);
+    if (!out || !m) return LPMM_EINVAL;
+    std::copy(m->entries.T, m->entries.T + kCodes, out);
+    return m->nearest.n;
 }
 
 int lpmm_quant_ablation(int norm, int map, int is_signed, int rounding, uint64_t seed, const float* in,
@@ -1652,8 +1660,8 @@ int lpmm_quant_ablation(int norm, int map, int is_signed, int rounding, uint64_t
     int64_t rows, cols;
     const int rc = check_shape(shape, &rows, &cols);
     if (rc) return rc;
-    AblMap m;
-    if (!ablation_valid(norm, is_signed) || !ablation_map(map, is_signed, &m)) return LPMM_EINVAL;
+    const AblationMap* m = ablation_map(map, is_signed);
+    if (!ablation_valid(norm, is_signed) || !m) return LPMM_EINVAL;
     if (rounding != LPMM_ROUND_NEAREST && rounding != LPMM_ROUND_STOCHASTIC) return LPMM_EINVAL;
     if (!in || !codes || !scale_a || (norm == LPMM_NORM_RANK1 && !scale_b)) return LPMM_EINVAL;
     if (!aligned(in, 4) || !aligned(codes, 4) || !aligned(scale_a, 4)) return LPMM_EINVAL;
@@ -1674,20 +1682,20 @@ int lpmm_quant_ablation(int norm, int map, int is_signed, int rounding, uint64_t
         const int r = launch_maxima(q, 256, s);       // this call needs no init, hence no device context
         if (r) return r;
     }
-#define LPMM_ABL_BLOCK(SR, UNITS)                                                                                      \
-    if (norm == LPMM_NORM_B128) hipLaunchKernelGGL((abl_quant_block_kernel<128, SR, UNITS>), dim3(blocks), dim3(kThreads), 0, s, a, m); \
-    else hipLaunchKernelGGL((abl_quant_block_kernel<2048, SR, UNITS>), dim3(blocks), dim3(kThreads), 0, s, a, m);
+#define LPMM_ABL_BLOCK(SR, UNITS, M)                                                                                      \
+    if (norm == LPMM_NORM_B128) hipLaunchKernelGGL((abl_quant_block_kernel<128, SR, UNITS>), dim3(blocks), dim3(kThreads), 0, s, a, M); \
+    else hipLaunchKernelGGL((abl_quant_block_kernel<2048, SR, UNITS>), dim3(blocks), dim3(kThreads), 0, s, a, M);
     const bool shorter = a.stochastic && a.P <= kAblShortElems;
     const int blocks = shorter ? grid_for(a.P, 2 * kCvtUnitElems / kThreads) : grid;
     if (norm == LPMM_NORM_RANK1) {
-#define LPMM_RANK1(SR)                                                                                                                  \
-    if (a.P <= kAblShortElems) hipLaunchKernelGGL((abl_quant_rank1_kernel<SR, 2>), dim3(rank_grid(a.P, 2)), dim3(kThreads), 0, s, a, m); \
-    else hipLaunchKernelGGL((abl_quant_rank1_kernel<SR, kCvtUnits>), dim3(grid), dim3(kThreads), 0, s, a, m);
-        if (a.stochastic) { LPMM_RANK1(true) } else { LPMM_RANK1(false) }
+#define LPMM_RANK1(SR, M)                                                                                                                  \
+    if (a.P <= kAblShortElems) hipLaunchKernelGGL((abl_quant_rank1_kernel<SR, 2>), dim3(rank_grid(a.P, 2)), dim3(kThreads), 0, s, a, M); \
+    else hipLaunchKernelGGL((abl_quant_rank1_kernel<SR, kCvtUnits>), dim3(grid), dim3(kThreads), 0, s, a, M);
+        if (a.stochastic) { LPMM_RANK1(true, m->stochastic) } else { LPMM_RANK1(false, m->nearest) }
 #undef LPMM_RANK1
-    } else if (shorter) { LPMM_ABL_BLOCK(true, 2) }
-    else if (a.stochastic) { LPMM_ABL_BLOCK(true, kCvtUnits) }
-    else { LPMM_ABL_BLOCK(false, kCvtUnits) }
+    } else if (shorter) { LPMM_ABL_BLOCK(true, 2, m->stochastic) }
+    else if (a.stochastic) { LPMM_ABL_BLOCK(true, kCvtUnits, m->stochastic) }
+    else { LPMM_ABL_BLOCK(false, kCvtUnits, m->nearest) }
 #undef LPMM_ABL_BLOCK
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
@@ -1698,8 +1706,8 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
     int64_t rows, cols;
     const int rc = check_shape(shape, &rows, &cols);
     if (rc) return rc;
-    AblMap m;
-    if (!ablation_valid(norm, is_signed) || !ablation_map(map, is_signed, &m)) return LPMM_EINVAL;
+    const AblationMap* m = ablation_map(map, is_signed);
+    if (!ablation_valid(norm, is_signed) || !m) return LPMM_EINVAL;
     if (!codes || !scale_a || !out || (norm == LPMM_NORM_RANK1 && !scale_b)) return LPMM_EINVAL;
     if (!aligned(codes, 4) || !aligned(out, 4) || !aligned(scale_a, 4)) return LPMM_EINVAL;
     AblArgs a{};
@@ -1709,7 +1717,7 @@ int lpmm_dequant_ablation(int norm, int map, int is_signed, const uint8_t* codes
     a.sb = const_cast<float*>(scale_b);
     a.rows = rows; a.cols = cols; a.P = rows * cols;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(abl_dequant_kernel, dim3(grid_for(a.P, kCvtElems / kThreads)), dim3(kThreads), 0, s, a, m, norm);
+    hipLaunchKernelGGL(abl_dequant_kernel, dim3(grid_for(a.P, kCvtElems / kThreads)), dim3(kThreads), 0, s, a, m->entries, norm);
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
 }

@@ -27,6 +27,7 @@ struct AblMap {
                               // above the midpoints of neighbouring entries
     int bucket[kCodes];       // of v, kBuckets beyond the last one
     int n;                    // entries
+    uint32_t zero4;           // the codes of four zeros: a zero's is the same under every scale and either rounding
     float least;              // of the normalized values: 0, signed maps -1
 };
 // stochastic rounding, by the number of entries below a value: 2^24 over the distance from the entry below it to the next, so that the
@@ -130,12 +131,17 @@ __device__ __forceinline__ uint32_t abl_stochastic(const AblLds& m, int n_entrie
 // is taken unless the random number itself is that close to 0 or 1.  So what counts as a doubt hangs on the random number alone, about
 // one element in 10^4 whatever the values; one that is 0, next to 0 or its own scale (n is an entry, or all but one) is no likelier.
 // (Where closeness of p' to 0 or 1 was a doubt, one zero under a map that has one sent its wave both ways: DE, 4096 x 4096,
-// stochastic rounding, block 128, 1 % zeros 47.7 us, 30 without; with division and search for everything 39.)  NaN comes out as
+// stochastic rounding, block 128, 1 % zeros 47.7 us, 30 without; with division and search for everything 39.)  A wave of nothing but
+// zeros, rows that had no gradient yet, needs none of it (nine rows of ten, rank-1: 50 us, 37 so; 45 with division and search).  NaN comes out as
 // the first entry both ways; extreme scales count as doubts.
 constexpr float kMarginSr = 256.0f;          // 2^-16 in units of 2^-24
 template <bool SR>
-__device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, float least, uint64_t seed, int64_t idx, const float x[4],
+__device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, const AblMap& map, uint64_t seed, int64_t idx, const float x[4],
                                                const float s[4], const float inv[4], bool tame) {
+    uint32_t bits = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bits |= __float_as_uint(x[e]) << 1;
+    if (__ballot(bits != 0) == 0) return map.zero4;
     uint32_t w = 0;
     bool doubt = !tame;
     const uint64_t z0 = abl_generator(seed, uint64_t(idx));
@@ -148,7 +154,7 @@ __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, f
     float close = 0x1p24f, off_centre = 0.0f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const float n = __builtin_amdgcn_fmed3f(x[e] * inv[e], least, 1.0f);
+        const float n = __builtin_amdgcn_fmed3f(x[e] * inv[e], map.least, 1.0f);
         const SearchEntry b = search_entry(m.bucket, n);
         const uint32_t below = b.base + (n > b.thr ? 1u : 0u);
         if constexpr (SR) {
@@ -172,7 +178,7 @@ __device__ __forceinline__ uint32_t abl_codes4(const AblLds& m, int n_entries, f
         for (int e = 0; e < 4; ++e) {
             const float n = (s[e] == 0.0f) ? 0.0f : x[e] / s[e];
             uint32_t q;
-            if constexpr (SR) q = abl_stochastic(m, n_entries, n, u[e] * 0x1p-24f);
+            if constexpr (SR) q = abl_stochastic(m, map.n, n, u[e] * 0x1p-24f);
             else q = uint32_t(abl_count_below(m.v, n));        // nearest entry, ties to the lower index
             w |= q << (4 * e);
         }
@@ -223,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs
         const int64_t base = first + u * kCvtUnitElems;
         if (base >= a.P) continue;
         const float s[4] = {sc[u], sc[u], sc[u], sc[u]}, i = abl_inverse<SR>(sc[u]), inv[4] = {i, i, i, i};
-        cvt_store_codes(a.q_out, base, a.P, abl_codes4<SR>(s_map, m.n, m.least, a.seed, base, x[u], s, inv, scale_is_tame(sc[u])));
+        cvt_store_codes(a.q_out, base, a.P, abl_codes4<SR>(s_map, m, a.seed, base, x[u], s, inv, scale_is_tame(sc[u])));
         if constexpr (BLOCK == 128)
             if ((threadIdx.x & 31) == 0) a.sa[base >> 7] = sc[u];
     }
@@ -255,7 +261,7 @@ __global__ __launch_bounds__(kThreads) void abl_quant_rank1_kernel(const AblArgs
             inv[e] = abl_inverse<SR>(s[u][e]);
             tame = bool(int(tame) & int(scale_is_tame(s[u][e])));
         }
-        cvt_store_codes(a.q_out, base, a.P, abl_codes4<SR>(s_map, m.n, m.least, a.seed, base, x[u], s[u], inv, tame));
+        cvt_store_codes(a.q_out, base, a.P, abl_codes4<SR>(s_map, m, a.seed, base, x[u], s[u], inv, tame));
     }
 }
 

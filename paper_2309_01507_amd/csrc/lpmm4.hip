@@ -1607,10 +1607,12 @@ bool build_ablation_map(int map, int is_signed, AblationMap* m) {
     *m = AblationMap{};
     std::copy(T, T + n, m->entries.T);
     build_thresholds_n(T, n, thr);
+    const float* zero = std::find(T, T + n, 0.0f);
     auto fill_search = [&](AblMap* s, const float* v, int count) {
         for (int i = 0; i < kCodes; ++i) s->v[i] = i < count ? v[i] : std::numeric_limits<float>::infinity();
         std::fill(s->bucket, s->bucket + kCodes, kBuckets);
         s->n = n;
+        s->zero4 = 0x1111u * (zero < T + n ? uint32_t(zero - T) : 0u);       // maps without a zero have nothing below their first entry
         s->least = is_signed ? -1.0f : 0.0f;
         return one_per_bucket(v, count, s->bucket);
     };

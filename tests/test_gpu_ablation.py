@@ -207,3 +207,25 @@ def test_zeros_cost_stochastic_rounding_no_second_route(signed):
     lpmm.ensure_init(4096)
     t = {name: best(x) for name, x in (("dense", dense), ("half", half), ("small", small), ("dense again", dense))}
     assert max(t["half"], t["small"]) < 1.25 * max(t["dense"], t["dense again"]), t
+
+
+@pytest.mark.parametrize("norm,map_name,signed", COMBOS)
+@pytest.mark.parametrize("stochastic", [False, True])
+def test_runs_of_zeros(norm, map_name, signed, stochastic):
+    """Waves of nothing but zeros, of either sign, inside blocks and rows with other values and in ones without, at a tensor's end too."""
+    rng = np.random.default_rng(29)
+    x = rng.random((37, 1001)).astype(np.float32)
+    if signed:
+        x *= rng.choice(np.float32([-1, 1]), x.shape)
+    flat = x.reshape(-1)
+    for first in range(0, flat.size, 2048):
+        k = first + int(rng.integers(0, 1024))
+        flat[k:k + int(rng.integers(200, 1500))] = rng.choice(np.float32([0.0, -0.0]))
+    x[5:9], flat[-700:] = 0.0, 0.0
+    x[:, 300:310] = 0.0
+    want_codes, want_sa, want_sb = oracle.quant_ablation(x, norm, map_name, signed, stochastic, 4713)
+    codes, sa, sb = _gpu_quant(x, norm, map_name, signed, stochastic, 4713)
+    np.testing.assert_array_equal(sa.cpu().numpy(), want_sa)
+    if norm == "rank1":
+        np.testing.assert_array_equal(sb.cpu().numpy(), want_sb)
+    np.testing.assert_array_equal(oracle.unpack_codes(codes.cpu().numpy(), x.size), oracle.unpack_codes(want_codes, x.size))

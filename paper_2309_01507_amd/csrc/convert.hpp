@@ -261,81 +261,107 @@ __global__ __launch_bounds__(kThreads) void quant_vb_kernel(const QuantArgs q) {
 //
 // A workgroup takes rows_per_wg rows x a strip of 8 * TX columns: TX lanes take 8 columns each of one row, 256 / TX rows side by
 // side.  Column maxima stay in registers down the tile, a row's maximum is reduced over its lanes, and one global atomic per row and
-// per column of the tile follows at the end.  A maximum may be taken twice, so nothing needs a branch at the edges: lanes beyond the
-// last column repeat the last 8 of them, rows beyond the last one repeat that.
+// per column of the tile follows at the end.  A maximum may be taken twice, so nothing needs a branch at the edges: the last lane that
+// has columns takes the last 8 of the row, lanes and rows beyond repeat what others take.  As few lanes to a row as its columns need:
+// with 16 for every narrow matrix a wave took its 4 rows no sooner than 128 columns (with codes, us, before and so: 2000000 x 16 94 and
+// 86, 1000000 x 32 72 and 64).  SINGLE: matrices of up to 64 columns whose rows begin anywhere; lane x takes columns x, x + TX and so on, an
+// element at a time (2000001 x 15 149 in 16-byte loads by 16 lanes, 142 by 4, 99 so; 1000001 x 33 113, 110 and 89).
 // Bound by those atomics and by latency where the matrix is small, else by memory.  Strips of 1024 columns by 4 to 32 rows, as the
 // filling of the chip asked for them, sent two to three times as many atomics, which were what the pass took: 3000 x 1001 18.6 us, 6.3
 // so, 1000 x 1001 8.0 and 4.2, 4096 x 4096 15.3 and 13.8, 11008 x 4096 43 and 35.5 (5.1 TB/s).
+// Wide matrices of few rows: `run` strips to a workgroup, see launch_maxima.
 constexpr int kMaxTileRows = 512;
 constexpr int kMaxCols = 8;               // of a lane
 
 struct MaxTiling {
     int rows_per_wg;      // <= kMaxTileRows
     int strips;           // ceil(cols / (8 * TX))
+    int run;              // strips that a workgroup takes one after the other
+    int groups;           // ceil(strips / run)
+    int whole;            // all rows in one tile: column maxima are complete, and stored
 };
 
+// maximum over the TX lanes of a row of the bits of values >= +0, the same in all of them
 template <int TX>
+__device__ __forceinline__ uint32_t lanes_allmax(uint32_t v) {
+    static_assert(TX == 4 || TX == 8 || TX == 16 || TX == 32, "lanes of a row: a quad to a half-wave");
+    if constexpr (TX == 32) return __float_as_uint(group32_allmax(__uint_as_float(v)));
+    v = dpp_umax<0xB1>(v);
+    v = dpp_umax<0x4E>(v);
+    if constexpr (TX >= 8) v = dpp_umax<0x141>(v);
+    if constexpr (TX >= 16) v = dpp_umax<0x140>(v);
+    return v;
+}
+
+template <int TX, bool SINGLE>
 __global__ __launch_bounds__(kThreads) void quant_v_max_kernel(const QuantArgs q, const MaxTiling t) {
-    static_assert(TX == 16 || TX == 32, "lanes of a row: a DPP row or a half-wave");
     constexpr int kTy = kThreads / TX, kDepth = 4;
     __shared__ uint32_t s_row[kMaxTileRows];
     __shared__ uint32_t s_col[kTy][TX * kMaxCols];
-    const int64_t strip0 = int64_t(blockIdx.x % t.strips) * (TX * kMaxCols);
-    const int64_t row0 = int64_t(blockIdx.x / t.strips) * t.rows_per_wg;
+    const int first = int(blockIdx.x % t.groups) * t.run, end = min(first + t.run, t.strips);
+    const int64_t row0 = int64_t(blockIdx.x / t.groups) * t.rows_per_wg;
     const int64_t left = q.rows - row0;
     const int n = left < t.rows_per_wg ? int(left) : t.rows_per_wg;
     const int x = threadIdx.x % TX, y = threadIdx.x / TX;
-    const int64_t own = strip0 + kMaxCols * x, last = q.cols > kMaxCols ? q.cols - kMaxCols : 0;
-    const float* p = q.x_in + row0 * q.cols + (own < last ? own : last);
-    const bool wide = q.cols >= kMaxCols;
-    const int last_col = int(q.cols < kMaxCols ? q.cols : kMaxCols) - 1;
+    const int64_t last = SINGLE ? 0 : q.cols - kMaxCols;
     // a value's bits, 0 unless it is above 0 (a NaN raises no maximum)
     auto bits = [](float v) { return v > 0.0f ? __float_as_uint(v) : 0u; };
-    uint32_t cm[kMaxCols];
+    for (int strip = first; strip < end; ++strip) {
+        const int64_t strip0 = int64_t(strip) * (TX * kMaxCols), own = strip0 + kMaxCols * x;
+        const float* p = q.x_in + row0 * q.cols + (SINGLE ? 0 : own < last ? own : last);
+        int off[kMaxCols];
 #pragma unroll
-    for (int e = 0; e < kMaxCols; ++e) cm[e] = 0u;
-    for (int base = 0; base < n; base += kTy * kDepth) {          // the same rounds in all lanes
-        float v[kDepth][kMaxCols];
+        for (int e = 0; e < kMaxCols; ++e) off[e] = x + e * TX < int(q.cols) ? x + e * TX : int(q.cols) - 1;
+        uint32_t cm[kMaxCols];
 #pragma unroll
-        for (int u = 0; u < kDepth; ++u) {
-            const int il = base + u * kTy + y;
-            const float* pr = p + int64_t(il < n ? il : n - 1) * q.cols;
-            if (wide) {
-                const v4f_a4 a = reinterpret_cast<const v4f_a4*>(pr)[0], b = *reinterpret_cast<const v4f_a4*>(pr + 4);
-                v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
-                v[u][4] = b.x; v[u][5] = b.y; v[u][6] = b.z; v[u][7] = b.w;
-            } else {
+        for (int e = 0; e < kMaxCols; ++e) cm[e] = 0u;
+        for (int base = 0; base < n; base += kTy * kDepth) {          // the same rounds in all lanes
+            float v[kDepth][kMaxCols];
 #pragma unroll
-                for (int e = 0; e < kMaxCols; ++e) v[u][e] = pr[e < last_col ? e : last_col];
+            for (int u = 0; u < kDepth; ++u) {
+                const int il = base + u * kTy + y;
+                const float* pr = p + int64_t(il < n ? il : n - 1) * q.cols;
+                if constexpr (SINGLE) {
+#pragma unroll
+                    for (int e = 0; e < kMaxCols; ++e) v[u][e] = pr[off[e]];
+                } else {
+                    const v4f_a4 a = reinterpret_cast<const v4f_a4*>(pr)[0], b = *reinterpret_cast<const v4f_a4*>(pr + 4);
+                    v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
+                    v[u][4] = b.x; v[u][5] = b.y; v[u][6] = b.z; v[u][7] = b.w;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u) {
+                const int il = base + u * kTy + y;
+                uint32_t rm = 0u;
+#pragma unroll
+                for (int e = 0; e < kMaxCols; ++e) {
+                    const uint32_t z = bits(v[u][e]);
+                    cm[e] = max(cm[e], z);
+                    rm = max(rm, z);
+                }
+                const uint32_t all = lanes_allmax<TX>(rm);
+                if (x == 0 && il < n) s_row[il] = strip == first ? all : max(s_row[il], all);
             }
         }
 #pragma unroll
-        for (int u = 0; u < kDepth; ++u) {
-            const int il = base + u * kTy + y;
-            uint32_t rm = 0u;
+        for (int e = 0; e < kMaxCols; ++e) s_col[y][SINGLE ? x + e * TX : x * kMaxCols + e] = cm[e];
+        __syncthreads();
+        if (int(threadIdx.x) < TX * kMaxCols) {
+            const int64_t lane_own = strip0 + (SINGLE ? threadIdx.x : threadIdx.x & ~(kMaxCols - 1)), lane0 = SINGLE || lane_own < last ? lane_own : last;
+            const int64_t col = SINGLE ? lane_own : lane0 + threadIdx.x % kMaxCols;
+            uint32_t m = 0u;
 #pragma unroll
-            for (int e = 0; e < kMaxCols; ++e) {
-                const uint32_t z = bits(v[u][e]);
-                cm[e] = max(cm[e], z);
-                rm = max(rm, z);
+            for (int k = 0; k < kTy; ++k) m = max(m, s_col[k][threadIdx.x]);
+            if (m && lane_own < q.cols) {
+                if (t.whole) q.sb[col] = __uint_as_float(m);
+                else atomicMax(reinterpret_cast<unsigned int*>(q.sb) + col, m);
             }
-            const float all = TX == 16 ? row16_allmax(__uint_as_float(rm)) : group32_allmax(__uint_as_float(rm));
-            if (x == 0 && il < n) s_row[il] = __float_as_uint(all);
         }
+        if (strip + 1 < end) __syncthreads();
     }
-#pragma unroll
-    for (int e = 0; e < kMaxCols; ++e) s_col[y][x * kMaxCols + e] = cm[e];
-    __syncthreads();
     for (int k = threadIdx.x; k < n; k += kThreads)
         if (s_row[k]) atomicMax(reinterpret_cast<unsigned int*>(q.sa) + row0 + k, s_row[k]);
-    if (int(threadIdx.x) < TX * kMaxCols) {
-        const int64_t lane_own = strip0 + (threadIdx.x & ~(kMaxCols - 1)), lane0 = lane_own < last ? lane_own : last;
-        const int64_t col = lane0 + threadIdx.x % kMaxCols;
-        uint32_t m = 0u;
-#pragma unroll
-        for (int k = 0; k < kTy; ++k) m = max(m, s_col[k][threadIdx.x]);
-        if (m && lane_own < q.cols && col < q.cols) atomicMax(reinterpret_cast<unsigned int*>(q.sb) + col, m);
-    }
 }
 
 // second moment, after the maxima: codes against min(r_i, c_j)

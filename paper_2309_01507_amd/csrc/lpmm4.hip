@@ -1158,12 +1158,18 @@ int rank_grid(int64_t elems, int units) { return grid_for(elems, units * kCvtUni
 // than two workgroups per CU (11008 x 4096: 16, 32 and 64 rows 35.5 us, 128, the last of whose workgroups run alone, 45; 4096 x 4096 at
 // 32, 64 and 128 14.4, 13.8, 19; 200 x 16000 at 16, 32 and 64 5.8, 5.6, 6.4).  Tall ones take more: atomics on one column's maximum
 // follow each other (3000 x 1001 at 16, 32 and 64 8.2, 6.3, 6.5 us; 16384 x 80 at 64, 128 and 256 7.8, 6.5, 7.6).
+// So do those on one row's maximum, one per strip at about 12 ns, and a matrix of few rows has nothing to do meanwhile: there a
+// workgroup takes a run of strips, about 1 us each, so that the two balance at the root of the strips.  With all rows in one tile the columns'
+// maxima are complete, and stored.  (With codes, us: strips of 1024 columns with atomics for both, of 256, and so: 1 x 1000003 22.5, 55,
+// 22.7; 1 x 10000000 151, 483, 100; 4 x 4000000 84, 216, 69; 8 x 4000000 105, 235, 92; 16 x 1000000 57, 72, 42; 20 x 100000 14.5, 14.6, 12.0.)
+constexpr int64_t kMaxFewRows = 64;
 int launch_maxima(const QuantArgs& q, int n_cu, hipStream_t s) {
     hipLaunchKernelGGL(clear_two_kernel, dim3(grid_for(q.rows + q.cols, 4, 1024)), dim3(kThreads), 0, s, q.sa, q.rows, q.sb,
                        q.cols);
     LPMM_HIP(hipGetLastError());
-    const bool narrow = q.cols <= 16 * kMaxCols;
-    const int64_t strip = (narrow ? 16 : 32) * kMaxCols;
+    int tx = 4;
+    while (tx < 32 && tx * kMaxCols < q.cols) tx *= 2;
+    const int64_t strip = tx * kMaxCols;
     MaxTiling t;
     t.strips = int((q.cols + strip - 1) / strip);
     auto tiles = [&](int64_t per) { return t.strips * ((q.rows + per - 1) / per); };
@@ -1171,9 +1177,17 @@ int launch_maxima(const QuantArgs& q, int n_cu, hipStream_t s) {
     while (per > 16 && tiles(per) < 2 * int64_t(n_cu)) per /= 2;
     while (per < kMaxTileRows && per * per < q.rows / 3) per *= 2;
     t.rows_per_wg = int(per);
-    const dim3 grid(unsigned(tiles(per))), block(kThreads);
-    if (narrow) hipLaunchKernelGGL(quant_v_max_kernel<16>, grid, block, 0, s, q, t);
-    else hipLaunchKernelGGL(quant_v_max_kernel<32>, grid, block, 0, s, q, t);
+    t.run = q.rows > kMaxFewRows ? 1 : std::max(1, int(std::sqrt(double(t.strips)) / 9.0));
+    t.groups = (t.strips + t.run - 1) / t.run;
+    t.whole = q.rows <= per;
+    const dim3 grid(unsigned(t.groups * ((q.rows + per - 1) / per))), block(kThreads);
+    const bool single = q.cols < kMaxCols || (tx <= 8 && q.cols % 4 != 0);
+    if (single && tx == 4) hipLaunchKernelGGL((quant_v_max_kernel<4, true>), grid, block, 0, s, q, t);
+    else if (single) hipLaunchKernelGGL((quant_v_max_kernel<8, true>), grid, block, 0, s, q, t);
+    else if (tx == 4) hipLaunchKernelGGL((quant_v_max_kernel<4, false>), grid, block, 0, s, q, t);
+    else if (tx == 8) hipLaunchKernelGGL((quant_v_max_kernel<8, false>), grid, block, 0, s, q, t);
+    else if (tx == 16) hipLaunchKernelGGL((quant_v_max_kernel<16, false>), grid, block, 0, s, q, t);
+    else hipLaunchKernelGGL((quant_v_max_kernel<32, false>), grid, block, 0, s, q, t);
     LPMM_HIP(hipGetLastError());
     return LPMM_OK;
 }

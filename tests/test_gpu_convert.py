@@ -1,5 +1,5 @@
-"""Stand-alone compress / decompress at the edges of their tiles: 4 elements per lane, 4096 per workgroup, strips of 128 or
-256 columns and 16 to 512 rows for the maxima; arrays at 4-byte alignment; nothing written behind a buffer's end; a NaN
+"""Stand-alone compress / decompress at the edges of their tiles: 4 elements per lane, 4096 per workgroup (with rank-1 scales 2048 in
+tensors of up to 2^27), strips of 32 to 256 columns and 16 to 512 rows for the maxima; arrays at 4-byte alignment; nothing written behind a buffer's end; a NaN
 costs no other element its code."""
 import numpy as np
 import pytest
@@ -114,7 +114,7 @@ def test_nan_raises_no_block_scale(what):
 
 @pytest.mark.parametrize("rows,cols", [(1, 1), (16, 8), (17, 9), (33, 128), (31, 136), (65, 264), (300, 519), (5, 2049), (12289, 129), (800001, 3)])
 def test_maxima_at_the_edges_of_their_tiles(rows, cols):
-    """Lanes repeat the last 8 columns and rows the last one; 16 lanes a row up to 128 columns, 32 beyond; 16 to 512 rows a tile."""
+    """Lanes repeat the last 8 columns and rows the last one; 4 to 16 lanes a row up to 128 columns, 32 beyond; 16 to 512 rows a tile."""
     print(f"[gpu-test] maxima {rows}x{cols}", flush=True)
     lpmm.ensure_init(4096)
     gen = torch.Generator(device=DEV).manual_seed(rows + cols)
@@ -134,6 +134,52 @@ def test_maxima_at_the_edges_of_their_tiles(rows, cols):
         lpmm.lpmm_quant_state(1, x, rows, cols, codes, r[:rows], c[:cols])
         assert torch.equal(r[:rows], z.amax(1)) and torch.equal(c[:cols], z.amax(0))
         assert r[rows] == -5.0 and c[cols] == -5.0
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 150001), (3, 600007), (8, 300000), (33, 90001), (64, 100003), (65, 90001),    # runs of strips
+                                       (1, 5), (4, 3), (70001, 7), (5000, 9), (4097, 15), (3001, 33), (513, 63),             # one at a time
+                                       (5000, 8), (4097, 12), (3001, 32), (2049, 36), (1025, 64), (1025, 65)])
+def test_maxima_of_few_rows_and_of_few_columns(rows, cols):
+    """Up to 64 rows a workgroup takes several strips, and stores the columns' maxima where it has all rows; 4, 8, 16 or 32 lanes a
+    row, up to 64 columns an element at a time where rows begin anywhere."""
+    print(f"[gpu-test] maxima {rows}x{cols}", flush=True)
+    lpmm.ensure_init(4096)
+    gen = torch.Generator(device=DEV).manual_seed(rows + cols)
+    v = torch.rand(rows, cols, generator=gen, device=DEV) - 0.5 / min(rows, cols)
+    v[torch.rand(rows, cols, generator=gen, device=DEV) < 0.01] = float("nan")
+    z = torch.where(v > 0, v, torch.zeros_like(v))
+    for words in (0, 1):
+        buf = torch.empty(rows * cols + 8, device=DEV)
+        x = buf[words:words + rows * cols]
+        x.copy_(v.reshape(-1))
+        codes = torch.zeros((rows * cols + 7) // 8 * 4, dtype=torch.uint8, device=DEV)[:(rows * cols + 1) // 2]
+        r, c = torch.full((rows + 1,), -5.0, device=DEV), torch.full((cols + 1,), -5.0, device=DEV)
+        lpmm.lpmm_quant_state(1, x, rows, cols, codes, r[:rows], c[:cols])
+        assert torch.equal(r[:rows], z.amax(1)) and torch.equal(c[:cols], z.amax(0))
+        assert r[rows] == -5.0 and c[cols] == -5.0
+
+
+def test_a_single_long_row_takes_no_queue_of_atomics():
+    """One row of 10^7 elements against a square of as many: 100 us and 27; 480 with an atomic on the row's maximum per 256 columns."""
+    lpmm.ensure_init(1 << 22)
+    n = 3162 * 3162
+    x = torch.rand(n, device=DEV)
+    codes, scales = torch.zeros((n + 7) // 8 * 4, dtype=torch.uint8, device=DEV)[:n // 2], torch.zeros(n + 1, device=DEV)
+
+    def best(rows, cols):
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                lpmm.lpmm_quant_state(1, x, rows, cols, codes, scales[cols:cols + rows], scales[:cols])
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times[1:])
+
+    row, square = best(1, n), best(3162, 3162)
+    assert row < 8 * square, (row, square)
 
 
 @pytest.mark.parametrize("rows,cols", [(3, 683), (2, 1025), (16384, 8192), (16385, 8193)])

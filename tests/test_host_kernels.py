@@ -42,4 +42,5 @@ def test_the_quantizer_study_is_handed_what_it_uses(kernels):
         assert k[".group_segment_fixed_size"] <= 64 and explicit(k) <= 160, name
     for part in ("abl_quant_block_kernel", "abl_quant_rank1_kernel"):
         for name, k in _named(kernels, part).items():
-            assert explicit(k) <= 288, name
+            # 88 bytes of addresses and sizes, three tables of 16 words, some scalars; the other rounding's tables would be 128 more
+            assert explicit(k) <= 88 + 3 * 64 + 32, name

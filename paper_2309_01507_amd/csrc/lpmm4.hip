@@ -664,18 +664,36 @@ void factor_down_geometry(Tensor4* a, int64_t rw, int64_t cap) {
     a->rs = row_spacing_log2(a->cols * 4, rw, a->gy, "LPMM_RS");      // the parameters' rows
 }
 
-// Widest strips, in column blocks, of the update of a tensor on its own, whose tiles are those of the rank-1 form: 8 from 2^25 elements on,
-// else 4 (us at 4 and 8, bf16: 3000 x 3072 23.1, 24.1; 4096 x 4096 33.6, 33.5; 12288 x 4096 90.5, 89.3).  Strips of unequal width cost more
-// than that: the widest that wastes at most a sixteenth, from 3 blocks on, or else a wider one (fp32, a step: 20000 x 640 in strips of 3 + 2
-// 54.4, of 5 51.0; 30000 x 1152 of 5 + 4 111.1, of 3 107.4).
-// A step walking down the rows of one column block, as in plans, and now: 1024 x 1024 bf16 15.0, 14.4; 2500 x 1024 18.4, 16.9; 12288 x
-// 4096 112.3, 109.9; 4096 x 11008 109.6, 105.8; 200 x 25600 34.0, 28.7.
-int factor_widest(const Tensor4& a) {
-    const int most = a.P >= int64_t(1) << 25 ? kFlatBlocks : kFlatBlocks / 2;
-    auto even = [&](int w) { return round_up(a.nb, w) - a.nb <= a.nb / 16; };
-    for (int w = most; w >= 3; --w) if (even(w)) return w;
-    for (int w = most + 1; w <= kFlatBlocks; ++w) if (even(w)) return w;
-    return most;
+// The update of a factorized tensor on its own, in the rank-1 form's tiles: strips of 1 to 8 column blocks by 1 to 8 rows of a group.
+// Rows of a power of two up to 8192 elements, which are taken 32 KiB apart: strips of 8 blocks from 2^25 elements on, below of 4, cut as the
+// rank-1 form's (us at 4 and 8, bf16: 4096 x 4096 33.6, 33.5; 12288 x 4096 90.5, 89.3); also 8 in multiples of 2^23 elements, where the
+// eighths of the tensor that the XCDs work on lie at multiples of 4 MiB (us, down the rows of one block as in plans, at 4, at 8, bf16: 4096 x 2048
+// 27.2, 27.8, 26.2; 16384 x 1024 53.4, 54.1, 51.5; 12288 x 2048 63.8, 68.3, 62.5; at others 8 is the slower: 6144 x 2048 33.7, 33.5, 35.1).
+// Others from 2^24 elements on: strips of 8 blocks, below 2^25 elements of 4, or the next width down to 3 or up to 8 that wastes at most a
+// sixteenth (fp32, a step: 20000 x 640 in strips of 3 + 2 54.4, of 5 51.0; 30000 x 1152 of 5 + 4 111.1, of 3 107.4).
+// The rest get the tiling with the least ceil(tiles / CU) * (units of a group + 0.8 for a workgroup's start), where a CU has 3.5 tiles done
+// no later than fewer: in strips of 3 to 5 blocks cut until there are just over 3 tiles per CU they wait for the CUs that have a fourth, or
+// for a strip of one block left over (us, down the rows, in those strips, and so, bf16: 3125 x 640 17.7, 18.6, 17.5; 4464 x 896 20.8, 21.7,
+// 20.8; 9516 x 1664 46.6, 49.4, 47.4; fp32: 3125 x 1280 21.1, 21.9, 20.9; over 300 shapes 25 by more than 1.5 % slower than down the rows, and 9).
+void factor_alone_geometry(Tensor4* a, int n_cu, int grad_bytes) {
+    const bool apart = a->cols <= 8192 && (a->cols & (a->cols - 1)) == 0;
+    if (apart || a->P >= int64_t(1) << 24) {
+        const int most = a->P >= int64_t(1) << 25 || (apart && a->P % (int64_t(1) << 23) == 0) ? kFlatBlocks : kFlatBlocks / 2;
+        auto even = [&](int w) { return round_up(a->nb, w) - a->nb <= a->nb / 16; };
+        int widest = most;
+        while (widest >= 3 && !even(widest)) --widest;
+        if (widest < 3) for (widest = most + 1; widest <= kFlatBlocks && !even(widest);) ++widest;
+        if (apart || widest <= kFlatBlocks) return rank1_fast_geometry(a, n_cu, 0, 0, grad_bytes, 0, std::min(widest, kFlatBlocks));
+    }
+    int widest = 1, rows = kGroups;
+    int64_t least = std::numeric_limits<int64_t>::max();
+    for (int gx = 1; gx <= std::min(a->nb, kFlatBlocks); ++gx)
+        for (int per = 1; per <= 8; per *= 2) {
+            const int64_t tiles = ((a->nb + gx - 1) / gx) * ((a->rows + kGroups * per - 1) / (kGroups * per));
+            const int64_t cost = std::max<int64_t>(2 * ((tiles + n_cu - 1) / n_cu), 7) * (5 * gx * per + 4);
+            if (cost < least) { least = cost; widest = gx; rows = kGroups * per; }
+        }
+    rank1_fast_geometry(a, 0, rows, 0, grad_bytes, 0, widest);
 }
 
 // rw_hint: rows of a plan's update tiles, 0 for a tensor on its own.  Statistics: strips of 256 columns by rw2 rows, a wave per row.
@@ -687,7 +705,7 @@ void factor_geometry(Tensor4* a, int n_cu, int64_t rw_hint, int64_t rw2_hint, in
         const int64_t cap = (int64_t(1) << 29) / a->cols;         // lane offsets inside a tile stay below 2^31 bytes
         a->nb = int(a->cols / LPMM_BLOCK);
         if (rw_hint > 0) factor_down_geometry(a, rw_hint, cap);
-        else rank1_fast_geometry(a, n_cu, 0, 0, grad_bytes, 0, factor_widest(*a));
+        else factor_alone_geometry(a, n_cu, grad_bytes);
         a->strips2 = (a->nb + 1) / 2;
         int64_t rw2 = env_int("LPMM_RW2", 0);
         if (rw2 <= 0) rw2 = rw2_hint;

@@ -152,9 +152,10 @@ def test_other_launch_geometries(env):
 
 
 @pytest.mark.parametrize("rows,cols,bf16", [(1, 128, False), (9, 640, True), (67, 1152, False), (130, 1408, True), (33, 4224, False),
-                                            (1030, 512, True), (8200, 4224, False)])
-def test_strips_of_all_widths(rows, cols, bf16):
-    """Update tiles of a tensor on its own: strips of 3, 4, 5 and 8 blocks, of unequal width, super-tiles cut off."""
+                                            (1030, 512, True), (8200, 4224, False),
+                                            (1100, 1920, True), (5000, 768, False), (3000, 3072, True), (700, 5120, False), (4090, 2048, True)])
+def test_tilings_of_a_tensor_on_its_own(rows, cols, bf16):
+    """Update tiles as they are chosen: of one block and 8 rows for small tensors, of more blocks or rows for larger ones."""
     assert run(rows, cols, steps=2, bf16=bf16) == 0
 
 

@@ -159,6 +159,49 @@ def test_tilings_of_a_tensor_on_its_own(rows, cols, bf16):
     assert run(rows, cols, steps=2, bf16=bf16) == 0
 
 
+@pytest.mark.parametrize("gx", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("rw,rs", [(8, 0), (8, 3), (16, 2), (32, 2), (64, 4)])
+def test_strips_of_all_widths(gx, rw, rs):
+    """Update tiles along the rows of strips of 1 to 8 column blocks, the last one narrower (11 blocks: 1 to 5), of 1 to 8 rows of a
+    group, in super-tiles of up to 128 rows that up to 8 workgroups share and that the tensor's end cuts off."""
+    assert run(203, 1408, steps=2, bf16=bool(gx & 1), env={"LPMM_GX": str(gx), "LPMM_RW": str(rw), "LPMM_RS": str(rs)}) == 0
+
+
+@pytest.mark.parametrize("launches,route", [(2, {"LPMM_FLOW": "0"}), (1, {"LPMM_FLOW_MIN": "0"})], ids=["by-phases", "one-launch"])
+@pytest.mark.parametrize("env", [{}, {"LPMM_GX": "8", "LPMM_RW": "16"}, {"LPMM_GX": "2", "LPMM_RW": "300", "LPMM_RW2": "7"},
+                                 {"LPMM_GX": "4", "LPMM_RW": "24"}, {"LPMM_RW": "64", "LPMM_RS": "3", "LPMM_RW2": "32", "LPMM_RS2": "3"},
+                                 {"LPMM_RW": "40", "LPMM_RS": "2", "LPMM_RW2": "24", "LPMM_RS2": "1"}])
+def test_plan_walks_down_the_rows_in_all_tilings(launches, route, env):
+    """In plans the update walks down the rows of 1 to 8 column blocks a workgroup; forced tilings on both routes."""
+    hp, seed = oracle.Hyper(), 57
+    shapes = [(300, 1024), (257, 2048), (64, 128), (1030, 1024)]
+    os.environ.update({**route, **env})
+    try:
+        lpmm.ensure_init(4096)
+        dev, ref = [], []
+        for tid, (rows, cols) in enumerate(shapes):
+            w_ref = workloads.weights(seed, tid, rows, cols).reshape(-1)
+            dev.append((to_dev(w_ref.copy()), torch.empty(rows * cols, device=DEV), lpmm.new_state_factor(rows, cols, DEV)))
+            ref.append((w_ref, oracle.state_zero_factor(rows, cols)))
+        plan = lpmm.new_plan([lpmm.make_desc(w, g, st) for w, g, st in dev], 0, DEV)
+        assert lpmm.lpmm_adamw4_plan_launches(plan) == launches
+        for t in (1, 2):
+            for tid, ((rows, cols), (w, g, st)) in enumerate(zip(shapes, dev)):
+                g.copy_(to_dev(workloads.grads(seed, tid, t, rows, cols, "col_lognormal").reshape(-1)))
+            lpmm.lpmm_adamw4_step_multi(plan, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.weight_decay, t)
+            torch.cuda.synchronize()
+            for (rows, cols), (w, g, st), (w_ref, st_ref) in zip(shapes, dev, ref):
+                mt, _ = oracle.adamw4_factor_step(w_ref, g.cpu().numpy(), st_ref, hp, t, want_moments=True)
+                assert compare(download(st), st_ref, w.cpu().numpy(), w_ref, mt, f"{rows}x{cols} step {t}") == 0
+                st.v_row.copy_(to_dev(st_ref.v_row))
+                st.v_col.copy_(to_dev(st_ref.v_col))
+                w.copy_(to_dev(w_ref))
+        lpmm.lpmm_adamw4_plan_release(plan)
+    finally:
+        for k in {**route, **env}:
+            os.environ.pop(k, None)
+
+
 def test_first_moment_does_not_depend_on_the_launch_geometry():
     """The sums' order changes with the tiling, the first moment's bits must not."""
     rows, cols = 300, 1024

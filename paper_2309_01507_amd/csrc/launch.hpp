@@ -222,8 +222,11 @@ __device__ __forceinline__ Segment find_segment(const Segment* seg, int n_seg, i
 // ROLES: 0 = A and B work interleaved in one launch; 1 = A work only; 2 = B work only; 3 = A work
 // only of a group without rank-1 tensors (block-wise and fp32-state tensors: no rank-1 code); 4 = B work only of tensors on
 // the general tiles.  The single-role kernels exist because a kernel's register and LDS footprint is that of its heaviest
-// path.
-template <bool BF16, int ROLES>
+// path.  PLAIN: for plans with rows of whole blocks only, without the ragged and the general tiles, of which the ragged statistics take 89
+// registers (fp32; bf16 92) where the plain ones take 73 (78), and the factorized form's 74 (78) where 66 (62) do.  Sets of a few matrices, where latency
+// counts, us with them and without, bf16: rank-1 4 of 1024 x 1024 18.1, 17.9, 2 of 512 x 512 11.7, 11.2, a layer of width 1024 35.9, 35.5;
+// factorized 20.8, 19.5, 12.1, 11.3, 38.4, 37.5; 8 of 4096 x 4096 the same.
+template <bool BF16, int ROLES, bool PLAIN = false>
 __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);
     constexpr bool kOnlyA = ROLES == 1 || ROLES == 3;
@@ -242,12 +245,12 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
         const Hyper ht = for_tensor(h, a);
         const int wg = b_before - sg.wg_begin;
         TicketSync sync{a.counter, unsigned(wg), 0u};
-        if (ROLES == 4 || a.kind == kQuantGeneral) {
+        if (ROLES == 4 || (!PLAIN && a.kind == kQuantGeneral)) {
             pass2_general_chunk<BF16>(a, h, int64_t(wg) * kGenChunkElems);
             __syncthreads();
             sync.staged();
         } else if constexpr (!kOnlyA && ROLES != 4) {
-            if (a.kind == kQuantFast) update_tile<BF16, false>(a, ht, wg, s, sync);
+            if (PLAIN || a.kind == kQuantFast) update_tile<BF16, false>(a, ht, wg, s, sync);
             else update_ragged<BF16, false>(a, ht, wg, s, sync);
         }
         finish_rank1(a, unsigned(wg), unsigned(a.n_wg2), sync.ticket, s_last);
@@ -263,7 +266,7 @@ __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const H
             b128_work<BF16>(a, ht, wg, s);
         } else if (ROLES == 3) {
             // not reached: the host launches this variant only for groups without rank-1 tensors
-        } else if (a.kind == kQuantFast) {
+        } else if (PLAIN || a.kind == kQuantFast) {
             maxima_tile<BF16>(a, ht, wg, s);
         } else if (a.kind == kQuantRagged) {
             maxima_ragged<BF16>(a, ht, wg, s);
@@ -396,7 +399,7 @@ __global__ __launch_bounds__(kThreads) void factor_plan_totals(const DetPhase ph
 // statistics pass (next to block-wise and fp32-state tensors, which are complete after it), "B" work
 // the update pass.  ROLES: 0 = both interleaved, 1 = A only, 2 = B only.  Separate kernels, so that the
 // rank-1 kernels above keep their register footprint.
-template <bool BF16, int ROLES>
+template <bool BF16, int ROLES, bool PLAIN = false>
 __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);
     __shared__ Lds s;
@@ -412,7 +415,7 @@ __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, 
         const Hyper ht = for_tensor(h, a);
         const int wg = b_before - sg.wg_begin;
         NoSync sync;            // the ticket at the end: six of 1024 x 1024 fp32 26.1 us, 26.5 with it in the tile's middle
-        if (a.kind == kFactorFast) {
+        if (PLAIN || a.kind == kFactorFast) {
             factor_update_tile_down<BF16, false>(a, ht, wg, s, sync);
         } else if (a.kind == kFactorRagged) {
             factor_update_ragged<BF16>(a, ht, wg, s);
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void factor_phase_kernel(const Phase ph, 
         if (a.kind == kFp32State)
             adamw32_tile<BF16>(a.p, a.g, reinterpret_cast<float*>(a.mq), reinterpret_cast<float*>(a.vq), a.P, ht, wg);
         else if (a.kind == kQuantBlockV) b128_work<BF16>(a, ht, wg, s);
-        else if (a.kind == kFactorFast) factor_stats_tile<BF16>(a, wg, s);
+        else if (PLAIN || a.kind == kFactorFast) factor_stats_tile<BF16>(a, wg, s);
         else if (a.kind == kFactorRagged) factor_stats_ragged<BF16>(a, wg, s);
         else factor_stats_general_tile<BF16>(a, wg, a.n_wg, s);
     }

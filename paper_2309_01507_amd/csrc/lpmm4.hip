@@ -811,6 +811,7 @@ struct PlanHost {
     bool factor = false;                // the plan's 2-dimensional tensors keep a factorized second moment
     bool sgdm = false;                  // a plan of SGD-with-momentum tensors (lpmm_sgdm4_step_multi)
     bool serial = false;                // LPMM_MULTI_STREAMS=0: every pass a launch of its own on the caller's stream
+    bool plain = false;                 // rows of whole blocks only: launches by phases in the kernels without ragged and general tiles
     bool flow = false;                  // the whole step is one launch (flow.hpp)
     bool flow_any = false;              // ... with ragged matrices or rows shorter than 128 elements
     FlowArgs flow_args{};
@@ -1976,12 +1977,12 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     // 64 326 / 314).  A group's passes follow each other in any case.  Factorized plans take their launches one after the other: a
     // statistics pass and an update each run at the memory system's rate alone, and side by side they only get in each other's way
     // (7B-shaped set: 14.71 ms per step against 14.84, 354 M set 0.841 against 0.854).
+    auto narrow_kind = [](int kind) { return kind == kQuantGeneral || kind == kFactorGeneral; };
     const int stream_mode = env_int("LPMM_MULTI_STREAMS", host->factor || host->sgdm ? 0 : 2);
     for (size_t j = 0; j <= groups.size() && !host->flow; ++j) {
         PhaseLaunch pl{};
         int64_t elems_a = 0, elems_b = 0, elems_gen = 0;
         int64_t narrow_a = 0, narrow_b = 0;     // of elems_a and elems_b, those on the general tiles of either form
-        auto narrow_kind = [](int kind) { return kind == kQuantGeneral || kind == kFactorGeneral; };
         pl.ph.tensors = reinterpret_cast<const Tensor4Table*>(d_tens);
         if (j < groups.size())
             for (int64_t i = groups[j].first; i < groups[j].second; ++i) {
@@ -2065,6 +2066,7 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
         host->phases.push_back(pl);
     }
     host->serial = stream_mode == 0 && !host->sgdm;
+    host->plain = std::all_of(tens, tens + n, [&](const Tensor4& t) { return t.kind != kQuantRagged && t.kind != kFactorRagged && !narrow_kind(t.kind); });
     bool any_b = false;
     for (const PhaseLaunch& pl : host->phases) any_b = any_b || pl.ph.n_b > 0;
     if (stream_mode >= 2 && groups.size() > 1 && !host->sgdm && any_b && !host->flow) {
@@ -2166,21 +2168,25 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
     // roles: 0 = A and B work in one launch, 1 = A only, 2 = B only, 3 = A only without rank-1 tensors
     // B work: behind it, where they are apart, the tensors on the general tiles
     auto launch = [&](int roles, int grid, hipStream_t on, const PhaseLaunch& pl) -> int {
-#define LPMM_PHASE_CASE(K, R)                                                                               \
-        if (bf16) hipLaunchKernelGGL((K<true, R>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);            \
-        else hipLaunchKernelGGL((K<false, R>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);
+#define LPMM_PHASE_LAUNCH(K, R, PLAIN)                                                                      \
+        if (bf16) hipLaunchKernelGGL((K<true, R, PLAIN>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);     \
+        else hipLaunchKernelGGL((K<false, R, PLAIN>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);
+#define LPMM_PHASE_CASE(K, R) { LPMM_PHASE_LAUNCH(K, R, false) }
+#define LPMM_PHASE_PASS(K, R) { if (host->plain) { LPMM_PHASE_LAUNCH(K, R, true) } else { LPMM_PHASE_LAUNCH(K, R, false) } }
         if (host->factor) {
-            if (roles == 0) { LPMM_PHASE_CASE(factor_phase_kernel, 0) }
-            else if (roles == 2) { LPMM_PHASE_CASE(factor_phase_kernel, 2) }
-            else { LPMM_PHASE_CASE(factor_phase_kernel, 1) }
+            if (roles == 0) LPMM_PHASE_CASE(factor_phase_kernel, 0)
+            else if (roles == 2) LPMM_PHASE_PASS(factor_phase_kernel, 2)
+            else LPMM_PHASE_PASS(factor_phase_kernel, 1)
         } else {
-            if (roles == 0) { LPMM_PHASE_CASE(phase_kernel, 0) }
-            else if (roles == 1) { LPMM_PHASE_CASE(phase_kernel, 1) }
-            else if (roles == 2 && pl.b_general) { LPMM_PHASE_CASE(phase_kernel, 4) }
-            else if (roles == 2) { LPMM_PHASE_CASE(phase_kernel, 2) }
-            else { LPMM_PHASE_CASE(phase_kernel, 3) }
+            if (roles == 0) LPMM_PHASE_CASE(phase_kernel, 0)
+            else if (roles == 1) LPMM_PHASE_PASS(phase_kernel, 1)
+            else if (roles == 2 && pl.b_general) LPMM_PHASE_CASE(phase_kernel, 4)
+            else if (roles == 2) LPMM_PHASE_PASS(phase_kernel, 2)
+            else LPMM_PHASE_CASE(phase_kernel, 3)
         }
 #undef LPMM_PHASE_CASE
+#undef LPMM_PHASE_PASS
+#undef LPMM_PHASE_LAUNCH
         LPMM_HIP(hipGetLastError());
         if (roles == 2 && pl.grid_gen > 0) {
             if (bf16) hipLaunchKernelGGL((phase_kernel<true, 4>), dim3(pl.grid_gen), dim3(kThreads), 0, on, pl.gen, h);

@@ -95,6 +95,14 @@ def test_multi_matches_oracle_bf16_grads():
     _run_set(_mini_transformer(), "col_lognormal", True, steps=4, seed=12, env={"LPMM_PHASE_MPARAMS": "1"})
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("env", [{}, {"LPMM_PHASE_MPARAMS": "1"}, {"LPMM_MULTI_STREAMS": "0"}], ids=["default", "groups", "serial"])
+def test_plans_of_whole_blocks(env, bf16):
+    """Sets without ragged and general tiles by phases: kernels of their own for both passes, with fp32-state tensors in the first."""
+    specs = [sp for sp in _mini_transformer() if sp.cols % 128 == 0]
+    _run_set(specs + [workloads.TensorSpec("thin", 3, 128), workloads.TensorSpec("wide", 2, 4224)], "col_lognormal", bf16, steps=3, seed=15, env=env)
+
+
 @pytest.mark.parametrize("env", [{}, {"LPMM_MULTI_STREAMS": "0"}, {"LPMM_MULTI_STREAMS": "1"}], ids=["default", "serial", "fused"])
 @pytest.mark.parametrize("shapes,launches", [([(3000, 96)] * 4 + [(256, 1024)] * 4, 2), ([(30000, 96)] * 3 + [(512, 640)], 3),
                                              ([(700, 96), (33, 100)], 2)], ids=["dealt", "apart", "alone"])

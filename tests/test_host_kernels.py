@@ -44,3 +44,12 @@ def test_the_quantizer_study_is_handed_what_it_uses(kernels):
         for name, k in _named(kernels, part).items():
             # 88 bytes of addresses and sizes, three tables of 16 words, some scalars; the other rounding's tables would be 128 more
             assert explicit(k) <= 88 + 3 * 64 + 32, name
+
+
+@pytest.mark.parametrize("part,waves", [("12phase_kernelILb0ELi1ELb1E", 6), ("12phase_kernelILb1ELi1ELb1E", 6),
+                                        ("19factor_phase_kernelILb0ELi1ELb1E", 7), ("19factor_phase_kernelILb1ELi1ELb1E", 7)])
+def test_first_passes_of_plain_plans_keep_their_waves(kernels, part, waves):
+    """Plans by phases with rows of whole blocks only do not pay for the ragged statistics tiles' registers: six waves on a SIMD
+    (rank-1) and seven (factorized) of 512 registers in steps of 8."""
+    for name, k in _named(kernels, part).items():
+        assert 512 // ((k[".vgpr_count"] + 7) // 8 * 8) >= waves and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_count"])

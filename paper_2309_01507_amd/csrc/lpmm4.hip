@@ -335,7 +335,7 @@ void ragged_geometry(Tensor4* a, int n_cu, int64_t tall, int shrink = 0) {
     a->rw2 = int(rw2);
     a->rs2 = 0;
     a->n_wg = int(a->strips2 * ((rows2 + rw2 - 1) / rw2));
-    if (rows2 != a->rows) a->n_wg += int((a->P - last_row_begin(*a) + kLastRowElems - 1) / kLastRowElems);
+    if (a->P & 7) a->n_wg += int((a->P - tail_begin(*a) + kLastRowElems - 1) / kLastRowElems);
 }
 
 // first or second pass of the rank-1 step on one tensor

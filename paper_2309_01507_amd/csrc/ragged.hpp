@@ -164,6 +164,7 @@ struct RagStats {
     int strip, tile, grp, l, n, n_stat, rounds;
     int64_t row0;
     uint32_t cols, at, col0;      // the lane's first position in the strip and column
+    uint32_t elems;               // of the tile's groups
     bool live, edge;
     Rsrc rg, rv;
     uint32_t off_g, off_v;        // byte offsets of the lane's elements in the half-wave's first row
@@ -182,14 +183,17 @@ struct RagStats {
         live = col0 < cols;
         edge = uint32_t(strip) * 256u + 262u >= cols;
         const int64_t e0 = row0 * a.cols;
-        // what the tile's lanes own: up to where the lanes of the row behind its last one begin, so that those read zeros
-        const uint32_t elems = (uint32_t(n) * cols + 7u) / 8u * 8u;
+        // what the tile's lanes own: up to where the lanes of the row behind its last one begin, so that those read zeros; up to the
+        // last whole group of the tensor
+        elems = (uint32_t(n) * cols + 7u) / 8u * 8u;
+        if (e0 + elems > a.P) elems -= 8u;
         rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + e0 * int(kBytes), elems * kBytes);
         const uint32_t e = uint32_t(grp) * cols + col0;
         off_g = live ? e * kBytes : kNowhere;
         off_v = live ? e >> 1 : kNowhere;
         if (a.vq) rv = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (e0 >> 1), elems >> 1);
     }
+    __device__ __forceinline__ bool whole(int il) const { return uint32_t(il) * cols + col0 < elems; }       // the lane's group in row il, if edge
     __device__ __forceinline__ bool next_row(int e) const { return col0 + uint32_t(e) >= cols; }      // of element e, if edge
     __device__ __forceinline__ void load_grad(int k, float4 (&g)[BF16 ? 1 : 2]) const {
         const uint32_t off = off_g + uint32_t(k) * (cols * 8u * kBytes);
@@ -275,7 +279,7 @@ __device__ __forceinline__ void maxima_ragged_tile(const Tensor4& a, const Hyper
     auto one = [&](const Row8<BF16>& x, int k, auto edge) {
         constexpr bool kEdge = decltype(edge)::value;
         const int il = t.grp + k * kGroups;
-        const bool in = il < t.n;                                 // behind the tile: zeros
+        const bool in = il < t.n && (!kEdge || t.whole(il));      // behind the tile: zeros
         float g[8], vt[8];
         unpack_grad8<BF16>(x.g, g);
         if (__builtin_expect(tame, 1)) {
@@ -330,14 +334,14 @@ __device__ __forceinline__ void maxima_ragged_tile(const Tensor4& a, const Hyper
     }
 }
 
-// The part of the last row that the tiles leave out.  A workgroup requests its elements all at once (one after the other, two
-// round trips each, they were the end of the pass: 847 x 4973 bf16 9.1 us, 6.7 so).
+// The elements that the tiles leave out, all in the last row.  A workgroup requests its elements all at once (one after the other, two
+// round trips each, a last row was the end of the pass: 847 x 4973 bf16 9.1 us, 6.7 so).
 constexpr int kLastEach = kLastRowElems / kThreads;
 template <bool BF16>
-struct LastRow {
+struct Tail {
     int64_t first, col0, left;      // first element, its column, elements from there on
-    __device__ __forceinline__ LastRow(const Tensor4& a, int part) {
-        first = last_row_begin(a) + int64_t(part) * kLastRowElems;
+    __device__ __forceinline__ Tail(const Tensor4& a, int part) {
+        first = tail_begin(a) + int64_t(part) * kLastRowElems;
         col0 = first - (a.rows - 1) * a.cols;
         left = a.P - first;
     }
@@ -355,8 +359,8 @@ struct LastRow {
 };
 
 template <bool BF16>
-__device__ __forceinline__ void maxima_last_row(const Tensor4& a, const Hyper& h, int part) {
-    const LastRow<BF16> t(a, part);
+__device__ __forceinline__ void maxima_tail(const Tensor4& a, const Hyper& h, int part) {
+    const Tail<BF16> t(a, part);
     const float r_old = a.r[a.rows - 1];
     float c[kLastEach], rmax = 0.0f;
     uint32_t g[kLastEach], q[kLastEach];
@@ -383,7 +387,7 @@ template <bool BF16>
 __device__ __forceinline__ void maxima_ragged(const Tensor4& a, const Hyper& h, int wg, Lds& s) {
     const int tiles = int((class_rows(a) + a.rw2 - 1) / a.rw2) * a.strips2;
     if (wg < tiles) maxima_ragged_tile<BF16>(a, h, wg, s);
-    else maxima_last_row<BF16>(a, h, wg - tiles);
+    else maxima_tail<BF16>(a, h, wg - tiles);
 }
 
 // One block of the second pass.  l = lane of the group.
@@ -674,10 +678,10 @@ __device__ __forceinline__ void factor_stats_ragged_tile(const Tensor4& a, int w
     }
 }
 
-// The part of the last row that the tiles leave out.
+// The elements that the tiles leave out.
 template <bool BF16>
-__device__ __forceinline__ void factor_stats_last_row(const Tensor4& a, int part, Lds& s) {
-    const LastRow<BF16> t(a, part);
+__device__ __forceinline__ void factor_stats_tail(const Tensor4& a, int part, Lds& s) {
+    const Tail<BF16> t(a, part);
     const int lane = threadIdx.x & 63;
     uint32_t g[kLastEach];
     float sum = 0.0f;
@@ -696,7 +700,7 @@ __device__ __forceinline__ void factor_stats_last_row(const Tensor4& a, int part
         const float all = (s.col[0] + s.col[1]) + (s.col[2] + s.col[3]);
         atomic_add_f32(a.r_new + a.rows - 1, all);
         atomic_add_f32(tot + tot_new_word(part & (a.tot_slots - 1)), all);
-        if (part == 0) atomic_add_f32(tot + tot_old_word(0), a.r[a.rows - 1]);
+        if (part == 0 && class_rows(a) == 0) atomic_add_f32(tot + tot_old_word(0), a.r[a.rows - 1]);
     }
 }
 
@@ -704,7 +708,7 @@ template <bool BF16>
 __device__ __forceinline__ void factor_stats_ragged(const Tensor4& a, int wg, Lds& s) {
     const int tiles = int((class_rows(a) + a.rw2 - 1) / a.rw2) * a.strips2;
     if (wg < tiles) factor_stats_ragged_tile<BF16>(a, wg, s);
-    else factor_stats_last_row<BF16>(a, wg - tiles, s);
+    else factor_stats_tail<BF16>(a, wg - tiles, s);
 }
 
 // Update pass: the blocks of update_ragged_tile; s.cold holds the columns' new statistics by position, s.blk_vmax the rows'

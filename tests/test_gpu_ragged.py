@@ -176,9 +176,12 @@ def test_tiles_near_two_gigabytes(monkeypatch, rows, cols, plan, bf16):
     (9, 519, False),
     (8, 1290, True),         # tiles of 8 rows, whole
     (520, 131, True),        # several tall tiles, one strip
-    (31, 2308, False),       # P = 4 (mod 8): a last row of its own, in two parts
+    (31, 2308, False),       # P = 4 (mod 8): the last 4 elements apart
     (2, 4099, True),
-    (66, 776, True),         # P = 0 (mod 8): no last row
+    (1, 4101, False),        # a single row: in parts
+    (257, 129, True),        # P = 1, a tile of one row behind a whole one
+    (15, 137, False),        # P = 7
+    (66, 776, True),         # P = 0 (mod 8): nothing apart
 ])
 def test_statistics_tiles_at_their_edges(rows, cols, bf16):
     """Lanes of 8 elements that start a shift into their row and end in the next one, for both forms of the second moment.  The
@@ -187,3 +190,25 @@ def test_statistics_tiles_at_their_edges(rows, cols, bf16):
     print(f"[gpu-test] ragged statistics {rows}x{cols} bf16={bf16}", flush=True)
     assert run_parity(rows, cols, steps=3, recipe="col_lognormal", bf16=bf16, seed=76) == 0
     assert run(rows, cols, steps=2, bf16=bf16) == 0
+
+
+@pytest.mark.parametrize("rows,cols,bf16", [(41, 2101, False), (9, 2051, True), (64, 2052, True), (264, 2049, False), (2, 2053, True)])
+def test_nan_gradients_behind_the_last_whole_group(monkeypatch, rows, cols, bf16):
+    """The elements behind the last multiple of 8 have the largest statistics of their columns and get NaN gradients: they raise no
+    maximum, and neither does what the tiles read in their place.  As from the general kernels, which take an element at a time."""
+    n, tail = rows * cols, rows * cols % 8
+    lpmm.ensure_init(rows + cols)
+    gen = torch.Generator(device=DEV).manual_seed(rows)
+    dtype = torch.bfloat16 if bf16 else torch.float32
+    g1 = (torch.rand(n, device=DEV, generator=gen) * 1e-3).to(dtype)
+    g2 = torch.zeros_like(g1)
+    g1[n - tail:], g2[n - tail:] = 64.0, float("nan")
+    out = []
+    for general in ("0", "1"):
+        monkeypatch.setenv("LPMM_FORCE_GENERAL", general)
+        w, st = torch.zeros(n, device=DEV), lpmm.new_state(rows, cols, DEV)
+        for t, g in ((1, g1), (2, g2)):
+            (lpmm.lpmm_adamw4_step_bf16g if bf16 else lpmm.lpmm_adamw4_step)(w, g, st, HP.lr, HP.beta1, HP.beta2, HP.eps, HP.weight_decay, t)
+        out.append((st.v_rowmax.clone(), st.v_colmax.clone()))
+    assert torch.isfinite(out[0][0]).all() and torch.isfinite(out[0][1]).all()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])

@@ -164,7 +164,7 @@ struct RagStats {
     int strip, tile, grp, l, n, n_stat, rounds;
     int64_t row0;
     uint32_t cols, at, col0;      // the lane's first position in the strip and column
-    uint32_t elems;               // of the tile's groups
+    int n_lane;                   // rows whose group of the lane's columns is whole: n, or n - 1 at the tensor's end
     bool live, edge;
     Rsrc rg, rv;
     uint32_t off_g, off_v;        // byte offsets of the lane's elements in the half-wave's first row
@@ -185,15 +185,15 @@ struct RagStats {
         const int64_t e0 = row0 * a.cols;
         // what the tile's lanes own: up to where the lanes of the row behind its last one begin, so that those read zeros; up to the
         // last whole group of the tensor
-        elems = (uint32_t(n) * cols + 7u) / 8u * 8u;
+        uint32_t elems = (uint32_t(n) * cols + 7u) / 8u * 8u;
         if (e0 + elems > a.P) elems -= 8u;
+        n_lane = uint32_t(n - 1) * cols + col0 < elems ? n : n - 1;
         rg = tile_rsrc(reinterpret_cast<const char*>(a.g) + e0 * int(kBytes), elems * kBytes);
         const uint32_t e = uint32_t(grp) * cols + col0;
         off_g = live ? e * kBytes : kNowhere;
         off_v = live ? e >> 1 : kNowhere;
         if (a.vq) rv = tile_rsrc(reinterpret_cast<const uint8_t*>(a.vq) + (e0 >> 1), elems >> 1);
     }
-    __device__ __forceinline__ bool whole(int il) const { return uint32_t(il) * cols + col0 < elems; }       // the lane's group in row il, if edge
     __device__ __forceinline__ bool next_row(int e) const { return col0 + uint32_t(e) >= cols; }      // of element e, if edge
     __device__ __forceinline__ void load_grad(int k, float4 (&g)[BF16 ? 1 : 2]) const {
         const uint32_t off = off_g + uint32_t(k) * (cols * 8u * kBytes);
@@ -279,7 +279,7 @@ __device__ __forceinline__ void maxima_ragged_tile(const Tensor4& a, const Hyper
     auto one = [&](const Row8<BF16>& x, int k, auto edge) {
         constexpr bool kEdge = decltype(edge)::value;
         const int il = t.grp + k * kGroups;
-        const bool in = il < t.n && (!kEdge || t.whole(il));      // behind the tile: zeros
+        const bool in = il < t.n_lane;                            // behind the tile: zeros
         float g[8], vt[8];
         unpack_grad8<BF16>(x.g, g);
         if (__builtin_expect(tame, 1)) {

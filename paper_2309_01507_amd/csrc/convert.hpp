@@ -269,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void quant_vb_kernel(const QuantArgs q) {
 // Bound by those atomics and by latency where the matrix is small, else by memory.  Strips of 1024 columns by 4 to 32 rows, as the
 // filling of the chip asked for them, sent two to three times as many atomics, which were what the pass took: 3000 x 1001 18.6 us, 6.3
 // so, 1000 x 1001 8.0 and 4.2, 4096 x 4096 15.3 and 13.8, 11008 x 4096 43 and 35.5 (5.1 TB/s).
-// Wide matrices of few rows: `run` strips to a workgroup, see launch_maxima.
+// Wide matrices: `run` strips to a workgroup, see launch_maxima.
 constexpr int kMaxTileRows = 512;
 constexpr int kMaxCols = 8;               // of a lane
 

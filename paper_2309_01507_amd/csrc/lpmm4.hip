@@ -1177,11 +1177,11 @@ int rank_grid(int64_t elems, int units) { return grid_for(elems, units * kCvtUni
 // than two workgroups per CU (11008 x 4096: 16, 32 and 64 rows 35.5 us, 128, the last of whose workgroups run alone, 45; 4096 x 4096 at
 // 32, 64 and 128 14.4, 13.8, 19; 200 x 16000 at 16, 32 and 64 5.8, 5.6, 6.4).  Tall ones take more: atomics on one column's maximum
 // follow each other (3000 x 1001 at 16, 32 and 64 8.2, 6.3, 6.5 us; 16384 x 80 at 64, 128 and 256 7.8, 6.5, 7.6).
-// So do those on one row's maximum, one per strip at about 12 ns, and a matrix of few rows has nothing to do meanwhile: there a
-// workgroup takes a run of strips, about 1 us each, so that the two balance at the root of the strips.  With all rows in one tile the columns'
-// maxima are complete, and stored.  (With codes, us: strips of 1024 columns with atomics for both, of 256, and so: 1 x 1000003 22.5, 55,
-// 22.7; 1 x 10000000 151, 483, 100; 4 x 4000000 84, 216, 69; 8 x 4000000 105, 235, 92; 16 x 1000000 57, 72, 42; 20 x 100000 14.5, 14.6, 12.0.)
-constexpr int64_t kMaxFewRows = 64;
+// So do those on one row's maximum, one per strip at about 12 ns, and a matrix of some hundred rows or fewer has nothing to do meanwhile:
+// workgroups take runs of strips, about 1 us each, so that the two balance at the root of the strips (rows of up to 82000 elements take
+// single ones).  With all rows in one tile the columns' maxima are complete, and stored.  (With codes, us: strips of 1024 columns with atomics for
+// both, of 256, and so: 1 x 1000003 22.5, 55, 22.7; 1 x 10000000 151, 483, 100; 4 x 4000000 84, 216, 69; 8 x 4000000 105, 235, 92; 16 x
+// 1000000 57, 72, 42; 20 x 100000 14.5, 14.6, 12.0; 70 x 500000 67, 83, 65; 128 x 500000 107, 119, 101; 1024 x 100000 158, 158, 156.)
 int launch_maxima(const QuantArgs& q, int n_cu, hipStream_t s) {
     hipLaunchKernelGGL(clear_two_kernel, dim3(grid_for(q.rows + q.cols, 4, 1024)), dim3(kThreads), 0, s, q.sa, q.rows, q.sb,
                        q.cols);
@@ -1196,7 +1196,7 @@ int launch_maxima(const QuantArgs& q, int n_cu, hipStream_t s) {
     while (per > 16 && tiles(per) < 2 * int64_t(n_cu)) per /= 2;
     while (per < kMaxTileRows && per * per < q.rows / 3) per *= 2;
     t.rows_per_wg = int(per);
-    t.run = q.rows > kMaxFewRows ? 1 : std::max(1, int(std::sqrt(double(t.strips)) / 9.0));
+    t.run = std::max(1, int(std::sqrt(double(t.strips)) / 9.0));
     t.groups = (t.strips + t.run - 1) / t.run;
     t.whole = q.rows <= per;
     const dim3 grid(unsigned(t.groups * ((q.rows + per - 1) / per))), block(kThreads);

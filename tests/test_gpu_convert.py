@@ -136,11 +136,11 @@ def test_maxima_at_the_edges_of_their_tiles(rows, cols):
         assert r[rows] == -5.0 and c[cols] == -5.0
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 150001), (3, 600007), (8, 300000), (33, 90001), (64, 100003), (65, 90001),    # runs of strips
+@pytest.mark.parametrize("rows,cols", [(1, 150001), (3, 600007), (8, 300000), (33, 90001), (64, 100003), (70, 200001), (200, 83001),    # runs of strips
                                        (1, 5), (4, 3), (70001, 7), (5000, 9), (4097, 15), (3001, 33), (513, 63),             # one at a time
                                        (5000, 8), (4097, 12), (3001, 32), (2049, 36), (1025, 64), (1025, 65)])
 def test_maxima_of_few_rows_and_of_few_columns(rows, cols):
-    """Up to 64 rows a workgroup takes several strips, and stores the columns' maxima where it has all rows; 4, 8, 16 or 32 lanes a
+    """In rows of more than 82000 elements a workgroup takes several strips, and stores the columns' maxima where it has all rows; 4, 8, 16 or 32 lanes a
     row, up to 64 columns an element at a time where rows begin anywhere."""
     print(f"[gpu-test] maxima {rows}x{cols}", flush=True)
     lpmm.ensure_init(4096)

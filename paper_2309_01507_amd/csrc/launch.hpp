@@ -225,7 +225,8 @@ __device__ __forceinline__ Segment find_segment(const Segment* seg, int n_seg, i
 // path.  PLAIN: for plans with rows of whole blocks only, without the ragged and the general tiles, of which the ragged statistics take 89
 // registers (fp32; bf16 92) where the plain ones take 73 (78), and the factorized form's 74 (78) where 66 (62) do.  Sets of a few matrices, where latency
 // counts, us with them and without, bf16: rank-1 4 of 1024 x 1024 18.1, 17.9, 2 of 512 x 512 11.7, 11.2, a layer of width 1024 35.9, 35.5;
-// factorized 20.8, 19.5, 12.1, 11.3, 38.4, 37.5; 8 of 4096 x 4096 the same.
+// factorized 20.8, 19.5, 12.1, 11.3, 38.4, 37.5; 8 of 4096 x 4096 the same.  Long factorized launches keep the second pass with them
+// (the host's rule has the figures).
 template <bool BF16, int ROLES, bool PLAIN = false>
 __global__ __launch_bounds__(kThreads) void phase_kernel(const Phase ph, const HyperArg ha) {
     const Hyper h = resolve(ha);

@@ -795,6 +795,7 @@ struct PhaseLaunch {
     // the B tensors on the general tiles where they have a launch of their own, behind that of the others
     Phase gen;
     int grid_gen;
+    bool plain_b;       // B work alone in the kernel without the ragged and the general tiles
     bool a_has_rank1;   // some A tensor takes the first pass of the rank-1 path (else the lighter kernel variant runs)
     // tensors with more than two dimensions among the B tensors: two small kernels run before their second pass
     NdPhase nd;
@@ -2067,6 +2068,16 @@ int lpmm_adamw4_plan_build_nd(const lpmm_tensor_desc* descs, int64_t n, const in
     }
     host->serial = stream_mode == 0 && !host->sgdm;
     host->plain = std::all_of(tens, tens + n, [&](const Tensor4& t) { return t.kind != kQuantRagged && t.kind != kFactorRagged && !narrow_kind(t.kind); });
+    // The factorized update is six waves on a SIMD with the ragged tile in the kernel and eight without.  Where a launch is long that is
+    // more streams over the memory than it serves well, so the lighter kernel is for launches below 2^25 parameters (with the ragged tile
+    // and without, us, bf16 gradients: 4 of 1024 x 1024 20.9 and 19.4, 12 layers of width 256 34.4 and 33.4, 16 of 1024 x 1024 44.2 and
+    // 43.4, 24 62.5 and 61.8, 8192 x 4096 89.7 and 89.9; 2 layers of width 1024 with 50257 x 1024 beside them 190.1 and 194.6, 12 such
+    // layers 454 and 461).
+    for (PhaseLaunch& pl : host->phases) {
+        int64_t elems = 0;
+        for (int k = 0; k < pl.ph.n_seg_b; ++k) elems += tens[pl.ph.seg_b[k].tensor].P;
+        pl.plain_b = host->plain && (!host->factor || elems < int64_t(1) << 25);
+    }
     bool any_b = false;
     for (const PhaseLaunch& pl : host->phases) any_b = any_b || pl.ph.n_b > 0;
     if (stream_mode >= 2 && groups.size() > 1 && !host->sgdm && any_b && !host->flow) {
@@ -2172,7 +2183,7 @@ int adamw4_step_multi_impl(void* plan, float lr, const float* lr_dev, float beta
         if (bf16) hipLaunchKernelGGL((K<true, R, PLAIN>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);     \
         else hipLaunchKernelGGL((K<false, R, PLAIN>), dim3(grid), dim3(kThreads), (R == 3 ? pad3 : 0), on, pl.ph, h);
 #define LPMM_PHASE_CASE(K, R) { LPMM_PHASE_LAUNCH(K, R, false) }
-#define LPMM_PHASE_PASS(K, R) { if (host->plain) { LPMM_PHASE_LAUNCH(K, R, true) } else { LPMM_PHASE_LAUNCH(K, R, false) } }
+#define LPMM_PHASE_PASS(K, R) { if (R == 2 ? pl.plain_b : host->plain) { LPMM_PHASE_LAUNCH(K, R, true) } else { LPMM_PHASE_LAUNCH(K, R, false) } }
         if (host->factor) {
             if (roles == 0) LPMM_PHASE_CASE(factor_phase_kernel, 0)
             else if (roles == 2) LPMM_PHASE_PASS(factor_phase_kernel, 2)

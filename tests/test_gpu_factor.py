@@ -202,6 +202,22 @@ def test_plan_walks_down_the_rows_in_all_tilings(launches, route, env):
             os.environ.pop(k, None)
 
 
+@pytest.mark.parametrize("cols", [8064, 8192])
+def test_plans_of_whole_blocks_below_and_from_2_25_parameters(cols):
+    """By phases, 4096 rows of whole blocks: below 2^25 parameters the second pass is the kernel without the ragged tile."""
+    rows, hp, seed = 4096, oracle.Hyper(), 58
+    lpmm.ensure_init(4096)
+    w_ref, st_ref = workloads.weights(seed, 0, rows, cols).reshape(-1), oracle.state_zero_factor(rows, cols)
+    w, g, st = to_dev(w_ref.copy()), to_dev(workloads.grads(seed, 0, 1, rows, cols, "col_lognormal").reshape(-1)), lpmm.new_state_factor(rows, cols, DEV)
+    plan = lpmm.new_plan([lpmm.make_desc(w, g, st)], 0, DEV)
+    assert lpmm.lpmm_adamw4_plan_launches(plan) == 2
+    lpmm.lpmm_adamw4_step_multi(plan, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.weight_decay, 1)
+    torch.cuda.synchronize()
+    mt, _ = oracle.adamw4_factor_step(w_ref, g.cpu().numpy(), st_ref, hp, 1, want_moments=True)
+    assert compare(download(st), st_ref, w.cpu().numpy(), w_ref, mt, f"{rows}x{cols}") == 0
+    lpmm.lpmm_adamw4_plan_release(plan)
+
+
 def test_first_moment_does_not_depend_on_the_launch_geometry():
     """The sums' order changes with the tiling, the first moment's bits must not."""
     rows, cols = 300, 1024

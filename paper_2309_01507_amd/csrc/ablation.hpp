@@ -5,13 +5,15 @@
 // them is on an optimizer step's path except B128 / signed DE, B128 / Linear and rank-1 / Linear, which the step
 // kernels implement themselves; these kernels are for studying the quantizers on real tensors.
 //
-// Laid out like the stand-alone conversions (4 elements per lane, kCvtElems per workgroup).  The compress kernels are
+// Laid out like the stand-alone conversions: 4 elements per lane, 4096 per workgroup; with stochastic rounding or rank-1 scales 2048 in
+// smaller tensors (kAblShortElems).  The compress kernels are
 // bound by the vector units, not by memory, so what counts is instructions per element.  As in the step kernels a value is normalized
 // with an approximate reciprocal and its code found through a table of 257 (signed maps: 513) buckets in LDS, and a wave in which
 // that leaves a doubt does its four elements again with IEEE divisions and a search.  Of the rest most is SplitMix64: six 32-bit
 // multiplications, which run at a quarter of the rate.
 // Measured on 4096 x 4096, DE-0, stochastic rounding: compress under the three normalizations 43, 43 and 45 us with a division and a
-// search of four dependent LDS reads per element, 32, 32 and 38 this way (42 vector instructions an element); decompress 13.  SplitMix64
+// search of four dependent LDS reads per element, 32, 32 and 38 this way (57, 58 and 69 vector instructions an element, 9 of them to set
+// the tables up; 83 to 85 % of the issue cycles); decompress 12.6.  SplitMix64
 // with its cross products as dot products of 16-bit halves, at the full rate, takes as long (all six calls 152.4 us, 153.3).
 #pragma once
 
@@ -191,7 +193,7 @@ __device__ __forceinline__ float abl_inverse(float s) { return approx_inv(s) * (
 
 // Block-wise normalization: a workgroup takes UNITS runs of 1024 elements, four (two blocks of 2048 or 32 of 128) or, with
 // stochastic rounding in tensors of at most 2^21 elements, two: there the chain of a lane's 16 roundings is what the call
-// takes (64 x 64: 8.8 us with four, 7.8 with two; 4096 x 100: 9.1, 7.9).
+// takes (a call with the copies of its arguments, before AblSearch: 64 x 64 8.8 us with four, 7.8 with two; 4096 x 100: 9.1, 7.9).
 constexpr int64_t kAblShortElems = int64_t(1) << 21;
 template <int BLOCK, bool SR, int UNITS>
 __global__ __launch_bounds__(kThreads) void abl_quant_block_kernel(const AblArgs a, const AblSearch<SR> m) {

@@ -3,11 +3,11 @@
 //
 // What bounds these kernels is memory: 4 bytes of fp32 and half a byte of codes per element, each touched once.  So a
 // lane owns FOUR consecutive elements of the row-major flattening (one 128-bit access, 16 bits of codes), a wave's
-// access is contiguous, a workgroup takes kCvtUnits runs of 1024 elements whose loads are all issued before the first
-// use, and the 64-bit division that finds a position's row is done once per workgroup, for its first element.
+// access is contiguous, a workgroup takes four runs of 1024 elements (with rank-1 scales two, see kRankShortElems) whose loads are all issued
+// before the first use, and the 64-bit division that finds a position's row is done once per workgroup, for its first element.
 // Measured on an 11008 x 4096 moment, before (one lane per 8 elements, scalar accesses, a 64-bit division each) and now:
-// compress the first moment 106 -> 55 us, its codes alone for the second 170 -> 39 us, decompress the first 111 -> 37 us,
-// the second 139 -> 55 us.  The fp32 arrays and the
+// compress the first moment 106 -> 39 us, its codes alone for the second 170 -> 35 us, decompress the first 111 -> 31 us,
+// the second 139 -> 30.5 us.  The fp32 arrays and the
 // scales need only be 4-byte aligned: the wide accesses are typed so.
 // What is read for the last time and the decompressed values pass by the memory-side cache (non-temporal), which then still
 // holds what a later kernel reads again: the second moment for its codes, the codes and scales for the way back.  Both moments

@@ -8,7 +8,7 @@
 // the strip's first column, p = 0 .. width + 127: a block that starts in the strip may reach up to 127 columns beyond
 // it, and beyond the end of the row position p continues with the next row's first columns.  The strip's column vectors sit in
 // LDS indexed by p, so only the row of an element needs a compare per element.  (1024 x 50257 with bf16 gradients: 779 us per
-// step on the general kernels, 170 with the maxima taken per element in the update, 161 with the passes as they are.)
+// step on the general kernels, 170 with the maxima taken per element in the update, 140 with the passes as they are.)
 //
 // Two ways to cut a matrix (chosen by the host):
 //   cols <= 1024:  one strip; a tile is a run of a.rw consecutive blocks, each of the 8 groups of a workgroup takes an
